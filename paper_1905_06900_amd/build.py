@@ -30,7 +30,7 @@ HIP_FLAGS = [
 # makes the matrix instructions work on ordinary registers directly.
 EXTRA_FLAGS = {
     "tables_full.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "train.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "assign.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

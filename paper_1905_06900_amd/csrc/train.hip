@@ -23,127 +23,9 @@
 //     (the distance-table kernel of tables_full.hip).
 #include "common.h"
 #include "device_util.h"
-#include "f64_tile.h"
+#include "assign.h"
 
 namespace dcpq {
-
-
-constexpr int kAssignQ = 32;       // points per workgroup (2 row tiles of 16)
-constexpr int kAssignC = 256;      // centroids per step of a workgroup (4 wavefronts x 64)
-
-// Smaller of two (value, index) pairs; equal values -> smaller index.
-__device__ inline void take_smaller(double &v, uint32_t &i, double ov, uint32_t oi)
-{
-    if (ov < v || (ov == v && oi < i)) { v = ov; i = oi; }
-}
-
-// Nearest centroid of the j-th sub-vector of every point, j = blockIdx.y.  A workgroup owns kAssignQ
-// points and walks all centroids of C_j in steps of kAssignC; operand and result layout of the matrix
-// instruction as in the distance-table kernel (lane l: A row l % 16, column l / 16; B row l / 16, column
-// l % 16; value v of the result is row 4 v + l / 16, column l % 16), centroid columns interleaved by 4.
-// The term ||x||^2 is the same for every centroid of a point and is left out of the comparison.
-// points: rows of `ld` floats; sub-vector j starts at column j * dsub.  labels: [n][m] of LabelT.
-// dist (optional): [n][m] fp32 squared distance to the chosen centroid.
-template <typename LabelT>
-__global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
-                                                     const float *__restrict__ cb, int m, int dsub, int ncent,
-                                                     LabelT *__restrict__ labels, float *__restrict__ dist)
-{
-    __shared__ double red_v[4][kAssignQ];
-    __shared__ uint32_t red_i[4][kAssignQ];
-    __shared__ double ny[kAssignQ];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = blockIdx.y;
-    const uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kAssignQ;
-    const float *cbj = cb + static_cast<size_t>(j) * ncent * dsub;
-    const int lr = lane & 15, lk = lane >> 4;
-    constexpr int MT = kAssignQ / 16;
-
-    double best_v[MT][4];
-    uint32_t best_i[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) { best_v[mt][v] = INFINITY; best_i[mt][v] = 0xFFFFFFFFu; }
-    double na[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) na[mt] = 0.0;
-
-    const float *ap[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const uint64_t q = q0 + mt * 16 + lr;
-        ap[mt] = points + static_cast<size_t>(q < n ? q : n - 1) * ld + j * dsub;
-    }
-    for (int c0 = 0; c0 < ncent; c0 += kAssignC) {                    // uniform
-        const int cw = c0 + wave * 64;                                // first centroid of this wavefront
-        double4_t acc[MT][4];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = double4_t{0.0, 0.0, 0.0, 0.0};
-        double nb[4] = {0.0, 0.0, 0.0, 0.0};
-        // this lane's four centroids, clamped to valid ones (the others are skipped below)
-        const float *bp[4];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int c = cw + lr * 4 + nt;
-            bp[nt] = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
-        }
-        f64_tile_products<MT>(ap, bp, dsub, lk, c0 == 0, acc, na, nb);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            nb[nt] += __shfl_xor(nb[nt], 16);
-            nb[nt] += __shfl_xor(nb[nt], 32);
-        }
-        // this lane's four centroids against its eight result rows, in increasing centroid index
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int c = cw + lr * 4 + nt;
-            if (c < ncent) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        // a lane meets its centroids in increasing index, so "strictly smaller" keeps the first of equals
-                        const double val = fma(-2.0, acc[mt][nt][v], nb[nt]);
-                        const bool better = val < best_v[mt][v];
-                        best_v[mt][v] = better ? val : best_v[mt][v];
-                        best_i[mt][v] = better ? static_cast<uint32_t>(c) : best_i[mt][v];
-                    }
-            }
-        }
-    }
-    // the 16 lanes with the same l / 16 hold candidates for the same rows: reduce over them, then over
-    // the four wavefronts through LDS
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                const double ov = __shfl_xor(best_v[mt][v], off);
-                const uint32_t oi = __shfl_xor(best_i[mt][v], off);
-                take_smaller(best_v[mt][v], best_i[mt][v], ov, oi);
-            }
-            if (lr == 0) { red_v[wave][mt * 16 + v * 4 + lk] = best_v[mt][v]; red_i[wave][mt * 16 + v * 4 + lk] = best_i[mt][v]; }
-        }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        na[mt] += __shfl_xor(na[mt], 16);
-        na[mt] += __shfl_xor(na[mt], 32);
-        if (wave == 0 && lk == 0) ny[mt * 16 + lr] = na[mt];
-    }
-    __syncthreads();
-    if (tid < kAssignQ && q0 + tid < n) {
-        double v = red_v[0][tid];
-        uint32_t i = red_i[0][tid];
-        for (int w = 1; w < 4; ++w) take_smaller(v, i, red_v[w][tid], red_i[w][tid]);
-        const size_t o = (q0 + tid) * static_cast<size_t>(m) + j;
-        labels[o] = static_cast<LabelT>(i);
-        if (dist) dist[o] = static_cast<float>(fmax(0.0, ny[tid] + v));
-    }
-}
 
 // sums[label][t] += point[t] (double), counts[label] += 1.  One thread per (point, component).
 __global__ __launch_bounds__(256) void accumulate_kernel(const float *__restrict__ points, uint64_t n, int ld, int d,
@@ -275,29 +157,6 @@ __global__ __launch_bounds__(1024) void final_codebook_kernel(const float *__res
 
 // ---- host side --------------------------------------------------------------------------------------
 
-static int launch_assign(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int ncent, void *labels,
-                         int label_bytes, float *dist, hipStream_t st)
-{
-    if (n == 0) return DCPQ_OK;
-    const dim3 grid(static_cast<unsigned>((n + kAssignQ - 1) / kAssignQ), m);
-    switch (label_bytes) {
-        case 1:
-            DCPQ_LAUNCH(kStageTrain, st, assign_kernel<uint8_t>, grid, dim3(256), 0, points, n, ld, cb, m, dsub, ncent,
-                        static_cast<uint8_t *>(labels), dist);
-            break;
-        case 2:
-            DCPQ_LAUNCH(kStageTrain, st, assign_kernel<uint16_t>, grid, dim3(256), 0, points, n, ld, cb, m, dsub, ncent,
-                        static_cast<uint16_t *>(labels), dist);
-            break;
-        default:
-            DCPQ_LAUNCH(kStageTrain, st, assign_kernel<uint32_t>, grid, dim3(256), 0, points, n, ld, cb, m, dsub, ncent,
-                        static_cast<uint32_t *>(labels), dist);
-            break;
-    }
-    DCPQ_CHECK_LAUNCH("assign_kernel");
-    return DCPQ_OK;
-}
-
 static size_t means_bytes(int k, int d) { return align_up(sizeof(double) * static_cast<size_t>(k) * d + sizeof(uint32_t) * k, 256); }
 
 // centroids[c] = mean of the points labelled c (ws: means_bytes(k, d))
@@ -352,7 +211,7 @@ extern "C" int dcpq_assign(const float *points, uint64_t n, int ld, const float 
 {
     clear_error();
     if (!dcpq_shape_supported(m, dsub)) return fail(DCPQ_EUNSUPPORTED, "assign: m=%d dsub=%d not supported", m, dsub);
-    DCPQ_REQUIRE(n < (1ull << 32) * kAssignQ, "assign: n out of range");
+    DCPQ_REQUIRE(n < (1ull << 37), "assign: n out of range");
     DCPQ_REQUIRE(ld >= m * dsub, "assign: row stride %d below m * dsub = %d", ld, m * dsub);
     DCPQ_REQUIRE(label_bytes == 1 || label_bytes == 2 || label_bytes == 4, "assign: label_bytes=%d (1, 2 or 4)", label_bytes);
     DCPQ_REQUIRE(n_entries >= 1 && (label_bytes == 4 || n_entries <= (1 << (8 * label_bytes))),
