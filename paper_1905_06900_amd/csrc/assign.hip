@@ -3,14 +3,19 @@
 //
 // Computed in two steps with the result of one.  A filter evaluates |c|^2 - 2 <x, c> for all centroids on
 // the bf16 matrix cores with every fp32 number split into two bf16 numbers (x = xh + xl + an error of at most
-// 2^-18 |x|; three products xh ch + xl ch + xh cl, and |c|^2 as three bf16 numbers against ones, all along the
-// K dimension of one matrix product), and keeps per point the three smallest minima over cells of 16
-// centroids.  A bound on the filter's error, from the norms at hand, says which cells can hold the nearest
+// 2^-18 |x|; the three products xh ch + xl ch + xh cl lie side by side along the K dimension of one matrix
+// product whose accumulators start from |c|^2), and keeps per point the three smallest minima over cells of
+// 16 or 32 centroids.  A bound on the filter's error, from the norms at hand, says which cells can hold the nearest
 // centroid: those, almost always one or two, are evaluated in double precision.  A point with more such cells
 // than were kept (or whose values are not finite) is compared with all centroids in double precision.
 //
-// What bounds it: the matrix pipe (KS instructions of 32 cycles per 32 x 32 distances, KS = ceil((3 d + 4) / 16)),
-// beside 1.0 vector instruction per lane and distance for the minima.
+// What bounds it: the matrix pipe (KS instructions of 32 cycles per 32 x 32 distances, KS = ceil(3 d / 16)) is busy
+// half of the time; beside it the vector port takes 9 instructions per 32 x 32 distances and 64 lanes for the minima
+// and as many again for the conversion of the centroids (shared by the points of a workgroup), and the LDS a third
+// to a half of the cycles for the operands.  250007 vectors, 8 sub-quantizers of 16 components and 65536 centroids:
+// 11.1 ms = 1.13 PFLOP/s of bf16 products, what a large library matrix product reaches here (1.16); with all
+// distances on the double-precision matrix pipe 97 ms.  d = 32: 6.0 ms per 100000 x 4 (32.7 in double precision);
+// d = 60: 9.6 ms per 20000 x 16 (58.8).
 #include "common.h"
 #include "assign.h"
 
@@ -26,15 +31,18 @@ struct __attribute__((packed, aligned(4))) f4_any { float v[4]; };
 // and split the centroids (else every wavefront has points of its own).  RS: centroids staged together.
 template <int KS, int P, bool SPLIT>
 struct AssignCfg {
-    static constexpr int RS = KS <= 7 ? 128 : 32;              // centroids per stage
+    static constexpr int RS = KS <= 6 ? 128 : 64;              // centroids per stage
+    static constexpr int AHEAD = KS * P <= 12 ? 2 : 1;              // operand sets of a tile (2: read one tile ahead)
+    static constexpr int TPC = SPLIT ? 1 : RS / 32;            // tiles of 32 centroids per cell
     static constexpr int TPR = 256 / RS;                       // threads that convert one centroid
-    static constexpr int DPMAX = (16 * KS - 4) / 3 & ~3;       // largest padded sub-vector length
+    static constexpr int DPMAX = 16 * KS / 3 & ~3;             // largest padded sub-vector length
     static constexpr int NG = (DPMAX / 4 + TPR - 1) / TPR;     // groups of 4 components per thread
     static constexpr int STRIDE = KS * 32 + 16;                // bytes per staged row (an odd number of 16-byte units)
     static constexpr int PTS = SPLIT ? 32 * P : 128 * P;       // points per workgroup
     static constexpr int NE = SPLIT ? 8 : 2;                   // lanes that hold minima of one point
-    static constexpr int STAGE_BYTES = 2 * RS * STRIDE;
-    static constexpr int ENT_BYTES = PTS * NE * 5 * 4 + PTS * 4;
+    static constexpr int BUF_BYTES = RS * STRIDE + RS * 4;     // the rows, then |c|^2 of every row
+    static constexpr int STAGE_BYTES = 2 * BUF_BYTES;
+    static constexpr int ENT_BYTES = PTS * NE * 5 * 4 + 3 * PTS * 4;    // minima, three lists of points
     static constexpr int LDS_BYTES = STAGE_BYTES > ENT_BYTES ? STAGE_BYTES : ENT_BYTES;
     static_assert(!SPLIT || RS == 128, "one 32-centroid tile per wavefront and stage");
 };
@@ -74,17 +82,18 @@ __device__ inline void store_label(void *labels, int label_bytes, size_t o, uint
 
 // Nearest centroid of the j-th sub-vector of every point, j = blockIdx.y.  points: rows of `ld` floats;
 // sub-vector j starts at column j * dsub.  labels: [n][m].  dist (optional): [n][m] fp32 squared distance.
-// dp: dsub rounded up to a multiple of 4, 3 dp + 4 <= 16 KS.
+// dp: dsub rounded up to a multiple of 4, 3 dp <= 16 KS.
 template <int KS, int P, bool SPLIT>
-__global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
+__global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
                                                      const float *__restrict__ cb, int m, int dsub, int dp, int ncent,
                                                      void *__restrict__ labels, int label_bytes, float *__restrict__ dist)
 {
     using C = AssignCfg<KS, P, SPLIT>;
     extern __shared__ __align__(16) uint8_t smem[];
-    __shared__ float mu[128];
+    __shared__ __align__(16) float mu[128];
     __shared__ float s_cmax[4];
-    __shared__ uint32_t s_nhard;
+    __shared__ float xnorm2[C::PTS];
+    __shared__ uint32_t s_count[3];                                 // points in the lists below
     __shared__ double red_v[4];
     __shared__ uint32_t red_i[4];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -106,13 +115,13 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
             }
         mu[tid] = sum / static_cast<float>(ns);
     }
-    if (tid == 0) s_nhard = 0;
+    if (tid < 3) s_count[tid] = 0;
     for (int t = tid; t < C::STAGE_BYTES / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);
     __syncthreads();
 
     const int srow = tid / C::TPR, spart = tid % C::TPR;
     // The point side of the product: column `col` of B, K positions 16 ks + 8 half + e:
-    // [ -2 xh | -2 xl | -2 xh | 1 1 1 | 0 ... ] against the centroids' [ ch | ch | cl | |c|^2 in three parts | 0 ... ].
+    // [ -2 xh | -2 xl | -2 xh | 0 ... ] against the centroids' [ ch | ch | cl | 0 ... ].
     // Converted in rows by the whole workgroup, RS points at a time, and read back as operands.
     v8bf bq[P][KS];
 #pragma unroll
@@ -122,6 +131,7 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
             const uint64_t q = q0 + p * (SPLIT ? 32 : 128) + sub * C::RS + srow;
             const float *x = points + static_cast<size_t>(q < n ? q : n - 1) * ld + j * dsub;
             uint8_t *row = smem + srow * C::STRIDE;
+            float norm = 0.0f;
 #pragma unroll 1
             for (int g = 0; g < C::NG; ++g) {
                 const int o = 4 * (spart + C::TPR * g);
@@ -130,19 +140,19 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int t = o + e < dsub ? o + e : dsub - 1;
-                        const float v = o + e < dsub ? -2.0f * (x[t] - mu[t]) : 0.0f;
+                        const float u = o + e < dsub ? x[t] - mu[t] : 0.0f, v = -2.0f * u;
                         h[e] = static_cast<__bf16>(v);
                         l[e] = static_cast<__bf16>(v - static_cast<float>(h[e]));
+                        norm = fmaf(u, u, norm);
                     }
                     *reinterpret_cast<v4bf *>(row + 2 * o) = h;
                     *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = l;
                     *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = h;
                 }
             }
-            if (spart == 0) {
-                const __bf16 one = static_cast<__bf16>(1.0f);
-                *reinterpret_cast<v4bf *>(row + 6 * dp) = v4bf{one, one, one, static_cast<__bf16>(0.0f)};
-            }
+#pragma unroll
+            for (int off = 1; off < C::TPR; off <<= 1) norm += __shfl_xor(norm, off);
+            if (spart == 0 && p * (SPLIT ? 32 : 128) + sub * C::RS + srow < C::PTS) xnorm2[p * (SPLIT ? 32 : 128) + sub * C::RS + srow] = norm;
             __syncthreads();
             if (SPLIT || wave * 32 / C::RS == sub) {
                 const uint8_t *b = smem + ((SPLIT ? 0 : wave * 32 % C::RS) + col) * C::STRIDE + half * 16;
@@ -158,7 +168,7 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
     auto load_stage = [&](int c0) {
         const int c = c0 + srow;
         const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
-        if ((dsub & 3) == 0) {
+        if (dp == dsub) {
 #pragma unroll
             for (int g = 0; g < C::NG; ++g) {
                 const int o = 4 * (spart + C::TPR * g);
@@ -172,7 +182,8 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int o = 4 * (spart + C::TPR * g) + e;
-                    pre[g][e] = src[o < dsub ? o : 0];
+                    const float v = src[o < dsub ? o : 0];
+                    pre[g][e] = o < dsub ? v : 0.0f;                  // (mu is zero there)
                 }
         }
     };
@@ -185,9 +196,11 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
             const int o = 4 * (spart + C::TPR * g);
             if (o < dp) {
                 v4bf h, l;
+                const float4 mv = *reinterpret_cast<const float4 *>(mu + o);
+                const float ref[4] = {mv.x, mv.y, mv.z, mv.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float v = o + e < dsub ? pre[g][e] - mu[o + e] : 0.0f;
+                    const float v = pre[g][e] - ref[e];
                     h[e] = static_cast<__bf16>(v);
                     l[e] = static_cast<__bf16>(v - static_cast<float>(h[e]));
                     norm = fmaf(v, v, norm);
@@ -199,22 +212,9 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
         }
 #pragma unroll
         for (int off = 1; off < C::TPR; off <<= 1) norm += __shfl_xor(norm, off);
-        if (spart == 0) {
-            v4bf nn;
-            if (c0 + srow < ncent) {
-                cmax2 = fmaxf(cmax2, norm);
-                if (!(norm < INFINITY)) cmax2 = INFINITY;            // (also NaN)
-                nn[0] = static_cast<__bf16>(norm);
-                const float r1 = norm - static_cast<float>(nn[0]);
-                nn[1] = static_cast<__bf16>(r1);
-                nn[2] = static_cast<__bf16>(r1 - static_cast<float>(nn[1]));
-            } else {                                                 // past the last centroid: never the nearest
-                nn[0] = static_cast<__bf16>(3e38f);
-                nn[1] = nn[2] = static_cast<__bf16>(0.0f);
-            }
-            nn[3] = static_cast<__bf16>(0.0f);
-            *reinterpret_cast<v4bf *>(row + 6 * dp) = nn;
-        }
+        if (c0 + srow < ncent) cmax2 = norm < INFINITY ? fmaxf(cmax2, norm) : INFINITY;      // (NaN counts as infinite)
+        else norm = INFINITY;                                                               // past the last centroid: never the nearest
+        if (spart == 0) reinterpret_cast<float *>(buf + C::RS * C::STRIDE)[srow] = norm;
     };
 
     // three smallest cell minima of each of this lane's points, and the cells of the first two
@@ -222,31 +222,74 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
     uint32_t i1[P], i2[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) { b1[p] = b2[p] = b3[p] = INFINITY; i1[p] = i2[p] = 0; }
-    auto compute_tile = [&](const uint8_t *buf, int t, uint32_t cell) {
-        const uint8_t *a = buf + (t * 32 + col) * C::STRIDE + half * 16;
-        v16f acc[P];
+    float mn[P];                              // minimum of the cell so far
+    // One wavefront's tiles of a stage.  Short operands of a tile are read one tile ahead; the minimum over the 16 filter
+    // values of one tile of points (row 8 (v / 4) + 4 half + v % 4 in value v) is taken while the matrix
+    // instructions of the next run.
+    auto read_tile = [&](const uint8_t *buf, int t, v8bf (&a)[KS], v16f &norm) {
+        const uint8_t *ra = buf + (t * 32 + col) * C::STRIDE + half * 16;
 #pragma unroll
-        for (int p = 0; p < P; ++p)
+        for (int ks = 0; ks < KS; ++ks) a[ks] = *reinterpret_cast<const v8bf *>(ra + ks * 32);
+        const float *nr = reinterpret_cast<const float *>(buf + C::RS * C::STRIDE) + t * 32 + 4 * half;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[p][v] = 0.0f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const v8bf av = *reinterpret_cast<const v8bf *>(a + ks * 32);
-#pragma unroll
-            for (int p = 0; p < P; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bq[p][ks], acc[p], 0, 0, 0);
+        for (int v = 0; v < 16; v += 4) {
+            const float4 x = *reinterpret_cast<const float4 *>(nr + 2 * v);
+            norm[v] = x.x; norm[v + 1] = x.y; norm[v + 2] = x.z; norm[v + 3] = x.w;
         }
+    };
+    auto minimum = [](const v16f &acc) {
+        float m0 = fminf(fminf(acc[0], acc[1]), acc[2]), m1 = fminf(fminf(acc[3], acc[4]), acc[5]);
+#pragma unroll
+        for (int v = 6; v < 14; v += 4) {
+            m0 = fminf(fminf(acc[v], acc[v + 1]), m0);
+            m1 = fminf(fminf(acc[v + 2], acc[v + 3]), m1);
+        }
+        m0 = fminf(fminf(acc[14], acc[15]), m0);
+        return fminf(m0, m1);
+    };
+    auto compute_cell = [&](const uint8_t *buf, int t0) {
+        constexpr int AH = C::AHEAD;
+        v8bf a[AH][KS];
+        v16f norm[AH], acc[2];
+        if constexpr (AH == 2) read_tile(buf, t0, a[0], norm[0]);
+#pragma unroll
+        for (int x = 0; x <= C::TPC * P; ++x) {                       // step x: products of (tile x / P, points x % P), minimum of step x - 1
+            const int t = x / P, p = x % P;
+            if (x < C::TPC * P) {
+                if constexpr (AH == 2) {
+                    if (p == 0 && t + 1 < C::TPC) read_tile(buf, t0 + t + 1, a[(t + 1) & 1], norm[(t + 1) & 1]);
+                } else {
+                    if (p == 0) read_tile(buf, t0 + t, a[0], norm[0]);
+                }
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    acc[x & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t % AH][ks], bq[p][ks], ks == 0 ? norm[t % AH] : acc[x & 1], 0, 0, 0);
+            }
+            if (x > 0) {
+                const int q = (x - 1) % P;
+                const float v = minimum(acc[(x - 1) & 1]);
+                mn[q] = x <= P ? v : fminf(mn[q], v);
+                asm volatile("" : "+v"(mn[q]));                       // (keeps it here: its use is behind a branch)
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {                         // matrix and vector instructions in turn
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, (9 + KS - 1) / KS, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto enter = [&](uint32_t cell) {         // entering the three smallest becomes rare as the walk goes on
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            float mn = acc[p][0];
-#pragma unroll
-            for (int v = 1; v + 1 < 16; v += 2) mn = fminf(fminf(acc[p][v], acc[p][v + 1]), mn);
-            mn = fminf(mn, acc[p][15]);
-            const bool c1 = mn < b1[p], c2 = mn < b2[p];
-            i2[p] = c1 ? i1[p] : c2 ? cell : i2[p];
+            if (!__builtin_amdgcn_ballot_w64(mn[p] < b3[p])) continue;          // uniform
+            const bool c1 = mn[p] < b1[p], c2 = mn[p] < b2[p];
+            const uint32_t second = c2 ? cell : i2[p];
+            i2[p] = c1 ? i1[p] : second;
             i1[p] = c1 ? cell : i1[p];
-            b3[p] = __builtin_amdgcn_fmed3f(b2[p], b3[p], mn);
-            b2[p] = __builtin_amdgcn_fmed3f(b1[p], b2[p], mn);
-            b1[p] = fminf(b1[p], mn);
+            b3[p] = __builtin_amdgcn_fmed3f(b2[p], b3[p], mn[p]);
+            b2[p] = __builtin_amdgcn_fmed3f(b1[p], b2[p], mn[p]);
+            b1[p] = fminf(b1[p], mn[p]);
         }
     };
     const int nst = (ncent + C::RS - 1) / C::RS;
@@ -254,20 +297,18 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
     store_stage(0, smem);
     __syncthreads();
     for (int s = 0; s < nst; ++s) {                                   // uniform
-        const uint8_t *buf = smem + (s & 1) * (C::RS * C::STRIDE);
         if (s + 1 < nst) load_stage((s + 1) * C::RS);
-        if constexpr (SPLIT) compute_tile(buf, wave, s * (C::RS / 32) + wave);
-        else {
-#pragma unroll 1
-            for (int t = 0; t < C::RS / 32; ++t) compute_tile(buf, t, s * (C::RS / 32) + t);
-        }
-        if (s + 1 < nst) store_stage((s + 1) * C::RS, smem + ((s + 1) & 1) * (C::RS * C::STRIDE));
+        compute_cell(smem + (s & 1) * C::BUF_BYTES, SPLIT ? wave : 0);
+        enter(SPLIT ? s * (C::RS / 32) + wave : s);
+        if (s + 1 < nst) store_stage((s + 1) * C::RS, smem + ((s + 1) & 1) * C::BUF_BYTES);
         __syncthreads();
     }
 
     // hand the minima over: ent[point][lane that held them][b1, b2, b3, i1, i2]
     float *ent = reinterpret_cast<float *>(smem);
-    uint32_t *hard = reinterpret_cast<uint32_t *>(smem + C::PTS * C::NE * 20);        // points for the full comparison
+    uint32_t *list[3];                        // points with one cell to look at, with several, and for the full comparison
+#pragma unroll
+    for (int k = 0; k < 3; ++k) list[k] = reinterpret_cast<uint32_t *>(smem + C::PTS * C::NE * 20) + k * C::PTS;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int pt = SPLIT ? p * 32 + col : p * 128 + wave * 32 + col;
@@ -288,63 +329,141 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
     auto filter_error = [](float xn, float c1) {
         return xn * c1 * (kSplit + 2.1f * kAdd) + c1 * c1 * (1.1f * kAdd) + 1e-35f * (1.0f + xn + c1);
     };
-    const int l16 = tid & 15;
-    for (int pt = tid >> 4; pt < C::PTS; pt += 16) {                  // 16 lanes per point
-        const uint64_t q = q0 + pt;
-        if (q >= n) break;
-        const float *x = points + static_cast<size_t>(q) * ld + j * dsub;
-        float xn2 = 0.0f;
-        for (int t = l16; t < dsub; t += 16) { const float v = x[t] - mu[t]; xn2 = fmaf(v, v, xn2); }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) xn2 += __shfl_xor(xn2, off);
-        const float xn = sqrtf(xn2) * 1.001f;
+    // Largest filter value a nearest centroid can have.  The nearest centroid is no farther than the one with the
+    // smallest filter value, so its norm is at most |x| plus that distance.
+    auto threshold = [&](int pt) {
         const float *e = ent + pt * C::NE * 5;
+        const float xn = sqrtf(xnorm2[pt]) * 1.001f;
         float gmin = INFINITY;
 #pragma unroll
         for (int k = 0; k < C::NE; ++k) gmin = fminf(gmin, e[k * 5]);
-        // The nearest centroid is no farther than the one with the smallest filter value, so its norm is at
-        // most |x| plus that distance.
         const float d2 = fmaxf(xn * xn + gmin + filter_error(xn, cmax), 0.0f);
         const float c1 = fminf(cmax, (xn + sqrtf(d2)) * 1.001f);
-        const float thr = gmin + 2.0f * filter_error(xn, c1);
+        return gmin + 2.0f * filter_error(xn, c1);
+    };
+    for (int pt = tid; pt < C::PTS; pt += 256) {
+        if (q0 + pt >= n) break;
+        const float *e = ent + pt * C::NE * 5;
+        const float thr = threshold(pt);
         bool full = !(thr < 1e37f);
+        int cells = 0, last = 0;
 #pragma unroll
-        for (int k = 0; k < C::NE; ++k) full = full || e[k * 5 + 2] <= thr;
-        if (full) {
-            if (l16 == 0) hard[atomicAdd(&s_nhard, 1u)] = static_cast<uint32_t>(pt);
+        for (int k = 0; k < C::NE; ++k) {
+            full = full || e[k * 5 + 2] <= thr;
+            if (e[k * 5] <= thr) { ++cells; last = 2 * k; }
+            if (e[k * 5 + 1] <= thr) { ++cells; last = 2 * k + 1; }
+        }
+        const int kind = full ? 2 : cells == 1 ? 0 : 1;
+        list[kind][atomicAdd(&s_count[kind], 1u)] = static_cast<uint32_t>(pt) | static_cast<uint32_t>(last) << 16;
+    }
+    __syncthreads();
+    const int l16 = tid & 15;
+    // centroid of 16-lane group position l16 in tile t of the cell of entry k of a point
+    auto cell_centroid = [&](const float *e, int k, int t) {
+        const int h = C::NE == 2 ? k >> 1 : (k >> 1) & 1;
+        const uint32_t cell = __float_as_uint(e[(k >> 1) * 5 + 3 + (k & 1)]);
+        return (cell * C::TPC + t) * 32 + 8 * (l16 >> 2) + 4 * h + (l16 & 3);
+    };
+    auto put = [&](uint64_t q, double best, uint32_t bi) {
+        const size_t o = static_cast<size_t>(q) * m + j;
+        store_label(labels, label_bytes, o, bi);
+        if (dist) dist[o] = static_cast<float>(best);
+    };
+    // One cell: distances in fp32 from the differences are within (dsub + 4) 2^-23 of themselves, so usually one
+    // centroid is left; only where several are (or the distance itself is wanted) is double precision needed.
+    // 16 lanes per point.
+    const float near = 1.0f + 2.2f * static_cast<float>(dsub + 4) / 8388608.0f;
+    const uint32_t n_one = s_count[0], n_several = s_count[1], n_hard = s_count[2];
+    for (uint32_t t0 = tid >> 4; t0 < n_one; t0 += 16) {
+        const uint32_t rec = list[0][t0];
+        const int pt = static_cast<int>(rec & 0xFFFFu), k = static_cast<int>(rec >> 16);
+        const uint64_t q = q0 + pt;
+        const float *x = points + static_cast<size_t>(q) * ld + j * dsub, *e = ent + pt * C::NE * 5;
+        uint32_t c[C::TPC];
+        const float *row[C::TPC];
+        float v[C::TPC];
+#pragma unroll
+        for (int t = 0; t < C::TPC; ++t) {
+            c[t] = cell_centroid(e, k, t);
+            row[t] = cbj + static_cast<size_t>(c[t] < static_cast<uint32_t>(ncent) ? c[t] : ncent - 1) * dsub;
+            v[t] = 0.0f;
+        }
+        int d0 = 0;
+#pragma unroll 4
+        for (; d0 + 4 <= dsub; d0 += 4) {
+            const f4_any a = *reinterpret_cast<const f4_any *>(x + d0);
+#pragma unroll
+            for (int t = 0; t < C::TPC; ++t) {
+                const f4_any b = *reinterpret_cast<const f4_any *>(row[t] + d0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { const float u = a.v[i] - b.v[i]; v[t] = fmaf(u, u, v[t]); }
+            }
+        }
+        for (; d0 < dsub; ++d0)
+#pragma unroll
+            for (int t = 0; t < C::TPC; ++t) { const float u = x[d0] - row[t][d0]; v[t] = fmaf(u, u, v[t]); }
+        float mn = INFINITY;
+#pragma unroll
+        for (int t = 0; t < C::TPC; ++t) {
+            if (c[t] >= static_cast<uint32_t>(ncent)) v[t] = INFINITY;
+            mn = fminf(mn, v[t]);
+        }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) mn = fminf(mn, __shfl_xor(mn, off));
+        const float lim = mn * near + 1e-34f;
+        int left = 0;
+        uint32_t bi = 0xFFFFFFFFu;
+#pragma unroll
+        for (int t = 0; t < C::TPC; ++t)
+            if (v[t] <= lim) { ++left; bi = min(bi, c[t]); }
+        int total = left;
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) total += __shfl_xor(total, off);
+        if (total == 1 && !dist) {
+            if (left) put(q, 0.0, bi);
             continue;
         }
         double best = INFINITY;
-        uint32_t bi = 0xFFFFFFFFu;
-#pragma unroll 1
-        for (int k = 0; k < 2 * C::NE; ++k) {
-            const float *ek = e + (k >> 1) * 5;
-            if (ek[k & 1] <= thr) {
-                const int h = C::NE == 2 ? k >> 1 : (k >> 1) & 1;
-                const uint32_t cell = __float_as_uint(ek[3 + (k & 1)]);
-                const uint32_t c = cell * 32 + 8 * (l16 >> 2) + 4 * h + (l16 & 3);
-                if (c < static_cast<uint32_t>(ncent)) {
-                    const double v = exact_distance(x, cbj + static_cast<size_t>(c) * dsub, dsub);
-                    take_smaller(best, bi, v, c);
-                }
-            }
-        }
+        bi = 0xFFFFFFFFu;
+#pragma unroll
+        for (int t = 0; t < C::TPC; ++t)
+            if ((v[t] <= lim || !(lim < INFINITY)) && c[t] < static_cast<uint32_t>(ncent)) take_smaller(best, bi, exact_distance(x, row[t], dsub), c[t]);
 #pragma unroll
         for (int off = 1; off < 16; off <<= 1) {
             const double ov = __shfl_xor(best, off);
             const uint32_t oi = __shfl_xor(bi, off);
             take_smaller(best, bi, ov, oi);
         }
-        if (l16 == 0) {
-            const size_t o = static_cast<size_t>(q) * m + j;
-            store_label(labels, label_bytes, o, bi);
-            if (dist) dist[o] = static_cast<float>(best);
-        }
+        if (l16 == 0) put(q, best, bi);
     }
-    __syncthreads();
-    const uint32_t nhard = s_nhard;
-    for (uint32_t hi = 0; hi < nhard; ++hi) {                         // uniform
-        const uint64_t q = q0 + hard[hi];
+    // several cells
+    for (uint32_t t0 = tid >> 4; t0 < n_several; t0 += 16) {
+        const int pt = static_cast<int>(list[1][t0] & 0xFFFFu);
+        const uint64_t q = q0 + pt;
+        const float *x = points + static_cast<size_t>(q) * ld + j * dsub, *e = ent + pt * C::NE * 5;
+        const float thr = threshold(pt);
+        double best = INFINITY;
+        uint32_t bi = 0xFFFFFFFFu;
+#pragma unroll 1
+        for (int k = 0; k < 2 * C::NE; ++k)
+            if (e[(k >> 1) * 5 + (k & 1)] <= thr) {
+#pragma unroll
+                for (int t = 0; t < C::TPC; ++t) {
+                    const uint32_t c = cell_centroid(e, k, t);
+                    if (c < static_cast<uint32_t>(ncent)) take_smaller(best, bi, exact_distance(x, cbj + static_cast<size_t>(c) * dsub, dsub), c);
+                }
+            }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {
+            const double ov = __shfl_xor(best, off);
+            const uint32_t oi = __shfl_xor(bi, off);
+            take_smaller(best, bi, ov, oi);
+        }
+        if (l16 == 0) put(q, best, bi);
+    }
+    // the whole workgroup compares the points whose cells are not all known with every centroid
+    for (uint32_t hi = 0; hi < n_hard; ++hi) {                        // uniform
+        const uint64_t q = q0 + (list[2][hi] & 0xFFFFu);
         const float *x = points + static_cast<size_t>(q) * ld + j * dsub;
         double best = INFINITY;
         uint32_t bi = 0xFFFFFFFFu;
@@ -359,9 +478,7 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ p
         __syncthreads();
         if (tid == 0) {
             for (int w = 1; w < 4; ++w) take_smaller(best, bi, red_v[w], red_i[w]);
-            const size_t o = static_cast<size_t>(q) * m + j;
-            store_label(labels, label_bytes, o, bi);
-            if (dist) dist[o] = static_cast<float>(best);
+            put(q, best, bi);
         }
         __syncthreads();
     }
@@ -385,14 +502,17 @@ template <int KS>
 static int launch_assign_ks(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
                             void *labels, int label_bytes, float *dist, hipStream_t st)
 {
-    // two rounds of the 256 CUs with tiles that large, else the tile that gives more workgroups
+    // The largest tile of points that still gives two workgroups per CU (the centroids are converted once per
+    // workgroup and read from LDS once per wavefront, so large tiles are cheaper: 204 cycles per 32 x 32 distances with
+    // 512 points at d = 16, 290 with 256); below that the four wavefronts split the centroids (2000 points, 8 x 16
+    // components: 0.50 ms; 1.3 ms with 256-point tiles, which leave most CUs without work).
     auto enough = [&](int pts) { return (n + pts - 1) / pts * static_cast<uint64_t>(m) >= 512; };
-    if constexpr (KS <= 5) {
+    if constexpr (KS <= 6) {
         if (enough(AssignCfg<KS, 4, false>::PTS)) return launch_assign_t<KS, 4, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
     }
-    if (enough(AssignCfg<KS, KS <= 16 ? 2 : 1, false>::PTS) || KS > 7)
-        return launch_assign_t<KS, KS <= 16 ? 2 : 1, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    if constexpr (KS <= 7) return launch_assign_t<KS, 1, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    if (enough(AssignCfg<KS, KS <= 12 ? 2 : 1, false>::PTS) || KS > 6)
+        return launch_assign_t<KS, KS <= 12 ? 2 : 1, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    if constexpr (KS <= 6) return launch_assign_t<KS, 1, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
     return DCPQ_OK;
 }
 
@@ -400,11 +520,11 @@ int launch_assign(const float *points, uint64_t n, int ld, const float *cb, int 
                   int label_bytes, float *dist, hipStream_t st)
 {
     if (n == 0) return DCPQ_OK;
-    const int dp = (dsub + 3) & ~3, ks = (3 * dp + 4 + 15) / 16;
+    const int dp = (dsub + 3) & ~3, ks = (3 * dp + 15) / 16;
 #define DCPQ_ASSIGN_KS(K) \
     if (ks <= K) return launch_assign_ks<K>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    DCPQ_ASSIGN_KS(1) DCPQ_ASSIGN_KS(2) DCPQ_ASSIGN_KS(3) DCPQ_ASSIGN_KS(4) DCPQ_ASSIGN_KS(5) DCPQ_ASSIGN_KS(7)
-    DCPQ_ASSIGN_KS(9) DCPQ_ASSIGN_KS(12) DCPQ_ASSIGN_KS(13) DCPQ_ASSIGN_KS(16) DCPQ_ASSIGN_KS(20) DCPQ_ASSIGN_KS(25)
+    DCPQ_ASSIGN_KS(1) DCPQ_ASSIGN_KS(2) DCPQ_ASSIGN_KS(3) DCPQ_ASSIGN_KS(4) DCPQ_ASSIGN_KS(5) DCPQ_ASSIGN_KS(6)
+    DCPQ_ASSIGN_KS(8) DCPQ_ASSIGN_KS(10) DCPQ_ASSIGN_KS(12) DCPQ_ASSIGN_KS(16) DCPQ_ASSIGN_KS(20) DCPQ_ASSIGN_KS(24)
 #undef DCPQ_ASSIGN_KS
     return fail(DCPQ_EUNSUPPORTED, "assign: dsub=%d not supported", dsub);
 }

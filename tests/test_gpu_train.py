@@ -53,6 +53,46 @@ def test_assign_against_the_oracle(n, m, dsub, ncent):
         np.testing.assert_allclose(dist[:, j], rd, rtol=1e-5, atol=1e-12 * float((p_np.astype(np.float64) ** 2).sum(1).max()))
 
 
+@pytest.mark.parametrize("dsub", [1, 3, 5, 8, 10, 12, 16, 20, 24, 32, 40, 52, 60, 84, 100, 128])
+@pytest.mark.parametrize("n,ncent", [(31, 1), (129, 33), (300, 129), (1027, 1000)])
+def test_assign_at_the_edges_of_tiles_and_vector_lengths(dsub, n, ncent):
+    # every length of the filter's matrix product, tiles of points and centroids that are not full, and (last point
+    # and centroids) a large offset with small differences, where the filter's error bound exceeds the distances
+    print("assign edges dsub=%d n=%d ncent=%d" % (dsub, n, ncent), flush=True)
+    g = gen(17 * dsub + n)
+    pts = torch.randn((n, dsub), generator=g, device=DEV)
+    cb = torch.randn((1, ncent, dsub), generator=g, device=DEV)
+    if ncent > 40:
+        cb[0, 20:40] = 3000.0 + 1e-3 * torch.randn((20, dsub), generator=g, device=DEV)
+        cb[0, 39] = cb[0, 21]                                   # equal centroids: the smaller index must win
+        pts[-1] = 3000.0
+        pts[0] = cb[0, 39]
+    labels, dist = binding.assign(pts, cb, want_dist=True)
+    labels2 = binding.assign(pts, cb)
+    torch.cuda.synchronize()
+    p_np, c_np = to_np(pts), to_np(cb)[0]
+    ref, rd = oracle.assign(p_np, c_np, want_dist=True)
+    check_labels(to_np(labels)[:, 0], p_np, c_np, ref, "dsub %d" % dsub)
+    np.testing.assert_array_equal(to_np(labels), to_np(labels2))
+    np.testing.assert_allclose(to_np(dist)[:, 0], rd, rtol=1e-5, atol=1e-12 * float((p_np.astype(np.float64) ** 2).sum(1).max()))
+
+
+@pytest.mark.parametrize("n,m,dsub", [(66_000, 8, 4), (140_000, 1, 16), (34_000, 16, 30)])
+def test_assign_with_the_large_point_tiles(n, m, dsub):
+    print("assign large tiles n=%d m=%d dsub=%d" % (n, m, dsub), flush=True)
+    g = gen(n)
+    pts = torch.randn((n, m * dsub), generator=g, device=DEV)
+    cb = torch.randn((m, 200, dsub), generator=g, device=DEV)
+    labels = to_np(binding.assign(pts, cb))
+    p64, c64 = pts.double().cpu(), cb.double().cpu()
+    for j in range(m):
+        x, c = p64[:, j * dsub:(j + 1) * dsub], c64[j]
+        d = (x ** 2).sum(1, keepdim=True) + (c ** 2).sum(1)[None] - 2.0 * (x @ c.T)
+        chosen = d.gather(1, torch.from_numpy(labels[:, j].astype(np.int64))[:, None])[:, 0]
+        best = d.min(1).values
+        assert bool((chosen <= best + 1e-12 * ((x ** 2).sum(1) + float((c ** 2).sum(1).max()))).all()), "sub-quantizer %d" % j
+
+
 @pytest.mark.parametrize("b", [16, 8])
 def test_encode_against_the_oracle(b):
     m, dsub, n = (4, 8, 3000) if b == 16 else (8, 4, 20000)
