@@ -312,6 +312,21 @@ def test_scan_selection_with_one_large_group_of_equal_candidates():
     scan_vs_oracle(codes2, qtab[1:], r)
 
 
+@pytest.mark.parametrize("r", [1, 900, 10_000, 15_900, 16_500])
+def test_scan_selection_deals_out_only_the_groups_that_reach_r(r):
+    # tens of thousands of codes tie in the bucket of the r-th candidate (more than the selection holds), for r up to
+    # where ranks are counted and (the last one) beyond it, where the sorting network takes over
+    rng = np.random.default_rng(r)
+    N = 120_000
+    codes = rng.integers(0, 65536, size=(N, 8)).astype(np.uint16)
+    qtab = rng.integers(10, 60, size=(3, 8, 256)).astype(np.uint8)
+    qtab[:, 0, :100] = 1
+    qtab[:, 1:, :] = rng.integers(0, 2, size=(3, 7, 1))
+    qtab[2, 1, :64] += 3
+    print("selection r=%d" % r, flush=True)
+    scan_vs_oracle(codes, qtab, r, modes=(binding.SCAN_AUTO,))
+
+
 def test_small_tables_edges_degenerate_range_and_r_beyond_n():
     rng = np.random.default_rng(5)
     m, dsub = 8, 16
