@@ -671,7 +671,7 @@ __global__ __launch_bounds__(256) void ivf_scan_single_kernel(const CodeT *__res
                                                              const IvfUnit *__restrict__ units,
                                                              const uint32_t *__restrict__ nunits,
                                                              const uint8_t *__restrict__ qtab, int nprobe, uint32_t r,
-                                                             uint32_t cap, uint32_t upd, uint32_t qflush, int *t_cur,
+                                                             uint32_t cap, uint32_t upd, uint32_t qflush, Bound *bound,
                                                              uint32_t *count, uint32_t *chist, uint64_t *__restrict__ keys)
 {
     constexpr int BPC = M * static_cast<int>(sizeof(CodeT));
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256) void ivf_scan_single_kernel(const CodeT *__res
     };
     auto load_bound = [&]() {
         if constexpr (SAMPLE) return 0;
-        const int t = __hip_atomic_load(&t_cur[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int t = __hip_atomic_load(&bound[q].t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return t >= 255 ? 0x7fffffff : t;
     };
     // The unit's first codes and its tables travel together: the code loads are issued first, the table words
@@ -738,10 +738,10 @@ __global__ __launch_bounds__(256) void ivf_scan_single_kernel(const CodeT *__res
         if (static_cast<uint32_t>(lane) < qlen) {
             const uint64_t key = wq[lane];
             if (first + lane < cap) keys[cell * cap + first + lane] = key;
-            else atomicMin(&t_cur[q], -1);               // slice full: stop appending, the query is redone
+            else atomicMin(&bound[q].t, -1);               // slice full: stop appending, the query is redone
             atomicAdd(&chist[static_cast<size_t>(q) * 256 + static_cast<uint32_t>(key >> 32)], 1u);
         }
-        if (first / upd != (first + qlen) / upd) lower_bound_of(q, r, t_cur, chist);   // uniform
+        if (first / upd != (first + qlen) / upd) lower_bound_of(q, r, bound, chist);   // uniform
         qlen = 0;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(1024) void ivf_refine_kernel(const float *__restric
 struct IvfScanPlan {
     size_t off_hist, off_thr, off_counter, off_nunits, zero_bytes, off_tie, off_units, off_keys, off_spill, total;
     // single pass: sample histogram, cursors, appended histogram (cleared with the rest); bounds, flags, buffers
-    size_t off_shist, off_fcount, off_chist, off_tcur, off_flags, off_fkeys, off_fsort, off_probed, off_sunits, off_nsunits;
+    size_t off_shist, off_fcount, off_chist, off_bound, off_flags, off_fkeys, off_fsort, off_probed, off_sunits, off_nsunits;
     uint32_t cap, upd, qflush, sortcap;
 };
 
@@ -923,7 +923,7 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
         p.qflush = static_cast<uint32_t>(lim < 1 ? 1 : lim > 64 ? 64 : lim);
     }
     p.sortcap = next_pow2(2 * r) < kSortLdsKeys ? kSortLdsKeys : next_pow2(2 * r);
-    p.off_tcur = off;    off = align_up(off + sizeof(int32_t) * Q, 256);
+    p.off_bound = off;    off = align_up(off + sizeof(Bound) * Q, 256);
     p.off_flags = off;   off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);     // and "any of them"
     p.off_probed = off;  off = align_up(off + sizeof(uint32_t) * Q, 256);
     p.off_sunits = off;  off = align_up(off + sizeof(IvfUnit) * Q * kIvfSampleUnits, 256);
@@ -964,22 +964,22 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, const int32_t 
     uint32_t *shist = reinterpret_cast<uint32_t *>(base + p.off_shist);
     uint32_t *fcount = reinterpret_cast<uint32_t *>(base + p.off_fcount);
     uint32_t *chist = reinterpret_cast<uint32_t *>(base + p.off_chist);
-    int *t_cur = reinterpret_cast<int *>(base + p.off_tcur);
+    Bound *bound = reinterpret_cast<Bound *>(base + p.off_bound);
     uint32_t *flags = reinterpret_cast<uint32_t *>(base + p.off_flags);
     uint64_t *fkeys = reinterpret_cast<uint64_t *>(base + p.off_fkeys);
     uint64_t *fsort = reinterpret_cast<uint64_t *>(base + p.off_fsort);
     // single pass: bounds from a sample of the probed lists, one pass over all their units, exact selection
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_single_kernel<M, CodeT, true>),
                 dim3(nq, (nprobe + kIvfUnitsPerQuery / kIvfSampleStep + 3) / 4), dim3(256),
-                lds_tab + 4 * 256 * 4, codes, sunits, nsunits, qtab, nprobe, r, p.cap, p.upd, p.qflush, t_cur, shist, chist, fkeys);
+                lds_tab + 4 * 256 * 4, codes, sunits, nsunits, qtab, nprobe, r, p.cap, p.upd, p.qflush, bound, shist, chist, fkeys);
     DCPQ_CHECK_LAUNCH("ivf_scan_single_kernel<sample>");
     // As in the flat scan, the bound starts at the bucket where the sample's count reaches what r codes of all the
     // query's probed codes would leave in a sample of that size, plus slack; a query whose bucket holds fewer than
     // r codes after all is flagged by the selection and redone below.
-    rc = launch_sample_threshold(shist, nq, r, 0, t_cur, st, probed);
+    rc = launch_sample_threshold(shist, nq, r, 0, bound, st, probed);
     if (rc) return rc;
     DCPQ_LAUNCH(kStageIvfScan, st, (ivf_scan_single_kernel<M, CodeT, false>), dim3(nq, kIvfUnitsPerQuery / 4), dim3(256),
-                lds_tab + 4 * 64 * 8, codes, units, nunits, qtab, nprobe, r, p.cap, p.upd, p.qflush, t_cur, fcount, chist,
+                lds_tab + 4 * 64 * 8, codes, units, nunits, qtab, nprobe, r, p.cap, p.upd, p.qflush, bound, fcount, chist,
                 fkeys);
     DCPQ_CHECK_LAUNCH("ivf_scan_single_kernel");
     rc = launch_fast_select(fkeys, fcount, chist, nq, r, kFastSlices, p.cap, p.sortcap, 0, fsort, cand_id, cand_qd, flags, st);

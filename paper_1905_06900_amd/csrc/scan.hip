@@ -37,6 +37,62 @@ enum ScanMode { kHist = 0, kTieCount = 1, kCollect = 2 };
 // Queries are addressed by their position p in the active list: query id = qlist ? qlist[p] : p.
 // Workspace arrays (hist, thr, tie, counter, keys) are indexed by p; qtab by the query id.
 // CodeT: uint16_t (the codes as stored) or uint8_t (their low-byte plane).
+// The short step that follows a histogram or a tie count is done by the workgroup that finishes a query tile last
+// (done: one counter per tile, at zero on entry), which saves a launch of its own (4.5 us each on a stream of
+// short kernels):
+//   sample histogram   starting bounds (starting_bound, with want_r, want_n and limit)
+//   histogram          thr = (bucket of the r-th smallest, ids still needed from it)
+//   tie count          counts of the bucket per unit -> quotas per unit, in place
+struct TileEnd {
+    uint32_t *done;         // NULL: nothing follows
+    Bound *bound;           // NULL unless this is the sample histogram
+    uint32_t *thr;
+    uint32_t want_r;
+    uint64_t want_n;
+    bool limit;
+};
+
+// T = bucket holding the r-th smallest qd; need = ids still to take from bucket T (one wavefront).
+__device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, uint32_t *thr)
+{
+    uint32_t c[4], cum[4];
+    wave_prefix_of_buckets(hist, c, cum);
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+        if (cum[z] - c[z] < r && cum[z] >= r) { thr[0] = 4 * lane + z; thr[1] = r - (cum[z] - c[z]); }
+    // fewer than r codes in all (inverted lists only): bucket "256" takes everything
+    if (lane == 63 && cum[3] < r) { thr[0] = 256; thr[1] = 0; }
+}
+
+// Turns per-unit counts of bucket T into per-unit quotas: units are in id order, so unit u may
+// take min(count_u, need - sum of counts before u) ids (its smallest ones).  One workgroup of 256 threads.
+__device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need, uint32_t *part /* LDS [257] */)
+{
+    const int t = threadIdx.x;
+    uint32_t &carry = part[256];
+    __syncthreads();
+    if (t == 0) carry = 0;
+    __syncthreads();
+    for (uint32_t base = 0; base < nunits; base += 256) {
+        const uint32_t u = base + t;
+        const uint32_t c = u < nunits ? row[u] : 0u;
+        part[t] = c;
+        __syncthreads();
+        for (int off = 1; off < 256; off <<= 1) {
+            const uint32_t add = t >= off ? part[t - off] : 0u;
+            __syncthreads();
+            part[t] += add;
+            __syncthreads();
+        }
+        const uint32_t before = carry + part[t] - c;       // exclusive prefix in id order
+        if (u < nunits) row[u] = before >= need ? 0u : min(c, need - before);
+        __syncthreads();
+        if (t == 255) carry += part[255];
+        __syncthreads();
+    }
+}
+
 template <int M, int QT, int MODE, typename CodeT>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t unit_stride,
@@ -46,7 +102,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const uint32_t *__restrict__ thr,   // [nq][2]            (kTieCount, kCollect: read)
     uint32_t *__restrict__ tie,         // [nq][nunits]       (kTieCount: counts out; kCollect: quotas in)
     uint32_t *__restrict__ counter,     // [nq]               (kCollect)
-    uint64_t *__restrict__ keys)        // [nq][r]            (kCollect)
+    uint64_t *__restrict__ keys,        // [nq][r]            (kCollect)
+    const TileEnd end_of)               // what follows when all workgroups of a query tile have finished
 {
     extern __shared__ __align__(16) uint8_t smem[];
     uint8_t *ltab = smem;                                                   // [QT][M][256]
@@ -149,62 +206,48 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
                     if (q < nqt) tie[static_cast<size_t>(q0 + q) * nunits + u] = aux[q];
             }
         }
-    }
-}
 
-// T = bucket holding the r-th smallest qd; need = ids still to take from bucket T.
-__global__ __launch_bounds__(256) void threshold_kernel(const uint32_t *__restrict__ hist, uint32_t r,
-                                                        const uint32_t *__restrict__ nq_dev,
-                                                        uint32_t *__restrict__ thr)
-{
-    __shared__ uint32_t cum[256];
-    const int q = blockIdx.x, b = threadIdx.x;
-    if (nq_dev && q >= static_cast<int>(*nq_dev)) return;
-    cum[b] = hist[static_cast<size_t>(q) * 256 + b];
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {            // inclusive scan (Hillis-Steele)
-        const uint32_t add = b >= off ? cum[b - off] : 0u;
-        __syncthreads();
-        cum[b] += add;
-        __syncthreads();
-    }
-    const uint32_t before = b ? cum[b - 1] : 0u;
-    if (before < r && cum[b] >= r) { thr[2 * q] = b; thr[2 * q + 1] = r - before; }
-    // fewer than r codes in all (inverted lists only): bucket "256" takes everything
-    if (b == 255 && cum[255] < r) { thr[2 * q] = 256; thr[2 * q + 1] = 0; }
-}
-
-// Turns per-unit counts of bucket T into per-unit quotas: units are in id order, so unit u may
-// take min(count_u, need - sum of counts before u) ids (its smallest ones).
-__global__ __launch_bounds__(256) void tie_quota_kernel(uint32_t *__restrict__ tie, uint32_t nunits,
-                                                        const uint32_t *__restrict__ nq_dev,
-                                                        const uint32_t *__restrict__ thr)
-{
-    __shared__ uint32_t part[256];
-    __shared__ uint32_t carry;
-    const int q = blockIdx.x, t = threadIdx.x;
-    if (nq_dev && q >= static_cast<int>(*nq_dev)) return;
-    uint32_t *row = tie + static_cast<size_t>(q) * nunits;
-    const uint32_t need = thr[2 * q + 1];
-    if (t == 0) carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < nunits; base += 256) {
-        const uint32_t u = base + t;
-        const uint32_t c = u < nunits ? row[u] : 0u;
-        part[t] = c;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const uint32_t add = t >= off ? part[t - off] : 0u;
+        if (MODE != kCollect && end_of.done) {
+            // Everything this workgroup has added is in place before its count is.  (Histograms are only added to by
+            // device-scope atomics, whose completion is all there is to wait for; a release fence would write back the
+            // second-level cache once per workgroup: 100 us for the sample of 251 queries.  The tie counts are stores.)
+            if (MODE == kHist) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __syncthreads();
-            part[t] += add;
+            uint32_t *last = reinterpret_cast<uint32_t *>(smem);
+            if (tid == 0) *last = atomicAdd(&end_of.done[q0 / QT], 1u) == nxb - 1;
             __syncthreads();
+            const bool mine = *last != 0;
+            __syncthreads();
+            if (mine) {                                               // uniform
+                if (MODE != kHist) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (MODE == kHist) {
+                    for (int q = wave; q < nqt; q += kScanWaves) {
+                        const uint32_t *h = hist + static_cast<size_t>(q0 + q) * 256;
+                        if (end_of.bound) starting_bound(h, end_of.want_r, end_of.want_n, end_of.limit, end_of.bound + q0 + q);
+                        else exact_threshold(h, r, end_of.thr + 2 * (q0 + q));
+                    }
+                } else {
+                    for (int q = 0; q < nqt; ++q)
+                        tie_quotas(tie + static_cast<size_t>(q0 + q) * nunits, nunits, end_of.thr[2 * (q0 + q) + 1], reinterpret_cast<uint32_t *>(smem));
+                }
+            }
         }
-        const uint32_t before = carry + part[t] - c;       // exclusive prefix in id order
-        if (u < nunits) row[u] = before >= need ? 0u : min(c, need - before);
-        __syncthreads();
-        if (t == 255) carry += part[255];
-        __syncthreads();
     }
+}
+
+// The same steps as kernels of their own, for the inverted-list variant (a wavefront, and a workgroup, per query).
+__global__ __launch_bounds__(256) void threshold_kernel(const uint32_t *__restrict__ hist, int nq, uint32_t r, uint32_t *__restrict__ thr)
+{
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (q < nq) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
+}
+
+__global__ __launch_bounds__(256) void tie_quota_kernel(uint32_t *__restrict__ tie, uint32_t nunits, const uint32_t *__restrict__ thr)
+{
+    __shared__ uint32_t part[257];
+    const int q = blockIdx.x;
+    tie_quotas(tie + static_cast<size_t>(q) * nunits, nunits, thr[2 * q + 1], part);
 }
 
 // Sort the r collected keys of each active query by (qd, id) and split them into the two outputs.
@@ -266,14 +309,14 @@ int launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st)
 
 int launch_threshold(const uint32_t *hist, int nq, uint32_t r, uint32_t *thr, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageSelect, st, threshold_kernel, dim3(nq), dim3(256), 0, hist, r, nullptr, thr);
+    DCPQ_LAUNCH(kStageSelect, st, threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, hist, nq, r, thr);
     DCPQ_CHECK_LAUNCH("threshold_kernel");
     return DCPQ_OK;
 }
 
 int launch_tie_quota(uint32_t *tie, uint32_t nunits, int nq, const uint32_t *thr, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageSelect, st, tie_quota_kernel, dim3(nq), dim3(256), 0, tie, nunits, nullptr, thr);
+    DCPQ_LAUNCH(kStageSelect, st, tie_quota_kernel, dim3(nq), dim3(256), 0, tie, nunits, thr);
     DCPQ_CHECK_LAUNCH("tie_quota_kernel");
     return DCPQ_OK;
 }
@@ -325,12 +368,7 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
     p.off_hist = off;    off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
     p.off_thr = off;     off = align_up(off + sizeof(uint32_t) * 2 * Q, 256);
     p.off_counter = off; off = align_up(off + sizeof(uint32_t) * Q, 256);
-    p.zero_bytes = off;
-    p.off_tie = off;     off = align_up(off + sizeof(uint32_t) * Q * p.nunits, 256);
-    p.off_keys = off;    off = align_up(off + sizeof(uint64_t) * Q * r, 256);
-    p.off_spill = off;   // sort area in global memory, only when r keys do not fit the LDS sort
-    if (np2 > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * np2, 256);
-
+    p.off_done = off;    off = align_up(off + sizeof(uint32_t) * 3 * qtiles, 256);
     p.fqt = static_cast<uint32_t>(mode == DCPQ_SCAN_THREE_PASS ? 0 : fast_query_tile(m, nq, mode));
     p.fast = p.fqt != 0;
     if (p.fast) {
@@ -352,6 +390,20 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
         p.codes_per_block = static_cast<uint32_t>(cpb);
         p.fblocks = static_cast<uint32_t>((rest + cpb - 1) / cpb);
         p.slices = p.fblocks < static_cast<uint32_t>(kFastSlices) ? p.fblocks : kFastSlices;
+        p.off_fzero = off;
+        p.off_fcount = off;  off = align_up(off + sizeof(uint32_t) * Q * p.slices, 256);
+        p.off_chist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
+        p.off_shist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
+        p.fzero_bytes = off - p.off_fzero;
+        p.off_nflag = off;   off = align_up(off + 256, 256);
+    }
+    p.zero_bytes = off;
+    p.off_tie = off;     off = align_up(off + sizeof(uint32_t) * Q * p.nunits, 256);
+    p.off_keys = off;    off = align_up(off + sizeof(uint64_t) * Q * r, 256);
+    p.off_spill = off;   // sort area in global memory, only when r keys do not fit the LDS sort
+    if (np2 > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * np2, 256);
+
+    if (p.fast) {
         {
             const uint64_t share = 32ull * r / p.slices;         // 32 r per query in all: twice the even share
             p.cap = static_cast<uint32_t>(share < 1024 ? 1024 : share);
@@ -412,13 +464,7 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
             p.pilot_runs = (p.s_nunits + pb - 1) / pb;
             p.pilot_blocks = (p.s_nunits + p.pilot_runs - 1) / p.pilot_runs;
         }
-        p.off_fzero = off;
-        p.off_fcount = off;  off = align_up(off + sizeof(uint32_t) * Q * p.slices, 256);
-        p.off_chist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
-        p.off_shist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
-        p.off_nflag = off;   off = align_up(off + 256, 256);
-        p.fzero_bytes = off - p.off_fzero;
-        p.off_tcur = off;    off = align_up(off + sizeof(int32_t) * Q, 256);
+        p.off_bound = off;   off = align_up(off + sizeof(Bound) * Q, 256);
         p.off_flags = off;   off = align_up(off + sizeof(uint32_t) * Q, 256);
         p.off_qlist = off;   off = align_up(off + sizeof(int32_t) * Q, 256);
         p.off_qsw = off;     off = align_up(off + static_cast<size_t>(p.ntiles) * fast_table_bytes(m, p.fqt), 256);
@@ -434,7 +480,7 @@ template <int M, int MODE, typename CodeT>
 static void launch_scan_pass(int stage, const CodeT *codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
                              uint64_t stride, const uint8_t *qtab, int nq, const int *qlist, const uint32_t *nq_dev,
                              uint32_t r, uint32_t *hist, const uint32_t *thr, uint32_t *tie, uint32_t *counter,
-                             uint64_t *keys, bool few_expected, hipStream_t st)
+                             uint64_t *keys, const TileEnd &end_of, bool few_expected, hipStream_t st)
 {
     constexpr int QT = scan_qt(M);
     const uint64_t nxb = (nunits + kScanWaves - 1) / kScanWaves;
@@ -444,10 +490,11 @@ static void launch_scan_pass(int stage, const CodeT *codes, uint64_t n_codes, ui
     const uint32_t grid = static_cast<uint32_t>(items < most ? (items ? items : 1) : most);
     const size_t lds = static_cast<size_t>(QT) * M * 256 + (MODE == kHist ? QT * 256 * 4 : 0);
     DCPQ_LAUNCH(stage, st, (scan_kernel<M, QT, MODE, CodeT>), dim3(grid), dim3(kScanThreads), lds, codes, n_codes, unit,
-                nunits, stride, qtab, nq, qlist, nq_dev, r, hist, thr, tie, counter, keys);
+                nunits, stride, qtab, nq, qlist, nq_dev, r, hist, thr, tie, counter, keys, end_of);
 }
 
-// The three passes for the queries qlist[0 .. *nq_dev) (or all nq when qlist is null).
+// The three passes for the queries qlist[0 .. *nq_dev) (or all nq when qlist is null).  The counters (zero_bytes of the
+// workspace) are at zero.
 template <int M, typename CodeT>
 static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, const int *qlist,
                              const uint32_t *nq_dev, uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base,
@@ -461,23 +508,21 @@ static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t
     uint64_t *keys = reinterpret_cast<uint64_t *>(base + p.off_keys);
     uint64_t *sorted = reinterpret_cast<uint64_t *>(base + p.off_spill);
     const bool few = qlist != nullptr;
+    uint32_t *done = reinterpret_cast<uint32_t *>(base + p.off_done);
+    const size_t qtiles = (static_cast<size_t>(nq) + p.qt - 1) / p.qt;
+    TileEnd after_hist{}, after_ties{};
+    after_hist.done = done + qtiles;
+    after_ties.done = done + 2 * qtiles;
+    after_hist.thr = after_ties.thr = thr;
 
-    const size_t nwords = p.zero_bytes / sizeof(uint32_t);
-    DCPQ_LAUNCH(kStageMisc, st, zero_words_kernel, dim3((nwords + 255) / 256), dim3(256), 0,
-                reinterpret_cast<uint32_t *>(base), nwords);
-    DCPQ_CHECK_LAUNCH("zero_words_kernel");
     launch_scan_pass<M, kHist>(kStageScanHist, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist, nq_dev, r,
-                               hist, thr, tie, counter, keys, few, st);
+                               hist, thr, tie, counter, keys, after_hist, few, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<hist>");
-    DCPQ_LAUNCH(kStageSelect, st, threshold_kernel, dim3(nq), dim3(256), 0, hist, r, nq_dev, thr);
-    DCPQ_CHECK_LAUNCH("threshold_kernel");
     launch_scan_pass<M, kTieCount>(kStageScanTieCount, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist,
-                                   nq_dev, r, hist, thr, tie, counter, keys, few, st);
+                                   nq_dev, r, hist, thr, tie, counter, keys, after_ties, few, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<tiecount>");
-    DCPQ_LAUNCH(kStageSelect, st, tie_quota_kernel, dim3(nq), dim3(256), 0, tie, p.nunits, nq_dev, thr);
-    DCPQ_CHECK_LAUNCH("tie_quota_kernel");
     launch_scan_pass<M, kCollect>(kStageScanCollect, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist,
-                                  nq_dev, r, hist, thr, tie, counter, keys, few, st);
+                                  nq_dev, r, hist, thr, tie, counter, keys, TileEnd{}, few, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<collect>");
     const uint32_t np2 = next_pow2(r);
     DCPQ_LAUNCH(kStageSelect, st, sort_candidates_kernel, dim3(nq), dim3(1024), spill ? 0 : sizeof(uint64_t) * np2,
@@ -488,47 +533,53 @@ static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t
 
 template <int M, typename CodeT>
 static int launch_sample_hist_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,
-                                uint32_t *shist, const ScanPlan &p, hipStream_t st)
+                                uint32_t *shist, const ScanPlan &p, const TileEnd &end_of, hipStream_t st)
 {
     // (with a pilot pass: runs 0, kPilotEvery, 2 kPilotEvery, ... of the sample)
     launch_scan_pass<M, kHist>(kStageScanHist, codes, n_codes, p.s_unit, p.s1_nunits, p.pilot ? p.s_stride * kPilotEvery : p.s_stride,
-                               qtab, nq, nullptr, nullptr, r, shist, nullptr, nullptr, nullptr, nullptr, false, st);
+                               qtab, nq, nullptr, nullptr, r, shist, nullptr, nullptr, nullptr, nullptr, end_of, false, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<sample hist>");
     return DCPQ_OK;
 }
 
+// want_r, want_n, limit: rank wanted, size of the array the sample stands for, whether ties may be limited by id (see starting_bound)
 template <typename CodeT>
 int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                       uint32_t *shist, const ScanPlan &p, hipStream_t st)
+                       uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit, Bound *bound,
+                       uint32_t *done, hipStream_t st)
 {
+    TileEnd e{};
+    e.done = done;
+    e.bound = bound;
+    e.limit = limit;
+    e.want_r = want_r;
+    e.want_n = want_n;
     switch (m) {
-        case 4: return launch_sample_hist_m<4, CodeT>(codes, n_codes, qtab, nq, r, shist, p, st);
-        case 8: return launch_sample_hist_m<8, CodeT>(codes, n_codes, qtab, nq, r, shist, p, st);
-        case 16: return launch_sample_hist_m<16, CodeT>(codes, n_codes, qtab, nq, r, shist, p, st);
-        case 32: return launch_sample_hist_m<32, CodeT>(codes, n_codes, qtab, nq, r, shist, p, st);
+        case 4: return launch_sample_hist_m<4, CodeT>(codes, n_codes, qtab, nq, r, shist, p, e, st);
+        case 8: return launch_sample_hist_m<8, CodeT>(codes, n_codes, qtab, nq, r, shist, p, e, st);
+        case 16: return launch_sample_hist_m<16, CodeT>(codes, n_codes, qtab, nq, r, shist, p, e, st);
+        case 32: return launch_sample_hist_m<32, CodeT>(codes, n_codes, qtab, nq, r, shist, p, e, st);
         default: return fail(DCPQ_EUNSUPPORTED, "sample histogram: m=%d not supported", m);
     }
 }
 
 template int launch_sample_hist<uint16_t>(const uint16_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *,
-                                          const ScanPlan &, hipStream_t);
+                                          const ScanPlan &, uint32_t, uint64_t, bool, Bound *, uint32_t *, hipStream_t);
 template int launch_sample_hist<uint8_t>(const uint8_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *,
-                                         const ScanPlan &, hipStream_t);
+                                         const ScanPlan &, uint32_t, uint64_t, bool, Bound *, uint32_t *, hipStream_t);
 
 template <int M, typename CodeT>
 static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,
-                         uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, hipStream_t st)
+                         uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
 {
     const ScanPlan p = plan_scan(n_codes, M, nq, r, mode);
     uint8_t *base = static_cast<uint8_t *>(ws);
+    int rc = DCPQ_OK;
+    if (!cleared) rc = launch_zero_words(reinterpret_cast<uint32_t *>(base), p.zero_bytes / sizeof(uint32_t), st);
+    if (rc) return rc;
     if (!p.fast)
         return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, nullptr, nullptr, r, cand_id, cand_qd, base, p, st);
-
-    const size_t nwords = p.fzero_bytes / sizeof(uint32_t);
-    DCPQ_LAUNCH(kStageMisc, st, zero_words_kernel, dim3((nwords + 255) / 256), dim3(256), 0,
-                reinterpret_cast<uint32_t *>(base + p.off_fzero), nwords);
-    DCPQ_CHECK_LAUNCH("zero_words_kernel");
-    int rc = launch_scan_fast(codes, n_codes, M, qtab, nq, r, cand_id, cand_qd, base, p, st);
+    rc = launch_scan_fast(codes, n_codes, M, qtab, nq, r, cand_id, cand_qd, base, p, st);
     if (rc) return rc;
     // queries the single pass could not finish (their count is known on the device only)
     return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, reinterpret_cast<const int *>(base + p.off_qlist),
@@ -538,30 +589,32 @@ static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
 
 template <typename CodeT>
 static int launch_scan_any(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                           uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, hipStream_t st)
+                           uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
 {
     if (nq == 0) return DCPQ_OK;
     switch (m) {
-        case 1: return launch_scan_m<1, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
-        case 2: return launch_scan_m<2, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
-        case 4: return launch_scan_m<4, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
-        case 8: return launch_scan_m<8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
-        case 16: return launch_scan_m<16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
-        case 32: return launch_scan_m<32, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
+        case 1: return launch_scan_m<1, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+        case 2: return launch_scan_m<2, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+        case 4: return launch_scan_m<4, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+        case 8: return launch_scan_m<8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+        case 16: return launch_scan_m<16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+        case 32: return launch_scan_m<32, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
         default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
     }
 }
 
+size_t scan_clear_words(uint64_t n_codes, int m, int nq, uint32_t r, int mode) { return plan_scan(n_codes, m, nq, r, mode).zero_bytes / sizeof(uint32_t); }
+
 int launch_scan(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, hipStream_t st)
+                uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
 {
-    return launch_scan_any(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
+    return launch_scan_any(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
 }
 
 int launch_scan(const uint8_t *plane, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, hipStream_t st)
+                uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
 {
-    return launch_scan_any(plane, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, mode, st);
+    return launch_scan_any(plane, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
 }
 
 }  // namespace dcpq
@@ -635,7 +688,7 @@ static int scan_checked(const CodeT *codes, uint64_t n_codes, int m, const uint8
     const size_t need = dcpq_scan_workspace_bytes(n_codes, m, nq, r);
     if (workspace_bytes < need)
         return fail(DCPQ_EWORKSPACE, "scan_candidates: workspace %zu < %zu bytes", workspace_bytes, need);
-    return launch_scan(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, workspace, mode, as_stream(stream));
+    return launch_scan(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, workspace, mode, false, as_stream(stream));
 }
 
 extern "C" int dcpq_scan_candidates(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,

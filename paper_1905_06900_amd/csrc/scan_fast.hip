@@ -63,6 +63,8 @@ namespace dcpq {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 
+constexpr uint32_t kLimited = 1u << 31;     // flag in `upd`: queries may want only the smaller ids of their starting bucket
+
 template <int M, int QT, int WAVES>
 struct FastCfg {
     static constexpr int NQB = QT / 16;             // 16-query blocks per table row
@@ -147,37 +149,15 @@ __global__ __launch_bounds__(256) void swizzle_tables_kernel(const uint8_t *__re
     *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Starting bucket bound of every query from the histogram of a sample of S of the n codes.
-// The bucket of the sample's r-th smallest qd is a bound that cannot fail (the sample is part of the
-// array), but it lets r / S of all codes through.  The array's r-th smallest qd is about the sample's
-// (r S / n)-th smallest, so the bound starts at the bucket where the sample's cumulative count reaches
-// e + 5 sqrt(e) + 5 with e = r S / n (five standard deviations of the count above its mean: a query in
-// ten million starts too low), or r if that is smaller.  Should that bucket hold fewer than r codes of the whole array after all, the
-// selection sees fewer than r appended candidates and has the query redone by the three-pass path.
-__global__ __launch_bounds__(256) void sample_threshold_kernel(const uint32_t *__restrict__ shist, uint32_t r,
+// Starting bounds from sample histograms, a wavefront per query (see starting_bound).
+__global__ __launch_bounds__(256) void sample_threshold_kernel(const uint32_t *__restrict__ shist, int nq, uint32_t r,
                                                                uint64_t n_codes, const uint32_t *__restrict__ n_each,
-                                                               int *__restrict__ t_cur)
+                                                               Bound *__restrict__ bound)
 {
-    __shared__ uint32_t cum[256];
-    const int q = blockIdx.x, b = threadIdx.x;
-    cum[b] = shist[static_cast<size_t>(q) * 256 + b];
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t add = b >= off ? cum[b - off] : 0u;
-        __syncthreads();
-        cum[b] += add;
-        __syncthreads();
-    }
-    uint32_t rs = r;
-    if (n_each) n_codes = n_each[q];                      // every query scans its own codes (probed lists)
-    if (n_codes) {                                        // 0: the sample's own r-th smallest
-        const float e = static_cast<float>(r) * static_cast<float>(cum[255]) / static_cast<float>(n_codes);
-        const float want = e + 5.0f * sqrtf(e) + 5.0f;
-        if (want < static_cast<float>(r)) rs = static_cast<uint32_t>(want) + 1u;
-    }
-    const uint32_t before = b ? cum[b - 1] : 0u;
-    if (before < rs && cum[b] >= rs) t_cur[q] = b;
-    if (b == 255 && cum[255] < rs) t_cur[q] = 255;
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (q >= nq) return;
+    // (n_each: every query scans its own codes, the probed lists)
+    starting_bound(shist + static_cast<size_t>(q) * 256, r, n_each ? n_each[q] : n_codes, false, bound + q);
 }
 
 // Low bytes of the M sub-codes of one code, reordered by residue class: byte (j & 3) * CLS + (j >> 2).
@@ -213,24 +193,25 @@ __device__ inline void transposed_low_bytes(const uint32_t (&w)[M * sizeof(CodeT
 // bound is to be recomputed, else -1.  Kept out of line: it is the rare path and would otherwise be
 // replicated at every call site.
 __device__ __noinline__ int append_candidate(uint64_t rec, int q0, uint32_t slice, uint32_t nslices, uint32_t cap, uint32_t upd,
-                                             int *t_cur, uint32_t *count, uint32_t *chist, uint64_t *keys)
+                                             Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *keys)
 {
     const uint32_t q = q0 + static_cast<uint32_t>(rec >> 40);
     const uint32_t qd = static_cast<uint32_t>(rec >> 32) & 255u;
+    if ((upd & kLimited) && qd == bound[q].t0 && static_cast<uint32_t>(rec) > bound[q].last) return -1;
     const size_t cell = static_cast<size_t>(q) * nslices + slice;
     const uint32_t pos = atomicAdd(&count[cell], 1u);
     if (pos < cap) keys[cell * cap + pos] = rec & 0xFFFFFFFFFFull;
-    else if (cap) atomicMin(&t_cur[q], -1);            // slice full: stop appending, query is redone
+    else if (cap) atomicMin(&bound[q].t, -1);            // slice full: stop appending, query is redone
     // (cap = 0: the pilot pass, which only counts)
     atomicAdd(&chist[static_cast<size_t>(q) * 256 + qd], 1u);
-    return (pos + 1) % upd == 0 ? static_cast<int>(q) : -1;
+    return (pos + 1) % (upd & ~kLimited) == 0 ? static_cast<int>(q) : -1;
 }
 
 template <int M, int QT, int WAVES, typename CodeT>
 __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     const CodeT *__restrict__ codes, uint64_t code_end, uint64_t block_stride, uint32_t block_groups, uint32_t total_groups,
     uint32_t gshift, uint32_t gstride, const uint8_t *__restrict__ qsw, int nq, uint32_t r, uint32_t nslices, uint32_t cap,
-    uint32_t upd, uint32_t qflush, int *t_cur, uint32_t *count, uint32_t *chist, uint64_t *__restrict__ keys)
+    uint32_t upd, uint32_t qflush, Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *__restrict__ keys)
 {
     // The codes of workgroup y (blockIdx.y) are 64-code groups y * block_groups ... (block_groups of them, fewer
     // at the end: total_groups in all); group g of the workgroup starts at code
@@ -257,8 +238,12 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     // absent query has the bound -1 that nothing reaches.
     auto start_value = [&](int q) {
         int t = -1;
-        if (q < nq) t = __hip_atomic_load(&t_cur[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cap == 0 && t >= 255) t = -1;
+        if (q < nq) {
+            t = __hip_atomic_load(&bound[q].t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (cap == 0 && t >= 255) t = -1;
+            // none of this workgroup's codes is wanted from the starting bucket?
+            else if ((upd & kLimited) && static_cast<uint32_t>(t) == bound[q].t0 && static_cast<uint64_t>(blockIdx.y) * block_stride > bound[q].last) --t;
+        }
         return t >= 255 ? static_cast<int>(128u * M - 0x80000000u) : static_cast<int>(128u * M - static_cast<uint32_t>(t) - 1u);
     };
     {
@@ -339,13 +324,13 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         int qu = -1;
-        if (static_cast<uint32_t>(lane) < qlen) qu = append_candidate(wq[lane], q0, slice, nslices, cap, upd, t_cur, count, chist, keys);
+        if (static_cast<uint32_t>(lane) < qlen) qu = append_candidate(wq[lane], q0, slice, nslices, cap, upd, bound, count, chist, keys);
         // the queries whose bound is due, one after the other, each by the whole wavefront
         uint64_t due = __builtin_amdgcn_ballot_w64(qu >= 0);
         while (due) {                                    // uniform
             const int src = __builtin_ctzll(due);
             due &= due - 1;
-            lower_bound_of(__shfl(qu, src), r, t_cur, chist);
+            lower_bound_of(__shfl(qu, src), r, bound, chist);
         }
         qlen = 0;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -634,8 +619,14 @@ __global__ __launch_bounds__(1024) void fast_select_kernel(const uint64_t *__res
                                                           uint32_t id_mul, uint64_t *__restrict__ spill,
                                                           uint32_t *__restrict__ cand_id,
                                                           uint8_t *__restrict__ cand_qd,
-                                                          uint32_t *__restrict__ flags)
+                                                          uint32_t *__restrict__ flags, int *__restrict__ qlist,
+                                                          uint32_t *__restrict__ nflag)
 {
+    // flagged queries are also listed, in any order, where the caller wants a list
+    auto flag_query = [&](int q) {
+        flags[q] = 1;
+        if (qlist) qlist[atomicAdd(nflag, 1u)] = q;
+    };
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ uint32_t cum[256];                // inclusive prefix of the bucket counts
     __shared__ uint32_t wsum[16];
@@ -649,7 +640,7 @@ __global__ __launch_bounds__(1024) void fast_select_kernel(const uint64_t *__res
         n += c;
     }
     if (over || n < r) {                        // a slice overflowed, or the starting bound was too low after all
-        if (tid == 0) flags[q] = 1;
+        if (tid == 0) flag_query(q);
         return;
     }
     if (tid < 256) cum[tid] = chist[static_cast<size_t>(q) * 256 + tid];
@@ -758,7 +749,7 @@ __global__ __launch_bounds__(1024) void fast_select_kernel(const uint64_t *__res
         __syncthreads();
     }
     if (keep > sortcap) {                        // tie bucket does not fit the sort area
-        if (tid == 0) flags[q] = 1;
+        if (tid == 0) flag_query(q);
         return;
     }
     uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(q) * sortcap;
@@ -786,22 +777,6 @@ __global__ __launch_bounds__(1024) void fast_select_kernel(const uint64_t *__res
     if (tid == 0) flags[q] = 0;
 }
 
-// Ordered list of the flagged queries and their number (one wavefront).
-__global__ __launch_bounds__(64) void collect_flags_kernel(const uint32_t *__restrict__ flags, int nq,
-                                                           int *__restrict__ qlist, uint32_t *__restrict__ nflag)
-{
-    const int lane = threadIdx.x;
-    uint32_t total = 0;
-    for (int base = 0; base < nq; base += 64) {
-        const int q = base + lane;
-        const bool f = q < nq && flags[q] != 0;
-        const uint64_t mask = __ballot(f);
-        if (f) qlist[total + __popcll(mask & ((1ull << lane) - 1ull))] = q;
-        total += __popcll(mask);
-    }
-    if (lane == 0) *nflag = total;
-}
-
 // ---- host side ------------------------------------------------------------------------------
 
 template <int M, int QT, int WAVES, typename CodeT>
@@ -810,12 +785,13 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
 {
     using C = FastCfg<M, QT, WAVES>;
     uint8_t *qsw = base + p.off_qsw;
-    int *t_cur = reinterpret_cast<int *>(base + p.off_tcur);
+    Bound *bound = reinterpret_cast<Bound *>(base + p.off_bound);
     uint32_t *fcount = reinterpret_cast<uint32_t *>(base + p.off_fcount);
     uint32_t *chist = reinterpret_cast<uint32_t *>(base + p.off_chist);
     uint32_t *shist = reinterpret_cast<uint32_t *>(base + p.off_shist);
     uint64_t *fkeys = reinterpret_cast<uint64_t *>(base + p.off_fkeys);
     uint64_t *fsort = reinterpret_cast<uint64_t *>(base + p.off_fsort);
+    uint32_t *done = reinterpret_cast<uint32_t *>(base + p.off_done);
     uint32_t *flags = reinterpret_cast<uint32_t *>(base + p.off_flags);
     int *qlist = reinterpret_cast<int *>(base + p.off_qlist);
     uint32_t *nflag = reinterpret_cast<uint32_t *>(base + p.off_nflag);
@@ -831,57 +807,50 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     DCPQ_LAUNCH(kStageMisc, st, (swizzle_tables_kernel<M, QT>), dim3((C::VJ * 256 * C::NQB + 255) / 256, p.ntiles),
                 dim3(256), 0, qtab, nq, qsw);
     DCPQ_CHECK_LAUNCH("swizzle_tables_kernel");
-    // sample histogram -> starting bounds
-    int rc = launch_sample_hist(codes, n_codes, M, qtab, nq, r, shist, p, st);
+    // Sample histogram -> starting bounds.  With a pilot pass the histogram covered one run in kPilotEvery of the sample.
+    // It gives a bound for the pilot pass: the bucket below which the whole sample (taken as the array, its wanted rank
+    // pilot_r as r) should hold pilot_r codes with the usual slack.
+    int rc = launch_sample_hist(codes, n_codes, M, qtab, nq, r, shist, p, p.pilot ? p.pilot_r : r, p.pilot ? p.s_count : n_codes,
+                                !p.pilot, bound, done, st);
     if (rc) return rc;
     if (p.pilot) {
         if (p.s_unit != 256) return fail(DCPQ_EINVAL, "single-pass scan: the pilot pass reads runs of 256 codes");
-        // The histogram covered one run in kPilotEvery of the sample.  It gives a bound for the pilot pass: the
-        // bucket below which the whole sample (taken as the array, its wanted rank pilot_r as r) should hold
-        // pilot_r codes with the usual slack.  The pilot pass counts every sample code at or below that bound
-        // exactly, and the starting bound of the scan is the bucket where those counts reach pilot_r -- the bucket
-        // a histogram of the whole sample would have given (255, and with it the redo path, if the counts never
-        // get there).
-        rc = launch_sample_threshold(shist, nq, p.pilot_r, p.s_count, t_cur, st);
-        if (rc) return rc;
+        // The pilot pass counts every sample code at or below that bound exactly, and the starting bound of the scan
+        // is the bucket where those counts reach pilot_r -- the bucket a histogram of the whole sample would have given
+        // (255, and with it the redo path, if the counts never get there).
         DCPQ_LAUNCH(kStageScanHist, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.pilot_blocks), dim3(WAVES * 64),
                     C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.pilot_runs) * p.s_stride, p.pilot_runs * (p.s_unit / 64),
                     p.s_nunits * (p.s_unit / 64), 2u, static_cast<uint32_t>(p.s_stride), qsw, nq, p.pilot_r, p.slices, 0u, 16u, 4u,
-                    t_cur, fcount, chist, fkeys);
+                    bound, fcount, chist, fkeys);
         DCPQ_CHECK_LAUNCH("scan_fast_kernel<pilot>");
-        rc = launch_sample_threshold(chist, nq, p.pilot_r, 0, t_cur, st);      // 0: the counted codes' own pilot_r-th smallest
+        rc = launch_sample_threshold(chist, nq, p.pilot_r, 0, bound, st);      // 0: the counted codes' own pilot_r-th smallest
         if (rc) return rc;
         rc = launch_zero_words(reinterpret_cast<uint32_t *>(base + p.off_fzero), p.fzero_bytes / sizeof(uint32_t), st);
-        if (rc) return rc;
-    } else {
-        rc = launch_sample_threshold(shist, nq, r, n_codes, t_cur, st);
         if (rc) return rc;
     }
     // the scan: one contiguous stretch of codes per workgroup
     DCPQ_LAUNCH(kStageScanFast, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.fblocks), dim3(WAVES * 64),
                 C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.codes_per_block), p.codes_per_block / 64,
-                static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd, p.qflush, t_cur, fcount,
-                chist, fkeys);
+                static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd | (p.pilot ? 0u : kLimited), p.qflush, bound,
+                fcount, chist, fkeys);
     DCPQ_CHECK_LAUNCH("scan_fast_kernel");
-    // exact selection + list of queries to redo
-    rc = launch_fast_select(fkeys, fcount, chist, nq, r, p.slices, p.cap, p.sortcap, n_codes, fsort, cand_id, cand_qd, flags, st);
+    // exact selection, and the list of queries to redo
+    rc = launch_fast_select(fkeys, fcount, chist, nq, r, p.slices, p.cap, p.sortcap, n_codes, fsort, cand_id, cand_qd, flags, st, qlist, nflag);
     if (rc) return rc;
-    DCPQ_LAUNCH(kStageSelect, st, collect_flags_kernel, dim3(1), dim3(64), 0, flags, nq, qlist, nflag);
-    DCPQ_CHECK_LAUNCH("collect_flags_kernel");
     return DCPQ_OK;
 }
 
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, int *t_cur, hipStream_t st,
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st,
                             const uint32_t *n_each)
 {
-    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3(nq), dim3(256), 0, shist, r, n_codes, n_each, t_cur);
+    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, n_each, bound);
     DCPQ_CHECK_LAUNCH("sample_threshold_kernel");
     return DCPQ_OK;
 }
 
 int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32_t *chist, int nq, uint32_t r,
                        uint32_t nslices, uint32_t cap, uint32_t sortcap, uint64_t n_ids, uint64_t *spill, uint32_t *cand_id,
-                       uint8_t *cand_qd, uint32_t *flags, hipStream_t st)
+                       uint8_t *cand_qd, uint32_t *flags, hipStream_t st, int *qlist, uint32_t *nflag)
 {
     {
         const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(&fast_select_kernel), static_cast<int>(kSelectLdsMost));
@@ -896,7 +865,7 @@ int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32
     const uint64_t mul64 = (2048ull << 32) / n;
     const uint32_t id_mul = mul64 > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(mul64);
     DCPQ_LAUNCH(kStageSelect, st, fast_select_kernel, dim3(nq), dim3(1024), lds,
-                keys, count, chist, r, nslices, cap, sortcap, use_lds, rankcap, id_mul, spill, cand_id, cand_qd, flags);
+                keys, count, chist, r, nslices, cap, sortcap, use_lds, rankcap, id_mul, spill, cand_id, cand_qd, flags, qlist, nflag);
     DCPQ_CHECK_LAUNCH("fast_select_kernel");
     return DCPQ_OK;
 }

@@ -23,6 +23,13 @@ constexpr int kFastSlices = 16;      // at most; fewer when there are fewer work
 
 constexpr uint32_t kPilotEvery = 16;
 
+// Running bucket bound of a query in the single-pass scans (one 16-byte record per query).
+struct __attribute__((aligned(16))) Bound {
+    int t;              // codes above this bucket are not wanted (only ever lowered, by atomicMin)
+    uint32_t t0, last;  // of the starting bucket t0 only the ids up to `last` are wanted
+    uint32_t pad;
+};
+
 struct ScanPlan {
     // three-pass path
     uint32_t unit;        // codes scanned by one wavefront
@@ -31,7 +38,9 @@ struct ScanPlan {
     size_t off_hist;      // uint32 [nq][256]
     size_t off_thr;       // uint32 [nq][2]   (threshold bucket, ids still needed from it)
     size_t off_counter;   // uint32 [nq]
-    size_t zero_bytes;    // the three arrays above are contiguous from offset 0 and cleared together
+    size_t off_done;      // uint32 [3][ceil(nq / qt)]  finished workgroups of a query tile (sample, redo histogram, redo tie count)
+    size_t zero_bytes;    // everything that a call expects at zero lies together from offset 0: the four arrays
+                          // above and, for the single-pass path, fcount, chist, shist and nflag
     size_t off_tie;       // uint32 [nq][nunits]
     size_t off_keys;      // uint64 [nq][r]
     size_t off_spill;     // uint64 [nq][next_pow2(r)], only when r keys do not fit the LDS sort
@@ -56,12 +65,12 @@ struct ScanPlan {
     uint32_t pilot_r;             // rank wanted within the sample: what r codes of the array leave in it, plus slack
     uint32_t pilot_blocks;        // workgroups per tile of the pilot pass ...
     uint32_t pilot_runs;          // ... and sample runs per workgroup
-    size_t off_fzero, fzero_bytes;   // fcount, chist, shist, nflag: cleared together
+    size_t off_fzero, fzero_bytes;   // fcount, chist, shist: cleared once more after a pilot pass
     size_t off_fcount;    // uint32 [nq][slices]
     size_t off_chist;     // uint32 [nq][256]
     size_t off_shist;     // uint32 [nq][256]
     size_t off_nflag;     // uint32 [1] (+ padding)
-    size_t off_tcur;      // int32 [nq]
+    size_t off_bound;     // Bound [nq]
     size_t off_flags;     // uint32 [nq]
     size_t off_qlist;     // int32 [nq]
     size_t off_qsw;       // uint8 [ntiles][fast_table_bytes(m, fqt)]
@@ -77,7 +86,8 @@ size_t fast_table_bytes(int m, int qt);
 // CodeT: uint16_t (the codes as stored) or uint8_t (their low-byte plane); both are instantiated.
 template <typename CodeT>
 int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                       uint32_t r, uint32_t *shist, const ScanPlan &p, hipStream_t st);
+                       uint32_t r, uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit,
+                       Bound *bound, uint32_t *done, hipStream_t st);
 template <typename CodeT>
 int launch_scan_fast(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
                      uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p,
@@ -86,12 +96,12 @@ int launch_scan_fast(const CodeT *codes, uint64_t n_codes, int m, const uint8_t 
 // Steps of the single-pass selection that the inverted-list variant reuses.
 // n_codes: size of the array the sample was drawn from (the sample's own size is the histogram's total)
 // n_each (optional): the number of codes each query scans, where it is not the same n_codes for all of them
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, int *t_cur, hipStream_t st,
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st,
                             const uint32_t *n_each = nullptr);
-// n_ids: the ids are below this (0 = unknown)
+// n_ids: the ids are below this (0 = unknown); qlist, nflag (optional): the flagged queries, in any order, and their number
 int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32_t *chist, int nq, uint32_t r,
                        uint32_t nslices, uint32_t cap, uint32_t sortcap, uint64_t n_ids, uint64_t *spill, uint32_t *cand_id,
-                       uint8_t *cand_qd, uint32_t *flags, hipStream_t st);
+                       uint8_t *cand_qd, uint32_t *flags, hipStream_t st, int *qlist = nullptr, uint32_t *nflag = nullptr);
 
 // Small shared steps of the three-pass selection, reused by the inverted-list variant.
 int launch_zero_words(uint32_t *p, size_t nwords, hipStream_t st);
@@ -132,11 +142,68 @@ __device__ inline void load_low_bytes(const uint16_t *__restrict__ codes, uint64
     }
 }
 
+// Inclusive prefix sums of 256 bucket counts over a wavefront, lane l owning buckets 4l .. 4l + 3: c becomes
+// the counts, cum the inclusive prefixes.  The counts may just have been added by other workgroups' atomics.
+__device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c)[4], uint32_t (&cum)[4])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int z = 0; z < 4; ++z) c[z] = __hip_atomic_load(&hist[4 * lane + z], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t mine = c[0] + c[1] + c[2] + c[3];
+    uint32_t incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t other = __shfl(incl, lane >= d ? lane - d : lane);
+        if (lane >= d) incl += other;
+    }
+    uint32_t run = incl - mine;
+#pragma unroll
+    for (int z = 0; z < 4; ++z) { run += c[z]; cum[z] = run; }
+}
+
+// Starting bucket bound of a query from the histogram of a sample of S of the n codes, by one wavefront.
+// The bucket of the sample's r-th smallest qd is a bound that cannot fail (the sample is part of the
+// array), but it lets r / S of all codes through.  The array's r-th smallest qd is about the sample's
+// (r S / n)-th smallest, so the bound starts at the bucket where the sample's cumulative count reaches
+// e + 5 sqrt(e) + 5 with e = r S / n (five standard deviations of the count above its mean: a query in
+// ten million starts too low), or r if that is smaller.  Should that bucket hold fewer than r codes of the whole array after all, the
+// selection sees fewer than r appended candidates and has the query redone by the three-pass path.
+// Where so many codes tie in that bucket that more than 16 r would be appended, only the codes with ids up to
+// twice the share of the bucket that is wanted are (`limit`; ties are broken by id, and the sample's runs are spread
+// over the array).
+__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, bool limit, Bound *bound)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t c[4], cum[4];
+    wave_prefix_of_buckets(shist, c, cum);
+    const uint32_t total = __shfl(cum[3], 63);
+    uint32_t rs = r;
+    if (n) {                                                  // 0: the sample's own r-th smallest
+        const float e = static_cast<float>(r) * static_cast<float>(total) / static_cast<float>(n);
+        const float want = e + 5.0f * sqrtf(e) + 5.0f;
+        if (want < static_cast<float>(r)) rs = static_cast<uint32_t>(want) + 1u;
+    }
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+        const uint32_t before = cum[z] - c[z];
+        if (before < rs && cum[z] >= rs) {                    // one lane, one bucket
+            uint32_t last = 0xFFFFFFFFu;
+            const float expect = static_cast<float>(cum[z]) * (static_cast<float>(n) / static_cast<float>(total));
+            if (limit && expect > 16.0f * static_cast<float>(r)) {
+                const float upto = 2.0f * static_cast<float>(n) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
+                if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
+            }
+            *bound = Bound{4 * lane + z, static_cast<uint32_t>(4 * lane + z), last, 0u};
+        }
+    }
+    if (lane == 63 && total < rs) *bound = Bound{255, 255u, 0xFFFFFFFFu, 0u};
+}
+
 // Lowers query q's bucket bound to the bucket that holds its r-th best appended candidate (nothing
 // happens while fewer than r are appended).  Called by
 // a whole wavefront: lane l reads the counts of buckets 4l .. 4l+3, a wavefront prefix sum locates the
 // bucket.  The counts only grow, so any snapshot of them gives a bound that is still valid later.
-static __device__ __noinline__ void lower_bound_of(int q, uint32_t r, int *t_cur, const uint32_t *chist)
+static __device__ __noinline__ void lower_bound_of(int q, uint32_t r, Bound *bound, const uint32_t *chist)
 {
     const int lane = threadIdx.x & 63;
     uint32_t c[4];
@@ -159,7 +226,7 @@ static __device__ __noinline__ void lower_bound_of(int q, uint32_t r, int *t_cur
             cum += c[z];
             if (cum < r) tn = 4 * lane + z + 1;
         }
-        atomicMin(&t_cur[q], tn);
+        atomicMin(&bound[q].t, tn);
     }
 }
 

@@ -166,15 +166,16 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
     for (int q0 = 0; q0 < nq; q0 += p.chunk) {
         const int nc = (nq - q0 < p.chunk) ? nq - q0 : p.chunk;
         const float *y = queries + static_cast<size_t>(q0) * D;
-        int rc = launch_small_tables(y, nc, derived, m, dsub, bbar, codes, code_bytes, n_codes, r, qtab, bounds, nullptr, st);
+        int rc = launch_small_tables(y, nc, derived, m, dsub, bbar, codes, code_bytes, n_codes, r, qtab, bounds, nullptr, st,
+                                     reinterpret_cast<uint32_t *>(base + p.off_scan), scan_clear_words(n_codes, m, nc, r, DCPQ_SCAN_AUTO));
         if (rc) return rc;
         // the quantized tables have 256 entries whatever bbar is, and 1-byte sub-codes are their own low-byte plane
         if (code_bytes == 1)
             rc = launch_scan(static_cast<const uint8_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd, base + p.off_scan,
-                             DCPQ_SCAN_AUTO, st);
+                             DCPQ_SCAN_AUTO, true, st);
         else
             rc = launch_scan(static_cast<const uint16_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd,
-                             base + p.off_scan, DCPQ_SCAN_AUTO, st);
+                             base + p.off_scan, DCPQ_SCAN_AUTO, true, st);
         if (rc) return rc;
         uint32_t *ids_c = ids + static_cast<size_t>(q0) * k;
         float *dist_c = dist + static_cast<size_t>(q0) * k;

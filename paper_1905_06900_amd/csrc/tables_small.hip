@@ -35,7 +35,7 @@ template <int M, typename CodeT>
 __global__ __launch_bounds__(256) void small_tables_kernel(
     const float *__restrict__ queries, const float *__restrict__ derived, int dsub, int small_bits,
     const CodeT *__restrict__ codes, uint32_t n_first, uint8_t *__restrict__ qtab,
-    float *__restrict__ bounds, float *__restrict__ small)
+    float *__restrict__ bounds, float *__restrict__ small, uint32_t *__restrict__ clear, size_t clear_words)
 {
     extern __shared__ float lds[];
     float *ly = lds;                       // [M*dsub]
@@ -44,6 +44,7 @@ __global__ __launch_bounds__(256) void small_tables_kernel(
     const int q = blockIdx.x, tid = threadIdx.x;
     const int D = M * dsub;
     const int ks = 1 << small_bits, mask = ks - 1;
+    for (size_t w = static_cast<size_t>(q) * 256 + tid; w < clear_words; w += static_cast<size_t>(gridDim.x) * 256) clear[w] = 0u;
     for (int t = tid; t < D; t += 256) ly[t] = queries[static_cast<size_t>(q) * D + t];
     __syncthreads();
 
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(256) void small_tables_kernel(
 template <typename CodeT>
 static int launch_small_tables_t(const float *queries, int nq, const float *derived, int m, int dsub, int small_bits,
                                  const CodeT *codes, uint64_t n_codes, uint32_t r, uint8_t *qtab,
-                                 float *bounds, float *small, hipStream_t st)
+                                 float *bounds, float *small, hipStream_t st, uint32_t *clear, size_t clear_words)
 {
     if (nq == 0) return DCPQ_OK;
     const uint32_t n_first = static_cast<uint32_t>(r < n_codes ? r : n_codes);
@@ -109,7 +110,7 @@ static int launch_small_tables_t(const float *queries, int nq, const float *deri
 #define DCPQ_LAUNCH_SMALL(MV)                                                                                 \
     case MV:                                                                                                  \
         DCPQ_LAUNCH(kStageSmallTables, st, (small_tables_kernel<MV, CodeT>), dim3(nq), dim3(256), lds, queries, \
-                    derived, dsub, small_bits, codes, n_first, qtab, bounds, small);                          \
+                    derived, dsub, small_bits, codes, n_first, qtab, bounds, small, clear, clear_words);      \
         break;
     switch (m) {
         DCPQ_LAUNCH_SMALL(1) DCPQ_LAUNCH_SMALL(2) DCPQ_LAUNCH_SMALL(4) DCPQ_LAUNCH_SMALL(8)
@@ -123,13 +124,13 @@ static int launch_small_tables_t(const float *queries, int nq, const float *deri
 
 int launch_small_tables(const float *queries, int nq, const float *derived, int m, int dsub, int small_bits,
                         const void *codes, int code_bytes, uint64_t n_codes, uint32_t r, uint8_t *qtab,
-                        float *bounds, float *small, hipStream_t st)
+                        float *bounds, float *small, hipStream_t st, uint32_t *clear, size_t clear_words)
 {
     if (code_bytes == 1)
         return launch_small_tables_t(queries, nq, derived, m, dsub, small_bits, static_cast<const uint8_t *>(codes),
-                                     n_codes, r, qtab, bounds, small, st);
+                                     n_codes, r, qtab, bounds, small, st, clear, clear_words);
     return launch_small_tables_t(queries, nq, derived, m, dsub, small_bits, static_cast<const uint16_t *>(codes),
-                                 n_codes, r, qtab, bounds, small, st);
+                                 n_codes, r, qtab, bounds, small, st, clear, clear_words);
 }
 
 int launch_derive(const float *codebooks, int m, int dsub, int full_bits, int small_bits, float *derived, hipStream_t st)
