@@ -77,7 +77,7 @@ __host__ __device__ inline uint64_t make_key(uint32_t major, uint32_t id)
 }
 
 // Internal launchers used by dcpq_search (same contracts as the public calls, no validation).
-// clear: words this launch sets to zero on the side (the counters of the scan that follows); small_bits = bbar; codes: uint8 (code_bytes 1) or uint16 (2) sub-codes
+// clear: words (a multiple of 4) this launch sets to zero on the side (the counters of the scan that follows); small_bits = bbar; codes: uint8 (code_bytes 1) or uint16 (2) sub-codes
 int launch_small_tables(const float *queries, int nq, const float *derived, int m, int dsub, int small_bits,
                         const void *codes, int code_bytes, uint64_t n_codes, uint32_t r, uint8_t *qtab,
                         float *bounds, float *small, hipStream_t st, uint32_t *clear = nullptr, size_t clear_words = 0);
@@ -109,5 +109,13 @@ size_t refine_split_bytes(int nq, uint32_t r, int m, int code_bytes);
 int launch_refine_split(const float *queries, const float *codebooks, int dsub, uint32_t table_size, const void *codes,
                         int code_bytes, uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k,
                         uint32_t *ids, float *dist, void *mid, void *ws, hipStream_t st);
+
+int launch_topk_of_keys(const uint64_t *keys, int nq, uint32_t r, uint32_t k, uint32_t *ids, float *dist, void *ws, hipStream_t st);
+// pass one and the distances of pass two for small problems (scan_small.hip)
+bool small_search_pays(uint64_t n_codes, int m, int nq);
+size_t small_search_bytes(uint64_t n_codes, int nq, uint32_t r);
+size_t small_search_clear_words(uint64_t n_codes, int nq, uint32_t r);
+int launch_small_search(const float *queries, int nq, const float *codebooks, int m, int dsub, uint32_t table_size, const void *codes,
+                        int code_bytes, uint64_t n_codes, const uint8_t *qtab, uint32_t r, void *ws, const uint64_t **keys, hipStream_t st);
 
 }  // namespace dcpq

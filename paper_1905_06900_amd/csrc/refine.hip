@@ -11,6 +11,7 @@
 
 #include "common.h"
 #include "device_util.h"
+#include "refine_entry.h"
 
 namespace dcpq {
 
@@ -25,37 +26,13 @@ static uint32_t next_pow2_r(uint32_t x)
     return p;
 }
 
-constexpr int kFromTables = 0, kOnDemand = 1, kFromTerms = 2;     // where refine_topk_kernel takes its entries from
-
-// Double-precision squared distance between a query sub-vector and a centroid row (Eq. 1), rounded to fp32
-// once: the value a full table holds.
-__device__ inline float entry_on_demand(const float *__restrict__ yj, const float *__restrict__ cen, int dsub, bool vec4)
-{
-    double dj = 0.0;
-    if (vec4) {
-#pragma unroll 4
-        for (int tt = 0; tt < dsub; tt += 4) {
-            const float4 cv = *reinterpret_cast<const float4 *>(cen + tt);
-            const float4 yv = *reinterpret_cast<const float4 *>(yj + tt);
-            const double d0 = static_cast<double>(yv.x) - static_cast<double>(cv.x);
-            const double d1 = static_cast<double>(yv.y) - static_cast<double>(cv.y);
-            const double d2 = static_cast<double>(yv.z) - static_cast<double>(cv.z);
-            const double d3 = static_cast<double>(yv.w) - static_cast<double>(cv.w);
-            dj = fma(d0, d0, dj); dj = fma(d1, d1, dj); dj = fma(d2, d2, dj); dj = fma(d3, d3, dj);
-        }
-    } else {
-        for (int tt = 0; tt < dsub; ++tt) {
-            const double df = static_cast<double>(yj[tt]) - static_cast<double>(cen[tt]);
-            dj = fma(df, df, dj);
-        }
-    }
-    return static_cast<float>(dj);
-}
+constexpr int kFromTables = 0, kOnDemand = 1, kFromTerms = 2, kFromKeys = 3;     // where refine_topk_kernel takes its entries from
 
 // CodeT: uint16_t or uint8_t sub-codes; table_size = 2^b entries per sub-quantizer.
 // MODE = kFromTables: `src` = the full tables [nq][M][table_size], an entry is looked up.
 // MODE = kFromTerms:  `src` = the entries themselves, [M][gridDim.x * r] (sub-quantizer, then query, then
 //   candidate), computed on demand by refine_terms_kernel below.
+// MODE = kFromKeys:   `src` = the keys (distance bits, id) themselves, uint64 [nq][r] (M and CodeT do not matter).
 // MODE = kOnDemand:   `src` = the queries [nq][M * dsub]; an entry (Eq. 1: squared distance between the
 //   query's sub-vector and the centroid the sub-code names) is computed when a candidate asks for it,
 //   straight from the codebook `cb` [M][table_size] rows of dsub floats, cstride floats apart -- the refinement of Alg. 3 computes table
@@ -250,6 +227,9 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
                 if (j == 0 && t < n_pow2) a[t] = id < n_codes ? make_key(__float_as_uint(d), id) : ~0ull;
             }
         }
+    } else if constexpr (MODE == kFromKeys) {
+        const uint64_t *keys = reinterpret_cast<const uint64_t *>(src) + static_cast<size_t>(q) * r;
+        for (uint32_t t = threadIdx.x; t < n_pow2; t += blockDim.x) a[t] = t < r ? keys[t] : ~0ull;
     } else if constexpr (MODE == kFromTerms) {
         const size_t total = static_cast<size_t>(gridDim.x) * r;
         for (uint32_t t = threadIdx.x; t < n_pow2; t += blockDim.x) {
@@ -626,6 +606,14 @@ int launch_refine_split(const float *queries, const float *codebooks, int dsub, 
                                               cand_id, nq, r, k, ids, dist, mid, ws, st);
     return launch_refine_split_t<uint16_t>(queries, codebooks, dsub, table_size, static_cast<const uint16_t *>(codes), n_codes, m,
                                            cand_id, nq, r, k, ids, dist, mid, ws, st);
+}
+
+// keys: uint64 [nq][r], (fp32 bits of the distance, id)
+int launch_topk_of_keys(const uint64_t *keys, int nq, uint32_t r, uint32_t k, uint32_t *ids, float *dist, void *ws, hipStream_t st)
+{
+    if (nq == 0) return DCPQ_OK;
+    return launch_refine_m<1, uint8_t, kFromKeys>(reinterpret_cast<const float *>(keys), 0, nullptr, 0, 0, nullptr, 0, nullptr, nq, r, k, ids,
+                                                  dist, ws, st);
 }
 
 }  // namespace dcpq

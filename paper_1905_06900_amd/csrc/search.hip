@@ -49,6 +49,11 @@ static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int f
         scan_bytes = st > scan_bytes ? st : scan_bytes;
         refine_bytes = rt > refine_bytes ? rt : refine_bytes;
     }
+    // small problems take the two-kernel form, whose arrays lie in the same region
+    if (small_search_pays(n_codes, m, nq)) {
+        const size_t b = small_search_bytes(n_codes, nq, r);
+        scan_bytes = b > scan_bytes ? b : scan_bytes;
+    }
     p.off_scan = off;    off = align_up(off + scan_bytes, 256);
     p.off_refine = off;  off = align_up(off + refine_bytes, 256);
     p.total = off;
@@ -148,6 +153,16 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         return fail(DCPQ_EINVAL, "search: DCPQ_REFINE_SPLIT: %zu bytes of sub-codes and entries per chunk do not fit the table "
                                  "region (%zu bytes), or chunk * r reaches 2^32, or the queries are not 16-byte aligned",
                     refine_split_bytes(p.chunk, r, m, b / 8), p.tables_bytes);
+    // small problems: candidates and their distances in two kernels (entries on demand, as DCPQ_REFINE_DIRECT computes them)
+    if (small_search_pays(n_codes, m, nq) && p.chunk == nq && (refine_mode == DCPQ_REFINE_AUTO || refine_mode == DCPQ_REFINE_DIRECT)) {
+        int rc = launch_small_tables(queries, nq, derived, m, dsub, bbar, codes, code_bytes, n_codes, r, qtab, bounds, nullptr, st,
+                                     reinterpret_cast<uint32_t *>(base + p.off_scan), small_search_clear_words(n_codes, nq, r));
+        if (rc) return rc;
+        const uint64_t *keys = nullptr;
+        rc = launch_small_search(queries, nq, codebooks, m, dsub, 1u << b, codes, code_bytes, n_codes, qtab, r, base + p.off_scan, &keys, st);
+        if (rc) return rc;
+        return launch_topk_of_keys(keys, nq, r, k, ids, dist, base + p.off_refine, st);
+    }
     const bool any_split = mode_full == DCPQ_REFINE_SPLIT || mode_tail == DCPQ_REFINE_SPLIT;
     const bool any_direct = mode_full == DCPQ_REFINE_DIRECT || mode_tail == DCPQ_REFINE_DIRECT;
     // On demand in one kernel, a candidate gathers m centroid rows; a row shorter than a 64-byte unit that does not divide it

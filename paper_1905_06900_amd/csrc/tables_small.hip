@@ -26,77 +26,156 @@ __global__ __launch_bounds__(256) void derive_kernel(const float *__restrict__ c
     derived[static_cast<size_t>(j) * per_sub + e] = __fdiv_rn(acc, static_cast<float>(groups));
 }
 
-// One workgroup per query.  LDS: the query (D floats) and its m * 2^bbar small-table entries.
+// A workgroup takes QPB queries.  LDS: the queries (D floats each) and their m * 2^bbar small-table entries.
 // The quantized tables are written with 256 entries each whatever bbar is: entry e holds the
 // quantized distance of derived centroid (e mod 2^bbar), so that a scan which looks a table up by
 // the low BYTE of a sub-code gets the entry of its low bbar BITS (property P1 of Sec. 3.1 for any
 // bbar <= 8).  `small`, when asked for, keeps the 2^bbar floating-point entries as they are.
-template <int M, typename CodeT>
-__global__ __launch_bounds__(256) void small_tables_kernel(
-    const float *__restrict__ queries, const float *__restrict__ derived, int dsub, int small_bits,
+// Bound by reading the derived codebooks (one row per thread, out of the L2) and the table gathers of the walk for qmax:
+// two queries share every row and every code where there are enough queries (512 queries of 16 x 60 components: 60 us with a
+// workgroup of 256 threads per query, 78 with 1024 threads per query, 51 with two queries, 54 with four); with few queries
+// it is a chain of memory round trips, which 1024 threads shorten (251 queries of 8 x 16, r = 10000: 23 -> 12 us).
+constexpr int kSmallTabThreads = 1024;
+
+template <int M, int QPB, typename CodeT>
+__global__ __launch_bounds__(kSmallTabThreads) void small_tables_kernel(
+    const float *__restrict__ queries, int nq, const float *__restrict__ derived, int dsub, int small_bits,
     const CodeT *__restrict__ codes, uint32_t n_first, uint8_t *__restrict__ qtab,
     float *__restrict__ bounds, float *__restrict__ small, uint32_t *__restrict__ clear, size_t clear_words)
 {
-    extern __shared__ float lds[];
-    float *ly = lds;                       // [M*dsub]
-    float *ltab = lds + M * dsub;          // [M][2^bbar]
-    __shared__ float red[4];
-    const int q = blockIdx.x, tid = threadIdx.x;
+    extern __shared__ __align__(16) float lds[];
+    const int q0 = blockIdx.x * QPB, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int D = M * dsub;
     const int ks = 1 << small_bits, mask = ks - 1;
-    for (size_t w = static_cast<size_t>(q) * 256 + tid; w < clear_words; w += static_cast<size_t>(gridDim.x) * 256) clear[w] = 0u;
-    for (int t = tid; t < D; t += 256) ly[t] = queries[static_cast<size_t>(q) * D + t];
+    float *ltab = lds;                     // [QPB][M][2^bbar]
+    float *ly = lds + QPB * M * ks;        // [QPB][M*dsub]
+    __shared__ float red[QPB][16];
+    for (size_t w = static_cast<size_t>(blockIdx.x) * kSmallTabThreads + tid; w < clear_words / 4; w += static_cast<size_t>(gridDim.x) * kSmallTabThreads)
+        reinterpret_cast<uint4 *>(clear)[w] = make_uint4(0u, 0u, 0u, 0u);
+    for (int t = tid; t < QPB * D; t += kSmallTabThreads) {
+        const int q = q0 + t / D;          // (past the last query: any valid one)
+        ly[t] = queries[static_cast<size_t>(q < nq ? q : nq - 1) * D + t % D];
+    }
     __syncthreads();
 
-    // Eq. 1 on the derived codebooks: thread i owns entry i of every table.
+    // minimum or maximum over the workgroup, one value per query; the barriers also order the LDS accesses around it
+    auto reduce = [&](float (&v)[QPB], bool want_max) {
+#pragma unroll
+        for (int p = 0; p < QPB; ++p)
+            for (int off = 32; off > 0; off >>= 1) {
+                const float o = __shfl_xor(v[p], off, kWave);
+                v[p] = want_max ? fmaxf(v[p], o) : fminf(v[p], o);
+            }
+        __syncthreads();
+        if (lane == 0)
+#pragma unroll
+            for (int p = 0; p < QPB; ++p) red[p][wave] = v[p];
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < QPB; ++p) {
+            v[p] = red[p][0];
+            for (int w = 1; w < kSmallTabThreads / kWave; ++w) v[p] = want_max ? fmaxf(v[p], red[p][w]) : fminf(v[p], red[p][w]);
+        }
+    };
+
+    // Eq. 1 on the derived codebooks: a thread owns entries (j, i) and works them out for all QPB queries, the squares
+    // added one by one in ascending t.
     const bool vec4 = (dsub & 3) == 0 && (reinterpret_cast<uintptr_t>(derived) & 15) == 0;      // uniform
-    float lo = INFINITY;
-    if (tid < ks) {
-        for (int j = 0; j < M; ++j) {
-            const float *c = derived + (static_cast<size_t>(j) * ks + tid) * dsub;
-            float acc = 0.0f;
-            if (vec4) {
-                // a centroid row as 16-byte vectors (a thread reads its own row: 4-byte loads would touch as many
-                // memory lines four times as often); the squares are still added one by one in ascending t
-                for (int t = 0; t < dsub; t += 4) {
-                    const float4 c4 = *reinterpret_cast<const float4 *>(c + t);
-                    float diff = __fsub_rn(ly[j * dsub + t], c4.x);
-                    acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-                    diff = __fsub_rn(ly[j * dsub + t + 1], c4.y);
-                    acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-                    diff = __fsub_rn(ly[j * dsub + t + 2], c4.z);
-                    acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-                    diff = __fsub_rn(ly[j * dsub + t + 3], c4.w);
-                    acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-                }
-            } else {
-                for (int t = 0; t < dsub; ++t) {
-                    const float diff = __fsub_rn(ly[j * dsub + t], c[t]);
-                    acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+    float lo[QPB];
+#pragma unroll
+    for (int p = 0; p < QPB; ++p) lo[p] = INFINITY;
+    for (int e = tid; e < M * ks; e += kSmallTabThreads) {
+        const int j = e >> small_bits;
+        const float *c = derived + static_cast<size_t>(e) * dsub, *y = ly + j * dsub;
+        float acc[QPB];
+#pragma unroll
+        for (int p = 0; p < QPB; ++p) acc[p] = 0.0f;
+        if (vec4) {
+#pragma unroll 4
+            for (int t = 0; t < dsub; t += 4) {
+                const float4 c4 = *reinterpret_cast<const float4 *>(c + t);
+                const float cv[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+                for (int p = 0; p < QPB; ++p) {
+                    const float4 y4 = *reinterpret_cast<const float4 *>(y + p * D + t);
+                    const float yv[4] = {y4.x, y4.y, y4.z, y4.w};
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const float diff = __fsub_rn(yv[z], cv[z]);
+                        acc[p] = __fadd_rn(acc[p], __fmul_rn(diff, diff));
+                    }
                 }
             }
-            ltab[j * ks + tid] = acc;
-            lo = fminf(lo, acc);
+        } else {
+            for (int t = 0; t < dsub; ++t) {
+                const float cv = c[t];
+#pragma unroll
+                for (int p = 0; p < QPB; ++p) {
+                    const float diff = __fsub_rn(y[p * D + t], cv);
+                    acc[p] = __fadd_rn(acc[p], __fmul_rn(diff, diff));
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < QPB; ++p) {
+            ltab[p * M * ks + e] = acc[p];
+            lo[p] = fminf(lo[p], acc[p]);
         }
     }
-    const float qmin = block_reduce(lo, false, red);   // also publishes ltab (barriers inside)
+    reduce(lo, false);                     // (also publishes ltab)
 
     // qmax: largest small-table distance to the first n_first codes, sum over j increasing.
-    float hi = -INFINITY;
-    for (uint32_t i = tid; i < n_first; i += 256) {
+    float hi[QPB];
+#pragma unroll
+    for (int p = 0; p < QPB; ++p) hi[p] = -INFINITY;
+    for (uint32_t i = tid; i < n_first; i += kSmallTabThreads) {
         const CodeT *c = codes + static_cast<size_t>(i) * M;
-        float d = ltab[c[0] & mask];
-        for (int j = 1; j < M; ++j) d = __fadd_rn(d, ltab[j * ks + (c[j] & mask)]);
-        hi = fmaxf(hi, d);
+        float d[QPB];
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const int e = j * ks + (c[j] & mask);
+#pragma unroll
+            for (int p = 0; p < QPB; ++p) d[p] = j == 0 ? ltab[p * M * ks + e] : __fadd_rn(d[p], ltab[p * M * ks + e]);
+        }
+#pragma unroll
+        for (int p = 0; p < QPB; ++p) hi[p] = fmaxf(hi[p], d[p]);
     }
-    const float qmax = block_reduce(hi, true, red);
+    reduce(hi, true);
 
-    for (int j = 0; j < M; ++j) {
-        const float v = ltab[j * ks + (tid & mask)];
-        qtab[(static_cast<size_t>(q) * M + j) * kSmallSize + tid] = quantize_entry(v, qmin, qmax);
-        if (small && tid < ks) small[(static_cast<size_t>(q) * M + j) * ks + tid] = v;
+    for (int v = tid; v < QPB * M * kSmallSize; v += kSmallTabThreads) {
+        const int p = v / (M * kSmallSize), e = v % (M * kSmallSize);
+        if (q0 + p >= nq) break;           // (increasing in v)
+        const int j = e / kSmallSize, i = e % kSmallSize;
+        float qmin = lo[0], qmax = hi[0];
+#pragma unroll
+        for (int x = 1; x < QPB; ++x)
+            if (p == x) { qmin = lo[x]; qmax = hi[x]; }
+        const float val = ltab[(p * M + j) * ks + (i & mask)];
+        qtab[static_cast<size_t>(q0 + p) * M * kSmallSize + e] = quantize_entry(val, qmin, qmax);
+        if (small && i < ks) small[(static_cast<size_t>(q0 + p) * M + j) * ks + i] = val;
     }
-    if (tid == 0) { bounds[2 * q] = qmin; bounds[2 * q + 1] = qmax; }
+    if (tid < QPB && q0 + tid < nq) {
+        float qmin = lo[0], qmax = hi[0];
+#pragma unroll
+        for (int x = 1; x < QPB; ++x)
+            if (tid == x) { qmin = lo[x]; qmax = hi[x]; }
+        bounds[2 * (q0 + tid)] = qmin;
+        bounds[2 * (q0 + tid) + 1] = qmax;
+    }
+}
+
+template <int M, int QPB, typename CodeT>
+static int launch_small_tables_m(const float *queries, int nq, const float *derived, int dsub, int small_bits, const CodeT *codes,
+                                 uint32_t n_first, uint8_t *qtab, float *bounds, float *small, hipStream_t st, uint32_t *clear,
+                                 size_t clear_words)
+{
+    const size_t lds = sizeof(float) * QPB * (static_cast<size_t>(M) * dsub + (static_cast<size_t>(M) << small_bits));
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(&small_tables_kernel<M, QPB, CodeT>), static_cast<int>(lds));
+    if (arc) return arc;
+    DCPQ_LAUNCH(kStageSmallTables, st, (small_tables_kernel<M, QPB, CodeT>), dim3((nq + QPB - 1) / QPB), dim3(kSmallTabThreads), lds,
+                queries, nq, derived, dsub, small_bits, codes, n_first, qtab, bounds, small, clear, clear_words);
+    DCPQ_CHECK_LAUNCH("small_tables_kernel");
+    return DCPQ_OK;
 }
 
 template <typename CodeT>
@@ -106,20 +185,17 @@ static int launch_small_tables_t(const float *queries, int nq, const float *deri
 {
     if (nq == 0) return DCPQ_OK;
     const uint32_t n_first = static_cast<uint32_t>(r < n_codes ? r : n_codes);
-    const size_t lds = sizeof(float) * (static_cast<size_t>(m) * dsub + (static_cast<size_t>(m) << small_bits));
 #define DCPQ_LAUNCH_SMALL(MV)                                                                                 \
     case MV:                                                                                                  \
-        DCPQ_LAUNCH(kStageSmallTables, st, (small_tables_kernel<MV, CodeT>), dim3(nq), dim3(256), lds, queries, \
-                    derived, dsub, small_bits, codes, n_first, qtab, bounds, small, clear, clear_words);      \
-        break;
+        if (nq >= 500) /* a workgroup per CU and more */                                                      \
+            return launch_small_tables_m<MV, 2, CodeT>(queries, nq, derived, dsub, small_bits, codes, n_first, qtab, bounds, small, st, clear, clear_words); \
+        return launch_small_tables_m<MV, 1, CodeT>(queries, nq, derived, dsub, small_bits, codes, n_first, qtab, bounds, small, st, clear, clear_words);
     switch (m) {
         DCPQ_LAUNCH_SMALL(1) DCPQ_LAUNCH_SMALL(2) DCPQ_LAUNCH_SMALL(4) DCPQ_LAUNCH_SMALL(8)
         DCPQ_LAUNCH_SMALL(16) DCPQ_LAUNCH_SMALL(32)
         default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
     }
 #undef DCPQ_LAUNCH_SMALL
-    DCPQ_CHECK_LAUNCH("small_tables_kernel");
-    return DCPQ_OK;
 }
 
 int launch_small_tables(const float *queries, int nq, const float *derived, int m, int dsub, int small_bits,

@@ -98,3 +98,42 @@ def test_unsupported_widths_are_refused():
     cb = torch.zeros((2, 4096, 4), dtype=torch.float32, device=DEV)      # b = 12
     with pytest.raises(binding.DcpqError):
         binding.derive_codebooks(cb, 8)
+
+
+@pytest.mark.parametrize("b,bbar,m,dsub,N,Q,r", [
+    (16, 8, 8, 12, 4096, 3, 4096),          # r = N, one full step of the first kernel
+    (16, 8, 4, 32, 4097, 1, 100),           # one code beyond it
+    (16, 8, 1, 7, 130_001, 9, 1),           # ragged last stretch, r = 1
+    (16, 8, 16, 5, 300_003, 2, 9000),       # several rounds of candidates per stretch
+    (8, 6, 32, 4, 50_001, 5, 700),
+    (16, 8, 8, 16, 1_200_003, 1, 12_000),   # a stretch per workgroup (no adding up of histograms)
+    (8, 4, 2, 16, 1_000_001, 4, 3000),      # two sub-codes of 16 values each: tens of thousands of ties at the bound
+])
+def test_small_problems_in_two_kernels(b, bbar, m, dsub, N, Q, r):
+    # the same search through the staged calls (scan, full tables, refine)
+    print("small PQ %dx%d,%d dsub=%d N=%d Q=%d r=%d" % (m, bbar, b, dsub, N, Q, r), flush=True)
+    k = min(100, r)
+    cb, codes, queries = make_case(m, dsub, b, bbar, N, Q, 9100 + N % 97)
+    derived = binding.derive_codebooks(cb, bbar)
+    qtab, _, _ = binding.build_small_tables(queries, derived, codes, r)
+    cand_id, _ = binding.scan_candidates(codes, qtab, r)
+    want_ids, want_dist = binding.refine_direct_topk(queries, cb, codes, cand_id, k)
+    for mode in (binding.REFINE_AUTO, binding.REFINE_DIRECT):
+        ids, dist = binding.search(queries, cb, derived, codes, r, k, refine_mode=mode)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(to_np(ids), to_np(want_ids))
+        np.testing.assert_array_equal(to_np(dist), to_np(want_dist))
+
+
+@pytest.mark.parametrize("Q", [1, 499, 500, 501])
+def test_small_tables_with_one_and_two_queries_per_workgroup(Q):
+    m, dsub, b, bbar, N, r = 8, 6, 16, 8, 3000, 700
+    cb, codes, queries = make_case(m, dsub, b, bbar, N, Q, 77)
+    derived = binding.derive_codebooks(cb, bbar)
+    qtab, bounds, small = (to_np(x) for x in binding.build_small_tables(queries, derived, codes, r, want_small=True))
+    q_np, d_np, c_np = to_np(queries), to_np(derived), to_np(codes)
+    for q in {0, Q // 2, Q - 1}:
+        D = oracle.compute_tables_f32(q_np[q], d_np)
+        lo, hi = oracle.bounds(D, c_np, r)
+        np.testing.assert_array_equal(small[q], D)
+        np.testing.assert_array_equal(bounds[q], np.array([lo, hi], np.float32))
