@@ -232,8 +232,10 @@ int dcpq_search_bits_chunk(int m, int nq, int b, int chunk_queries);
  *                       for m = 16, four for m = 32) is smaller than 4 MB, the codebooks as a whole
  *                       are not, and the chunk has at least 2^16 candidates; else DIRECT (dcpq_search
  *                       uses this).
- *                       dcpq_search_refine_mode reports the choice for the first chunk of a batch of
- *                       nq queries under the default chunking
+ *                       dcpq_search_refine_mode reports this size rule for the first chunk of a batch of
+ *                       nq queries under the default chunking.  It says how the entries come about in
+ *                       principle; a search computes them in another of these forms, for all or some
+ *                       of its queries, where that is faster (which can depend on the codes)
  * All give the fp32 sum, j increasing, of the M entries; TABLES and the on-demand modes agree within
  * the 1e-5 bar and may differ in the last bit (and then in the order of near-ties). */
 #define DCPQ_REFINE_AUTO 0

@@ -47,10 +47,14 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
                                                           const uint32_t *__restrict__ cand_id, uint32_t r,
                                                           uint32_t k, uint32_t n_pow2, int use_lds,
                                                           uint32_t memo_slots, uint64_t *__restrict__ spill,
-                                                          uint32_t *__restrict__ ids, float *__restrict__ dist)
+                                                          uint32_t *__restrict__ ids, float *__restrict__ dist,
+                                                          uint32_t *__restrict__ left)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const int q = blockIdx.x;
+    // left (optional).  kOnDemand: set for the queries whose entries cannot be memoized; they are left to the kernels that
+    // split the work by sub-quantizer.  kFromTerms: only the queries set there are worked on.
+    if (MODE == kFromTerms && left && left[q] == 0) return;           // uniform
     uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(q) * n_pow2;
     constexpr bool DIRECT = MODE == kOnDemand;
     const float *tq = nullptr;
@@ -205,6 +209,10 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
                 }
             }
         }
+        if (left) {                                                      // uniform
+            if (threadIdx.x == 0) left[q] = memo ? 0u : 1u;
+            if (!memo) return;
+        }
         if (!memo) {                                                     // uniform
             // One lane per (candidate, sub-quantizer): the M lanes of a candidate are neighbours in a wavefront, each
             // computes one entry, and the sums are formed in ascending j from the neighbours' values.
@@ -347,10 +355,22 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
     }
 }
 
+// Slots per sub-quantizer of the hash set that memoizes entries in the one-kernel form, 0 when it does not (below 8192
+// (candidate, sub-quantizer) pairs per query collecting and looking up costs more than it saves: measured at r = 1000, m = 4).
+uint32_t refine_memo_slots(int m, int dsub, uint32_t r)
+{
+    if (static_cast<uint64_t>(r) * m < 8u * 1024u) return 0;
+    const uint32_t np2 = next_pow2_r(r);
+    const size_t lds = (np2 <= kRefineLdsKeys ? sizeof(uint64_t) * np2 : 0) + sizeof(float) * m * dsub;
+    uint32_t slots = 512;
+    while (slots >= 64 && lds + static_cast<size_t>(9) * m * slots > static_cast<size_t>(140) * 1024) slots /= 2;
+    return slots < 64 ? 0 : slots;
+}
+
 template <int M, typename CodeT, int MODE>
 static int launch_refine_m(const float *src, uint32_t table_size, const float *cb, int dsub, int cstride, const CodeT *codes,
                            uint64_t n_codes, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids,
-                           float *dist, void *ws, hipStream_t st)
+                           float *dist, void *ws, hipStream_t st, uint32_t *left = nullptr)
 {
     const uint32_t np2 = next_pow2_r(r);
     const int use_lds = np2 <= kRefineLdsKeys;
@@ -358,20 +378,16 @@ static int launch_refine_m(const float *src, uint32_t table_size, const float *c
     // on demand: a hash set of the query's distinct (sub-quantizer, sub-code) pairs with their entries, as many
     // slots per sub-quantizer (a power of two, at most 512) as the LDS left beside the keys, the query and the
     // kernel's static arrays (17 KB) holds; none if that is fewer than 64
-    // (below 8192 (candidate, sub-quantizer) pairs per query collecting and looking up costs more than it saves:
-    // measured at r = 1000, m = 4)
     uint32_t memo_slots = 0;
-    if (MODE == kOnDemand && static_cast<uint64_t>(r) * M >= 8u * 1024u) {
-        memo_slots = 512;
-        while (memo_slots >= 64 && lds + static_cast<size_t>(9) * M * memo_slots > static_cast<size_t>(140) * 1024) memo_slots /= 2;
-        if (memo_slots < 64) memo_slots = 0;
+    if (MODE == kOnDemand) {
+        memo_slots = refine_memo_slots(M, dsub, r);
         lds += static_cast<size_t>(9) * M * memo_slots;                 // keys, entries, and the list of slots in use
     }
     const int rc = allow_dynamic_lds(reinterpret_cast<const void *>(&refine_topk_kernel<M, CodeT, MODE>), static_cast<int>(lds));
     if (rc) return rc;
     DCPQ_LAUNCH(kStageRefine, st, (refine_topk_kernel<M, CodeT, MODE>), dim3(nq), dim3(1024), lds, src, table_size, cb, dsub,
                 cstride, codes, static_cast<uint32_t>(n_codes), cand_id, r, k, np2, use_lds, memo_slots, static_cast<uint64_t *>(ws),
-                ids, dist);
+                ids, dist, left);
     DCPQ_CHECK_LAUNCH("refine_topk_kernel");
     return DCPQ_OK;
 }
@@ -397,12 +413,12 @@ int launch_pad_rows(const float *src, size_t nrows, int dsub, int cstride, float
 template <typename CodeT, int MODE>
 static int launch_refine_t(const float *src, uint32_t table_size, const float *cb, int dsub, int cstride, const CodeT *codes,
                            uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids,
-                           float *dist, void *ws, hipStream_t st)
+                           float *dist, void *ws, hipStream_t st, uint32_t *left = nullptr)
 {
     if (nq == 0) return DCPQ_OK;
 #define DCPQ_LAUNCH_REFINE(MV)                                                                                      \
     case MV:                                                                                                        \
-        return launch_refine_m<MV, CodeT, MODE>(src, table_size, cb, dsub, cstride, codes, n_codes, cand_id, nq, r, k, ids, dist, ws, st);
+        return launch_refine_m<MV, CodeT, MODE>(src, table_size, cb, dsub, cstride, codes, n_codes, cand_id, nq, r, k, ids, dist, ws, st, left);
     switch (m) {
         DCPQ_LAUNCH_REFINE(1) DCPQ_LAUNCH_REFINE(2) DCPQ_LAUNCH_REFINE(4) DCPQ_LAUNCH_REFINE(8)
         DCPQ_LAUNCH_REFINE(16) DCPQ_LAUNCH_REFINE(32)
@@ -424,13 +440,13 @@ int launch_refine(const float *tables, uint32_t table_size, const void *codes, i
 
 int launch_refine_direct(const float *queries, const float *codebooks, int dsub, int cstride, uint32_t table_size, const void *codes,
                          int code_bytes, uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k,
-                         uint32_t *ids, float *dist, void *ws, hipStream_t st)
+                         uint32_t *ids, float *dist, void *ws, hipStream_t st, uint32_t *left)
 {
     if (code_bytes == 1)
         return launch_refine_t<uint8_t, kOnDemand>(queries, table_size, codebooks, dsub, cstride, static_cast<const uint8_t *>(codes), n_codes,
-                                              m, cand_id, nq, r, k, ids, dist, ws, st);
+                                              m, cand_id, nq, r, k, ids, dist, ws, st, left);
     return launch_refine_t<uint16_t, kOnDemand>(queries, table_size, codebooks, dsub, cstride, static_cast<const uint16_t *>(codes), n_codes, m,
-                                           cand_id, nq, r, k, ids, dist, ws, st);
+                                           cand_id, nq, r, k, ids, dist, ws, st, left);
 }
 
 
@@ -449,15 +465,15 @@ int launch_refine_direct(const float *queries, const float *codebooks, int dsub,
 //   refine_terms_kernel   entry[j][candidate] (Eq. 1, as in the one-kernel form: fp64, rounded to fp32 once)
 //   refine_topk_kernel<kFromTerms>   fp32 sum over j increasing, then the k smallest by (distance, id)
 // Candidates are numbered query * r + position, as in cand_id.
-constexpr uint32_t kSplitChunk = 2048;      // candidates per workgroup of refine_terms_kernel (256 threads x 8)
 
 template <int M, typename CodeT>
 __global__ __launch_bounds__(256) void gather_codes_kernel(const CodeT *__restrict__ codes, uint32_t n_codes,
                                                            const uint32_t *__restrict__ cand_id, uint32_t total,
-                                                           CodeT *__restrict__ plane)
+                                                           uint32_t r, const uint32_t *__restrict__ left, CodeT *__restrict__ plane)
 {
     const uint32_t t = blockIdx.x * 256u + threadIdx.x;
     if (t >= total) return;
+    if (left && left[t / r] == 0) return;
     const uint32_t id = cand_id[t];
     constexpr int BYTES = M * static_cast<int>(sizeof(CodeT));
     CodeT c[M];
@@ -481,70 +497,153 @@ __global__ __launch_bounds__(256) void gather_codes_kernel(const CodeT *__restri
     for (int j = 0; j < M; ++j) plane[static_cast<size_t>(j) * total + t] = c[j];
 }
 
+// A workgroup works out the entries of one sub-quantizer for one query's candidates (or, with few queries, for a
+// stretch of them).
 // P > 0: rows of P 16-byte parts (dsub = 4 P).  Lane l of a wavefront reading its own row with P loads would
 // send P separate requests per row to the second-level cache, whose request rate is what bounds this kernel
 // (2.9 requests per entry measured at dsub = 12); instead the P * 64 parts of the wavefront's 64 rows are
 // fetched in row order, lane after lane, so that the parts of a row travel in one request (two when the row
 // lies across a 64-byte boundary), parked in LDS, and each lane then picks up its row there.
 // P = 0: rows of any length, each read by its own lane.
+// Where the candidates repeat sub-codes (encoded data: 20 to 1000 different ones among 2000 to 10000 candidates) every
+// entry is worked out once: the distinct sub-codes are collected in an LDS hash set, their entries computed, and the
+// candidates look them up.  Whether anything repeats shows in the first 256 candidates; with nearly all different
+// (random codes) the entries are computed one by one.  Either way the same bits.
+constexpr uint32_t kTermSlots = 2048;       // hash slots; half of them may be taken
+
 template <typename CodeT, int P>
-__global__ __launch_bounds__(256) void refine_terms_kernel(const float *__restrict__ queries, int m, int dsub,
+__global__ __launch_bounds__(256) void refine_terms_kernel(const float *__restrict__ queries, int nq, int m, int dsub,
                                                            const float *__restrict__ cb, uint32_t table_size,
                                                            const CodeT *__restrict__ plane, uint32_t total, uint32_t r,
+                                                           uint32_t stretches, uint32_t stretch, const uint32_t *__restrict__ left,
                                                            float *__restrict__ terms)
 {
     __shared__ float4 stage[P ? 256 * P : 1];
+    __shared__ uint32_t hkey[kTermSlots];
+    __shared__ float hval[kTermSlots];
+    __shared__ uint16_t hlist[kTermSlots / 2];
+    __shared__ uint32_t s_claimed, s_over;
+    constexpr uint32_t kEmpty = 0xFFFFFFFFu, kFirst = 256;
     const uint32_t x = blockIdx.x & 7u;                                // the XCD this workgroup is expected on
-    const uint32_t first = (blockIdx.x >> 3) * kSplitChunk;            // its stretch of candidates
+    // m >= 8: sub-quantizers x, x + 8, ..., one after the other over all queries; m < 8: sub-quantizer x mod m, the queries
+    // of part x / m out of 8 / m
+    uint32_t item = blockIdx.x >> 3;
+    const uint32_t s0 = item % stretches;
+    item /= stretches;
+    int j;
+    uint32_t q;
+    if (m >= 8) {
+        j = static_cast<int>(x + 8u * (item / static_cast<uint32_t>(nq)));
+        q = item % static_cast<uint32_t>(nq);
+    } else {
+        j = static_cast<int>(x % static_cast<uint32_t>(m));
+        q = item * (8u / static_cast<uint32_t>(m)) + x / static_cast<uint32_t>(m);
+    }
+    if (q >= static_cast<uint32_t>(nq) || j >= m) return;              // uniform
+    if (left && left[q] == 0) return;                                  // uniform
+    const uint32_t begin = s0 * stretch, n = begin < r ? min(stretch, r - begin) : 0u;
+    if (n == 0) return;                                                // uniform
     const bool vec4 = (dsub & 3) == 0;
-    const int D = m * dsub;
-    const uint32_t lane = threadIdx.x & 63u;
-    float4 *ws = stage + (threadIdx.x >> 6) * (64 * P);                // this wavefront's rows
-    // m >= 8: sub-quantizers x, x + 8, ..., every candidate of the stretch; m < 8: sub-quantizer x mod m, the
-    // candidates of part x / m out of 8 / m (threads are dealt to the parts in turn)
-    const uint32_t parts = m >= 8 ? 1u : 8u / static_cast<uint32_t>(m), part = m >= 8 ? 0u : x / static_cast<uint32_t>(m);
-    for (int j = m >= 8 ? static_cast<int>(x) : static_cast<int>(x % static_cast<uint32_t>(m)); j < m; j += 8) {
-        const CodeT *pj = plane + static_cast<size_t>(j) * total;
-        const float *cj = cb + static_cast<size_t>(j) * table_size * dsub;
-        float *tj = terms + static_cast<size_t>(j) * total;
-        // (the same number of rounds for every thread: kSplitChunk is a multiple of 256 * parts)
-#pragma unroll 2
-        for (uint32_t i = threadIdx.x + 256u * part; i < kSplitChunk; i += 256u * parts) {
-            const uint32_t t = first + i;
-            const bool live = t < total;
-            const uint32_t code = live ? pj[t] : 0u;                   // past the end: any valid row, result dropped
-            const float *yj = queries + static_cast<size_t>(live ? t / r : 0u) * D + j * dsub;
-            float e;
-            if constexpr (P > 0) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    float4 *ws = stage + (tid >> 6) * (64 * P);                        // this wavefront's rows
+    const size_t at = static_cast<size_t>(j) * total + static_cast<size_t>(q) * r + begin;
+    const CodeT *pj = plane + at;
+    float *tj = terms + at;
+    const float *cj = cb + static_cast<size_t>(j) * table_size * dsub;
+    const float *yj = queries + (static_cast<size_t>(q) * m + j) * dsub;
+
+    // the entry of this lane's sub-code (all 64 lanes take part; the value of a lane without a sub-code of its own is not used)
+    auto entry = [&](uint32_t code) -> float {
+        if constexpr (P > 0) {
 #pragma unroll
-                for (int c = 0; c < P; ++c) {
-                    const uint32_t f = 64u * c + lane;                 // part f % P of the row of lane f / P
-                    const uint32_t owner = f / P;
-                    const uint32_t oc = static_cast<uint32_t>(__shfl(static_cast<int>(code), static_cast<int>(owner)));
-                    ws[f] = *reinterpret_cast<const float4 *>(cj + static_cast<size_t>(oc) * dsub + 4u * (f - owner * P));
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                double dj = 0.0;
-#pragma unroll
-                for (int c = 0; c < P; ++c) {                          // the arithmetic of entry_on_demand, part by part
-                    const float4 cv = ws[lane * P + c];
-                    const float4 yv = *reinterpret_cast<const float4 *>(yj + 4 * c);
-                    const double d0 = static_cast<double>(yv.x) - static_cast<double>(cv.x);
-                    const double d1 = static_cast<double>(yv.y) - static_cast<double>(cv.y);
-                    const double d2 = static_cast<double>(yv.z) - static_cast<double>(cv.z);
-                    const double d3 = static_cast<double>(yv.w) - static_cast<double>(cv.w);
-                    dj = fma(d0, d0, dj); dj = fma(d1, d1, dj); dj = fma(d2, d2, dj); dj = fma(d3, d3, dj);
-                }
-                e = static_cast<float>(dj);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // every lane has its row before the next round parks new ones
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            } else {
-                e = entry_on_demand(yj, cj + static_cast<size_t>(code) * dsub, dsub, vec4);
+            for (int c = 0; c < P; ++c) {
+                const uint32_t f = 64u * c + lane;                     // part f % P of the row of lane f / P
+                const uint32_t owner = f / P;
+                const uint32_t oc = static_cast<uint32_t>(__shfl(static_cast<int>(code), static_cast<int>(owner)));
+                ws[f] = *reinterpret_cast<const float4 *>(cj + static_cast<size_t>(oc) * dsub + 4u * (f - owner * P));
             }
-            if (live) tj[t] = e;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            double dj = 0.0;
+#pragma unroll
+            for (int c = 0; c < P; ++c) {                              // the arithmetic of entry_on_demand, part by part
+                const float4 cv = ws[lane * P + c];
+                const float4 yv = *reinterpret_cast<const float4 *>(yj + 4 * c);
+                const double d0 = static_cast<double>(yv.x) - static_cast<double>(cv.x);
+                const double d1 = static_cast<double>(yv.y) - static_cast<double>(cv.y);
+                const double d2 = static_cast<double>(yv.z) - static_cast<double>(cv.z);
+                const double d3 = static_cast<double>(yv.w) - static_cast<double>(cv.w);
+                dj = fma(d0, d0, dj); dj = fma(d1, d1, dj); dj = fma(d2, d2, dj); dj = fma(d3, d3, dj);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // every lane has its row before the next round parks new ones
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            return static_cast<float>(dj);
+        } else {
+            return entry_on_demand(yj, cj + static_cast<size_t>(code) * dsub, dsub, vec4);
+        }
+    };
+    auto first_slot = [](uint32_t c) { return ((c * 40503u) >> 3) & (kTermSlots - 1u); };
+    auto collect = [&](uint32_t c) {
+        uint32_t h = first_slot(c);
+        for (int probes = 0; probes < 64; ++probes) {
+            uint32_t cur = __hip_atomic_load(&hkey[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (cur == c) return;                                      // (nearly always already there)
+            if (cur == kEmpty) {
+                cur = atomicCAS(&hkey[h], kEmpty, c);
+                if (cur == kEmpty) {
+                    const uint32_t slot = atomicAdd(&s_claimed, 1u);
+                    if (slot < kTermSlots / 2) hlist[slot] = static_cast<uint16_t>(h);
+                    else s_over = 1;                                   // the set is half full: give up
+                    return;
+                }
+                if (cur == c) return;
+            }
+            h = (h + 1u) & (kTermSlots - 1u);
+        }
+        s_over = 1;                                                    // benign race: every writer stores 1
+    };
+
+    bool memo = dsub > 16 && n >= 2 * kFirst;
+    if (memo) {                                                        // uniform
+        for (uint32_t t = tid; t < kTermSlots; t += 256) hkey[t] = kEmpty;
+        if (tid == 0) { s_claimed = 0; s_over = 0; }
+        __syncthreads();
+        collect(pj[tid]);                                              // (kFirst = the workgroup's threads)
+        __syncthreads();
+        memo = s_claimed <= kFirst * 5 / 8;
+        __syncthreads();
+    }
+    if (memo) {                                                        // uniform
+        for (uint32_t t = kFirst + tid; t < n; t += 256) {
+            collect(pj[t]);
+            if (__hip_atomic_load(&s_over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
+        }
+        __syncthreads();
+        memo = s_over == 0;
+    }
+    if (memo) {                                                        // uniform
+        const uint32_t used = s_claimed;
+        for (uint32_t base = tid - lane; base < used; base += 256) {   // uniform over the wavefront
+            const uint32_t u = base + lane, h = hlist[u < used ? u : used - 1];
+            const float e = entry(hkey[h]);
+            if (u < used) hval[h] = e;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t t = tid; t < n; t += 256) {
+            const uint32_t c = pj[t];
+            uint32_t h = first_slot(c);
+            while (hkey[h] != c) h = (h + 1u) & (kTermSlots - 1u);     // it is there: every sub-code was collected
+            tj[t] = hval[h];
+        }
+    } else {
+#pragma unroll 2
+        for (uint32_t base = tid - lane; base < n; base += 256) {      // uniform over the wavefront
+            const uint32_t t = base + lane;
+            const float e = entry(pj[t < n ? t : n - 1]);
+            if (t < n) tj[t] = e;
         }
     }
 }
@@ -559,7 +658,7 @@ size_t refine_split_bytes(int nq, uint32_t r, int m, int code_bytes)
 template <typename CodeT>
 static int launch_refine_split_t(const float *queries, const float *codebooks, int dsub, uint32_t table_size, const CodeT *codes,
                                  uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids,
-                                 float *dist, void *mid, void *ws, hipStream_t st)
+                                 float *dist, void *mid, void *ws, hipStream_t st, uint32_t *left)
 {
     const uint32_t total = static_cast<uint32_t>(static_cast<size_t>(nq) * r);
     CodeT *plane = static_cast<CodeT *>(mid);
@@ -568,7 +667,7 @@ static int launch_refine_split_t(const float *queries, const float *codebooks, i
 #define DCPQ_LAUNCH_GATHER(MV)                                                                                      \
     case MV:                                                                                                        \
         DCPQ_LAUNCH(kStageRefine, st, (gather_codes_kernel<MV, CodeT>), g1, dim3(256), 0, codes,                     \
-                    static_cast<uint32_t>(n_codes), cand_id, total, plane);                                        \
+                    static_cast<uint32_t>(n_codes), cand_id, total, r, left, plane);                                        \
         break;
     switch (m) {
         DCPQ_LAUNCH_GATHER(1) DCPQ_LAUNCH_GATHER(2) DCPQ_LAUNCH_GATHER(4) DCPQ_LAUNCH_GATHER(8)
@@ -577,35 +676,40 @@ static int launch_refine_split_t(const float *queries, const float *codebooks, i
     }
 #undef DCPQ_LAUNCH_GATHER
     DCPQ_CHECK_LAUNCH("gather_codes_kernel");
-    const uint32_t stretches = (total + kSplitChunk - 1) / kSplitChunk;
+    // a query's candidates in stretches of 512 and more, so that few queries still give two workgroups per CU and more
+    uint32_t stretches = 1;
+    while (static_cast<uint64_t>(nq) * m * stretches < 1024 && r / (2 * stretches) >= 512) stretches *= 2;
+    const uint32_t stretch = (r + stretches - 1) / stretches;
+    const uint32_t items = m >= 8 ? static_cast<uint32_t>(nq) * (m / 8) : (static_cast<uint32_t>(nq) * m + 7) / 8;
 #define DCPQ_LAUNCH_TERMS(PV)                                                                                       \
     case PV:                                                                                                        \
-        DCPQ_LAUNCH(kStageRefine, st, (refine_terms_kernel<CodeT, PV>), dim3(8u * stretches), dim3(256), 0, queries, m, dsub,    \
-                    codebooks, table_size, plane, total, r, terms);                                                 \
+        DCPQ_LAUNCH(kStageRefine, st, (refine_terms_kernel<CodeT, PV>), dim3(8u * items * stretches), dim3(256), 0, queries, nq, m, dsub,    \
+                    codebooks, table_size, plane, total, r, stretches, stretch, left, terms);                             \
         break;
-    // rows of up to 8 whole 16-byte parts go through LDS (codebooks are 16-byte aligned: the callers check)
-    switch (dsub % 4 == 0 && dsub <= 32 ? dsub / 4 : 0) {
+    // rows of up to 8 whole 16-byte parts, and 15 (60 components), go through LDS (codebooks are 16-byte aligned: the callers check)
+    switch (dsub % 4 == 0 ? dsub / 4 : 0) {
         DCPQ_LAUNCH_TERMS(1) DCPQ_LAUNCH_TERMS(2) DCPQ_LAUNCH_TERMS(3) DCPQ_LAUNCH_TERMS(4) DCPQ_LAUNCH_TERMS(5)
         DCPQ_LAUNCH_TERMS(6) DCPQ_LAUNCH_TERMS(7) DCPQ_LAUNCH_TERMS(8)
-        default: DCPQ_LAUNCH(kStageRefine, st, (refine_terms_kernel<CodeT, 0>), dim3(8u * stretches), dim3(256), 0, queries, m,
-                             dsub, codebooks, table_size, plane, total, r, terms);
+        default: DCPQ_LAUNCH(kStageRefine, st, (refine_terms_kernel<CodeT, 0>), dim3(8u * items * stretches), dim3(256), 0, queries, nq, m,
+                             dsub, codebooks, table_size, plane, total, r, stretches, stretch, left, terms);
     }
 #undef DCPQ_LAUNCH_TERMS
     DCPQ_CHECK_LAUNCH("refine_terms_kernel");
-    return launch_refine_t<CodeT, kFromTerms>(terms, table_size, nullptr, 0, 0, codes, n_codes, m, cand_id, nq, r, k, ids, dist, ws, st);
+    return launch_refine_t<CodeT, kFromTerms>(terms, table_size, nullptr, 0, 0, codes, n_codes, m, cand_id, nq, r, k, ids, dist, ws, st, left);
 }
 
-// mid: refine_split_bytes(nq, r, m, code_bytes) bytes, 256-byte aligned; nq * r must fit 32 bits (the caller checks both)
+// mid: refine_split_bytes(nq, r, m, code_bytes) bytes, 256-byte aligned; nq * r must fit 32 bits (the caller checks both);
+// left (optional): only the queries with a non-zero value
 int launch_refine_split(const float *queries, const float *codebooks, int dsub, uint32_t table_size, const void *codes,
                         int code_bytes, uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k,
-                        uint32_t *ids, float *dist, void *mid, void *ws, hipStream_t st)
+                        uint32_t *ids, float *dist, void *mid, void *ws, hipStream_t st, uint32_t *left)
 {
     if (nq == 0) return DCPQ_OK;
     if (code_bytes == 1)
         return launch_refine_split_t<uint8_t>(queries, codebooks, dsub, table_size, static_cast<const uint8_t *>(codes), n_codes, m,
-                                              cand_id, nq, r, k, ids, dist, mid, ws, st);
+                                              cand_id, nq, r, k, ids, dist, mid, ws, st, left);
     return launch_refine_split_t<uint16_t>(queries, codebooks, dsub, table_size, static_cast<const uint16_t *>(codes), n_codes, m,
-                                           cand_id, nq, r, k, ids, dist, mid, ws, st);
+                                           cand_id, nq, r, k, ids, dist, mid, ws, st, left);
 }
 
 // keys: uint64 [nq][r], (fp32 bits of the distance, id)

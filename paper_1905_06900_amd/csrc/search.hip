@@ -84,16 +84,20 @@ extern "C" size_t dcpq_search_workspace_bytes(uint64_t n_codes, int m, int nq, u
 }
 
 // How pass two gets its table entries: looked up in full tables built first (DCPQ_REFINE_TABLES), or computed
-// on demand, in one kernel (DCPQ_REFINE_DIRECT) or split by sub-quantizer (DCPQ_REFINE_SPLIT).  On demand a
-// query gathers r m centroid rows; with tables it writes 2^b m entries and then makes r m scattered 4-byte
-// lookups.  Measured on MI355X a gathered row costs about 8 ps more than a table lookup (27 against 19 ps for
-// random 16-bit sub-codes, dsub = 12) and a 2^16-entry table 60 to 200 ns to build (dsub = 12 to 60), which
-// puts the break-even near r = 8000 for b = 16; the rule below scales that with the table size.
-// The split form pays when the sub-codebooks that one XCD would serve (one in eight of them) fit its 4 MB
-// cache with room to spare while the codebooks as a whole do not (measured at m = 8, dsub = 12, r = 4000:
-// 2.9 times faster with 64 queries, 2.2 times with 4096; with rows of exactly 4 MB per sub-quantizer and
-// codes that follow the queries, 1.4 times slower), and the batch is not tiny; it is possible when its
-// intermediate arrays fit the table region and candidate numbers 32 bits.
+// on demand, in one kernel (DCPQ_REFINE_DIRECT) or split by sub-quantizer (DCPQ_REFINE_SPLIT).  Measured on MI355X,
+// microseconds for tables / one kernel / split:
+//   m = 8, dsub = 12, random codes: 300 queries, r = 9000: 734 / 712 / 242;  16 queries, r = 4000: 87 / 181 / 37;  2 queries, r = 1000: 45 / 51 / 27
+//   m = 8, dsub = 16, encoded codes: 251, r = 10000: 376 / 232 / 178;  1000, r = 2000: 691 / 118 / 169
+//   m = 16, dsub = 60, encoded codes: 512, r = 5000, N = 10 M: 1850 / 139 / 267;  N = 3 M: 1850 / 1358 / 351;  3, r = 6000: 285 / 15 / 40
+//   m = 4, dsub = 32, random codes: 1000, r = 1000: 607 / 124 / 104;  100, r = 10000: 168 / 231 / 103
+//   b = 8 (tables of 256 entries), m = 16, dsub = 8: 333, r = 2000: 47 / 97 / -
+// The one-kernel form wins where the candidates of a query name few enough sub-codes to memoize their entries, and loses
+// widely where they do not; that shows on the device only.  So with 16-bit sub-codes: split where a sub-codebook
+// (two for m = 16, four for m = 32) is smaller than one XCD's 4 MB cache (dsub < 16 at m = 8: the split form is never far
+// behind there), where there is nothing to memoize, or where the batch is small (below 2^18 candidates the attempt costs what
+// it can save: 50 queries, r = 3000: 33 one kernel, 35 split, 50 one after the other); else the one-kernel form first, and the split form for the queries
+// that it gives up.  Tables for 8-bit sub-codes, and where the split form's arrays do not fit and r > 2^b / 8 (a gathered row
+// costs about 8 ps more than a table lookup and a 2^16-entry table 60 to 200 ns to build).
 static bool split_possible(const SearchPlan &p, int m, int b, int nq, uint32_t r, const float *queries)
 {
     // (its kernels read query sub-vectors 16 bytes at a time from where the caller keeps them)
@@ -101,17 +105,30 @@ static bool split_possible(const SearchPlan &p, int m, int b, int nq, uint32_t r
            (reinterpret_cast<uintptr_t>(queries) & 15) == 0;
 }
 
-static bool split_pays(int m, int dsub, int b, int nq, uint32_t r)
+// the split form at once, without an attempt to memoize?
+static bool split_first(int m, int dsub, int b, int nq, uint32_t r)
 {
     const size_t sub = (sizeof(float) * static_cast<size_t>(dsub)) << b;
-    return sub * ((m + 7) / 8) < (4u << 20) && sub * m > (4u << 20) && static_cast<uint64_t>(nq) * r >= (1u << 16);
+    return sub * ((m + 7) / 8) < (4u << 20) || refine_memo_slots(m, dsub, r) == 0 || static_cast<uint64_t>(nq) * r < (1u << 18);
 }
 
-static int refine_mode_for(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r, const float *queries)
+// what dcpq_search runs
+static int refine_form(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r, const float *queries)
+{
+    if (requested != DCPQ_REFINE_AUTO) return requested;
+    const bool split = b == 16 && split_possible(p, m, b, nq, r, queries);
+    if (r > (1u << b) / 8 && !split) return DCPQ_REFINE_TABLES;
+    return split && split_first(m, dsub, b, nq, r) ? DCPQ_REFINE_SPLIT : DCPQ_REFINE_DIRECT;
+}
+
+// the size rule that dcpq_search_refine_mode reports
+static int refine_mode_for(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r)
 {
     if (requested != DCPQ_REFINE_AUTO) return requested;
     if (r > (1u << b) / 8) return DCPQ_REFINE_TABLES;
-    return split_possible(p, m, b, nq, r, queries) && split_pays(m, dsub, b, nq, r) ? DCPQ_REFINE_SPLIT : DCPQ_REFINE_DIRECT;
+    const size_t sub = (sizeof(float) * static_cast<size_t>(dsub)) << b;
+    const bool pays = sub * ((m + 7) / 8) < (4u << 20) && sub * m > (4u << 20) && static_cast<uint64_t>(nq) * r >= (1u << 16);
+    return pays && split_possible(p, m, b, nq, r, nullptr) ? DCPQ_REFINE_SPLIT : DCPQ_REFINE_DIRECT;
 }
 
 extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codebooks, const float *derived, int m,
@@ -147,8 +164,8 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
     const int D = m * dsub;
     const int code_bytes = b / 8;
     const int tail = nq % p.chunk;
-    const int mode_full = refine_mode_for(refine_mode, p, m, dsub, b, p.chunk, r, queries);
-    const int mode_tail = tail ? refine_mode_for(refine_mode, p, m, dsub, b, tail, r, queries) : mode_full;
+    const int mode_full = refine_form(refine_mode, p, m, dsub, b, p.chunk, r, queries);
+    const int mode_tail = tail ? refine_form(refine_mode, p, m, dsub, b, tail, r, queries) : mode_full;
     if (mode_full == DCPQ_REFINE_SPLIT && !split_possible(p, m, b, p.chunk, r, queries))
         return fail(DCPQ_EINVAL, "search: DCPQ_REFINE_SPLIT: %zu bytes of sub-codes and entries per chunk do not fit the table "
                                  "region (%zu bytes), or chunk * r reaches 2^32, or the queries are not 16-byte aligned",
@@ -198,6 +215,15 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         if (mode == DCPQ_REFINE_SPLIT) {
             rc = launch_refine_split(y, codebooks, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c, dist_c,
                                      tables, base + p.off_refine, st);
+        } else if (mode == DCPQ_REFINE_DIRECT && refine_mode == DCPQ_REFINE_AUTO && b == 16 && split_possible(p, m, b, nc, r, queries) &&
+                   refine_memo_slots(m, dsub, r) != 0) {
+            // (the integer distances are not needed any more: their place holds the queries left to the split form)
+            uint32_t *left = reinterpret_cast<uint32_t *>(cand_qd);
+            rc = launch_refine_direct(y, codebooks, dsub, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c,
+                                      dist_c, base + p.off_refine, st, left);
+            if (rc) return rc;
+            rc = launch_refine_split(y, codebooks, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c, dist_c,
+                                     tables, base + p.off_refine, st, left);
         } else if (mode == DCPQ_REFINE_DIRECT) {
             rc = launch_refine_direct(y, rows, dsub, cstride, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c,
                                       dist_c, base + p.off_refine, st);
@@ -225,5 +251,5 @@ extern "C" int dcpq_search_refine_mode(int m, int dsub, int b, int nq, uint32_t 
 {
     if (nq <= 0 || !m_supported(m) || !dcpq_bits_supported(b, 1) || r == 0) return refine_mode;
     const SearchPlan p = plan_search(1, m, nq, r, b, 0);
-    return refine_mode_for(refine_mode, p, m, dsub, b, p.chunk, r, nullptr);
+    return refine_mode_for(refine_mode, p, m, dsub, b, p.chunk, r);
 }

@@ -104,6 +104,55 @@ def test_on_demand_refinement_with_r_above_the_lds_sort():
     c.check_pass_two(dids, ddist)
 
 
+@pytest.mark.parametrize("m,dsub,Q,r,distinct", [
+    (8, 20, 3, 600, 40),            # entries of repeated sub-codes computed once (rows through LDS)
+    (16, 60, 2, 2000, 900),         # ... with rows longer than the LDS parts, nearly half of the slots taken
+    (4, 36, 5, 1500, 3000),         # hardly anything repeats
+    (8, 24, 3, 9000, 1500),         # more distinct sub-codes than half of the slots: given up late; several stretches
+    (32, 5, 2, 511, 10),            # too few candidates for a set
+    (2, 18, 7, 4097, 100),          # fewer sub-quantizers than XCDs
+])
+def test_split_refinement_with_repeated_sub_codes(m, dsub, Q, r, distinct):
+    print("split refinement m=%d dsub=%d Q=%d r=%d distinct=%d" % (m, dsub, Q, r, distinct), flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(m * 1000 + r)
+    N, k = 40_000, 50
+    cb = torch.randn((m, 65536, dsub), generator=g, device=DEV)
+    values = torch.randint(-32768, 32768, (m, distinct), generator=g, device=DEV, dtype=torch.int16)
+    pick = torch.randint(0, distinct, (N, m), generator=g, device=DEV)
+    codes = torch.stack([values[j][pick[:, j]] for j in range(m)], 1).contiguous().view(torch.uint16)
+    queries = torch.randn((Q, m * dsub), generator=g, device=DEV)
+    derived = binding.derive_codebooks(cb)
+    want = binding.search(queries, cb, derived, codes, r, k, refine_mode=binding.REFINE_DIRECT)
+    got = binding.search(queries, cb, derived, codes, r, k, refine_mode=binding.REFINE_SPLIT)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_np(got[0]), to_np(want[0]))
+    np.testing.assert_array_equal(to_np(got[1]), to_np(want[1]))
+
+
+@pytest.mark.parametrize("repeats", [True, False])
+def test_queries_the_memoized_form_gives_up_are_finished_by_the_split_form(repeats):
+    # 2^18 candidates and more of rows that no cache holds: the one-kernel form is tried first; half of the queries look at
+    # codes that repeat (memoized), the others (or, in the second case, all) at codes that do not
+    print("memoized form with leftovers, repeats=%s" % repeats, flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(5)
+    m, dsub, N, Q, r, k = 8, 20, 300_000, 160, 2000, 30
+    cb = 0.1 * torch.randn((m, 65536, dsub), generator=g, device=DEV)
+    cb[:, :64] += 4.0                                           # codes below 64 lie near 4, the others near 0
+    cb[:, :64] -= cb[:, :64].mean(1, keepdim=True) - 4.0
+    codes = torch.randint(64, 65536, (N, m), generator=g, device=DEV, dtype=torch.int32)
+    if repeats:
+        codes[: N // 2] = torch.randint(0, 64, (N // 2, m), generator=g, device=DEV, dtype=torch.int32)
+    codes = codes.to(torch.int16).contiguous().view(torch.uint16)
+    queries = 0.1 * torch.randn((Q, m * dsub), generator=g, device=DEV)
+    queries[: Q // 2] += 4.0
+    derived = binding.derive_codebooks(cb)
+    ids, dist = binding.search(queries, cb, derived, codes, r, k)
+    want = binding.search(queries, cb, derived, codes, r, k, refine_mode=binding.REFINE_SPLIT)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_np(ids), to_np(want[0]))
+    np.testing.assert_array_equal(to_np(dist), to_np(want[1]))
+
+
 @pytest.mark.parametrize("case", ["few distinct sub-codes", "set too small"])
 def test_on_demand_refinement_with_memoized_entries(case):
     # The one-kernel on-demand refinement collects the distinct (sub-quantizer, sub-code) pairs of a query's
