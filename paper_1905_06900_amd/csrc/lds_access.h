@@ -21,4 +21,11 @@ __device__ inline lds_v4i lds_read_v4i(uint32_t off)
     return *reinterpret_cast<ptr_t>(static_cast<uintptr_t>(off));
 }
 
+// One byte at LDS byte offset `off`.
+__device__ inline uint32_t lds_read_u8(uint32_t off)
+{
+    typedef const uint8_t __attribute__((address_space(3))) *ptr_t;
+    return *reinterpret_cast<ptr_t>(static_cast<uintptr_t>(off));
+}
+
 }  // namespace dcpq

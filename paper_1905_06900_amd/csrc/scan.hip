@@ -382,7 +382,10 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
         // workgroups end unevenly, the more so the longer a workgroup runs).
         const uint64_t total = 128ull * p.ntiles > 2048 ? 128ull * p.ntiles : 2048;
         const uint64_t want = p.ntiles == 1 ? 256 : (total + p.ntiles - 1) / p.ntiles;
-        const uint64_t most = (rest + 16383) / 16384;
+        // (down to 4096 codes where the chip would be left half empty: 100 queries over 1 M codes are 2 tiles)
+        uint64_t least = 16384;
+        while (least > 4096 && (rest + least - 1) / least * p.ntiles < 192) least >>= 1;
+        const uint64_t most = (rest + least - 1) / least;
         uint64_t fb = want < most ? want : most;
         if (fb < 1) fb = 1;
         uint64_t cpb = (rest + fb - 1) / fb;
@@ -409,31 +412,25 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
             p.cap = static_cast<uint32_t>(share < 1024 ? 1024 : share);
         }
         p.upd = r / 16 < 16 ? 16 : r / 16;                   // appends to one slice between bound updates
-        // Candidates waiting in the wavefronts' queues are invisible to the bound.  With few queries and
-        // thousands of wavefronts they would outnumber r, so a wavefront hands its queue over as soon as
-        // it holds its share of r / 4 waiting candidates per query (between 4 and a full queue of 64).
-        {
-            const uint64_t conc = 256 / p.ntiles ? 256 / p.ntiles : 1;             // workgroups of a tile at a time
-            const uint64_t blocks = conc < p.fblocks ? conc : p.fblocks;
-            const uint64_t tile_q = Q < p.fqt ? Q : p.fqt;
-            uint64_t lim = static_cast<uint64_t>(r / 4) * tile_q / (blocks * 16);
-            p.qflush = static_cast<uint32_t>(lim < 4 ? 4 : lim > 64 ? 64 : lim);
-        }
         const uint32_t want_sort = next_pow2(2 * r);
         p.sortcap = want_sort < kSortLdsKeys ? kSortLdsKeys : want_sort;
-        // sample: runs of 256 codes spread evenly over the array, 32 r to 256 r codes (at least 64 Ki)
-        // (the larger the sample, the closer the starting bound and the fewer candidates are appended,
-        // but its cost grows with the number of queries: 256 r codes for 16 queries, 32 r from 128 on)
+        // Sample: runs of 256 codes spread evenly over the array.  The larger it is, the closer the starting bound and the
+        // fewer candidates are noted, but its cost grows with the number of queries: 32 r codes, 64 r for few
+        // queries, and no more than holds 256 of the r wanted codes (the slack of the starting bound is a
+        // third then), but at least 64 Ki.
         uint64_t mul = 4096 / (Q ? Q : 1);
-        mul = mul < 32 ? 32 : mul > 256 ? 256 : mul;
-        uint64_t s_codes = mul * r < 65536 ? 65536 : mul * r;
-        // With a pilot pass (below; worth its extra launches when the histogram of the sample would take a
-        // tenth of a millisecond or more) the sample costs several times less per code, and is taken twice as
-        // large where it is small against the array (measured at N = 1e8, r = 4000, 4096 queries: sample and
+        mul = mul < 32 ? 32 : mul > 64 ? 64 : mul;
+        uint64_t s_codes = mul * r;
+        const uint64_t enough = 256 * (n_codes / r);
+        if (s_codes > enough) s_codes = enough;
+        if (s_codes < 65536) s_codes = 65536;
+        // With a pilot pass (below; worth its three extra launches when the histogram of the sample would take more
+        // than 60 microseconds) the sample costs several times less per code, and is taken twice as large where it holds
+        // few of the wanted codes (measured at N = 1e8, r = 4000, 4096 queries: sample and
         // scan together 41.25, 40.93, 40.72, 40.90 ms with 1, 2, 4, 8 times the sample; at N = 1e7, r = 5000
         // the larger sample costs what it saves).
-        const bool want_pilot = s_codes * Q * static_cast<uint64_t>(m) >= 500000000ull;
-        if (want_pilot && n_codes / r >= 10000) s_codes *= 2;
+        const bool want_pilot = s_codes * Q * static_cast<uint64_t>(m) >= 330000000ull;
+        if (want_pilot && s_codes < 32 * (n_codes / r)) s_codes *= 2;
         if (s_codes > n_codes) s_codes = n_codes;
         p.s_unit = 256;
         p.s_nunits = static_cast<uint32_t>((s_codes + 255) / 256);
@@ -471,6 +468,20 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
         p.off_fkeys = off;   off = align_up(off + sizeof(uint64_t) * Q * p.slices * p.cap, 256);
         p.off_fsort = off;
         if (p.sortcap > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * p.sortcap, 256);
+        // Room for the candidates that a wavefront notes for the end of its workgroup: two and a half times its even share of
+        // r (of the rank wanted in the sample) candidates per query; what does not fit is appended one by one.
+        {
+            const uint64_t tile_q = Q < p.fqt ? Q : p.fqt;
+            uint64_t share = tile_q * r / (static_cast<uint64_t>(p.fblocks) * kNoteWaves);
+            if (p.pilot) {
+                const uint64_t ps = tile_q * p.pilot_r / (static_cast<uint64_t>(p.pilot_blocks) * kNoteWaves);
+                share = ps > share ? ps : share;
+            }
+            uint64_t w = (5 * share / 2 + 127) / 64 * 64;
+            p.wcap = static_cast<uint32_t>(w > 4096 ? 4096 : w);
+            const uint64_t blocks = p.fblocks > p.pilot_blocks ? p.fblocks : p.pilot_blocks;
+            p.off_notes = off; off = align_up(off + sizeof(uint64_t) * p.ntiles * blocks * kNoteWaves * p.wcap, 256);
+        }
     }
     p.total = off;
     return p;

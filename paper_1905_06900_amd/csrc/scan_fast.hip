@@ -38,10 +38,11 @@
 //    turns out too low (fewer than r appended), the query is flagged and redone by the three-pass
 //    path of scan.hip.
 //
-// 4. Appends stay off the critical path.  A query's buffer and append cursor are split into slices by
-//    the workgroup's position along the codes (same-address returning atomics serialize in the L2),
-//    and a wavefront hands its pending candidates over early when few queries face many
-//    wavefronts, so that candidates waiting in queues never outnumber r.
+// 4. Appends stay off the critical path.  A wavefront notes its candidates in memory of its own; at the end of the
+//    workgroup they are counted per query and bucket in LDS and go to their queries' buffers with one returning
+//    atomic per query (a candidate at a time, the same-address atomics paced the scan as soon as more than a few
+//    in 100000 pairs were candidates).  A query's buffer and append cursor are split into slices by the workgroup's
+//    position along the codes.  A wavefront whose notes are full appends one by one.
 //
 // 5. The inner loop is a software pipeline.  The vector instruction port of a SIMD (matrix and
 //    ordinary vector instructions share it) and the LDS are both close to full, and an LDS read
@@ -187,20 +188,31 @@ __device__ inline void transposed_low_bytes(const uint32_t (&w)[M * sizeof(CodeT
     }
 }
 
-// Appends one candidate (rec: id in bits 0..31, qd in 32..39, query-in-tile in 40..47) to slice
-// `slice` of its query's buffer (unless cap = 0) and counts it in the query's exact per-bucket histogram.  Returns the
-// query when this append is one of those (every `upd`-th of the slice) after which the query's bucket
-// bound is to be recomputed, else -1.  Kept out of line: it is the rare path and would otherwise be
-// replicated at every call site.
-__device__ __noinline__ int append_candidate(uint64_t rec, int q0, uint32_t slice, uint32_t nslices, uint32_t cap, uint32_t upd,
-                                             Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *keys)
+// Takes one candidate (rec: id in bits 0..31, query-in-tile from bit 32).  With dst given it is noted there, with its integer
+// distance in bits 32..39 and the query from bit 40, for the workgroup to append at its end; otherwise (the wavefront's
+// notes are full) it is appended at once, to slice `slice` of its query's buffer (unless cap = 0), and counted in the query's exact
+// per-bucket histogram, and the query is returned when this append is one of those (every `upd`-th of the slice) after
+// which the query's bucket bound is to be recomputed; else -1.  Kept out of line: it is the rare path and would otherwise be
+// replicated at every call site.  The integer distance is looked up again (tables at LDS offset 0): 64
+// candidates are handed over together, one per lane, so that costs less than getting it out of the accumulators.
+template <int M, int QT, typename CodeT>
+__device__ __noinline__ int take_candidate(uint64_t rec, uint64_t *dst, const CodeT *codes, int q0, uint32_t slice, uint32_t nslices,
+                                           uint32_t cap, uint32_t upd, Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *keys)
 {
-    const uint32_t q = q0 + static_cast<uint32_t>(rec >> 40);
-    const uint32_t qd = static_cast<uint32_t>(rec >> 32) & 255u;
-    if ((upd & kLimited) && qd == bound[q].t0 && static_cast<uint32_t>(rec) > bound[q].last) return -1;
+    const uint32_t id = static_cast<uint32_t>(rec), qt = static_cast<uint32_t>(rec >> 32), q = q0 + qt;
+    uint32_t low[M], sum = 0;
+    load_low_bytes<M>(codes, id, low);
+#pragma unroll
+    for (int j = 0; j < M; ++j) sum += lds_read_u8(swz_offset<QT>(j, static_cast<int>(low[j]), static_cast<int>(qt))) ^ 0x80u;
+    const uint32_t qd = min(sum, 255u);
+    if (dst) {
+        *dst = make_key(qt << 8 | qd, id);
+        return -1;
+    }
+    if ((upd & kLimited) && qd == bound[q].t0 && id > bound[q].last) return -1;
     const size_t cell = static_cast<size_t>(q) * nslices + slice;
     const uint32_t pos = atomicAdd(&count[cell], 1u);
-    if (pos < cap) keys[cell * cap + pos] = rec & 0xFFFFFFFFFFull;
+    if (pos < cap) keys[cell * cap + pos] = make_key(qd, id);
     else if (cap) atomicMin(&bound[q].t, -1);            // slice full: stop appending, query is redone
     // (cap = 0: the pilot pass, which only counts)
     atomicAdd(&chist[static_cast<size_t>(q) * 256 + qd], 1u);
@@ -211,7 +223,7 @@ template <int M, int QT, int WAVES, typename CodeT>
 __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     const CodeT *__restrict__ codes, uint64_t code_end, uint64_t block_stride, uint32_t block_groups, uint32_t total_groups,
     uint32_t gshift, uint32_t gstride, const uint8_t *__restrict__ qsw, int nq, uint32_t r, uint32_t nslices, uint32_t cap,
-    uint32_t upd, uint32_t qflush, Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *__restrict__ keys)
+    uint32_t upd, Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *keys, uint64_t *notes, uint32_t wcap)
 {
     // The codes of workgroup y (blockIdx.y) are 64-code groups y * block_groups ... (block_groups of them, fewer
     // at the end: total_groups in all); group g of the workgroup starts at code
@@ -317,14 +329,21 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     static_assert(C::QCAP == 64, "flush hands one record to each lane");
     uint32_t qlen = 0;
     const uint32_t slice = blockIdx.y % nslices;
+    // notes of this wavefront: candidates that the workgroup appends together at its end
+    uint64_t *mine = notes + (static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * (WAVES * static_cast<size_t>(wcap)) + static_cast<size_t>(wave) * wcap;
+    uint32_t nrec = 0;                                       // wave-uniform
     auto flush = [&]() {
         // the wavefront runs in lockstep; the barriers say that every push is in place before the
         // entries are read, and that every lane has read its entry before the next push overwrites it
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const bool note = nrec + qlen <= wcap;               // uniform
         int qu = -1;
-        if (static_cast<uint32_t>(lane) < qlen) qu = append_candidate(wq[lane], q0, slice, nslices, cap, upd, bound, count, chist, keys);
+        if (static_cast<uint32_t>(lane) < qlen)
+            qu = take_candidate<M, QT, CodeT>(wq[lane], note ? mine + nrec + lane : nullptr, codes, q0, slice, nslices, cap, upd, bound,
+                                              count, chist, keys);
+        if (note) nrec += qlen;
         // the queries whose bound is due, one after the other, each by the whole wavefront
         uint64_t due = __builtin_amdgcn_ballot_w64(qu >= 0);
         while (due) {                                    // uniform
@@ -486,39 +505,32 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
             // codes in this group: fewer than 64 in the last group of the stretch, none past it
             const uint32_t gbase = group_base(g);
             const int nlive = g < ngroups && gbase < cend ? static_cast<int>(min(64u, cend - gbase)) : 0;
-            // Which of the 4 UC results hold the hit(s): one compare per result, whose outcome is a lane mask
-            // in scalar registers, so that the search for the (usually single) result with a hit runs on the
-            // scalar unit and only that result is decoded on the vector unit.
+            // This lane's hits as a bit mask (bit 4 u + v: result v of step u, one instruction per result), then one round
+            // for the first hit of every lane, one for the second, ...: a chunk with many hits takes little longer than
+            // one with a single hit.
+            uint32_t hits = 0;
 #pragma unroll
-            for (int u = 0; u < UC; ++u) {
-                const int first = (p * U + uc + u) * C::CPS;    // first code of the step within the group
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (!__builtin_amdgcn_ballot_w64(acc[u][v] < 0)) continue;      // uniform
-                    // (the empty asm keeps the compiler from precomputing, and then spilling, this sum for
-                    // every step of a group outside the loop)
-                    int slot = code_slot_of(v);
-                    asm volatile("" : "+v"(slot));
-                    const int code = first + slot;
-                    const bool h = acc[u][v] < 0 && code < nlive;
-                    const uint64_t mask = __builtin_amdgcn_ballot_w64(h);
-                    if (!mask) continue;                         // uniform
-                    const uint32_t cnt = __popcll(mask);
-                    if (qlen + cnt > C::QCAP) flush();           // uniform: make room (cnt <= 64 = QCAP)
-                    if (h) {
-                        const uint32_t id = gbase + static_cast<uint32_t>(code);
-                        // result - start value + 128 M is the unsaturated sum (unsigned wrap-around is intended)
-                        const uint32_t sum = static_cast<uint32_t>(acc[u][v]) - static_cast<uint32_t>(acc0[v]) + 128u * M;
-                        const uint32_t qd = min(sum, 255u);
-                        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
-                            static_cast<uint32_t>(mask >> 32),
-                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
-                        wq[qlen + rank] = (static_cast<uint64_t>((static_cast<uint32_t>(query_of(v)) << 8) | qd) << 32) | id;
-                    }
-                    qlen = __builtin_amdgcn_readfirstlane(qlen + cnt);      // wave-uniform: keep it scalar
+            for (int x = 4 * UC - 1; x >= 0; --x)
+                hits = __builtin_amdgcn_alignbit(hits, static_cast<uint32_t>(acc[x >> 2][x & 3]), 31);    // (hits << 1) | sign
+            // (the empty asm keeps the compiler from precomputing, and then spilling, the code numbers of every step of a
+            // group outside the loop)
+            int first = (p * U + uc) * C::CPS;                     // first code of the chunk within the group
+            asm volatile("" : "+v"(first));
+            do {                                                   // uniform
+                const int x = __builtin_ctz(hits | 0x10000u), u = x >> 2, v = x & 3;
+                const int code = first + u * C::CPS + code_slot_of(v);
+                const bool h = hits != 0 && code < nlive;
+                hits &= hits - 1;
+                const uint64_t mask = __builtin_amdgcn_ballot_w64(h);
+                const uint32_t cnt = __popcll(mask);
+                if (qlen + cnt > C::QCAP) flush();                 // uniform: make room (cnt <= 64 = QCAP)
+                if (h) {
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+                    wq[qlen + rank] = make_key(static_cast<uint32_t>(query_of(v)), gbase + static_cast<uint32_t>(code));
                 }
-            }
-            if (qlen >= qflush) flush();                       // uniform: keep the invisible backlog small
+                qlen = __builtin_amdgcn_readfirstlane(qlen + cnt);          // wave-uniform: keep it scalar
+            } while (__builtin_amdgcn_ballot_w64(hits != 0));
         }
     };
 
@@ -577,6 +589,65 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
         }
     }
     flush();
+
+    // ---- the workgroup's candidates to their queries' buffers ---------------------------------
+    // One returning atomic per query and workgroup instead of one per candidate, and one count per bucket that occurs: atomics on
+    // the few cache lines of a query's cursors and counts follow each other at 13 to 20 ns (251 queries, r = 10000 from
+    // 1 M codes: 410 us, of which 30 are the scan itself).  The tables are no longer needed: their LDS holds the counts.
+    __syncthreads();
+    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem);                                    // [QT][256]
+    uint32_t *lcur = reinterpret_cast<uint32_t *>(smem + C::TAB_BYTES + C::SCR_BYTES);       // [QT] position of the next one
+    uint32_t *lt0 = lcur + QT, *llast = lt0 + QT;                                            // starting buckets and their limits
+    static_assert(QT * 256 * 4 <= C::TAB_BYTES && 3 * 4 * QT <= C::Q_BYTES, "counts in place of the tables");
+    for (int v = tid; v < QT * 256; v += WAVES * 64) lhist[v] = 0;
+    if (tid < QT) {
+        const bool limited = (upd & kLimited) && q0 + tid < nq;
+        lt0[tid] = limited ? bound[q0 + tid].t0 : 256u;
+        llast[tid] = limited ? bound[q0 + tid].last : 0u;
+    }
+    __syncthreads();
+    auto wanted = [&](uint64_t rec) {
+        const uint32_t qt = static_cast<uint32_t>(rec >> 40), qd = static_cast<uint32_t>(rec >> 32) & 255u;
+        return qd != lt0[qt] || static_cast<uint32_t>(rec) <= llast[qt];
+    };
+    for (uint32_t t = lane; t < nrec; t += 64) {
+        const uint64_t rec = mine[t];
+        if (wanted(rec)) atomicAdd(&lhist[static_cast<uint32_t>(rec >> 32)], 1u);            // (query << 8) | qd
+    }
+    __syncthreads();
+    const bool more = cap && gridDim.x * gridDim.y > 256;    // workgroups that can still use a lower bound
+    for (int qt = wave; qt < QT && q0 + qt < nq; qt += WAVES) {
+        uint32_t total = 0;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const uint32_t c = lhist[qt * 256 + 64 * z + lane];
+            if (c) atomicAdd(&chist[static_cast<size_t>(q0 + qt) * 256 + 64 * z + lane], c);
+            total += c;
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
+        if (lane == 0) lcur[qt] = total;
+    }
+    if (cap == 0) return;                                    // uniform over the grid: the pilot pass only counts
+    __syncthreads();
+    if (tid < QT && q0 + tid < nq) {
+        const uint32_t total = lcur[tid];
+        if (total) {
+            const uint32_t first = atomicAdd(&count[static_cast<size_t>(q0 + tid) * nslices + slice], total);
+            lcur[tid] = first;
+            if (first + total > cap) atomicMin(&bound[q0 + tid].t, -1);      // slice full: stop appending, query is redone
+        }
+    }
+    __syncthreads();
+    for (uint32_t t = lane; t < nrec; t += 64) {
+        const uint64_t rec = mine[t];
+        if (!wanted(rec)) continue;
+        const uint32_t qt = static_cast<uint32_t>(rec >> 40);
+        const uint32_t pos = atomicAdd(&lcur[qt], 1u);
+        if (pos < cap) keys[((static_cast<size_t>(q0) + qt) * nslices + slice) * cap + pos] = rec & 0xFFFFFFFFFFull;
+    }
+    if (more)                                                // uniform
+        for (int qt = wave; qt < QT && q0 + qt < nq; qt += WAVES) lower_bound_of(q0 + qt, r, bound, chist);
 }
 
 // Bound by its passes over the appended candidates (L2) and by the chain of short steps of one workgroup.  Dealing
@@ -784,6 +855,7 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
                          uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p, hipStream_t st)
 {
     using C = FastCfg<M, QT, WAVES>;
+    static_assert(WAVES <= kNoteWaves, "room for the notes");
     uint8_t *qsw = base + p.off_qsw;
     Bound *bound = reinterpret_cast<Bound *>(base + p.off_bound);
     uint32_t *fcount = reinterpret_cast<uint32_t *>(base + p.off_fcount);
@@ -791,6 +863,7 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     uint32_t *shist = reinterpret_cast<uint32_t *>(base + p.off_shist);
     uint64_t *fkeys = reinterpret_cast<uint64_t *>(base + p.off_fkeys);
     uint64_t *fsort = reinterpret_cast<uint64_t *>(base + p.off_fsort);
+    uint64_t *notes = reinterpret_cast<uint64_t *>(base + p.off_notes);
     uint32_t *done = reinterpret_cast<uint32_t *>(base + p.off_done);
     uint32_t *flags = reinterpret_cast<uint32_t *>(base + p.off_flags);
     int *qlist = reinterpret_cast<int *>(base + p.off_qlist);
@@ -820,8 +893,8 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
         // (255, and with it the redo path, if the counts never get there).
         DCPQ_LAUNCH(kStageScanHist, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.pilot_blocks), dim3(WAVES * 64),
                     C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.pilot_runs) * p.s_stride, p.pilot_runs * (p.s_unit / 64),
-                    p.s_nunits * (p.s_unit / 64), 2u, static_cast<uint32_t>(p.s_stride), qsw, nq, p.pilot_r, p.slices, 0u, 16u, 4u,
-                    bound, fcount, chist, fkeys);
+                    p.s_nunits * (p.s_unit / 64), 2u, static_cast<uint32_t>(p.s_stride), qsw, nq, p.pilot_r, p.slices, 0u, 16u,
+                    bound, fcount, chist, fkeys, notes, p.wcap);
         DCPQ_CHECK_LAUNCH("scan_fast_kernel<pilot>");
         rc = launch_sample_threshold(chist, nq, p.pilot_r, 0, bound, st);      // 0: the counted codes' own pilot_r-th smallest
         if (rc) return rc;
@@ -831,8 +904,8 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     // the scan: one contiguous stretch of codes per workgroup
     DCPQ_LAUNCH(kStageScanFast, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.fblocks), dim3(WAVES * 64),
                 C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.codes_per_block), p.codes_per_block / 64,
-                static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd | (p.pilot ? 0u : kLimited), p.qflush, bound,
-                fcount, chist, fkeys);
+                static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd | (p.pilot ? 0u : kLimited), bound,
+                fcount, chist, fkeys, notes, p.wcap);
     DCPQ_CHECK_LAUNCH("scan_fast_kernel");
     // exact selection, and the list of queries to redo
     rc = launch_fast_select(fkeys, fcount, chist, nq, r, p.slices, p.cap, p.sortcap, n_codes, fsort, cand_id, cand_qd, flags, st, qlist, nflag);

@@ -22,6 +22,7 @@ inline uint32_t next_pow2(uint32_t x)
 constexpr int kFastSlices = 16;      // at most; fewer when there are fewer workgroups along the codes
 
 constexpr uint32_t kPilotEvery = 16;
+constexpr int kNoteWaves = 16;       // wavefronts per workgroup of the single-pass kernel, at most
 
 // Running bucket bound of a query in the single-pass scans (one 16-byte record per query).
 struct __attribute__((aligned(16))) Bound {
@@ -53,7 +54,7 @@ struct ScanPlan {
     uint32_t slices;          // slices per query: min(kFastSlices, fblocks)
     uint32_t cap;             // candidate-buffer entries per query and slice
     uint32_t upd;             // appended candidates between two bound updates
-    uint32_t qflush;          // a wavefront appends its pending candidates once it holds this many
+    uint32_t wcap;            // candidates a wavefront can note until its workgroup ends
     uint32_t sortcap;         // keys the final selection can sort (power of two)
     uint32_t s_unit, s_nunits;    // sample: s_nunits runs of s_unit codes ...
     uint64_t s_stride;            // ... starting every s_stride codes
@@ -76,6 +77,7 @@ struct ScanPlan {
     size_t off_qsw;       // uint8 [ntiles][fast_table_bytes(m, fqt)]
     size_t off_fkeys;     // uint64 [nq][slices][cap]
     size_t off_fsort;     // uint64 [nq][sortcap], only when sortcap exceeds the LDS sort
+    size_t off_notes;     // uint64 [ntiles * max(fblocks, pilot_blocks)][kNoteWaves][wcap]
     size_t total;
 };
 // mode: DCPQ_SCAN_AUTO picks the single-pass query tile from the batch size; DCPQ_SCAN_TILE16/32/64 force it
