@@ -24,13 +24,16 @@ namespace dcpq {
 
 constexpr int kIvfUnitsPerQuery = 1024;   // upper bound of scan units per query (unit size adapts)
 constexpr int kIvfMaxProbe = 512;         // nprobe supported by the per-query planning kernels
-constexpr uint32_t kIvfSampleStep = 32;   // the first 1 / kIvfSampleStep of every probed list is the sample that gives the scan its starting bounds
-constexpr int kIvfSampleUnits = kIvfMaxProbe + kIvfUnitsPerQuery / static_cast<int>(kIvfSampleStep);   // sample units a query can have
+constexpr uint32_t kIvfSampleStep = 32;   // the first 1 / kIvfSampleStep of every probed list (at most) is the sample that gives the scan its starting bounds
+constexpr uint32_t kIvfBins = 65536;      // bins of list ids that the scan's work is ordered by
+constexpr uint32_t kIvfMinPart = 512;     // codes a workgroup of the single-pass scan takes at least
+constexpr uint32_t kIvfNotes = 1024;      // candidates it can note until it has walked its part
 
 struct IvfUnit {
     uint64_t begin;    // first code of the unit (global position)
     uint32_t count;    // codes in the unit
-    uint32_t p;        // index of the list in the query's probe order (selects the tables)
+    uint32_t p;        // index of the list in the query's probe order (selects the tables); in the single-pass
+                       // scan's list of parts q * nprobe + p
 };
 
 // ------------------------------------------------------------------------------------------------
@@ -384,88 +387,162 @@ __global__ __launch_bounds__(256) void ivf_qmax_kernel(const float *__restrict__
 // Scan step: per-query unit lists.
 // ------------------------------------------------------------------------------------------------
 // One workgroup per query: probed lists sorted by list id (so that units follow increasing vector
-// id), a unit size that keeps the query within kIvfUnitsPerQuery units, and the unit records.
+// id), a unit size that keeps the query within kIvfUnitsPerQuery units, and the unit records; and the query's
+// share of the single-pass scan's work, cut into about `parts` parts of equal length (no part spans two lists).
+// The parts of all queries lie in one list that `cursor` fills.  Without `bins` a query's parts are written here, one
+// behind the other; with them only their places are drawn (`rank`, within the bin of the list), ivf_bin_base_kernel
+// and ivf_parts_kernel do the rest.
+// (Everything after the sort is done by all threads at once, two lists each: one thread's walk over 64 lists, with a
+// 64-bit division each, and a round of loads per list took 57 us for 1024 queries.)
+__device__ inline uint32_t ivf_bin_of(uint32_t list, uint32_t nlist)
+{
+    return nlist <= kIvfBins ? list : static_cast<uint32_t>(static_cast<uint64_t>(list) * kIvfBins / nlist);
+}
+
 __global__ __launch_bounds__(256) void ivf_plan_kernel(const int32_t *__restrict__ probe, int nprobe,
-                                                      const int64_t *__restrict__ offsets, uint32_t r,
-                                                      IvfUnit *__restrict__ units, uint32_t *__restrict__ nunits,
-                                                      uint32_t *__restrict__ count, IvfUnit *__restrict__ sunits,
-                                                      uint32_t *__restrict__ nsunits, uint32_t *__restrict__ probed)
+                                                      const int64_t *__restrict__ offsets, uint32_t nlist, uint32_t r,
+                                                      uint32_t parts, IvfUnit *__restrict__ units,
+                                                      uint32_t *__restrict__ nunits, uint32_t *__restrict__ count,
+                                                      uint32_t *__restrict__ probed, uint32_t *__restrict__ part_of,
+                                                      uint32_t *__restrict__ bins, uint32_t *__restrict__ rank,
+                                                      uint32_t *__restrict__ cursor, IvfUnit *__restrict__ items)
 {
     __shared__ uint64_t key[kIvfMaxProbe];         // (list id << 32) | probe position
-    __shared__ uint32_t ubase[kIvfMaxProbe + 1];
-    __shared__ uint32_t sbase[kIvfMaxProbe + 1];   // the same for the sample units
-    __shared__ uint64_t lsize[kIvfMaxProbe];       // codes in the s-th probed list (lists in id order)
-    __shared__ uint32_t s_unit;
-    const int q = blockIdx.x, tid = threadIdx.x;
+    __shared__ uint32_t ubase[kIvfMaxProbe + 1];   // first unit of the s-th probed list (lists in id order)
+    __shared__ uint32_t pbase[kIvfMaxProbe + 1];   // first part
+    __shared__ uint64_t lbeg[kIvfMaxProbe];        // position and number of its codes
+    __shared__ uint64_t lsize[kIvfMaxProbe];
+    __shared__ unsigned long long s_total;
+    __shared__ uint32_t wsum[2][4], s_base;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) s_total = 0;
     uint32_t np2 = 1;
     while (np2 < static_cast<uint32_t>(nprobe)) np2 <<= 1;
     for (uint32_t p = tid; p < np2; p += 256)
         key[p] = p < static_cast<uint32_t>(nprobe)
                      ? make_key(static_cast<uint32_t>(probe[static_cast<size_t>(q) * nprobe + p]), p) : ~0ull;
     bitonic_sort(key, np2);
-    // (the list sizes are fetched by all threads at once: the planning below is one thread's walk over them)
     for (int s = tid; s < nprobe; s += 256) {
         const int l = static_cast<int>(key[s] >> 32);
-        lsize[s] = static_cast<uint64_t>(offsets[l + 1] - offsets[l]);
+        lbeg[s] = static_cast<uint64_t>(offsets[l]);
+        lsize[s] = static_cast<uint64_t>(offsets[l + 1]) - lbeg[s];
+        atomicAdd(&s_total, static_cast<unsigned long long>(lsize[s]));
     }
     __syncthreads();
+    const uint64_t total = s_total;
+    // three units per probed list on average, and at least 512 less one per list in all (measured: fewer,
+    // longer units leave the chip unevenly loaded, more of them pay the latency of a wavefront's first
+    // loads too often); never more than the unit table holds
+    uint64_t want = 4ull * nprobe < 512 ? 512 : 4ull * nprobe;
+    if (want > static_cast<uint64_t>(kIvfUnitsPerQuery)) want = kIvfUnitsPerQuery;
+    uint64_t unit = (total + (want - nprobe) - 1) / (want - nprobe);
+    unit = (unit + 63) / 64 * 64;
+    if (unit < 256) unit = 256;
+    uint64_t part = (total + parts - 1) / parts;
+    part = (part + 255) / 256 * 256;
+    if (part < kIvfMinPart) part = kIvfMinPart;
+    // exclusive prefix sums of the units and parts per list, two lists per thread
+    uint32_t nu[2], ni[2], incl[2];
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+        const int s = 2 * tid + z;
+        nu[z] = s < nprobe ? static_cast<uint32_t>((lsize[s] + unit - 1) / unit) : 0u;
+        ni[z] = s < nprobe ? static_cast<uint32_t>((lsize[s] + part - 1) / part) : 0u;
+    }
+    incl[0] = nu[0] + nu[1];
+    incl[1] = ni[0] + ni[1];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t a = __shfl(incl[0], lane >= o ? lane - o : lane), b = __shfl(incl[1], lane >= o ? lane - o : lane);
+        if (lane >= o) { incl[0] += a; incl[1] += b; }
+    }
+    if (lane == 63) { wsum[0][wave] = incl[0]; wsum[1][wave] = incl[1]; }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) { incl[0] += wsum[0][w]; incl[1] += wsum[1][w]; }
+#pragma unroll
+    for (int z = 1; z >= 0; --z) {
+        incl[0] -= nu[z];
+        incl[1] -= ni[z];
+        if (2 * tid + z < nprobe) { ubase[2 * tid + z] = incl[0]; pbase[2 * tid + z] = incl[1]; }
+    }
+    const uint32_t all_units = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3];
+    const uint32_t all_parts = wsum[1][0] + wsum[1][1] + wsum[1][2] + wsum[1][3];
     if (tid == 0) {
-        uint64_t total = 0;
-        for (int s = 0; s < nprobe; ++s) total += lsize[s];
-        // three units per probed list on average, and at least 512 less one per list in all (measured: fewer,
-        // longer units leave the chip unevenly loaded, more of them pay the latency of a wavefront's first
-        // loads too often); never more than the unit table holds
-        uint64_t want = 4ull * nprobe < 512 ? 512 : 4ull * nprobe;
-        if (want > static_cast<uint64_t>(kIvfUnitsPerQuery)) want = kIvfUnitsPerQuery;
-        uint64_t unit = (total + (want - nprobe) - 1) / (want - nprobe);
-        unit = (unit + 63) / 64 * 64;
-        if (unit < 256) unit = 256;
-        uint32_t u = 0, su = 0;
-        for (int s = 0; s < nprobe; ++s) {
-            const uint64_t size = lsize[s];
-            ubase[s] = u;
-            u += static_cast<uint32_t>((size + unit - 1) / unit);
-            sbase[s] = su;                                   // (at most one unit per list and one per kIvfSampleStep scan units)
-            su += static_cast<uint32_t>(((size + kIvfSampleStep - 1) / kIvfSampleStep + unit - 1) / unit);
-        }
-        ubase[nprobe] = u;
-        sbase[nprobe] = su;
-        nsunits[q] = su;
-        s_unit = static_cast<uint32_t>(unit);
-        nunits[q] = u;
+        ubase[nprobe] = all_units;
+        pbase[nprobe] = all_parts;
+        nunits[q] = all_units;
+        part_of[q] = static_cast<uint32_t>(part);
         count[q] = static_cast<uint32_t>(total < r ? total : r);
         probed[q] = static_cast<uint32_t>(total < 0xFFFFFFFFull ? total : 0xFFFFFFFFull);     // codes in the probed lists
+        if (!bins) s_base = atomicAdd(cursor, all_parts);
     }
     __syncthreads();
-    const uint32_t unit = s_unit;
-    // The sample that gives the scan its starting bound: the first ceil(size / kIvfSampleStep) codes of every probed
-    // list (a list keeps its codes in no order that matters here), so that every list is in it with the same weight; cut
-    // into units no longer than the scan's, so that a long list's share is not one wavefront's work.
-    for (int s = 0; s < nprobe; ++s) {
-        const int l = static_cast<int>(key[s] >> 32);
-        const uint64_t lo = static_cast<uint64_t>(offsets[l]), size = static_cast<uint64_t>(offsets[l + 1]) - lo;
-        const uint64_t part = (size + kIvfSampleStep - 1) / kIvfSampleStep;
-        const uint32_t nu = sbase[s + 1] - sbase[s];
-        for (uint32_t c = tid; c < nu; c += 256) {
-            IvfUnit rec;
-            rec.begin = lo + static_cast<uint64_t>(c) * unit;
-            rec.count = static_cast<uint32_t>(min(static_cast<uint64_t>(unit), part - static_cast<uint64_t>(c) * unit));
-            rec.p = static_cast<uint32_t>(key[s] & 0xFFFFFFFFu);
-            sunits[static_cast<size_t>(q) * kIvfSampleUnits + sbase[s] + c] = rec;
+    // the list that holds entry x of a prefix array: the last s with base[s] <= x
+    auto list_of = [&](const uint32_t *base, uint32_t x) {
+        uint32_t lo = 0, hi = static_cast<uint32_t>(nprobe);
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (base[mid] <= x) lo = mid; else hi = mid;
+        }
+        return lo;
+    };
+    for (uint32_t x = tid; x < all_units; x += 256) {
+        const uint32_t s = list_of(ubase, x);
+        const uint64_t first = static_cast<uint64_t>(x - ubase[s]) * unit;
+        units[static_cast<size_t>(q) * kIvfUnitsPerQuery + x] =
+            IvfUnit{lbeg[s] + first, static_cast<uint32_t>(min(unit, lsize[s] - first)), static_cast<uint32_t>(key[s])};
+    }
+    if (bins) {
+        for (uint32_t s = tid; s < static_cast<uint32_t>(nprobe); s += 256) {
+            const uint32_t n = pbase[s + 1] - pbase[s];
+            if (n) rank[static_cast<size_t>(q) * nprobe + static_cast<uint32_t>(key[s])] =
+                atomicAdd(&bins[ivf_bin_of(static_cast<uint32_t>(key[s] >> 32), nlist)], n);
+        }
+    } else {
+        for (uint32_t x = tid; x < all_parts; x += 256) {
+            const uint32_t s = list_of(pbase, x);
+            const uint64_t first = static_cast<uint64_t>(x - pbase[s]) * part;
+            items[s_base + x] = IvfUnit{lbeg[s] + first, static_cast<uint32_t>(min(part, lsize[s] - first)),
+                                        static_cast<uint32_t>(q) * nprobe + static_cast<uint32_t>(key[s])};
         }
     }
-    for (int s = 0; s < nprobe; ++s) {
-        const int l = static_cast<int>(key[s] >> 32);
-        const uint64_t lo = static_cast<uint64_t>(offsets[l]), size = static_cast<uint64_t>(offsets[l + 1]) - lo;
-        const uint32_t nu = ubase[s + 1] - ubase[s];
-        for (uint32_t c = tid; c < nu; c += 256) {
-            IvfUnit rec;
-            rec.begin = lo + static_cast<uint64_t>(c) * unit;
-            rec.count = static_cast<uint32_t>(min(static_cast<uint64_t>(unit), size - static_cast<uint64_t>(c) * unit));
-            rec.p = static_cast<uint32_t>(key[s] & 0xFFFFFFFFu);
-            units[static_cast<size_t>(q) * kIvfUnitsPerQuery + ubase[s] + c] = rec;
-        }
+}
+
+// bins[b]: number of parts in bin b -> place of its first part (in any order of 256-bin blocks).
+__global__ __launch_bounds__(256) void ivf_bin_base_kernel(uint32_t *__restrict__ bins, uint32_t nbins, uint32_t *__restrict__ cursor)
+{
+    __shared__ uint32_t wsum[4], s_base;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t b = blockIdx.x * 256 + tid;
+    const uint32_t c = b < nbins ? bins[b] : 0u;
+    uint32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t other = __shfl(incl, lane >= o ? lane - o : lane);
+        if (lane >= o) incl += other;
     }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    if (tid == 0) s_base = atomicAdd(cursor, wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+    for (int w = 0; w < wave; ++w) incl += wsum[w];
+    __syncthreads();
+    if (b < nbins) bins[b] = s_base + incl - c;
+}
+
+// The parts of (query, probed list) pair e, at the places drawn for them; a thread per pair.
+__global__ __launch_bounds__(256) void ivf_parts_kernel(const int32_t *__restrict__ probe, uint32_t npairs, uint32_t nprobe,
+                                                       const int64_t *__restrict__ offsets, uint32_t nlist,
+                                                       const uint32_t *__restrict__ bins, const uint32_t *__restrict__ rank,
+                                                       const uint32_t *__restrict__ part_of, IvfUnit *__restrict__ items)
+{
+    const uint32_t e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= npairs) return;
+    const uint32_t l = static_cast<uint32_t>(probe[e]), part = part_of[e / nprobe];
+    const uint64_t lo = static_cast<uint64_t>(offsets[l]), size = static_cast<uint64_t>(offsets[l + 1]) - lo;
+    if (size == 0) return;
+    IvfUnit *out = items + bins[ivf_bin_of(l, nlist)] + rank[e];
+    for (uint64_t first = 0; first < size; first += part)
+        *out++ = IvfUnit{lo + first, static_cast<uint32_t>(min(static_cast<uint64_t>(part), size - first)), e};
 }
 
 enum IvfMode { kIvfHist = 0, kIvfTieCount = 1, kIvfCollect = 2 };
@@ -478,8 +555,7 @@ constexpr int kIvfAhead = 4;     // 64-code groups whose codes a wavefront loads
 template <int M, int MODE, typename CodeT>
 __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
                                      const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab,
-                                     int nprobe, uint32_t r, uint32_t unit_step,
-                                     const uint32_t *__restrict__ flags, uint32_t *__restrict__ hist,
+                                     int nprobe, uint32_t r, uint32_t *__restrict__ hist,
                                      const uint32_t *__restrict__ thr, uint32_t *__restrict__ tie,
                                      uint32_t *__restrict__ counter, uint64_t *__restrict__ keys)
 {
@@ -488,8 +564,7 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
     const uint32_t u = blockIdx.x * 4 + wave;
     uint8_t *tab = smem + wave * (M * 256);                                      // [M][256]
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + 4 * M * 256) + wave * 256;   // kIvfHist only
-    // every unit_step-th unit only (sampling), and only the queries with a flag when flags are given
-    const bool active = u < nunits[q] && u % unit_step == 0 && (!flags || flags[q] != 0);
+    const bool active = u < nunits[q];
     IvfUnit un{0, 0, 0};
     if (active) un = units[static_cast<size_t>(q) * kIvfUnitsPerQuery + u];
     if (active) {
@@ -577,37 +652,23 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
 }
 
 // Grid (kIvfUnitsPerQuery / 4, min(nq, kIvfRedoRows)): a wavefront takes the same unit number of every
-// kIvfRedoRows-th query.  With flags given (nq of them and, as entry nq, whether any is set: ivf_any_flag_kernel)
-// only flagged queries are scanned, and since that is the rare case
+// kIvfRedoRows-th query.  Only flagged queries are scanned (*nflag of them), and since that is the rare case
 // (the three passes redo what the single pass could not finish) a row of workgroups serves many queries, so
 // that a launch with nothing to do costs a few thousand empty workgroups, not one per (query, 4 units).
 constexpr int kIvfRedoRows = 32;
 
-// flags[nq] = whether any of flags[0 .. nq) is set.  One workgroup.
-__global__ __launch_bounds__(1024) void ivf_any_flag_kernel(uint32_t *__restrict__ flags, int nq)
-{
-    __shared__ uint32_t any;
-    if (threadIdx.x == 0) any = 0;
-    __syncthreads();
-    uint32_t mine = 0;
-    for (int q = threadIdx.x; q < nq; q += 1024) mine |= flags[q];
-    if (mine) any = 1;                                       // benign race: every writer stores 1
-    __syncthreads();
-    if (threadIdx.x == 0) flags[nq] = any;
-}
-
 template <int M, int MODE, typename CodeT>
 __global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
                                                       const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab,
-                                                      int nprobe, int nq, uint32_t r, uint32_t unit_step,
+                                                      int nprobe, int nq, uint32_t r, const uint32_t *__restrict__ nflag,
                                                       const uint32_t *__restrict__ flags, uint32_t *__restrict__ hist,
                                                       const uint32_t *__restrict__ thr, uint32_t *__restrict__ tie,
                                                       uint32_t *__restrict__ counter, uint64_t *__restrict__ keys)
 {
-    if (flags && flags[nq] == 0) return;                     // no query is flagged: one load, not nq / gridDim.y
+    if (*nflag == 0) return;                                 // no query is flagged: one load, not nq / gridDim.y
     for (int q = blockIdx.y; q < nq; q += gridDim.y) {
-        if (flags && flags[q] == 0) continue;
-        ivf_scan_unit<M, MODE, CodeT>(q, codes, units, nunits, qtab, nprobe, r, unit_step, flags, hist, thr, tie, counter, keys);
+        if (flags[q] == 0) continue;
+        ivf_scan_unit<M, MODE, CodeT>(q, codes, units, nunits, qtab, nprobe, r, hist, thr, tie, counter, keys);
         // the next query's tables overwrite this one's: every lane is done with them
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -615,20 +676,28 @@ __global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__
     }
 }
 
-// The same scan in ONE pass over the probed lists (each pass reads every probed code from HBM, and no
-// two queries share them, so passes are what the scan costs).  As in the flat single pass, a query has
+// The same scan in ONE pass over the probed lists (each pass reads every probed code from memory, so passes are what
+// the scan costs).  As in the flat single pass, a query has
 // a running bucket bound, initialised from the histogram of a sample (the first 1 / kIvfSampleStep of every list) and
 // lowered as exact per-bucket counts of appended candidates accumulate; pairs at or below the bound are
 // appended to the query's sliced buffer, the exact r are selected afterwards, and a query whose buffer
 // overflows (or whose lists hold fewer than r codes) is redone by the three passes above.
-// Grid (nq, kIvfUnitsPerQuery / 4): the query index varies fastest, so only a few wavefronts of one
-// query run at a time and the candidates waiting in their queues stay few against r.
 //
-// The kernel is bound by the stream of codes from HBM, so a wavefront is built around keeping that
+// One workgroup per part (a run of codes of one list, for one query): the tables are read once per part, and the
+// wavefronts walk it together, one set of codes after the other.  The parts are ordered by list, and consecutive ones
+// go to the same XCD (workgroup i runs on XCD i mod 8), so that the queries that probe the same list read
+// it at about the same time through one second-level cache, while the parts of one query are spread over the whole
+// launch.
+//
+// Candidates are noted in LDS and appended together when the part is done: one returning atomic on the query's cursor
+// and one addition per bucket that occurs, instead of one per candidate on the few counters that all of a query's
+// candidates share (they serialize in the L2 at 13 to 20 ns each).
+// The bound is lowered at these points only; it starts where a few r candidates are expected.
+//
+// The kernel is bound by the stream of codes, so a wavefront is built around keeping that
 // stream in flight: the codes stay in registers as loaded (their low bytes are picked out when they
 // are looked up), in two sets of kIvfRawWords words per lane; while one set is processed the loads
-// of the next are under way, the first of them issued together with the load of the unit's tables,
-// and nothing in the kernel waits for another wavefront.
+// of the next are under way, the first of them issued together with the load of the part's tables.
 constexpr int kIvfRawWords = 16;         // registers per lane and set that hold codes in flight
 
 // The bytes of code i as stored, in RW words (a narrower code is zero-extended).
@@ -663,142 +732,261 @@ __device__ inline uint32_t low_byte_of(const uint32_t (&w)[RW], int j)
     else return (w[j >> 2] >> (8 * (j & 3))) & 255u;
 }
 
-// SAMPLE: the pass that finds the starting bounds -- `units` and `nunits` are the sample's (the first
-// 1 / kIvfSampleStep of every probed list), nothing is appended, and `count` is the per-query histogram of the
-// integer distances ([nq][256]).
-template <int M, typename CodeT, bool SAMPLE>
-__global__ __launch_bounds__(256) void ivf_scan_single_kernel(const CodeT *__restrict__ codes,
-                                                             const IvfUnit *__restrict__ units,
-                                                             const uint32_t *__restrict__ nunits,
-                                                             const uint8_t *__restrict__ qtab, int nprobe, uint32_t r,
-                                                             uint32_t cap, uint32_t upd, uint32_t qflush, Bound *bound,
-                                                             uint32_t *count, uint32_t *chist, uint64_t *__restrict__ keys)
+// Codes of one set of a wavefront, from `p` codes behind `begin`; past the end (`hi` codes behind it) the last code is
+// read again (a valid address), to be masked by the caller.
+template <int M, typename CodeT, int GPB, int RW>
+__device__ inline void load_raw_set(const CodeT *__restrict__ codes, uint64_t begin, uint32_t base0, uint32_t hi, uint32_t (&w)[GPB][RW])
 {
-    constexpr int BPC = M * static_cast<int>(sizeof(CodeT));
-    constexpr int RW = BPC >= 4 ? BPC / 4 : 1;                // words per code
-    constexpr int GPB = RW >= kIvfRawWords ? 1 : kIvfRawWords / RW;   // 64-code groups per set
+    const uint32_t lane = threadIdx.x & 63;
+#pragma unroll
+    for (int g = 0; g < GPB; ++g) {
+        const uint32_t k = base0 + g * 64 + lane;
+        load_raw_code<M, CodeT, RW>(codes, begin + (k < hi ? k : hi - 1), w[g]);
+    }
+}
+
+template <int M, typename CodeT>
+struct IvfRaw {
+    static constexpr int BPC = M * static_cast<int>(sizeof(CodeT));
+    static constexpr int RW = BPC >= 4 ? BPC / 4 : 1;                // words per code
+    static constexpr int GPB = RW >= kIvfRawWords ? 1 : kIvfRawWords / RW;   // 64-code groups per set
+    static constexpr uint32_t SET = 64 * GPB;
+};
+
+template <int M, typename CodeT>
+__global__ __launch_bounds__(256) void ivf_scan_parts_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ items,
+                                                            const uint32_t *__restrict__ nitems,
+                                                            const uint8_t *__restrict__ qtab, uint32_t nprobe, uint32_t r,
+                                                            uint32_t cap, uint32_t upd, Bound *bound,
+                                                            uint32_t *count, uint32_t *chist, uint64_t *__restrict__ keys)
+{
+    constexpr int RW = IvfRaw<M, CodeT>::RW, GPB = IvfRaw<M, CodeT>::GPB;
+    constexpr uint32_t SET = IvfRaw<M, CodeT>::SET;
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int q = blockIdx.x;
-    const uint32_t u = blockIdx.y * 4 + wave;
-    // (SAMPLE: `units` and `nunits` are the sample's, kIvfSampleUnits records per query)
-    if (u >= nunits[q]) return;                              // uniform per wavefront; the kernel has no workgroup barrier
-    uint8_t *tab = smem + wave * (M * 256);                                           // [M][256]
-    uint64_t *wq = reinterpret_cast<uint64_t *>(smem + 4 * M * 256) + wave * 64;      // pending candidates
-    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + 4 * M * 256) + wave * 256;  // SAMPLE: this wavefront's histogram
-    if constexpr (SAMPLE) {
-#pragma unroll
-        for (int b = 0; b < 4; ++b) lhist[lane + 64 * b] = 0;
-    }
-    const IvfUnit un = units[static_cast<size_t>(q) * (SAMPLE ? kIvfSampleUnits : kIvfUnitsPerQuery) + u];
-    if (un.count == 0) return;                               // uniform (the planner makes no empty units)
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // consecutive parts on one XCD: each of the eight takes an eighth of the list
+    const uint32_t n_all = *nitems, per = (n_all + 7) / 8;
+    const uint64_t idx = static_cast<uint64_t>(blockIdx.y) * gridDim.x + blockIdx.x;      // gridDim.x is a multiple of 8
+    const uint64_t at = (idx & 7) * per + (idx >> 3);
+    if ((idx >> 3) >= per || at >= n_all) return;                // uniform
+    const IvfUnit un = items[at];
+    const int q = static_cast<int>(un.p / nprobe);
+    uint8_t *tab = smem;                                                              // [M][256]
+    uint64_t *notes = reinterpret_cast<uint64_t *>(smem + M * 256);                   // [kIvfNotes]
+    __shared__ uint32_t s_n, s_first, bhist[256];
 
-    auto load_set = [&](uint32_t base0, uint32_t (&w)[GPB][RW]) {
-#pragma unroll
-        for (int g = 0; g < GPB; ++g) {
-            const uint32_t k = base0 + g * 64 + lane;
-            // past the end of the unit the last code is read again (a valid address); it is masked below
-            load_raw_code<M, CodeT, RW>(codes, un.begin + (k < un.count ? k : un.count - 1), w[g]);
-        }
-    };
+    // The wavefronts take the part's sets of codes in turn; a part that has less than a set for each is cut evenly.
+    const bool turns = un.count >= 4 * SET;
+    const uint32_t strip = turns ? SET : (un.count + 255) / 256 * 64;
+    const uint32_t lo = wave * strip, hi = turns ? un.count : min(un.count, lo + strip);
     auto load_bound = [&]() {
-        if constexpr (SAMPLE) return 0;
         const int t = __hip_atomic_load(&bound[q].t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return t >= 255 ? 0x7fffffff : t;
     };
-    // The unit's first codes and its tables travel together: the code loads are issued first, the table words
-    // follow them and go from their registers straight to LDS.  (Held in an array across the code loads, the table
-    // words were put in scratch memory by the compiler: 2 KB written and read back per wavefront, a gigabyte of
-    // traffic per batch at 1024 queries x 64 lists.)
+    // The part's first codes and its tables travel together: the code loads are issued first, the table words
+    // follow them and go from their registers straight to LDS.
     uint32_t wa[GPB][RW], wb[GPB][RW];
-    load_set(0, wa);
+    if (lo < hi) load_raw_set<M, CodeT, GPB, RW>(codes, un.begin, lo, hi, wa);       // uniform per wavefront
     int T = load_bound();
     {
         constexpr int NTW = M * 256 / 16;                                // 16-byte words of the tables
-        const uint4 *src = reinterpret_cast<const uint4 *>(qtab + (static_cast<size_t>(q) * nprobe + un.p) * M * 256);
+        const uint4 *src = reinterpret_cast<const uint4 *>(qtab + static_cast<size_t>(un.p) * M * 256);
         uint4 *dst = reinterpret_cast<uint4 *>(tab);
 #pragma unroll
-        for (int v = 0; v < (NTW + 63) / 64; ++v)
-            if (NTW % 64 == 0 || lane + 64 * v < NTW) dst[lane + 64 * v] = src[lane + 64 * v];
+        for (int v = 0; v < (NTW + 255) / 256; ++v)
+            if (NTW % 256 == 0 || tid + 256 * v < NTW) dst[tid + 256 * v] = src[tid + 256 * v];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    bhist[tid] = 0;
+    if (tid == 0) s_n = 0;
+    __syncthreads();
 
-    const size_t cell = static_cast<size_t>(q) * kFastSlices + u % kFastSlices;
-    uint32_t qlen = 0;                                   // wave-uniform
-    auto flush = [&]() {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const size_t cell = static_cast<size_t>(q) * kFastSlices + static_cast<uint32_t>(at) % kFastSlices;
+    // n keys, the wavefront's lane l holding key l of them, straight to the query's buffer
+    auto append = [&](uint64_t key, bool mine, uint32_t rank, uint32_t n) {
         uint32_t first = 0;
-        if (lane == 0) first = atomicAdd(&count[cell], qlen);
-        first = __builtin_amdgcn_readfirstlane(__shfl(first, 0, kWave));
-        if (static_cast<uint32_t>(lane) < qlen) {
-            const uint64_t key = wq[lane];
-            if (first + lane < cap) keys[cell * cap + first + lane] = key;
+        if (lane == 0) first = atomicAdd(&count[cell], n);
+        first = __builtin_amdgcn_readfirstlane(first);
+        if (mine) {
+            if (first + rank < cap) keys[cell * cap + first + rank] = key;
             else atomicMin(&bound[q].t, -1);               // slice full: stop appending, the query is redone
             atomicAdd(&chist[static_cast<size_t>(q) * 256 + static_cast<uint32_t>(key >> 32)], 1u);
         }
-        if (first / upd != (first + qlen) / upd) lower_bound_of(q, r, bound, chist);   // uniform
-        qlen = 0;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (first / upd != (first + n) / upd) lower_bound_of(q, r, bound, chist);   // uniform
     };
     auto process = [&](uint32_t base0, const uint32_t (&w)[GPB][RW], int bound) {
 #pragma unroll
         for (int g = 0; g < GPB; ++g) {
             const uint32_t base = base0 + g * 64;
-            if (base >= un.count) break;                              // uniform
+            if (base >= hi) break;                                    // uniform
             const uint32_t k = base + lane;
             uint32_t s = 0;
 #pragma unroll
             for (int j = 0; j < M; ++j) s += tab[j * 256 + low_byte_of<CodeT, RW>(w[g], j)];
             const uint32_t qd = min(s, 255u);
-            if constexpr (SAMPLE) {
-                if (k < un.count) atomicAdd(&lhist[qd], 1u);
-                continue;
-            }
-            const bool h = k < un.count && static_cast<int>(qd) <= bound;
+            const bool h = k < hi && static_cast<int>(qd) <= bound;
             const uint64_t mask = __builtin_amdgcn_ballot_w64(h);
             if (!mask) continue;                                      // uniform
             const uint32_t cnt = __popcll(mask);
-            if (qlen + cnt > 64) flush();                             // uniform
-            if (h) {
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
-                wq[qlen + rank] = make_key(qd, static_cast<uint32_t>(un.begin + k));
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+            const uint64_t key = make_key(qd, static_cast<uint32_t>(un.begin + k));
+            uint32_t pos = 0;
+            // (a full buffer's counter is not counted on, so that it cannot wrap)
+            if (lane == 0) pos = *static_cast<volatile uint32_t *>(&s_n) < kIvfNotes ? atomicAdd(&s_n, cnt) : kIvfNotes;
+            pos = __builtin_amdgcn_readfirstlane(pos);
+            const bool noted = pos + rank < kIvfNotes;
+            if (h && noted) notes[pos + rank] = key;
+            if (pos + cnt > kIvfNotes) {                               // uniform
+                const uint32_t fit = pos < kIvfNotes ? kIvfNotes - pos : 0u;
+                append(key, h && !noted, rank - fit, cnt - fit);
             }
-            qlen = __builtin_amdgcn_readfirstlane(qlen + cnt);
-            if (qlen >= qflush) flush();                              // uniform
         }
     };
 
-    constexpr uint32_t SET = 64 * GPB;
-    for (uint32_t base0 = 0; base0 < un.count; base0 += 2 * SET) {
+    // (64-bit positions: a part may be close to 2^32 codes long)
+    constexpr uint64_t STEP = 4 * SET;
+    for (uint64_t base0 = lo; base0 < hi && T >= 0; base0 += 2 * STEP) {
         int Tn = T;
-        if (base0 + SET < un.count) { load_set(base0 + SET, wb); Tn = load_bound(); }
-        process(base0, wa, T);
-        if (base0 + SET >= un.count) break;
+        if (base0 + STEP < hi) { load_raw_set<M, CodeT, GPB, RW>(codes, un.begin, static_cast<uint32_t>(base0 + STEP), hi, wb); Tn = load_bound(); }
+        process(static_cast<uint32_t>(base0), wa, T);
+        if (base0 + STEP >= hi) break;
         T = Tn;
-        if (base0 + 2 * SET < un.count) { load_set(base0 + 2 * SET, wa); Tn = load_bound(); }
-        process(base0 + SET, wb, T);
+        if (base0 + 2 * STEP < hi) { load_raw_set<M, CodeT, GPB, RW>(codes, un.begin, static_cast<uint32_t>(base0 + 2 * STEP), hi, wa); Tn = load_bound(); }
+        process(static_cast<uint32_t>(base0 + STEP), wb, T);
         T = Tn;
     }
-    if constexpr (SAMPLE) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __syncthreads();
+    const uint32_t n = s_n < kIvfNotes ? s_n : kIvfNotes;
+    if (n == 0) return;                                               // uniform
+    if (tid == 0) s_first = atomicAdd(&count[cell], n);
+    __syncthreads();
+    const uint32_t first = s_first;
+    if (first + n > cap && tid == 0) atomicMin(&bound[q].t, -1);      // slice full: stop appending, the query is redone
+    for (uint32_t x = tid; x < n; x += 256) {
+        const uint64_t key = notes[x];
+        if (first + x < cap) keys[cell * cap + first + x] = key;
+        atomicAdd(&bhist[static_cast<uint32_t>(key >> 32)], 1u);
+    }
+    __syncthreads();
+    if (bhist[tid]) atomicAdd(&chist[static_cast<size_t>(q) * 256 + tid], bhist[tid]);
+    if (first / upd != (first + n) / upd) {                           // uniform
+        // (the additions of the other wavefronts may still be under way: any snapshot of the counts gives a valid bound)
+        if (wave == 0) lower_bound_of(q, r, bound, chist);
+    }
+}
+
+// The starting bounds: a histogram of the integer distances of the first 1 / step of every probed list, and
+// from it the bucket that r of the query's probed codes would reach (starting_bound), by the workgroup that ends the
+// query last.  step is kIvfSampleStep, and more where that would be a sample of over 32 K codes, as long as 16 of the r are
+// expected in it.  Grid (nq, rows): the sample is cut into sets of codes, of which every wavefront of the query's takes
+// as many (lists differ in length by orders of magnitude: with a wavefront per list the longest one's took 1.7 ms).
+// Bound by the latency of fetching a 2 KB table and a few hundred codes per list; a
+// workgroup counts in LDS and adds up once.  (As a wavefront per list with a histogram of its own the additions to
+// global memory alone were 6 million for 1024 queries x 64 lists: 309 us.)
+template <int M>
+struct IvfSampleCfg { static constexpr int WAVES = M <= 8 ? 16 : M == 16 ? 8 : 4; };   // tables of at most 32 KB in LDS
+
+template <int M, typename CodeT>
+__global__ __launch_bounds__(64 * IvfSampleCfg<M>::WAVES) void ivf_sample_kernel(const CodeT *__restrict__ codes,
+                                                            const int64_t *__restrict__ offsets,
+                                                            const int32_t *__restrict__ probe, int nprobe,
+                                                            const uint8_t *__restrict__ qtab, uint32_t r,
+                                                            const uint32_t *__restrict__ probed, uint32_t *__restrict__ shist,
+                                                            uint32_t *__restrict__ done, Bound *bound)
+{
+    constexpr int NW = IvfSampleCfg<M>::WAVES, COPIES = 4;
+    constexpr int RW = IvfRaw<M, CodeT>::RW, GPB = IvfRaw<M, CodeT>::GPB;
+    constexpr uint32_t SET = IvfRaw<M, CodeT>::SET;
+    __shared__ __align__(16) uint8_t tabs[NW][M * 256];
+    __shared__ uint32_t lhist[COPIES][256];
+    __shared__ uint64_t lbeg[kIvfMaxProbe];
+    __shared__ uint32_t lpart[kIvfMaxProbe], sbase[kIvfMaxProbe + 1];      // codes of a list in the sample; its first set
+    __shared__ uint32_t s_last;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), np = static_cast<uint32_t>(nprobe);
+    for (int v = tid; v < COPIES * 256; v += 64 * NW) (&lhist[0][0])[v] = 0;
+    uint32_t step = kIvfSampleStep;
+    while (probed[q] / step > 32768 && r / step >= 32) step *= 2;
+    for (uint32_t p = tid; p < np; p += 64 * NW) {
+        const int l = probe[static_cast<size_t>(q) * np + p];
+        lbeg[p] = static_cast<uint64_t>(offsets[l]);
+        lpart[p] = static_cast<uint32_t>((static_cast<uint64_t>(offsets[l + 1]) - lbeg[p] + step - 1) / step);
+    }
+    __syncthreads();
+    if (wave == 0) {                                           // exclusive prefix sums of the sets per list
+        uint32_t run = 0;
+        for (uint32_t p0 = 0; p0 < np; p0 += 64) {
+            const uint32_t n = p0 + lane < np ? (lpart[p0 + lane] + SET - 1) / SET : 0u;
+            uint32_t incl = n;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t c = lhist[lane + 64 * b];
-            if (c) atomicAdd(&count[static_cast<size_t>(q) * 256 + lane + 64 * b], c);
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t other = __shfl(incl, lane >= o ? lane - o : lane);
+                if (lane >= o) incl += other;
+            }
+            if (p0 + lane < np) sbase[p0 + lane] = run + incl - n;
+            run += __shfl(incl, 63);
         }
-        return;
+        if (lane == 0) sbase[np] = run;
     }
-    if (qlen) flush();
+    __syncthreads();
+    const uint32_t nsets = sbase[np], w = blockIdx.y * NW + wave, all = gridDim.y * NW;
+    uint32_t x = static_cast<uint32_t>(static_cast<uint64_t>(nsets) * w / all);             // this wavefront's sets: [x, end)
+    const uint32_t end = static_cast<uint32_t>(static_cast<uint64_t>(nsets) * (w + 1) / all);
+    uint8_t *tab = tabs[wave];
+    uint32_t *hist = lhist[wave % COPIES];
+    if (x < end) {                                                     // uniform per wavefront
+        uint32_t p = 0;
+        for (uint32_t hi = np; hi - p > 1;) {                          // the last list whose first set is at or before x
+            const uint32_t mid = (p + hi) >> 1;
+            if (sbase[mid] <= x) p = mid; else hi = mid;
+        }
+        bool fresh = true;
+        uint32_t wa[GPB][RW];
+        for (; x < end; ++x) {
+            while (sbase[p + 1] <= x) { ++p; fresh = true; }           // (lists without a set are passed over)
+            const uint32_t base0 = (x - sbase[p]) * SET, hi = lpart[p];
+            load_raw_set<M, CodeT, GPB, RW>(codes, lbeg[p], base0, hi, wa);
+            if (fresh) {
+                fresh = false;
+                constexpr int NTW = M * 256 / 16;                                // 16-byte words of the tables
+                const uint4 *src = reinterpret_cast<const uint4 *>(qtab + (static_cast<size_t>(q) * np + p) * M * 256);
+                uint4 *dst = reinterpret_cast<uint4 *>(tab);
+                // the wavefront's own tables: its lanes are done with the previous list's, the fences order the accesses
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+                for (int v = 0; v < (NTW + 63) / 64; ++v)
+                    if (NTW % 64 == 0 || lane + 64 * v < NTW) dst[lane + 64 * v] = src[lane + 64 * v];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+#pragma unroll
+            for (int g = 0; g < GPB; ++g) {
+                uint32_t s = 0;
+#pragma unroll
+                for (int j = 0; j < M; ++j) s += tab[j * 256 + low_byte_of<CodeT, RW>(wa[g], j)];
+                if (base0 + g * 64 + lane < hi) atomicAdd(&hist[min(s, 255u)], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    for (int v = tid; v < 256; v += 64 * NW) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int z = 0; z < COPIES; ++z) c += lhist[z][v];
+        if (c) atomicAdd(&shist[static_cast<size_t>(q) * 256 + v], c);
+    }
+    // every addition is in place before this workgroup's count is (device-scope atomics: their completion is all there
+    // is to wait for)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) s_last = atomicAdd(&done[q], 1u) == gridDim.y - 1;
+    __syncthreads();
+    // (a query with so many ties at the starting bucket that they would overflow its buffer is left to the three passes)
+    if (s_last && wave == 0) starting_bound(shist + static_cast<size_t>(q) * 256, r, probed[q], kCrowdedSkip, bound + q);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -889,8 +1077,12 @@ __global__ __launch_bounds__(1024) void ivf_refine_kernel(const float *__restric
 struct IvfScanPlan {
     size_t off_hist, off_thr, off_counter, off_nunits, zero_bytes, off_tie, off_units, off_keys, off_spill, total;
     // single pass: sample histogram, cursors, appended histogram (cleared with the rest); bounds, flags, buffers
-    size_t off_shist, off_fcount, off_chist, off_bound, off_flags, off_fkeys, off_fsort, off_probed, off_sunits, off_nsunits;
-    uint32_t cap, upd, qflush, sortcap;
+    size_t off_shist, off_fcount, off_chist, off_bound, off_flags, off_fkeys, off_fsort, off_probed;
+    // its parts: bins of list ids, cursor, finished sample workgroups (cleared with the rest); places, lengths, records
+    size_t off_bins, off_cursor, off_done, off_rank, off_part, off_items, off_qlist;
+    bool order;              // parts ordered by list
+    uint32_t parts;          // parts per query, about (and one more per probed list at most)
+    uint32_t cap, upd, sortcap;
 };
 
 static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
@@ -906,28 +1098,28 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     p.off_shist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
     p.off_fcount = off;  off = align_up(off + sizeof(uint32_t) * Q * kFastSlices, 256);
     p.off_chist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
+    // Parts: at least 128 per query, and 4096 in all, for 2048 resident workgroups.  They are ordered by list (two short launches more) where
+    // there are queries enough to share lists or to crowd one another's cursors.
+    p.parts = nq >= 32 ? 128u : 4096u / static_cast<uint32_t>(nq < 2 ? 2 : nq);
+    p.order = nq > 4;
+    p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);
+    p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);
+    p.off_bins = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * kIvfBins : 0), 256);
     p.zero_bytes = off;  // everything above is cleared together
+    p.off_rank = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * Q * kIvfMaxProbe : 0), 256);
+    p.off_part = off;    off = align_up(off + sizeof(uint32_t) * Q, 256);
+    p.off_qlist = off;   off = align_up(off + sizeof(int) * Q, 256);
+    p.off_items = off;   off = align_up(off + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe), 256);
     p.off_units = off;   off = align_up(off + sizeof(IvfUnit) * Q * kIvfUnitsPerQuery, 256);
     p.off_keys = off;    off = align_up(off + sizeof(uint64_t) * Q * r, 256);
     p.off_spill = off;
     if (next_pow2(r) > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * next_pow2(r), 256);
     p.cap = 2 * r < 1024 ? 1024 : 2 * r;                 // per slice; 32 r per query in all
     p.upd = r / 16 < 16 ? 16 : r / 16;                   // appends to one slice between bound updates
-    // Pending candidates a wavefront may hold: the wavefronts of one query that run at the same time
-    // (about 2048 workgroups of 4 are resident, the query index varies fastest) together keep at most r / 4
-    // candidates away from the bound.
-    {
-        const size_t resident = 2048 / Q ? 2048 / Q : 1;
-        const size_t waves = 4 * resident < static_cast<size_t>(kIvfUnitsPerQuery) ? 4 * resident : kIvfUnitsPerQuery;
-        const size_t lim = r / 4 / waves;
-        p.qflush = static_cast<uint32_t>(lim < 1 ? 1 : lim > 64 ? 64 : lim);
-    }
     p.sortcap = next_pow2(2 * r) < kSortLdsKeys ? kSortLdsKeys : next_pow2(2 * r);
     p.off_bound = off;    off = align_up(off + sizeof(Bound) * Q, 256);
-    p.off_flags = off;   off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);     // and "any of them"
+    p.off_flags = off;   off = align_up(off + sizeof(uint32_t) * Q, 256);
     p.off_probed = off;  off = align_up(off + sizeof(uint32_t) * Q, 256);
-    p.off_sunits = off;  off = align_up(off + sizeof(IvfUnit) * Q * kIvfSampleUnits, 256);
-    p.off_nsunits = off; off = align_up(off + sizeof(uint32_t) * Q, 256);
     p.off_fkeys = off;   off = align_up(off + sizeof(uint64_t) * Q * kFastSlices * p.cap, 256);
     p.off_fsort = off;
     if (p.sortcap > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * p.sortcap, 256);
@@ -936,7 +1128,7 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
 }
 
 template <int M, typename CodeT>
-static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, const int32_t *probe, int nprobe,
+static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, const int32_t *probe, int nprobe,
                       const uint8_t *qtab, int nq, uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint32_t *count,
                       uint8_t *base, hipStream_t st)
 {
@@ -954,11 +1146,24 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, const int32_t 
     rc = launch_fill_u64(keys, static_cast<size_t>(nq) * r, ~0ull, st);     // unused slots read as padding
     if (rc) return rc;
     uint32_t *probed = reinterpret_cast<uint32_t *>(base + p.off_probed);
-    IvfUnit *sunits = reinterpret_cast<IvfUnit *>(base + p.off_sunits);
-    uint32_t *nsunits = reinterpret_cast<uint32_t *>(base + p.off_nsunits);
-    DCPQ_LAUNCH(kStageIvf, st, ivf_plan_kernel, dim3(nq), dim3(256), 0, probe, nprobe, offsets, r, units, nunits, count, sunits,
-                nsunits, probed);
+    uint32_t *bins = p.order ? reinterpret_cast<uint32_t *>(base + p.off_bins) : nullptr;
+    uint32_t *cursor = reinterpret_cast<uint32_t *>(base + p.off_cursor);
+    uint32_t *done = reinterpret_cast<uint32_t *>(base + p.off_done);      // [nq], and behind them the number of flagged queries
+    uint32_t *rank = reinterpret_cast<uint32_t *>(base + p.off_rank);
+    uint32_t *part_of = reinterpret_cast<uint32_t *>(base + p.off_part);
+    IvfUnit *items = reinterpret_cast<IvfUnit *>(base + p.off_items);
+    DCPQ_LAUNCH(kStageIvf, st, ivf_plan_kernel, dim3(nq), dim3(256), 0, probe, nprobe, offsets, static_cast<uint32_t>(nlist), r,
+                p.parts, units, nunits, count, probed, part_of, bins, rank, cursor, items);
     DCPQ_CHECK_LAUNCH("ivf_plan_kernel");
+    if (p.order) {
+        const uint32_t nbins = static_cast<uint32_t>(nlist) < kIvfBins ? static_cast<uint32_t>(nlist) : kIvfBins;
+        const uint32_t npairs = static_cast<uint32_t>(nq) * static_cast<uint32_t>(nprobe);
+        DCPQ_LAUNCH(kStageIvf, st, ivf_bin_base_kernel, dim3((nbins + 255) / 256), dim3(256), 0, bins, nbins, cursor);
+        DCPQ_CHECK_LAUNCH("ivf_bin_base_kernel");
+        DCPQ_LAUNCH(kStageIvf, st, ivf_parts_kernel, dim3((npairs + 255) / 256), dim3(256), 0, probe, npairs,
+                    static_cast<uint32_t>(nprobe), offsets, static_cast<uint32_t>(nlist), bins, rank, part_of, items);
+        DCPQ_CHECK_LAUNCH("ivf_parts_kernel");
+    }
     const dim3 grid(kIvfUnitsPerQuery / 4, nq < kIvfRedoRows ? nq : kIvfRedoRows);
     const size_t lds_tab = 4 * M * 256;
     uint32_t *shist = reinterpret_cast<uint32_t *>(base + p.off_shist);
@@ -969,36 +1174,44 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, const int32_t 
     uint64_t *fkeys = reinterpret_cast<uint64_t *>(base + p.off_fkeys);
     uint64_t *fsort = reinterpret_cast<uint64_t *>(base + p.off_fsort);
     // single pass: bounds from a sample of the probed lists, one pass over all their units, exact selection
-    DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_single_kernel<M, CodeT, true>),
-                dim3(nq, (nprobe + kIvfUnitsPerQuery / kIvfSampleStep + 3) / 4), dim3(256),
-                lds_tab + 4 * 256 * 4, codes, sunits, nsunits, qtab, nprobe, r, p.cap, p.upd, p.qflush, bound, shist, chist, fkeys);
-    DCPQ_CHECK_LAUNCH("ivf_scan_single_kernel<sample>");
     // As in the flat scan, the bound starts at the bucket where the sample's count reaches what r codes of all the
     // query's probed codes would leave in a sample of that size, plus slack; a query whose bucket holds fewer than
     // r codes after all is flagged by the selection and redone below.
-    rc = launch_sample_threshold(shist, nq, r, 0, bound, st, probed);
+    {
+        // two workgroups per query, or as many as bring the launch to 1024, up to four wavefronts per list
+        constexpr int NW = IvfSampleCfg<M>::WAVES;
+        const int most = (4 * nprobe + NW - 1) / NW;
+        int rows = nq >= 512 ? 2 : 1024 / nq;
+        if (rows > most) rows = most;
+        DCPQ_LAUNCH(kStageIvf, st, (ivf_sample_kernel<M, CodeT>), dim3(nq, rows), dim3(64 * NW), 0, codes, offsets, probe, nprobe,
+                    qtab, r, probed, shist, done, bound);
+        DCPQ_CHECK_LAUNCH("ivf_sample_kernel");
+    }
+    {
+        const uint64_t most = static_cast<uint64_t>(nq) * (p.parts + nprobe);     // workgroups behind the last part leave at once
+        const uint64_t gx = most < (1u << 20) ? (most + 7) / 8 * 8 : (1u << 20);
+        DCPQ_LAUNCH(kStageIvfScan, st, (ivf_scan_parts_kernel<M, CodeT>), dim3(static_cast<unsigned>(gx), static_cast<unsigned>((most + gx - 1) / gx)),
+                    dim3(256), M * 256 + kIvfNotes * 8, codes, items, cursor, qtab, static_cast<uint32_t>(nprobe), r, p.cap, p.upd,
+                    bound, fcount, chist, fkeys);
+        DCPQ_CHECK_LAUNCH("ivf_scan_parts_kernel");
+    }
+    uint32_t *nflag = done + nq;
+    rc = launch_fast_select(fkeys, fcount, chist, nq, r, kFastSlices, p.cap, p.sortcap, 0, fsort, cand_id, cand_qd, flags, st,
+                            reinterpret_cast<int *>(base + p.off_qlist), nflag);
     if (rc) return rc;
-    DCPQ_LAUNCH(kStageIvfScan, st, (ivf_scan_single_kernel<M, CodeT, false>), dim3(nq, kIvfUnitsPerQuery / 4), dim3(256),
-                lds_tab + 4 * 64 * 8, codes, units, nunits, qtab, nprobe, r, p.cap, p.upd, p.qflush, bound, fcount, chist,
-                fkeys);
-    DCPQ_CHECK_LAUNCH("ivf_scan_single_kernel");
-    rc = launch_fast_select(fkeys, fcount, chist, nq, r, kFastSlices, p.cap, p.sortcap, 0, fsort, cand_id, cand_qd, flags, st);
-    if (rc) return rc;
-    DCPQ_LAUNCH(kStageIvf, st, ivf_any_flag_kernel, dim3(1), dim3(1024), 0, flags, nq);
-    DCPQ_CHECK_LAUNCH("ivf_any_flag_kernel");
     // the queries it flagged (a full slice, or fewer than r codes in the probed lists): three passes
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfHist, CodeT>), grid, dim3(256), lds_tab + 4 * 256 * 4, codes, units,
-                nunits, qtab, nprobe, nq, r, 1u, flags, hist, thr, tie, counter, keys);
+                nunits, qtab, nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<hist>");
     rc = launch_threshold(hist, nq, r, thr, st);
     if (rc) return rc;
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfTieCount, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, 1u, flags, hist, thr, tie, counter, keys);
+                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<tiecount>");
     rc = launch_tie_quota(tie, kIvfUnitsPerQuery, nq, thr, st);
     if (rc) return rc;
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfCollect, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, 1u, flags, hist, thr, tie, counter, keys);
+                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<collect>");
     return launch_sort_candidates(keys, nq, r, spill, cand_id, cand_qd, st, flags);
 }
@@ -1131,12 +1344,12 @@ static int ivf_scan_checked(const char *what, const CodeT *codes, const int64_t 
     hipStream_t st = as_stream(stream);
     uint8_t *base = static_cast<uint8_t *>(workspace);
     switch (m) {
-        case 1: return ivf_scan_m<1>(codes, offsets, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
-        case 2: return ivf_scan_m<2>(codes, offsets, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
-        case 4: return ivf_scan_m<4>(codes, offsets, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
-        case 8: return ivf_scan_m<8>(codes, offsets, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
-        case 16: return ivf_scan_m<16>(codes, offsets, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
-        case 32: return ivf_scan_m<32>(codes, offsets, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
+        case 1: return ivf_scan_m<1>(codes, offsets, nlist, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
+        case 2: return ivf_scan_m<2>(codes, offsets, nlist, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
+        case 4: return ivf_scan_m<4>(codes, offsets, nlist, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
+        case 8: return ivf_scan_m<8>(codes, offsets, nlist, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
+        case 16: return ivf_scan_m<16>(codes, offsets, nlist, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
+        case 32: return ivf_scan_m<32>(codes, offsets, nlist, probe, nprobe, qtab, nq, r, cand_id, cand_qd, count, base, st);
         default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
     }
 }

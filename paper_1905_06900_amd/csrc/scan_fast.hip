@@ -152,13 +152,12 @@ __global__ __launch_bounds__(256) void swizzle_tables_kernel(const uint8_t *__re
 
 // Starting bounds from sample histograms, a wavefront per query (see starting_bound).
 __global__ __launch_bounds__(256) void sample_threshold_kernel(const uint32_t *__restrict__ shist, int nq, uint32_t r,
-                                                               uint64_t n_codes, const uint32_t *__restrict__ n_each,
+                                                               uint64_t n_codes,
                                                                Bound *__restrict__ bound)
 {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q >= nq) return;
-    // (n_each: every query scans its own codes, the probed lists)
-    starting_bound(shist + static_cast<size_t>(q) * 256, r, n_each ? n_each[q] : n_codes, false, bound + q);
+    starting_bound(shist + static_cast<size_t>(q) * 256, r, n_codes, kCrowdedAppend, bound + q);
 }
 
 // Low bytes of the M sub-codes of one code, reordered by residue class: byte (j & 3) * CLS + (j >> 2).
@@ -913,10 +912,9 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     return DCPQ_OK;
 }
 
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st,
-                            const uint32_t *n_each)
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, n_each, bound);
+    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, bound);
     DCPQ_CHECK_LAUNCH("sample_threshold_kernel");
     return DCPQ_OK;
 }

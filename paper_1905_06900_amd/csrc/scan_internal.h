@@ -97,9 +97,7 @@ int launch_scan_fast(const CodeT *codes, uint64_t n_codes, int m, const uint8_t 
 
 // Steps of the single-pass selection that the inverted-list variant reuses.
 // n_codes: size of the array the sample was drawn from (the sample's own size is the histogram's total)
-// n_each (optional): the number of codes each query scans, where it is not the same n_codes for all of them
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st,
-                            const uint32_t *n_each = nullptr);
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st);
 // n_ids: the ids are below this (0 = unknown); qlist, nflag (optional): the flagged queries, in any order, and their number
 int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32_t *chist, int nq, uint32_t r,
                        uint32_t nslices, uint32_t cap, uint32_t sortcap, uint64_t n_ids, uint64_t *spill, uint32_t *cand_id,
@@ -171,9 +169,10 @@ __device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c
 // ten million starts too low), or r if that is smaller.  Should that bucket hold fewer than r codes of the whole array after all, the
 // selection sees fewer than r appended candidates and has the query redone by the three-pass path.
 // Where so many codes tie in that bucket that more than 16 r would be appended, only the codes with ids up to
-// twice the share of the bucket that is wanted are (`limit`; ties are broken by id, and the sample's runs are spread
-// over the array).
-__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, bool limit, Bound *bound)
+// twice the share of the bucket that is wanted are (kCrowdedLimit; ties are broken by id, and the sample's runs are spread
+// over the array), or none at all, which flags the query (kCrowdedSkip; no order of the ids is known).
+enum Crowded { kCrowdedAppend = 0, kCrowdedLimit = 1, kCrowdedSkip = 2 };
+__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound)
 {
     const int lane = threadIdx.x & 63;
     uint32_t c[4], cum[4];
@@ -191,11 +190,13 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
         if (before < rs && cum[z] >= rs) {                    // one lane, one bucket
             uint32_t last = 0xFFFFFFFFu;
             const float expect = static_cast<float>(cum[z]) * (static_cast<float>(n) / static_cast<float>(total));
-            if (limit && expect > 16.0f * static_cast<float>(r)) {
+            int t = 4 * lane + z;
+            if (crowded == kCrowdedSkip && n && expect > 16.0f * static_cast<float>(r)) t = -1;
+            if (crowded == kCrowdedLimit && expect > 16.0f * static_cast<float>(r)) {
                 const float upto = 2.0f * static_cast<float>(n) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
                 if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
             }
-            *bound = Bound{4 * lane + z, static_cast<uint32_t>(4 * lane + z), last, 0u};
+            *bound = Bound{t, static_cast<uint32_t>(4 * lane + z), last, 0u};
         }
     }
     if (lane == 63 && total < rs) *bound = Bound{255, 255u, 0xFFFFFFFFu, 0u};

@@ -119,6 +119,31 @@ def test_ivf_other_code_shapes(m, dsub):
     run_ivf_case(d, w.nprobe, w.r, 50)
 
 
+@pytest.mark.parametrize("m", [1, 4, 8, 16, 32])
+@pytest.mark.parametrize("Q,nlist,nprobe,r", [(1, 64, 64, 700), (4, 64, 3, 700), (5, 64, 64, 129), (70, 64, 20, 50)])
+def test_ivf_scan_parts_of_lopsided_lists(m, Q, nlist, nprobe, r):
+    """The single-pass scan's parts: lists of 0 to 65 codes, of part sizes and one less and more, and one list that holds
+    most of the array and is cut into many parts, for few queries (parts in the queries' order) and many (by list)."""
+    sizes = torch.tensor([0, 1, 2, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2049, 4095, 4097] * 4)[:nlist]
+    sizes[40] = 90_001
+    N = int(sizes.sum())
+    from dataclasses import replace
+    w = replace(synth.scaled(synth.WORKLOADS[3], N=N, Q=Q, r=r, nlist=nlist, nprobe=nprobe), m=m, dsub=128 // m)
+    print("ivf parts: m=%d Q=%d N=%d nlist=%d nprobe=%d r=%d" % (m, Q, N, nlist, nprobe, r), flush=True)
+    d = synth.make_ivf(w, DEV)
+    off = torch.zeros(nlist + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(sizes, 0)
+    d["offsets"] = off.to(DEV)
+    run_ivf_case(d, nprobe, r, 40, plane=m == 8)
+
+
+def test_ivf_more_lists_than_bins():
+    """Above 65536 lists several of them share a bin of the scan's order."""
+    w = synth.scaled(synth.WORKLOADS[3], N=400_000, Q=9, r=300, nlist=70_001, nprobe=100)
+    print("ivf case: nlist=70001", flush=True)
+    run_ivf_case(synth.make_ivf(w, DEV), w.nprobe, w.r, 50)
+
+
 def test_ivf_argument_errors():
     q = torch.zeros((2, 128), device=DEV); coarse = torch.zeros((8, 128), device=DEV)
     with pytest.raises(binding.DcpqError) as e:
