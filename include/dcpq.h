@@ -101,6 +101,7 @@ int dcpq_build_tables_n(const float *queries, int nq, const float *codebooks, in
  *   codes   : const uint16_t [n_codes][m]     qtab : const uint8_t [nq][m][256]
  *   cand_id : uint32_t [nq][r] (output)       cand_qd : uint8_t [nq][r] (output)
  *   workspace : at least dcpq_scan_workspace_bytes(n_codes, m, nq, r) bytes, 256-byte aligned
+ *             (a smaller one is accepted, and slower, down to what dcpq_scan_plan reports)
  * Requires 1 <= r <= n_codes < 2^32; codes and qtab 16-byte aligned.
  * ------------------------------------------------------------------------------------------- */
 size_t dcpq_scan_workspace_bytes(uint64_t n_codes, int m, int nq, uint32_t r);
@@ -115,7 +116,8 @@ int dcpq_scan_query_tile(int m);
  * single-pass scan its starting bounds: [6] runs of 256 codes, [7] codes between the starts of two runs,
  * [8] 16 when the histogram pass reads one run in 16 and the single-pass kernel counts the whole sample
  * below the bound that gives (the pilot pass, large arrays), 1 when the histogram pass reads every run,
- * [9] the rank wanted within the sample (all 0 for the three-pass algorithm). */
+ * [9] the rank wanted within the sample (all 0 for the three-pass algorithm).  With ninfo >= 11 also [10] the bytes of the
+ * smallest workspace that is accepted. */
 int dcpq_scan_plan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, uint64_t *info, int ninfo);
 int dcpq_scan_candidates(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
                          uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *workspace,
@@ -150,7 +152,7 @@ int dcpq_scan_candidates_packed(const uint8_t *plane, uint64_t n_codes, int m, c
  * harnesses that forbid hipMalloc) and have no workspace to pass: the scratch memory is an array
  * inside the library, DCPQ_STATIC_SCRATCH_BYTES per GPU, held from the first call on that GPU until
  * the process ends.  Inputs, outputs, order and error behaviour as dcpq_scan_candidates; the call
- * itself allocates nothing.  A problem whose dcpq_scan_workspace_bytes exceeds
+ * itself allocates nothing.  A problem whose smallest workspace (dcpq_scan_plan) exceeds
  * dcpq_static_scratch_bytes() is refused with DCPQ_EWORKSPACE before anything is launched.  All
  * calls on one GPU share the one array: two of them must not overlap in time (they would race),
  * whichever streams they use. */

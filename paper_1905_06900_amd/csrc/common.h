@@ -88,12 +88,14 @@ int launch_full_tables(const float *queries, int nq, const float *codebooks, int
 int launch_distance_tables(const float *queries, int nq, const float *codebooks, int m, int dsub, int ncent,
                            float *tables, int stage, hipStream_t st);
 // mode: DCPQ_SCAN_AUTO or DCPQ_SCAN_THREE_PASS; cleared: the first scan_clear_words(...) words of ws are zero already
+// what a workspace must hold (dcpq_scan_workspace_bytes: what it does best with); room: bytes at ws, no less than that
+size_t scan_least_bytes(uint64_t n_codes, int m, int nq, uint32_t r);
 size_t scan_clear_words(uint64_t n_codes, int m, int nq, uint32_t r, int mode);
 int launch_scan(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st);
+                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st);
 // the same reading the low-byte plane of the codes (uint8 [n_codes][m])
 int launch_scan(const uint8_t *plane, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st);
+                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st);
 int launch_refine(const float *tables, uint32_t table_size, const void *codes, int code_bytes, uint64_t n_codes, int m,
                   const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids, float *dist, void *ws,
                   hipStream_t st);

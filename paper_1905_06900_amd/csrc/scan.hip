@@ -352,7 +352,7 @@ int fast_query_tile(int m, int nq, int mode)
     }
 }
 
-ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
+ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t room)
 {
     ScanPlan p{};
     p.qt = scan_qt(m);
@@ -392,7 +392,10 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
         cpb = (cpb + 1023) / 1024 * 1024;
         p.codes_per_block = static_cast<uint32_t>(cpb);
         p.fblocks = static_cast<uint32_t>((rest + cpb - 1) / cpb);
+        // (no more slices than stretches of 16 Ki codes: a slice has room for 1024 candidates or more, whatever r is)
+        const uint64_t long_blocks = (rest + 16383) / 16384;
         p.slices = p.fblocks < static_cast<uint32_t>(kFastSlices) ? p.fblocks : kFastSlices;
+        if (p.slices > long_blocks) p.slices = static_cast<uint32_t>(long_blocks);
         p.off_fzero = off;
         p.off_fcount = off;  off = align_up(off + sizeof(uint32_t) * Q * p.slices, 256);
         p.off_chist = off;   off = align_up(off + sizeof(uint32_t) * 256 * Q, 256);
@@ -461,7 +464,11 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
             p.pilot_runs = (p.s_nunits + pb - 1) / pb;
             p.pilot_blocks = (p.s_nunits + p.pilot_runs - 1) / p.pilot_runs;
         }
-        p.off_bound = off;   off = align_up(off + sizeof(Bound) * Q, 256);
+        if (off - p.off_tie >= sizeof(Bound) * Q) {
+            p.off_bound = p.off_tie;
+        } else {                                             // r = 1 and a single unit
+            p.off_bound = off;   off = align_up(off + sizeof(Bound) * Q, 256);
+        }
         p.off_flags = off;   off = align_up(off + sizeof(uint32_t) * Q, 256);
         p.off_qlist = off;   off = align_up(off + sizeof(int32_t) * Q, 256);
         p.off_qsw = off;     off = align_up(off + static_cast<size_t>(p.ntiles) * fast_table_bytes(m, p.fqt), 256);
@@ -480,6 +487,9 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode)
             uint64_t w = (5 * share / 2 + 127) / 64 * 64;
             p.wcap = static_cast<uint32_t>(w > 4096 ? 4096 : w);
             const uint64_t blocks = p.fblocks > p.pilot_blocks ? p.fblocks : p.pilot_blocks;
+            // a smaller workspace holds fewer of them, or none (every candidate is then appended by itself)
+            const uint64_t fit = (room > off ? room - off : 0) / (sizeof(uint64_t) * p.ntiles * blocks * kNoteWaves) / 64 * 64;
+            if (fit < p.wcap) p.wcap = static_cast<uint32_t>(fit);
             p.off_notes = off; off = align_up(off + sizeof(uint64_t) * p.ntiles * blocks * kNoteWaves * p.wcap, 256);
         }
     }
@@ -581,9 +591,9 @@ template int launch_sample_hist<uint8_t>(const uint8_t *, uint64_t, int, const u
 
 template <int M, typename CodeT>
 static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,
-                         uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
+                         uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
 {
-    const ScanPlan p = plan_scan(n_codes, M, nq, r, mode);
+    const ScanPlan p = plan_scan(n_codes, M, nq, r, mode, room);
     uint8_t *base = static_cast<uint8_t *>(ws);
     int rc = DCPQ_OK;
     if (!cleared) rc = launch_zero_words(reinterpret_cast<uint32_t *>(base), p.zero_bytes / sizeof(uint32_t), st);
@@ -600,32 +610,46 @@ static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
 
 template <typename CodeT>
 static int launch_scan_any(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                           uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
+                           uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
 {
     if (nq == 0) return DCPQ_OK;
     switch (m) {
-        case 1: return launch_scan_m<1, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
-        case 2: return launch_scan_m<2, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
-        case 4: return launch_scan_m<4, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
-        case 8: return launch_scan_m<8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
-        case 16: return launch_scan_m<16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
-        case 32: return launch_scan_m<32, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+        case 1: return launch_scan_m<1, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+        case 2: return launch_scan_m<2, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+        case 4: return launch_scan_m<4, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+        case 8: return launch_scan_m<8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+        case 16: return launch_scan_m<16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+        case 32: return launch_scan_m<32, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
         default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
     }
 }
 
+// Enough for every algorithm the caller may ask for, in a workspace of `room` bytes.
+static size_t scan_bytes_of_all_modes(uint64_t n_codes, int m, int nq, uint32_t r, size_t room)
+{
+    size_t most = 0;
+    const int modes[] = {DCPQ_SCAN_AUTO, DCPQ_SCAN_THREE_PASS, DCPQ_SCAN_TILE16, DCPQ_SCAN_TILE32, DCPQ_SCAN_TILE64};
+    for (int mode : modes) {
+        const size_t t = plan_scan(n_codes, m, nq, r, mode, room).total;
+        most = t > most ? t : most;
+    }
+    return most;
+}
+
+size_t scan_least_bytes(uint64_t n_codes, int m, int nq, uint32_t r) { return scan_bytes_of_all_modes(n_codes, m, nq, r, 0); }
+
 size_t scan_clear_words(uint64_t n_codes, int m, int nq, uint32_t r, int mode) { return plan_scan(n_codes, m, nq, r, mode).zero_bytes / sizeof(uint32_t); }
 
 int launch_scan(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
+                uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
 {
-    return launch_scan_any(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+    return launch_scan_any(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
 }
 
 int launch_scan(const uint8_t *plane, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                uint32_t *cand_id, uint8_t *cand_qd, void *ws, int mode, bool cleared, hipStream_t st)
+                uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
 {
-    return launch_scan_any(plane, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, mode, cleared, st);
+    return launch_scan_any(plane, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
 }
 
 }  // namespace dcpq
@@ -658,20 +682,14 @@ extern "C" int dcpq_scan_plan(uint64_t n_codes, int m, int nq, uint32_t r, int m
         info[8] = p.fast && p.pilot ? kPilotEvery : (p.fast ? 1 : 0);
         info[9] = p.fast ? p.pilot_r : 0;
     }
+    if (ninfo >= 11) info[10] = scan_least_bytes(n_codes, m, nq, r);
     return DCPQ_OK;
 }
 
 extern "C" size_t dcpq_scan_workspace_bytes(uint64_t n_codes, int m, int nq, uint32_t r)
 {
     if (nq <= 0 || !m_supported(m) || n_codes == 0 || r == 0 || r > (1u << 26)) return 0;
-    // enough for every algorithm the caller may ask for
-    size_t most = 0;
-    const int modes[] = {DCPQ_SCAN_AUTO, DCPQ_SCAN_THREE_PASS, DCPQ_SCAN_TILE16, DCPQ_SCAN_TILE32, DCPQ_SCAN_TILE64};
-    for (int mode : modes) {
-        const size_t t = plan_scan(n_codes, m, nq, r, mode).total;
-        most = t > most ? t : most;
-    }
-    return most;
+    return scan_bytes_of_all_modes(n_codes, m, nq, r, ~static_cast<size_t>(0));
 }
 
 template <typename CodeT>
@@ -696,10 +714,10 @@ static int scan_checked(const CodeT *codes, uint64_t n_codes, int m, const uint8
     DCPQ_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255) == 0, "scan_candidates: workspace must be 256-byte aligned");
     DCPQ_REQUIRE((reinterpret_cast<uintptr_t>(codes) & 15) == 0 && (reinterpret_cast<uintptr_t>(qtab) & 15) == 0,
                  "scan_candidates: codes (or their plane) and qtab must be 16-byte aligned");
-    const size_t need = dcpq_scan_workspace_bytes(n_codes, m, nq, r);
+    const size_t need = scan_least_bytes(n_codes, m, nq, r);
     if (workspace_bytes < need)
         return fail(DCPQ_EWORKSPACE, "scan_candidates: workspace %zu < %zu bytes", workspace_bytes, need);
-    return launch_scan(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, workspace, mode, false, as_stream(stream));
+    return launch_scan(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, workspace, workspace_bytes, mode, false, as_stream(stream));
 }
 
 extern "C" int dcpq_scan_candidates(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
@@ -729,7 +747,9 @@ extern "C" int dcpq_scan_candidates_mode(const uint16_t *codes, uint64_t n_codes
 // that forbid allocation) and have no workspace to hand over: the scan's workspace is this array,
 // which every GPU the library runs on holds from the first call until the process ends.
 constexpr size_t kStaticScratchBytes = DCPQ_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// (the counters of finished workgroups and, at r = 1, the bounds come on top of what the stated size has always admitted)
+constexpr size_t kStaticRoom = kStaticScratchBytes + (256u << 10);
+static __device__ __align__(256) unsigned char scratch[kStaticRoom];
 
 namespace {
 constexpr int kMostDevices = 64;
@@ -762,10 +782,10 @@ extern "C" int dcpq_scan_candidates_static(const uint16_t *codes, uint64_t n_cod
     clear_error();
     // the size check comes first: a problem that does not fit is refused before the device is touched
     if (nq > 0 && m_supported(m) && n_codes >= 1 && r >= 1 && r <= (1u << 26)) {
-        const size_t need = dcpq_scan_workspace_bytes(n_codes, m, nq, r);
-        if (need > kStaticScratchBytes)
+        const size_t need = scan_least_bytes(n_codes, m, nq, r);
+        if (need > kStaticRoom)
             return fail(DCPQ_EWORKSPACE, "scan_candidates_static: the scan needs %zu bytes of scratch, the static array holds %zu",
-                        need, kStaticScratchBytes);
+                        need, kStaticRoom);
     }
     void *ws = nullptr;
     if (nq > 0) {
@@ -774,5 +794,5 @@ extern "C" int dcpq_scan_candidates_static(const uint16_t *codes, uint64_t n_cod
     }
     // every counter the kernels expect at zero is cleared by the scan itself (a fill kernel, so the
     // call may be captured), whatever the previous call left in the array
-    return scan_checked(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, kStaticScratchBytes, DCPQ_SCAN_AUTO, stream);
+    return scan_checked(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, kStaticRoom, DCPQ_SCAN_AUTO, stream);
 }

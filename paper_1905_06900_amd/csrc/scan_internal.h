@@ -71,7 +71,7 @@ struct ScanPlan {
     size_t off_chist;     // uint32 [nq][256]
     size_t off_shist;     // uint32 [nq][256]
     size_t off_nflag;     // uint32 [1] (+ padding)
-    size_t off_bound;     // Bound [nq]
+    size_t off_bound;     // Bound [nq], in the place of tie, keys and spill: only the redo uses those, and it never reads a bound
     size_t off_flags;     // uint32 [nq]
     size_t off_qlist;     // int32 [nq]
     size_t off_qsw;       // uint8 [ntiles][fast_table_bytes(m, fqt)]
@@ -81,7 +81,8 @@ struct ScanPlan {
     size_t total;
 };
 // mode: DCPQ_SCAN_AUTO picks the single-pass query tile from the batch size; DCPQ_SCAN_TILE16/32/64 force it
-ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode = 0);
+// room: bytes of the workspace; the notes (the last array, a matter of speed only) shrink to what is left of it
+ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode = 0, size_t room = ~static_cast<size_t>(0));
 
 int fast_query_tile(int m, int nq, int mode);   // 0 when the single-pass path does not exist for this m (and tile)
 size_t fast_table_bytes(int m, int qt);

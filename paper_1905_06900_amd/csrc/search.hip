@@ -8,7 +8,8 @@ namespace dcpq {
 
 struct SearchPlan {
     int chunk;
-    size_t off_qtab, off_bounds, off_cand_id, off_cand_qd, off_tables, tables_bytes, off_scan, off_refine, total;
+    size_t off_qtab, off_bounds, off_cand_id, off_cand_qd, off_tables, tables_bytes, off_scan, off_refine;
+    size_t least, total;       // bytes a workspace must hold, and does best with
 };
 
 static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int full_bits, int chunk_queries)
@@ -28,6 +29,21 @@ static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int f
     p.off_bounds = off;  off = align_up(off + sizeof(float) * 2 * static_cast<size_t>(chunk), 256);
     p.off_cand_id = off; off = align_up(off + sizeof(uint32_t) * static_cast<size_t>(chunk) * r, 256);
     p.off_cand_qd = off; off = align_up(off + static_cast<size_t>(chunk) * r, 256);
+    // The scan and the refinement lay their scratch out for the number of queries they are given, and
+    // a smaller batch does not always need less (fewer queries can mean more units or slices), so
+    // the regions hold the larger of what a full chunk and what the ragged last chunk need: those
+    // are the only two batch sizes the loop below ever passes.
+    const int tail = nq % chunk;
+    size_t scan_bytes = dcpq_scan_workspace_bytes(n_codes, m, chunk, r), least_bytes = scan_least_bytes(n_codes, m, chunk, r);
+    size_t refine_bytes = dcpq_refine_workspace_bytes(chunk, r);
+    if (tail) {
+        const size_t st = dcpq_scan_workspace_bytes(n_codes, m, tail, r), rt = dcpq_refine_workspace_bytes(tail, r);
+        const size_t lt = scan_least_bytes(n_codes, m, tail, r);
+        scan_bytes = st > scan_bytes ? st : scan_bytes;
+        least_bytes = lt > least_bytes ? lt : least_bytes;
+        refine_bytes = rt > refine_bytes ? rt : refine_bytes;
+    }
+    p.off_refine = off;  off = align_up(off + refine_bytes, 256);
     // the full tables of a chunk (table mode), or the codebooks with their rows padded to whole 64-byte units
     // (on-demand mode with rows shorter than that; 16 floats per row), or the sub-code planes and entries of the
     // split on-demand mode (used only where they fit): the region holds the larger of the first two
@@ -37,26 +53,15 @@ static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int f
         p.tables_bytes = tables > padded ? tables : padded;
         p.off_tables = off;  off = align_up(off + p.tables_bytes, 256);
     }
-    // The scan and the refinement lay their scratch out for the number of queries they are given, and
-    // a smaller batch does not always need less (fewer queries can mean more units or slices), so
-    // the regions hold the larger of what a full chunk and what the ragged last chunk need: those
-    // are the only two batch sizes the loop below ever passes.
-    const int tail = nq % chunk;
-    size_t scan_bytes = dcpq_scan_workspace_bytes(n_codes, m, chunk, r);
-    size_t refine_bytes = dcpq_refine_workspace_bytes(chunk, r);
-    if (tail) {
-        const size_t st = dcpq_scan_workspace_bytes(n_codes, m, tail, r), rt = dcpq_refine_workspace_bytes(tail, r);
-        scan_bytes = st > scan_bytes ? st : scan_bytes;
-        refine_bytes = rt > refine_bytes ? rt : refine_bytes;
+    p.off_scan = off;    // last: the scan's own last array is as long as the workspace allows
+    p.least = align_up(off + least_bytes, 256);
+    p.total = align_up(off + scan_bytes, 256);
+    // small problems take the two-kernel form where its arrays fit, over the tables (which it does not use) and the scan's
+    // (asked of the chunk: a batch of one chunk reserves no more than one with a ragged chunk behind it)
+    if (small_search_pays(n_codes, m, chunk)) {
+        const size_t t = align_up(p.off_tables + small_search_bytes(n_codes, chunk, r), 256);
+        p.total = t > p.total ? t : p.total;
     }
-    // small problems take the two-kernel form, whose arrays lie in the same region
-    if (small_search_pays(n_codes, m, nq)) {
-        const size_t b = small_search_bytes(n_codes, nq, r);
-        scan_bytes = b > scan_bytes ? b : scan_bytes;
-    }
-    p.off_scan = off;    off = align_up(off + scan_bytes, 256);
-    p.off_refine = off;  off = align_up(off + refine_bytes, 256);
-    p.total = off;
     return p;
 }
 
@@ -152,8 +157,9 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
     DCPQ_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255) == 0, "search: workspace must be 256-byte aligned");
     DCPQ_REQUIRE((reinterpret_cast<uintptr_t>(codes) & 15) == 0, "search: codes must be 16-byte aligned");
     const SearchPlan p = plan_search(n_codes, m, nq, r, b, chunk_queries);
-    if (workspace_bytes < p.total)
-        return fail(DCPQ_EWORKSPACE, "search: workspace %zu < %zu bytes", workspace_bytes, p.total);
+    if (workspace_bytes < p.least)
+        return fail(DCPQ_EWORKSPACE, "search: workspace %zu < %zu bytes", workspace_bytes, p.least);
+    const size_t room = workspace_bytes - p.off_scan;
     uint8_t *base = static_cast<uint8_t *>(workspace);
     uint8_t *qtab = base + p.off_qtab;
     float *bounds = reinterpret_cast<float *>(base + p.off_bounds);
@@ -171,12 +177,13 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
                                  "region (%zu bytes), or chunk * r reaches 2^32, or the queries are not 16-byte aligned",
                     refine_split_bytes(p.chunk, r, m, b / 8), p.tables_bytes);
     // small problems: candidates and their distances in two kernels (entries on demand, as DCPQ_REFINE_DIRECT computes them)
-    if (small_search_pays(n_codes, m, nq) && p.chunk == nq && (refine_mode == DCPQ_REFINE_AUTO || refine_mode == DCPQ_REFINE_DIRECT)) {
+    if (small_search_pays(n_codes, m, nq) && p.chunk == nq && small_search_bytes(n_codes, nq, r) <= workspace_bytes - p.off_tables &&
+        (refine_mode == DCPQ_REFINE_AUTO || refine_mode == DCPQ_REFINE_DIRECT)) {
         int rc = launch_small_tables(queries, nq, derived, m, dsub, bbar, codes, code_bytes, n_codes, r, qtab, bounds, nullptr, st,
-                                     reinterpret_cast<uint32_t *>(base + p.off_scan), small_search_clear_words(n_codes, nq, r));
+                                     reinterpret_cast<uint32_t *>(base + p.off_tables), small_search_clear_words(n_codes, nq, r));
         if (rc) return rc;
         const uint64_t *keys = nullptr;
-        rc = launch_small_search(queries, nq, codebooks, m, dsub, 1u << b, codes, code_bytes, n_codes, qtab, r, base + p.off_scan, &keys, st);
+        rc = launch_small_search(queries, nq, codebooks, m, dsub, 1u << b, codes, code_bytes, n_codes, qtab, r, tables, &keys, st);
         if (rc) return rc;
         return launch_topk_of_keys(keys, nq, r, k, ids, dist, base + p.off_refine, st);
     }
@@ -204,10 +211,10 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         // the quantized tables have 256 entries whatever bbar is, and 1-byte sub-codes are their own low-byte plane
         if (code_bytes == 1)
             rc = launch_scan(static_cast<const uint8_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd, base + p.off_scan,
-                             DCPQ_SCAN_AUTO, true, st);
+                             room, DCPQ_SCAN_AUTO, true, st);
         else
             rc = launch_scan(static_cast<const uint16_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd,
-                             base + p.off_scan, DCPQ_SCAN_AUTO, true, st);
+                             base + p.off_scan, room, DCPQ_SCAN_AUTO, true, st);
         if (rc) return rc;
         uint32_t *ids_c = ids + static_cast<size_t>(q0) * k;
         float *dist_c = dist + static_cast<size_t>(q0) * k;

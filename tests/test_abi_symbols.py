@@ -103,3 +103,16 @@ def test_search_workspace_covers_a_ragged_last_chunk(lib):
     # r above the supported range: no size is promised
     assert lib.dcpq_search_workspace_bytes(1 << 28, 8, 16, (1 << 26) + 1, 0) == 0
     assert lib.dcpq_scan_workspace_bytes(1 << 28, 8, 16, (1 << 26) + 1) == 0
+
+
+def test_smallest_scan_workspace_fits_the_static_scratch(lib):
+    """The arrays that only speed the scan up do not count against the static scratch: these problems fit its 64 MiB
+    without them (40 to 66 MB) and must not be refused for want of room."""
+    info = (ctypes.c_uint64 * 11)()
+    lib.dcpq_scan_workspace_bytes.restype = ctypes.c_size_t
+    lib.dcpq_scan_workspace_bytes.argtypes = [ctypes.c_uint64, ctypes.c_int, ctypes.c_int, ctypes.c_uint32]
+    for n, m, q, r in ((25_779_964, 32, 204, 588), (31_853, 16, 1027, 10), (653_859, 16, 436, 79), (21_643_743, 4, 71, 2071),
+                       (32_483_834, 32, 387, 37), (5, 4, 5358, 5), (5_500_638, 4, 85, 2298)):
+        assert lib.dcpq_scan_plan(ctypes.c_uint64(n), m, q, ctypes.c_uint32(r), 0, info, 11) == 0
+        assert info[10] <= 64 << 20, (n, m, q, r, info[10])
+        assert info[10] <= lib.dcpq_scan_workspace_bytes(n, m, q, r)

@@ -551,3 +551,35 @@ def test_scan_estimated_bound_too_low_is_redone(N, Q, pilot):
         binding.profile_enable(False)
     print("redo stages (ms, launches): hist+sample %s, tie count %s, collect %s"
           % (stages.get("scan_hist"), stages.get("scan_tiecount"), stages.get("scan_collect")), flush=True)
+
+
+@pytest.mark.parametrize("m,N,Q,r", [(4, 90_001, 5, 600), (8, 300_017, 70, 1500), (8, 2_000_003, 17, 4000), (16, 33_001, 130, 9000)])
+def test_smallest_workspace_gives_the_same_results(m, N, Q, r):
+    """A workspace smaller than the stated size is accepted as long as it holds what the scan cannot do without; the
+    scan then notes fewer candidates, or none, and small problems take the general kernels.  Same results, bit for bit."""
+    print("m=%d N=%d Q=%d r=%d" % (m, N, Q, r), flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    cb = torch.randn((m, 65536, 12), generator=g, device=DEV)
+    derived = binding.derive_codebooks(cb)
+    queries = torch.randn((Q, m * 12), generator=g, device=DEV)
+    codes = torch.randint(-32768, 32768, (N, m), generator=g, device=DEV, dtype=torch.int16).view(torch.uint16)
+    qtab, _, _ = binding.build_small_tables(queries, derived, codes, r)
+
+    def smallest(call):
+        with pytest.raises(binding.DcpqError) as e:
+            call(torch.empty(256, dtype=torch.uint8, device=DEV))
+        assert e.value.code == binding.EWORKSPACE
+        return int(str(e.value).rsplit("<", 1)[1].split()[0])
+
+    scan = lambda ws=None: binding.scan_candidates(codes, qtab, r, workspace=ws)
+    search = lambda ws=None: binding.search(queries, cb, derived, codes, r, 100, workspace=ws)
+    for call, full in ((scan, binding.scan_workspace_bytes(N, m, Q, r)), (search, binding.search_workspace_bytes(N, m, Q, r, 0, 16))):
+        want = call()
+        least = smallest(call)
+        assert least <= full and (call is search or least < full)
+        for size in {least, (least + full) // 2}:
+            got = call(torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV))
+            torch.cuda.synchronize()
+            for a, b in zip(got, want):
+                np.testing.assert_array_equal(to_np(a), to_np(b))
