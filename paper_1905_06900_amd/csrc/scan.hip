@@ -377,11 +377,14 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t
         const uint64_t rest = n_codes;
         // (a single tile does the same work in every workgroup, and one round of the 256 CUs measured
         // fastest for it; with several tiles the work per workgroup varies and more rounds even it out)
-        // Several tiles: at least 2048 workgroups in all and at least 128 per tile (measured: 4096 queries = 64
-        // tiles take 45.3 ms with 2048 workgroups, 41.5 ms with 8192, 43.4 ms with 131072; the rounds of
-        // workgroups end unevenly, the more so the longer a workgroup runs).
-        const uint64_t total = 128ull * p.ntiles > 2048 ? 128ull * p.ntiles : 2048;
-        const uint64_t want = p.ntiles == 1 ? 256 : (total + p.ntiles - 1) / p.ntiles;
+        // Several tiles: whole rounds of the 256 CUs (the tables of a tile leave a CU room for one workgroup; 11 tiles in
+        // 1034 workgroups, 10 more than four rounds, take 1.10 ms, in 2035 0.99, in 1023 0.955).  64 workgroups per tile and
+        // four rounds at least: a workgroup loads its tables and ends with its appends while its CU does nothing else (16 tiles,
+        // N = 1e7: 1.54 ms with 128 per tile, 1.49 with 64).  Twice as many where they would be longer than 2^20 codes, since
+        // the rounds end unevenly, the more so the longer a workgroup runs (64 tiles, N = 1e8: 41.1 ms with 128, 41.7 with 64, 43.5 with 32).
+        const uint64_t lots = rest > (64ull << 20) ? 2 : 1;
+        const uint64_t total = lots * (64ull * p.ntiles > 1024 ? 64ull * p.ntiles : 1024);
+        const uint64_t want = p.ntiles == 1 ? 256 : ((total + 255) / 256 * 256) / p.ntiles;
         // (down to 4096 codes where the chip would be left half empty: 100 queries over 1 M codes are 2 tiles)
         uint64_t least = 16384;
         while (least > 4096 && (rest + least - 1) / least * p.ntiles < 192) least >>= 1;
