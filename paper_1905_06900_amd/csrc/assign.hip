@@ -3,9 +3,9 @@
 //
 // Computed in two steps with the result of one.  A filter evaluates |c|^2 - 2 <x, c> for all centroids on
 // the bf16 matrix cores with every fp32 number split into two bf16 numbers (x = xh + xl + an error of at most
-// 2^-18 |x|; the three products xh ch + xl ch + xh cl lie side by side along the K dimension of one matrix
-// product whose accumulators start from |c|^2), and keeps per point the three smallest minima over cells of
-// 16 or 32 centroids.  A bound on the filter's error, from the norms at hand, says which cells can hold the nearest
+// 2^-17 |x|; the three products xh ch + xl ch + xh cl, and xl cl where it costs no further matrix instruction, lie
+// side by side along the K dimension of one matrix product whose accumulators start from |c|^2), and keeps per
+// point the three smallest minima over cells of 16, 32 or 64 centroids (16 of every 32 that a cell spans).  A bound on the filter's error, from the norms at hand, says which cells can hold the nearest
 // centroid: those, almost always one or two, are evaluated in double precision.  A point with more such cells
 // than were kept (or whose values are not finite) is compared with all centroids in double precision.
 //
@@ -82,7 +82,7 @@ __device__ inline void store_label(void *labels, int label_bytes, size_t o, uint
 
 // Nearest centroid of the j-th sub-vector of every point, j = blockIdx.y.  points: rows of `ld` floats;
 // sub-vector j starts at column j * dsub.  labels: [n][m].  dist (optional): [n][m] fp32 squared distance.
-// dp: dsub rounded up to a multiple of 4, 3 dp <= 16 KS.
+// dp: dsub rounded up to a multiple of 4, 3 dp <= 16 KS (4 dp <= 16 KS: all four products, half the filter's error).
 template <int KS, int P, bool SPLIT>
 __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
                                                      const float *__restrict__ cb, int m, int dsub, int dp, int ncent,
@@ -102,6 +102,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     const uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * C::PTS;
     const float *cbj = cb + static_cast<size_t>(j) * ncent * dsub;
     const int col = lane & 31, half = lane >> 5;
+    const bool four = KS <= 3 && 4 * dp <= 16 * KS;                 // K has room for the product xl cl (sub-vectors of up to 12)
 
     // A reference vector subtracted from points and centroids: distances do not change, norms (and with them the
     // filter's error) shrink.  The mean of up to 64 centroids spread over the codebook; any vector would do.
@@ -121,7 +122,8 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
 
     const int srow = tid / C::TPR, spart = tid % C::TPR;
     // The point side of the product: column `col` of B, K positions 16 ks + 8 half + e:
-    // [ -2 xh | -2 xl | -2 xh | 0 ... ] against the centroids' [ ch | ch | cl | 0 ... ].
+    // [ -2 xh | -2 xl | -2 xh | 0 ... ] against the centroids' [ ch | ch | cl | 0 ... ]; with room for four products
+    // [ -2 xh | -2 xl | -2 xh | -2 xl | 0 ... ] against [ ch | ch | cl | cl | 0 ... ].
     // Converted in rows by the whole workgroup, RS points at a time, and read back as operands.
     v8bf bq[P][KS];
 #pragma unroll
@@ -148,6 +150,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                     *reinterpret_cast<v4bf *>(row + 2 * o) = h;
                     *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = l;
                     *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = h;
+                    if (four) *reinterpret_cast<v4bf *>(row + 2 * (3 * dp + o)) = l;
                 }
             }
 #pragma unroll
@@ -208,6 +211,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                 *reinterpret_cast<v4bf *>(row + 2 * o) = h;
                 *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = h;
                 *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = l;
+                if (four) *reinterpret_cast<v4bf *>(row + 2 * (3 * dp + o)) = l;
             }
         }
 #pragma unroll
@@ -322,12 +326,17 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     __syncthreads();
     const float cmax = sqrtf(fmaxf(fmaxf(s_cmax[0], s_cmax[1]), fmaxf(s_cmax[2], s_cmax[3]))) * 1.001f;
 
-    // Error of a filter value, |c| <= c1:  2 |<x, c>| has 3 dropped products of relative size 2^-18 each; the K additions
+    // Error of a filter value, |c| <= c1.  bf16 has 8 significant bits: for 2^e <= |x| < 2^(e+1) the first rounding
+    // leaves |xl| <= 2^(e-8) and the second, of a number in a binade below that (or exactly on it, and then without
+    // error), at most 2^(e-17).  So |xl| <= 2^-8 |x|, x - xh - xl is at most 2^-17 |x|, and what the product of two
+    // numbers loses is xl cl (2^-16) and what the two remainders multiply (2^-17 each): 2^-15 |x| |c|, twice that in
+    // 2 |<x, c>|, 16 / 2^18; without the loss of xl cl half as much (15.91 and 7.98 are reached).  The K additions
     // (with the roundings of x - mu, c - mu and |c|^2 counted among them) lose at most 2^-23 of the sum of the
     // magnitudes each.  The last term covers values that vanish below the smallest bf16 numbers.
-    constexpr float kSplit = 6.2f / 262144.0f, kAdd = (16.0f * KS + 16.0f) / 8388608.0f;
-    auto filter_error = [](float xn, float c1) {
-        return xn * c1 * (kSplit + 2.1f * kAdd) + c1 * c1 * (1.1f * kAdd) + 1e-35f * (1.0f + xn + c1);
+    constexpr float kSplit3 = 16.2f / 262144.0f, kSplit4 = 8.1f / 262144.0f, kAdd = (16.0f * KS + 16.0f) / 8388608.0f;
+    const float split = four ? kSplit4 : kSplit3;
+    auto filter_error = [split](float xn, float c1) {
+        return xn * c1 * (split + 2.1f * kAdd) + c1 * c1 * (1.1f * kAdd) + 1e-35f * (1.0f + xn + c1);
     };
     // Largest filter value a nearest centroid can have.  The nearest centroid is no farther than the one with the
     // smallest filter value, so its norm is at most |x| plus that distance.

@@ -93,6 +93,42 @@ def test_assign_with_the_large_point_tiles(n, m, dsub):
         assert bool((chosen <= best + 1e-12 * ((x ** 2).sum(1) + float((c ** 2).sum(1).max()))).all()), "sub-quantizer %d" % j
 
 
+# The components at which a number and the sum of its two bf16 parts are as far apart, and the product of the two second
+# parts as large, as they get: just below and just above the middle between two bf16 numbers.
+SPLIT_BELOW = 1 + 2.0 ** -8 - 2.0 ** -16 + 2.0 ** -17 - 2.0 ** -23
+SPLIT_ABOVE = 1 + 2.0 ** -8 + 2.0 ** -16 - 2.0 ** -17 + 2.0 ** -23
+
+
+def worst_split_case(dsub, scale):
+    """256 centroids, all zero but 1 and 129, and a point along centroid 1 that is nearest to it but whose split products
+    favour 129.  scale 1: the point is centroid 1; above: their last components are 0 and just enough to make 129 the farther one."""
+    c = np.zeros((256, dsub), np.float32)
+    c[1], c[129] = SPLIT_BELOW, SPLIT_ABOVE
+    if scale != 1:
+        c[[1, 129], -1] = 0.0
+    x = np.float32(scale) * c[1:2]
+    d2 = lambda i: ((x[0].astype(np.float64) - c[i].astype(np.float64)) ** 2).sum()
+    if scale != 1:
+        c[129, -1] = np.sqrt(d2(1) - d2(129)) * (1 + 1e-4)
+    assert 0.0 <= d2(1) < d2(129) < d2(0)
+    return x, c
+
+
+@pytest.mark.parametrize("dsub,scale", [(1, 1), (2, 1), (4, 1), (8, 1)] + [(d, s) for d in (12, 16, 20) for s in (4, 8, 16, 64)])
+def test_assign_where_the_split_products_are_farthest_from_the_product(dsub, scale):
+    print("assign worst split dsub=%d scale=%d" % (dsub, scale), flush=True)
+    x, c = worst_split_case(dsub, scale)
+    pts = torch.from_numpy(np.repeat(x, 40, 0)).to(DEV)
+    labels, dist = binding.assign(pts, torch.from_numpy(c)[None].to(DEV), want_dist=True)
+    codes = binding.encode(pts, torch.from_numpy(c)[None].to(DEV))
+    torch.cuda.synchronize()
+    ref, rd = oracle.assign(x, c, want_dist=True)
+    assert ref[0] == 1
+    np.testing.assert_array_equal(to_np(labels)[:, 0], 1)
+    np.testing.assert_array_equal(to_np(codes)[:, 0], 1)
+    np.testing.assert_allclose(to_np(dist)[:, 0], rd[0], rtol=1e-6, atol=1e-12)
+
+
 @pytest.mark.parametrize("b", [16, 8])
 def test_encode_against_the_oracle(b):
     m, dsub, n = (4, 8, 3000) if b == 16 else (8, 4, 20000)
