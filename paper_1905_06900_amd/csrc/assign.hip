@@ -7,7 +7,8 @@
 // side by side along the K dimension of one matrix product whose accumulators start from |c|^2), and keeps per
 // point the three smallest minima over cells of 16, 32 or 64 centroids (16 of every 32 that a cell spans).  A bound on the filter's error, from the norms at hand, says which cells can hold the nearest
 // centroid: those, almost always one or two, are evaluated in double precision.  A point with more such cells
-// than were kept (or whose values are not finite) is compared with all centroids in double precision.
+// than were kept (or whose values are not finite) is compared with all centroids in double precision.  That is
+// most of the time where a codebook repeats itself, and with sub-vectors of one or two components.
 //
 // What bounds it: the matrix pipe (KS instructions of 32 cycles per 32 x 32 distances, KS = ceil(3 d / 16)) is busy
 // half of the time; beside it the vector port takes 9 instructions per 32 x 32 distances and 64 lanes for the minima
@@ -27,6 +28,14 @@ typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 
 struct __attribute__((packed, aligned(4))) f4_any { float v[4]; };
 
+// Comparison of points with all centroids in double precision.
+constexpr int kTogether = 32;     // points that a workgroup takes at a time, 8 per wavefront ...
+constexpr int kPerWave = 8;
+constexpr int kTileRows = 256;    // ... against 256 centroids, 4 per lane, 16 components at a time ...
+constexpr int kTileComps = 16;
+constexpr int kTileStride = 4 * kTileComps + 16;    // ... in rows of an odd number of 16-byte units
+constexpr uint32_t kFewHard = 8;  // up to so many points are taken one by one, by all threads (0.115 ms each at 65536 x 16, 32 together 1.3 ms)
+
 // KS: steps of 16 along K.  P: tiles of 32 points per wavefront.  SPLIT: the four wavefronts share the points
 // and split the centroids (else every wavefront has points of its own).  RS: centroids staged together.
 template <int KS, int P, bool SPLIT>
@@ -42,8 +51,13 @@ struct AssignCfg {
     static constexpr int NE = SPLIT ? 8 : 2;                   // lanes that hold minima of one point
     static constexpr int BUF_BYTES = RS * STRIDE + RS * 4;     // the rows, then |c|^2 of every row
     static constexpr int STAGE_BYTES = 2 * BUF_BYTES;
-    static constexpr int ENT_BYTES = PTS * NE * 5 * 4 + 3 * PTS * 4;    // minima, three lists of points
-    static constexpr int LDS_BYTES = STAGE_BYTES > ENT_BYTES ? STAGE_BYTES : ENT_BYTES;
+    static constexpr int LIST_BYTES = 3 * PTS * 4;             // three lists of points, behind them the minima ...
+    static constexpr int ENT_BYTES = LIST_BYTES + PTS * NE * 5 * 4;
+    static constexpr bool ROWS_IN_LDS = KS > 1;                // ... and in their place rows and points of the full comparison
+    static constexpr int ROW_BYTES = ROWS_IN_LDS ? kTileRows * kTileStride : 0;
+    static constexpr int LAST_BYTES = LIST_BYTES + ROW_BYTES + DPMAX * kTogether * 8;
+    static constexpr int USED_BYTES = ENT_BYTES > LAST_BYTES ? ENT_BYTES : LAST_BYTES;
+    static constexpr int LDS_BYTES = STAGE_BYTES > USED_BYTES ? STAGE_BYTES : USED_BYTES;
     static_assert(!SPLIT || RS == 128, "one 32-centroid tile per wavefront and stage");
 };
 
@@ -309,10 +323,10 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     }
 
     // hand the minima over: ent[point][lane that held them][b1, b2, b3, i1, i2]
-    float *ent = reinterpret_cast<float *>(smem);
+    float *ent = reinterpret_cast<float *>(smem + C::LIST_BYTES);
     uint32_t *list[3];                        // points with one cell to look at, with several, and for the full comparison
 #pragma unroll
-    for (int k = 0; k < 3; ++k) list[k] = reinterpret_cast<uint32_t *>(smem + C::PTS * C::NE * 20) + k * C::PTS;
+    for (int k = 0; k < 3; ++k) list[k] = reinterpret_cast<uint32_t *>(smem) + k * C::PTS;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int pt = SPLIT ? p * 32 + col : p * 128 + wave * 32 + col;
@@ -470,7 +484,121 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         }
         if (l16 == 0) put(q, best, bi);
     }
-    // the whole workgroup compares the points whose cells are not all known with every centroid
+    // Points whose cells are not all known are compared with every centroid.  They are few where centroids are well
+    // apart; where a codebook repeats itself, or its sub-vectors are so short that the filter cannot tell its centroids
+    // apart, they are most.
+    if (n_hard > kFewHard) {                                          // uniform
+        // 32 points at a time: their components lie in LDS in double precision, [component][point]; a wavefront takes 8 of
+        // them against 4 centroids per lane, so that one read of a component serves 32 products (bound by the
+        // double-precision vector instructions, two per component: seven tenths of their rate).  The centroids' rows reach the
+        // lanes through LDS, 16 components at a time, read one step ahead; rows of up to 4 components are read where they
+        // are.  20000 x 8 x 16, all centroids equal: 18 ms, an eighth of points and centroids zeros: 3.2 ms (one point at a
+        // time: 88 and 11.9; all distances on the double-precision matrix pipe: 8.0 both); 20000 x 32 x 1: 15.6 (82; 17.5).
+        uint8_t *tile = smem + C::LIST_BYTES;
+        double *xd = reinterpret_cast<double *>(tile + C::ROW_BYTES);
+        float4 ahead[4];
+        auto load_rows = [&](int c0, int o0) {                        // (4 lanes per row)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int f = tid + 256 * i, c = c0 + (f >> 2), o = o0 + 4 * (f & 3);
+                const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+                if (o + 4 <= dsub) {
+                    const f4_any v = *reinterpret_cast<const f4_any *>(src + o);
+                    ahead[i] = make_float4(v.v[0], v.v[1], v.v[2], v.v[3]);
+                } else {
+                    ahead[i] = make_float4(o < dsub ? src[o] : 0.0f, o + 1 < dsub ? src[o + 1] : 0.0f, o + 2 < dsub ? src[o + 2] : 0.0f, 0.0f);
+                }
+            }
+        };
+        const int last = (ncent - 1) / kTileRows * kTileRows;
+        for (uint32_t h0 = 0; h0 < n_hard; h0 += kTogether) {         // uniform
+            const uint32_t np = min(n_hard - h0, static_cast<uint32_t>(kTogether));
+            __syncthreads();                                          // the minima and the previous points are no longer read
+            for (int t = tid; t < kTogether * dsub; t += 256) {
+                const int p = t / dsub, o = t % dsub;
+                const uint64_t q = q0 + (list[2][h0 + (static_cast<uint32_t>(p) < np ? p : 0)] & 0xFFFFu);
+                xd[o * kTogether + p] = static_cast<double>(points[static_cast<size_t>(q) * ld + j * dsub + o]);
+            }
+            const double *xw = xd + wave * kPerWave;
+            double best[kPerWave];
+            uint32_t bi[kPerWave];
+#pragma unroll
+            for (int p = 0; p < kPerWave; ++p) { best[p] = INFINITY; bi[p] = 0xFFFFFFFFu; }
+            if constexpr (C::ROWS_IN_LDS) load_rows(last, 0);
+            else __syncthreads();
+            // (from the last centroid to the first, so that "no farther" leaves the smallest index of equal distances)
+            for (int c0 = last; c0 >= 0; c0 -= kTileRows) {           // uniform
+                double acc[4][kPerWave];                              // (as exact_distance adds them up)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int p = 0; p < kPerWave; ++p) acc[k][p] = 0.0;
+                for (int o0 = 0; o0 < dsub; o0 += kTileComps) {       // uniform
+                    if constexpr (C::ROWS_IN_LDS) {
+                        __syncthreads();                              // the rows before these are no longer read
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            *reinterpret_cast<float4 *>(tile + ((tid + 256 * i) >> 2) * kTileStride + 16 * (tid & 3)) = ahead[i];
+                        __syncthreads();                              // (also publishes the points)
+                        const bool more = o0 + kTileComps < dsub;
+                        if (more || c0 > 0) load_rows(more ? c0 : c0 - kTileRows, more ? o0 + kTileComps : 0);
+                    }
+#pragma unroll 1
+                    for (int o = o0; o < o0 + kTileComps && o < dsub; o += 4) {        // uniform
+                        float b[4][4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            if constexpr (C::ROWS_IN_LDS) {
+                                const float4 v = *reinterpret_cast<const float4 *>(tile + (64 * k + lane) * kTileStride + 4 * (o - o0));
+                                b[k][0] = v.x; b[k][1] = v.y; b[k][2] = v.z; b[k][3] = v.w;
+                            } else {
+                                const int c = c0 + 64 * k + lane;
+                                const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) b[k][e] = src[e < dsub ? e : 0];
+                            }
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (o + e >= dsub) break;                 // uniform
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const double cv = static_cast<double>(b[k][e]);
+#pragma unroll
+                                for (int p = 0; p < kPerWave; ++p) {
+                                    const double u = xw[(o + e) * kTogether + p] - cv;
+                                    acc[k][p] = fma(u, u, acc[k][p]);
+                                }
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int k = 3; k >= 0; --k) {
+                    const int c = c0 + 64 * k + lane;
+                    if (c >= ncent) continue;
+#pragma unroll
+                    for (int p = 0; p < kPerWave; ++p) {
+                        const bool take = acc[k][p] <= best[p];
+                        best[p] = take ? acc[k][p] : best[p];
+                        bi[p] = take ? static_cast<uint32_t>(c) : bi[p];
+                    }
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < kPerWave; ++p) {
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const double ov = __shfl_xor(best[p], off);
+                    const uint32_t oi = __shfl_xor(bi[p], off);
+                    take_smaller(best[p], bi[p], ov, oi);
+                }
+                const uint32_t h = wave * kPerWave + p;
+                if (lane == 0 && h < np) put(q0 + (list[2][h0 + h] & 0xFFFFu), best[p], bi[p]);
+            }
+        }
+        return;
+    }
     for (uint32_t hi = 0; hi < n_hard; ++hi) {                        // uniform
         const uint64_t q = q0 + (list[2][hi] & 0xFFFFu);
         const float *x = points + static_cast<size_t>(q) * ld + j * dsub;

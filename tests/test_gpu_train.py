@@ -77,6 +77,30 @@ def test_assign_at_the_edges_of_tiles_and_vector_lengths(dsub, n, ncent):
     np.testing.assert_allclose(to_np(dist)[:, 0], rd, rtol=1e-5, atol=1e-12 * float((p_np.astype(np.float64) ** 2).sum(1).max()))
 
 
+@pytest.mark.parametrize("dsub,ncent", [(1, 300), (3, 257), (4, 256), (5, 700), (16, 1000), (21, 255), (60, 300), (128, 513)])
+@pytest.mark.parametrize("n", [9, 33, 300])
+def test_assign_where_most_centroids_repeat(dsub, ncent, n):
+    # the filter cannot tell repeated centroids apart, so nearly all points are compared with all centroids: numbers of
+    # points and centroids around the tiles of that comparison, the smallest index of equal centroids, and points that
+    # are not finite among the others
+    print("assign repeats dsub=%d ncent=%d n=%d" % (dsub, ncent, n), flush=True)
+    g = gen(31 * dsub + n)
+    few = torch.randn((7, dsub), generator=g, device=DEV)
+    cb = few[torch.randint(0, 7, (ncent,), generator=g, device=DEV)][None].contiguous()
+    pts = few[torch.randint(0, 7, (n,), generator=g, device=DEV)] + 0.01 * torch.randn((n, dsub), generator=g, device=DEV)
+    pts[3] = 0.0
+    pts[5, dsub // 2] = float("nan")
+    pts[7, 0] = float("inf")
+    labels, dist = binding.assign(pts, cb, want_dist=True)
+    torch.cuda.synchronize()
+    labels, dist, p_np, c_np = to_np(labels)[:, 0], to_np(dist)[:, 0], to_np(pts), to_np(cb)[0]
+    d2 = ((p_np[:, None].astype(np.float64) - c_np[None]) ** 2).sum(2)
+    fine = np.isfinite(p_np).all(1)
+    np.testing.assert_array_equal(labels[fine], d2[fine].argmin(1))         # (numpy: the first of equals)
+    np.testing.assert_allclose(dist[fine], d2[fine].min(1), rtol=1e-6)
+    assert labels[5] == -1 and labels[7] == 0 and np.isinf(dist[7])        # no distance at all; all distances infinite
+
+
 @pytest.mark.parametrize("n,m,dsub", [(66_000, 8, 4), (140_000, 1, 16), (34_000, 16, 30)])
 def test_assign_with_the_large_point_tiles(n, m, dsub):
     print("assign large tiles n=%d m=%d dsub=%d" % (n, m, dsub), flush=True)
