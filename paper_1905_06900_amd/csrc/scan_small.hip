@@ -92,14 +92,14 @@ __global__ __launch_bounds__(kSmallThreads) void small_hist_kernel(const CodeT *
     uint8_t *ltab = smem;                                                     // [QT][M][256]
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + QT * M * 256);      // [4][QT][256]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q0 = blockIdx.y * QT, nqt = min(QT, nq - q0);
+    const int q0 = blockIdx.x * QT, nqt = min(QT, nq - q0);
     {
         const uint4 *src = reinterpret_cast<const uint4 *>(qtab + static_cast<size_t>(q0) * M * 256);
         for (int v = tid; v < nqt * M * 16; v += kSmallThreads) reinterpret_cast<uint4 *>(ltab)[v] = src[v];
         for (int v = tid; v < 4 * QT * 256; v += kSmallThreads) lhist[v] = 0;
     }
     __syncthreads();
-    const uint32_t begin = blockIdx.x * unit, end = min(n_codes, begin + unit);
+    const uint32_t begin = blockIdx.y * unit, end = min(n_codes, begin + unit);
     for (uint32_t base = begin; base < end; base += kSmallStep) {             // uniform
         const uint32_t i0 = base + wave * 256 + lane * 4;
         if (i0 >= end) continue;
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_hist_kernel(const CodeT *
     __syncthreads();
     for (int v = tid; v < nqt * 256; v += kSmallThreads) {
         const uint32_t c = lhist[v] + lhist[QT * 256 + v] + lhist[2 * QT * 256 + v] + lhist[3 * QT * 256 + v];
-        uint32_t *h = &bhist[(static_cast<size_t>(q0 + (v >> 8)) * nstretch + blockIdx.x / per) * 256 + (v & 255)];
+        uint32_t *h = &bhist[(static_cast<size_t>(q0 + (v >> 8)) * nstretch + blockIdx.y / per) * 256 + (v & 255)];
         if (per == 1) *h = c;
         else if (c) atomicAdd(h, c);
     }
@@ -147,8 +147,8 @@ __global__ __launch_bounds__(kSmallThreads) void small_collect_kernel(
     __shared__ float ent[kList * M];
     extern __shared__ __align__(16) float ly[];          // the query
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q = blockIdx.y, D = M * dsub;
-    const uint32_t blk = blockIdx.x;
+    const int q = blockIdx.x, D = M * dsub;
+    const uint32_t blk = blockIdx.y;
     for (int t = tid; t < D; t += kSmallThreads) ly[t] = queries[static_cast<size_t>(q) * D + t];
     {
         const int bucket = tid & 255, part = tid >> 8;
@@ -295,10 +295,11 @@ static int launch_small_m(const float *queries, int nq, const float *codebooks, 
     uint32_t *hist = reinterpret_cast<uint32_t *>(base + p.off_hist);
     uint64_t *keys = reinterpret_cast<uint64_t *>(base + p.off_keys);
     const size_t lds = static_cast<size_t>(QT) * M * 256 + 4 * QT * 256 * sizeof(uint32_t);
-    DCPQ_LAUNCH(kStageScanHist, st, (small_hist_kernel<M, CodeT>), dim3(p.nblocks, (nq + QT - 1) / QT), dim3(kSmallThreads), lds, codes,
+    // (queries along x: a batch over a few hundred 8-bit codes can have more of them than the 65535 that y is sure to take)
+    DCPQ_LAUNCH(kStageScanHist, st, (small_hist_kernel<M, CodeT>), dim3((nq + QT - 1) / QT, p.nblocks), dim3(kSmallThreads), lds, codes,
                 static_cast<uint32_t>(n_codes), p.unit, p.per, p.nstretch, qtab, nq, p.npad, qd, hist);
     DCPQ_CHECK_LAUNCH("small_hist_kernel");
-    DCPQ_LAUNCH(kStageScanCollect, st, (small_collect_kernel<M, CodeT>), dim3(p.nstretch, nq), dim3(kSmallThreads),
+    DCPQ_LAUNCH(kStageScanCollect, st, (small_collect_kernel<M, CodeT>), dim3(nq, p.nstretch), dim3(kSmallThreads),
                 sizeof(float) * M * dsub, codes, static_cast<uint32_t>(n_codes), p.unit * p.per, p.nstretch, qd, p.npad, hist, r, queries,
                 codebooks, dsub, table_size, keys);
     DCPQ_CHECK_LAUNCH("small_collect_kernel");

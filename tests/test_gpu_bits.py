@@ -137,3 +137,19 @@ def test_small_tables_with_one_and_two_queries_per_workgroup(Q):
         lo, hi = oracle.bounds(D, c_np, r)
         np.testing.assert_array_equal(small[q], D)
         np.testing.assert_array_equal(bounds[q], np.array([lo, hi], np.float32))
+
+
+def test_more_queries_than_a_grid_has_rows():
+    # 8-bit codes leave room for chunks of millions of queries; over so short an array they are a small problem
+    m, dsub, N, Q, r, k = 1, 4, 300, 70_001, 20, 5
+    print("small problem of %d queries" % Q, flush=True)
+    cb, codes, queries = make_case(m, dsub, 8, 8, N, Q, 4711)
+    derived = binding.derive_codebooks(cb, 8)
+    ids, dist = (to_np(t) for t in binding.search(queries, cb, derived, codes, r, k))
+    torch.cuda.synchronize()
+    cb_np, c_np, q_np = to_np(cb), to_np(codes), to_np(queries)
+    sel = [0, 35_000, 65_535, 65_536, Q - 1]
+    ref = oracle.search_flat(cb_np, to_np(derived), c_np, q_np[sel], r, k, 8, 8)
+    for a, q in enumerate(sel):
+        exact = oracle.refine(q_np[q], cb_np, c_np, ids[q], 8)
+        assert_topk_matches(ids[q], dist[q], ref["ids"][a], ref["dist"][a], exact, cand_ref=ref["cand_id"][a], tag="query %d" % q)
