@@ -66,30 +66,42 @@ __device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, uint32_
 }
 
 // Turns per-unit counts of bucket T into per-unit quotas: units are in id order, so unit u may
-// take min(count_u, need - sum of counts before u) ids (its smallest ones).  One workgroup of 256 threads.
-__device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need, uint32_t *part /* LDS [257] */)
+// take min(count_u, need - sum of counts before u) ids (its smallest ones).  One wavefront; a lane takes 8
+// neighbouring units, and the counts of the next 512 are on their way while these are added up.  (The counts may
+// just have been stored by other workgroups.)
+__device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need)
 {
-    const int t = threadIdx.x;
-    uint32_t &carry = part[256];
-    __syncthreads();
-    if (t == 0) carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < nunits; base += 256) {
-        const uint32_t u = base + t;
-        const uint32_t c = u < nunits ? row[u] : 0u;
-        part[t] = c;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const uint32_t add = t >= off ? part[t - off] : 0u;
-            __syncthreads();
-            part[t] += add;
-            __syncthreads();
+    constexpr uint32_t PER = 8, STEP = 64 * PER;
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t next[PER];
+    auto load = [&](uint32_t base) {
+#pragma unroll
+        for (uint32_t z = 0; z < PER; ++z) {
+            const uint32_t u = base + lane * PER + z;
+            next[z] = u < nunits ? __hip_atomic_load(&row[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
         }
-        const uint32_t before = carry + part[t] - c;       // exclusive prefix in id order
-        if (u < nunits) row[u] = before >= need ? 0u : min(c, need - before);
-        __syncthreads();
-        if (t == 255) carry += part[255];
-        __syncthreads();
+    };
+    load(0);
+    uint32_t carry = 0;                                        // ids of the bucket in the units before these
+    for (uint32_t base = 0; base < nunits; base += STEP) {     // uniform
+        uint32_t c[PER], mine = 0;
+#pragma unroll
+        for (uint32_t z = 0; z < PER; ++z) { c[z] = next[z]; mine += c[z]; }
+        if (base + STEP < nunits && carry < need) load(base + STEP);      // (no ids left to take: the rest is all zeros)
+        uint32_t incl = mine;
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t other = __shfl(incl, lane >= d ? lane - d : lane);
+            if (lane >= d) incl += other;
+        }
+        uint32_t before = carry + incl - mine;                 // exclusive prefix in id order
+#pragma unroll
+        for (uint32_t z = 0; z < PER; ++z) {
+            const uint32_t u = base + lane * PER + z;
+            if (u < nunits) row[u] = before >= need ? 0u : min(c[z], need - before);
+            before += c[z];
+        }
+        carry += __shfl(incl, 63);
     }
 }
 
@@ -203,16 +215,16 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
             if (u < nunits && lane == 0) {
 #pragma unroll
                 for (int q = 0; q < QT; ++q)
-                    if (q < nqt) tie[static_cast<size_t>(q0 + q) * nunits + u] = aux[q];
+                    if (q < nqt) __hip_atomic_store(&tie[static_cast<size_t>(q0 + q) * nunits + u], aux[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
 
         if (MODE != kCollect && end_of.done) {
             // Everything this workgroup has added is in place before its count is.  (Histograms are only added to by
-            // device-scope atomics, whose completion is all there is to wait for; a release fence would write back the
-            // second-level cache once per workgroup: 100 us for the sample of 251 queries.  The tie counts are stores.)
-            if (MODE == kHist) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            // device-scope atomics, and tie counts written by device-scope stores, whose completion is all there is to wait
+            // for; a release fence would write back the second-level cache once per workgroup: 100 us for the sample of 251
+            // queries.)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             uint32_t *last = reinterpret_cast<uint32_t *>(smem);
             if (tid == 0) *last = atomicAdd(&end_of.done[q0 / QT], 1u) == nxb - 1;
@@ -220,7 +232,6 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
             const bool mine = *last != 0;
             __syncthreads();
             if (mine) {                                               // uniform
-                if (MODE != kHist) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (MODE == kHist) {
                     for (int q = wave; q < nqt; q += kScanWaves) {
                         const uint32_t *h = hist + static_cast<size_t>(q0 + q) * 256;
@@ -228,26 +239,27 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
                         else exact_threshold(h, r, end_of.thr + 2 * (q0 + q));
                     }
                 } else {
-                    for (int q = 0; q < nqt; ++q)
-                        tie_quotas(tie + static_cast<size_t>(q0 + q) * nunits, nunits, end_of.thr[2 * (q0 + q) + 1], reinterpret_cast<uint32_t *>(smem));
+                    for (int q = wave; q < nqt; q += kScanWaves)
+                        tie_quotas(tie + static_cast<size_t>(q0 + q) * nunits, nunits, end_of.thr[2 * (q0 + q) + 1]);
                 }
             }
         }
     }
 }
 
-// The same steps as kernels of their own, for the inverted-list variant (a wavefront, and a workgroup, per query).
+// The same steps as kernels of their own, a wavefront per query: for the inverted-list variant, and for three passes over
+// all queries of a batch, where the launches are worth it (each tile's queries would wait for the one workgroup that ends
+// it: 21 queries over 1.6 M codes of one sub-code 738 us, 153 this way; 138 queries over 0.26 M 153 and 140).
 __global__ __launch_bounds__(256) void threshold_kernel(const uint32_t *__restrict__ hist, int nq, uint32_t r, uint32_t *__restrict__ thr)
 {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q < nq) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
 }
 
-__global__ __launch_bounds__(256) void tie_quota_kernel(uint32_t *__restrict__ tie, uint32_t nunits, const uint32_t *__restrict__ thr)
+__global__ __launch_bounds__(64) void tie_quota_kernel(uint32_t *__restrict__ tie, uint32_t nunits, const uint32_t *__restrict__ thr)
 {
-    __shared__ uint32_t part[257];
     const int q = blockIdx.x;
-    tie_quotas(tie + static_cast<size_t>(q) * nunits, nunits, thr[2 * q + 1], part);
+    tie_quotas(tie + static_cast<size_t>(q) * nunits, nunits, thr[2 * q + 1]);
 }
 
 // Sort the r collected keys of each active query by (qd, id) and split them into the two outputs.
@@ -316,7 +328,7 @@ int launch_threshold(const uint32_t *hist, int nq, uint32_t r, uint32_t *thr, hi
 
 int launch_tie_quota(uint32_t *tie, uint32_t nunits, int nq, const uint32_t *thr, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageSelect, st, tie_quota_kernel, dim3(nq), dim3(256), 0, tie, nunits, thr);
+    DCPQ_LAUNCH(kStageSelect, st, tie_quota_kernel, dim3(nq), dim3(64), 0, tie, nunits, thr);
     DCPQ_CHECK_LAUNCH("tie_quota_kernel");
     return DCPQ_OK;
 }
@@ -535,16 +547,26 @@ static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t
     uint32_t *done = reinterpret_cast<uint32_t *>(base + p.off_done);
     const size_t qtiles = (static_cast<size_t>(nq) + p.qt - 1) / p.qt;
     TileEnd after_hist{}, after_ties{};
-    after_hist.done = done + qtiles;
-    after_ties.done = done + 2 * qtiles;
+    if (few) {
+        after_hist.done = done + qtiles;
+        after_ties.done = done + 2 * qtiles;
+    }
     after_hist.thr = after_ties.thr = thr;
 
     launch_scan_pass<M, kHist>(kStageScanHist, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist, nq_dev, r,
                                hist, thr, tie, counter, keys, after_hist, few, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<hist>");
+    if (!few) {
+        const int rc = launch_threshold(hist, nq, r, thr, st);
+        if (rc) return rc;
+    }
     launch_scan_pass<M, kTieCount>(kStageScanTieCount, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist,
                                    nq_dev, r, hist, thr, tie, counter, keys, after_ties, few, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<tiecount>");
+    if (!few) {
+        const int rc = launch_tie_quota(tie, p.nunits, nq, thr, st);
+        if (rc) return rc;
+    }
     launch_scan_pass<M, kCollect>(kStageScanCollect, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist,
                                   nq_dev, r, hist, thr, tie, counter, keys, TileEnd{}, few, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<collect>");
