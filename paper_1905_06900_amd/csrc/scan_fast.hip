@@ -593,49 +593,71 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     // One returning atomic per query and workgroup instead of one per candidate, and one count per bucket that occurs: atomics on
     // the few cache lines of a query's cursors and counts follow each other at 13 to 20 ns (251 queries, r = 10000 from
     // 1 M codes: 410 us, of which 30 are the scan itself).  The tables are no longer needed: their LDS holds the counts.
-    __syncthreads();
+    // A workgroup with up to four candidates per query counts their buckets one by one: clearing and reading all counters
+    // of a tile takes it longer (300 queries, r = 10 from 4 M codes: 208 us for the scan).
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem);                                    // [QT][256]
-    uint32_t *lcur = reinterpret_cast<uint32_t *>(smem + C::TAB_BYTES + C::SCR_BYTES);       // [QT] position of the next one
+    uint32_t *lcur = reinterpret_cast<uint32_t *>(smem + C::TAB_BYTES + C::SCR_BYTES);       // [QT] number, then position of the next one
     uint32_t *lt0 = lcur + QT, *llast = lt0 + QT;                                            // starting buckets and their limits
-    static_assert(QT * 256 * 4 <= C::TAB_BYTES && 3 * 4 * QT <= C::Q_BYTES, "counts in place of the tables");
-    for (int v = tid; v < QT * 256; v += WAVES * 64) lhist[v] = 0;
+    uint32_t *ldue = llast + QT, *lrec = ldue + QT;                                          // bounds to be lowered; notes per wavefront
+    static_assert(QT * 256 * 4 <= C::TAB_BYTES && 4 * (4 * QT + WAVES) <= C::Q_BYTES, "counts in place of the tables");
+    __syncthreads();
+    if (lane == 0) lrec[wave] = nrec;
     if (tid < QT) {
         const bool limited = (upd & kLimited) && q0 + tid < nq;
+        lcur[tid] = 0;
         lt0[tid] = limited ? bound[q0 + tid].t0 : 256u;
         llast[tid] = limited ? bound[q0 + tid].last : 0u;
     }
     __syncthreads();
+    uint32_t all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) all += lrec[w];
+    if (all == 0) return;                                    // uniform
     auto wanted = [&](uint64_t rec) {
         const uint32_t qt = static_cast<uint32_t>(rec >> 40), qd = static_cast<uint32_t>(rec >> 32) & 255u;
         return qd != lt0[qt] || static_cast<uint32_t>(rec) <= llast[qt];
     };
-    for (uint32_t t = lane; t < nrec; t += 64) {
-        const uint64_t rec = mine[t];
-        if (wanted(rec)) atomicAdd(&lhist[static_cast<uint32_t>(rec >> 32)], 1u);            // (query << 8) | qd
-    }
-    __syncthreads();
-    const bool more = cap && gridDim.x * gridDim.y > 256;    // workgroups that can still use a lower bound
-    for (int qt = wave; qt < QT && q0 + qt < nq; qt += WAVES) {
-        uint32_t total = 0;
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            const uint32_t c = lhist[qt * 256 + 64 * z + lane];
-            if (c) atomicAdd(&chist[static_cast<size_t>(q0 + qt) * 256 + 64 * z + lane], c);
-            total += c;
+    const bool few = all <= 4 * QT;                          // uniform
+    if (few) {
+        for (uint32_t t = lane; t < nrec; t += 64) {
+            const uint64_t rec = mine[t];
+            if (!wanted(rec)) continue;
+            atomicAdd(&chist[static_cast<size_t>(q0) * 256 + static_cast<uint32_t>(rec >> 32)], 1u);     // (query << 8) | qd
+            atomicAdd(&lcur[static_cast<uint32_t>(rec >> 40)], 1u);
         }
+    } else {
+        for (int v = tid; v < QT * 256; v += WAVES * 64) lhist[v] = 0;
+        __syncthreads();
+        for (uint32_t t = lane; t < nrec; t += 64) {
+            const uint64_t rec = mine[t];
+            if (wanted(rec)) atomicAdd(&lhist[static_cast<uint32_t>(rec >> 32)], 1u);
+        }
+        __syncthreads();
+        for (int qt = wave; qt < QT && q0 + qt < nq; qt += WAVES) {
+            uint32_t total = 0;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
-        if (lane == 0) lcur[qt] = total;
+            for (int z = 0; z < 4; ++z) {
+                const uint32_t c = lhist[qt * 256 + 64 * z + lane];
+                if (c) atomicAdd(&chist[static_cast<size_t>(q0 + qt) * 256 + 64 * z + lane], c);
+                total += c;
+            }
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
+            if (lane == 0) lcur[qt] = total;
+        }
     }
     if (cap == 0) return;                                    // uniform over the grid: the pilot pass only counts
     __syncthreads();
-    if (tid < QT && q0 + tid < nq) {
-        const uint32_t total = lcur[tid];
+    if (tid < QT) {
+        const uint32_t total = lcur[tid], every = upd & ~kLimited;
+        uint32_t due = 0;
         if (total) {
             const uint32_t first = atomicAdd(&count[static_cast<size_t>(q0 + tid) * nslices + slice], total);
             lcur[tid] = first;
+            due = !few || first / every != (first + total) / every;
             if (first + total > cap) atomicMin(&bound[q0 + tid].t, -1);      // slice full: stop appending, query is redone
         }
+        ldue[tid] = due;
     }
     __syncthreads();
     for (uint32_t t = lane; t < nrec; t += 64) {
@@ -645,8 +667,9 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
         const uint32_t pos = atomicAdd(&lcur[qt], 1u);
         if (pos < cap) keys[((static_cast<size_t>(q0) + qt) * nslices + slice) * cap + pos] = rec & 0xFFFFFFFFFFull;
     }
-    if (more)                                                // uniform
-        for (int qt = wave; qt < QT && q0 + qt < nq; qt += WAVES) lower_bound_of(q0 + qt, r, bound, chist);
+    if (gridDim.x * gridDim.y > 256)                         // uniform: are there workgroups that can still use a lower bound?
+        for (int qt = wave; qt < QT; qt += WAVES)
+            if (ldue[qt]) lower_bound_of(q0 + qt, r, bound, chist);          // uniform
 }
 
 // Bound by its passes over the appended candidates (L2) and by the chain of short steps of one workgroup.  Dealing
