@@ -117,13 +117,13 @@ static bool split_first(int m, int dsub, int b, int nq, uint32_t r)
     return sub * ((m + 7) / 8) < (4u << 20) || refine_memo_slots(m, dsub, r) == 0 || static_cast<uint64_t>(nq) * r < (1u << 18);
 }
 
-// what dcpq_search runs
-static int refine_form(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r, const float *queries)
+// What a chunk of nq queries runs.
+enum Form { kTables, kOneKernel, kSplit, kOneKernelThenSplit };
+static Form refine_form(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r, const float *queries)
 {
-    if (requested != DCPQ_REFINE_AUTO) return requested;
-    const bool split = b == 16 && split_possible(p, m, b, nq, r, queries);
-    if (r > (1u << b) / 8 && !split) return DCPQ_REFINE_TABLES;
-    return split && split_first(m, dsub, b, nq, r) ? DCPQ_REFINE_SPLIT : DCPQ_REFINE_DIRECT;
+    if (requested != DCPQ_REFINE_AUTO) return requested == DCPQ_REFINE_TABLES ? kTables : requested == DCPQ_REFINE_DIRECT ? kOneKernel : kSplit;
+    if (b != 16 || !split_possible(p, m, b, nq, r, queries)) return r > (1u << b) / 8 ? kTables : kOneKernel;
+    return split_first(m, dsub, b, nq, r) ? kSplit : kOneKernelThenSplit;
 }
 
 // the size rule that dcpq_search_refine_mode reports
@@ -170,9 +170,9 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
     const int D = m * dsub;
     const int code_bytes = b / 8;
     const int tail = nq % p.chunk;
-    const int mode_full = refine_form(refine_mode, p, m, dsub, b, p.chunk, r, queries);
-    const int mode_tail = tail ? refine_form(refine_mode, p, m, dsub, b, tail, r, queries) : mode_full;
-    if (mode_full == DCPQ_REFINE_SPLIT && !split_possible(p, m, b, p.chunk, r, queries))
+    const Form full = refine_form(refine_mode, p, m, dsub, b, p.chunk, r, queries);
+    const Form last = tail ? refine_form(refine_mode, p, m, dsub, b, tail, r, queries) : full;
+    if (full == kSplit && !split_possible(p, m, b, p.chunk, r, queries))
         return fail(DCPQ_EINVAL, "search: DCPQ_REFINE_SPLIT: %zu bytes of sub-codes and entries per chunk do not fit the table "
                                  "region (%zu bytes), or chunk * r reaches 2^32, or the queries are not 16-byte aligned",
                     refine_split_bytes(p.chunk, r, m, b / 8), p.tables_bytes);
@@ -187,16 +187,15 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         if (rc) return rc;
         return launch_topk_of_keys(keys, nq, r, k, ids, dist, base + p.off_refine, st);
     }
-    const bool any_split = mode_full == DCPQ_REFINE_SPLIT || mode_tail == DCPQ_REFINE_SPLIT;
-    const bool any_direct = mode_full == DCPQ_REFINE_DIRECT || mode_tail == DCPQ_REFINE_DIRECT;
     // On demand in one kernel, a candidate gathers m centroid rows; a row shorter than a 64-byte unit that does not divide it
     // lies across two memory lines more often than it has to, so such codebooks are copied once per call into
     // rows of 16 floats (25 -> 33 MB at m = 8, dsub = 12: 30 microseconds, 6 % off the refinement).  Longer rows
-    // gain nothing and the copy costs more (measured at dsub = 60), so they are read in place.
+    // gain nothing and the copy costs more (measured at dsub = 60), so they are read in place.  The copy lies in the
+    // region that the other forms use for arrays of their own: it is made where the whole chunks run this form, and the last
+    // chunk, which comes after them, may still read it if it does too.
     const float *rows = codebooks;
     int cstride = dsub;
-    // (the split form reads the codebooks in place and uses the region for its own arrays: no copy then)
-    if (any_direct && !any_split && dsub < 16 && 16 % dsub != 0) {
+    if (full == kOneKernel && dsub < 16 && 16 % dsub != 0) {
         cstride = 16;
         int rc = launch_pad_rows(codebooks, static_cast<size_t>(m) << b, dsub, cstride, tables, st);
         if (rc) return rc;
@@ -218,12 +217,12 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         if (rc) return rc;
         uint32_t *ids_c = ids + static_cast<size_t>(q0) * k;
         float *dist_c = dist + static_cast<size_t>(q0) * k;
-        const int mode = nc == p.chunk ? mode_full : mode_tail;
-        if (mode == DCPQ_REFINE_SPLIT) {
+        switch (nc == p.chunk ? full : last) {
+        case kSplit:
             rc = launch_refine_split(y, codebooks, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c, dist_c,
                                      tables, base + p.off_refine, st);
-        } else if (mode == DCPQ_REFINE_DIRECT && refine_mode == DCPQ_REFINE_AUTO && b == 16 && split_possible(p, m, b, nc, r, queries) &&
-                   refine_memo_slots(m, dsub, r) != 0) {
+            break;
+        case kOneKernelThenSplit: {
             // (the integer distances are not needed any more: their place holds the queries left to the split form)
             uint32_t *left = reinterpret_cast<uint32_t *>(cand_qd);
             rc = launch_refine_direct(y, codebooks, dsub, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c,
@@ -231,14 +230,18 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
             if (rc) return rc;
             rc = launch_refine_split(y, codebooks, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c, dist_c,
                                      tables, base + p.off_refine, st, left);
-        } else if (mode == DCPQ_REFINE_DIRECT) {
+            break;
+        }
+        case kOneKernel:
             rc = launch_refine_direct(y, rows, dsub, cstride, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c,
                                       dist_c, base + p.off_refine, st);
-        } else {
+            break;
+        case kTables:
             rc = launch_distance_tables(y, nc, codebooks, m, dsub, 1 << b, tables, kStageFullTables, st);
             if (rc) return rc;
             rc = launch_refine(tables, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c, dist_c,
                                base + p.off_refine, st);
+            break;
         }
         if (rc) return rc;
     }

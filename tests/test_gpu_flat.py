@@ -361,6 +361,40 @@ def test_scan_selection_with_one_large_group_of_equal_candidates():
     scan_vs_oracle(codes2, qtab[1:], r)
 
 
+def stages_of(call):
+    """{stage: launches} of the library's kernels in one call"""
+    binding.profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return {name: launches for name, (_, launches) in binding.profile_read().items() if launches}
+    finally:
+        binding.profile_enable(False)
+
+
+def test_codebooks_are_padded_only_for_the_form_that_reads_the_copy():
+    # the memoized form with leftovers reads the codebooks where they are: rows of 12 floats (which the plain one-kernel
+    # form would have copied into rows of 16) take no launch more than rows of 16, and the explicit form does
+    print("padded codebooks", flush=True)
+    m, N, Q, r, k = 16, 40_000, 300, 1000, 20
+    launches = {}
+    for dsub in (12, 16):
+        g = torch.Generator(device=DEV); g.manual_seed(dsub)
+        cb = torch.randn((m, 65536, dsub), generator=g, device=DEV)
+        codes = torch.randint(-32768, 32768, (N, m), generator=g, device=DEV, dtype=torch.int32).to(torch.int16).view(torch.uint16)
+        queries = torch.randn((Q, m * dsub), generator=g, device=DEV)
+        derived = binding.derive_codebooks(cb)
+        for mode in (binding.REFINE_AUTO, binding.REFINE_DIRECT):
+            launches[dsub, mode] = stages_of(lambda: binding.search(queries, cb, derived, codes, r, k, refine_mode=mode))["refine_topk"]
+        got = binding.search(queries, cb, derived, codes, r, k)
+        want = binding.search(queries, cb, derived, codes, r, k, refine_mode=binding.REFINE_SPLIT)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(to_np(got[0]), to_np(want[0]))
+        np.testing.assert_array_equal(to_np(got[1]), to_np(want[1]))
+    assert launches[12, binding.REFINE_AUTO] == launches[16, binding.REFINE_AUTO] > 2
+    assert launches[12, binding.REFINE_DIRECT] == launches[16, binding.REFINE_DIRECT] + 1 == 2
+
+
 @pytest.mark.parametrize("r", [1, 900, 10_000, 15_900, 16_500])
 def test_scan_selection_deals_out_only_the_groups_that_reach_r(r):
     # tens of thousands of codes tie in the bucket of the r-th candidate (more than the selection holds), for r up to
