@@ -48,12 +48,14 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
                                                           uint32_t k, uint32_t n_pow2, int use_lds,
                                                           uint32_t memo_slots, uint64_t *__restrict__ spill,
                                                           uint32_t *__restrict__ ids, float *__restrict__ dist,
-                                                          uint32_t *__restrict__ left)
+                                                          uint32_t *__restrict__ left, CodeT *__restrict__ plane)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const int q = blockIdx.x;
     // left (optional).  kOnDemand: set for the queries whose entries cannot be memoized; they are left to the kernels that
-    // split the work by sub-quantizer.  kFromTerms: only the queries set there are worked on.
+    // split the work by sub-quantizer, and the sub-codes of their candidates are put where those look for them (plane, as
+    // gather_codes_kernel lays it out; a launch of its own for that would cost 4.5 us where nothing is left).
+    // kFromTerms: only the queries set there are worked on.
     if (MODE == kFromTerms && left && left[q] == 0) return;           // uniform
     uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(q) * n_pow2;
     constexpr bool DIRECT = MODE == kOnDemand;
@@ -211,7 +213,18 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
         }
         if (left) {                                                      // uniform
             if (threadIdx.x == 0) left[q] = memo ? 0u : 1u;
-            if (!memo) return;
+            if (!memo) {                                                 // uniform
+                const size_t total = static_cast<size_t>(gridDim.x) * r;
+                for (uint32_t t = threadIdx.x; t < r; t += blockDim.x) {
+                    const size_t at = static_cast<size_t>(q) * r + t;
+                    const uint32_t id = cand_id[at];
+                    uint32_t c[M];
+                    load_code(id < n_codes ? id : 0u, c);                // (pad slots: any valid sub-code)
+#pragma unroll
+                    for (int jj = 0; jj < M; ++jj) plane[jj * total + at] = static_cast<CodeT>(c[jj]);
+                }
+                return;
+            }
         }
         if (!memo) {                                                     // uniform
             // One lane per (candidate, sub-quantizer): the M lanes of a candidate are neighbours in a wavefront, each
@@ -370,7 +383,7 @@ uint32_t refine_memo_slots(int m, int dsub, uint32_t r)
 template <int M, typename CodeT, int MODE>
 static int launch_refine_m(const float *src, uint32_t table_size, const float *cb, int dsub, int cstride, const CodeT *codes,
                            uint64_t n_codes, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids,
-                           float *dist, void *ws, hipStream_t st, uint32_t *left = nullptr)
+                           float *dist, void *ws, hipStream_t st, uint32_t *left = nullptr, void *plane = nullptr)
 {
     const uint32_t np2 = next_pow2_r(r);
     const int use_lds = np2 <= kRefineLdsKeys;
@@ -387,7 +400,7 @@ static int launch_refine_m(const float *src, uint32_t table_size, const float *c
     if (rc) return rc;
     DCPQ_LAUNCH(kStageRefine, st, (refine_topk_kernel<M, CodeT, MODE>), dim3(nq), dim3(1024), lds, src, table_size, cb, dsub,
                 cstride, codes, static_cast<uint32_t>(n_codes), cand_id, r, k, np2, use_lds, memo_slots, static_cast<uint64_t *>(ws),
-                ids, dist, left);
+                ids, dist, left, static_cast<CodeT *>(plane));
     DCPQ_CHECK_LAUNCH("refine_topk_kernel");
     return DCPQ_OK;
 }
@@ -413,12 +426,12 @@ int launch_pad_rows(const float *src, size_t nrows, int dsub, int cstride, float
 template <typename CodeT, int MODE>
 static int launch_refine_t(const float *src, uint32_t table_size, const float *cb, int dsub, int cstride, const CodeT *codes,
                            uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids,
-                           float *dist, void *ws, hipStream_t st, uint32_t *left = nullptr)
+                           float *dist, void *ws, hipStream_t st, uint32_t *left = nullptr, void *plane = nullptr)
 {
     if (nq == 0) return DCPQ_OK;
 #define DCPQ_LAUNCH_REFINE(MV)                                                                                      \
     case MV:                                                                                                        \
-        return launch_refine_m<MV, CodeT, MODE>(src, table_size, cb, dsub, cstride, codes, n_codes, cand_id, nq, r, k, ids, dist, ws, st, left);
+        return launch_refine_m<MV, CodeT, MODE>(src, table_size, cb, dsub, cstride, codes, n_codes, cand_id, nq, r, k, ids, dist, ws, st, left, plane);
     switch (m) {
         DCPQ_LAUNCH_REFINE(1) DCPQ_LAUNCH_REFINE(2) DCPQ_LAUNCH_REFINE(4) DCPQ_LAUNCH_REFINE(8)
         DCPQ_LAUNCH_REFINE(16) DCPQ_LAUNCH_REFINE(32)
@@ -440,13 +453,13 @@ int launch_refine(const float *tables, uint32_t table_size, const void *codes, i
 
 int launch_refine_direct(const float *queries, const float *codebooks, int dsub, int cstride, uint32_t table_size, const void *codes,
                          int code_bytes, uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k,
-                         uint32_t *ids, float *dist, void *ws, hipStream_t st, uint32_t *left)
+                         uint32_t *ids, float *dist, void *ws, hipStream_t st, uint32_t *left, void *mid)
 {
     if (code_bytes == 1)
         return launch_refine_t<uint8_t, kOnDemand>(queries, table_size, codebooks, dsub, cstride, static_cast<const uint8_t *>(codes), n_codes,
-                                              m, cand_id, nq, r, k, ids, dist, ws, st, left);
+                                              m, cand_id, nq, r, k, ids, dist, ws, st, left, mid);
     return launch_refine_t<uint16_t, kOnDemand>(queries, table_size, codebooks, dsub, cstride, static_cast<const uint16_t *>(codes), n_codes, m,
-                                           cand_id, nq, r, k, ids, dist, ws, st, left);
+                                           cand_id, nq, r, k, ids, dist, ws, st, left, mid);
 }
 
 
@@ -468,12 +481,10 @@ int launch_refine_direct(const float *queries, const float *codebooks, int dsub,
 
 template <int M, typename CodeT>
 __global__ __launch_bounds__(256) void gather_codes_kernel(const CodeT *__restrict__ codes, uint32_t n_codes,
-                                                           const uint32_t *__restrict__ cand_id, uint32_t total,
-                                                           uint32_t r, const uint32_t *__restrict__ left, CodeT *__restrict__ plane)
+                                                           const uint32_t *__restrict__ cand_id, uint32_t total, CodeT *__restrict__ plane)
 {
     const uint32_t t = blockIdx.x * 256u + threadIdx.x;
     if (t >= total) return;
-    if (left && left[t / r] == 0) return;
     const uint32_t id = cand_id[t];
     constexpr int BYTES = M * static_cast<int>(sizeof(CodeT));
     CodeT c[M];
@@ -667,15 +678,17 @@ static int launch_refine_split_t(const float *queries, const float *codebooks, i
 #define DCPQ_LAUNCH_GATHER(MV)                                                                                      \
     case MV:                                                                                                        \
         DCPQ_LAUNCH(kStageRefine, st, (gather_codes_kernel<MV, CodeT>), g1, dim3(256), 0, codes,                     \
-                    static_cast<uint32_t>(n_codes), cand_id, total, r, left, plane);                                        \
+                    static_cast<uint32_t>(n_codes), cand_id, total, plane);                                                      \
         break;
-    switch (m) {
-        DCPQ_LAUNCH_GATHER(1) DCPQ_LAUNCH_GATHER(2) DCPQ_LAUNCH_GATHER(4) DCPQ_LAUNCH_GATHER(8)
-        DCPQ_LAUNCH_GATHER(16) DCPQ_LAUNCH_GATHER(32)
-        default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
+    if (!left) {                                 // (with it the one-kernel form has put the sub-codes of its leftovers there)
+        switch (m) {
+            DCPQ_LAUNCH_GATHER(1) DCPQ_LAUNCH_GATHER(2) DCPQ_LAUNCH_GATHER(4) DCPQ_LAUNCH_GATHER(8)
+            DCPQ_LAUNCH_GATHER(16) DCPQ_LAUNCH_GATHER(32)
+            default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
+        }
+        DCPQ_CHECK_LAUNCH("gather_codes_kernel");
     }
 #undef DCPQ_LAUNCH_GATHER
-    DCPQ_CHECK_LAUNCH("gather_codes_kernel");
     // a query's candidates in stretches of 512 and more, so that few queries still give two workgroups per CU and more
     uint32_t stretches = 1;
     while (static_cast<uint64_t>(nq) * m * stretches < 1024 && r / (2 * stretches) >= 512) stretches *= 2;
@@ -686,7 +699,7 @@ static int launch_refine_split_t(const float *queries, const float *codebooks, i
         DCPQ_LAUNCH(kStageRefine, st, (refine_terms_kernel<CodeT, PV>), dim3(8u * items * stretches), dim3(256), 0, queries, nq, m, dsub,    \
                     codebooks, table_size, plane, total, r, stretches, stretch, left, terms);                             \
         break;
-    // rows of up to 8 whole 16-byte parts, and 15 (60 components), go through LDS (codebooks are 16-byte aligned: the callers check)
+    // rows of up to 8 whole 16-byte parts go through LDS (codebooks are 16-byte aligned: the callers check)
     switch (dsub % 4 == 0 ? dsub / 4 : 0) {
         DCPQ_LAUNCH_TERMS(1) DCPQ_LAUNCH_TERMS(2) DCPQ_LAUNCH_TERMS(3) DCPQ_LAUNCH_TERMS(4) DCPQ_LAUNCH_TERMS(5)
         DCPQ_LAUNCH_TERMS(6) DCPQ_LAUNCH_TERMS(7) DCPQ_LAUNCH_TERMS(8)
@@ -699,7 +712,7 @@ static int launch_refine_split_t(const float *queries, const float *codebooks, i
 }
 
 // mid: refine_split_bytes(nq, r, m, code_bytes) bytes, 256-byte aligned; nq * r must fit 32 bits (the caller checks both);
-// left (optional): only the queries with a non-zero value
+// left (optional): only the queries with a non-zero value, whose sub-codes lie in mid already
 int launch_refine_split(const float *queries, const float *codebooks, int dsub, uint32_t table_size, const void *codes,
                         int code_bytes, uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k,
                         uint32_t *ids, float *dist, void *mid, void *ws, hipStream_t st, uint32_t *left)

@@ -226,7 +226,7 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
             // (the integer distances are not needed any more: their place holds the queries left to the split form)
             uint32_t *left = reinterpret_cast<uint32_t *>(cand_qd);
             rc = launch_refine_direct(y, codebooks, dsub, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c,
-                                      dist_c, base + p.off_refine, st, left);
+                                      dist_c, base + p.off_refine, st, left, tables);
             if (rc) return rc;
             rc = launch_refine_split(y, codebooks, dsub, 1u << b, codes, code_bytes, n_codes, m, cand_id, nc, r, k, ids_c, dist_c,
                                      tables, base + p.off_refine, st, left);
