@@ -101,7 +101,9 @@ extern "C" size_t dcpq_search_workspace_bytes(uint64_t n_codes, int m, int nq, u
 // (two for m = 16, four for m = 32) is smaller than one XCD's 4 MB cache (dsub < 16 at m = 8: the split form is never far
 // behind there), where there is nothing to memoize, or where the batch is small (below 2^18 candidates the attempt costs what
 // it can save: 50 queries, r = 3000: 33 one kernel, 35 split, 50 one after the other); else the one-kernel form first, and the split form for the queries
-// that it gives up.  Tables for 8-bit sub-codes, and where the split form's arrays do not fit and r > 2^b / 8 (a gathered row
+// that it gives up.  A query with a few candidates (an entry per thread of its workgroup at most) is worked out in one kernel at
+// once, where that reads the codebooks in place (m = 8, dsub = 16, r = 10, searches of 20 / 300 / 1000 queries: 78 / 168 / 278 us
+// against 82 / 172 / 285 split; r = 100: 90 / 198 / 330 and 94 / 199 / 329; r = 400: 89 / 230 / 404 and 89 / 222 / 381).  Tables for 8-bit sub-codes, and where the split form's arrays do not fit and r > 2^b / 8 (a gathered row
 // costs about 8 ps more than a table lookup and a 2^16-entry table 60 to 200 ns to build).
 static bool split_possible(const SearchPlan &p, int m, int b, int nq, uint32_t r, const float *queries)
 {
@@ -117,12 +119,16 @@ static bool split_first(int m, int dsub, int b, int nq, uint32_t r)
     return sub * ((m + 7) / 8) < (4u << 20) || refine_memo_slots(m, dsub, r) == 0 || static_cast<uint64_t>(nq) * r < (1u << 18);
 }
 
+// rows that the one-kernel form reads from a copy (see below)
+static bool pads_rows(int dsub) { return dsub < 16 && 16 % dsub != 0; }
+
 // What a chunk of nq queries runs.
 enum Form { kTables, kOneKernel, kSplit, kOneKernelThenSplit };
 static Form refine_form(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r, const float *queries)
 {
     if (requested != DCPQ_REFINE_AUTO) return requested == DCPQ_REFINE_TABLES ? kTables : requested == DCPQ_REFINE_DIRECT ? kOneKernel : kSplit;
     if (b != 16 || !split_possible(p, m, b, nq, r, queries)) return r > (1u << b) / 8 ? kTables : kOneKernel;
+    if (static_cast<uint64_t>(r) * m <= 1024 && !pads_rows(dsub)) return kOneKernel;
     return split_first(m, dsub, b, nq, r) ? kSplit : kOneKernelThenSplit;
 }
 
@@ -195,7 +201,7 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
     // chunk, which comes after them, may still read it if it does too.
     const float *rows = codebooks;
     int cstride = dsub;
-    if (full == kOneKernel && dsub < 16 && 16 % dsub != 0) {
+    if (full == kOneKernel && pads_rows(dsub)) {
         cstride = 16;
         int rc = launch_pad_rows(codebooks, static_cast<size_t>(m) << b, dsub, cstride, tables, st);
         if (rc) return rc;
