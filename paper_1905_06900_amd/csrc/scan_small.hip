@@ -23,11 +23,14 @@ constexpr int kSmallStep = 4096;            // codes a workgroup takes at a time
 constexpr uint32_t kSmallMostBlocks = 256;  // workgroups along the codes that compute qd ...
 // Stretches with a histogram of their own.  Every collector reads the histograms of all of them (with 128 stretches that was
 // half of the time for 16 queries over 1 M codes: 114 us, 76 with 32) and walks the qd bytes of its own (3 M codes, 8
-// queries: 147 us with 32 stretches, 107 with 128): their number grows with the root of codes per query.
+// queries: 147 us with 32 stretches, 107 with 128): their number grows with the root of codes per query.  Below that root
+// no more of them than give two collectors per CU: 550 queries over 60000 codes took 212 us with a collector for every
+// 4096 codes.
 static uint32_t small_stretches(uint64_t n_codes, int nq)
 {
     const double s = sqrt(static_cast<double>(n_codes) / (80.0 * nq));
-    return s < 16.0 ? 16u : s > 128.0 ? 128u : static_cast<uint32_t>(s);
+    const uint32_t fill = 512u / static_cast<uint32_t>(nq < 512 ? nq : 512), least = fill < 16u ? fill : 16u;
+    return s < least ? least : s > 128.0 ? 128u : static_cast<uint32_t>(s);
 }
 constexpr int small_qt(int m) { return m <= 8 ? 8 : 64 / m; }      // queries whose tables share a workgroup (<= 16 KiB)
 
