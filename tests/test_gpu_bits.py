@@ -108,6 +108,9 @@ def test_unsupported_widths_are_refused():
     (8, 6, 32, 4, 50_001, 5, 700),
     (16, 8, 8, 16, 1_200_003, 1, 12_000),   # a stretch per workgroup (no adding up of histograms)
     (8, 4, 2, 16, 1_000_001, 4, 3000),      # two sub-codes of 16 values each: tens of thousands of ties at the bound
+    (16, 4, 1, 6, 1_500_007, 1, 12_000),    # ... and of one: all candidates in the first stretch, more than its list holds
+    (16, 1, 8, 8, 700_001, 2, 9000),
+    (16, 8, 8, 6, 30_001, 300, 200),        # queries enough for one stretch each
 ])
 def test_small_problems_in_two_kernels(b, bbar, m, dsub, N, Q, r):
     # the same search through the staged calls (scan, full tables, refine)
@@ -123,6 +126,12 @@ def test_small_problems_in_two_kernels(b, bbar, m, dsub, N, Q, r):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(to_np(ids), to_np(want_ids))
         np.testing.assert_array_equal(to_np(dist), to_np(want_dist))
+    ids, dist, cb_np, codes_np = to_np(ids), to_np(dist), to_np(cb), to_np(codes).astype(np.uint16)
+    for q in {0, Q - 1}:
+        y = to_np(queries)[q:q + 1]
+        ref = oracle.search_flat(cb_np, to_np(derived), codes_np, y, r, k, b=b, bbar=bbar)
+        exact = oracle.refine(y[0], cb_np, codes_np, ids[q], b=b)
+        assert_topk_matches(ids[q], dist[q], ref["ids"][0], ref["dist"][0], exact, cand_ref=ref["cand_id"][0], tag="query %d" % q)
 
 
 @pytest.mark.parametrize("Q", [1, 499, 500, 501])
