@@ -893,7 +893,7 @@ __global__ __launch_bounds__(64 * IvfSampleCfg<M>::WAVES) void ivf_sample_kernel
                                                             const int32_t *__restrict__ probe, int nprobe,
                                                             const uint8_t *__restrict__ qtab, uint32_t r,
                                                             const uint32_t *__restrict__ probed, uint32_t *__restrict__ shist,
-                                                            uint32_t *__restrict__ done, Bound *bound)
+                                                            uint32_t *__restrict__ done, uint32_t cap, Bound *bound)
 {
     constexpr int NW = IvfSampleCfg<M>::WAVES, COPIES = 4;
     constexpr int RW = IvfRaw<M, CodeT>::RW, GPB = IvfRaw<M, CodeT>::GPB;
@@ -985,8 +985,10 @@ __global__ __launch_bounds__(64 * IvfSampleCfg<M>::WAVES) void ivf_sample_kernel
     __syncthreads();
     if (tid == 0) s_last = atomicAdd(&done[q], 1u) == gridDim.y - 1;
     __syncthreads();
-    // (a query with so many ties at the starting bucket that they would overflow its buffer is left to the three passes)
-    if (s_last && wave == 0) starting_bound(shist + static_cast<size_t>(q) * 256, r, probed[q], kCrowdedSkip, bound + q);
+    // A query with so many ties at the starting bucket that they would overflow its buffer is left to the three passes, at
+    // seven eighths of the buffer (the slices do not fill evenly).  The buffer is the measure, not r: below r = 512 it holds more
+    // than 32 r (255 queries, r = 3, two lists of 1400 codes: 168 us, 250 with every query left to the three passes).
+    if (s_last && wave == 0) starting_bound(shist + static_cast<size_t>(q) * 256, r, probed[q], kCrowdedSkip, bound + q, 0.875f * kFastSlices * static_cast<float>(cap));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1184,7 +1186,7 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
         int rows = nq >= 512 ? 2 : 1024 / nq;
         if (rows > most) rows = most;
         DCPQ_LAUNCH(kStageIvf, st, (ivf_sample_kernel<M, CodeT>), dim3(nq, rows), dim3(64 * NW), 0, codes, offsets, probe, nprobe,
-                    qtab, r, probed, shist, done, bound);
+                    qtab, r, probed, shist, done, p.cap, bound);
         DCPQ_CHECK_LAUNCH("ivf_sample_kernel");
     }
     {

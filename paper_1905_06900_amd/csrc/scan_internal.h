@@ -171,9 +171,10 @@ __device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c
 // selection sees fewer than r appended candidates and has the query redone by the three-pass path.
 // Where so many codes tie in that bucket that more than 16 r would be appended, only the codes with ids up to
 // twice the share of the bucket that is wanted are (kCrowdedLimit; ties are broken by id, and the sample's runs are spread
-// over the array), or none at all, which flags the query (kCrowdedSkip; no order of the ids is known).
+// over the array).  Where no order of the ids is known and more than `room` would be, none is, which flags the query
+// (kCrowdedSkip).
 enum Crowded { kCrowdedAppend = 0, kCrowdedLimit = 1, kCrowdedSkip = 2 };
-__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound)
+__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f)
 {
     const int lane = threadIdx.x & 63;
     uint32_t c[4], cum[4];
@@ -192,7 +193,7 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
             uint32_t last = 0xFFFFFFFFu;
             const float expect = static_cast<float>(cum[z]) * (static_cast<float>(n) / static_cast<float>(total));
             int t = 4 * lane + z;
-            if (crowded == kCrowdedSkip && n && expect > 16.0f * static_cast<float>(r)) t = -1;
+            if (crowded == kCrowdedSkip && n && expect > room) t = -1;
             if (crowded == kCrowdedLimit && expect > 16.0f * static_cast<float>(r)) {
                 const float upto = 2.0f * static_cast<float>(n) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
                 if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
