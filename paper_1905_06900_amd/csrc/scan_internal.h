@@ -171,8 +171,9 @@ __device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c
 // selection sees fewer than r appended candidates and has the query redone by the three-pass path.
 // Where so many codes tie in that bucket that more than 16 r would be appended, only the codes with ids up to
 // twice the share of the bucket that is wanted are (kCrowdedLimit; ties are broken by id, and the sample's runs are spread
-// over the array).  Where no order of the ids is known and more than `room` would be, none is, which flags the query
-// (kCrowdedSkip).
+// over the array).  Where no order of the ids is known and more than `room` would be (kCrowdedSkip), the bound starts one
+// bucket lower if that is likely to do (a standard deviation above the mean instead of five), and otherwise below all
+// buckets, which flags the query.
 enum Crowded { kCrowdedAppend = 0, kCrowdedLimit = 1, kCrowdedSkip = 2 };
 __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f)
 {
@@ -181,8 +182,9 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
     wave_prefix_of_buckets(shist, c, cum);
     const uint32_t total = __shfl(cum[3], 63);
     uint32_t rs = r;
+    float e = 0.0f;
     if (n) {                                                  // 0: the sample's own r-th smallest
-        const float e = static_cast<float>(r) * static_cast<float>(total) / static_cast<float>(n);
+        e = static_cast<float>(r) * static_cast<float>(total) / static_cast<float>(n);
         const float want = e + 5.0f * sqrtf(e) + 5.0f;
         if (want < static_cast<float>(r)) rs = static_cast<uint32_t>(want) + 1u;
     }
@@ -193,7 +195,7 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
             uint32_t last = 0xFFFFFFFFu;
             const float expect = static_cast<float>(cum[z]) * (static_cast<float>(n) / static_cast<float>(total));
             int t = 4 * lane + z;
-            if (crowded == kCrowdedSkip && n && expect > room) t = -1;
+            if (crowded == kCrowdedSkip && n && expect > room) t = static_cast<float>(before) >= e + sqrtf(e) ? t - 1 : -1;
             if (crowded == kCrowdedLimit && expect > 16.0f * static_cast<float>(r)) {
                 const float upto = 2.0f * static_cast<float>(n) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
                 if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
