@@ -26,7 +26,7 @@ constexpr int kIvfUnitsPerQuery = 1024;   // upper bound of scan units per query
 constexpr int kIvfMaxProbe = 512;         // nprobe supported by the per-query planning kernels
 constexpr uint32_t kIvfSampleStep = 32;   // the first 1 / kIvfSampleStep of every probed list (at most) is the sample that gives the scan its starting bounds
 constexpr uint32_t kIvfBins = 65536;      // bins of list ids that the scan's work is ordered by
-constexpr uint32_t kIvfMinPart = 512;     // codes a workgroup of the single-pass scan takes at least
+constexpr uint32_t kIvfMinPart = 512;     // codes a workgroup of the single-pass scan takes at least (large batches: twice as many)
 constexpr uint32_t kIvfNotes = 1024;      // candidates it can note until it has walked its part
 
 struct IvfUnit {
@@ -401,7 +401,7 @@ __device__ inline uint32_t ivf_bin_of(uint32_t list, uint32_t nlist)
 
 __global__ __launch_bounds__(256) void ivf_plan_kernel(const int32_t *__restrict__ probe, int nprobe,
                                                       const int64_t *__restrict__ offsets, uint32_t nlist, uint32_t r,
-                                                      uint32_t parts, IvfUnit *__restrict__ units,
+                                                      uint32_t parts, uint32_t min_part, IvfUnit *__restrict__ units,
                                                       uint32_t *__restrict__ nunits, uint32_t *__restrict__ count,
                                                       uint32_t *__restrict__ probed, uint32_t *__restrict__ part_of,
                                                       uint32_t *__restrict__ bins, uint32_t *__restrict__ rank,
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(256) void ivf_plan_kernel(const int32_t *__restrict
     if (unit < 256) unit = 256;
     uint64_t part = (total + parts - 1) / parts;
     part = (part + 255) / 256 * 256;
-    if (part < kIvfMinPart) part = kIvfMinPart;
+    if (part < min_part) part = min_part;
     // exclusive prefix sums of the units and parts per list, two lists per thread
     uint32_t nu[2], ni[2], incl[2];
 #pragma unroll
@@ -879,7 +879,9 @@ __global__ __launch_bounds__(256) void ivf_scan_parts_kernel(const CodeT *__rest
 // The starting bounds: a histogram of the integer distances of the first 1 / step of every probed list, and
 // from it the bucket that r of the query's probed codes would reach (starting_bound), by the workgroup that ends the
 // query last.  step is kIvfSampleStep, and more where that would be a sample of over 32 K codes, as long as 16 of the r are
-// expected in it.  Grid (nq, rows): the sample is cut into sets of codes, of which every wavefront of the query's takes
+// expected in it, and less where it would be one of under 1 K (every list gives one code at least: of short lists of unequal
+// length the short ones would give too many, and too low a bound sends the query to the three passes: 1416 queries, 8
+// lists of 225 codes: 450 us, now 348).  Grid (nq, rows): the sample is cut into sets of codes, of which every wavefront of the query's takes
 // as many (lists differ in length by orders of magnitude: with a wavefront per list the longest one's took 1.7 ms).
 // Bound by the latency of fetching a 2 KB table and a few hundred codes per list; a
 // workgroup counts in LDS and adds up once.  (As a wavefront per list with a histogram of its own the additions to
@@ -908,6 +910,7 @@ __global__ __launch_bounds__(64 * IvfSampleCfg<M>::WAVES) void ivf_sample_kernel
     for (int v = tid; v < COPIES * 256; v += 64 * NW) (&lhist[0][0])[v] = 0;
     uint32_t step = kIvfSampleStep;
     while (probed[q] / step > 32768 && r / step >= 32) step *= 2;
+    while (probed[q] / step < 1024 && step > 1) step /= 2;
     for (uint32_t p = tid; p < np; p += 64 * NW) {
         const int l = probe[static_cast<size_t>(q) * np + p];
         lbeg[p] = static_cast<uint64_t>(offsets[l]);
@@ -1083,7 +1086,8 @@ struct IvfScanPlan {
     // its parts: bins of list ids, cursor, finished sample workgroups (cleared with the rest); places, lengths, records
     size_t off_bins, off_cursor, off_done, off_rank, off_part, off_items, off_qlist;
     bool order;              // parts ordered by list
-    uint32_t parts;          // parts per query, about (and one more per probed list at most)
+    uint32_t parts;          // parts per query, about (and one more per probed list at most) ...
+    uint32_t min_part;       // ... of no fewer codes than this
     uint32_t cap, upd, sortcap;
 };
 
@@ -1103,6 +1107,9 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     // Parts: at least 128 per query, and 4096 in all, for 2048 resident workgroups.  They are ordered by list (two short launches more) where
     // there are queries enough to share lists or to crowd one another's cursors.
     p.parts = nq >= 32 ? 128u : 4096u / static_cast<uint32_t>(nq < 2 ? 2 : nq);
+    // (a part reads tables of 256 bytes per sub-quantizer; where queries are many enough parts are left with longer ones:
+    // 1040 queries, 5 lists of 11000 codes of 16: 463 us with parts of 512 codes, 418 with 1024)
+    p.min_part = nq >= 256 ? 2 * kIvfMinPart : kIvfMinPart;
     p.order = nq > 4;
     p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);
     p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);
@@ -1155,7 +1162,7 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
     uint32_t *part_of = reinterpret_cast<uint32_t *>(base + p.off_part);
     IvfUnit *items = reinterpret_cast<IvfUnit *>(base + p.off_items);
     DCPQ_LAUNCH(kStageIvf, st, ivf_plan_kernel, dim3(nq), dim3(256), 0, probe, nprobe, offsets, static_cast<uint32_t>(nlist), r,
-                p.parts, units, nunits, count, probed, part_of, bins, rank, cursor, items);
+                p.parts, p.min_part, units, nunits, count, probed, part_of, bins, rank, cursor, items);
     DCPQ_CHECK_LAUNCH("ivf_plan_kernel");
     if (p.order) {
         const uint32_t nbins = static_cast<uint32_t>(nlist) < kIvfBins ? static_cast<uint32_t>(nlist) : kIvfBins;
