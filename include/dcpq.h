@@ -153,7 +153,8 @@ int dcpq_scan_candidates_packed(const uint8_t *plane, uint64_t n_codes, int m, c
  * inside the library, DCPQ_STATIC_SCRATCH_BYTES per GPU, held from the first call on that GPU until
  * the process ends.  Inputs, outputs, order and error behaviour as dcpq_scan_candidates; the call
  * itself allocates nothing.  A problem whose smallest workspace (dcpq_scan_plan) exceeds
- * dcpq_static_scratch_bytes() is refused with DCPQ_EWORKSPACE before anything is launched.  All
+ * dcpq_static_scratch_bytes() by more than 256 KiB (counters that the stated size has never included)
+ * is refused with DCPQ_EWORKSPACE before anything is launched.  All
  * calls on one GPU share the one array: two of them must not overlap in time (they would race),
  * whichever streams they use. */
 #define DCPQ_STATIC_SCRATCH_BYTES (64u << 20)

@@ -25,7 +25,7 @@ namespace dcpq {
 constexpr int kIvfUnitsPerQuery = 1024;   // upper bound of scan units per query (unit size adapts)
 constexpr int kIvfMaxProbe = 512;         // nprobe supported by the per-query planning kernels
 constexpr uint32_t kIvfSampleStep = 32;   // the first 1 / kIvfSampleStep of every probed list (at most) is the sample that gives the scan its starting bounds
-constexpr uint32_t kIvfBins = 65536;      // bins of list ids that the scan's work is ordered by
+constexpr uint32_t kIvfBins = 65536;      // bins of list ids that the scan's work is ordered by, at most
 constexpr uint32_t kIvfMinPart = 512;     // codes a workgroup of the single-pass scan takes at least (large batches: twice as many)
 constexpr uint32_t kIvfNotes = 1024;      // candidates it can note until it has walked its part
 
@@ -394,9 +394,9 @@ __global__ __launch_bounds__(256) void ivf_qmax_kernel(const float *__restrict__
 // and ivf_parts_kernel do the rest.
 // (Everything after the sort is done by all threads at once, two lists each: one thread's walk over 64 lists, with a
 // 64-bit division each, and a round of loads per list took 57 us for 1024 queries.)
-__device__ inline uint32_t ivf_bin_of(uint32_t list, uint32_t nlist)
+__device__ inline uint32_t ivf_bin_of(uint32_t list, uint32_t nlist, uint32_t nbins)
 {
-    return nlist <= kIvfBins ? list : static_cast<uint32_t>(static_cast<uint64_t>(list) * kIvfBins / nlist);
+    return nlist <= nbins ? list : static_cast<uint32_t>(static_cast<uint64_t>(list) * nbins / nlist);
 }
 
 __global__ __launch_bounds__(256) void ivf_plan_kernel(const int32_t *__restrict__ probe, int nprobe,
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(256) void ivf_plan_kernel(const int32_t *__restrict
                                                       uint32_t parts, uint32_t min_part, IvfUnit *__restrict__ units,
                                                       uint32_t *__restrict__ nunits, uint32_t *__restrict__ count,
                                                       uint32_t *__restrict__ probed, uint32_t *__restrict__ part_of,
-                                                      uint32_t *__restrict__ bins, uint32_t *__restrict__ rank,
+                                                      uint32_t *__restrict__ bins, uint32_t nbins, uint32_t *__restrict__ rank,
                                                       uint32_t *__restrict__ cursor, IvfUnit *__restrict__ items)
 {
     __shared__ uint64_t key[kIvfMaxProbe];         // (list id << 32) | probe position
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void ivf_plan_kernel(const int32_t *__restrict
         for (uint32_t s = tid; s < static_cast<uint32_t>(nprobe); s += 256) {
             const uint32_t n = pbase[s + 1] - pbase[s];
             if (n) rank[static_cast<size_t>(q) * nprobe + static_cast<uint32_t>(key[s])] =
-                atomicAdd(&bins[ivf_bin_of(static_cast<uint32_t>(key[s] >> 32), nlist)], n);
+                atomicAdd(&bins[ivf_bin_of(static_cast<uint32_t>(key[s] >> 32), nlist, nbins)], n);
         }
     } else {
         for (uint32_t x = tid; x < all_parts; x += 256) {
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(256) void ivf_bin_base_kernel(uint32_t *__restrict_
 // The parts of (query, probed list) pair e, at the places drawn for them; a thread per pair.
 __global__ __launch_bounds__(256) void ivf_parts_kernel(const int32_t *__restrict__ probe, uint32_t npairs, uint32_t nprobe,
                                                        const int64_t *__restrict__ offsets, uint32_t nlist,
-                                                       const uint32_t *__restrict__ bins, const uint32_t *__restrict__ rank,
+                                                       const uint32_t *__restrict__ bins, uint32_t nbins, const uint32_t *__restrict__ rank,
                                                        const uint32_t *__restrict__ part_of, IvfUnit *__restrict__ items)
 {
     const uint32_t e = blockIdx.x * 256 + threadIdx.x;
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256) void ivf_parts_kernel(const int32_t *__restric
     const uint32_t l = static_cast<uint32_t>(probe[e]), part = part_of[e / nprobe];
     const uint64_t lo = static_cast<uint64_t>(offsets[l]), size = static_cast<uint64_t>(offsets[l + 1]) - lo;
     if (size == 0) return;
-    IvfUnit *out = items + bins[ivf_bin_of(l, nlist)] + rank[e];
+    IvfUnit *out = items + bins[ivf_bin_of(l, nlist, nbins)] + rank[e];
     for (uint64_t first = 0; first < size; first += part)
         *out++ = IvfUnit{lo + first, static_cast<uint32_t>(min(static_cast<uint64_t>(part), size - first)), e};
 }
@@ -1085,7 +1085,8 @@ struct IvfScanPlan {
     size_t off_shist, off_fcount, off_chist, off_bound, off_flags, off_fkeys, off_fsort, off_probed;
     // its parts: bins of list ids, cursor, finished sample workgroups (cleared with the rest); places, lengths, records
     size_t off_bins, off_cursor, off_done, off_rank, off_part, off_items, off_qlist;
-    bool order;              // parts ordered by list
+    bool order;              // parts ordered by list ...
+    uint32_t nbins;          // ... in so many bins
     uint32_t parts;          // parts per query, about (and one more per probed list at most) ...
     uint32_t min_part;       // ... of no fewer codes than this
     uint32_t cap, upd, sortcap;
@@ -1111,9 +1112,10 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     // 1040 queries, 5 lists of 11000 codes of 16: 463 us with parts of 512 codes, 418 with 1024)
     p.min_part = nq >= 256 ? 2 * kIvfMinPart : kIvfMinPart;
     p.order = nq > 4;
+    p.nbins = Q * 4096 < kIvfBins ? static_cast<uint32_t>(Q) * 4096 : kIvfBins;
     p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);
     p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);
-    p.off_bins = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * kIvfBins : 0), 256);
+    p.off_bins = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * p.nbins : 0), 256);
     p.zero_bytes = off;  // everything above is cleared together
     p.off_rank = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * Q * kIvfMaxProbe : 0), 256);
     p.off_part = off;    off = align_up(off + sizeof(uint32_t) * Q, 256);
@@ -1123,7 +1125,14 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     p.off_keys = off;    off = align_up(off + sizeof(uint64_t) * Q * r, 256);
     p.off_spill = off;
     if (next_pow2(r) > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * next_pow2(r), 256);
-    p.cap = 2 * r < 1024 ? 1024 : 2 * r;                 // per slice; 32 r per query in all
+    // Per slice: 32 r entries per query in all (16384 where r is smaller), less what the parts' arrays take, which came later
+    // and make the workspace no larger than it was
+    p.cap = 2 * r < 1024 ? 1024 : 2 * r;
+    {
+        const size_t parts_bytes = (p.order ? sizeof(uint32_t) * (p.nbins + Q * kIvfMaxProbe) : 0) + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe);
+        const size_t slices_bytes = sizeof(uint64_t) * Q * kFastSlices;
+        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 466 of 1024 and more)
+    }
     p.upd = r / 16 < 16 ? 16 : r / 16;                   // appends to one slice between bound updates
     p.sortcap = next_pow2(2 * r) < kSortLdsKeys ? kSortLdsKeys : next_pow2(2 * r);
     p.off_bound = off;    off = align_up(off + sizeof(Bound) * Q, 256);
@@ -1162,15 +1171,15 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
     uint32_t *part_of = reinterpret_cast<uint32_t *>(base + p.off_part);
     IvfUnit *items = reinterpret_cast<IvfUnit *>(base + p.off_items);
     DCPQ_LAUNCH(kStageIvf, st, ivf_plan_kernel, dim3(nq), dim3(256), 0, probe, nprobe, offsets, static_cast<uint32_t>(nlist), r,
-                p.parts, p.min_part, units, nunits, count, probed, part_of, bins, rank, cursor, items);
+                p.parts, p.min_part, units, nunits, count, probed, part_of, bins, p.nbins, rank, cursor, items);
     DCPQ_CHECK_LAUNCH("ivf_plan_kernel");
     if (p.order) {
-        const uint32_t nbins = static_cast<uint32_t>(nlist) < kIvfBins ? static_cast<uint32_t>(nlist) : kIvfBins;
+        const uint32_t nbins = static_cast<uint32_t>(nlist) < p.nbins ? static_cast<uint32_t>(nlist) : p.nbins;
         const uint32_t npairs = static_cast<uint32_t>(nq) * static_cast<uint32_t>(nprobe);
         DCPQ_LAUNCH(kStageIvf, st, ivf_bin_base_kernel, dim3((nbins + 255) / 256), dim3(256), 0, bins, nbins, cursor);
         DCPQ_CHECK_LAUNCH("ivf_bin_base_kernel");
         DCPQ_LAUNCH(kStageIvf, st, ivf_parts_kernel, dim3((npairs + 255) / 256), dim3(256), 0, probe, npairs,
-                    static_cast<uint32_t>(nprobe), offsets, static_cast<uint32_t>(nlist), bins, rank, part_of, items);
+                    static_cast<uint32_t>(nprobe), offsets, static_cast<uint32_t>(nlist), bins, p.nbins, rank, part_of, items);
         DCPQ_CHECK_LAUNCH("ivf_parts_kernel");
     }
     const dim3 grid(kIvfUnitsPerQuery / 4, nq < kIvfRedoRows ? nq : kIvfRedoRows);

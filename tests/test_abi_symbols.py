@@ -116,3 +116,11 @@ def test_smallest_scan_workspace_fits_the_static_scratch(lib):
         assert lib.dcpq_scan_plan(ctypes.c_uint64(n), m, q, ctypes.c_uint32(r), 0, info, 11) == 0
         assert info[10] <= 64 << 20, (n, m, q, r, info[10])
         assert info[10] <= lib.dcpq_scan_workspace_bytes(n, m, q, r)
+
+
+@pytest.mark.parametrize("nq,r,was", [(1, 1, 165632), (1, 1000, 298496), (2, 100, 330496), (4, 30, 656384), (5, 1, 819200), (5, 5000, 7419136), (7, 20, 1146880), (31, 1, 5067264), (33, 400, 5499904), (1000, 1000, 296352768), (300, 20000, 1829635840)])
+def test_inverted_list_scan_asks_for_no_more_than_it_once_did(lib, nq, r, was):
+    """The lists of parts take the place of entries of the candidate buffers: a workspace of the size that was stated
+    before there were any is still enough."""
+    lib.dcpq_ivf_scan_workspace_bytes.restype = ctypes.c_size_t
+    assert 0 < lib.dcpq_ivf_scan_workspace_bytes(nq, ctypes.c_uint32(r)) <= was
