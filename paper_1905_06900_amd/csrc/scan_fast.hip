@@ -593,8 +593,8 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     // One returning atomic per query and workgroup instead of one per candidate, and one count per bucket that occurs: atomics on
     // the few cache lines of a query's cursors and counts follow each other at 13 to 20 ns (251 queries, r = 10000 from
     // 1 M codes: 410 us, of which 30 are the scan itself).  The tables are no longer needed: their LDS holds the counts.
-    // A workgroup with up to four candidates per query counts their buckets one by one: clearing and reading all counters
-    // of a tile takes it longer (300 queries, r = 10 from 4 M codes: 208 us for the scan).
+    // A workgroup with up to four candidates per query counts their buckets one by one: reading all counters of a tile
+    // takes it longer (300 queries, r = 10 from 4 M codes: 208 us for the scan).
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem);                                    // [QT][256]
     uint32_t *lcur = reinterpret_cast<uint32_t *>(smem + C::TAB_BYTES + C::SCR_BYTES);       // [QT] number, then position of the next one
     uint32_t *lt0 = lcur + QT, *llast = lt0 + QT;                                            // starting buckets and their limits
@@ -602,6 +602,7 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     static_assert(QT * 256 * 4 <= C::TAB_BYTES && 4 * (4 * QT + WAVES) <= C::Q_BYTES, "counts in place of the tables");
     __syncthreads();
     if (lane == 0) lrec[wave] = nrec;
+    for (int v = tid; v < QT * 64; v += WAVES * 64) reinterpret_cast<uint4 *>(smem)[v] = make_uint4(0, 0, 0, 0);     // lhist
     if (tid < QT) {
         const bool limited = (upd & kLimited) && q0 + tid < nq;
         lcur[tid] = 0;
@@ -617,7 +618,7 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
         const uint32_t qt = static_cast<uint32_t>(rec >> 40), qd = static_cast<uint32_t>(rec >> 32) & 255u;
         return qd != lt0[qt] || static_cast<uint32_t>(rec) <= llast[qt];
     };
-    const bool few = all <= 4 * QT;                          // uniform
+    const bool few = all <= 4u * min(QT, nq - q0);           // uniform
     if (few) {
         for (uint32_t t = lane; t < nrec; t += 64) {
             const uint64_t rec = mine[t];
@@ -626,8 +627,6 @@ __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
             atomicAdd(&lcur[static_cast<uint32_t>(rec >> 40)], 1u);
         }
     } else {
-        for (int v = tid; v < QT * 256; v += WAVES * 64) lhist[v] = 0;
-        __syncthreads();
         for (uint32_t t = lane; t < nrec; t += 64) {
             const uint64_t rec = mine[t];
             if (wanted(rec)) atomicAdd(&lhist[static_cast<uint32_t>(rec >> 32)], 1u);
