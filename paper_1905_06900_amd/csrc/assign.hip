@@ -28,13 +28,11 @@ typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 
 struct __attribute__((packed, aligned(4))) f4_any { float v[4]; };
 
-// Comparison of points with all centroids in double precision.
-constexpr int kTogether = 32;     // points that a workgroup takes at a time, 8 per wavefront ...
-constexpr int kPerWave = 8;
-constexpr int kTileRows = 256;    // ... against 256 centroids, 4 per lane, 16 components at a time ...
+// Comparison of points with all centroids in double precision: components staged together, in rows of an odd number of
+// 16-byte units; up to kFewHard points are taken one by one, by all threads (0.115 ms each at 65536 x 16, 32 together 1.3 ms).
 constexpr int kTileComps = 16;
-constexpr int kTileStride = 4 * kTileComps + 16;    // ... in rows of an odd number of 16-byte units
-constexpr uint32_t kFewHard = 8;  // up to so many points are taken one by one, by all threads (0.115 ms each at 65536 x 16, 32 together 1.3 ms)
+constexpr int kTileStride = 4 * kTileComps + 16;
+constexpr uint32_t kFewHard = 8;
 
 // KS: steps of 16 along K.  P: tiles of 32 points per wavefront.  SPLIT: the four wavefronts share the points
 // and split the centroids (else every wavefront has points of its own).  RS: centroids staged together.
@@ -53,9 +51,13 @@ struct AssignCfg {
     static constexpr int STAGE_BYTES = 2 * BUF_BYTES;
     static constexpr int LIST_BYTES = 3 * PTS * 4;             // three lists of points, behind them the minima ...
     static constexpr int ENT_BYTES = LIST_BYTES + PTS * NE * 5 * 4;
-    static constexpr bool ROWS_IN_LDS = KS > 1;                // ... and in their place rows and points of the full comparison
-    static constexpr int ROW_BYTES = ROWS_IN_LDS ? kTileRows * kTileStride : 0;
-    static constexpr int LAST_BYTES = LIST_BYTES + ROW_BYTES + DPMAX * kTogether * 8;
+    // The full comparison: points per wavefront and centroids per lane, points and centroids at a time.  (The tiles that split
+    // the centroids are for few points: registers for more at a time would halve the wavefronts in flight there.)
+    static constexpr int PER_WAVE = SPLIT ? 4 : 8, PER_LANE = SPLIT ? 1 : 4;
+    static constexpr int TOGETHER = 4 * PER_WAVE, ROWS = 64 * PER_LANE;
+    static constexpr bool ROWS_IN_LDS = KS > 1;                // ... and in place of the minima its rows and points
+    static constexpr int ROW_BYTES = ROWS_IN_LDS ? ROWS * kTileStride : 0;
+    static constexpr int LAST_BYTES = LIST_BYTES + ROW_BYTES + DPMAX * TOGETHER * 8;
     static constexpr int USED_BYTES = ENT_BYTES > LAST_BYTES ? ENT_BYTES : LAST_BYTES;
     static constexpr int LDS_BYTES = STAGE_BYTES > USED_BYTES ? STAGE_BYTES : USED_BYTES;
     static_assert(!SPLIT || RS == 128, "one 32-centroid tile per wavefront and stage");
@@ -487,19 +489,24 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     // Points whose cells are not all known are compared with every centroid.  They are few where centroids are well
     // apart; where a codebook repeats itself, or its sub-vectors are so short that the filter cannot tell its centroids
     // apart, they are most.
+    // (the thread's number is taken afresh, so that nothing derived from it is kept, spilled, over the loop above)
+    int tid_now = tid;
+    asm volatile("" : "+v"(tid_now));
     if (n_hard > kFewHard) {                                          // uniform
+        const int tid = tid_now, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         // 32 points at a time: their components lie in LDS in double precision, [component][point]; a wavefront takes 8 of
-        // them against 4 centroids per lane, so that one read of a component serves 32 products (bound by the
+        // them against 4 centroids per lane, so that eight components read serve 32 products (bound by the
         // double-precision vector instructions, two per component: seven tenths of their rate).  The centroids' rows reach the
         // lanes through LDS, 16 components at a time, read one step ahead; rows of up to 4 components are read where they
         // are.  20000 x 8 x 16, all centroids equal: 18 ms, an eighth of points and centroids zeros: 3.2 ms (one point at a
         // time: 88 and 11.9; all distances on the double-precision matrix pipe: 8.0 both); 20000 x 32 x 1: 15.6 (82; 17.5).
         uint8_t *tile = smem + C::LIST_BYTES;
         double *xd = reinterpret_cast<double *>(tile + C::ROW_BYTES);
-        float4 ahead[4];
+        constexpr int LOADS = C::PER_LANE;                               // 16-byte parts of a tile per thread
+        float4 ahead[LOADS];
         auto load_rows = [&](int c0, int o0) {                        // (4 lanes per row)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < LOADS; ++i) {
                 const int f = tid + 256 * i, c = c0 + (f >> 2), o = o0 + 4 * (f & 3);
                 const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
                 if (o + 4 <= dsub) {
@@ -510,44 +517,44 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                 }
             }
         };
-        const int last = (ncent - 1) / kTileRows * kTileRows;
-        for (uint32_t h0 = 0; h0 < n_hard; h0 += kTogether) {         // uniform
-            const uint32_t np = min(n_hard - h0, static_cast<uint32_t>(kTogether));
+        const int last = (ncent - 1) / C::ROWS * C::ROWS;
+        for (uint32_t h0 = 0; h0 < n_hard; h0 += C::TOGETHER) {         // uniform
+            const uint32_t np = min(n_hard - h0, static_cast<uint32_t>(C::TOGETHER));
             __syncthreads();                                          // the minima and the previous points are no longer read
-            for (int t = tid; t < kTogether * dsub; t += 256) {
+            for (int t = tid; t < C::TOGETHER * dsub; t += 256) {
                 const int p = t / dsub, o = t % dsub;
                 const uint64_t q = q0 + (list[2][h0 + (static_cast<uint32_t>(p) < np ? p : 0)] & 0xFFFFu);
-                xd[o * kTogether + p] = static_cast<double>(points[static_cast<size_t>(q) * ld + j * dsub + o]);
+                xd[o * C::TOGETHER + p] = static_cast<double>(points[static_cast<size_t>(q) * ld + j * dsub + o]);
             }
-            const double *xw = xd + wave * kPerWave;
-            double best[kPerWave];
-            uint32_t bi[kPerWave];
+            const double *xw = xd + wave * C::PER_WAVE;
+            double best[C::PER_WAVE];
+            uint32_t bi[C::PER_WAVE];
 #pragma unroll
-            for (int p = 0; p < kPerWave; ++p) { best[p] = INFINITY; bi[p] = 0xFFFFFFFFu; }
+            for (int p = 0; p < C::PER_WAVE; ++p) { best[p] = INFINITY; bi[p] = 0xFFFFFFFFu; }
             if constexpr (C::ROWS_IN_LDS) load_rows(last, 0);
             else __syncthreads();
             // (from the last centroid to the first, so that "no farther" leaves the smallest index of equal distances)
-            for (int c0 = last; c0 >= 0; c0 -= kTileRows) {           // uniform
-                double acc[4][kPerWave];                              // (as exact_distance adds them up)
+            for (int c0 = last; c0 >= 0; c0 -= C::ROWS) {           // uniform
+                double acc[C::PER_LANE][C::PER_WAVE];                              // (as exact_distance adds them up)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+                for (int k = 0; k < C::PER_LANE; ++k)
 #pragma unroll
-                    for (int p = 0; p < kPerWave; ++p) acc[k][p] = 0.0;
+                    for (int p = 0; p < C::PER_WAVE; ++p) acc[k][p] = 0.0;
                 for (int o0 = 0; o0 < dsub; o0 += kTileComps) {       // uniform
                     if constexpr (C::ROWS_IN_LDS) {
                         __syncthreads();                              // the rows before these are no longer read
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
+                        for (int i = 0; i < LOADS; ++i)
                             *reinterpret_cast<float4 *>(tile + ((tid + 256 * i) >> 2) * kTileStride + 16 * (tid & 3)) = ahead[i];
                         __syncthreads();                              // (also publishes the points)
                         const bool more = o0 + kTileComps < dsub;
-                        if (more || c0 > 0) load_rows(more ? c0 : c0 - kTileRows, more ? o0 + kTileComps : 0);
+                        if (more || c0 > 0) load_rows(more ? c0 : c0 - C::ROWS, more ? o0 + kTileComps : 0);
                     }
 #pragma unroll 1
                     for (int o = o0; o < o0 + kTileComps && o < dsub; o += 4) {        // uniform
-                        float b[4][4];
+                        float b[C::PER_LANE][4];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
+                        for (int k = 0; k < C::PER_LANE; ++k) {
                             if constexpr (C::ROWS_IN_LDS) {
                                 const float4 v = *reinterpret_cast<const float4 *>(tile + (64 * k + lane) * kTileStride + 4 * (o - o0));
                                 b[k][0] = v.x; b[k][1] = v.y; b[k][2] = v.z; b[k][3] = v.w;
@@ -562,11 +569,11 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                         for (int e = 0; e < 4; ++e) {
                             if (o + e >= dsub) break;                 // uniform
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) {
+                            for (int k = 0; k < C::PER_LANE; ++k) {
                                 const double cv = static_cast<double>(b[k][e]);
 #pragma unroll
-                                for (int p = 0; p < kPerWave; ++p) {
-                                    const double u = xw[(o + e) * kTogether + p] - cv;
+                                for (int p = 0; p < C::PER_WAVE; ++p) {
+                                    const double u = xw[(o + e) * C::TOGETHER + p] - cv;
                                     acc[k][p] = fma(u, u, acc[k][p]);
                                 }
                             }
@@ -574,11 +581,11 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                     }
                 }
 #pragma unroll
-                for (int k = 3; k >= 0; --k) {
+                for (int k = C::PER_LANE - 1; k >= 0; --k) {
                     const int c = c0 + 64 * k + lane;
                     if (c >= ncent) continue;
 #pragma unroll
-                    for (int p = 0; p < kPerWave; ++p) {
+                    for (int p = 0; p < C::PER_WAVE; ++p) {
                         const bool take = acc[k][p] <= best[p];
                         best[p] = take ? acc[k][p] : best[p];
                         bi[p] = take ? static_cast<uint32_t>(c) : bi[p];
@@ -586,14 +593,14 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                 }
             }
 #pragma unroll
-            for (int p = 0; p < kPerWave; ++p) {
+            for (int p = 0; p < C::PER_WAVE; ++p) {
 #pragma unroll
                 for (int off = 1; off < 64; off <<= 1) {
                     const double ov = __shfl_xor(best[p], off);
                     const uint32_t oi = __shfl_xor(bi[p], off);
                     take_smaller(best[p], bi[p], ov, oi);
                 }
-                const uint32_t h = wave * kPerWave + p;
+                const uint32_t h = wave * C::PER_WAVE + p;
                 if (lane == 0 && h < np) put(q0 + (list[2][h0 + h] & 0xFFFFu), best[p], bi[p]);
             }
         }
