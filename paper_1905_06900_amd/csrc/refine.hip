@@ -26,6 +26,9 @@ static uint32_t next_pow2_r(uint32_t x)
     return p;
 }
 
+// LDS bytes of n keys, up to a whole 16-byte vector (the query behind them is read in vectors, and r = 1 makes one key)
+__host__ __device__ inline size_t key_bytes(uint32_t n) { return (sizeof(uint64_t) * n + 15) & ~static_cast<size_t>(15); }
+
 constexpr int kFromTables = 0, kOnDemand = 1, kFromTerms = 2, kFromKeys = 3;     // where refine_topk_kernel takes its entries from
 
 // CodeT: uint16_t or uint8_t sub-codes; table_size = 2^b entries per sub-quantizer.
@@ -63,7 +66,7 @@ __global__ __launch_bounds__(1024) void refine_topk_kernel(const float *__restri
     float *ly = nullptr;
     if constexpr (DIRECT) {
         const int D = M * dsub;
-        ly = reinterpret_cast<float *>(smem + (use_lds ? sizeof(uint64_t) * n_pow2 : 0));     // the query
+        ly = reinterpret_cast<float *>(smem + (use_lds ? key_bytes(n_pow2) : 0));     // the query
         for (int t = threadIdx.x; t < D; t += blockDim.x) ly[t] = src[static_cast<size_t>(q) * D + t];
         __syncthreads();
     } else if constexpr (MODE == kFromTables) {
@@ -387,7 +390,7 @@ static int launch_refine_m(const float *src, uint32_t table_size, const float *c
 {
     const uint32_t np2 = next_pow2_r(r);
     const int use_lds = np2 <= kRefineLdsKeys;
-    size_t lds = (use_lds ? sizeof(uint64_t) * np2 : 0) + (MODE == kOnDemand ? sizeof(float) * M * dsub : 0);
+    size_t lds = (use_lds ? key_bytes(np2) : 0) + (MODE == kOnDemand ? sizeof(float) * M * dsub : 0);
     // on demand: a hash set of the query's distinct (sub-quantizer, sub-code) pairs with their entries, as many
     // slots per sub-quantizer (a power of two, at most 512) as the LDS left beside the keys, the query and the
     // kernel's static arrays (17 KB) holds; none if that is fewer than 64

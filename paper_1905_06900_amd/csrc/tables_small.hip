@@ -37,6 +37,9 @@ __global__ __launch_bounds__(256) void derive_kernel(const float *__restrict__ c
 // it is a chain of memory round trips, which 1024 threads shorten (251 queries of 8 x 16, r = 10000: 23 -> 12 us).
 constexpr int kSmallTabThreads = 1024;
 
+// floats of the tables, up to a whole 16-byte vector (one query, one sub-quantizer and bbar = 1 make two floats)
+__host__ __device__ inline int table_floats(int qpb, int m, int small_bits) { return ((qpb * m << small_bits) + 3) & ~3; }
+
 template <int M, int QPB, typename CodeT>
 __global__ __launch_bounds__(kSmallTabThreads) void small_tables_kernel(
     const float *__restrict__ queries, int nq, const float *__restrict__ derived, int dsub, int small_bits,
@@ -48,7 +51,7 @@ __global__ __launch_bounds__(kSmallTabThreads) void small_tables_kernel(
     const int D = M * dsub;
     const int ks = 1 << small_bits, mask = ks - 1;
     float *ltab = lds;                     // [QPB][M][2^bbar]
-    float *ly = lds + QPB * M * ks;        // [QPB][M*dsub]
+    float *ly = lds + table_floats(QPB, M, small_bits);        // [QPB][M*dsub], 16-byte aligned (it is read in vectors)
     __shared__ float red[QPB][16];
     for (size_t w = static_cast<size_t>(blockIdx.x) * kSmallTabThreads + tid; w < clear_words / 4; w += static_cast<size_t>(gridDim.x) * kSmallTabThreads)
         reinterpret_cast<uint4 *>(clear)[w] = make_uint4(0u, 0u, 0u, 0u);
@@ -169,7 +172,7 @@ static int launch_small_tables_m(const float *queries, int nq, const float *deri
                                  uint32_t n_first, uint8_t *qtab, float *bounds, float *small, hipStream_t st, uint32_t *clear,
                                  size_t clear_words)
 {
-    const size_t lds = sizeof(float) * QPB * (static_cast<size_t>(M) * dsub + (static_cast<size_t>(M) << small_bits));
+    const size_t lds = sizeof(float) * (static_cast<size_t>(QPB) * M * dsub + table_floats(QPB, M, small_bits));
     const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(&small_tables_kernel<M, QPB, CodeT>), static_cast<int>(lds));
     if (arc) return arc;
     DCPQ_LAUNCH(kStageSmallTables, st, (small_tables_kernel<M, QPB, CodeT>), dim3((nq + QPB - 1) / QPB), dim3(kSmallTabThreads), lds,

@@ -162,3 +162,24 @@ def test_more_queries_than_a_grid_has_rows():
     for a, q in enumerate(sel):
         exact = oracle.refine(q_np[q], cb_np, c_np, ids[q], 8)
         assert_topk_matches(ids[q], dist[q], ref["ids"][a], ref["dist"][a], exact, cand_ref=ref["cand_id"][a], tag="query %d" % q)
+
+
+@pytest.mark.parametrize("Q,b,dsub", [(1, 16, 4), (7, 8, 8), (499, 16, 4), (501, 16, 12)])
+def test_smallest_tables_and_candidate_sets(Q, b, dsub):
+    # one sub-quantizer with two derived centroids, and one candidate: two floats of tables, and one key, lie in front of
+    # the query in LDS, which is read in 16-byte vectors
+    print("smallest tables Q=%d b=%d dsub=%d" % (Q, b, dsub), flush=True)
+    cb, codes, queries = make_case(1, dsub, b, 1, 900, Q, 13)
+    derived = binding.derive_codebooks(cb, 1)
+    qtab, bounds, small = (to_np(x) for x in binding.build_small_tables(queries, derived, codes, 50, want_small=True))
+    q_np, d_np, cb_np, c_np = to_np(queries), to_np(derived), to_np(cb), to_np(codes).astype(np.uint16)
+    cand = torch.randint(0, 900, (Q, 1), device=DEV, dtype=torch.int32).view(torch.uint32)
+    ids, dist = (to_np(x) for x in binding.refine_direct_topk(queries, cb, codes, cand, 1))
+    np.testing.assert_array_equal(ids, to_np(cand))
+    for q in {0, Q // 2, Q - 1}:
+        D = oracle.compute_tables_f32(q_np[q], d_np)
+        np.testing.assert_array_equal(small[q], D)
+        lo, hi = oracle.bounds(D, c_np, 50, 1)
+        np.testing.assert_array_equal(bounds[q], np.array([lo, hi], np.float32))
+        np.testing.assert_array_equal(qtab[q], np.tile(oracle.quantize(D, lo, hi), (1, 128)))
+        np.testing.assert_allclose(dist[q], oracle.refine(q_np[q], cb_np, c_np, ids[q], b), rtol=1e-6)
