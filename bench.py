@@ -134,7 +134,7 @@ def run_flat(w, args, steps, warmup, with_cpu, headline):
             roofline = hbm_roofline(dom, wbytes, dom_ms, dom_launches, steps, w.name, "table writes to HBM")
     elif dom == "refine_topk":
         # pass two: per candidate one code and m centroid rows (on demand) or m table entries
-        direct = binding.search_refine_mode(w.m, w.dsub, w.b, w.Q, w.r, refine_mode) != binding.REFINE_TABLES
+        direct = not stages["full_tables"][1]
         per_cand = code_bytes + w.m * (4 * w.dsub if direct else 4)
         roofline = hbm_roofline(dom, float(w.Q) * w.r * per_cand / (dom_launches / steps), dom_ms, dom_launches, steps, w.name,
                                 "scattered reads (one code and m %s per candidate)" % ("centroid rows" if direct else "table entries"))
@@ -156,8 +156,8 @@ def run_flat(w, args, steps, warmup, with_cpu, headline):
                    "code_bytes": code_bytes, "seed": w.seed},
         "roofline": roofline,
         "stage_ms_per_step": {s: round(v[0] / steps, 3) for s, v in stages.items() if v[1]},
-        "refine_mode": {binding.REFINE_TABLES: "tables", binding.REFINE_DIRECT: "direct", binding.REFINE_SPLIT: "split"}[
-            binding.search_refine_mode(w.m, w.dsub, w.b, w.Q, w.r, refine_mode)],
+        # what was asked for, and whether full tables were built for it or entries computed on demand
+        "refine_mode": args.refine, "table_entries": "full tables" if stages["full_tables"][1] else "on demand",
         "setup_s": round(setup_s, 2),
     }
 

@@ -231,14 +231,20 @@ int dcpq_search_bits_chunk(int m, int nq, int b, int chunk_queries);
  *                       region of the workspace that the tables would take: they fit whenever
  *                       r * (4 + b / 8) <= 4 * 2^b; DCPQ_EINVAL if they do not, if chunk * r
  *                       reaches 2^32, or if `queries` is not 16-byte aligned
- *   DCPQ_REFINE_AUTO    TABLES when r > 2^b / 8; else SPLIT when it is possible, a sub-codebook (two
- *                       for m = 16, four for m = 32) is smaller than 4 MB, the codebooks as a whole
- *                       are not, and the chunk has at least 2^16 candidates; else DIRECT (dcpq_search
- *                       uses this).
- *                       dcpq_search_refine_mode reports this size rule for the first chunk of a batch of
- *                       nq queries under the default chunking.  It says how the entries come about in
- *                       principle; a search computes them in another of these forms, for all or some
- *                       of its queries, where that is faster (which can depend on the codes)
+ *   DCPQ_REFINE_AUTO    what is fastest for the shape (dcpq_search uses this).  8-bit sub-codes: TABLES when
+ *                       r > 32, else DIRECT.  16-bit sub-codes, where SPLIT is possible: DIRECT when
+ *                       r * m <= 1024 and dsub is 1, 2, 4, 8 or at least 16; SPLIT when a sub-codebook (two for
+ *                       m = 16, four for m = 32) is smaller than 4 MB, when r * m < 8192 or when the chunk has fewer than 2^18
+ *                       candidates; else DIRECT for the queries whose candidates repeat few enough
+ *                       sub-codes to compute every entry once, and SPLIT for the others (which shows on the
+ *                       device).  Where SPLIT is not possible: TABLES when r > 8192, else DIRECT.  Small
+ *                       problems (n_codes * nq * max(m, 4) <= 2^27, in one chunk) compute their entries on
+ *                       demand while they collect the candidates, under AUTO and under DIRECT.
+ *   dcpq_search_refine_mode reports the size rule that AUTO began with, for the first chunk of a batch of nq
+ *                       queries under the default chunking: TABLES when r > 2^b / 8; else SPLIT when it is
+ *                       possible, a sub-codebook (two, four) is smaller than 4 MB, the codebooks as a whole
+ *                       are not, and the chunk has at least 2^16 candidates; else DIRECT.  It does not say
+ *                       which kernels a search runs (dcpq_profile_read does).
  * All give the fp32 sum, j increasing, of the M entries; TABLES and the on-demand modes agree within
  * the 1e-5 bar and may differ in the last bit (and then in the order of near-ties). */
 #define DCPQ_REFINE_AUTO 0
@@ -279,7 +285,7 @@ int dcpq_plain_search(const float *tables, uint32_t n_entries, const void *codes
  * paragraph of Sec. 3.2.  The paper names the steps and leaves their insides to standard algorithms;
  * what these calls compute:
  *   nearest centroid    the smallest (squared distance, index), distances in double precision from
- *                       the fp32 inputs (matrix cores);
+ *                       the fp32 inputs;
  *   k-means (step 1)    `iters` times { assign every point; centroid = mean of its members, double
  *                       precision sums rounded to fp32 once; a centroid without members keeps its
  *                       value }, then one more assignment; the initial centroids are an input;

@@ -319,7 +319,7 @@ REFINE_AUTO, REFINE_TABLES, REFINE_DIRECT, REFINE_SPLIT = 0, 1, 2, 3
 
 
 def search_refine_mode(m: int, dsub: int, b: int, nq: int, r: int, refine_mode: int = REFINE_AUTO) -> int:
-    """The mode pass two of `search` runs in for (the first chunk of) a batch of nq queries."""
+    """The size rule that REFINE_AUTO began with (see dcpq_search_refine_mode); not which kernels a search runs."""
     return int(lib().dcpq_search_refine_mode(m, dsub, b, nq, r, refine_mode))
 
 

@@ -619,6 +619,8 @@ __global__ __launch_bounds__(256) void refine_terms_kernel(const float *__restri
         s_over = 1;                                                    // benign race: every writer stores 1
     };
 
+    // (rows of 16 components are read about as fast as a set is filled: 8 x 16, encoded codes, 1000 queries, r = 2000: 172 us
+    // computing every entry, 170 with a set; 251, r = 10000: 178 and 238; random codes, 1000 queries: 192 and 200)
     bool memo = dsub > 16 && n >= 2 * kFirst;
     if (memo) {                                                        // uniform
         for (uint32_t t = tid; t < kTermSlots; t += 256) hkey[t] = kEmpty;

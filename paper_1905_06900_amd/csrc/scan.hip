@@ -385,7 +385,7 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t
     p.fast = p.fqt != 0;
     if (p.fast) {
         p.ntiles = static_cast<uint32_t>((Q + p.fqt - 1) / p.fqt);
-        // workgroups along the codes, at least 16 Ki codes each
+        // workgroups along the codes, of 16 Ki codes and more (fewer, down to 4 Ki, on short arrays)
         const uint64_t rest = n_codes;
         // (a single tile does the same work in every workgroup, and one round of the 256 CUs measured
         // fastest for it; with several tiles the work per workgroup varies and more rounds even it out)

@@ -132,7 +132,7 @@ static Form refine_form(int requested, const SearchPlan &p, int m, int dsub, int
     return split_first(m, dsub, b, nq, r) ? kSplit : kOneKernelThenSplit;
 }
 
-// the size rule that dcpq_search_refine_mode reports
+// the size rule that dcpq_search_refine_mode reports; a search goes by refine_form
 static int refine_mode_for(int requested, const SearchPlan &p, int m, int dsub, int b, int nq, uint32_t r)
 {
     if (requested != DCPQ_REFINE_AUTO) return requested;

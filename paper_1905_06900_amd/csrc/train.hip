@@ -9,8 +9,8 @@
 //                                  j-th sub-vector
 //
 // The paper leaves the insides of steps 1 and 2 to standard algorithms; what is computed here:
-//   - nearest centroid: smallest (distance, index); distances ||x||^2 + ||c||^2 - 2 <x, c> with the inner
-//     products on the double-precision matrix cores (v_mfma_f64_16x16x4_f64), compared in double precision;
+//   - nearest centroid: smallest (distance, index), distances in double precision (assign.hip: a filter on the bf16
+//     matrix cores with a proven error bound, double precision for what it leaves);
 //   - a k-means iteration assigns every point and replaces each centroid by the mean of its members
 //     (double-precision sums, one division, rounded to fp32); a centroid without members keeps its value;
 //     initial centroids are an input; after the last iteration the points are assigned once more;

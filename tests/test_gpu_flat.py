@@ -60,13 +60,35 @@ def test_cfg0_scaled_on_demand_refinement(case0):
     np.testing.assert_allclose(to_np(sdist), to_np(c.dist), rtol=2e-7)
 
 
+def stages_of(call):
+    """{stage: launches} of the library's kernels in one call"""
+    binding.profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return {name: launches for name, (_, launches) in binding.profile_read().items() if launches}
+    finally:
+        binding.profile_enable(False)
+
+
+def one_kernel_refinement(queries, cb, derived, codes, r, k):
+    """Pass two in the one-kernel form over the staged scan's candidates: a search of a small problem computes its entries
+    while it collects them, whatever mode is asked for."""
+    qtab, _, _ = binding.build_small_tables(queries, derived, codes, r)
+    cand_id, _ = binding.scan_candidates(codes, qtab, r)
+    out = []
+    assert stages_of(lambda: out.extend(binding.refine_direct_topk(queries, cb, codes, cand_id, k))) == {"refine_topk": 1}
+    return out
+
+
 @pytest.mark.parametrize("cfg,N,Q,r,chunk", [(0, 90_001, 37, 1000, 16), (2, 150_001, 290, 4000, 280),
                                              (4, 40_001, 21, 700, 0)])
 def test_split_on_demand_refinement(cfg, N, Q, r, chunk):
     # Pass two split by sub-quantizer (m = 4: two parts of the candidates per sub-quantizer; m = 8: one
     # sub-quantizer per slice; m = 16: two) gives the bits of the one-kernel form, with a ragged last chunk too,
-    # and matches the oracle.  The middle case is large enough for the library to pick the split form by itself
-    # for the full chunk (280 x 4000 candidates) and the one-kernel form for the last 10 queries.
+    # and matches the oracle.  In the middle case the library picks the split form by itself (rows of 12 floats: one
+    # sub-codebook is smaller than an XCD's cache), for the full chunk (280 x 4000 candidates) and for the last 10 queries;
+    # the size rule that search_refine_mode reports draws the line elsewhere.
     w = small_flat(cfg, N, Q, r)
     print("split refinement: cfg%d recipe N=%d Q=%d r=%d chunk=%d" % (cfg, N, Q, r, chunk), flush=True)
     c = FlatCase(w, DEV)
@@ -88,9 +110,9 @@ def test_split_on_demand_refinement(cfg, N, Q, r, chunk):
 
 
 def test_on_demand_refinement_with_r_above_the_lds_sort():
-    # r = 9000 candidates per query: the refinement's keys go to the global spill area instead of LDS (and the default
-    # mode would be full tables); the on-demand forms, memoized (tie-heavy cfg0 codes repeat sub-codes) and split,
-    # still agree bit for bit and with the oracle
+    # r = 9000 candidates per query: the refinement's keys go to the global spill area instead of LDS; the on-demand
+    # forms, memoized (tie-heavy cfg0 codes repeat sub-codes), split, and computed while the candidates are collected, still
+    # agree bit for bit and with the oracle
     w = small_flat(0, 100_003, 5, 9000)
     print("on-demand refinement, keys spilled: m=%d N=%d Q=%d r=%d" % (w.m, w.N, w.Q, w.r), flush=True)
     c = FlatCase(w, DEV)
@@ -100,6 +122,9 @@ def test_on_demand_refinement_with_r_above_the_lds_sort():
     torch.cuda.synchronize()
     np.testing.assert_array_equal(to_np(dids), to_np(sids))
     np.testing.assert_array_equal(to_np(ddist), to_np(sdist))
+    oids, odist = one_kernel_refinement(c.queries, c.cb, c.derived, c.codes, w.r, w.k)
+    np.testing.assert_array_equal(to_np(oids), to_np(sids))
+    np.testing.assert_array_equal(to_np(odist), to_np(sdist))
     c.oracle()
     c.check_pass_two(dids, ddist)
 
@@ -124,9 +149,15 @@ def test_split_refinement_with_repeated_sub_codes(m, dsub, Q, r, distinct):
     derived = binding.derive_codebooks(cb)
     want = binding.search(queries, cb, derived, codes, r, k, refine_mode=binding.REFINE_DIRECT)
     got = binding.search(queries, cb, derived, codes, r, k, refine_mode=binding.REFINE_SPLIT)
+    one = one_kernel_refinement(queries, cb, derived, codes, r, k)
     torch.cuda.synchronize()
-    np.testing.assert_array_equal(to_np(got[0]), to_np(want[0]))
-    np.testing.assert_array_equal(to_np(got[1]), to_np(want[1]))
+    for other in (want, one):
+        np.testing.assert_array_equal(to_np(got[0]), to_np(other[0]))
+        np.testing.assert_array_equal(to_np(got[1]), to_np(other[1]))
+    cb_np, codes_np, y = to_np(cb), to_np(codes), to_np(queries)
+    ref = oracle.search_flat(cb_np, to_np(derived), codes_np, y[:1], r, k)
+    ids, dist = to_np(got[0])[0], to_np(got[1])[0]
+    assert_topk_matches(ids, dist, ref["ids"][0], ref["dist"][0], oracle.refine(y[0], cb_np, codes_np, ids), cand_ref=ref["cand_id"][0])
 
 
 @pytest.mark.parametrize("repeats", [True, False])
@@ -179,6 +210,9 @@ def test_on_demand_refinement_with_memoized_entries(case):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(to_np(dids), to_np(sids))
     np.testing.assert_array_equal(to_np(ddist), to_np(sdist))
+    oids, odist = one_kernel_refinement(c.queries, c.cb, c.derived, c.codes, w.r, w.k)
+    np.testing.assert_array_equal(to_np(oids), to_np(sids))
+    np.testing.assert_array_equal(to_np(odist), to_np(sdist))
     c.oracle()
     c.check_pass_two(dids, ddist)
 
@@ -361,17 +395,6 @@ def test_scan_selection_with_one_large_group_of_equal_candidates():
     scan_vs_oracle(codes2, qtab[1:], r)
 
 
-def stages_of(call):
-    """{stage: launches} of the library's kernels in one call"""
-    binding.profile_enable(True)
-    try:
-        call()
-        torch.cuda.synchronize()
-        return {name: launches for name, (_, launches) in binding.profile_read().items() if launches}
-    finally:
-        binding.profile_enable(False)
-
-
 def test_codebooks_are_padded_only_for_the_form_that_reads_the_copy():
     # the memoized form with leftovers reads the codebooks where they are: rows of 12 floats (which the plain one-kernel
     # form would have copied into rows of 16) take no launch more than rows of 16, and the explicit form does
@@ -395,10 +418,10 @@ def test_codebooks_are_padded_only_for_the_form_that_reads_the_copy():
     assert launches[12, binding.REFINE_DIRECT] == launches[16, binding.REFINE_DIRECT] + 1 == 2
 
 
-@pytest.mark.parametrize("r", [1, 900, 10_000, 15_900, 16_500])
+@pytest.mark.parametrize("r", [1, 900, 10_000, 15_700, 15_701, 15_900, 16_500])
 def test_scan_selection_deals_out_only_the_groups_that_reach_r(r):
-    # tens of thousands of codes tie in the bucket of the r-th candidate (more than the selection holds), for r up to
-    # where ranks are counted and (the last one) beyond it, where the sorting network takes over
+    # tens of thousands of codes tie in the bucket of the r-th candidate (more than the selection holds), for r up to 15700,
+    # where the room for counting ranks ends, and beyond it, where the sorting network takes over
     rng = np.random.default_rng(r)
     N = 120_000
     codes = rng.integers(0, 65536, size=(N, 8)).astype(np.uint16)

@@ -19,7 +19,7 @@ def test_flat_search_captured_in_a_graph_replays_to_the_eager_result(cfg, N, Q, 
     w = synth.scaled(synth.WORKLOADS[cfg], N=N, Q=Q, r=r)
     if cfg == 2:
         assert binding.scan_plan(w.N, w.m, w.Q, w.r)["pilot_every"] == 16
-        assert binding.search_refine_mode(w.m, w.dsub, 16, w.Q, w.r) == binding.REFINE_SPLIT
+        assert binding.search_refine_mode(w.m, w.dsub, 16, w.Q, w.r) == binding.REFINE_SPLIT      # (as the search does here)
     print("graph capture: flat search, cfg%d recipe, N=%d Q=%d r=%d" % (cfg, w.N, w.Q, w.r), flush=True)
     d = synth.make_flat(w, DEV)
     cb, codes, queries = d["codebooks"], d["codes"], d["queries"]
