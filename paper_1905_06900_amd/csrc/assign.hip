@@ -1,7 +1,8 @@
 // Nearest centroid of every sub-vector (encoding, the assignment step of k-means): the smallest
 // (squared distance, index) with distances in double precision.
 //
-// Computed in two steps with the result of one.  A filter evaluates |c|^2 - 2 <x, c> for all centroids on
+// Small codebooks, and few points with long sub-vectors, take all products on the double-precision matrix pipe
+// (assign_f64_kernel; f64_is_faster says where).  The others are computed in two steps with the result of one.  A filter evaluates |c|^2 - 2 <x, c> for all centroids on
 // the bf16 matrix cores with every fp32 number split into two bf16 numbers (x = xh + xl + an error of at most
 // 2^-17 |x|; the three products xh ch + xl ch + xh cl, and xl cl where it costs no further matrix instruction, lie
 // side by side along the K dimension of one matrix product whose accumulators start from |c|^2), and keeps per
@@ -10,15 +11,16 @@
 // than were kept (or whose values are not finite) is compared with all centroids in double precision.  That is
 // most of the time where a codebook repeats itself, and with sub-vectors of one or two components.
 //
-// What bounds it: the matrix pipe (KS instructions of 32 cycles per 32 x 32 distances, KS = ceil(3 d / 16)) is busy
-// half of the time; beside it the vector port takes 9 instructions per 32 x 32 distances and 64 lanes for the minima
-// and as many again for the conversion of the centroids (shared by the points of a workgroup), and the LDS a third
-// to a half of the cycles for the operands.  250007 vectors, 8 sub-quantizers of 16 components and 65536 centroids:
-// 11.1 ms = 1.13 PFLOP/s of bf16 products, what a large library matrix product reaches here (1.16); with all
-// distances on the double-precision matrix pipe 97 ms.  d = 32: 6.0 ms per 100000 x 4 (32.7 in double precision);
-// d = 60: 9.6 ms per 20000 x 16 (58.8).
+// What bounds it: matrix and vector instructions, which leave a SIMD 6 % of its cycles if they do not overlap: the
+// matrix pipe (KS instructions of 32 cycles per 32 x 32 distances, KS = ceil(3 d / 16)) is busy 0.56 of the time, and 16
+// vector instructions per 32 x 32 distances (9 for the minima, the rest the conversion of the centroids, shared by the
+// points of a workgroup) 0.38; the LDS 0.22.  250007 vectors, 8
+// sub-quantizers of 16 components and 65536 centroids: 11.2 ms = 1.1 PFLOP/s of bf16 products, what a large library
+// matrix product reaches here (1.16); with all distances on the double-precision matrix pipe 97 ms.  d = 32: 6.2 ms per
+// 100000 x 4 (32.7 in double precision); d = 60: 9.8 ms per 20000 x 16 (58.8).
 #include "common.h"
 #include "assign.h"
+#include "f64_tile.h"
 
 namespace dcpq {
 
@@ -628,6 +630,149 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     }
 }
 
+// The same result with all inner products on the double-precision matrix pipe (f64_is_faster: where).  A workgroup takes kF64Points points and walks the centroids in steps of
+// kF64Cents; |c|^2 - 2 <x, c> and the distance by difference are each within (dsub + 8) 2^-53 of the magnitudes they are
+// made of, so a smallest value that no other comes near is the nearest centroid in either form.  Where another does (equal
+// centroids above all), or a value is not finite, a wavefront compares the point with every centroid by difference.
+// What bounds it: below 60 components what is done with the products (eight vector instructions each, as many cycles as the
+// matrix instructions of 16 components take), above that the matrix pipe.  Two wavefronts per SIMD, which is what 256
+// registers leave; without that bound the compiler takes 272 and one wavefront takes 1.8 times as long.
+constexpr int kF64Points = 32, kF64Cents = 256;
+
+__global__ __launch_bounds__(256, 2) void assign_f64_kernel(const float *__restrict__ points, uint64_t n, int ld,
+                                                         const float *__restrict__ cb, int m, int dsub, int ncent,
+                                                         void *__restrict__ labels, int label_bytes, float *__restrict__ dist)
+{
+    constexpr int MT = kF64Points / 16;
+    __shared__ double red_v[4][kF64Points], norm[kF64Points], limit[kF64Points], red_c[4];
+    __shared__ uint32_t red_i[4][kF64Points], close[kF64Points];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = blockIdx.y, lr = lane & 15, lk = lane >> 4;
+    const uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * kF64Points;
+    const float *cbj = cb + static_cast<size_t>(j) * ncent * dsub;
+
+    // value v of the result tile (mt, nt): point 16 mt + 4 v + l / 16, centroid 4 (l % 16) + nt of the wavefront's 64
+    double best[MT][4], na[MT], cmax = 0.0;
+    // Of the second smallest value the upper word is kept.  Upper words of numbers below 2^1017 are ordered as floats of the
+    // same bits are (2^265 is the largest magnitude that finite fp32 inputs give).
+    float second[MT][4];
+    auto upper = [](double x) { return __uint_as_float(static_cast<uint32_t>(__double_as_longlong(x) >> 32)); };
+    uint32_t bi[MT][4];
+    const float *ap[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { best[mt][v] = INFINITY; second[mt][v] = 3.4e38f; bi[mt][v] = 0xFFFFFFFFu; }
+        na[mt] = 0.0;
+        const uint64_t q = q0 + mt * 16 + lr;
+        ap[mt] = points + static_cast<size_t>(q < n ? q : n - 1) * ld + j * dsub;
+    }
+    for (int c0 = 0; c0 < ncent; c0 += kF64Cents) {                   // uniform
+        const int cw = c0 + wave * 64;
+        if (cw >= ncent) break;                                       // uniform (the first wavefront takes the points' norms)
+        double4_t acc[MT][4];
+        double nb[4] = {0.0, 0.0, 0.0, 0.0};
+        const float *bp[4];
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = double4_t{0.0, 0.0, 0.0, 0.0};
+            const int c = cw + lr * 4 + nt;
+            bp[nt] = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+        }
+        f64_tile_products<MT>(ap, bp, dsub, lk, c0 == 0, acc, na, nb);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            nb[nt] += __shfl_xor(nb[nt], 16);
+            nb[nt] += __shfl_xor(nb[nt], 32);
+            const int c = cw + lr * 4 + nt;
+            if (c >= ncent) continue;
+            cmax = nb[nt] < INFINITY ? fmax(cmax, nb[nt]) : INFINITY;            // (NaN counts as infinite)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const double val = fma(-2.0, acc[mt][nt][v], nb[nt]);
+                    const bool better = val < best[mt][v];
+                    const float other = better ? upper(best[mt][v]) : upper(val);
+                    second[mt][v] = other < second[mt][v] ? other : second[mt][v];        // (that of infinity is not a number here)
+                    best[mt][v] = better ? val : best[mt][v];
+                    bi[mt][v] = better ? static_cast<uint32_t>(c) : bi[mt][v];
+                }
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) cmax = fmax(cmax, __shfl_xor(cmax, off));
+    if (lane == 0) red_c[wave] = cmax;
+    double own[MT][4];                                                // the smallest value of this lane
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            own[mt][v] = best[mt][v];
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                const double ov = __shfl_xor(best[mt][v], off);
+                const uint32_t oi = __shfl_xor(bi[mt][v], off);
+                take_smaller(best[mt][v], bi[mt][v], ov, oi);
+            }
+            const int p = mt * 16 + v * 4 + lk;
+            if (lr == 0) { red_v[wave][p] = best[mt][v]; red_i[wave][p] = bi[mt][v]; }
+        }
+        na[mt] += __shfl_xor(na[mt], 16);
+        na[mt] += __shfl_xor(na[mt], 32);
+        if (wave == 0 && lk == 0) norm[mt * 16 + lr] = na[mt];
+    }
+    __syncthreads();
+    double v = INFINITY;
+    uint32_t i = 0xFFFFFFFFu;
+    if (tid < kF64Points) {
+        for (int w = 0; w < 4; ++w) take_smaller(v, i, red_v[w][tid], red_i[w][tid]);
+        // both forms' errors for two centroids, of magnitudes up to (|x| + |c|)^2 <= 2 |x|^2 + 2 |c|^2 (infinite, or not
+        // a number, where any value is not finite)
+        const double c2 = fmax(fmax(red_c[0], red_c[1]), fmax(red_c[2], red_c[3]));
+        limit[tid] = v + (dsub + 8) * 0x1p-50 * (norm[tid] + c2);
+        close[tid] = 0;
+    }
+    __syncthreads();
+    // the values that lie within the limit: the smallest one itself, and any other
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int p = mt * 16 + v * 4 + lk;
+            const double lim = limit[p];
+            const uint32_t up = __float_as_uint(second[mt][v]);        // the smallest number of this upper word:
+            const double low = __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(up) << 32 | (up >> 31 ? 0xFFFFFFFFu : 0u)));
+            if (own[mt][v] <= lim) atomicAdd(&close[p], low <= lim ? 2u : 1u);
+        }
+    __syncthreads();
+    auto put = [&](uint64_t q, double d, uint32_t i) {
+        const size_t o = static_cast<size_t>(q) * m + j;
+        store_label(labels, label_bytes, o, i);
+        if (dist) dist[o] = static_cast<float>(d);
+    };
+    auto sure = [&](int p) { return close[p] == 1 && limit[p] < INFINITY; };
+    if (tid < kF64Points && q0 + tid < n && sure(tid)) {
+        const uint64_t q = q0 + tid;
+        put(q, dist ? exact_distance(points + static_cast<size_t>(q) * ld + j * dsub, cbj + static_cast<size_t>(i) * dsub, dsub) : 0.0, i);
+    }
+    for (int p = wave; p < kF64Points; p += 4) {                      // uniform
+        if (q0 + p >= n || sure(p)) continue;                        // uniform
+        const float *x = points + static_cast<size_t>(q0 + p) * ld + j * dsub;
+        double d = INFINITY;
+        uint32_t i = 0xFFFFFFFFu;
+        for (int c = lane; c < ncent; c += 64) take_smaller(d, i, exact_distance(x, cbj + static_cast<size_t>(c) * dsub, dsub), c);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double ov = __shfl_xor(d, off);
+            const uint32_t oi = __shfl_xor(i, off);
+            take_smaller(d, i, ov, oi);
+        }
+        if (lane == 0) put(q0 + p, d, i);
+    }
+}
+
 template <int KS, int P, bool SPLIT>
 static int launch_assign_t(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
                            void *labels, int label_bytes, float *dist, hipStream_t st)
@@ -660,10 +805,36 @@ static int launch_assign_ks(const float *points, uint64_t n, int ld, const float
     return DCPQ_OK;
 }
 
+// Which kernel.  The filter saves products, and what follows it costs each point the reading of a few rows one by one, 256
+// to 512 points to a workgroup; the double-precision products cost more per distance but nothing after them, and take
+// points in tens.  So they are the faster where centroids are few, or points so few that the filter's tiles leave the chip
+// idle, and the longer the rows the more so.  Measured with 4 sub-quantizers, filter against products, in us: 1000 points,
+// 256 centroids of 8 components 18 and 11, of 32 24 and 12, of 60 84 and 17, of 128 127 and 18; 12000 points, 256 of 16
+// 41 and 34 (512: 45 and 44); 250000 points, 256 of 16 385 and 608, of 32 1150 and 736 (rows of 128 bytes meet in the
+// same sets of the first-level cache; of 28: 668 and 780), of 60 1037 and 1070 (with distances 0.74 of the time), of 128
+// 3531 and 1412; 1024 of 128 4790 and 4550, of 60 1516 and 3100; 65536 of 128, 1000 points 4933 and 2516, 6000 4770 and 6900.
+static bool f64_is_faster(uint64_t sub_vectors, int dsub, int ncent, bool want_dist)
+{
+    const uint64_t pairs = sub_vectors * static_cast<uint64_t>(ncent);
+    if (dsub > 32) {
+        if (sub_vectors <= 4096 || pairs <= 1u << 25) return true;
+        return ncent <= 256 ? dsub > 64 || want_dist : ncent <= 512 && dsub > 96;
+    }
+    if (dsub <= 2 && ncent <= (dsub == 1 ? 4096 : 1024)) return sub_vectors <= 16384;        // (the filter cannot tell many apart)
+    if (ncent > 512) return false;
+    return dsub == 32 || pairs <= (dsub <= 8 ? 1u << 22 : 1u << 23);
+}
+
 int launch_assign(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int ncent, void *labels,
                   int label_bytes, float *dist, hipStream_t st)
 {
     if (n == 0) return DCPQ_OK;
+    if (f64_is_faster(n * static_cast<uint64_t>(m), dsub, ncent, dist != nullptr)) {
+        DCPQ_LAUNCH(kStageTrain, st, assign_f64_kernel, dim3(static_cast<unsigned>((n + kF64Points - 1) / kF64Points), m), dim3(256),
+                    0, points, n, ld, cb, m, dsub, ncent, labels, label_bytes, dist);
+        DCPQ_CHECK_LAUNCH("assign_f64_kernel");
+        return DCPQ_OK;
+    }
     const int dp = (dsub + 3) & ~3, ks = (3 * dp + 15) / 16;
 #define DCPQ_ASSIGN_KS(K) \
     if (ks <= K) return launch_assign_ks<K>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);

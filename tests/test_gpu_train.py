@@ -153,6 +153,55 @@ def test_assign_where_the_split_products_are_farthest_from_the_product(dsub, sca
     np.testing.assert_allclose(to_np(dist)[:, 0], rd[0], rtol=1e-6, atol=1e-12)
 
 
+@pytest.mark.parametrize("dsub", [1, 2, 3, 4, 7, 8, 9, 12, 16, 21, 31, 32, 33, 40, 60, 64, 100, 128])
+@pytest.mark.parametrize("data", ["normal", "repeats", "offset", "lattice", "split"])
+def test_assign_few_points_and_many_agree(dsub, data):
+    # Few points against a small codebook take the products in double precision, many the bf16 filter (rows of 32 components
+    # always the former here): the same labels and the same bits of the distances, which are those of a comparison by
+    # difference.  Equal and nearly equal centroids, points half-way between two, and values that are not finite.
+    print("assign few and many dsub=%d %s" % (dsub, data), flush=True)
+    g = gen(dsub + 1000 * len(data))
+    n, ncent = 300, 300 if dsub <= 32 else 600
+    pts = torch.randn((n, dsub), generator=g, device=DEV)
+    cb = torch.randn((ncent, dsub), generator=g, device=DEV)
+    if data == "repeats":
+        cb = cb[torch.randint(0, 7, (ncent,), generator=g, device=DEV)].contiguous()
+        pts[5, dsub // 2], pts[7, 0] = float("nan"), float("inf")
+    elif data == "offset":
+        cb = 3000.0 + 1e-3 * cb
+        pts = 3000.0 + 1e-3 * pts
+        cb[17, 0] = float("nan")
+    elif data == "lattice":
+        cb = torch.randint(-1, 2, (ncent, dsub), generator=g, device=DEV).float() * 0.1
+        pts = torch.randint(-2, 3, (n, dsub), generator=g, device=DEV).float() * 0.05
+    elif data == "split":
+        x, c = worst_split_case(dsub, 1)
+        cb = torch.zeros((ncent, dsub), device=DEV)
+        cb[:256] = torch.from_numpy(c).to(DEV)
+        pts = torch.from_numpy(np.repeat(x, n, 0)).to(DEV)
+    times = 200
+    few, few_dist = binding.assign(pts, cb[None], want_dist=True)
+    few2 = binding.assign(pts, cb[None])
+    many, many_dist = binding.assign(pts.repeat(times, 1), cb[None], want_dist=True)
+    many2 = binding.assign(pts.repeat(times, 1), cb[None])
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_np(few), to_np(few2))
+    np.testing.assert_array_equal(to_np(many), to_np(few.repeat(times, 1)))
+    np.testing.assert_array_equal(to_np(many2), to_np(few.repeat(times, 1)))
+    np.testing.assert_array_equal(to_np(many_dist), to_np(few_dist.repeat(times, 1)))
+    few, few_dist, p_np, c_np = to_np(few)[:, 0], to_np(few_dist)[:, 0], to_np(pts).astype(np.float64), to_np(cb).astype(np.float64)
+    d2 = np.zeros((n, ncent))
+    for t in range(dsub):
+        d2 += (p_np[:, None, t] - c_np[None, :, t]) ** 2
+    fine = np.isfinite(p_np).all(1)
+    # (the kernels add with fused multiply-adds: (dsub + 1) roundings of 2^-53 on either side, twice)
+    best = np.nanmin(d2[fine], 1)
+    assert (d2[fine][np.arange(fine.sum()), few[fine]] <= best * (1 + 4 * (dsub + 1) * 2.0 ** -53)).all()
+    np.testing.assert_allclose(few_dist[fine], best, rtol=2.0 ** -23)
+    if data == "repeats":
+        assert few[5] == -1 and few[7] == 0 and np.isinf(few_dist[7])
+
+
 @pytest.mark.parametrize("b", [16, 8])
 def test_encode_against_the_oracle(b):
     m, dsub, n = (4, 8, 3000) if b == 16 else (8, 4, 20000)
