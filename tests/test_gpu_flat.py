@@ -182,6 +182,11 @@ def test_queries_the_memoized_form_gives_up_are_finished_by_the_split_form(repea
     torch.cuda.synchronize()
     np.testing.assert_array_equal(to_np(ids), to_np(want[0]))
     np.testing.assert_array_equal(to_np(dist), to_np(want[1]))
+    cb_np, codes_np, y, ids, dist = to_np(cb), to_np(codes), to_np(queries), to_np(ids), to_np(dist)
+    for q in (0, Q - 1):
+        ref = oracle.search_flat(cb_np, to_np(derived), codes_np, y[q:q + 1], r, k)
+        assert_topk_matches(ids[q], dist[q], ref["ids"][0], ref["dist"][0], oracle.refine(y[q], cb_np, codes_np, ids[q]),
+                            cand_ref=ref["cand_id"][0], tag="query %d" % q)
 
 
 @pytest.mark.parametrize("case", ["few distinct sub-codes", "set too small"])
