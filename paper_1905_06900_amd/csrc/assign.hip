@@ -634,9 +634,10 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
 // kF64Cents; |c|^2 - 2 <x, c> and the distance by difference are each within (dsub + 8) 2^-53 of the magnitudes they are
 // made of, so a smallest value that no other comes near is the nearest centroid in either form.  Where another does (equal
 // centroids above all), or a value is not finite, a wavefront compares the point with every centroid by difference.
-// What bounds it: below 60 components what is done with the products (eight vector instructions each, as many cycles as the
-// matrix instructions of 16 components take), above that the matrix pipe.  Two wavefronts per SIMD, which is what 256
-// registers leave; without that bound the compiler takes 272 and one wavefront takes 1.8 times as long.
+// What bounds it: the matrix pipe for long rows (250000 x 4 points, 1024 centroids of 128 components: 4.5 ms, 0.75 of its
+// peak; of 60 components half, of 16 a third), and the more the shorter they are what is done with each value, eight vector
+// instructions.  Two wavefronts per SIMD, which is what 256 registers leave; without that bound the compiler takes 272, and
+// with one wavefront it takes up to 1.8 times as long.
 constexpr int kF64Points = 32, kF64Cents = 256;
 
 __global__ __launch_bounds__(256, 2) void assign_f64_kernel(const float *__restrict__ points, uint64_t n, int ld,
