@@ -154,19 +154,22 @@ def test_assign_where_the_split_products_are_farthest_from_the_product(dsub, sca
 
 
 @pytest.mark.parametrize("dsub", [1, 2, 3, 4, 7, 8, 9, 12, 16, 21, 31, 32, 33, 40, 60, 64, 100, 128])
-@pytest.mark.parametrize("data", ["normal", "repeats", "offset", "lattice", "split"])
+@pytest.mark.parametrize("data", ["normal", "repeats", "some repeat", "offset", "lattice", "split"])
 def test_assign_few_points_and_many_agree(dsub, data):
     # Few points against a small codebook take the products in double precision, many the bf16 filter (rows of 32 components
-    # always the former here): the same labels and the same bits of the distances, which are those of a comparison by
+    # the latter both times, at these sizes): the same labels and the same bits of the distances, which are those of a comparison by
     # difference.  Equal and nearly equal centroids, points half-way between two, and values that are not finite.
     print("assign few and many dsub=%d %s" % (dsub, data), flush=True)
     g = gen(dsub + 1000 * len(data))
-    n, ncent = 300, 300 if dsub <= 32 else 600
+    n, ncent = 300, 300 if dsub < 32 else 600
     pts = torch.randn((n, dsub), generator=g, device=DEV)
     cb = torch.randn((ncent, dsub), generator=g, device=DEV)
     if data == "repeats":
         cb = cb[torch.randint(0, 7, (ncent,), generator=g, device=DEV)].contiguous()
         pts[5, dsub // 2], pts[7, 0] = float("nan"), float("inf")
+    elif data == "some repeat":                                 # a few to a third of the points of a tile near equal centroids
+        cb[1::2] = 20.0 + cb[torch.randint(0, 7, (ncent // 2,), generator=g, device=DEV) * 2]
+        pts += 20.0 * (torch.rand((n, 1), generator=g, device=DEV) < torch.arange(n, device=DEV)[:, None] / (3.0 * n))
     elif data == "offset":
         cb = 3000.0 + 1e-3 * cb
         pts = 3000.0 + 1e-3 * pts
