@@ -22,7 +22,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 FP64_MFMA_PEAK_TFLOPS = 78.6   # MI355X published dense fp64 matrix rate
-SCAN_STAGES = ("scan_fast", "scan_hist", "scan_tiecount", "scan_collect")
+SCAN_STAGES = ("scan_fast", "scan_hist", "scan_tiecount", "scan_collect", "scan_cells", "cells_sort")
 METRIC = "queries/sec at k=100 + scan GB/s vs HBM peak (PQ 8x16, N=100M, 1 GPU)"
 
 
@@ -114,7 +114,7 @@ def run_flat(w, args, steps, warmup, with_cpu, headline):
     # the dominant kernel among those a roofline is defined for (the selection and the small tables are
     # several short launches each; on the smallest workload their launch latencies add up to more than the scan)
     dom = max((s for s in stages if s in SCAN_STAGES + ("full_tables", "refine_topk") and stages[s][1]),
-              key=lambda s: stages[s][0])
+              key=lambda s: stages[s][0] if s != "cells_sort" else 0.0)
     dom_ms, dom_launches = stages[dom]
     scan_ms = sum(stages.get(s, (0.0, 0))[0] for s in SCAN_STAGES) / steps
     if dom == "full_tables":
@@ -132,6 +132,12 @@ def run_flat(w, args, steps, warmup, with_cpu, headline):
                         "limiter": "fp64 matrix instructions (K = dsub = %d per sub-quantizer)" % w.dsub}
         else:
             roofline = hbm_roofline(dom, wbytes, dom_ms, dom_launches, steps, w.name, "table writes to HBM")
+    elif dom == "scan_cells":
+        # lines of memory that the looked-up stretches and settled codes touch (counters; they depend on the data)
+        dom_launches = steps                                     # (the second launch serves a few per cent of the queries)
+        roofline = hbm_roofline(dom, committed_traffic(dom, w.name) or float(w.N * code_bytes), dom_ms, dom_launches, steps, w.name,
+                                "scattered reads of cells within the bounds; vector issue 75 %", {
+                                    "pairs_per_s": round(w.N * w.Q / (scan_ms * 1e-3), 1) if scan_ms > 0 else None})
     elif dom == "refine_topk":
         # pass two: per candidate one code and m centroid rows (on demand) or m table entries
         direct = not stages["full_tables"][1]

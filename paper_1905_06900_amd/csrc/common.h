@@ -47,7 +47,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 enum Stage {
     kStageSmallTables = 0, kStageScanHist, kStageScanTieCount, kStageScanCollect, kStageScanFast,
     kStageSelect, kStageFullTables, kStageRefine, kStageIvf, kStageMisc,
-    kStageIvfProbe, kStageIvfTables, kStageIvfScan, kStageIvfRefine, kStagePlainScan, kStageTrain, kNumStages
+    kStageIvfProbe, kStageIvfTables, kStageIvfScan, kStageIvfRefine, kStagePlainScan, kStageTrain, kStageScanCells, kStageCellsSort, kNumStages
 };
 namespace prof {
 bool enabled();
@@ -91,11 +91,21 @@ int launch_distance_tables(const float *queries, int nq, const float *codebooks,
 // what a workspace must hold (dcpq_scan_workspace_bytes: what it does best with); room: bytes at ws, no less than that
 size_t scan_least_bytes(uint64_t n_codes, int m, int nq, uint32_t r);
 size_t scan_clear_words(uint64_t n_codes, int m, int nq, uint32_t r, int mode);
+// cells (optional): room for sorting the codes into cells (scan_cells.hip), free until the scan has ended
+struct CellsArea {
+    void *ptr;               // cells_bytes(...) bytes, 256-byte aligned
+    const float *derived;    // [m][2^small_bits][dsub]
+    int dsub, small_bits;
+};
+bool cells_may_pay(uint64_t n_codes, int m, int nq);
+size_t cells_bytes(uint64_t n_codes, int m, int nq);
 int launch_scan(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st);
+                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st,
+                const CellsArea *cells = nullptr);
 // the same reading the low-byte plane of the codes (uint8 [n_codes][m])
 int launch_scan(const uint8_t *plane, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st);
+                uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st,
+                const CellsArea *cells = nullptr);
 int launch_refine(const float *tables, uint32_t table_size, const void *codes, int code_bytes, uint64_t n_codes, int m,
                   const uint32_t *cand_id, int nq, uint32_t r, uint32_t k, uint32_t *ids, float *dist, void *ws,
                   hipStream_t st);

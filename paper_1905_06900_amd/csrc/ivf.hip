@@ -991,7 +991,7 @@ __global__ __launch_bounds__(64 * IvfSampleCfg<M>::WAVES) void ivf_sample_kernel
     // A query with so many ties at the starting bucket that they would overflow its buffer is left to the three passes, at
     // seven eighths of the buffer (the slices do not fill evenly).  The buffer is the measure, not r: below r = 512 it holds more
     // than 32 r (255 queries, r = 3, two lists of 1400 codes: 168 us, 250 with every query left to the three passes).
-    if (s_last && wave == 0) starting_bound(shist + static_cast<size_t>(q) * 256, r, probed[q], kCrowdedSkip, bound + q, 0.875f * kFastSlices * static_cast<float>(cap));
+    if (s_last && wave == 0) starting_bound<false>(shist + static_cast<size_t>(q) * 256, r, probed[q], kCrowdedSkip, bound + q, 0.875f * kFastSlices * static_cast<float>(cap));
 }
 
 // ------------------------------------------------------------------------------------------------

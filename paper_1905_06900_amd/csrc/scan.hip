@@ -50,6 +50,7 @@ struct TileEnd {
     uint32_t want_r;
     uint64_t want_n;
     bool limit;
+    bool guess;             // a guess below the bound is asked for too
 };
 
 // T = bucket holding the r-th smallest qd; need = ids still to take from bucket T (one wavefront).
@@ -235,7 +236,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
                 if (MODE == kHist) {
                     for (int q = wave; q < nqt; q += kScanWaves) {
                         const uint32_t *h = hist + static_cast<size_t>(q0 + q) * 256;
-                        if (end_of.bound) starting_bound(h, end_of.want_r, end_of.want_n, end_of.limit, end_of.bound + q0 + q);
+                        if (end_of.bound && end_of.guess) starting_bound<true>(h, end_of.want_r, end_of.want_n, end_of.limit, end_of.bound + q0 + q);
+                        else if (end_of.bound) starting_bound<false>(h, end_of.want_r, end_of.want_n, end_of.limit, end_of.bound + q0 + q);
                         else exact_threshold(h, r, end_of.thr + 2 * (q0 + q));
                     }
                 } else {
@@ -591,13 +593,14 @@ static int launch_sample_hist_m(const CodeT *codes, uint64_t n_codes, const uint
 // want_r, want_n, limit: rank wanted, size of the array the sample stands for, whether ties may be limited by id (see starting_bound)
 template <typename CodeT>
 int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                       uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit, Bound *bound,
+                       uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit, bool guess, Bound *bound,
                        uint32_t *done, hipStream_t st)
 {
     TileEnd e{};
     e.done = done;
     e.bound = bound;
     e.limit = limit;
+    e.guess = guess;
     e.want_r = want_r;
     e.want_n = want_n;
     switch (m) {
@@ -610,13 +613,13 @@ int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_
 }
 
 template int launch_sample_hist<uint16_t>(const uint16_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *,
-                                          const ScanPlan &, uint32_t, uint64_t, bool, Bound *, uint32_t *, hipStream_t);
+                                          const ScanPlan &, uint32_t, uint64_t, bool, bool, Bound *, uint32_t *, hipStream_t);
 template int launch_sample_hist<uint8_t>(const uint8_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *,
-                                         const ScanPlan &, uint32_t, uint64_t, bool, Bound *, uint32_t *, hipStream_t);
+                                         const ScanPlan &, uint32_t, uint64_t, bool, bool, Bound *, uint32_t *, hipStream_t);
 
 template <int M, typename CodeT>
 static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,
-                         uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
+                         uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st, const CellsArea *cells)
 {
     const ScanPlan p = plan_scan(n_codes, M, nq, r, mode, room);
     uint8_t *base = static_cast<uint8_t *>(ws);
@@ -625,7 +628,7 @@ static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     if (rc) return rc;
     if (!p.fast)
         return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, nullptr, nullptr, r, cand_id, cand_qd, base, p, st);
-    rc = launch_scan_fast(codes, n_codes, M, qtab, nq, r, cand_id, cand_qd, base, p, st);
+    rc = launch_scan_fast(codes, n_codes, M, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
     if (rc) return rc;
     // queries the single pass could not finish (their count is known on the device only)
     return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, reinterpret_cast<const int *>(base + p.off_qlist),
@@ -635,16 +638,16 @@ static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
 
 template <typename CodeT>
 static int launch_scan_any(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                           uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
+                           uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st, const CellsArea *cells)
 {
     if (nq == 0) return DCPQ_OK;
     switch (m) {
-        case 1: return launch_scan_m<1, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
-        case 2: return launch_scan_m<2, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
-        case 4: return launch_scan_m<4, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
-        case 8: return launch_scan_m<8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
-        case 16: return launch_scan_m<16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
-        case 32: return launch_scan_m<32, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+        case 1: return launch_scan_m<1, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
+        case 2: return launch_scan_m<2, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
+        case 4: return launch_scan_m<4, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
+        case 8: return launch_scan_m<8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
+        case 16: return launch_scan_m<16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
+        case 32: return launch_scan_m<32, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
         default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
     }
 }
@@ -666,15 +669,15 @@ size_t scan_least_bytes(uint64_t n_codes, int m, int nq, uint32_t r) { return sc
 size_t scan_clear_words(uint64_t n_codes, int m, int nq, uint32_t r, int mode) { return plan_scan(n_codes, m, nq, r, mode).zero_bytes / sizeof(uint32_t); }
 
 int launch_scan(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
+                uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st, const CellsArea *cells)
 {
-    return launch_scan_any(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+    return launch_scan_any(codes, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
 }
 
 int launch_scan(const uint8_t *plane, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st)
+                uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st, const CellsArea *cells)
 {
-    return launch_scan_any(plane, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st);
+    return launch_scan_any(plane, n_codes, m, qtab, nq, r, cand_id, cand_qd, ws, room, mode, cleared, st, cells);
 }
 
 }  // namespace dcpq

@@ -57,6 +57,8 @@
 
 #include "common.h"
 #include "lds_access.h"
+#include <cmath>
+
 #include "scan_internal.h"
 
 namespace dcpq {
@@ -152,12 +154,12 @@ __global__ __launch_bounds__(256) void swizzle_tables_kernel(const uint8_t *__re
 
 // Starting bounds from sample histograms, a wavefront per query (see starting_bound).
 __global__ __launch_bounds__(256) void sample_threshold_kernel(const uint32_t *__restrict__ shist, int nq, uint32_t r,
-                                                               uint64_t n_codes,
+                                                               uint64_t n_codes, uint32_t guess_r,
                                                                Bound *__restrict__ bound)
 {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q >= nq) return;
-    starting_bound(shist + static_cast<size_t>(q) * 256, r, n_codes, kCrowdedAppend, bound + q);
+    starting_bound(shist + static_cast<size_t>(q) * 256, r, n_codes, kCrowdedAppend, bound + q, 0.0f, guess_r);
 }
 
 // Low bytes of the M sub-codes of one code, reordered by residue class: byte (j & 3) * CLS + (j >> 2).
@@ -222,8 +224,9 @@ template <int M, int QT, int WAVES, typename CodeT>
 __global__ __launch_bounds__(WAVES * 64) void scan_fast_kernel(
     const CodeT *__restrict__ codes, uint64_t code_end, uint64_t block_stride, uint32_t block_groups, uint32_t total_groups,
     uint32_t gshift, uint32_t gstride, const uint8_t *__restrict__ qsw, int nq, uint32_t r, uint32_t nslices, uint32_t cap,
-    uint32_t upd, Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *keys, uint64_t *notes, uint32_t wcap)
+    uint32_t upd, Bound *bound, uint32_t *count, uint32_t *chist, uint64_t *keys, uint64_t *notes, uint32_t wcap, const uint32_t *served)
 {
+    if (served && *served) return;                           // the scan over cells has served the batch
     // The codes of workgroup y (blockIdx.y) are 64-code groups y * block_groups ... (block_groups of them, fewer
     // at the end: total_groups in all); group g of the workgroup starts at code
     //   y * block_stride + (g >> gshift) * gstride + (g mod 2^gshift) * 64
@@ -873,7 +876,7 @@ __global__ __launch_bounds__(1024) void fast_select_kernel(const uint64_t *__res
 
 template <int M, int QT, int WAVES, typename CodeT>
 static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,
-                         uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p, hipStream_t st)
+                         uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p, const CellsArea *cells, hipStream_t st)
 {
     using C = FastCfg<M, QT, WAVES>;
     static_assert(WAVES <= kNoteWaves, "room for the notes");
@@ -905,7 +908,7 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     // It gives a bound for the pilot pass: the bucket below which the whole sample (taken as the array, its wanted rank
     // pilot_r as r) should hold pilot_r codes with the usual slack.
     int rc = launch_sample_hist(codes, n_codes, M, qtab, nq, r, shist, p, p.pilot ? p.pilot_r : r, p.pilot ? p.s_count : n_codes,
-                                !p.pilot, bound, done, st);
+                                !p.pilot, cells && !p.pilot, bound, done, st);
     if (rc) return rc;
     if (p.pilot) {
         if (p.s_unit != 256) return fail(DCPQ_EINVAL, "single-pass scan: the pilot pass reads runs of 256 codes");
@@ -915,18 +918,24 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
         DCPQ_LAUNCH(kStageScanHist, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.pilot_blocks), dim3(WAVES * 64),
                     C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.pilot_runs) * p.s_stride, p.pilot_runs * (p.s_unit / 64),
                     p.s_nunits * (p.s_unit / 64), 2u, static_cast<uint32_t>(p.s_stride), qsw, nq, p.pilot_r, p.slices, 0u, 16u,
-                    bound, fcount, chist, fkeys, notes, p.wcap);
+                    bound, fcount, chist, fkeys, notes, p.wcap, nullptr);
         DCPQ_CHECK_LAUNCH("scan_fast_kernel<pilot>");
-        rc = launch_sample_threshold(chist, nq, p.pilot_r, 0, bound, st);      // 0: the counted codes' own pilot_r-th smallest
+        const double e = static_cast<double>(r) * static_cast<double>(p.s_count) / static_cast<double>(n_codes);
+        rc = launch_sample_threshold(chist, nq, p.pilot_r, 0, static_cast<uint32_t>(e + 2.0 * sqrt(e)) + 2u, bound, st);      // 0: the counted codes' own pilot_r-th smallest
         if (rc) return rc;
         rc = launch_zero_words(reinterpret_cast<uint32_t *>(base + p.off_fzero), p.fzero_bytes / sizeof(uint32_t), st);
+        if (rc) return rc;
+    }
+    const uint32_t *served = nullptr;
+    if (cells) {
+        rc = launch_scan_cells(codes, n_codes, M, qtab, nq, r, *cells, bound, p.slices, p.cap, fcount, chist, fkeys, &served, st);
         if (rc) return rc;
     }
     // the scan: one contiguous stretch of codes per workgroup
     DCPQ_LAUNCH(kStageScanFast, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.fblocks), dim3(WAVES * 64),
                 C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.codes_per_block), p.codes_per_block / 64,
                 static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd | (p.pilot ? 0u : kLimited), bound,
-                fcount, chist, fkeys, notes, p.wcap);
+                fcount, chist, fkeys, notes, p.wcap, served);
     DCPQ_CHECK_LAUNCH("scan_fast_kernel");
     // exact selection, and the list of queries to redo
     rc = launch_fast_select(fkeys, fcount, chist, nq, r, p.slices, p.cap, p.sortcap, n_codes, fsort, cand_id, cand_qd, flags, st, qlist, nflag);
@@ -934,9 +943,9 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     return DCPQ_OK;
 }
 
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st)
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, Bound *bound, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, bound);
+    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, guess_r, bound);
     DCPQ_CHECK_LAUNCH("sample_threshold_kernel");
     return DCPQ_OK;
 }
@@ -979,22 +988,22 @@ size_t fast_table_bytes(int m, int qt)
 
 template <typename CodeT>
 int launch_scan_fast(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                     uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p, hipStream_t st)
+                     uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p, const CellsArea *cells, hipStream_t st)
 {
     switch (m * 1000 + static_cast<int>(p.fqt)) {
-        case 4064: return launch_fast_t<4, 64, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
-        case 8064: return launch_fast_t<8, 64, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
-        case 8032: return launch_fast_t<8, 32, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
-        case 8016: return launch_fast_t<8, 16, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
-        case 16032: return launch_fast_t<16, 32, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
-        case 32016: return launch_fast_t<32, 16, 8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
+        case 4064: return launch_fast_t<4, 64, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
+        case 8064: return launch_fast_t<8, 64, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
+        case 8032: return launch_fast_t<8, 32, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
+        case 8016: return launch_fast_t<8, 16, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
+        case 16032: return launch_fast_t<16, 32, 16, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
+        case 32016: return launch_fast_t<32, 16, 8, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
         default: return fail(DCPQ_EUNSUPPORTED, "single-pass scan: m=%d with tiles of %u queries not supported", m, p.fqt);
     }
 }
 
 template int launch_scan_fast<uint16_t>(const uint16_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *, uint8_t *,
-                                        uint8_t *, const ScanPlan &, hipStream_t);
+                                        uint8_t *, const ScanPlan &, const CellsArea *, hipStream_t);
 template int launch_scan_fast<uint8_t>(const uint8_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *, uint8_t *,
-                                       uint8_t *, const ScanPlan &, hipStream_t);
+                                       uint8_t *, const ScanPlan &, const CellsArea *, hipStream_t);
 
 }  // namespace dcpq

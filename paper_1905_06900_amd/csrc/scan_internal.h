@@ -28,7 +28,7 @@ constexpr int kNoteWaves = 16;       // wavefronts per workgroup of the single-p
 struct __attribute__((aligned(16))) Bound {
     int t;              // codes above this bucket are not wanted (only ever lowered, by atomicMin)
     uint32_t t0, last;  // of the starting bucket t0 only the ids up to `last` are wanted
-    uint32_t pad;
+    int guess;          // t, or a lower bucket that is more likely than not to do (see starting_bound)
 };
 
 struct ScanPlan {
@@ -90,15 +90,19 @@ size_t fast_table_bytes(int m, int qt);
 template <typename CodeT>
 int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
                        uint32_t r, uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit,
-                       Bound *bound, uint32_t *done, hipStream_t st);
+                       bool guess, Bound *bound, uint32_t *done, hipStream_t st);
 template <typename CodeT>
 int launch_scan_fast(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                     uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p,
+                     uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base, const ScanPlan &p, const CellsArea *cells,
                      hipStream_t st);
+// The scan over cells, between the starting bounds and the selection; *used: the device flag that says whether it served the batch
+template <typename CodeT>
+int launch_scan_cells(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r, const CellsArea &area, const Bound *bound,
+                      uint32_t nslices, uint32_t cap, uint32_t *fcount, uint32_t *chist, uint64_t *keys, const uint32_t **used, hipStream_t st);
 
 // Steps of the single-pass selection that the inverted-list variant reuses.
 // n_codes: size of the array the sample was drawn from (the sample's own size is the histogram's total)
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, Bound *bound, hipStream_t st);
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, Bound *bound, hipStream_t st);
 // n_ids: the ids are below this (0 = unknown); qlist, nflag (optional): the flagged queries, in any order, and their number
 int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32_t *chist, int nq, uint32_t r,
                        uint32_t nslices, uint32_t cap, uint32_t sortcap, uint64_t n_ids, uint64_t *spill, uint32_t *cand_id,
@@ -174,8 +178,11 @@ __device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c
 // over the array).  Where no order of the ids is known and more than `room` would be (kCrowdedSkip), the bound starts one
 // bucket lower if that is likely to do (a standard deviation above the mean instead of five), and otherwise below all
 // buckets, which flags the query.
+// bound->guess: the same with two standard deviations (of rank guess_r where that is given), for a scan that can look again
+// at the queries for which it is too low.
 enum Crowded { kCrowdedAppend = 0, kCrowdedLimit = 1, kCrowdedSkip = 2 };
-__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f)
+template <bool GUESS = true>
+__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f, uint32_t guess_r = 0)
 {
     const int lane = threadIdx.x & 63;
     uint32_t c[4], cum[4];
@@ -187,6 +194,17 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
         e = static_cast<float>(r) * static_cast<float>(total) / static_cast<float>(n);
         const float want = e + 5.0f * sqrtf(e) + 5.0f;
         if (want < static_cast<float>(r)) rs = static_cast<uint32_t>(want) + 1u;
+        guess_r = static_cast<uint32_t>(e + 2.0f * sqrtf(e)) + 2u;
+    }
+    int guess = 255;
+    if constexpr (GUESS) {
+        if (guess_r == 0 || guess_r > rs) guess_r = rs;
+        int mine = -1;
+#pragma unroll
+        for (int z = 0; z < 4; ++z)
+            if (cum[z] - c[z] < guess_r && cum[z] >= guess_r) mine = 4 * lane + z;
+        const uint64_t where = __builtin_amdgcn_ballot_w64(mine >= 0);
+        if (where) guess = __shfl(mine, __builtin_ctzll(where));
     }
 #pragma unroll
     for (int z = 0; z < 4; ++z) {
@@ -200,10 +218,10 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
                 const float upto = 2.0f * static_cast<float>(n) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
                 if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
             }
-            *bound = Bound{t, static_cast<uint32_t>(4 * lane + z), last, 0u};
+            *bound = Bound{t, static_cast<uint32_t>(4 * lane + z), last, guess};
         }
     }
-    if (lane == 63 && total < rs) *bound = Bound{255, 255u, 0xFFFFFFFFu, 0u};
+    if (lane == 63 && total < rs) *bound = Bound{255, 255u, 0xFFFFFFFFu, 255};
 }
 
 // Lowers query q's bucket bound to the bucket that holds its r-th best appended candidate (nothing

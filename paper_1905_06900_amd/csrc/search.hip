@@ -213,13 +213,16 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         int rc = launch_small_tables(y, nc, derived, m, dsub, bbar, codes, code_bytes, n_codes, r, qtab, bounds, nullptr, st,
                                      reinterpret_cast<uint32_t *>(base + p.off_scan), scan_clear_words(n_codes, m, nc, r, DCPQ_SCAN_AUTO));
         if (rc) return rc;
+        // (the table region is free until pass two: where the codes fit it, the scan may sort them there)
+        const CellsArea area{base + p.off_tables, derived, dsub, bbar};
+        const CellsArea *cells = rows == codebooks && cells_may_pay(n_codes, m, nc) && cells_bytes(n_codes, m, nc) <= p.tables_bytes ? &area : nullptr;
         // the quantized tables have 256 entries whatever bbar is, and 1-byte sub-codes are their own low-byte plane
         if (code_bytes == 1)
             rc = launch_scan(static_cast<const uint8_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd, base + p.off_scan,
-                             room, DCPQ_SCAN_AUTO, true, st);
+                             room, DCPQ_SCAN_AUTO, true, st, cells);
         else
             rc = launch_scan(static_cast<const uint16_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd,
-                             base + p.off_scan, room, DCPQ_SCAN_AUTO, true, st);
+                             base + p.off_scan, room, DCPQ_SCAN_AUTO, true, st, cells);
         if (rc) return rc;
         uint32_t *ids_c = ids + static_cast<size_t>(q0) * k;
         float *dist_c = dist + static_cast<size_t>(q0) * k;
