@@ -127,6 +127,10 @@ int launch_refine_split(const float *queries, const float *codebooks, int dsub, 
 
 int launch_topk_of_keys(const uint64_t *keys, int nq, uint32_t r, uint32_t k, uint32_t *ids, float *dist, void *ws, hipStream_t st);
 // pass one and the distances of pass two for small problems (scan_small.hip)
+// 8-bit sub-codes scanned two at a time (scan_pairs.hip); plane [n_codes][m/2], ptab [nq][m/2][256]
+bool pairs_pay(uint64_t n_codes, int m, int nq);
+int launch_pair_codes(const uint8_t *codes, uint64_t n_codes, int m, uint8_t *plane, hipStream_t st);
+int launch_pair_tables(const uint8_t *qtab, int nq, int m, uint8_t *ptab, hipStream_t st);
 bool small_search_pays(uint64_t n_codes, int m, int nq);
 size_t small_search_bytes(uint64_t n_codes, int nq, uint32_t r);
 size_t small_search_clear_words(uint64_t n_codes, int nq, uint32_t r);

@@ -10,6 +10,7 @@ struct SearchPlan {
     int chunk;
     size_t off_qtab, off_bounds, off_cand_id, off_cand_qd, off_tables, tables_bytes, off_scan, off_refine;
     size_t least, total;       // bytes a workspace must hold, and does best with
+    size_t off_pairs, off_pair_tab;      // 8-bit sub-codes scanned in pairs (off_pairs 0: not at these sizes); the scan's arrays end there
 };
 
 static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int full_bits, int chunk_queries)
@@ -56,6 +57,18 @@ static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int f
     p.off_scan = off;    // last: the scan's own last array is as long as the workspace allows
     p.least = align_up(off + least_bytes, 256);
     p.total = align_up(off + scan_bytes, 256);
+    // (not where the codes can be sorted into cells)
+    if (full_bits == 8 && pairs_pay(n_codes, m, chunk) && !(cells_may_pay(n_codes, m, chunk) && cells_bytes(n_codes, m, chunk) <= p.tables_bytes)) {
+        size_t pair_bytes = dcpq_scan_workspace_bytes(n_codes, m / 2, chunk, r);
+        if (tail) {
+            const size_t st = dcpq_scan_workspace_bytes(n_codes, m / 2, tail, r);
+            pair_bytes = st > pair_bytes ? st : pair_bytes;
+        }
+        p.off_pairs = align_up(off + pair_bytes, 256);
+        p.off_pair_tab = align_up(p.off_pairs + n_codes * (m / 2), 256);
+        const size_t t = align_up(p.off_pair_tab + static_cast<size_t>(chunk) * (m / 2) * kSmallSize, 256);
+        p.total = t > p.total ? t : p.total;
+    }
     // small problems take the two-kernel form where its arrays fit, over the tables (which it does not use) and the scan's
     // (asked of the chunk: a batch of one chunk reserves no more than one with a ragged chunk behind it)
     if (small_search_pays(n_codes, m, chunk)) {
@@ -165,7 +178,6 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
     const SearchPlan p = plan_search(n_codes, m, nq, r, b, chunk_queries);
     if (workspace_bytes < p.least)
         return fail(DCPQ_EWORKSPACE, "search: workspace %zu < %zu bytes", workspace_bytes, p.least);
-    const size_t room = workspace_bytes - p.off_scan;
     uint8_t *base = static_cast<uint8_t *>(workspace);
     uint8_t *qtab = base + p.off_qtab;
     float *bounds = reinterpret_cast<float *>(base + p.off_bounds);
@@ -207,17 +219,30 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         if (rc) return rc;
         rows = tables;
     }
+    // up to 16 derived centroids: 8-bit sub-codes are scanned as pairs, where the workspace has room for these
+    const bool paired = p.off_pairs && bbar <= 4 && workspace_bytes >= p.off_pair_tab + static_cast<size_t>(p.chunk) * (m / 2) * kSmallSize;
+    const size_t room = (paired ? p.off_pairs : workspace_bytes) - p.off_scan;
+    uint8_t *plane = base + p.off_pairs, *ptab = base + p.off_pair_tab;
+    if (paired) {
+        const int rc = launch_pair_codes(static_cast<const uint8_t *>(codes), n_codes, m, plane, st);
+        if (rc) return rc;
+    }
+    const int ms = paired ? m / 2 : m;             // sub-quantizers of the scan
     for (int q0 = 0; q0 < nq; q0 += p.chunk) {
         const int nc = (nq - q0 < p.chunk) ? nq - q0 : p.chunk;
         const float *y = queries + static_cast<size_t>(q0) * D;
         int rc = launch_small_tables(y, nc, derived, m, dsub, bbar, codes, code_bytes, n_codes, r, qtab, bounds, nullptr, st,
-                                     reinterpret_cast<uint32_t *>(base + p.off_scan), scan_clear_words(n_codes, m, nc, r, DCPQ_SCAN_AUTO));
+                                     reinterpret_cast<uint32_t *>(base + p.off_scan), scan_clear_words(n_codes, ms, nc, r, DCPQ_SCAN_AUTO));
         if (rc) return rc;
         // (the table region is free until pass two: where the codes fit it, the scan may sort them there)
         const CellsArea area{base + p.off_tables, derived, dsub, bbar};
         const CellsArea *cells = rows == codebooks && cells_may_pay(n_codes, m, nc) && cells_bytes(n_codes, m, nc) <= p.tables_bytes ? &area : nullptr;
         // the quantized tables have 256 entries whatever bbar is, and 1-byte sub-codes are their own low-byte plane
-        if (code_bytes == 1)
+        if (paired) {
+            rc = launch_pair_tables(qtab, nc, m, ptab, st);
+            if (rc) return rc;
+            rc = launch_scan(plane, n_codes, ms, ptab, nc, r, cand_id, cand_qd, base + p.off_scan, room, DCPQ_SCAN_AUTO, true, st);
+        } else if (code_bytes == 1)
             rc = launch_scan(static_cast<const uint8_t *>(codes), n_codes, m, qtab, nc, r, cand_id, cand_qd, base + p.off_scan,
                              room, DCPQ_SCAN_AUTO, true, st, cells);
         else
