@@ -15,9 +15,11 @@
 // matrix pipe (KS instructions of 32 cycles per 32 x 32 distances, KS = ceil(3 d / 16)) is busy 0.56 of the time, and 16
 // vector instructions per 32 x 32 distances (9 for the minima, the rest the conversion of the centroids, shared by the
 // points of a workgroup) 0.38; the LDS 0.22.  250007 vectors, 8
-// sub-quantizers of 16 components and 65536 centroids: 11.2 ms = 1.1 PFLOP/s of bf16 products, what a large library
-// matrix product reaches here (1.16); with all distances on the double-precision matrix pipe 97 ms.  d = 32: 6.2 ms per
+// sub-quantizers of 16 components and 65536 centroids: 11.3 ms = 1.1 PFLOP/s of bf16 products, what a large library
+// matrix product reaches here (1.16), 8.7 ms where the points are whole numbers (two products instead of three); with all distances on the double-precision matrix pipe 97 ms.  d = 32: 6.2 ms per
 // 100000 x 4 (32.7 in double precision); d = 60: 9.8 ms per 20000 x 16 (58.8).
+#include <type_traits>
+
 #include "common.h"
 #include "assign.h"
 #include "f64_tile.h"
@@ -42,9 +44,14 @@ template <int KS, int P, bool SPLIT>
 struct AssignCfg {
     static constexpr int RS = KS <= 6 ? 128 : 64;              // centroids per stage
     static constexpr int AHEAD = KS * P <= 12 ? 2 : 1;              // operand sets of a tile (2: read one tile ahead)
+    static constexpr int LAG = AHEAD == 2 && P == 4 ? 2 : 1;       // steps from a product to its minimum (registers for LAG + 1 results)
     static constexpr int TPC = SPLIT ? 1 : RS / 32;            // tiles of 32 centroids per cell
     static constexpr int TPR = 256 / RS;                       // threads that convert one centroid
     static constexpr int DPMAX = 16 * KS / 3 & ~3;             // largest padded sub-vector length
+    // steps that hold the products xh ch and xh cl, and xh ch alone: all there is to add up where xl, or both xl and cl, are zero
+    static constexpr int KS2 = (2 * DPMAX + 15) / 16, KS1 = (DPMAX + 15) / 16;
+    // ... which is looked for with sub-vectors of up to 32 components, and not with few points: registers are scarce in the others
+    static constexpr bool LOOK = !SPLIT && KS <= 6 && KS2 < KS;
     static constexpr int NG = (DPMAX / 4 + TPR - 1) / TPR;     // groups of 4 components per thread
     static constexpr int STRIDE = KS * 32 + 16;                // bytes per staged row (an odd number of 16-byte units)
     static constexpr int PTS = SPLIT ? 32 * P : 128 * P;       // points per workgroup
@@ -112,6 +119,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     __shared__ float s_cmax[4];
     __shared__ float xnorm2[C::PTS];
     __shared__ uint32_t s_count[3];                                 // points in the lists below
+    __shared__ uint32_t s_whole, s_xlow, s_clow[3];                 // set: large components in mu; an xl, a cl (of a stage) that is not zero
     __shared__ double red_v[4];
     __shared__ uint32_t red_i[4];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -123,7 +131,12 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     const bool four = KS <= 3 && 4 * dp <= 16 * KS;                 // K has room for the product xl cl (sub-vectors of up to 12)
 
     // A reference vector subtracted from points and centroids: distances do not change, norms (and with them the
-    // filter's error) shrink.  The mean of up to 64 centroids spread over the codebook; any vector would do.
+    // filter's error) shrink.  The mean of up to 64 centroids spread over the codebook; any vector would do.  One with large
+    // components is rounded to whole numbers: points that are whole numbers (vectors of bytes) then stay so, and where they
+    // are below 256 in all components xh = x, and the product with xl, a third of the matrix instructions, is left out (of whole
+    // centroids, training's first ones, that with cl too).
+    if (tid == 0) s_whole = s_xlow = s_clow[0] = s_clow[1] = s_clow[2] = 0;
+    __syncthreads();
     if (tid < 128) {
         float sum = 0.0f;
         const int ns = ncent < 64 ? ncent : 64, step = ncent / ns;
@@ -133,17 +146,21 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                 sum += cbj[static_cast<size_t>(c) * dsub + tid];
             }
         mu[tid] = sum / static_cast<float>(ns);
+        if (fabsf(mu[tid]) >= 8.0f) s_whole = 1;
     }
+    __syncthreads();
+    if (tid < 128 && s_whole) mu[tid] = rintf(mu[tid]);
     if (tid < 3) s_count[tid] = 0;
     for (int t = tid; t < C::STAGE_BYTES / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);
     __syncthreads();
 
     const int srow = tid / C::TPR, spart = tid % C::TPR;
     // The point side of the product: column `col` of B, K positions 16 ks + 8 half + e:
-    // [ -2 xh | -2 xl | -2 xh | 0 ... ] against the centroids' [ ch | ch | cl | 0 ... ]; with room for four products
-    // [ -2 xh | -2 xl | -2 xh | -2 xl | 0 ... ] against [ ch | ch | cl | cl | 0 ... ].
+    // [ -2 xh | -2 xh | -2 xl | 0 ... ] against the centroids' [ ch | cl | ch | 0 ... ]; with room for four products
+    // [ -2 xh | -2 xh | -2 xl | -2 xl | 0 ... ] against [ ch | cl | ch | cl | 0 ... ].
     // Converted in rows by the whole workgroup, RS points at a time, and read back as operands.
     v8bf bq[P][KS];
+    bool low = false;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
 #pragma unroll 1
@@ -164,10 +181,11 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                         h[e] = static_cast<__bf16>(v);
                         l[e] = static_cast<__bf16>(v - static_cast<float>(h[e]));
                         norm = fmaf(u, u, norm);
+                        low = low || static_cast<float>(l[e]) != 0.0f;
                     }
                     *reinterpret_cast<v4bf *>(row + 2 * o) = h;
-                    *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = l;
-                    *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = h;
+                    *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = h;
+                    *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = l;
                     if (four) *reinterpret_cast<v4bf *>(row + 2 * (3 * dp + o)) = l;
                 }
             }
@@ -184,6 +202,10 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         }
     }
 
+    if (low) s_xlow = 1;
+    __syncthreads();
+    const bool low_points = !C::LOOK || __builtin_amdgcn_readfirstlane(s_xlow) != 0;          // uniform
+
     // staging: TPR threads convert one centroid
     float pre[C::NG][4];
     auto load_stage = [&](int c0) {
@@ -198,20 +220,27 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                 for (int e = 0; e < 4; ++e) pre[g][e] = v.v[e];
             }
         } else {
+            // (of both paths' loads the compiler would move the first, which they share, before the branch, copy it behind the loads
+            // of this stage and so wait for all of them before the products they are to run beside)
+            int same = 0;
+            asm volatile("" : "+v"(same));
 #pragma unroll
             for (int g = 0; g < C::NG; ++g)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int o = 4 * (spart + C::TPR * g) + e;
-                    const float v = src[o < dsub ? o : 0];
+                    const float v = src[same + (o < dsub ? o : 0)];
                     pre[g][e] = o < dsub ? v : 0.0f;                  // (mu is zero there)
                 }
         }
     };
     float cmax2 = 0.0f;                       // largest |c|^2 among the centroids this thread converted
-    auto store_stage = [&](int c0, uint8_t *buf) {
+    auto store_stage = [&](auto whole, int s, uint8_t *buf) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole)::value;               // the points are: look at cl
+        const int c0 = s * C::RS;
         uint8_t *row = buf + srow * C::STRIDE;
         float norm = 0.0f;
+        bool low = false;
 #pragma unroll
         for (int g = 0; g < C::NG; ++g) {
             const int o = 4 * (spart + C::TPR * g);
@@ -226,9 +255,10 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                     l[e] = static_cast<__bf16>(v - static_cast<float>(h[e]));
                     norm = fmaf(v, v, norm);
                 }
+                if (WHOLE) low = low || (__builtin_bit_cast(uint64_t, l) & 0x7FFF7FFF7FFF7FFFull) != 0;
                 *reinterpret_cast<v4bf *>(row + 2 * o) = h;
-                *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = h;
-                *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = l;
+                *reinterpret_cast<v4bf *>(row + 2 * (dp + o)) = l;
+                *reinterpret_cast<v4bf *>(row + 2 * (2 * dp + o)) = h;
                 if (four) *reinterpret_cast<v4bf *>(row + 2 * (3 * dp + o)) = l;
             }
         }
@@ -237,6 +267,10 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         if (c0 + srow < ncent) cmax2 = norm < INFINITY ? fmaxf(cmax2, norm) : INFINITY;      // (NaN counts as infinite)
         else norm = INFINITY;                                                               // past the last centroid: never the nearest
         if (spart == 0) reinterpret_cast<float *>(buf + C::RS * C::STRIDE)[srow] = norm;
+        if (WHOLE) {                                                 // (the flag of the stage after this one is cleared: it is read no more)
+            if (low) s_clow[s % 3] = 1;
+            if (tid == 0) s_clow[(s + 1) % 3] = 0;
+        }
     };
 
     // three smallest cell minima of each of this lane's points, and the cells of the first two
@@ -248,10 +282,11 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     // One wavefront's tiles of a stage.  Short operands of a tile are read one tile ahead; the minimum over the 16 filter
     // values of one tile of points (row 8 (v / 4) + 4 half + v % 4 in value v) is taken while the matrix
     // instructions of the next run.
-    auto read_tile = [&](const uint8_t *buf, int t, v8bf (&a)[KS], v16f &norm) {
+    auto read_tile = [&](const uint8_t *buf, int t, auto &a, v16f &norm) __attribute__((always_inline)) {
+        constexpr int K = sizeof(a) / sizeof(v8bf);
         const uint8_t *ra = buf + (t * 32 + col) * C::STRIDE + half * 16;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) a[ks] = *reinterpret_cast<const v8bf *>(ra + ks * 32);
+        for (int ks = 0; ks < K; ++ks) a[ks] = *reinterpret_cast<const v8bf *>(ra + ks * 32);
         const float *nr = reinterpret_cast<const float *>(buf + C::RS * C::STRIDE) + t * 32 + 4 * half;
 #pragma unroll
         for (int v = 0; v < 16; v += 4) {
@@ -269,13 +304,14 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         m0 = fminf(fminf(acc[14], acc[15]), m0);
         return fminf(m0, m1);
     };
-    auto compute_cell = [&](const uint8_t *buf, int t0) {
+    auto compute_cell = [&](auto steps, const uint8_t *buf, int t0) __attribute__((always_inline)) {
+        constexpr int K = decltype(steps)::value;                     // steps added up
         constexpr int AH = C::AHEAD;
-        v8bf a[AH][KS];
-        v16f norm[AH], acc[2];
+        v8bf a[AH][K];
+        v16f norm[AH], acc[C::LAG + 1];
         if constexpr (AH == 2) read_tile(buf, t0, a[0], norm[0]);
 #pragma unroll
-        for (int x = 0; x <= C::TPC * P; ++x) {                       // step x: products of (tile x / P, points x % P), minimum of step x - 1
+        for (int x = 0; x < C::TPC * P + C::LAG; ++x) {               // step x: products of (tile x / P, points x % P), minimum of step x - LAG
             const int t = x / P, p = x % P;
             if (x < C::TPC * P) {
                 if constexpr (AH == 2) {
@@ -284,19 +320,19 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                     if (p == 0) read_tile(buf, t0 + t, a[0], norm[0]);
                 }
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    acc[x & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t % AH][ks], bq[p][ks], ks == 0 ? norm[t % AH] : acc[x & 1], 0, 0, 0);
+                for (int ks = 0; ks < K; ++ks)
+                    acc[x % (C::LAG + 1)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t % AH][ks], bq[p][ks], ks == 0 ? norm[t % AH] : acc[x % (C::LAG + 1)], 0, 0, 0);
             }
-            if (x > 0) {
-                const int q = (x - 1) % P;
-                const float v = minimum(acc[(x - 1) & 1]);
-                mn[q] = x <= P ? v : fminf(mn[q], v);
+            if (x >= C::LAG) {
+                const int q = (x - C::LAG) % P;
+                const float v = minimum(acc[(x - C::LAG) % (C::LAG + 1)]);
+                mn[q] = x - C::LAG < P ? v : fminf(mn[q], v);
                 asm volatile("" : "+v"(mn[q]));                       // (keeps it here: its use is behind a branch)
             }
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {                         // matrix and vector instructions in turn
+            for (int ks = 0; ks < K; ++ks) {                          // matrix and vector instructions in turn
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, (9 + KS - 1) / KS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, (9 + K - 1) / K, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -315,15 +351,32 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         }
     };
     const int nst = (ncent + C::RS - 1) / C::RS;
-    load_stage(0);
-    store_stage(0, smem);
-    __syncthreads();
-    for (int s = 0; s < nst; ++s) {                                   // uniform
-        if (s + 1 < nst) load_stage((s + 1) * C::RS);
-        compute_cell(smem + (s & 1) * C::BUF_BYTES, SPLIT ? wave : 0);
-        enter(SPLIT ? s * (C::RS / 32) + wave : s);
-        if (s + 1 < nst) store_stage((s + 1) * C::RS, smem + ((s + 1) & 1) * C::BUF_BYTES);
+    auto walk = [&](auto whole) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        load_stage(0);
+        store_stage(whole, 0, smem);
         __syncthreads();
+        for (int s = 0; s < nst; ++s) {                               // uniform
+            if (s + 1 < nst) load_stage((s + 1) * C::RS);
+            const uint8_t *buf = smem + (s & 1) * C::BUF_BYTES;
+            const int t0 = SPLIT ? wave : 0;
+            if constexpr (!WHOLE) {
+                compute_cell(std::integral_constant<int, KS>{}, buf, t0);
+            } else if (C::KS1 == C::KS2 || __builtin_amdgcn_readfirstlane(s_clow[s % 3])) {      // uniform
+                compute_cell(std::integral_constant<int, C::KS2>{}, buf, t0);
+            } else {
+                compute_cell(std::integral_constant<int, C::KS1>{}, buf, t0);
+            }
+            enter(SPLIT ? s * (C::RS / 32) + wave : s);
+            if (s + 1 < nst) store_stage(whole, s + 1, smem + ((s + 1) & 1) * C::BUF_BYTES);
+            __syncthreads();
+        }
+    };
+    if constexpr (!C::LOOK) {
+        walk(std::false_type{});
+    } else {
+        if (low_points) walk(std::false_type{});
+        else walk(std::true_type{});
     }
 
     // hand the minima over: ent[point][lane that held them][b1, b2, b3, i1, i2]
@@ -350,9 +403,10 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     // numbers loses is xl cl (2^-16) and what the two remainders multiply (2^-17 each): 2^-15 |x| |c|, twice that in
     // 2 |<x, c>|, 16 / 2^18; without the loss of xl cl half as much (15.91 and 7.98 are reached).  The K additions
     // (with the roundings of x - mu, c - mu and |c|^2 counted among them) lose at most 2^-23 of the sum of the
-    // magnitudes each.  The last term covers values that vanish below the smallest bf16 numbers.
-    constexpr float kSplit3 = 16.2f / 262144.0f, kSplit4 = 8.1f / 262144.0f, kAdd = (16.0f * KS + 16.0f) / 8388608.0f;
-    const float split = four ? kSplit4 : kSplit3;
+    // magnitudes each.  The last term covers values that vanish below the smallest bf16 numbers.  With xl = 0 the remainder of c is
+    // all that is lost: 2^-17 |x| |c|, twice.
+    constexpr float kSplit3 = 16.2f / 262144.0f, kSplit4 = 8.1f / 262144.0f, kSplit2 = 4.05f / 262144.0f, kAdd = (16.0f * KS + 16.0f) / 8388608.0f;
+    const float split = !low_points ? kSplit2 : four ? kSplit4 : kSplit3;
     auto filter_error = [split](float xn, float c1) {
         return xn * c1 * (split + 2.1f * kAdd) + c1 * c1 * (1.1f * kAdd) + 1e-35f * (1.0f + xn + c1);
     };
