@@ -205,10 +205,12 @@ __global__ __launch_bounds__(1024) void ivf_select_probe_kernel(const float *__r
 // Tables step.  All arithmetic fp32, one rounding per operation, fixed order (feeds integers).
 // ------------------------------------------------------------------------------------------------
 
-// MODE 0: smallest entry of the (query, list) tables -> atomic min into qmin_bits[q].
+// MODE 0: the entries to `keep` [nq][nprobe][m][256], the smallest of a workgroup to the first bytes of its part of qtab; or,
+// without `keep`, the smallest entry of the (query, list) tables only -> atomic min into qmin_bits[q].
 // MODE 1: quantize with the query's bounds -> qtab[q][p][m][256].
 // grid (ceil(nprobe / kIvfTabProbes), nq), 256 threads; thread i owns entry i of every table of
-// kIvfTabProbes probed lists of the query.  The derived centroid is read once per component and used for
+// kIvfTabProbes probed lists of the query, of the sub-quantizers blockIdx.z * per_z on (all of them where the batch fills the
+// chip; a query or two are spread out).  The derived centroid is read once per component and used for
 // all of those lists' residuals (the kernel is bound by these reads, which all come from the L2); every
 // entry is still the sum over t, in ascending t, of the individually rounded squares.
 constexpr int kIvfTabProbes = 8;
@@ -218,18 +220,16 @@ __global__ __launch_bounds__(256) void ivf_tables_kernel(const float *__restrict
                                                         const int32_t *__restrict__ probe, int nprobe,
                                                         const float *__restrict__ derived, int m, int dsub,
                                                         uint32_t *__restrict__ qmin_bits, const float *__restrict__ bounds,
-                                                        uint8_t *__restrict__ qtab, float *__restrict__ keep)
+                                                        uint8_t *__restrict__ qtab, float *__restrict__ keep, int per_z)
 {
-    // keep (MODE 0, optional): the entries themselves, [nq][nprobe][m][256], for the quantization to read back
-    // instead of computing them a second time
     extern __shared__ __align__(16) float lds[];         // rho [kIvfTabProbes][m*dsub]
     __shared__ float red[4];
     const int p0 = blockIdx.x * kIvfTabProbes, q = blockIdx.y, tid = threadIdx.x;
     const int np = min(kIvfTabProbes, nprobe - p0);
-    const int D = m * dsub;
+    const int D = m * dsub, j0 = blockIdx.z * per_z, j1 = min(m, j0 + per_z);
     for (int pp = 0; pp < np; ++pp) {
         const int l = probe[static_cast<size_t>(q) * nprobe + p0 + pp];
-        for (int t = tid; t < D; t += 256)
+        for (int t = j0 * dsub + tid; t < j1 * dsub; t += 256)
             lds[pp * D + t] = __fsub_rn(queries[static_cast<size_t>(q) * D + t], coarse[static_cast<size_t>(l) * D + t]);
     }
     __syncthreads();
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void ivf_tables_kernel(const float *__restrict
         qmax = bounds[2 * q + 1];
     }
     float lo = INFINITY;
-    for (int j = 0; j < m; ++j) {
+    for (int j = j0; j < j1; ++j) {
         const float *c = derived + (static_cast<size_t>(j) * kSmallSize + tid) * dsub;
         float acc[kIvfTabProbes];
 #pragma unroll
@@ -290,7 +290,10 @@ __global__ __launch_bounds__(256) void ivf_tables_kernel(const float *__restrict
     }
     if (MODE == 0) {
         lo = block_reduce(lo, false, red);
-        if (tid == 0) atomicMin(&qmin_bits[q], __float_as_uint(lo));    // entries are >= +0
+        if (tid == 0) {
+            if (keep) *reinterpret_cast<float *>(qtab + ((static_cast<size_t>(q) * nprobe + p0) * m + j0) * kSmallSize) = lo;
+            else atomicMin(&qmin_bits[q], __float_as_uint(lo));         // entries are >= +0
+        }
     }
 }
 
@@ -308,6 +311,94 @@ __global__ __launch_bounds__(256) void ivf_quantize_kept_kernel(const float *__r
     o.x = quantize_entry(v.x, qmin, qmax); o.y = quantize_entry(v.y, qmin, qmax);
     o.z = quantize_entry(v.z, qmin, qmax); o.w = quantize_entry(v.w, qmin, qmax);
     *reinterpret_cast<uchar4 *>(qtab + e) = o;
+}
+
+// The bounds from kept entries: qmin from the minima that the workgroups of the first pass left in qtab, qmax by looking the
+// entries of the first min(r, total) codes up, in probe order.  One workgroup per query.  (With the entries worked out again from
+// the centroids, 256 threads and the prefix of the list sizes taken by one of them from memory: 69 us for 1024
+// queries, r = 1000, and 22 for one; so 17 and 5.)
+__global__ __launch_bounds__(1024) void ivf_bounds_kept_kernel(const float *__restrict__ keep, const uint8_t *__restrict__ qtab,
+                                                               const int32_t *__restrict__ probe, int nprobe, int m, int per_z,
+                                                               const uint16_t *__restrict__ codes, const int64_t *__restrict__ offsets,
+                                                               uint32_t r, float *__restrict__ bounds)
+{
+    __shared__ uint64_t first[kIvfMaxProbe];       // first code of a probed list
+    __shared__ uint32_t start[kIvfMaxProbe + 1];   // codes before it in probe order, r at most
+    __shared__ float red[2][16];
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+    const int32_t *pq = probe + static_cast<size_t>(q) * nprobe;
+    // (list sizes of 64 lists at a time, by every wavefront alike; the first one writes)
+    if (wave == 0) {
+        uint64_t before = 0;
+        for (int p0 = 0; p0 < nprobe; p0 += 64) {
+            const int p = p0 + lane;
+            uint64_t at = 0, n = 0;
+            if (p < nprobe) {
+                const int l = pq[p];
+                at = static_cast<uint64_t>(offsets[l]);
+                n = static_cast<uint64_t>(offsets[l + 1]) - at;
+            }
+            uint64_t incl = n;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint64_t o = __shfl(incl, lane >= d ? lane - d : lane);
+                if (lane >= d) incl += o;
+            }
+            const uint64_t b = before + incl - n;
+            if (p < nprobe) {
+                first[p] = at;
+                start[p] = static_cast<uint32_t>(b < r ? b : r);
+            }
+            before += __shfl(incl, 63);
+        }
+        if (lane == 0) start[nprobe] = static_cast<uint32_t>(before < r ? before : r);
+    }
+    float lo = INFINITY, hi = -INFINITY;
+    const int nz = (m + per_z - 1) / per_z, nmin = (nprobe + kIvfTabProbes - 1) / kIvfTabProbes * nz;
+    for (int t = tid; t < nmin; t += blockDim.x)
+        lo = fminf(lo, *reinterpret_cast<const float *>(qtab + ((static_cast<size_t>(q) * nprobe + t / nz * kIvfTabProbes) * m + t % nz * per_z) * kSmallSize));
+    __syncthreads();
+    const uint32_t n_first = start[nprobe];
+    const bool vec = (m & 7) == 0 && (reinterpret_cast<uintptr_t>(codes) & 15) == 0;       // uniform
+    for (uint32_t i = tid; i < n_first; i += blockDim.x) {
+        int a = 0, b = nprobe;                     // the list that holds it: start[a] <= i < start[a + 1] (empty ones are passed over)
+        while (b - a > 1) {
+            const int mid = (a + b) >> 1;
+            if (start[mid] <= i) a = mid; else b = mid;
+        }
+        const uint16_t *c = codes + (first[a] + (i - start[a])) * m;
+        const float *tab = keep + (static_cast<size_t>(q) * nprobe + a) * m * kSmallSize;
+        float d = 0.0f;
+        if (vec) {
+            for (int j = 0; j < m; j += 8) {
+                uint32_t low[8];
+                load_low_bytes<8>(c + j, 0, low);
+                float e[8];
+#pragma unroll
+                for (int z = 0; z < 8; ++z) e[z] = tab[(j + z) * kSmallSize + low[z]];
+#pragma unroll
+                for (int z = 0; z < 8; ++z) d = j + z == 0 ? e[z] : __fadd_rn(d, e[z]);
+            }
+        } else {
+            for (int j = 0; j < m; ++j) {
+                const float e = tab[j * kSmallSize + (c[j] & 255)];
+                d = j == 0 ? e : __fadd_rn(d, e);
+            }
+        }
+        hi = fmaxf(hi, d);
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        lo = fminf(lo, __shfl_xor(lo, o));
+        hi = fmaxf(hi, __shfl_xor(hi, o));
+    }
+    if (lane == 0) { red[0][wave] = lo; red[1][wave] = hi; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < nw; ++w) { lo = fminf(lo, red[0][w]); hi = fmaxf(hi, red[1][w]); }
+        bounds[2 * q] = n_first ? lo : 0.0f;       // (0, 0) when the probed lists are empty
+        bounds[2 * q + 1] = n_first ? hi : 0.0f;
+    }
 }
 
 // qmax: largest small-table distance over the first min(r, total) codes met walking the probed
@@ -1301,11 +1392,8 @@ extern "C" int dcpq_ivf_build_small_tables(const float *queries, int nq, const f
         return fail(DCPQ_EWORKSPACE, "ivf_build_small_tables: workspace too small");
     hipStream_t st = as_stream(stream);
     uint32_t *qmin_bits = static_cast<uint32_t *>(workspace);
-    // +inf as the starting minimum
-    rc = launch_fill_u64(reinterpret_cast<uint64_t *>(qmin_bits), (static_cast<size_t>(nq) + 1) / 2, 0x7f8000007f800000ull, st);
-    if (rc) return rc;
     const size_t lds = sizeof(float) * static_cast<size_t>(kIvfTabProbes) * m * dsub;
-    const dim3 tgrid((nprobe + kIvfTabProbes - 1) / kIvfTabProbes, nq);
+    dim3 tgrid((nprobe + kIvfTabProbes - 1) / kIvfTabProbes, nq);
     if (lds > 64 * 1024) {                  // LDS above 64 KiB must be requested per kernel (at most 128 KiB here)
         const int most = static_cast<int>(sizeof(float) * kIvfTabProbes * 32 * 128);
         rc = allow_dynamic_lds(reinterpret_cast<const void *>(&ivf_tables_kernel<0>), most);
@@ -1318,21 +1406,34 @@ extern "C" int dcpq_ivf_build_small_tables(const float *queries, int nq, const f
     float *keep = nullptr;
     if (workspace_bytes >= dcpq_ivf_tables_workspace_bytes_fast(nq, nprobe, m))
         keep = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + dcpq_ivf_tables_workspace_bytes(nq));
+    // (the minima of the first pass lie in qtab as floats)
+    if (keep && (reinterpret_cast<uintptr_t>(qtab) & 3) == 0) {
+        // one sub-quantizer per workgroup where all of them would not give every CU one
+        const int per_z = tgrid.x * tgrid.y < 256 ? 1 : m;
+        tgrid.z = m / per_z;
+        DCPQ_LAUNCH(kStageIvfTables, st, ivf_tables_kernel<0>, tgrid, dim3(256), lds, queries, coarse, probe, nprobe,
+                    derived, m, dsub, qmin_bits, bounds, qtab, keep, per_z);
+        DCPQ_CHECK_LAUNCH("ivf_tables_kernel<keep>");
+        DCPQ_LAUNCH(kStageIvfTables, st, ivf_bounds_kept_kernel, dim3(nq), dim3(nq <= 256 ? 1024 : 256), 0, keep, qtab, probe, nprobe, m, per_z,
+                    codes, offsets, r, bounds);
+        DCPQ_CHECK_LAUNCH("ivf_bounds_kept_kernel");
+        DCPQ_LAUNCH(kStageIvfTables, st, ivf_quantize_kept_kernel, dim3(static_cast<unsigned>((n_entries / 4 + 255) / 256)), dim3(256),
+                    0, keep, n_entries, static_cast<size_t>(nprobe) * m * kSmallSize, bounds, qtab);
+        DCPQ_CHECK_LAUNCH("ivf_quantize_kept_kernel");
+        return DCPQ_OK;
+    }
+    // +inf as the starting minimum
+    rc = launch_fill_u64(reinterpret_cast<uint64_t *>(qmin_bits), (static_cast<size_t>(nq) + 1) / 2, 0x7f8000007f800000ull, st);
+    if (rc) return rc;
     DCPQ_LAUNCH(kStageIvfTables, st, ivf_tables_kernel<0>, tgrid, dim3(256), lds, queries, coarse, probe, nprobe,
-                derived, m, dsub, qmin_bits, bounds, qtab, keep);
+                derived, m, dsub, qmin_bits, bounds, qtab, nullptr, m);
     DCPQ_CHECK_LAUNCH("ivf_tables_kernel<min>");
     DCPQ_LAUNCH(kStageIvfTables, st, ivf_qmax_kernel, dim3(nq), dim3(256), sizeof(float) * m * dsub, queries, coarse, probe, nprobe, derived, m, dsub,
                 codes, offsets, r, qmin_bits, bounds);
     DCPQ_CHECK_LAUNCH("ivf_qmax_kernel");
-    if (keep) {
-        DCPQ_LAUNCH(kStageIvfTables, st, ivf_quantize_kept_kernel, dim3(static_cast<unsigned>((n_entries / 4 + 255) / 256)), dim3(256),
-                    0, keep, n_entries, static_cast<size_t>(nprobe) * m * kSmallSize, bounds, qtab);
-        DCPQ_CHECK_LAUNCH("ivf_quantize_kept_kernel");
-    } else {
-        DCPQ_LAUNCH(kStageIvfTables, st, ivf_tables_kernel<1>, tgrid, dim3(256), lds, queries, coarse, probe, nprobe,
-                    derived, m, dsub, qmin_bits, bounds, qtab, nullptr);
-        DCPQ_CHECK_LAUNCH("ivf_tables_kernel<quantize>");
-    }
+    DCPQ_LAUNCH(kStageIvfTables, st, ivf_tables_kernel<1>, tgrid, dim3(256), lds, queries, coarse, probe, nprobe,
+                derived, m, dsub, qmin_bits, bounds, qtab, nullptr, m);
+    DCPQ_CHECK_LAUNCH("ivf_tables_kernel<quantize>");
     return DCPQ_OK;
 }
 
