@@ -738,7 +738,7 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
             if (c) atomicAdd(&hist[static_cast<size_t>(q) * 256 + v], c);
         }
     } else if (MODE == kIvfTieCount) {
-        if (lane == 0) tie[static_cast<size_t>(q) * kIvfUnitsPerQuery + u] = aux;
+        if (lane == 0) __hip_atomic_store(&tie[static_cast<size_t>(q) * kIvfUnitsPerQuery + u], aux, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -746,15 +746,16 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
 // kIvfRedoRows-th query.  Only flagged queries are scanned (*nflag of them), and since that is the rare case
 // (the three passes redo what the single pass could not finish) a row of workgroups serves many queries, so
 // that a launch with nothing to do costs a few thousand empty workgroups, not one per (query, 4 units).
+// The short step that follows a histogram (thresholds) or a tie count (quotas) is done by the workgroup that finishes a row
+// last, for the row's queries (done: a counter per row, zero on entry): two launches fewer, 4.5 us each where nothing is flagged.
 constexpr int kIvfRedoRows = 32;
 
 template <int M, int MODE, typename CodeT>
 __global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
                                                       const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab,
                                                       int nprobe, int nq, uint32_t r, const uint32_t *__restrict__ nflag,
-                                                      const uint32_t *__restrict__ flags, uint32_t *__restrict__ hist,
-                                                      const uint32_t *__restrict__ thr, uint32_t *__restrict__ tie,
-                                                      uint32_t *__restrict__ counter, uint64_t *__restrict__ keys)
+                                                      const uint32_t *__restrict__ flags, uint32_t *hist, uint32_t *thr, uint32_t *tie,
+                                                      uint32_t *__restrict__ counter, uint64_t *__restrict__ keys, uint32_t *__restrict__ done)
 {
     if (*nflag == 0) return;                                 // no query is flagged: one load, not nq / gridDim.y
     for (int q = blockIdx.y; q < nq; q += gridDim.y) {
@@ -764,6 +765,20 @@ __global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    if constexpr (MODE != kIvfCollect) {
+        __shared__ uint32_t s_last;
+        // (all that this workgroup has written went by device-scope atomics and stores: it is in place once they are complete)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicAdd(&done[blockIdx.y], 1u) == gridDim.x - 1;
+        __syncthreads();
+        if (s_last == 0) return;                             // uniform
+        for (int q = blockIdx.y + (threadIdx.x >> 6) * gridDim.y; q < nq; q += 4 * gridDim.y) {
+            if (flags[q] == 0) continue;
+            if (MODE == kIvfHist) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
+            else tie_quotas(tie + static_cast<size_t>(q) * kIvfUnitsPerQuery, kIvfUnitsPerQuery, thr[2 * q + 1]);
+        }
     }
 }
 
@@ -1205,7 +1220,7 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     p.order = nq > 4;
     p.nbins = Q * 4096 < kIvfBins ? static_cast<uint32_t>(Q) * 4096 : kIvfBins;
     p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);
-    p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);
+    p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1 + 2 * kIvfRedoRows), 256);
     p.off_bins = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * p.nbins : 0), 256);
     p.zero_bytes = off;  // everything above is cleared together
     p.off_rank = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * Q * kIvfMaxProbe : 0), 256);
@@ -1216,13 +1231,13 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     p.off_keys = off;    off = align_up(off + sizeof(uint64_t) * Q * r, 256);
     p.off_spill = off;
     if (next_pow2(r) > kSortLdsKeys) off = align_up(off + sizeof(uint64_t) * Q * next_pow2(r), 256);
-    // Per slice: 32 r entries per query in all (16384 where r is smaller), less what the parts' arrays take, which came later
+    // Per slice: 32 r entries per query in all (16384 where r is smaller), less what the parts' arrays and the redo's counters take, which came later
     // and make the workspace no larger than it was
     p.cap = 2 * r < 1024 ? 1024 : 2 * r;
     {
-        const size_t parts_bytes = (p.order ? sizeof(uint32_t) * (p.nbins + Q * kIvfMaxProbe) : 0) + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe);
+        const size_t parts_bytes = 512 + (p.order ? sizeof(uint32_t) * (p.nbins + Q * kIvfMaxProbe) : 0) + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe);
         const size_t slices_bytes = sizeof(uint64_t) * Q * kFastSlices;
-        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 466 of 1024 and more)
+        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 470 of 1024 and more)
     }
     p.upd = r / 16 < 16 ? 16 : r / 16;                   // appends to one slice between bound updates
     p.sortcap = next_pow2(2 * r) < kSortLdsKeys ? kSortLdsKeys : next_pow2(2 * r);
@@ -1250,9 +1265,8 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
     IvfUnit *units = reinterpret_cast<IvfUnit *>(base + p.off_units);
     uint64_t *keys = reinterpret_cast<uint64_t *>(base + p.off_keys);
     uint64_t *spill = reinterpret_cast<uint64_t *>(base + p.off_spill);
-    int rc = launch_zero_words(reinterpret_cast<uint32_t *>(base), p.zero_bytes / 4, st);
-    if (rc) return rc;
-    rc = launch_fill_u64(keys, static_cast<size_t>(nq) * r, ~0ull, st);     // unused slots read as padding
+    // counters to zero; unused slots of the keys read as padding
+    int rc = launch_zero_and_fill(reinterpret_cast<uint64_t *>(base), p.zero_bytes / 8, keys, static_cast<size_t>(nq) * r, ~0ull, st);
     if (rc) return rc;
     uint32_t *probed = reinterpret_cast<uint32_t *>(base + p.off_probed);
     uint32_t *bins = p.order ? reinterpret_cast<uint32_t *>(base + p.off_bins) : nullptr;
@@ -1309,18 +1323,15 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
                             reinterpret_cast<int *>(base + p.off_qlist), nflag);
     if (rc) return rc;
     // the queries it flagged (a full slice, or fewer than r codes in the probed lists): three passes
+    uint32_t *redo_done = nflag + 1;
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfHist, CodeT>), grid, dim3(256), lds_tab + 4 * 256 * 4, codes, units,
-                nunits, qtab, nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys);
+                nunits, qtab, nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<hist>");
-    rc = launch_threshold(hist, nq, r, thr, st);
-    if (rc) return rc;
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfTieCount, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys);
+                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done + kIvfRedoRows);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<tiecount>");
-    rc = launch_tie_quota(tie, kIvfUnitsPerQuery, nq, thr, st);
-    if (rc) return rc;
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfCollect, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys);
+                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, nullptr);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<collect>");
     return launch_sort_candidates(keys, nq, r, spill, cand_id, cand_qd, st, flags);
 }

@@ -111,6 +111,7 @@ int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32
 // Small shared steps of the three-pass selection, reused by the inverted-list variant.
 int launch_zero_words(uint32_t *p, size_t nwords, hipStream_t st);
 int launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
+int launch_zero_and_fill(uint64_t *z, size_t nz, uint64_t *p, size_t n, uint64_t v, hipStream_t st);      // z to zero, p to v
 int launch_threshold(const uint32_t *hist, int nq, uint32_t r, uint32_t *thr, hipStream_t st);
 int launch_tie_quota(uint32_t *tie, uint32_t nunits, int nq, const uint32_t *thr, hipStream_t st);
 // flags (may be null): only queries with a non-zero flag are sorted and written
@@ -164,6 +165,59 @@ __device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c
     uint32_t run = incl - mine;
 #pragma unroll
     for (int z = 0; z < 4; ++z) { run += c[z]; cum[z] = run; }
+}
+
+// T = bucket holding the r-th smallest qd; need = ids still to take from bucket T (one wavefront).
+__device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, uint32_t *thr)
+{
+    uint32_t c[4], cum[4];
+    wave_prefix_of_buckets(hist, c, cum);
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+        if (cum[z] - c[z] < r && cum[z] >= r) { thr[0] = 4 * lane + z; thr[1] = r - (cum[z] - c[z]); }
+    // fewer than r codes in all (inverted lists only): bucket "256" takes everything
+    if (lane == 63 && cum[3] < r) { thr[0] = 256; thr[1] = 0; }
+}
+
+// Turns per-unit counts of bucket T into per-unit quotas: units are in id order, so unit u may
+// take min(count_u, need - sum of counts before u) ids (its smallest ones).  One wavefront; a lane takes 8
+// neighbouring units, and the counts of the next 512 are on their way while these are added up.  (The counts may
+// just have been stored by other workgroups.)
+__device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need)
+{
+    constexpr uint32_t PER = 8, STEP = 64 * PER;
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t next[PER];
+    auto load = [&](uint32_t base) {
+#pragma unroll
+        for (uint32_t z = 0; z < PER; ++z) {
+            const uint32_t u = base + lane * PER + z;
+            next[z] = u < nunits ? __hip_atomic_load(&row[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        }
+    };
+    load(0);
+    uint32_t carry = 0;                                        // ids of the bucket in the units before these
+    for (uint32_t base = 0; base < nunits; base += STEP) {     // uniform
+        uint32_t c[PER], mine = 0;
+#pragma unroll
+        for (uint32_t z = 0; z < PER; ++z) { c[z] = next[z]; mine += c[z]; }
+        if (base + STEP < nunits && carry < need) load(base + STEP);      // (no ids left to take: the rest is all zeros)
+        uint32_t incl = mine;
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t other = __shfl(incl, lane >= d ? lane - d : lane);
+            if (lane >= d) incl += other;
+        }
+        uint32_t before = carry + incl - mine;                 // exclusive prefix in id order
+#pragma unroll
+        for (uint32_t z = 0; z < PER; ++z) {
+            const uint32_t u = base + lane * PER + z;
+            if (u < nunits) row[u] = before >= need ? 0u : min(c[z], need - before);
+            before += c[z];
+        }
+        carry += __shfl(incl, 63);
+    }
 }
 
 // Starting bucket bound of a query from the histogram of a sample of S of the n codes, by one wavefront.
