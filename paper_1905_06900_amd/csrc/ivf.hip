@@ -1182,6 +1182,66 @@ __global__ __launch_bounds__(1024) void ivf_refine_kernel(const float *__restric
     }
 }
 
+// The same distances as keys in memory, by 256 lanes to a workgroup and one (candidate, sub-quantizer) to a lane: for batches that
+// leave most of the chip idle with a workgroup per query.  The selection is a kernel of its own.  A chain of loads (id, code,
+// row): 4 us for one query with r = 1000 and 9 for the selection, where a workgroup that also sorts took 41.
+template <int M>
+__global__ __launch_bounds__(256) void ivf_refine_keys_kernel(const float *__restrict__ queries, const float *__restrict__ coarse,
+                                                              const float *__restrict__ cb, int dsub, const uint16_t *__restrict__ codes,
+                                                              const int64_t *__restrict__ offsets, const int32_t *__restrict__ probe,
+                                                              int nprobe, const uint32_t *__restrict__ cand_id, uint32_t r,
+                                                              uint64_t *__restrict__ keys)
+{
+    __shared__ uint32_t lbeg[kIvfMaxProbe], lend[kIvfMaxProbe];   // ids are 32-bit, so are list bounds
+    __shared__ int lst[kIvfMaxProbe];
+    const int q = blockIdx.y;
+    const int D = M * dsub;
+    const uint32_t lane = threadIdx.x & 63u;
+    const int j = static_cast<int>(threadIdx.x % M);
+    const uint32_t t = blockIdx.x * (256 / M) + threadIdx.x / M;
+    const uint32_t id = t < r ? cand_id[static_cast<size_t>(q) * r + t] : 0xFFFFFFFFu;
+    for (int p = threadIdx.x; p < nprobe; p += 256) {
+        const int l = probe[static_cast<size_t>(q) * nprobe + p];
+        lst[p] = l;
+        lbeg[p] = static_cast<uint32_t>(offsets[l]);
+        lend[p] = static_cast<uint32_t>(offsets[l + 1]);
+    }
+    __syncthreads();
+    int p = -1;                                                   // pad slots (id 0xFFFFFFFF) belong to no probed list
+    for (int z = j; z < nprobe; z += M)
+        if (id >= lbeg[z] && id < lend[z]) p = z;                 // the lists are disjoint: at most one
+#pragma unroll
+    for (int off = 1; off < M; off <<= 1) p = max(p, __shfl_xor(p, off));
+    double dj = 0.0;
+    if (p >= 0) {
+        const float *yj = queries + static_cast<size_t>(q) * D + j * dsub;
+        const float *cl = coarse + static_cast<size_t>(lst[p]) * D + j * dsub;
+        const float *cen = cb + (static_cast<size_t>(j) * kFullSize + codes[static_cast<size_t>(id) * M + j]) * dsub;
+        auto add = [&](float y, float l, float c) {
+            const double diff = (static_cast<double>(y) - static_cast<double>(l)) - static_cast<double>(c);
+            dj += diff * diff;
+        };
+        if ((dsub & 3) == 0) {
+#pragma unroll 4
+            for (int tt = 0; tt < dsub; tt += 4) {
+                const float4 yv = *reinterpret_cast<const float4 *>(yj + tt);
+                const float4 lv = *reinterpret_cast<const float4 *>(cl + tt);
+                const float4 cv = *reinterpret_cast<const float4 *>(cen + tt);
+                add(yv.x, lv.x, cv.x);
+                add(yv.y, lv.y, cv.y);
+                add(yv.z, lv.z, cv.z);
+                add(yv.w, lv.w, cv.w);
+            }
+        } else {
+            for (int tt = 0; tt < dsub; ++tt) add(yj[tt], cl[tt], cen[tt]);
+        }
+    }
+    double d = __shfl(dj, static_cast<int>(lane - j));
+#pragma unroll
+    for (int jj = 1; jj < M; ++jj) d += __shfl(dj, static_cast<int>(lane - j + jj));
+    if (j == 0 && t < r) keys[static_cast<size_t>(q) * r + t] = p >= 0 ? make_key(__float_as_uint(static_cast<float>(d)), id) : ~0ull;
+}
+
 // ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
@@ -1561,6 +1621,25 @@ extern "C" int dcpq_ivf_refine_topk(const float *queries, const float *coarse, i
     const size_t need = dcpq_ivf_refine_workspace_bytes(nq, r);
     if (need && (!workspace || workspace_bytes < need)) return fail(DCPQ_EWORKSPACE, "ivf_refine_topk: workspace too small");
     hipStream_t st = as_stream(stream);
+    // With room for the keys: distances by as many workgroups as it takes, then the selection of the flat search.  Whole searches
+    // against a workgroup per query that sorts as well, in us (20 M codes in 8192 lists, 32 probed): r = 1000, 1 query 88 and 119,
+    // 64 queries 174 and 209, 1024 queries 820 and 900; r = 4000: 117 and 323, 262 and 440, 1726 and 2184.
+    const size_t key_bytes = align_up(sizeof(uint64_t) * static_cast<size_t>(nq) * r, 256);
+    if (workspace && workspace_bytes >= key_bytes + dcpq_refine_workspace_bytes(nq, r) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
+        uint64_t *keys = static_cast<uint64_t *>(workspace);
+        switch (m) {
+#define DCPQ_IVF_KEYS(MV)                                                                                                     \
+    case MV:                                                                                                                  \
+        DCPQ_LAUNCH(kStageIvfRefine, st, ivf_refine_keys_kernel<MV>, dim3((r + 256 / MV - 1) / (256 / MV), nq), dim3(256), 0, queries, \
+                    coarse, codebooks, dsub, codes, offsets, probe, nprobe, cand_id, r, keys);                                \
+        break;
+            DCPQ_IVF_KEYS(1) DCPQ_IVF_KEYS(2) DCPQ_IVF_KEYS(4) DCPQ_IVF_KEYS(8) DCPQ_IVF_KEYS(16) DCPQ_IVF_KEYS(32)
+#undef DCPQ_IVF_KEYS
+            default: return fail(DCPQ_EUNSUPPORTED, "m=%d not supported", m);
+        }
+        DCPQ_CHECK_LAUNCH("ivf_refine_keys_kernel");
+        return launch_topk_of_keys(keys, nq, r, k, ids, dist, static_cast<uint8_t *>(workspace) + key_bytes, st);
+    }
     const uint32_t np2 = next_pow2(r);
     const int use_lds = np2 <= kSortLdsKeys;
     const size_t lds = use_lds ? sizeof(uint64_t) * np2 : 0;

@@ -1,0 +1,53 @@
+"""Inverted lists: the forms that only some sizes or inputs take, against each other and against plain torch."""
+import pytest
+import torch
+
+from paper_1905_06900_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _case(kind, m, dsub, n, nq, nlist, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    cb = 3.0 * torch.randn((m, 65536, dsub), generator=g, device=DEV)
+    coarse = 10.0 * torch.randn((nlist, m * dsub), generator=g, device=DEV)
+    codes = synth.random_codes(n, m, DEV, seed + 1).view(torch.int16)
+    if kind == "ties":                       # three different codes: full slices, and ties by the thousand at the bound
+        codes = codes[:3][torch.randint(0, 3, (n,), generator=g, device=DEV)].contiguous()
+    offsets = synth.zipf_list_offsets(nlist, n, DEV, seed + 2)
+    queries = coarse[torch.randint(0, nlist, (nq,), generator=g, device=DEV)] + torch.randn((nq, m * dsub), generator=g, device=DEV)
+    return cb, coarse, codes.view(torch.uint16), offsets, queries.contiguous()
+
+
+@pytest.mark.parametrize("kind,m,dsub,n,nq,nlist,nprobe,r,k", [
+    ("random", 8, 16, 200_003, 1, 64, 9, 1000, 100),       # one query: a workgroup per sub-quantizer of its tables
+    ("random", 4, 6, 50_021, 37, 64, 33, 777, 100),        # codes of 8 bytes; more lists than a wavefront's half
+    ("random", 16, 3, 30_011, 300, 32, 5, 129, 129),       # rows that are no whole 16 bytes
+    ("random", 8, 16, 3_001, 70, 64, 3, 2000, 60),         # fewer codes than r in the lists: every query is done again, and padded
+    ("ties", 8, 4, 400_009, 45, 16, 7, 600, 50),           # more queries than rows of the redo, quotas for ties
+    ("random", 8, 8, 300_007, 5, 32, 8, 20_000, 100),      # keys beyond what is sorted in LDS
+])
+def test_search_equals_its_steps(kind, m, dsub, n, nq, nlist, nprobe, r, k):
+    cb, coarse, codes, offsets, queries = _case(kind, m, dsub, n, nq, nlist, 77 + m)
+    derived = binding.derive_codebooks(cb)
+    ids, dist = binding.ivf_search(queries, coarse, cb, derived, codes, offsets, nprobe, r, k)
+    probe = binding.ivf_probe(queries, coarse, nprobe)
+    qtab, _ = binding.ivf_build_small_tables(queries, coarse, probe, derived, codes, offsets, r)
+    cand, qd, count = binding.ivf_scan_candidates(codes, offsets, probe, qtab, r)
+    ids2, dist2 = binding.ivf_refine_topk(queries, coarse, cb, codes, offsets, probe, cand, k)
+    assert torch.equal(ids.view(torch.int32), ids2.view(torch.int32))
+    assert torch.equal(dist, dist2)
+    # the candidates: the r smallest (integer distance, id) of all probed codes
+    low = (codes.view(torch.int16).to(torch.int64)) & 255
+    for q in range(0, nq, max(1, nq // 9)):
+        keys = []
+        for p, l in enumerate(probe[q].tolist()):
+            a, b = int(offsets[l]), int(offsets[l + 1])
+            s = sum(qtab[q, p, j].long()[low[a:b, j]] for j in range(m)).clamp(max=255)
+            keys.append(s << 32 | torch.arange(a, b, device=DEV))
+        want = torch.cat(keys).sort().values[:r]
+        assert int(count[q:q + 1].view(torch.int32)) == want.numel()
+        got = (qd[q].long() << 32 | (cand[q].view(torch.int32).long() & 0xFFFFFFFF))[:want.numel()]
+        assert torch.equal(got, want)
