@@ -57,69 +57,97 @@ __global__ __launch_bounds__(256) void clear_kernel(uint32_t *p, size_t nwords)
     if (i < nwords) p[i] = 0u;
 }
 
+constexpr uint32_t kAcceptKeys = 4096;        // proposers of a group that are sorted in LDS
+
 // ---- balanced assignment ----------------------------------------------------------------------------
-// state: labels[n] (0xFFFFFFFF = no group yet), room[kbar], left[0] = points without a group
-__global__ __launch_bounds__(256) void balanced_init_kernel(uint32_t *labels, int n, uint32_t *room, int kbar, uint32_t *left)
+// state: labels[n] (0xFFFFFFFF = no group yet), room[kbar], left[0] = points without a group; count[kbar]: proposers of a round
+__global__ __launch_bounds__(256) void balanced_init_kernel(uint32_t *labels, int n, uint32_t *room, uint32_t *count, int kbar, uint32_t *left)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) labels[i] = 0xFFFFFFFFu;
-    if (i < kbar) room[i] = static_cast<uint32_t>(n / kbar);
+    if (i < kbar) { room[i] = static_cast<uint32_t>(n / kbar); count[i] = 0; }
     if (i == 0) left[0] = static_cast<uint32_t>(n);
 }
 
-// prop[i] = the group with room nearest to point i (smallest (distance, index)), -1 for a point that has a group
+// Every point without a group goes into the list of the group with room that is nearest to it (smallest (distance, index)), as a
+// key (distance, point).  A wavefront takes 16 points, a row of distances at a time: 256 bytes to a load.  (With a thread per row
+// that leaves its proposal in an array, and every group looking through that: 56 us for a round and its acceptances, 65536 points and
+// 256 groups; so 33.)
+// list: np2 keys per group (np2 = n rounded up to a power of two).
+constexpr int kProposePoints = 16;
 __global__ __launch_bounds__(256) void propose_kernel(const float *__restrict__ T, int n, int kbar,
                                                       const uint32_t *__restrict__ labels, const uint32_t *__restrict__ room,
-                                                      int *__restrict__ prop)
+                                                      const uint32_t *__restrict__ left, uint32_t *__restrict__ count,
+                                                      uint64_t *__restrict__ list, uint32_t np2)
 {
-    __shared__ uint32_t lroom[256];
-    if (threadIdx.x < static_cast<unsigned>(kbar)) lroom[threadIdx.x] = room[threadIdx.x];
-    __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int p = -1;
-    if (labels[i] == 0xFFFFFFFFu) {
-        float best = INFINITY;
-        for (int l = 0; l < kbar; ++l) {
-            const float v = T[static_cast<size_t>(i) * kbar + l];
-            if (lroom[l] > 0 && (p < 0 || v < best)) { best = v; p = l; }
+    if (*left == 0) return;                                      // uniform: a round too many
+    const int lane = threadIdx.x & 63;
+    const int i0 = (blockIdx.x * 4 + static_cast<int>(threadIdx.x >> 6)) * kProposePoints;
+    if (i0 >= n) return;
+    bool open[4];
+    int first = 256;                                             // first group with room
+#pragma unroll
+    for (int z = 3; z >= 0; --z) {
+        const int l = 64 * z + lane;
+        open[z] = l < kbar && room[l] > 0;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(open[z]);
+        if (mask) first = 64 * z + __builtin_ctzll(mask);
+    }
+    uint64_t todo = __builtin_amdgcn_ballot_w64(lane < kProposePoints && i0 + lane < n && labels[min(i0 + lane, n - 1)] == 0xFFFFFFFFu);
+    while (todo) {                                               // uniform
+        const int i = i0 + __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const float *row = T + static_cast<size_t>(i) * kbar;
+        // distances are >= +0: they order like their bits, NaN behind all (unless the first group with room has it: that one is kept)
+        uint64_t best = ~0ull;
+        bool nan = false;
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const int l = 64 * z + lane;
+            if (!open[z]) continue;
+            const float v = row[l];
+            if (l == first && v != v) nan = true;
+            const uint64_t key = make_key(__float_as_uint(v), static_cast<uint32_t>(l));
+            best = key < best ? key : best;
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t o = __shfl_xor(best, off);
+            best = o < best ? o : best;
+        }
+        if (__builtin_amdgcn_ballot_w64(nan)) best = make_key(__float_as_uint(row[first]), static_cast<uint32_t>(first));
+        if (lane == 0 && best != ~0ull) {
+            const uint32_t l = static_cast<uint32_t>(best);
+            list[static_cast<size_t>(l) * np2 + atomicAdd(&count[l], 1u)] = make_key(static_cast<uint32_t>(best >> 32), static_cast<uint32_t>(i));
         }
     }
-    prop[i] = p;
 }
 
 // One workgroup per group: its proposers ordered by (distance, point), the first `room` of them accepted.
-// list: scratch of np2 keys per group (np2 = n rounded up to a power of two).
-__global__ __launch_bounds__(1024) void accept_kernel(const float *__restrict__ T, int n, int kbar, const int *__restrict__ prop,
-                                                      uint32_t *__restrict__ labels, uint32_t *__restrict__ room,
+__global__ __launch_bounds__(1024) void accept_kernel(uint32_t *__restrict__ labels, uint32_t *__restrict__ room, uint32_t *__restrict__ count,
                                                       uint32_t *__restrict__ left, uint64_t *__restrict__ list, uint32_t np2)
 {
-    __shared__ uint32_t s_n;
+    __shared__ uint64_t keys[kAcceptKeys];
     const int l = blockIdx.x, tid = threadIdx.x;
-    const uint32_t have = room[l];
-    if (have == 0) return;                                       // uniform
-    uint64_t *a = list + static_cast<size_t>(l) * np2;
-    if (tid == 0) s_n = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += 1024)
-        if (prop[i] == l) {
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            a[pos] = make_key(__float_as_uint(T[static_cast<size_t>(i) * kbar + l]), static_cast<uint32_t>(i));   // distances are >= +0
-        }
-    __syncthreads();
-    const uint32_t p = s_n;
+    const uint32_t p = count[l], have = room[l];
     if (p == 0) return;                                          // uniform
+    uint64_t *a = list + static_cast<size_t>(l) * np2;
     uint32_t take = p;
     if (p > have) {                                              // uniform: more proposers than room, keep the closest
         uint32_t s2 = 1;
         while (s2 < p) s2 <<= 1;
-        for (uint32_t t = p + tid; t < s2; t += 1024) a[t] = ~0ull;
+        if (s2 <= kAcceptKeys) {
+            for (uint32_t t = tid; t < s2; t += 1024) keys[t] = t < p ? a[t] : ~0ull;
+            a = keys;
+        } else {
+            for (uint32_t t = p + tid; t < s2; t += 1024) a[t] = ~0ull;
+        }
         __syncthreads();
         bitonic_sort(a, s2);
         take = have;
     }
     for (uint32_t t = tid; t < take; t += 1024) labels[static_cast<uint32_t>(a[t])] = static_cast<uint32_t>(l);
-    if (tid == 0) { room[l] = have - take; atomicSub(left, take); }
+    if (tid == 0) { room[l] = have - take; count[l] = 0; atomicSub(left, take); }
 }
 
 // Step 3: one workgroup per group l walks the labels in index order; the i-th member met gets the final
@@ -207,7 +235,7 @@ static uint32_t pow2_at_least(uint32_t x)
     return p;
 }
 
-struct SameSizePlan { size_t off_T, off_prop, off_room, off_left, off_list, off_means, total; uint32_t np2; };
+struct SameSizePlan { size_t off_T, off_count, off_room, off_left, off_list, off_means, total; uint32_t np2; };
 
 static SameSizePlan plan_same_size(int n, int d, int kbar)
 {
@@ -215,7 +243,7 @@ static SameSizePlan plan_same_size(int n, int d, int kbar)
     p.np2 = pow2_at_least(static_cast<uint32_t>(n));
     size_t off = 0;
     p.off_T = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(n) * kbar, 256);
-    p.off_prop = off;  off = align_up(off + sizeof(int) * static_cast<size_t>(n), 256);
+    p.off_count = off; off = align_up(off + sizeof(uint32_t) * static_cast<size_t>(n), 256);     // (kbar <= n counters; as much as there always was here)
     p.off_room = off;  off = align_up(off + sizeof(uint32_t) * kbar, 256);
     p.off_left = off;  off = align_up(off + 256, 256);
     p.off_list = off;  off = align_up(off + sizeof(uint64_t) * static_cast<size_t>(kbar) * p.np2, 256);
@@ -293,7 +321,7 @@ extern "C" int dcpq_kmeans_same_size(const float *points, int n, int d, int kbar
     if (workspace_bytes < p.total) return fail(DCPQ_EWORKSPACE, "kmeans_same_size: workspace %zu < %zu bytes", workspace_bytes, p.total);
     uint8_t *base = static_cast<uint8_t *>(workspace);
     float *T = reinterpret_cast<float *>(base + p.off_T);
-    int *prop = reinterpret_cast<int *>(base + p.off_prop);
+    uint32_t *count = reinterpret_cast<uint32_t *>(base + p.off_count);
     uint32_t *room = reinterpret_cast<uint32_t *>(base + p.off_room);
     uint32_t *left = reinterpret_cast<uint32_t *>(base + p.off_left);
     uint64_t *list = reinterpret_cast<uint64_t *>(base + p.off_list);
@@ -302,17 +330,21 @@ extern "C" int dcpq_kmeans_same_size(const float *points, int n, int d, int kbar
         int rc = launch_distance_tables(points, n, centroids, 1, d, kbar, T, kStageTrain, st);
         if (rc) return rc;
         const int nb = (n > kbar ? n : kbar);
-        DCPQ_LAUNCH(kStageTrain, st, balanced_init_kernel, dim3((nb + 255) / 256), dim3(256), 0, labels, n, room, kbar, left);
+        DCPQ_LAUNCH(kStageTrain, st, balanced_init_kernel, dim3((nb + 255) / 256), dim3(256), 0, labels, n, room, count, kbar, left);
         DCPQ_CHECK_LAUNCH("balanced_init_kernel");
-        // rounds until every point has a group; every round gives at least one point a group, and the count
-        // is read back after each (the only host synchronization in the library)
+        // rounds until every point has a group; every round gives at least one point a group.  The count is read back (the only
+        // host synchronization in the library) after eight rounds, which is what it takes as a rule, and after every four more: a
+        // round too many returns at once
         uint32_t h_left = static_cast<uint32_t>(n);
-        for (int round = 0; h_left > 0; ++round) {
+        for (int64_t round = 0, ahead = 8; h_left > 0; ahead = 4) {
             if (round > n) return fail(DCPQ_EHIP, "kmeans_same_size: balanced assignment did not finish");
-            DCPQ_LAUNCH(kStageTrain, st, propose_kernel, dim3((n + 255) / 256), dim3(256), 0, T, n, kbar, labels, room, prop);
-            DCPQ_CHECK_LAUNCH("propose_kernel");
-            DCPQ_LAUNCH(kStageTrain, st, accept_kernel, dim3(kbar), dim3(1024), 0, T, n, kbar, prop, labels, room, left, list, p.np2);
-            DCPQ_CHECK_LAUNCH("accept_kernel");
+            for (int64_t end = round + ahead; round < end; ++round) {
+                const int per = 4 * kProposePoints;
+                DCPQ_LAUNCH(kStageTrain, st, propose_kernel, dim3((n + per - 1) / per), dim3(256), 0, T, n, kbar, labels, room, left, count, list, p.np2);
+                DCPQ_CHECK_LAUNCH("propose_kernel");
+                DCPQ_LAUNCH(kStageTrain, st, accept_kernel, dim3(kbar), dim3(1024), 0, labels, room, count, left, list, p.np2);
+                DCPQ_CHECK_LAUNCH("accept_kernel");
+            }
             DCPQ_CHECK_HIP(hipMemcpyAsync(&h_left, left, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
             DCPQ_CHECK_HIP(hipStreamSynchronize(st));
         }
