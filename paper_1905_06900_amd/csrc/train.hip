@@ -70,11 +70,11 @@ __global__ __launch_bounds__(256) void balanced_init_kernel(uint32_t *labels, in
 }
 
 // Every point without a group goes into the list of the group with room that is nearest to it (smallest (distance, index)), as a
-// key (distance, point).  A wavefront takes 16 points, a row of distances at a time: 256 bytes to a load.  (With a thread per row
+// key (distance, point).  A wavefront takes 4 points, a row of distances at a time: 256 bytes to a load.  (With a thread per row
 // that leaves its proposal in an array, and every group looking through that: 56 us for a round and its acceptances, 65536 points and
 // 256 groups; so 33.)
 // list: np2 keys per group (np2 = n rounded up to a power of two).
-constexpr int kProposePoints = 16;
+constexpr int kProposePoints = 4;
 __global__ __launch_bounds__(256) void propose_kernel(const float *__restrict__ T, int n, int kbar,
                                                       const uint32_t *__restrict__ labels, const uint32_t *__restrict__ room,
                                                       const uint32_t *__restrict__ left, uint32_t *__restrict__ count,
@@ -215,7 +215,8 @@ static int launch_means(const float *points, uint64_t n, int ld, int m, int d, c
     return DCPQ_OK;
 }
 
-// k-means of m sub-quantizers at once: sub-vectors j of the points, centroids [m][k][d], labels [n][m]
+// k-means iterations of m sub-quantizers at once: sub-vectors j of the points, centroids [m][k][d], labels [n][m] (those the
+// centroids are the means of)
 static int launch_kmeans(const float *points, uint64_t n, int ld, int m, int d, int k, int iters, float *centroids, uint32_t *labels,
                          void *ws, hipStream_t st)
 {
@@ -225,7 +226,7 @@ static int launch_kmeans(const float *points, uint64_t n, int ld, int m, int d, 
         rc = launch_means(points, n, ld, m, d, labels, k, centroids, ws, st);
         if (rc) return rc;
     }
-    return launch_assign(points, n, ld, centroids, m, d, k, labels, 4, nullptr, st);
+    return DCPQ_OK;
 }
 
 static uint32_t pow2_at_least(uint32_t x)
@@ -298,7 +299,9 @@ extern "C" int dcpq_kmeans(const float *points, uint64_t n, int ld, int d, int k
     DCPQ_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255) == 0, "kmeans: workspace must be 256-byte aligned");
     if (workspace_bytes < means_bytes(k, d))
         return fail(DCPQ_EWORKSPACE, "kmeans: workspace %zu < %zu bytes", workspace_bytes, means_bytes(k, d));
-    return launch_kmeans(points, n, ld, 1, d, k, iters, centroids, labels, workspace, as_stream(stream));
+    const int rc = launch_kmeans(points, n, ld, 1, d, k, iters, centroids, labels, workspace, as_stream(stream));
+    if (rc) return rc;
+    return launch_assign(points, n, ld, centroids, 1, d, k, labels, 4, nullptr, as_stream(stream));
 }
 
 extern "C" size_t dcpq_kmeans_same_size_workspace_bytes(int n, int d, int kbar)
@@ -415,7 +418,8 @@ extern "C" int dcpq_build_quantizers(const float *train, uint64_t n_train, int m
     float *cbar = reinterpret_cast<float *>(base + p.off_cbar);
     const int k = 1 << b, kbar = 1 << bbar, D = m * dsub;
     hipStream_t st = as_stream(stream);
-    // step 1: k-means of the centroids the caller left in `codebooks`, in place, of as many sub-quantizers at once as the room
+    // step 1: k-means of the centroids the caller left in `codebooks`, in place (the points' labels after the last iteration are no
+    // result of the training and are not taken), of as many sub-quantizers at once as the room
     // for same-size k-means (256 rows of all centroids) holds labels and sums for.  One at a time leaves half of the chip idle
     // (131072 points, 65536 centroids of 16 components: an assignment for 8 sub-quantizers 6.5 ms one by one, 4.5 together).
     int together = 0;
