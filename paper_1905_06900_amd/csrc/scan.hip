@@ -406,11 +406,13 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t
         if (s_codes > enough) s_codes = enough;
         if (s_codes < 65536) s_codes = 65536;
         // With a pilot pass (below; worth its three extra launches when the histogram of the sample would take more
-        // than 60 microseconds) the sample costs several times less per code, and is taken twice as large where it holds
+        // than 30 to 40 microseconds: searches of 300 queries over 1e7 codes 607 us without and 577 with it, 600 over 2e7 1179 and
+        // 1134, 400 over 1e7 8-bit codes 668 and 631; not at m = 4, where so many codes tie that the pilot has most of its sample to
+        // count: 1000 queries over 4e6 skewed codes 798 without it) the sample costs several times less per code, and is taken twice as large where it holds
         // few of the wanted codes (measured at N = 1e8, r = 4000, 4096 queries: sample and
         // scan together 41.25, 40.93, 40.72, 40.90 ms with 1, 2, 4, 8 times the sample; at N = 1e7, r = 5000
         // the larger sample costs what it saves).
-        const bool want_pilot = s_codes * Q * static_cast<uint64_t>(m) >= 330000000ull;
+        const bool want_pilot = s_codes * Q * static_cast<uint64_t>(m) >= (m >= 8 ? 150000000ull : 330000000ull);
         if (want_pilot && s_codes < 32 * (n_codes / r)) s_codes *= 2;
         if (s_codes > n_codes) s_codes = n_codes;
         p.s_unit = 256;

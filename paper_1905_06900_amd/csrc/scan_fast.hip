@@ -154,12 +154,13 @@ __global__ __launch_bounds__(256) void swizzle_tables_kernel(const uint8_t *__re
 
 // Starting bounds from sample histograms, a wavefront per query (see starting_bound).
 __global__ __launch_bounds__(256) void sample_threshold_kernel(const uint32_t *__restrict__ shist, int nq, uint32_t r,
-                                                               uint64_t n_codes, uint32_t guess_r,
+                                                               uint64_t n_codes, uint32_t guess_r, uint64_t sample, uint32_t want_r,
                                                                Bound *__restrict__ bound)
 {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q >= nq) return;
-    starting_bound(shist + static_cast<size_t>(q) * 256, r, n_codes, kCrowdedAppend, bound + q, 0.0f, guess_r);
+    starting_bound(shist + static_cast<size_t>(q) * 256, r, 0, kCrowdedLimit, bound + q, 0.0f, guess_r, n_codes,
+                   static_cast<float>(n_codes) / static_cast<float>(sample), want_r);
 }
 
 // Low bytes of the M sub-codes of one code, reordered by residue class: byte (j & 3) * CLS + (j >> 2).
@@ -921,7 +922,7 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
                     bound, fcount, chist, fkeys, notes, p.wcap, nullptr);
         DCPQ_CHECK_LAUNCH("scan_fast_kernel<pilot>");
         const double e = static_cast<double>(r) * static_cast<double>(p.s_count) / static_cast<double>(n_codes);
-        rc = launch_sample_threshold(chist, nq, p.pilot_r, 0, static_cast<uint32_t>(e + 2.0 * sqrt(e)) + 2u, bound, st);      // 0: the counted codes' own pilot_r-th smallest
+        rc = launch_sample_threshold(chist, nq, p.pilot_r, n_codes, static_cast<uint32_t>(e + 2.0 * sqrt(e)) + 2u, p.s_count, r, bound, st);
         if (rc) return rc;
         rc = launch_zero_words(reinterpret_cast<uint32_t *>(base + p.off_fzero), p.fzero_bytes / sizeof(uint32_t), st);
         if (rc) return rc;
@@ -934,7 +935,7 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     // the scan: one contiguous stretch of codes per workgroup
     DCPQ_LAUNCH(kStageScanFast, st, (scan_fast_kernel<M, QT, WAVES, CodeT>), dim3(p.ntiles, p.fblocks), dim3(WAVES * 64),
                 C::LDS_BYTES, codes, n_codes, static_cast<uint64_t>(p.codes_per_block), p.codes_per_block / 64,
-                static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd | (p.pilot ? 0u : kLimited), bound,
+                static_cast<uint32_t>((n_codes + 63) / 64), 0u, 64u, qsw, nq, r, p.slices, p.cap, p.upd | kLimited, bound,
                 fcount, chist, fkeys, notes, p.wcap, served);
     DCPQ_CHECK_LAUNCH("scan_fast_kernel");
     // exact selection, and the list of queries to redo
@@ -943,9 +944,10 @@ static int launch_fast_t(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     return DCPQ_OK;
 }
 
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, Bound *bound, hipStream_t st)
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, uint64_t sample, uint32_t want_r,
+                            Bound *bound, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, guess_r, bound);
+    DCPQ_LAUNCH(kStageSelect, st, sample_threshold_kernel, dim3((nq + 3) / 4), dim3(256), 0, shist, nq, r, n_codes, guess_r, sample, want_r, bound);
     DCPQ_CHECK_LAUNCH("sample_threshold_kernel");
     return DCPQ_OK;
 }

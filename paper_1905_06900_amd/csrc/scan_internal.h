@@ -27,7 +27,7 @@ constexpr int kNoteWaves = 16;       // wavefronts per workgroup of the single-p
 // Running bucket bound of a query in the single-pass scans (one 16-byte record per query).
 struct __attribute__((aligned(16))) Bound {
     int t;              // codes above this bucket are not wanted (only ever lowered, by atomicMin)
-    uint32_t t0, last;  // of the starting bucket t0 only the ids up to `last` are wanted
+    uint32_t t0, last;  // of the starting bucket t0 only the ids up to `last` are wanted (256: no bucket is limited)
     int guess;          // t, or a lower bucket that is more likely than not to do (see starting_bound)
 };
 
@@ -102,7 +102,8 @@ int launch_scan_cells(const CodeT *codes, uint64_t n_codes, int m, const uint8_t
 
 // Steps of the single-pass selection that the inverted-list variant reuses.
 // n_codes: size of the array the sample was drawn from (the sample's own size is the histogram's total)
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, Bound *bound, hipStream_t st);
+int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, uint64_t sample, uint32_t want_r,
+                            Bound *bound, hipStream_t st);
 // n_ids: the ids are below this (0 = unknown); qlist, nflag (optional): the flagged queries, in any order, and their number
 int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32_t *chist, int nq, uint32_t r,
                        uint32_t nslices, uint32_t cap, uint32_t sortcap, uint64_t n_ids, uint64_t *spill, uint32_t *cand_id,
@@ -232,11 +233,13 @@ __device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need)
 // over the array).  Where no order of the ids is known and more than `room` would be (kCrowdedSkip), the bound starts one
 // bucket lower if that is likely to do (a standard deviation above the mean instead of five), and otherwise below all
 // buckets, which flags the query.
+// (n = 0, with exact counts of a sample: r is its rank already; `all` codes, `scale` times the sample, of which all_r are wanted.)
 // bound->guess: the same with two standard deviations (of rank guess_r where that is given), for a scan that can look again
 // at the queries for which it is too low.
 enum Crowded { kCrowdedAppend = 0, kCrowdedLimit = 1, kCrowdedSkip = 2 };
 template <bool GUESS = true>
-__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f, uint32_t guess_r = 0)
+__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f, uint32_t guess_r = 0,
+                                      uint64_t all = 0, float scale = 0.0f, uint32_t all_r = 0)
 {
     const int lane = threadIdx.x & 63;
     uint32_t c[4], cum[4];
@@ -245,6 +248,9 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
     uint32_t rs = r;
     float e = 0.0f;
     if (n) {                                                  // 0: the sample's own r-th smallest
+        all = n;
+        scale = static_cast<float>(n) / static_cast<float>(total);
+        all_r = r;
         e = static_cast<float>(r) * static_cast<float>(total) / static_cast<float>(n);
         const float want = e + 5.0f * sqrtf(e) + 5.0f;
         if (want < static_cast<float>(r)) rs = static_cast<uint32_t>(want) + 1u;
@@ -265,14 +271,14 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
         const uint32_t before = cum[z] - c[z];
         if (before < rs && cum[z] >= rs) {                    // one lane, one bucket
             uint32_t last = 0xFFFFFFFFu;
-            const float expect = static_cast<float>(cum[z]) * (static_cast<float>(n) / static_cast<float>(total));
+            const float expect = static_cast<float>(cum[z]) * scale;
             int t = 4 * lane + z;
             if (crowded == kCrowdedSkip && n && expect > room) t = static_cast<float>(before) >= e + sqrtf(e) ? t - 1 : -1;
-            if (crowded == kCrowdedLimit && expect > 16.0f * static_cast<float>(r)) {
-                const float upto = 2.0f * static_cast<float>(n) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
+            if (crowded == kCrowdedLimit && expect > 16.0f * static_cast<float>(all_r)) {
+                const float upto = 2.0f * static_cast<float>(all) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
                 if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
             }
-            *bound = Bound{t, static_cast<uint32_t>(4 * lane + z), last, guess};
+            *bound = Bound{t, last == 0xFFFFFFFFu ? 256u : static_cast<uint32_t>(4 * lane + z), last, guess};
         }
     }
     if (lane == 63 && total < rs) *bound = Bound{255, 255u, 0xFFFFFFFFu, 255};
