@@ -378,7 +378,7 @@ __global__ __launch_bounds__(1024) void cells_sort_kernel(const uint32_t *__rest
 // lanes, as many as suit their length, sixteen codes per lane at a time, the next ones on their way while these are looked up;
 // codes whose lower bound is within the bound go to a second queue; (4) when that is full, and at the end: id, code and
 // integer distance of the queued codes, four per thread, and those within the bound are appended to the query's buffer.
-// Bound by lines of memory: 1e8 codes, 4096 queries read 14.9 GB (stretches of 95 codes touch 2.5 lines, a settled code
+// Bound by lines of memory: 1e8 codes, 4096 queries read 30 GB (stretches of 95 codes touch 2.5 lines, a settled code
 // another) in 4.9 ms, beside 75 % of the vector issue slots; three steps under way instead of one changed nothing, nor did
 // stretches cut into equal units for every lane group (half of the instructions then went into finding the next unit).
 struct CellCfg {
