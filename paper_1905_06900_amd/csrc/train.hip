@@ -128,8 +128,12 @@ __global__ __launch_bounds__(1024) void accept_kernel(uint32_t *__restrict__ lab
                                                       uint32_t *__restrict__ left, uint64_t *__restrict__ list, uint32_t np2)
 {
     __shared__ uint64_t keys[kAcceptKeys];
+    __shared__ uint32_t s_count, s_room;
     const int l = blockIdx.x, tid = threadIdx.x;
-    const uint32_t p = count[l], have = room[l];
+    // (read by the thread that overwrites them at the end: another wavefront might start after that)
+    if (tid == 0) { s_count = count[l]; s_room = room[l]; }
+    __syncthreads();
+    const uint32_t p = s_count, have = s_room;
     if (p == 0) return;                                          // uniform
     uint64_t *a = list + static_cast<size_t>(l) * np2;
     uint32_t take = p;

@@ -271,6 +271,22 @@ def test_same_size_kmeans_against_the_oracle(n, d, kbar, iters):
     np.testing.assert_allclose(cent, rc, rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("n,kbar", [(4096, 64), (65536, 256), (65536, 16), (65536, 2)])
+def test_same_size_kmeans_where_every_group_has_room_for_its_proposers(n, kbar):
+    # groups of 64 to 32768 points apart from each other: every proposer is accepted at once, unsorted, by one to all wavefronts of
+    # the group's workgroup
+    print("same-size k-means, room for all, n=%d kbar=%d" % (n, kbar), flush=True)
+    g = gen(n + kbar)
+    of = (torch.arange(n, device=DEV) % kbar)[torch.randperm(n, generator=g, device=DEV)]
+    p = (100.0 * of[:, None] + torch.rand((n, 3), generator=g, device=DEV)).contiguous()
+    init = (100.0 * torch.arange(kbar, device=DEV)[:, None] + 0.5).expand(kbar, 3).contiguous()
+    cent, labels = binding.kmeans_same_size(p, init, 8)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_np(labels), to_np(of))
+    means = torch.stack([p.double()[of == l].mean(0) for l in range(kbar)])
+    np.testing.assert_allclose(to_np(cent), to_np(means), rtol=2.0 ** -23)
+
+
 def test_final_codebook_against_the_oracle():
     g = gen(31)
     for b, bbar, d in [(8, 3, 5), (16, 8, 12), (8, 8, 4)]:
