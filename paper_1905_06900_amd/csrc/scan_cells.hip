@@ -678,7 +678,7 @@ __global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
                 }
                 if (hits) {                                      // those of the stretch
                     auto below = [](int n) { return n >= 16 ? ~0u : (1u << (2 * (n & ~3) + (n & 3))) - 1u; };
-                    hits &= below(min(max(static_cast<int>(end0 - hit_at), 0), 16));
+                    hits &= below(end0 > hit_at ? static_cast<int>(min(end0 - hit_at, 16u)) : 0);
                     if (hit_at < start0) hits &= ~below(static_cast<int>(min(start0 - hit_at, 16u)));
                 }
                 full = queue();
@@ -777,9 +777,10 @@ static CellsPlan plan_cells(uint64_t n, int m, int nq)
 
 size_t cells_bytes(uint64_t n, int m, int nq) { return plan_cells(n, m, nq).total; }
 
+// (Fewer than 2^31 codes: a lane steps up to 1024 positions past the end of its stretch, and tiles are counted in 32 bits.)
 bool cells_may_pay(uint64_t n, int m, int nq)
 {
-    return m == 8 && n >= (4ull << 20) && static_cast<double>(n) * nq >= 8.0e9;
+    return m == 8 && n >= (4ull << 20) && n < (1ull << 31) && static_cast<double>(n) * nq >= 8.0e9;
 }
 
 template <typename CodeT>

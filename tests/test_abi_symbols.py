@@ -118,6 +118,17 @@ def test_smallest_scan_workspace_fits_the_static_scratch(lib):
         assert info[10] <= lib.dcpq_scan_workspace_bytes(n, m, q, r)
 
 
+def test_arrays_beyond_31_bit_positions_are_not_sorted_into_cells(lib):
+    """The scan over cells holds positions of codes in 32 bits and steps past the end of a stretch, so the rule that takes a
+    search there (dcpq::cells_may_pay) stops below 2^31 codes; dcpq_search itself takes fewer than 2^32."""
+    may = lib._ZN4dcpq13cells_may_payEmii
+    may.restype = ctypes.c_bool
+    may.argtypes = [ctypes.c_uint64, ctypes.c_int, ctypes.c_int]
+    for n in (1 << 31, (1 << 31) + 12345, (1 << 32) - 1):
+        assert not may(n, 8, 20_000)
+    assert may((1 << 31) - 1, 8, 20_000) and may(100_000_000, 8, 4096)
+
+
 @pytest.mark.parametrize("nq,r,was", [(1, 1, 165632), (1, 1000, 298496), (2, 100, 330496), (4, 30, 656384), (5, 1, 819200), (5, 5000, 7419136), (7, 20, 1146880), (31, 1, 5067264), (33, 400, 5499904), (1000, 1000, 296352768), (300, 20000, 1829635840)])
 def test_inverted_list_scan_asks_for_no_more_than_it_once_did(lib, nq, r, was):
     """The lists of parts take the place of entries of the candidate buffers: a workspace of the size that was stated
