@@ -1625,7 +1625,9 @@ extern "C" int dcpq_ivf_refine_topk(const float *queries, const float *coarse, i
     // against a workgroup per query that sorts as well, in us (20 M codes in 8192 lists, 32 probed): r = 1000, 1 query 88 and 119,
     // 64 queries 174 and 209, 1024 queries 820 and 900; r = 4000: 117 and 323, 262 and 440, 1726 and 2184.
     const size_t key_bytes = align_up(sizeof(uint64_t) * static_cast<size_t>(nq) * r, 256);
-    if (workspace && workspace_bytes >= key_bytes + dcpq_refine_workspace_bytes(nq, r) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
+    // (within the limits of a grid: 65535 queries along y, 2^32 threads along x)
+    const bool fits = nq <= 65535 && static_cast<uint64_t>(r) * m <= 0xFFFFF000ull;
+    if (fits && workspace && workspace_bytes >= key_bytes + dcpq_refine_workspace_bytes(nq, r) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
         uint64_t *keys = static_cast<uint64_t *>(workspace);
         switch (m) {
 #define DCPQ_IVF_KEYS(MV)                                                                                                     \

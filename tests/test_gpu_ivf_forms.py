@@ -51,3 +51,25 @@ def test_search_equals_its_steps(kind, m, dsub, n, nq, nlist, nprobe, r, k):
         assert int(count[q:q + 1].view(torch.int32)) == want.numel()
         got = (qd[q].long() << 32 | (cand[q].view(torch.int32).long() & 0xFFFFFFFF))[:want.numel()]
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("nq", [3, 65_535, 65_536, 70_001])      # more queries than a grid takes along y: a workgroup per query
+def test_refinement_of_very_many_queries(nq):
+    m, dsub, nlist, nprobe, r, k = 4, 4, 16, 2, 8, 3
+    cb, coarse, codes, offsets, queries = _case("random", m, dsub, 5_003, nq, nlist, 5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(nq)
+    probe = torch.rand((nq, nlist), generator=g, device=DEV).argsort(1)[:, :nprobe].to(torch.int32).contiguous()
+    cand = torch.randint(0, 5_003, (nq, r), generator=g, device=DEV, dtype=torch.int32)     # (those of other lists are padding)
+    L, ptr = binding.lib(), lambda t: t.data_ptr()
+
+    def refine(workspace_bytes):
+        ids, dist = torch.zeros((nq, k), dtype=torch.int32, device=DEV), torch.zeros((nq, k), device=DEV)
+        ws = torch.empty(max(workspace_bytes, 256), dtype=torch.uint8, device=DEV)
+        assert L.dcpq_ivf_refine_topk(ptr(queries), ptr(coarse), nlist, ptr(cb), m, dsub, ptr(codes), ptr(offsets), ptr(probe), nprobe, ptr(cand),
+                                      nq, r, k, ptr(ids), ptr(dist), ptr(ws), workspace_bytes, torch.cuda.current_stream().cuda_stream) == 0
+        return ids, dist
+
+    ids, dist = refine(8 * nq * r + 256 + L.dcpq_refine_workspace_bytes(nq, r))        # room for the keys
+    ids1, dist1 = refine(L.dcpq_ivf_refine_workspace_bytes(nq, r))
+    assert torch.equal(ids, ids1) and torch.equal(dist, dist1)
