@@ -748,7 +748,9 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
 // that a launch with nothing to do costs a few thousand empty workgroups, not one per (query, 4 units).
 // The short step that follows a histogram (thresholds) or a tie count (quotas) is done by the workgroup that finishes a row
 // last, for the row's queries (done: a counter per row, zero on entry): two launches fewer, 4.5 us each where nothing is flagged.
-constexpr int kIvfRedoRows = 32;
+// The counters lie a memory line apart: side by side, their returning atomics from all rows queue for one line (72 queries, all
+// flagged: 24 us for the histogram and 19 for the tie count so, 89 and 86 with the counters in one line).
+constexpr int kIvfRedoRows = 32, kIvfRedoLine = 32;          // rows; words from one counter to the next
 
 template <int M, int MODE, typename CodeT>
 __global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
@@ -771,13 +773,13 @@ __global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__
         // (all that this workgroup has written went by device-scope atomics and stores: it is in place once they are complete)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(&done[blockIdx.y], 1u) == gridDim.x - 1;
+        if (threadIdx.x == 0) s_last = atomicAdd(&done[blockIdx.y * kIvfRedoLine], 1u) == gridDim.x - 1;
         __syncthreads();
         if (s_last == 0) return;                             // uniform
         for (int q = blockIdx.y + (threadIdx.x >> 6) * gridDim.y; q < nq; q += 4 * gridDim.y) {
             if (flags[q] == 0) continue;
             if (MODE == kIvfHist) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
-            else tie_quotas(tie + static_cast<size_t>(q) * kIvfUnitsPerQuery, kIvfUnitsPerQuery, thr[2 * q + 1]);
+            else tie_quotas(tie + static_cast<size_t>(q) * kIvfUnitsPerQuery, nunits[q], thr[2 * q + 1]);
         }
     }
 }
@@ -1250,7 +1252,7 @@ struct IvfScanPlan {
     // single pass: sample histogram, cursors, appended histogram (cleared with the rest); bounds, flags, buffers
     size_t off_shist, off_fcount, off_chist, off_bound, off_flags, off_fkeys, off_fsort, off_probed;
     // its parts: bins of list ids, cursor, finished sample workgroups (cleared with the rest); places, lengths, records
-    size_t off_bins, off_cursor, off_done, off_rank, off_part, off_items, off_qlist;
+    size_t off_bins, off_cursor, off_done, off_redo, redo_rows, off_rank, off_part, off_items, off_qlist;
     bool order;              // parts ordered by list ...
     uint32_t nbins;          // ... in so many bins
     uint32_t parts;          // parts per query, about (and one more per probed list at most) ...
@@ -1280,7 +1282,10 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     p.order = nq > 4;
     p.nbins = Q * 4096 < kIvfBins ? static_cast<uint32_t>(Q) * 4096 : kIvfBins;
     p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);
-    p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1 + 2 * kIvfRedoRows), 256);
+    p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);
+    p.redo_rows = nq < kIvfRedoRows ? nq : kIvfRedoRows;
+    const size_t redo_bytes = sizeof(uint32_t) * 2 * kIvfRedoLine * p.redo_rows;      // (a multiple of 256)
+    p.off_redo = off;    off += redo_bytes;
     p.off_bins = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * p.nbins : 0), 256);
     p.zero_bytes = off;  // everything above is cleared together
     p.off_rank = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * Q * kIvfMaxProbe : 0), 256);
@@ -1295,9 +1300,9 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     // and make the workspace no larger than it was
     p.cap = 2 * r < 1024 ? 1024 : 2 * r;
     {
-        const size_t parts_bytes = 512 + (p.order ? sizeof(uint32_t) * (p.nbins + Q * kIvfMaxProbe) : 0) + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe);
+        const size_t parts_bytes = redo_bytes + (p.order ? sizeof(uint32_t) * (p.nbins + Q * kIvfMaxProbe) : 0) + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe);
         const size_t slices_bytes = sizeof(uint64_t) * Q * kFastSlices;
-        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 470 of 1024 and more)
+        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 322 of 1024 and more)
     }
     p.upd = r / 16 < 16 ? 16 : r / 16;                   // appends to one slice between bound updates
     p.sortcap = next_pow2(2 * r) < kSortLdsKeys ? kSortLdsKeys : next_pow2(2 * r);
@@ -1347,7 +1352,7 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
                     static_cast<uint32_t>(nprobe), offsets, static_cast<uint32_t>(nlist), bins, p.nbins, rank, part_of, items);
         DCPQ_CHECK_LAUNCH("ivf_parts_kernel");
     }
-    const dim3 grid(kIvfUnitsPerQuery / 4, nq < kIvfRedoRows ? nq : kIvfRedoRows);
+    const dim3 grid(kIvfUnitsPerQuery / 4, static_cast<uint32_t>(p.redo_rows));
     const size_t lds_tab = 4 * M * 256;
     uint32_t *shist = reinterpret_cast<uint32_t *>(base + p.off_shist);
     uint32_t *fcount = reinterpret_cast<uint32_t *>(base + p.off_fcount);
@@ -1383,12 +1388,12 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
                             reinterpret_cast<int *>(base + p.off_qlist), nflag);
     if (rc) return rc;
     // the queries it flagged (a full slice, or fewer than r codes in the probed lists): three passes
-    uint32_t *redo_done = nflag + 1;
+    uint32_t *redo_done = reinterpret_cast<uint32_t *>(base + p.off_redo);
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfHist, CodeT>), grid, dim3(256), lds_tab + 4 * 256 * 4, codes, units,
                 nunits, qtab, nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<hist>");
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfTieCount, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done + kIvfRedoRows);
+                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done + kIvfRedoLine * p.redo_rows);
     DCPQ_CHECK_LAUNCH("ivf_scan_kernel<tiecount>");
     DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfCollect, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
                 nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, nullptr);
