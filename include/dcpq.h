@@ -395,7 +395,8 @@ int dcpq_ivf_scan_candidates_packed(const uint8_t *plane, const int64_t *offsets
  * distance +inf.
  *   ids : uint32_t [nq][k]  dist : float [nq][k] (outputs)
  *   workspace : dcpq_ivf_refine_workspace_bytes(nq, r) (may be 0); with 8 nq r bytes, up to a multiple of 256, and
- *               dcpq_refine_workspace_bytes(nq, r) behind them it takes a faster form (same results) */
+ *               dcpq_refine_workspace_bytes(nq, r) behind them (dcpq_ivf_search has that room) it takes a faster form where r is
+ *               above 256, or above 128 with up to 64 queries (same results) */
 size_t dcpq_ivf_refine_workspace_bytes(int nq, uint32_t r);
 int dcpq_ivf_refine_topk(const float *queries, const float *coarse, int nlist, const float *codebooks, int m,
                          int dsub, const uint16_t *codes, const int64_t *offsets, const int32_t *probe,

@@ -1628,11 +1628,14 @@ extern "C" int dcpq_ivf_refine_topk(const float *queries, const float *coarse, i
     hipStream_t st = as_stream(stream);
     // With room for the keys: distances by as many workgroups as it takes, then the selection of the flat search.  Whole searches
     // against a workgroup per query that sorts as well, in us (20 M codes in 8192 lists, 32 probed): r = 1000, 1 query 88 and 119,
-    // 64 queries 174 and 209, 1024 queries 820 and 900; r = 4000: 117 and 323, 262 and 440, 1726 and 2184.
+    // 64 queries 174 and 209, 1024 queries 820 and 900; r = 4000: 117 and 323, 262 and 440, 1726 and 2184.  Not where the workgroup has few
+    // keys to sort: the refinement alone, m = 8, r = 100: 12.5 and 10.8 (1 query), 46.7 and 43.7 (1024); r = 50: 33 and 27 (1024); r = 200: 12.9
+    // and 15.2, but with m = 4 and 2000 queries 147 and 126; r = 400: 13 and 23, 208 and 236.
     const size_t key_bytes = align_up(sizeof(uint64_t) * static_cast<size_t>(nq) * r, 256);
     // (within the limits of a grid: 65535 queries along y, 2^32 threads along x)
     const bool fits = nq <= 65535 && static_cast<uint64_t>(r) * m <= 0xFFFFF000ull;
-    if (fits && workspace && workspace_bytes >= key_bytes + dcpq_refine_workspace_bytes(nq, r) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
+    const bool spread = r > 256 || (r > 128 && nq <= 64);
+    if (fits && spread && workspace && workspace_bytes >= key_bytes + dcpq_refine_workspace_bytes(nq, r) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
         uint64_t *keys = static_cast<uint64_t *>(workspace);
         switch (m) {
 #define DCPQ_IVF_KEYS(MV)                                                                                                     \

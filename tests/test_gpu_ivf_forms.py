@@ -53,9 +53,12 @@ def test_search_equals_its_steps(kind, m, dsub, n, nq, nlist, nprobe, r, k):
         assert torch.equal(got, want)
 
 
-@pytest.mark.parametrize("nq", [3, 65_535, 65_536, 70_001])      # more queries than a grid takes along y: a workgroup per query
-def test_refinement_of_very_many_queries(nq):
-    m, dsub, nlist, nprobe, r, k = 4, 4, 16, 2, 8, 3
+@pytest.mark.parametrize("nq,r,dsub", [
+    (3, 128, 4), (3, 129, 3), (64, 256, 4), (65, 256, 4), (65, 257, 4),      # the sizes from which the keys are worked out on their own
+    (65_535, 300, 4), (65_536, 300, 4), (70_001, 300, 3),                    # more queries than a grid takes along y
+])
+def test_refinement_with_and_without_room_for_the_keys(nq, r, dsub):
+    m, nlist, nprobe, k = 4, 16, 2, 3
     cb, coarse, codes, offsets, queries = _case("random", m, dsub, 5_003, nq, nlist, 5)
     g = torch.Generator(device=DEV)
     g.manual_seed(nq)
