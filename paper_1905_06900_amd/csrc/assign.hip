@@ -44,7 +44,9 @@ template <int KS, int P, bool SPLIT>
 struct AssignCfg {
     static constexpr int RS = KS <= 6 ? 128 : 64;              // centroids per stage
     static constexpr int AHEAD = KS * P <= 12 ? 2 : 1;              // operand sets of a tile (2: read one tile ahead)
-    static constexpr int LAG = AHEAD == 2 && P == 4 ? 2 : 1;       // steps from a product to its minimum (registers for LAG + 1 results)
+    // steps from a product to its minimum (registers for LAG + 1 results; at KS = 1 those of a third would leave room for two wavefronts
+    // per SIMD instead of three: 140000 points, 2 sub-quantizers of 4 components, 256 centroids 97 us so, 63 with LAG = 1)
+    static constexpr int LAG = AHEAD == 2 && P == 4 && KS > 1 ? 2 : 1;
     static constexpr int TPC = SPLIT ? 1 : RS / 32;            // tiles of 32 centroids per cell
     static constexpr int TPR = 256 / RS;                       // threads that convert one centroid
     static constexpr int DPMAX = 16 * KS / 3 & ~3;             // largest padded sub-vector length
@@ -107,8 +109,10 @@ __device__ inline void store_label(void *labels, int label_bytes, size_t o, uint
 
 // Nearest centroid of the j-th sub-vector of every point, j = blockIdx.y.  points: rows of `ld` floats;
 // sub-vector j starts at column j * dsub.  labels: [n][m].  dist (optional): [n][m] fp32 squared distance.
-// dp: dsub rounded up to a multiple of 4, 3 dp <= 16 KS (4 dp <= 16 KS: all four products, half the filter's error).
-template <int KS, int P, bool SPLIT>
+// dp: dsub rounded up to a multiple of 4, 3 dp <= 16 KS (4 dp <= 16 KS: all four products, half the filter's error).  FOURS: dsub is
+// one (a kernel of its own: with both ways of reading the centroids in one, the compiler moved the load that they share before the
+// branch and waited for it before the products; 300 points, 65536 centroids of 3 components: 0.30 ms so and 0.26 apart; of 8 0.38 and 0.28, of 21 0.73 and 0.64, of 32 0.75 and 0.52).
+template <int KS, int P, bool SPLIT, bool FOURS>
 __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
                                                      const float *__restrict__ cb, int m, int dsub, int dp, int ncent,
                                                      void *__restrict__ labels, int label_bytes, float *__restrict__ dist)
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     auto load_stage = [&](int c0) {
         const int c = c0 + srow;
         const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
-        if (dp == dsub) {
+        if constexpr (FOURS) {
 #pragma unroll
             for (int g = 0; g < C::NG; ++g) {
                 const int o = 4 * (spart + C::TPR * g);
@@ -220,17 +224,12 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                 for (int e = 0; e < 4; ++e) pre[g][e] = v.v[e];
             }
         } else {
-            // (of both paths' loads the compiler would move the first, which they share, before the branch, copy it behind the loads
-            // of this stage and so wait for all of them before the products they are to run beside)
-            int same = 0;
-            asm volatile("" : "+v"(same));
 #pragma unroll
             for (int g = 0; g < C::NG; ++g)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int o = 4 * (spart + C::TPR * g) + e;
-                    const float v = src[same + (o < dsub ? o : 0)];
-                    pre[g][e] = o < dsub ? v : 0.0f;                  // (mu is zero there)
+                    pre[g][e] = src[o < dsub ? o : 0];               // (past the last: set to zero when the stage is stored, not waited for here)
                 }
         }
     };
@@ -241,6 +240,13 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         uint8_t *row = buf + srow * C::STRIDE;
         float norm = 0.0f;
         bool low = false;
+        if constexpr (!FOURS) {                                      // (mu is zero there)
+#pragma unroll
+            for (int g = 0; g < C::NG; ++g)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * (spart + C::TPR * g) + e >= dsub) pre[g][e] = 0.0f;
+        }
 #pragma unroll
         for (int g = 0; g < C::NG; ++g) {
             const int o = 4 * (spart + C::TPR * g);
@@ -828,18 +834,26 @@ __global__ __launch_bounds__(256, 2) void assign_f64_kernel(const float *__restr
     }
 }
 
+template <int KS, int P, bool SPLIT, bool FOURS>
+static int launch_assign_f(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                           void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    using C = AssignCfg<KS, P, SPLIT>;
+    const auto kernel = &assign_kernel<KS, P, SPLIT, FOURS>;
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
+    if (arc) return arc;
+    DCPQ_LAUNCH(kStageTrain, st, (assign_kernel<KS, P, SPLIT, FOURS>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
+                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
+    DCPQ_CHECK_LAUNCH("assign_kernel");
+    return DCPQ_OK;
+}
+
 template <int KS, int P, bool SPLIT>
 static int launch_assign_t(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
                            void *labels, int label_bytes, float *dist, hipStream_t st)
 {
-    using C = AssignCfg<KS, P, SPLIT>;
-    const auto kernel = &assign_kernel<KS, P, SPLIT>;
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
-    if (arc) return arc;
-    DCPQ_LAUNCH(kStageTrain, st, (assign_kernel<KS, P, SPLIT>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
-                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
-    DCPQ_CHECK_LAUNCH("assign_kernel");
-    return DCPQ_OK;
+    if (dp == dsub) return launch_assign_f<KS, P, SPLIT, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    return launch_assign_f<KS, P, SPLIT, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
 }
 
 template <int KS>
