@@ -271,6 +271,19 @@ def test_same_size_kmeans_against_the_oracle(n, d, kbar, iters):
     np.testing.assert_allclose(cent, rc, rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("n,kbar", [(6, 2), (63, 9), (64, 1), (65, 13), (130, 2), (1000, 250), (4290, 10)])
+def test_same_size_kmeans_of_few_points_against_the_oracle(n, kbar):
+    # numbers of points around the 64 that propose together, down to one group; most around a few places, so that groups turn points away
+    print("same-size k-means of few, n=%d kbar=%d" % (n, kbar), flush=True)
+    g = gen(31 * n + kbar)
+    p = (4.0 * torch.randint(0, 3, (n, 3), generator=g, device=DEV) + torch.randn((n, 3), generator=g, device=DEV)).contiguous()
+    cent, labels = binding.kmeans_same_size(p, p[:kbar].clone(), 1)
+    torch.cuda.synchronize()
+    rc, rl = oracle.kmeans_same_size(to_np(p), to_np(p[:kbar]), 1)
+    np.testing.assert_array_equal(to_np(labels), rl.astype(np.int32))
+    np.testing.assert_allclose(to_np(cent), rc, rtol=1e-5, atol=1e-6)
+
+
 @pytest.mark.parametrize("n,kbar", [(4096, 64), (65536, 256), (65536, 16), (65536, 2)])
 def test_same_size_kmeans_where_every_group_has_room_for_its_proposers(n, kbar):
     # groups of 64 to 32768 points apart from each other: every proposer is accepted at once, unsorted, by one to all wavefronts of
