@@ -40,7 +40,7 @@ enum ScanMode { kHist = 0, kTieCount = 1, kCollect = 2 };
 // The short step that follows a histogram or a tie count is done by the workgroup that finishes a query tile last
 // (done: one counter per tile, at zero on entry), which saves a launch of its own (4.5 us each on a stream of
 // short kernels):
-//   sample histogram   starting bounds (starting_bound, with want_r, want_n and limit)
+//   sample histogram   starting bounds (starting_bound, with want_r, want_n and crowded)
 //   histogram          thr = (bucket of the r-th smallest, ids still needed from it)
 //   tie count          counts of the bucket per unit -> quotas per unit, in place
 struct TileEnd {
@@ -49,7 +49,7 @@ struct TileEnd {
     uint32_t *thr;
     uint32_t want_r;
     uint64_t want_n;
-    bool limit;
+    Crowded crowded;
     bool guess;             // a guess below the bound is asked for too
 };
 
@@ -183,8 +183,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
                 if (MODE == kHist) {
                     for (int q = wave; q < nqt; q += kScanWaves) {
                         const uint32_t *h = hist + static_cast<size_t>(q0 + q) * 256;
-                        if (end_of.bound && end_of.guess) starting_bound<true>(h, end_of.want_r, end_of.want_n, end_of.limit, end_of.bound + q0 + q);
-                        else if (end_of.bound) starting_bound<false>(h, end_of.want_r, end_of.want_n, end_of.limit, end_of.bound + q0 + q);
+                        if (end_of.bound && end_of.guess) starting_bound<true>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
+                        else if (end_of.bound) starting_bound<false>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
                         else exact_threshold(h, r, end_of.thr + 2 * (q0 + q));
                     }
                 } else {
@@ -407,12 +407,14 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t
         if (s_codes < 65536) s_codes = 65536;
         // With a pilot pass (below; worth its three extra launches when the histogram of the sample would take more
         // than 30 to 40 microseconds: searches of 300 queries over 1e7 codes 607 us without and 577 with it, 600 over 2e7 1179 and
-        // 1134, 400 over 1e7 8-bit codes 668 and 631; not at m = 4, where so many codes tie that the pilot has most of its sample to
-        // count: 1000 queries over 4e6 skewed codes 798 without it) the sample costs several times less per code, and is taken twice as large where it holds
+        // 1134, 440 over 1e6 247 and 225; m = 16 at 1.6e8 and 2.3e8 of the product below, 150 and 220 queries over 1e6 codes: 178 and 184, 196 and
+        // 190; m = 32 at 1.6e8 and 3.1e8, 77 and 148 queries: 234 and 242, 324 and 341; at m = 4 so many codes tie: 1000 queries over
+        // 4e6 skewed codes 798 without it) the sample costs several times less per code, and is taken twice as large where it holds
         // few of the wanted codes (measured at N = 1e8, r = 4000, 4096 queries: sample and
         // scan together 41.25, 40.93, 40.72, 40.90 ms with 1, 2, 4, 8 times the sample; at N = 1e7, r = 5000
         // the larger sample costs what it saves).
-        const bool want_pilot = s_codes * Q * static_cast<uint64_t>(m) >= (m >= 8 ? 150000000ull : 330000000ull);
+        const uint64_t pilot_from = m == 8 ? 150000000ull : m == 16 ? 220000000ull : 330000000ull;
+        const bool want_pilot = s_codes * Q * static_cast<uint64_t>(m) >= pilot_from;
         if (want_pilot && s_codes < 32 * (n_codes / r)) s_codes *= 2;
         if (s_codes > n_codes) s_codes = n_codes;
         p.s_unit = 256;
@@ -553,16 +555,16 @@ static int launch_sample_hist_m(const CodeT *codes, uint64_t n_codes, const uint
     return DCPQ_OK;
 }
 
-// want_r, want_n, limit: rank wanted, size of the array the sample stands for, whether ties may be limited by id (see starting_bound)
+// want_r, want_n, crowded: rank wanted, size of the array the sample stands for, what becomes of crowded buckets (see starting_bound)
 template <typename CodeT>
 int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r,
-                       uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit, bool guess, Bound *bound,
+                       uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, Crowded crowded, bool guess, Bound *bound,
                        uint32_t *done, hipStream_t st)
 {
     TileEnd e{};
     e.done = done;
     e.bound = bound;
-    e.limit = limit;
+    e.crowded = crowded;
     e.guess = guess;
     e.want_r = want_r;
     e.want_n = want_n;
@@ -576,9 +578,9 @@ int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_
 }
 
 template int launch_sample_hist<uint16_t>(const uint16_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *,
-                                          const ScanPlan &, uint32_t, uint64_t, bool, bool, Bound *, uint32_t *, hipStream_t);
+                                          const ScanPlan &, uint32_t, uint64_t, Crowded, bool, Bound *, uint32_t *, hipStream_t);
 template int launch_sample_hist<uint8_t>(const uint8_t *, uint64_t, int, const uint8_t *, int, uint32_t, uint32_t *,
-                                         const ScanPlan &, uint32_t, uint64_t, bool, bool, Bound *, uint32_t *, hipStream_t);
+                                         const ScanPlan &, uint32_t, uint64_t, Crowded, bool, Bound *, uint32_t *, hipStream_t);
 
 template <int M, typename CodeT>
 static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,

@@ -31,6 +31,10 @@ struct __attribute__((aligned(16))) Bound {
     int guess;          // t, or a lower bucket that is more likely than not to do (see starting_bound)
 };
 
+// What becomes of a query whose starting bucket holds many more codes than are wanted, or is about to
+// have its codes counted one by one (see starting_bound).
+enum Crowded { kCrowdedLimit, kCrowdedSkip, kCountBelow };
+
 struct ScanPlan {
     // three-pass path
     uint32_t unit;        // codes scanned by one wavefront
@@ -89,7 +93,7 @@ size_t fast_table_bytes(int m, int qt);
 // CodeT: uint16_t (the codes as stored) or uint8_t (their low-byte plane); both are instantiated.
 template <typename CodeT>
 int launch_sample_hist(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
-                       uint32_t r, uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, bool limit,
+                       uint32_t r, uint32_t *shist, const ScanPlan &p, uint32_t want_r, uint64_t want_n, Crowded crowded,
                        bool guess, Bound *bound, uint32_t *done, hipStream_t st);
 template <typename CodeT>
 int launch_scan_fast(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
@@ -100,10 +104,7 @@ template <typename CodeT>
 int launch_scan_cells(const CodeT *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq, uint32_t r, const CellsArea &area, const Bound *bound,
                       uint32_t nslices, uint32_t cap, uint32_t *fcount, uint32_t *chist, uint64_t *keys, const uint32_t **used, hipStream_t st);
 
-// Steps of the single-pass selection that the inverted-list variant reuses.
-// n_codes: size of the array the sample was drawn from (the sample's own size is the histogram's total)
-int launch_sample_threshold(const uint32_t *shist, int nq, uint32_t r, uint64_t n_codes, uint32_t guess_r, uint64_t sample, uint32_t want_r,
-                            Bound *bound, hipStream_t st);
+// The selection from what the single-pass scans have appended, for the inverted lists too.
 // n_ids: the ids are below this (0 = unknown); qlist, nflag (optional): the flagged queries, in any order, and their number
 int launch_fast_select(const uint64_t *keys, const uint32_t *count, const uint32_t *chist, int nq, uint32_t r,
                        uint32_t nslices, uint32_t cap, uint32_t sortcap, uint64_t n_ids, uint64_t *spill, uint32_t *cand_id,
@@ -151,11 +152,14 @@ __device__ inline void load_low_bytes(const uint16_t *__restrict__ codes, uint64
 
 // Inclusive prefix sums of 256 bucket counts over a wavefront, lane l owning buckets 4l .. 4l + 3: c becomes
 // the counts, cum the inclusive prefixes.  The counts may just have been added by other workgroups' atomics.
-__device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c)[4], uint32_t (&cum)[4])
+__device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c)[4], uint32_t (&cum)[4], int more_in = -1, uint32_t more = 0)
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int z = 0; z < 4; ++z) c[z] = __hip_atomic_load(&hist[4 * lane + z], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+        if (4 * lane + z == more_in) c[z] += more;
     const uint32_t mine = c[0] + c[1] + c[2] + c[3];
     uint32_t incl = mine;
 #pragma unroll
@@ -233,17 +237,19 @@ __device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need)
 // over the array).  Where no order of the ids is known and more than `room` would be (kCrowdedSkip), the bound starts one
 // bucket lower if that is likely to do (a standard deviation above the mean instead of five), and otherwise below all
 // buckets, which flags the query.
-// (n = 0, with exact counts of a sample: r is its rank already; `all` codes, `scale` times the sample, of which all_r are wanted.)
+// Before a pilot pass, which counts what is within its bound one by one, the bound is the bucket below (kCountBelow), and t0 the crowded
+// bucket: that one is known to do, and how many codes it holds the histogram says well enough.
+// (n = 0, with exact counts of a sample, and `more` in bucket more_in: r is its rank already; `all` codes, `scale` times the sample,
+// of which all_r are wanted.)
 // bound->guess: the same with two standard deviations (of rank guess_r where that is given), for a scan that can look again
 // at the queries for which it is too low.
-enum Crowded { kCrowdedAppend = 0, kCrowdedLimit = 1, kCrowdedSkip = 2 };
 template <bool GUESS = true>
-__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, int crowded, Bound *bound, float room = 0.0f, uint32_t guess_r = 0,
-                                      uint64_t all = 0, float scale = 0.0f, uint32_t all_r = 0)
+__device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_t n, Crowded crowded, Bound *bound, float room = 0.0f, uint32_t guess_r = 0,
+                                      uint64_t all = 0, float scale = 0.0f, uint32_t all_r = 0, int more_in = -1, uint32_t more = 0)
 {
     const int lane = threadIdx.x & 63;
     uint32_t c[4], cum[4];
-    wave_prefix_of_buckets(shist, c, cum);
+    wave_prefix_of_buckets(shist, c, cum, more_in, more);
     const uint32_t total = __shfl(cum[3], 63);
     uint32_t rs = r;
     float e = 0.0f;
@@ -278,10 +284,11 @@ __device__ inline void starting_bound(const uint32_t *shist, uint32_t r, uint64_
                 const float upto = 2.0f * static_cast<float>(all) * static_cast<float>(rs - before) / static_cast<float>(c[z]);
                 if (upto < 4294967040.0f) last = static_cast<uint32_t>(upto);
             }
-            *bound = Bound{t, last == 0xFFFFFFFFu ? 256u : static_cast<uint32_t>(4 * lane + z), last, guess};
+            if (crowded == kCountBelow && expect > 16.0f * static_cast<float>(all_r)) *bound = Bound{t - 1, static_cast<uint32_t>(t), last, guess};
+            else *bound = Bound{t, last == 0xFFFFFFFFu ? 256u : static_cast<uint32_t>(4 * lane + z), last, guess};
         }
     }
-    if (lane == 63 && total < rs) *bound = Bound{255, 255u, 0xFFFFFFFFu, 255};
+    if (lane == 63 && total < rs) *bound = Bound{255, 256u, 0xFFFFFFFFu, 255};
 }
 
 // Lowers query q's bucket bound to the bucket that holds its r-th best appended candidate (nothing
