@@ -97,7 +97,7 @@ struct CellsArea {
     const float *derived;    // [m][2^small_bits][dsub]
     int dsub, small_bits;
 };
-bool cells_may_pay(uint64_t n_codes, int m, int nq);
+bool cells_may_pay(uint64_t n_codes, int m, int nq, uint32_t r);
 size_t cells_bytes(uint64_t n_codes, int m, int nq);
 int launch_scan(const uint16_t *codes, uint64_t n_codes, int m, const uint8_t *qtab, int nq,
                 uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, void *ws, size_t room, int mode, bool cleared, hipStream_t st,

@@ -42,20 +42,31 @@ struct CellsCtl {
 // ---- groups of near derived centroids --------------------------------------------------------------
 // One workgroup per sub-quantizer, four threads per derived centroid: 16 seeds, each the centroid farthest from those before
 // it, then one round of {mean, nearest mean}.  Whatever the split, the bounds taken from it hold; it only decides how tight
-// they are.  A chain of short steps: the rows lie in LDS, 16 bytes a read, at an odd number of 16-byte units
-// (52 us for dsub = 16 with a thread per centroid and single floats, two rounds).  Workgroups m and above clear the counters of the call.
+// they are.  A chain of short steps: the rows lie in LDS, 16 bytes a read, at an odd number of 16-byte units, and a step is a
+// reduction without the LDS inside a wavefront and one atomic for each of these (dsub = 16: 18 us; 26 with shuffles of 64-bit keys through the
+// LDS, 52 with a thread per centroid and single floats, two rounds).  Workgroups m and above clear the counters of the call.
 __host__ __device__ inline int group_pitch(int dsub) { return ((dsub + 3) / 4 | 1) * 4; }      // floats
+// v of the lane that is N lanes on, around the row of 16; of the lane whose number differs in the bits of X, within four.
+template <int N>
+__device__ inline uint32_t around_row(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xF, 0xF, true); }
+template <int X>
+__device__ inline float within_four(float v)
+{
+    constexpr int perm = (0 ^ X) | (1 ^ X) << 2 | (2 ^ X) << 4 | (3 ^ X) << 6;
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), perm, 0xF, 0xF, true));
+}
+
 __global__ __launch_bounds__(1024) void cells_group_kernel(const float *__restrict__ derived, int m, int dsub, int small_bits,
                                                            uint8_t *__restrict__ map, uint32_t *__restrict__ clear, uint32_t nclear)
 {
     const int tid = threadIdx.x;
     if (static_cast<int>(blockIdx.x) >= m) {
         const uint32_t nb = gridDim.x - m;
-        for (uint32_t t = (blockIdx.x - m) * 1024 + tid; t < nclear; t += nb * 1024) clear[t] = 0;
+        for (uint32_t t = (blockIdx.x - m) * 1024 + tid; t < nclear / 4; t += nb * 1024) reinterpret_cast<uint4 *>(clear)[t] = make_uint4(0, 0, 0, 0);
         return;
     }
     extern __shared__ __align__(16) float group_lds[];
-    __shared__ unsigned long long far[kGroupsPerSub];            // the centroid farthest from its seed: distance, 255 - number
+    __shared__ uint32_t far[kGroupsPerSub];                      // the centroid farthest from its seed: distance (24 bits), 255 - number
     __shared__ int cnt[kGroupsPerSub];
     const int j = blockIdx.x, ks = 1 << small_bits, pitch = group_pitch(dsub), nv = (dsub + 3) / 4;
     float *rows = group_lds, *mean = group_lds + ks * pitch;                 // [ks][pitch], [16][pitch]
@@ -75,20 +86,20 @@ __global__ __launch_bounds__(1024) void cells_group_kernel(const float *__restri
             const float4 a = row[v], b = c[v];
             s += (a.x - b.x) * (a.x - b.x) + (a.y - b.y) * (a.y - b.y) + (a.z - b.z) * (a.z - b.z) + (a.w - b.w) * (a.w - b.w);
         }
-        s += __shfl_xor(s, 1);
-        return s + __shfl_xor(s, 2);
+        s += within_four<1>(s);
+        return s + within_four<2>(s);
     };
     float best = 3.0e38f;
     int label = 0, seed = 0;                                     // (the first seed: centroid 0)
     for (int g = 0; g < kGroupsPerSub; ++g) {
         const float s = distance(rows + seed * pitch);
         if (s < best) { best = s; label = g; }
-        unsigned long long key = static_cast<unsigned long long>(__float_as_uint(best)) << 32 | static_cast<uint32_t>(255 - e);
-        for (int off = 4; off < 64; off <<= 1) {
-            const unsigned long long o = __shfl_xor(key, off);
-            key = o > key ? o : key;
-        }
-        if ((tid & 63) == 0) atomicMax(&far[g], key);
+        uint32_t key = (__float_as_uint(best) & ~255u) | static_cast<uint32_t>(255 - e);       // (distances are >= +0: they order like their bits)
+        key = max(key, around_row<4>(key));
+        key = max(key, around_row<8>(key));
+        const uint32_t farthest = max(max(__builtin_amdgcn_readlane(key, 0), __builtin_amdgcn_readlane(key, 16)),
+                                      max(__builtin_amdgcn_readlane(key, 32), __builtin_amdgcn_readlane(key, 48)));
+        if ((tid & 63) == 0) atomicMax(&far[g], farthest);
         __syncthreads();
         seed = 255 - static_cast<int>(far[g] & 255u);
     }
@@ -394,14 +405,32 @@ struct CellCfg {
 };
 
 template <typename CodeT>
-__global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
-    const CodeT *__restrict__ codes, const uint8_t *__restrict__ qtab, const uint8_t *__restrict__ map, const uint32_t *__restrict__ offs,
-    const uint64_t *__restrict__ filled, const uint16_t *__restrict__ rem16, const uint32_t *__restrict__ ids, const Bound *__restrict__ bound,
-    uint32_t r, uint32_t parts, uint32_t nslices, uint32_t cap, uint32_t most_hits, uint32_t *__restrict__ fcount, uint32_t *__restrict__ chist,
-    uint64_t *__restrict__ keys, uint32_t *__restrict__ first_counts, int again, const CellsCtl *__restrict__ ctl)
+struct CellScan {
+    const CodeT *codes;
+    const uint8_t *qtab, *map;
+    const uint32_t *offs;
+    const uint64_t *filled;
+    const uint16_t *rem16;
+    const uint32_t *ids;
+    const Bound *bound;
+    uint32_t r, parts, nslices, cap, most_hits;
+    uint32_t *fcount, *chist;
+    uint64_t *keys;
+    uint32_t *first_counts;
+    const CellsCtl *ctl;
+};
+
+// One part of a query's cells, by a workgroup.  AGAIN: the second time, what lies between the guessed bucket and the bound.
+template <typename CodeT, bool AGAIN>
+__device__ __forceinline__ void scan_part_of_cells(const CellScan<CodeT> &a, uint32_t pair)
 {
-    if (!ctl->use) return;
     using C = CellCfg;
+    const CodeT *__restrict__ codes = a.codes;
+    const uint32_t *__restrict__ offs = a.offs, *__restrict__ ids = a.ids;
+    const uint16_t *__restrict__ rem16 = a.rem16;
+    const uint32_t r = a.r, parts = a.parts, nslices = a.nslices, cap = a.cap;
+    uint32_t *__restrict__ fcount = a.fcount;
+    uint64_t *__restrict__ keys = a.keys;
     extern __shared__ __align__(16) uint8_t smem[];
     struct Vars {
         int t;
@@ -418,31 +447,27 @@ __global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
     uint32_t *cellq = reinterpret_cast<uint32_t *>(smem + C::O_CELL), *hitq = reinterpret_cast<uint32_t *>(smem + C::O_HIT);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t q = blockIdx.x / parts, part = blockIdx.x % parts;
+    const uint32_t q = pair / parts, part = pair % parts;
 
-    const Bound bd = bound[q];
+    const Bound bd = a.bound[q];
     if (bd.t >= 255) {                                           // no bound: the redo path takes the query
         if (tid == 0 && part == 0) fcount[static_cast<size_t>(q) * nslices] = cap + 1;
         return;
     }
     // candidates are the codes with above < qd <= T: up to the guessed bucket at first, the rest of those up to the bound the
-    // second time, for queries with fewer than r so far
-    int T = min(bd.guess, bd.t), above = -1;
-    if (again) {
-        if (first_counts[q] >= r || T >= bd.t) return;           // uniform
-        above = T;
-        T = bd.t;
-    }
+    // second time
+    int T = AGAIN ? bd.t : min(bd.guess, bd.t);
+    const int above = AGAIN ? bd.guess : -1;
     const int first_t = T;
     for (int t = tid; t < kM * 64; t += C::THREADS)
-        reinterpret_cast<uint32_t *>(qt)[t] = reinterpret_cast<const uint32_t *>(qtab + static_cast<size_t>(q) * (kM * 256))[t];
+        reinterpret_cast<uint32_t *>(qt)[t] = reinterpret_cast<const uint32_t *>(a.qtab + static_cast<size_t>(q) * (kM * 256))[t];
     if (tid < 256) hist[tid] = 0;
     if (tid == 0) {
         sh.t = T;
         sh.next = sh.ncell = sh.celltaken = sh.nshort = sh.nlong = sh.codes = sh.total = sh.hits = sh.nhit = sh.paused = sh.nlist = 0;
     }
     __syncthreads();
-    group_minima(qt, map, G);
+    group_minima(qt, a.map, G);
     // sums of three nibbles' entries, capped at 127 (a lower bound still)
     for (int t = tid; t < 4096; t += C::THREADS)
         tab[t] = static_cast<uint8_t>(min(127u, G[5 * 16 + (t >> 8)] + G[6 * 16 + ((t >> 4) & 15)] + G[7 * 16 + (t & 15)]));
@@ -492,11 +517,12 @@ __global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
     auto load8 = [&](uint32_t at, bool live) __attribute__((always_inline)) {
         return *reinterpret_cast<const uint4 *>(rem16 + (live ? at : 0u));
     };
-    uint32_t sl = (blockIdx.x + static_cast<uint32_t>(wave)) % nslices;      // slice of this wavefront's next append
+    uint32_t sl = (pair + static_cast<uint32_t>(wave)) % nslices;      // slice of this wavefront's next append
 
+    const uint64_t *__restrict__ filled = a.filled;
     // counts per bucket: in LDS, and where several workgroups work on a query added to those in memory after every settling
     const bool shared_hist = parts > 1;
-    uint32_t *counts = chist + static_cast<size_t>(q) * 256;
+    uint32_t *counts = a.chist + static_cast<size_t>(q) * 256;
     // the first n entries of the second queue, by all threads: their integer distances, and those within the bound to the query's buffer
     auto settle = [&](uint32_t n) __attribute__((always_inline)) {
         constexpr int PER = C::HITS / C::THREADS;
@@ -547,16 +573,16 @@ __global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
             if (lane == 0) u = atomicAdd(&sh.next, 1u);
             u = __builtin_amdgcn_readfirstlane(u);
             if (u >= 4 * nlist) break;
-            const uint32_t a = s_list[u >> 2], b = 64 * (u & 3u) + lane;
-            const uint64_t some = filled[4 * a + (u & 3u)];
-            const uint32_t s = G[a >> 4] + G[16 + (a & 15)] + G[32 + (b >> 4)] + G[48 + (b & 15)];
+            const uint32_t ab = s_list[u >> 2], b = 64 * (u & 3u) + lane;
+            const uint64_t some = filled[4 * ab + (u & 3u)];
+            const uint32_t s = G[ab >> 4] + G[16 + (ab & 15)] + G[32 + (b >> 4)] + G[48 + (b & 15)];
             const bool have = static_cast<int>(s) + rest4 <= T && (some >> lane & 1u);
             const uint64_t mask = __builtin_amdgcn_ballot_w64(have);
             if (!mask) continue;
             uint32_t to = 0;
             if (lane == 0) to = atomicAdd(&sh.ncell, static_cast<uint32_t>(__popcll(mask)));
             to = __builtin_amdgcn_readfirstlane(to);
-            if (have) cellq[to + rank_in(mask)] = s << 16 | a << 8 | b;
+            if (have) cellq[to + rank_in(mask)] = s << 16 | ab << 8 | b;
         }
         __syncthreads();
         // (2) the sixteen cells of five nibbles of each, a lane per cell
@@ -731,16 +757,41 @@ __global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
             }
             __syncthreads();
             T = static_cast<int>(uniform_load(reinterpret_cast<uint32_t *>(&sh.t)));
-            over = uniform_load(&sh.hits) > most_hits;
+            over = uniform_load(&sh.hits) > a.most_hits;
             if (!paused || over) break;
         }
         if (last) break;
     }
     if (tid == 0) {
-        if (!again) atomicAdd(&first_counts[q], sh.total);
+        if (!AGAIN) atomicAdd(&a.first_counts[q], sh.total);
         if (over) atomicMax(&fcount[static_cast<size_t>(q) * nslices], cap + 1);     // too many codes to look at: the redo path takes the query
     }
     if (tid < 256 && !shared_hist) counts[tid] += hist[tid];
+}
+
+template <typename CodeT>
+__global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(CellScan<CodeT> a)
+{
+    if (a.ctl->use) scan_part_of_cells<CodeT, false>(a, blockIdx.x);
+}
+
+// The second time, for the few queries that found fewer than r codes up to their guessed bucket: a workgroup looks at up to 64
+// (query, part) pairs, a lane at each, and works on those that are left (a workgroup for each pair took 23 us where none is,
+// 4096 queries; so 5).
+template <typename CodeT>
+__global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_again_kernel(CellScan<CodeT> a, uint32_t pairs)
+{
+    if (!a.ctl->use) return;
+    const uint32_t pair = blockIdx.x + (threadIdx.x & 63u) * gridDim.x;
+    bool left = false;
+    if (pair < pairs) {
+        const Bound b = a.bound[pair / a.parts];
+        left = b.t < 255 && b.guess < b.t && a.first_counts[pair / a.parts] < a.r;
+    }
+    for (uint64_t todo = __builtin_amdgcn_ballot_w64(left); todo; todo &= todo - 1) {      // uniform, and the same in all wavefronts
+        scan_part_of_cells<CodeT, true>(a, blockIdx.x + static_cast<uint32_t>(__builtin_ctzll(todo)) * gridDim.x);
+        __syncthreads();                                         // (the LDS is read no more)
+    }
 }
 
 // ---- host side ------------------------------------------------------------------------------------
@@ -778,9 +829,11 @@ static CellsPlan plan_cells(uint64_t n, int m, int nq)
 size_t cells_bytes(uint64_t n, int m, int nq) { return plan_cells(n, m, nq).total; }
 
 // (Fewer than 2^31 codes: a lane steps up to 1024 positions past the end of its stretch, and tiles are counted in 32 bits.)
-bool cells_may_pay(uint64_t n, int m, int nq)
+// (Nor where a query wants more than a thousandth of the codes: with 420 and 840 codes to each that is wanted the decision declined for every
+// kind of codebook and codes that it was tried on, at 1200 and 2100 it served some: 9.7 -> 4.5 ms and 1.65 -> 0.87.)
+bool cells_may_pay(uint64_t n, int m, int nq, uint32_t r)
 {
-    return m == 8 && n >= (4ull << 20) && n < (1ull << 31) && static_cast<double>(n) * nq >= 8.0e9;
+    return m == 8 && n >= (4ull << 20) && n < (1ull << 31) && static_cast<double>(n) * nq >= 8.0e9 && n >= 1000ull * r;
 }
 
 template <typename CodeT>
@@ -804,6 +857,7 @@ static int launch_cells(const CodeT *codes, uint64_t n_codes, const uint8_t *qta
     if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&cells_sort_kernel<false>), sort_lds);
     if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&cells_sort_kernel<true>), sort_lds);
     if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&scan_cells_kernel<CodeT>), CellCfg::BYTES, true);
+    if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&scan_cells_again_kernel<CodeT>), CellCfg::BYTES, true);
     if (rc) return rc;
     DCPQ_LAUNCH(kStageCellsSort, st, cells_group_kernel, dim3(kM + 64), dim3(1024), group_lds, area.derived, kM, area.dsub, area.small_bits, map,
                 words(0), static_cast<uint32_t>(p.clear_words));
@@ -833,12 +887,14 @@ static int launch_cells(const CodeT *codes, uint64_t n_codes, const uint8_t *qta
     while (parts * 2 * static_cast<uint32_t>(nq) <= 2048 && parts < 16) parts *= 2;
     const uint64_t hits = 64ull * r + n_codes / 64;
     const uint32_t most = static_cast<uint32_t>(hits > 0x7FFFFFFFull ? 0x7FFFFFFFull : hits);
-    for (int again = 0; again < 2; ++again) {
-        if (again && parts < 8) parts = 8;                       // few queries are left: more workgroups for each
-        DCPQ_LAUNCH(kStageScanCells, st, (scan_cells_kernel<CodeT>), dim3(nq * parts), dim3(CellCfg::THREADS), CellCfg::BYTES, codes, qtab,
-                    map, offs, filled, rem, words(p.off_ids), bound, r, parts, nslices, cap, most, fcount, chist, keys, words(p.off_first), again, ctl);
-        DCPQ_CHECK_LAUNCH("scan_cells_kernel");
-    }
+    CellScan<CodeT> scan{codes, qtab, map, offs, filled, rem, words(p.off_ids), bound, r, parts, nslices, cap, most, fcount, chist, keys,
+                         words(p.off_first), ctl};
+    DCPQ_LAUNCH(kStageScanCells, st, (scan_cells_kernel<CodeT>), dim3(nq * parts), dim3(CellCfg::THREADS), CellCfg::BYTES, scan);
+    DCPQ_CHECK_LAUNCH("scan_cells_kernel");
+    if (parts < 8) scan.parts = 8;                               // few queries are left: more workgroups for each
+    const uint32_t left = static_cast<uint32_t>(nq) * scan.parts, blocks = left <= 1024 ? left : left <= 65536 ? 1024u : (left + 63) / 64;
+    DCPQ_LAUNCH(kStageScanCells, st, (scan_cells_again_kernel<CodeT>), dim3(blocks), dim3(CellCfg::THREADS), CellCfg::BYTES, scan, left);
+    DCPQ_CHECK_LAUNCH("scan_cells_again_kernel");
     return DCPQ_OK;
 }
 

@@ -58,7 +58,7 @@ static SearchPlan plan_search(uint64_t n_codes, int m, int nq, uint32_t r, int f
     p.least = align_up(off + least_bytes, 256);
     p.total = align_up(off + scan_bytes, 256);
     // (not where the codes can be sorted into cells)
-    if (full_bits == 8 && pairs_pay(n_codes, m, chunk) && !(cells_may_pay(n_codes, m, chunk) && cells_bytes(n_codes, m, chunk) <= p.tables_bytes)) {
+    if (full_bits == 8 && pairs_pay(n_codes, m, chunk) && !(cells_may_pay(n_codes, m, chunk, r) && cells_bytes(n_codes, m, chunk) <= p.tables_bytes)) {
         size_t pair_bytes = dcpq_scan_workspace_bytes(n_codes, m / 2, chunk, r);
         if (tail) {
             const size_t st = dcpq_scan_workspace_bytes(n_codes, m / 2, tail, r);
@@ -236,7 +236,7 @@ extern "C" int dcpq_search_bits(const float *queries, int nq, const float *codeb
         if (rc) return rc;
         // (the table region is free until pass two: where the codes fit it, the scan may sort them there)
         const CellsArea area{base + p.off_tables, derived, dsub, bbar};
-        const CellsArea *cells = rows == codebooks && cells_may_pay(n_codes, m, nc) && cells_bytes(n_codes, m, nc) <= p.tables_bytes ? &area : nullptr;
+        const CellsArea *cells = rows == codebooks && cells_may_pay(n_codes, m, nc, r) && cells_bytes(n_codes, m, nc) <= p.tables_bytes ? &area : nullptr;
         // the quantized tables have 256 entries whatever bbar is, and 1-byte sub-codes are their own low-byte plane
         if (paired) {
             rc = launch_pair_tables(qtab, nc, m, ptab, st);

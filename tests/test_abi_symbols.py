@@ -121,12 +121,13 @@ def test_smallest_scan_workspace_fits_the_static_scratch(lib):
 def test_arrays_beyond_31_bit_positions_are_not_sorted_into_cells(lib):
     """The scan over cells holds positions of codes in 32 bits and steps past the end of a stretch, so the rule that takes a
     search there (dcpq::cells_may_pay) stops below 2^31 codes; dcpq_search itself takes fewer than 2^32."""
-    may = lib._ZN4dcpq13cells_may_payEmii
+    may = lib._ZN4dcpq13cells_may_payEmiij
     may.restype = ctypes.c_bool
-    may.argtypes = [ctypes.c_uint64, ctypes.c_int, ctypes.c_int]
+    may.argtypes = [ctypes.c_uint64, ctypes.c_int, ctypes.c_int, ctypes.c_uint32]
     for n in (1 << 31, (1 << 31) + 12345, (1 << 32) - 1):
-        assert not may(n, 8, 20_000)
-    assert may((1 << 31) - 1, 8, 20_000) and may(100_000_000, 8, 4096)
+        assert not may(n, 8, 20_000, 100)
+    assert may((1 << 31) - 1, 8, 20_000, 100) and may(100_000_000, 8, 4096, 4000)
+    assert may(10_000_000, 8, 1000, 10_000) and not may(9_999_999, 8, 1000, 10_000)      # a thousandth of the codes wanted
 
 
 @pytest.mark.parametrize("nq,r,was", [(1, 1, 165632), (1, 1000, 298496), (2, 100, 330496), (4, 30, 656384), (5, 1, 819200), (5, 5000, 7419136), (7, 20, 1146880), (31, 1, 5067264), (33, 400, 5499904), (1000, 1000, 296352768), (300, 20000, 1829635840)])
