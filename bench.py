@@ -133,10 +133,13 @@ def run_flat(w, args, steps, warmup, with_cpu, headline):
         else:
             roofline = hbm_roofline(dom, wbytes, dom_ms, dom_launches, steps, w.name, "table writes to HBM")
     elif dom == "scan_cells":
-        # lines of memory that the looked-up stretches and settled codes touch (counters; they depend on the data)
-        dom_launches = steps                                     # (the second launch serves a few per cent of the queries)
-        roofline = hbm_roofline(dom, committed_traffic(dom, w.name) or float(w.N * code_bytes), dom_ms, dom_launches, steps, w.name,
-                                "scattered reads of cells within the bounds; vector issue 75 %", {
+        # Algorithmic bytes as for the other scans, one reading of the codes a step, though most codes are not looked at.  What the
+        # kernel moves (traffic, from committed counters of requests below the L2) is for a good part served by the last-level cache, so it
+        # is no fraction of the memory's rate.  Figures per step: both launches, the second for the queries that are left.
+        roofline = hbm_roofline(dom, float(w.N * code_bytes), dom_ms, steps, steps, w.name,
+                                "lines that scattered stretches and settled codes touch, below the L2; vector issue 75 %", {
+                                    "per": "step", "launches_per_step": dom_launches / steps, "hbm_traffic_frac": None,
+                                    "traffic_is": "requests below the L2, last-level cache included",
                                     "pairs_per_s": round(w.N * w.Q / (scan_ms * 1e-3), 1) if scan_ms > 0 else None})
     elif dom == "refine_topk":
         # pass two: per candidate one code and m centroid rows (on demand) or m table entries

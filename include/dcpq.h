@@ -218,6 +218,8 @@ int dcpq_build_small_tables_bits(const float *queries, int nq, const float *deri
 int dcpq_refine_topk_bits(const float *tables, uint32_t n_entries, const void *codes, int code_bytes,
                           uint64_t n_codes, int m, const uint32_t *cand_id, int nq, uint32_t r, uint32_t k,
                           uint32_t *ids, float *dist, void *workspace, size_t workspace_bytes, void *stream);
+/* b = 8, m >= 8: from 100 queries and n_codes * nq = 5e8 on the size holds the plane of pairs, n_codes * m / 2 bytes, in which two
+ * neighbouring sub-codes are scanned as one where bbar <= 4; a search with a larger bbar leaves those bytes unused. */
 size_t dcpq_search_bits_workspace_bytes(uint64_t n_codes, int m, int nq, uint32_t r, int b, int chunk_queries);
 int dcpq_search_bits_chunk(int m, int nq, int b, int chunk_queries);
 /* refine_mode: how pass two gets its table entries (Sec. 3.3, Refine step: the entries of the full

@@ -327,7 +327,7 @@ __global__ __launch_bounds__(1024) void ivf_bounds_kept_kernel(const float *__re
     __shared__ float red[2][16];
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
     const int32_t *pq = probe + static_cast<size_t>(q) * nprobe;
-    // (list sizes of 64 lists at a time, by every wavefront alike; the first one writes)
+    // (list sizes of 64 lists at a time, by the first wavefront)
     if (wave == 0) {
         uint64_t before = 0;
         for (int p0 = 0; p0 < nprobe; p0 += 64) {

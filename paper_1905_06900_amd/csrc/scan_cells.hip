@@ -13,10 +13,13 @@
 //
 // Where the groups say little (codebooks without near centroids, a bound that most cells are within) this saves nothing:
 // cells_decide_kernel estimates both costs on a sample of the codes and sets the flag by which either these kernels or the
-// single-pass scan return at once (no host synchronization).  A batch that is not served pays about 60 us for that.
+// single-pass scan return at once (no host synchronization).  A batch that is not served pays 50 to 60 us for that.
 //
-// Measured, whole searches: N = 1e8, 4096 queries, r = 4000: 41.2 -> 8.6 ms (sorting 1.8, scan 5.1, pass two 1.5); N = 1e7 encoded
-// vectors, 1000 queries, r = 2000: 1.49 -> 0.73 ms (sorting 0.22, scan 0.19).
+// Measured, whole searches, on codebooks of 16 parents per sub-quantizer, which the groups meet: N = 1e8, 4096 queries,
+// r = 4000: 41.2 -> 8.6 ms (sorting 1.8, scan 4.4 to 5, pass two 1.5); N = 1e7 encoded vectors, 1000 queries, r = 2000: 1.49 -> 0.72 ms
+// (sorting 0.21, scan 0.20).  On quantizers trained by Alg. 2 it depends on the vectors: of a mixture of 1024 tight components in
+// 128 dimensions 1.2e7 codes, 4096 queries, r = 2000 7.1 -> 2.5 ms, 4.2e6 codes, 2000 queries 1.86 -> 1.55; of Gaussian vectors, Gaussian ones
+// with a decaying spectrum and normalised ones of 4096 wide components every batch was declined (6 % of 1.05 ms, 1 % of 6).
 #include "lds_access.h"
 #include "scan_internal.h"
 
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(1024) void cells_sort_kernel(const uint32_t *__rest
 // codes whose lower bound is within the bound go to a second queue; (4) when that is full, and at the end: id, code and
 // integer distance of the queued codes, four per thread, and those within the bound are appended to the query's buffer.
 // Bound by lines of memory: 1e8 codes, 4096 queries read 30 GB (stretches of 95 codes touch 2.5 lines, a settled code
-// another) in 4.9 ms, beside 75 % of the vector issue slots; three steps under way instead of one changed nothing, nor did
+// another) in 4.3 to 4.9 ms, beside 75 % of the vector issue slots; three steps under way instead of one changed nothing, nor did
 // stretches cut into equal units for every lane group (half of the instructions then went into finding the next unit).
 struct CellCfg {
     static constexpr int THREADS = 512, WAVES = THREADS / 64;
@@ -405,32 +408,14 @@ struct CellCfg {
 };
 
 template <typename CodeT>
-struct CellScan {
-    const CodeT *codes;
-    const uint8_t *qtab, *map;
-    const uint32_t *offs;
-    const uint64_t *filled;
-    const uint16_t *rem16;
-    const uint32_t *ids;
-    const Bound *bound;
-    uint32_t r, parts, nslices, cap, most_hits;
-    uint32_t *fcount, *chist;
-    uint64_t *keys;
-    uint32_t *first_counts;
-    const CellsCtl *ctl;
-};
-
-// One part of a query's cells, by a workgroup.  AGAIN: the second time, what lies between the guessed bucket and the bound.
-template <typename CodeT, bool AGAIN>
-__device__ __forceinline__ void scan_part_of_cells(const CellScan<CodeT> &a, uint32_t pair)
+__global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(
+    const CodeT *__restrict__ codes, const uint8_t *__restrict__ qtab, const uint8_t *__restrict__ map, const uint32_t *__restrict__ offs,
+    const uint64_t *__restrict__ filled, const uint16_t *__restrict__ rem16, const uint32_t *__restrict__ ids, const Bound *__restrict__ bound,
+    uint32_t r, uint32_t parts, uint32_t nslices, uint32_t cap, uint32_t most_hits, uint32_t *__restrict__ fcount, uint32_t *__restrict__ chist,
+    uint64_t *__restrict__ keys, uint32_t *__restrict__ first_counts, int again, const CellsCtl *__restrict__ ctl)
 {
+    if (!ctl->use) return;
     using C = CellCfg;
-    const CodeT *__restrict__ codes = a.codes;
-    const uint32_t *__restrict__ offs = a.offs, *__restrict__ ids = a.ids;
-    const uint16_t *__restrict__ rem16 = a.rem16;
-    const uint32_t r = a.r, parts = a.parts, nslices = a.nslices, cap = a.cap;
-    uint32_t *__restrict__ fcount = a.fcount;
-    uint64_t *__restrict__ keys = a.keys;
     extern __shared__ __align__(16) uint8_t smem[];
     struct Vars {
         int t;
@@ -447,27 +432,31 @@ __device__ __forceinline__ void scan_part_of_cells(const CellScan<CodeT> &a, uin
     uint32_t *cellq = reinterpret_cast<uint32_t *>(smem + C::O_CELL), *hitq = reinterpret_cast<uint32_t *>(smem + C::O_HIT);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t q = pair / parts, part = pair % parts;
+    const uint32_t q = blockIdx.x / parts, part = blockIdx.x % parts;
 
-    const Bound bd = a.bound[q];
+    const Bound bd = bound[q];
     if (bd.t >= 255) {                                           // no bound: the redo path takes the query
         if (tid == 0 && part == 0) fcount[static_cast<size_t>(q) * nslices] = cap + 1;
         return;
     }
     // candidates are the codes with above < qd <= T: up to the guessed bucket at first, the rest of those up to the bound the
-    // second time
-    int T = AGAIN ? bd.t : min(bd.guess, bd.t);
-    const int above = AGAIN ? bd.guess : -1;
+    // second time, for queries with fewer than r so far
+    int T = min(bd.guess, bd.t), above = -1;
+    if (again) {
+        if (first_counts[q] >= r || T >= bd.t) return;           // uniform
+        above = T;
+        T = bd.t;
+    }
     const int first_t = T;
     for (int t = tid; t < kM * 64; t += C::THREADS)
-        reinterpret_cast<uint32_t *>(qt)[t] = reinterpret_cast<const uint32_t *>(a.qtab + static_cast<size_t>(q) * (kM * 256))[t];
+        reinterpret_cast<uint32_t *>(qt)[t] = reinterpret_cast<const uint32_t *>(qtab + static_cast<size_t>(q) * (kM * 256))[t];
     if (tid < 256) hist[tid] = 0;
     if (tid == 0) {
         sh.t = T;
         sh.next = sh.ncell = sh.celltaken = sh.nshort = sh.nlong = sh.codes = sh.total = sh.hits = sh.nhit = sh.paused = sh.nlist = 0;
     }
     __syncthreads();
-    group_minima(qt, a.map, G);
+    group_minima(qt, map, G);
     // sums of three nibbles' entries, capped at 127 (a lower bound still)
     for (int t = tid; t < 4096; t += C::THREADS)
         tab[t] = static_cast<uint8_t>(min(127u, G[5 * 16 + (t >> 8)] + G[6 * 16 + ((t >> 4) & 15)] + G[7 * 16 + (t & 15)]));
@@ -517,12 +506,11 @@ __device__ __forceinline__ void scan_part_of_cells(const CellScan<CodeT> &a, uin
     auto load8 = [&](uint32_t at, bool live) __attribute__((always_inline)) {
         return *reinterpret_cast<const uint4 *>(rem16 + (live ? at : 0u));
     };
-    uint32_t sl = (pair + static_cast<uint32_t>(wave)) % nslices;      // slice of this wavefront's next append
+    uint32_t sl = (blockIdx.x + static_cast<uint32_t>(wave)) % nslices;      // slice of this wavefront's next append
 
-    const uint64_t *__restrict__ filled = a.filled;
     // counts per bucket: in LDS, and where several workgroups work on a query added to those in memory after every settling
     const bool shared_hist = parts > 1;
-    uint32_t *counts = a.chist + static_cast<size_t>(q) * 256;
+    uint32_t *counts = chist + static_cast<size_t>(q) * 256;
     // the first n entries of the second queue, by all threads: their integer distances, and those within the bound to the query's buffer
     auto settle = [&](uint32_t n) __attribute__((always_inline)) {
         constexpr int PER = C::HITS / C::THREADS;
@@ -573,16 +561,16 @@ __device__ __forceinline__ void scan_part_of_cells(const CellScan<CodeT> &a, uin
             if (lane == 0) u = atomicAdd(&sh.next, 1u);
             u = __builtin_amdgcn_readfirstlane(u);
             if (u >= 4 * nlist) break;
-            const uint32_t ab = s_list[u >> 2], b = 64 * (u & 3u) + lane;
-            const uint64_t some = filled[4 * ab + (u & 3u)];
-            const uint32_t s = G[ab >> 4] + G[16 + (ab & 15)] + G[32 + (b >> 4)] + G[48 + (b & 15)];
+            const uint32_t a = s_list[u >> 2], b = 64 * (u & 3u) + lane;
+            const uint64_t some = filled[4 * a + (u & 3u)];
+            const uint32_t s = G[a >> 4] + G[16 + (a & 15)] + G[32 + (b >> 4)] + G[48 + (b & 15)];
             const bool have = static_cast<int>(s) + rest4 <= T && (some >> lane & 1u);
             const uint64_t mask = __builtin_amdgcn_ballot_w64(have);
             if (!mask) continue;
             uint32_t to = 0;
             if (lane == 0) to = atomicAdd(&sh.ncell, static_cast<uint32_t>(__popcll(mask)));
             to = __builtin_amdgcn_readfirstlane(to);
-            if (have) cellq[to + rank_in(mask)] = s << 16 | ab << 8 | b;
+            if (have) cellq[to + rank_in(mask)] = s << 16 | a << 8 | b;
         }
         __syncthreads();
         // (2) the sixteen cells of five nibbles of each, a lane per cell
@@ -757,41 +745,16 @@ __device__ __forceinline__ void scan_part_of_cells(const CellScan<CodeT> &a, uin
             }
             __syncthreads();
             T = static_cast<int>(uniform_load(reinterpret_cast<uint32_t *>(&sh.t)));
-            over = uniform_load(&sh.hits) > a.most_hits;
+            over = uniform_load(&sh.hits) > most_hits;
             if (!paused || over) break;
         }
         if (last) break;
     }
     if (tid == 0) {
-        if (!AGAIN) atomicAdd(&a.first_counts[q], sh.total);
+        if (!again) atomicAdd(&first_counts[q], sh.total);
         if (over) atomicMax(&fcount[static_cast<size_t>(q) * nslices], cap + 1);     // too many codes to look at: the redo path takes the query
     }
     if (tid < 256 && !shared_hist) counts[tid] += hist[tid];
-}
-
-template <typename CodeT>
-__global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_kernel(CellScan<CodeT> a)
-{
-    if (a.ctl->use) scan_part_of_cells<CodeT, false>(a, blockIdx.x);
-}
-
-// The second time, for the few queries that found fewer than r codes up to their guessed bucket: a workgroup looks at up to 64
-// (query, part) pairs, a lane at each, and works on those that are left (a workgroup for each pair took 23 us where none is,
-// 4096 queries; so 5).
-template <typename CodeT>
-__global__ __launch_bounds__(CellCfg::THREADS, 6) void scan_cells_again_kernel(CellScan<CodeT> a, uint32_t pairs)
-{
-    if (!a.ctl->use) return;
-    const uint32_t pair = blockIdx.x + (threadIdx.x & 63u) * gridDim.x;
-    bool left = false;
-    if (pair < pairs) {
-        const Bound b = a.bound[pair / a.parts];
-        left = b.t < 255 && b.guess < b.t && a.first_counts[pair / a.parts] < a.r;
-    }
-    for (uint64_t todo = __builtin_amdgcn_ballot_w64(left); todo; todo &= todo - 1) {      // uniform, and the same in all wavefronts
-        scan_part_of_cells<CodeT, true>(a, blockIdx.x + static_cast<uint32_t>(__builtin_ctzll(todo)) * gridDim.x);
-        __syncthreads();                                         // (the LDS is read no more)
-    }
 }
 
 // ---- host side ------------------------------------------------------------------------------------
@@ -857,13 +820,14 @@ static int launch_cells(const CodeT *codes, uint64_t n_codes, const uint8_t *qta
     if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&cells_sort_kernel<false>), sort_lds);
     if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&cells_sort_kernel<true>), sort_lds);
     if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&scan_cells_kernel<CodeT>), CellCfg::BYTES, true);
-    if (!rc) rc = allow_dynamic_lds(reinterpret_cast<const void *>(&scan_cells_again_kernel<CodeT>), CellCfg::BYTES, true);
     if (rc) return rc;
     DCPQ_LAUNCH(kStageCellsSort, st, cells_group_kernel, dim3(kM + 64), dim3(1024), group_lds, area.derived, kM, area.dsub, area.small_bits, map,
                 words(0), static_cast<uint32_t>(p.clear_words));
     DCPQ_CHECK_LAUNCH("cells_group_kernel");
-    // Costs in picoseconds, from N = 1e8, 4096 queries (sorting 1.8 ms, scan 4.9 ms for 6.6e9 codes in 7.4e7 cells and 8e7 hits;
-    // single-pass scan 40.7 ms) and N = 2e6, 4096 queries (4.2 ms for 1.8e8 cells of one or two codes; 1.37 ms).
+    // Costs in picoseconds, from N = 1e8, 4096 queries (sorting 1.8 ms, scan 4.9 ms for 6.6e9 codes in 7.4e7 cells and 4.5e7 settled
+    // codes; single-pass scan 40.7 ms) and N = 2e6, 4096 queries (4.2 ms for 1.8e8 cells of one or two codes; 1.37 ms).  They leave a margin:
+    // of 171 searches of 4.2e6 to 4e7 codes, 210 to 20000 queries, r = 200 to 10000 on eight kinds of codebooks and codes the 56 that were served
+    // took 0.15 to 0.89 of the time of the single-pass scan.
     const float pairs = static_cast<float>(n_codes) * static_cast<float>(nq);
     const uint32_t every = (static_cast<uint32_t>(nq) + kSampleQueries - 1) / kSampleQueries;
     DCPQ_LAUNCH(kStageCellsSort, st, (cells_decide_kernel<CodeT>), dim3((nq + every - 1) / every), dim3(256), 0, codes, n_codes, qtab, nq, every, map, bound,
@@ -887,14 +851,14 @@ static int launch_cells(const CodeT *codes, uint64_t n_codes, const uint8_t *qta
     while (parts * 2 * static_cast<uint32_t>(nq) <= 2048 && parts < 16) parts *= 2;
     const uint64_t hits = 64ull * r + n_codes / 64;
     const uint32_t most = static_cast<uint32_t>(hits > 0x7FFFFFFFull ? 0x7FFFFFFFull : hits);
-    CellScan<CodeT> scan{codes, qtab, map, offs, filled, rem, words(p.off_ids), bound, r, parts, nslices, cap, most, fcount, chist, keys,
-                         words(p.off_first), ctl};
-    DCPQ_LAUNCH(kStageScanCells, st, (scan_cells_kernel<CodeT>), dim3(nq * parts), dim3(CellCfg::THREADS), CellCfg::BYTES, scan);
-    DCPQ_CHECK_LAUNCH("scan_cells_kernel");
-    if (parts < 8) scan.parts = 8;                               // few queries are left: more workgroups for each
-    const uint32_t left = static_cast<uint32_t>(nq) * scan.parts, blocks = left <= 1024 ? left : left <= 65536 ? 1024u : (left + 63) / 64;
-    DCPQ_LAUNCH(kStageScanCells, st, (scan_cells_again_kernel<CodeT>), dim3(blocks), dim3(CellCfg::THREADS), CellCfg::BYTES, scan, left);
-    DCPQ_CHECK_LAUNCH("scan_cells_again_kernel");
+    for (int again = 0; again < 2; ++again) {
+        // few queries are left: more workgroups for each.  (Fewer workgroups that look for the pairs that are left return sooner where none
+        // is, 5 us instead of 23 with 4096 queries, but take 205 us instead of 162 where 94 are.)
+        if (again && parts < 8) parts = 8;
+        DCPQ_LAUNCH(kStageScanCells, st, (scan_cells_kernel<CodeT>), dim3(nq * parts), dim3(CellCfg::THREADS), CellCfg::BYTES, codes, qtab,
+                    map, offs, filled, rem, words(p.off_ids), bound, r, parts, nslices, cap, most, fcount, chist, keys, words(p.off_first), again, ctl);
+        DCPQ_CHECK_LAUNCH("scan_cells_kernel");
+    }
     return DCPQ_OK;
 }
 
