@@ -13,13 +13,14 @@
 //
 // Where the groups say little (codebooks without near centroids, a bound that most cells are within) this saves nothing:
 // cells_decide_kernel estimates both costs on a sample of the codes and sets the flag by which either these kernels or the
-// single-pass scan return at once (no host synchronization).  A batch that is not served pays 50 to 60 us for that.
+// single-pass scan return at once (no host synchronization).  A batch that is not served pays about 60 us for that
+// (the median of 73 searches, timed twice; single ones of a millisecond up to 110).
 //
 // Measured, whole searches, on codebooks of 16 parents per sub-quantizer, which the groups meet: N = 1e8, 4096 queries,
-// r = 4000: 41.2 -> 8.6 ms (sorting 1.8, scan 4.4 to 5, pass two 1.5); N = 1e7 encoded vectors, 1000 queries, r = 2000: 1.49 -> 0.72 ms
+// r = 4000: 41.1 -> 8.6 to 9.1 ms (sorting 1.8, scan 4.4 to 5, pass two 1.5); N = 1e7 encoded vectors, 1000 queries, r = 2000: 1.49 -> 0.72 ms
 // (sorting 0.21, scan 0.20).  On quantizers trained by Alg. 2 it depends on the vectors: of a mixture of 1024 tight components in
-// 128 dimensions 1.2e7 codes, 4096 queries, r = 2000 7.1 -> 2.5 ms, 4.2e6 codes, 2000 queries 1.86 -> 1.55; of Gaussian vectors, Gaussian ones
-// with a decaying spectrum and normalised ones of 4096 wide components every batch was declined (6 % of 1.05 ms, 1 % of 6).
+// 128 dimensions 1.2e7 codes, 4096 queries, r = 2000 7.1 -> 2.5 ms, 4.2e6 codes, 2000 queries 1.86 -> 1.58; of Gaussian vectors, Gaussian ones
+// with a decaying spectrum and normalised ones of 4096 wide components every batch was declined (2 to 6 % of 1.05 to 1.5 ms, 1 to 2 % of 6).
 #include "lds_access.h"
 #include "scan_internal.h"
 
