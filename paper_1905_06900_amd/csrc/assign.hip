@@ -2,7 +2,8 @@
 // (squared distance, index) with distances in double precision.
 //
 // Small codebooks, and few points with long sub-vectors, take all products on the double-precision matrix pipe
-// (assign_f64_kernel; f64_is_faster says where).  The others are computed in two steps with the result of one.  A filter evaluates |c|^2 - 2 <x, c> for all centroids on
+// (assign_f64_kernel; f64_is_faster says where), many points with sub-vectors of 5 to 64 components a filter with one fp16 product
+// (assign_half_kernel; the rule is in launch_assign_ks).  The others are computed in two steps with the result of one.  A filter evaluates |c|^2 - 2 <x, c> for all centroids on
 // the bf16 matrix cores with every fp32 number split into two bf16 numbers (x = xh + xl + an error of at most
 // 2^-17 |x|; the three products xh ch + xl ch + xh cl, and xl cl where it costs no further matrix instruction, lie
 // side by side along the K dimension of one matrix product whose accumulators start from |c|^2), and keeps per
@@ -16,8 +17,7 @@
 // vector instructions per 32 x 32 distances (9 for the minima, the rest the conversion of the centroids, shared by the
 // points of a workgroup) 0.38; the LDS 0.22.  250007 vectors, 8
 // sub-quantizers of 16 components and 65536 centroids: 11.3 ms = 1.1 PFLOP/s of bf16 products, what a large library
-// matrix product reaches here (1.16), 8.7 ms where the points are whole numbers (two products instead of three); with all distances on the double-precision matrix pipe 97 ms.  d = 32: 6.2 ms per
-// 100000 x 4 (32.7 in double precision); d = 60: 9.8 ms per 20000 x 16 (58.8).
+// matrix product reaches here (1.16); with all distances on the double-precision matrix pipe 97 ms.
 #include <type_traits>
 
 #include "common.h"
@@ -107,18 +107,17 @@ __device__ inline void store_label(void *labels, int label_bytes, size_t o, uint
     else static_cast<uint32_t *>(labels)[o] = i;
 }
 
-// Nearest centroid of the j-th sub-vector of every point, j = blockIdx.y.  points: rows of `ld` floats;
-// sub-vector j starts at column j * dsub.  labels: [n][m].  dist (optional): [n][m] fp32 squared distance.
+// Nearest centroid of the j-th sub-vector of a workgroup's points, whose numbers are at(0), at(1), ... at(np - 1).  points: rows of
+// `ld` floats; sub-vector j starts at column j * dsub.  labels: [n][m].  dist (optional): [n][m] fp32 squared distance.
 // dp: dsub rounded up to a multiple of 4, 3 dp <= 16 KS (4 dp <= 16 KS: all four products, half the filter's error).  FOURS: dsub is
 // one (a kernel of its own: with both ways of reading the centroids in one, the compiler moved the load that they share before the
 // branch and waited for it before the products; 300 points, 65536 centroids of 3 components: 0.30 ms so and 0.26 apart; of 8 0.38 and 0.28, of 21 0.73 and 0.64, of 32 0.75 and 0.52).
-template <int KS, int P, bool SPLIT, bool FOURS>
-__global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
-                                                     const float *__restrict__ cb, int m, int dsub, int dp, int ncent,
-                                                     void *__restrict__ labels, int label_bytes, float *__restrict__ dist)
+template <int KS, int P, bool SPLIT, bool FOURS, typename At>
+__device__ __forceinline__ void nearest_by_split_products(uint8_t *smem, At at, uint32_t np, const float *__restrict__ points, int ld,
+                                                          const float *__restrict__ cbj, int j, int m, int dsub, int dp, int ncent,
+                                                          void *__restrict__ labels, int label_bytes, float *__restrict__ dist)
 {
     using C = AssignCfg<KS, P, SPLIT>;
-    extern __shared__ __align__(16) uint8_t smem[];
     __shared__ __align__(16) float mu[128];
     __shared__ float s_cmax[4];
     __shared__ float xnorm2[C::PTS];
@@ -128,9 +127,6 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     __shared__ uint32_t red_i[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int j = blockIdx.y;
-    const uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * C::PTS;
-    const float *cbj = cb + static_cast<size_t>(j) * ncent * dsub;
     const int col = lane & 31, half = lane >> 5;
     const bool four = KS <= 3 && 4 * dp <= 16 * KS;                 // K has room for the product xl cl (sub-vectors of up to 12)
 
@@ -169,8 +165,8 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     for (int p = 0; p < P; ++p) {
 #pragma unroll 1
         for (int sub = 0; sub < (SPLIT ? 1 : 128 / C::RS); ++sub) {
-            const uint64_t q = q0 + p * (SPLIT ? 32 : 128) + sub * C::RS + srow;
-            const float *x = points + static_cast<size_t>(q < n ? q : n - 1) * ld + j * dsub;
+            const uint32_t pt = p * (SPLIT ? 32 : 128) + sub * C::RS + srow;
+            const float *x = points + static_cast<size_t>(at(pt < np ? pt : np - 1)) * ld + j * dsub;
             uint8_t *row = smem + srow * C::STRIDE;
             float norm = 0.0f;
 #pragma unroll 1
@@ -195,7 +191,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
             }
 #pragma unroll
             for (int off = 1; off < C::TPR; off <<= 1) norm += __shfl_xor(norm, off);
-            if (spart == 0 && p * (SPLIT ? 32 : 128) + sub * C::RS + srow < C::PTS) xnorm2[p * (SPLIT ? 32 : 128) + sub * C::RS + srow] = norm;
+            if (spart == 0 && pt < C::PTS) xnorm2[pt] = norm;
             __syncthreads();
             if (SPLIT || wave * 32 / C::RS == sub) {
                 const uint8_t *b = smem + ((SPLIT ? 0 : wave * 32 % C::RS) + col) * C::STRIDE + half * 16;
@@ -429,7 +425,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         return gmin + 2.0f * filter_error(xn, c1);
     };
     for (int pt = tid; pt < C::PTS; pt += 256) {
-        if (q0 + pt >= n) break;
+        if (static_cast<uint32_t>(pt) >= np) break;
         const float *e = ent + pt * C::NE * 5;
         const float thr = threshold(pt);
         bool full = !(thr < 1e37f);
@@ -464,7 +460,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     for (uint32_t t0 = tid >> 4; t0 < n_one; t0 += 16) {
         const uint32_t rec = list[0][t0];
         const int pt = static_cast<int>(rec & 0xFFFFu), k = static_cast<int>(rec >> 16);
-        const uint64_t q = q0 + pt;
+        const uint64_t q = at(pt);
         const float *x = points + static_cast<size_t>(q) * ld + j * dsub, *e = ent + pt * C::NE * 5;
         uint32_t c[C::TPC];
         const float *row[C::TPC];
@@ -526,7 +522,7 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
     // several cells
     for (uint32_t t0 = tid >> 4; t0 < n_several; t0 += 16) {
         const int pt = static_cast<int>(list[1][t0] & 0xFFFFu);
-        const uint64_t q = q0 + pt;
+        const uint64_t q = at(pt);
         const float *x = points + static_cast<size_t>(q) * ld + j * dsub, *e = ent + pt * C::NE * 5;
         const float thr = threshold(pt);
         double best = INFINITY;
@@ -581,11 +577,11 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
         };
         const int last = (ncent - 1) / C::ROWS * C::ROWS;
         for (uint32_t h0 = 0; h0 < n_hard; h0 += C::TOGETHER) {         // uniform
-            const uint32_t np = min(n_hard - h0, static_cast<uint32_t>(C::TOGETHER));
+            const uint32_t nh = min(n_hard - h0, static_cast<uint32_t>(C::TOGETHER));
             __syncthreads();                                          // the minima and the previous points are no longer read
             for (int t = tid; t < C::TOGETHER * dsub; t += 256) {
                 const int p = t / dsub, o = t % dsub;
-                const uint64_t q = q0 + (list[2][h0 + (static_cast<uint32_t>(p) < np ? p : 0)] & 0xFFFFu);
+                const uint64_t q = at(list[2][h0 + (static_cast<uint32_t>(p) < nh ? p : 0)] & 0xFFFFu);
                 xd[o * C::TOGETHER + p] = static_cast<double>(points[static_cast<size_t>(q) * ld + j * dsub + o]);
             }
             const double *xw = xd + wave * C::PER_WAVE;
@@ -663,13 +659,13 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
                     take_smaller(best[p], bi[p], ov, oi);
                 }
                 const uint32_t h = wave * C::PER_WAVE + p;
-                if (lane == 0 && h < np) put(q0 + (list[2][h0 + h] & 0xFFFFu), best[p], bi[p]);
+                if (lane == 0 && h < nh) put(at(list[2][h0 + h] & 0xFFFFu), best[p], bi[p]);
             }
         }
         return;
     }
     for (uint32_t hi = 0; hi < n_hard; ++hi) {                        // uniform
-        const uint64_t q = q0 + (list[2][hi] & 0xFFFFu);
+        const uint64_t q = at(list[2][hi] & 0xFFFFu);
         const float *x = points + static_cast<size_t>(q) * ld + j * dsub;
         double best = INFINITY;
         uint32_t bi = 0xFFFFFFFFu;
@@ -687,6 +683,662 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
             put(q, best, bi);
         }
         __syncthreads();
+    }
+}
+
+template <int KS, int P, bool SPLIT, bool FOURS>
+__global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void assign_kernel(const float *__restrict__ points, uint64_t n, int ld,
+                                                     const float *__restrict__ cb, int m, int dsub, int dp, int ncent,
+                                                     void *__restrict__ labels, int label_bytes, float *__restrict__ dist)
+{
+    using C = AssignCfg<KS, P, SPLIT>;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int j = blockIdx.y;
+    const uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * C::PTS;
+    const uint32_t np = n - q0 < C::PTS ? static_cast<uint32_t>(n - q0) : C::PTS;
+    nearest_by_split_products<KS, P, SPLIT, FOURS>(smem, [q0](uint32_t pt) { return q0 + pt; }, np, points, ld, cb + static_cast<size_t>(j) * ncent * dsub, j, m,
+                                                   dsub, dp, ncent, labels, label_bytes, dist);
+}
+
+// ---- many points, sub-vectors of 5 to 64 components ------------------------------------------------------------
+// The same result, with ONE fp16 product in the filter where the form above takes three or four bf16 ones: fp16 keeps 11 significant
+// bits, and the window that this leaves around the smallest filter value holds 1.05 to 1.25 centroids on average (65536 centroids of 12 to
+// 60 components, encoded data as well as Gaussian).  It is proven as above: from |x|, |c| and the lengths of the remainders x - xh and c - ch
+// themselves.  Points with four or more cells of one half of a tile in their window, 1 in 1000 or fewer, are walked again, 32 at a time, the
+// wavefronts sharing the centroids, and now that the window is known every centroid in it is listed and compared in double precision.  Where
+// the windows hold too many for that (centroids closer together than 2^-11 of their distance from the reference vector), the points
+// left go through the split products.
+//
+// Scale: points and centroids are multiplied by a power of two that brings the largest component of 64 centroids to 2^4, or the
+// largest of the workgroup's points below 2^14, whichever is less, so that only centroids some thousand times longer than those 64 overflow (all points
+// are then left to the split products); what falls below the normal numbers, 2^-14, is counted with the remainders whether the
+// matrix pipe keeps it or not.
+//
+// What bounds it (KS = 3, the common case of up to 16 components): a tile of 32 x 32 distances is one matrix instruction and eight for its minima; together, with random
+// numbers and nothing else to do, 29 ns per SIMD (21 and 16 each alone: the clock falls to 1.9 GHz meanwhile).  The walk takes 37 ns: another 1.3 vector instructions for the conversion of the
+// centroids, 1 for the cells, and the barriers between the stages (29 ns without these three).  1024 points per workgroup: the operands and norms of the
+// centroids, 40 clocks of the LDS per tile, then serve eight tiles of points.  250007 vectors, 8 sub-quantizers: 5.4 ms, of which the
+// walk 4.7, the cells 0.35, the second walk 0.35; the numbers of the cells in the low bits of their minima leave four of these per point and lane room in
+// the registers (three with a register each for their numbers: 1 % of the points were left open, and every workgroup walked again).
+constexpr uint32_t kCells = 512;              // cells of a codebook, at most: their numbers take nine bits
+template <int KS, int P>
+struct HalfCfg {
+    static constexpr int DPMAX = 16 * KS / 3 & ~3;
+    static constexpr int KH = (DPMAX + 15) / 16;                    // steps of 16 along K
+    static constexpr bool TWO = 2 * DPMAX <= 16 * KH;               // room for the product xl ch
+    static constexpr int RS = KH == 1 ? 256 : 128, TPR = 256 / RS, NG = (DPMAX / 4 + TPR - 1) / TPR;      // (as in AssignCfg)
+    static constexpr int TPC = 4;                                   // tiles of 32 centroids per cell
+    static constexpr int AHEAD = KH <= 4 ? 2 : 1, LAG = 2;
+    static constexpr int STRIDE = KH * 32 + 16, PTS = 128 * P, NE = 2;
+    static constexpr int BUF_BYTES = RS * STRIDE + RS * 4, STAGE_BYTES = 2 * BUF_BYTES;
+    // minima of a point: KEEP by each of the two lanes that held them, and what became of them
+    static constexpr int KEEP = 4, SLOTS = NE * KEEP;
+    static constexpr uint32_t ITEMS = 2 * PTS;                      // cells that are looked at for all points together, at most
+    static constexpr int ENT_BYTES = 2 * ITEMS * 2 + PTS * SLOTS * 4 + PTS * 5;
+    // the second walk: centroids listed for 32 points
+    static constexpr uint32_t FOUND = 2048;
+    static constexpr int FOUND_BYTES = STAGE_BYTES + FOUND * 8 + 32 * 12;
+    // the rest: up to 32 points whose centroids are split between the wavefronts, or each wavefront with points of its own
+    static constexpr bool SPLIT = KS <= 6;
+    static constexpr int MANY_P = KS <= 12 ? 2 : 1;
+    using Few = AssignCfg<KS, 1, SPLIT>;
+    using Many = AssignCfg<KS, MANY_P, false>;
+    static constexpr int max4(int a, int b, int c, int d) { return (a > b ? a : b) > (c > d ? c : d) ? (a > b ? a : b) : (c > d ? c : d); }
+    static constexpr int LDS_BYTES = max4(STAGE_BYTES > Few::LDS_BYTES ? STAGE_BYTES : Few::LDS_BYTES, ENT_BYTES, FOUND_BYTES, Many::LDS_BYTES);
+};
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+
+// v of the lane whose number differs in the bits of X, within four.
+template <int X>
+__device__ inline float other_of_four(float v)
+{
+    constexpr int perm = (0 ^ X) | (1 ^ X) << 2 | (2 ^ X) << 4 | (3 ^ X) << 6;
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), perm, 0xF, 0xF, true));
+}
+
+template <int KS, int P, bool FOURS>
+__global__ __launch_bounds__(256, 2) void assign_half_kernel(const float *__restrict__ points, uint64_t n, int ld, const float *__restrict__ cb,
+                                                             int m, int dsub, int dp, int ncent, void *__restrict__ labels, int label_bytes,
+                                                             float *__restrict__ dist)
+{
+    using C = HalfCfg<KS, P>;
+    constexpr int KH = C::KH;
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ __align__(16) float mus[128];                        // minus the reference vector, scaled
+    __shared__ float mu[128], s_cmax[4], s_crest[4], xnorm2[C::PTS], xrest2[C::PTS];
+    __shared__ uint32_t s_count[5], s_whole, s_xmax, s_cabs;
+    __shared__ uint16_t open[C::PTS];                               // points that the first walk has left open
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = blockIdx.y;
+    const uint64_t q0 = static_cast<uint64_t>(blockIdx.x) * C::PTS;
+    const uint32_t np = n - q0 < C::PTS ? static_cast<uint32_t>(n - q0) : C::PTS;
+    const float *cbj = cb + static_cast<size_t>(j) * ncent * dsub;
+    const int col = lane & 31, half = lane >> 5;
+
+    // reference vector and scale
+    if (tid == 0) s_whole = s_xmax = s_cabs = 0;
+    if (tid < 5) s_count[tid] = tid < 4 ? 0 : C::ITEMS;              // items, slow points, open points, (second walk) centroids found; items that there are
+    __syncthreads();
+    if (tid < 128) {
+        float sum = 0.0f, lo = 0.0f, hi = 0.0f;
+        const int ns = ncent < 64 ? ncent : 64, step = ncent / ns;
+        if (tid < dsub)
+            for (int s = 0; s < ns; ++s) {
+                const float v = cbj[static_cast<size_t>(s * step + s % step) * dsub + tid];
+                sum += v;
+                lo = s ? fminf(lo, v) : v;
+                hi = s ? fmaxf(hi, v) : v;
+            }
+        const float mean = sum / static_cast<float>(ns);
+        mu[tid] = mean;
+        if (fabsf(mean) >= 8.0f) s_whole = 1;
+        const float far = fmaxf(fabsf(hi - mean), fabsf(lo - mean)) + 1.0f * (fabsf(mean) >= 8.0f);
+        if (far < INFINITY) atomicMax(&s_cabs, __float_as_uint(far));
+    }
+    for (int t = tid; t < C::STAGE_BYTES / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    if (tid < 128 && s_whole) mu[tid] = rintf(mu[tid]);
+    __syncthreads();
+    {
+        float most = 0.0f;
+        for (uint32_t pt = tid >> 2; pt < np; pt += 64) {
+            const float *x = points + static_cast<size_t>(q0 + pt) * ld + j * dsub;
+            for (int o = tid & 3; o < dsub; o += 4) {
+                const float v = fabsf(x[o] - mu[o]);
+                most = v < INFINITY ? fmaxf(most, v) : most;
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) most = fmaxf(most, __shfl_xor(most, off));
+        if (lane == 0) atomicMax(&s_xmax, __float_as_uint(most));
+    }
+    __syncthreads();
+    // (x < 2^(exponent - 126) for the exponent field of x)
+    const int ec = static_cast<int>(s_cabs >> 23) - 126, ex = static_cast<int>(s_xmax >> 23) - 126;
+    const float scale = __uint_as_float(static_cast<uint32_t>(min(max(min(4 - ec, 14 - ex), -120), 120) + 127) << 23);
+    if (tid < 128) mus[tid] = -mu[tid] * scale;
+    __syncthreads();
+
+    const int srow = tid / C::TPR, spart = tid % C::TPR;
+    // The point side of the product, as in the other form: [ -2 xh | 0 ... ], with room for two products [ -2 xh | -2 xl | 0 ... ].  One row
+    // of LDS, by C::TPR threads; norm, rest: |x|^2 and the square of what is left out of x, of this thread's components
+    auto convert_point = [&](uint8_t *row, uint64_t q, float &norm, float &rest) __attribute__((always_inline)) {
+        const float *x = points + static_cast<size_t>(q) * ld + j * dsub;
+        norm = rest = 0.0f;
+#pragma unroll 1
+        for (int g = 0; g < C::NG; ++g) {
+            const int o = 4 * (spart + C::TPR * g);
+            if (o < dp) {
+                v4h h, l;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int t = o + e < dsub ? o + e : dsub - 1;
+                    const float u = o + e < dsub ? (x[t] - mu[t]) * scale : 0.0f, v = -2.0f * u;
+                    h[e] = static_cast<_Float16>(v);
+                    float left = v - static_cast<float>(h[e]);
+                    if (C::TWO) {
+                        l[e] = static_cast<_Float16>(left);
+                        left -= static_cast<float>(l[e]);
+                    }
+                    norm = fmaf(u, u, norm);
+                    rest = fmaf(0.25f * left, left, rest);
+                }
+                *reinterpret_cast<v4h *>(row + 2 * o) = h;
+                if (C::TWO) *reinterpret_cast<v4h *>(row + 2 * (dp + o)) = l;
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < C::TPR; off <<= 1) { norm += __shfl_xor(norm, off); rest += __shfl_xor(rest, off); }
+    };
+    v8h bq[P][KH];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        if (srow < 128) {                                             // (whole wavefronts)
+            const uint32_t pt = p * 128 + srow;
+            float norm, rest;
+            convert_point(smem + srow * C::STRIDE, q0 + (pt < np ? pt : np - 1), norm, rest);
+            if (spart == 0) { xnorm2[pt] = norm; xrest2[pt] = rest; }
+        }
+        __syncthreads();
+        const uint8_t *b = smem + (wave * 32 + col) * C::STRIDE + half * 16;
+#pragma unroll
+        for (int ks = 0; ks < KH; ++ks) bq[p][ks] = *reinterpret_cast<const v8h *>(b + ks * 32);
+        __syncthreads();
+    }
+
+    // staging: TPR threads convert one centroid
+    float pre[C::NG][4];
+    auto load_stage = [&](int c0) __attribute__((always_inline)) {
+        const int c = c0 + srow;
+        const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+#pragma unroll
+        for (int g = 0; g < C::NG; ++g) {
+            const int o = 4 * (spart + C::TPR * g);
+            if constexpr (FOURS) {
+                const f4_any v = *reinterpret_cast<const f4_any *>(src + (o < dsub ? o : 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) pre[g][e] = v.v[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) pre[g][e] = src[o + e < dsub ? o + e : 0];       // (past the last: set to zero when the stage is stored)
+            }
+        }
+    };
+    float cmax2 = 0.0f, crest2 = 0.0f;        // largest |c|^2 and |c - ch|^2 among the centroids this thread converted
+    auto store_stage = [&](int c0, uint8_t *buf) __attribute__((always_inline)) {
+        uint8_t *row = buf + srow * C::STRIDE;
+        float norm = 0.0f, rest = 0.0f;
+#pragma unroll
+        for (int g = 0; g < C::NG; ++g) {
+            const int o = 4 * (spart + C::TPR * g);
+            if (o < dp) {
+                v4h h;
+                const float4 mv = *reinterpret_cast<const float4 *>(mus + o);
+                const float ref[4] = {mv.x, mv.y, mv.z, mv.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float v = fmaf(pre[g][e], scale, ref[e]);        // (pre - mu), rounded once, scaled
+                    if (!FOURS && o + e >= dsub) v = 0.0f;
+                    h[e] = static_cast<_Float16>(v);
+                    norm = fmaf(v, v, norm);
+                    const float left = v - static_cast<float>(h[e]);
+                    rest = fmaf(left, left, rest);
+                }
+                *reinterpret_cast<v4h *>(row + 2 * o) = h;
+                if (C::TWO) *reinterpret_cast<v4h *>(row + 2 * (dp + o)) = h;
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < C::TPR; off <<= 1) { norm += __shfl_xor(norm, off); rest += __shfl_xor(rest, off); }
+        crest2 = fmaxf(crest2, rest);                                 // (rows past the last repeat it; infinite or not a number only where the norm is too large)
+        // (a component of 65504 and above would be infinite in fp16; NaN counts as infinite)
+        if (c0 + srow < ncent) cmax2 = norm < 4.0e9f ? fmaxf(cmax2, norm) : INFINITY;
+        else norm = 3.0e38f;                                         // past the last centroid: never the nearest (finite: the number of a cell goes into its minimum)
+        if (spart == 0) reinterpret_cast<float *>(buf + C::RS * C::STRIDE)[srow] = norm;
+    };
+
+    // the four smallest cell minima of each of this lane's points, in increasing order; the low bits hold the number of the cell
+    constexpr int KEEP = C::KEEP;
+    float best4[P][KEEP];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i) best4[p][i] = INFINITY;
+    float mn[P];                              // minimum of the cell so far
+    auto read_tile = [&](const uint8_t *buf, int t, v8h (&a)[KH], v16f &norm) __attribute__((always_inline)) {
+        const uint8_t *ra = buf + (t * 32 + col) * C::STRIDE + half * 16;
+#pragma unroll
+        for (int ks = 0; ks < KH; ++ks) a[ks] = *reinterpret_cast<const v8h *>(ra + ks * 32);
+        const float *nr = reinterpret_cast<const float *>(buf + C::RS * C::STRIDE) + t * 32 + 4 * half;
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+            const float4 x = *reinterpret_cast<const float4 *>(nr + 2 * v);
+            norm[v] = x.x; norm[v + 1] = x.y; norm[v + 2] = x.z; norm[v + 3] = x.w;
+        }
+    };
+    // minimum of 16 filter values and `with`, in eight instructions
+    auto minimum = [](const v16f &acc, float with) __attribute__((always_inline)) {
+        float m0 = fminf(fminf(acc[0], acc[1]), acc[2]), m1 = fminf(fminf(acc[3], acc[4]), acc[5]);
+#pragma unroll
+        for (int v = 6; v < 14; v += 4) {
+            m0 = fminf(fminf(acc[v], acc[v + 1]), m0);
+            m1 = fminf(fminf(acc[v + 2], acc[v + 3]), m1);
+        }
+        m0 = fminf(fminf(acc[14], acc[15]), m0);
+        return fminf(fminf(m0, m1), with);
+    };
+    // One wavefront's tiles of a stage, as in the other form: the minimum of step x - LAG while the products of step x run
+    auto compute_cell = [&](const uint8_t *buf, int t0) __attribute__((always_inline)) {
+        constexpr int AH = C::AHEAD;
+        v8h a[AH][KH];
+        v16f norm[AH], acc[C::LAG + 1];
+        if constexpr (AH == 2) read_tile(buf, t0, a[0], norm[0]);
+#pragma unroll
+        for (int x = 0; x < C::TPC * P + C::LAG; ++x) {
+            const int t = x / P, p = x % P;
+            if (x < C::TPC * P) {
+                if constexpr (AH == 2) {
+                    if (p == 0 && t + 1 < C::TPC) read_tile(buf, t0 + t + 1, a[(t + 1) & 1], norm[(t + 1) & 1]);
+                } else {
+                    if (p == 0) read_tile(buf, t0 + t, a[0], norm[0]);
+                }
+#pragma unroll
+                for (int ks = 0; ks < KH; ++ks)
+                    acc[x % (C::LAG + 1)] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[t % AH][ks], bq[p][ks], ks == 0 ? norm[t % AH] : acc[x % (C::LAG + 1)], 0, 0, 0);
+            }
+            if (x >= C::LAG) {
+                const int q = (x - C::LAG) % P;
+                mn[q] = minimum(acc[(x - C::LAG) % (C::LAG + 1)], x - C::LAG < P ? INFINITY : mn[q]);
+                asm volatile("" : "+v"(mn[q]));                       // (keeps it here: its use is behind a branch)
+            }
+#pragma unroll
+            for (int ks = 0; ks < KH; ++ks) {                         // matrix and vector instructions in turn
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, (8 + KH - 1) / KH, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto enter = [&](uint32_t cell) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(cell));                                // (in a vector register: one instruction for mask and number)
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const float v = __uint_as_float((__float_as_uint(mn[p]) & ~(kCells - 1u)) | cell);
+#pragma unroll
+            for (int i = KEEP - 1; i >= 0; --i) best4[p][i] = __builtin_amdgcn_fmed3f(i ? best4[p][i - 1] : -INFINITY, best4[p][i], v);
+        }
+    };
+    const int nst = (ncent + C::RS - 1) / C::RS;
+    load_stage(0);
+    store_stage(0, smem);
+    __syncthreads();
+    for (int s = 0; s < nst; ++s) {                                   // uniform
+        if (s + 1 < nst) load_stage((s + 1) * C::RS);
+#pragma unroll 1
+        for (int h = 0; h < C::RS / (32 * C::TPC); ++h) {
+            compute_cell(smem + (s & 1) * C::BUF_BYTES, h * C::TPC);
+            enter(s * (C::RS / (32 * C::TPC)) + h);
+        }
+        if (s + 1 < nst) store_stage((s + 1) * C::RS, smem + ((s + 1) & 1) * C::BUF_BYTES);
+        __syncthreads();
+    }
+
+    // hand the minima over: ent[point][half that held them][KEEP]
+    float *ent = reinterpret_cast<float *>(smem);
+    uint16_t *items = reinterpret_cast<uint16_t *>(ent + C::PTS * C::SLOTS), *res = items + C::ITEMS;        // cells to look at: (point, slot); what was found
+    uint16_t *first = res + C::ITEMS, *slow = first + C::PTS;         // first item of a point; points that need double precision
+    uint8_t *has = reinterpret_cast<uint8_t *>(slow + C::PTS);        // the slots of a point that are looked at
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        float *e = ent + (p * 128 + wave * 32 + col) * C::SLOTS + half * KEEP;
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i) e[i] = best4[p][i];
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { cmax2 = fmaxf(cmax2, __shfl_xor(cmax2, off)); crest2 = fmaxf(crest2, __shfl_xor(crest2, off)); }
+    if (lane == 0) { s_cmax[wave] = cmax2; s_crest[wave] = crest2; }
+    __syncthreads();
+    const float crest = sqrtf(fmaxf(fmaxf(s_crest[0], s_crest[1]), fmaxf(s_crest[2], s_crest[3]))) * 1.001f;
+    const float cmax = sqrtf(fmaxf(fmaxf(s_cmax[0], s_cmax[1]), fmaxf(s_cmax[2], s_cmax[3]))) * 1.001f;
+
+    // Error of a filter value, |c| <= c1: <x, c> - <xh, ch> = <x - xh, c> + <xh, c - ch>, doubled, with remainders of known lengths (fp16 has
+    // 11 significant bits: they are 2^-11 of the whole at most, and 0.4 of that as a rule).  A component below 2^-14 may lose all of it in the
+    // matrix pipe: `tiny` for dp of them.  The additions as in the other form.
+    constexpr float kNumber = kCells / 8388608.0f, kAddHalf = (16.0f * KH + 16.0f) / 8388608.0f;
+    const float tiny = sqrtf(static_cast<float>(dp)) * (1.01f / 16384.0f);
+    auto filter_error = [tiny, crest](float xn, float xr, float c1) {
+        return 2.0f * ((xn + xr) * (fminf(crest, c1 * (1.001f / 2048.0f)) + tiny) + xr * c1) + (xn * 2.1f + c1 * 1.1f) * c1 * kAddHalf + 1e-35f * (1.0f + xn + c1);
+    };
+    // Largest filter value a nearest centroid can have (as in the other form).
+    for (uint32_t pt = tid; pt < np; pt += 256) {
+        const float *e = ent + pt * C::SLOTS;
+        const float xn = sqrtf(xnorm2[pt]) * 1.001f, xr = sqrtf(xrest2[pt]) * 1.001f + tiny;
+        const float gmin = fminf(e[0], e[KEEP]);
+        const float d2 = fmaxf(xn * xn + gmin + (1.1f * kNumber) * fabsf(gmin) + filter_error(xn, xr, cmax), 0.0f);
+        const float c1 = fminf(cmax, (xn + sqrtf(d2)) * 1.001f);
+        const float window = 2.0f * filter_error(xn, xr, c1), thr = gmin + window + (2.1f * kNumber) * (fabsf(gmin) + window);      // (what the number of a cell takes of the value)
+        xnorm2[pt] = thr;                                             // (the norm is needed no more)
+        uint32_t slots = 0;
+#pragma unroll
+        for (int k = 0; k < C::SLOTS; ++k) slots |= (e[k] <= thr ? 1u : 0u) << k;
+        constexpr uint32_t kLast = 1u << (KEEP - 1) | 1u << (C::SLOTS - 1);
+        bool left = !(thr < 1e37f) || (slots & kLast);
+        uint32_t to = 0;
+        if (!left) {
+            to = atomicAdd(&s_count[0], static_cast<uint32_t>(__popc(slots)));
+            left = to + __popc(slots) > C::ITEMS;
+            if (left) atomicMin(&s_count[4], to);
+        }
+        if (left) {
+            open[atomicAdd(&s_count[2], 1u)] = static_cast<uint16_t>(pt);
+            slots = 0;
+        }
+        has[pt] = static_cast<uint8_t>(slots);
+        first[pt] = static_cast<uint16_t>(to);
+        for (; slots; slots &= slots - 1) items[to++] = static_cast<uint16_t>(pt * C::SLOTS + __builtin_ctz(slots));
+    }
+    __syncthreads();
+    auto put = [&](uint64_t q, double best, uint32_t bi) {
+        const size_t o = static_cast<size_t>(q) * m + j;
+        store_label(labels, label_bytes, o, bi);
+        if (dist) dist[o] = static_cast<float>(best);
+    };
+    // The 64 centroids of a cell, 16 lanes per cell: four lanes read a row together, 16 components at a time (a lane per row has four
+    // times as many requests to the first-level cache, as many as the whole walk can hide).  Distances in fp32
+    // from the differences are within (dsub + 4) 2^-23 of themselves, so usually one centroid is left; only where several are (or the
+    // distance itself is wanted) is double precision needed.
+    const float near = 1.0f + 2.2f * static_cast<float>(dsub + 4) / 8388608.0f;
+    const int l4 = tid & 3, quad = (tid >> 2) & 3;
+    constexpr int ROWS = 4 * C::TPC;                                  // rows per lane quad
+    // row i of a quad in a cell; half: of the lane that held its minimum
+    auto row_of = [](uint32_t cell, int half, int i, int quad) { return (cell * C::TPC + (i >> 2)) * 32 + 8 * (i & 3) + 4 * half + quad; };
+    auto distances = [&](const float *x, uint32_t cell, int half, float (&v)[ROWS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) v[i] = 0.0f;
+#pragma unroll 1
+        for (int o = 4 * l4; o < dsub; o += 16) {
+            float a[4];
+            f4_any b[ROWS];
+            const bool whole = FOURS || o + 4 <= dsub;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] = whole || o + c < dsub ? x[o + c] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {
+                const uint32_t c = row_of(cell, half, i, quad);
+                const float *row = cbj + static_cast<size_t>(c < static_cast<uint32_t>(ncent) ? c : ncent - 1) * dsub + o;
+                if (whole) b[i] = *reinterpret_cast<const f4_any *>(row);
+                else {
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) b[i].v[z] = o + z < dsub ? row[z] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { const float u = a[c] - b[i].v[c]; v[i] = fmaf(u, u, v[i]); }
+        }
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            v[i] += other_of_four<1>(v[i]);
+            v[i] += other_of_four<2>(v[i]);
+            if (row_of(cell, half, i, quad) >= static_cast<uint32_t>(ncent)) v[i] = INFINITY;
+        }
+    };
+    // every cell: its smallest distance (in place of the filter's), and (bits 9 ..) the row that has it: 4 i + quad, or 64 where
+    // several are too close to tell
+    const uint32_t n_items = min(s_count[0], s_count[4]), n_open = s_count[2];
+    for (uint32_t t0 = tid >> 4; t0 < n_items; t0 += 16) {
+        const uint32_t item = items[t0], pt = item / C::SLOTS, slot = item % C::SLOTS, cell = __float_as_uint(ent[item]) & (kCells - 1u);
+        float v[ROWS];
+        distances(points + static_cast<size_t>(q0 + pt) * ld + j * dsub, cell, slot / KEEP, v);
+        float least = v[0];
+#pragma unroll
+        for (int i = 1; i < ROWS; ++i) least = fminf(least, v[i]);
+        least = fminf(least, __shfl_xor(least, 4));
+        least = fminf(least, __shfl_xor(least, 8));
+        const float lim = least * near + 1e-34f;
+        uint32_t found = 0;                                           // number << 16 | sum of their rows
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) found += v[i] <= lim ? 0x10000u + 4 * i + quad : 0u;
+        found += __shfl_xor(found, 4);
+        found += __shfl_xor(found, 8);
+        if ((tid & 15) == 0) {
+            ent[item] = least;
+            res[t0] = static_cast<uint16_t>(cell | (found >> 16 == 1 ? found & 63u : 64u) << 9);
+        }
+    }
+    __syncthreads();
+    // every point: done where one centroid is left
+    auto centroid_of = [&](uint32_t r, uint32_t slot) { const uint32_t row = r >> 9; return row_of(r & (kCells - 1u), slot / KEEP, row >> 2, row & 3); };
+    for (uint32_t pt = tid; pt < np; pt += 256) {
+        const uint32_t slots = has[pt];
+        if (!slots) continue;
+        const float *e = ent + pt * C::SLOTS;
+        float least = INFINITY;
+#pragma unroll
+        for (int k = 0; k < C::SLOTS; ++k) least = slots >> k & 1u ? fminf(least, e[k]) : least;
+        const float lim = least * near + 1e-34f;
+        uint32_t close = 0;
+#pragma unroll
+        for (int k = 0; k < C::SLOTS; ++k) close |= (slots >> k & 1u) && e[k] <= lim ? 1u << k : 0u;
+        const uint32_t slot = __builtin_ctz(close), r = res[first[pt] + __popc(slots & ((1u << slot) - 1u))];
+        if ((close & (close - 1)) == 0 && r >> 9 < 64) {
+            const uint32_t c = centroid_of(r, slot);
+            const uint64_t q = q0 + pt;
+            put(q, dist ? exact_distance(points + static_cast<size_t>(q) * ld + j * dsub, cbj + static_cast<size_t>(c) * dsub, dsub) : 0.0, c);
+        } else {
+            xnorm2[pt] = lim;
+            slow[atomicAdd(&s_count[1], 1u)] = static_cast<uint16_t>(pt);
+        }
+    }
+    __syncthreads();
+    const uint32_t n_slow = s_count[1];
+    for (uint32_t t0 = tid >> 4; t0 < n_slow; t0 += 16) {
+        const uint32_t pt = slow[t0];
+        const uint64_t q = q0 + pt;
+        const float *x = points + static_cast<size_t>(q) * ld + j * dsub;
+        const float lim = xnorm2[pt];
+        double best = INFINITY;
+        uint32_t bi = 0xFFFFFFFFu;
+        uint32_t t = first[pt];
+        for (uint32_t slots = has[pt]; slots; slots &= slots - 1, ++t) {         // (the same for the 16 lanes)
+            const uint32_t slot = __builtin_ctz(slots), r = res[t];
+            if (!(ent[pt * C::SLOTS + slot] <= lim)) continue;
+            if (r >> 9 < 64) {
+                const uint32_t c = centroid_of(r, slot);
+                take_smaller(best, bi, exact_distance(x, cbj + static_cast<size_t>(c) * dsub, dsub), c);
+                continue;
+            }
+            const uint32_t cell = r & (kCells - 1u);
+            float v[ROWS];
+            distances(x, cell, slot / KEEP, v);
+            uint32_t take = 0;
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) take |= v[i] <= lim ? 1u << i : 0u;
+            for (; take; take &= take - 1) {
+                const uint32_t c = row_of(cell, slot / KEEP, __builtin_ctz(take), quad);
+                if (c < static_cast<uint32_t>(ncent)) take_smaller(best, bi, exact_distance(x, cbj + static_cast<size_t>(c) * dsub, dsub), c);
+            }
+        }
+#pragma unroll
+        for (int off = 4; off < 16; off <<= 1) {
+            const double ov = __shfl_xor(best, off);
+            const uint32_t oi = __shfl_xor(bi, off);
+            take_smaller(best, bi, ov, oi);
+        }
+        if ((tid & 15) == 0) put(q, best, bi);
+    }
+    if (n_open == 0) return;                                          // uniform
+
+    // ---- the second walk --------------------------------------------------------------------------------------
+    // 32 points at a time, up to a sixteenth of the workgroup's.  (More than that are open because their windows are crowded: an eighth of points
+    // and centroids zeros, 70000 x 8 x 16, 16384 centroids, 3.6 ms where this walk was tried first.)
+    uint32_t done = 0;
+    if (n_open <= C::PTS / 16 && cmax < INFINITY) {                    // uniform
+        __syncthreads();                                              // the minima are no longer read
+        uint64_t *found = reinterpret_cast<uint64_t *>(smem + C::STAGE_BYTES);                    // (point << 32) | centroid
+        unsigned long long *nearest = reinterpret_cast<unsigned long long *>(found + C::FOUND);       // of every point: distance, then ...
+        uint32_t *which = reinterpret_cast<uint32_t *>(nearest + 32);                             // ... centroid
+        for (; done < n_open; done += 32) {                           // uniform
+            const uint32_t mine = min(32u, n_open - done);
+            __syncthreads();                                          // (nor what the last 32 points left)
+            for (int t = tid; t < 32 * C::STRIDE / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);        // rows: zero past dp
+            __syncthreads();
+            if (srow < 32) {
+                float norm, rest;
+                convert_point(smem + srow * C::STRIDE, q0 + open[done + min(static_cast<uint32_t>(srow), mine - 1)], norm, rest);
+            }
+            if (tid < 32) { nearest[tid] = ~0ull; which[tid] = 0xFFFFFFFFu; }
+            if (tid == 0) s_count[3] = 0;
+            __syncthreads();
+            v8h bx[KH];
+#pragma unroll
+            for (int ks = 0; ks < KH; ++ks) bx[ks] = *reinterpret_cast<const v8h *>(smem + col * C::STRIDE + half * 16 + ks * 32);
+            const float window = static_cast<uint32_t>(col) < mine ? xnorm2[open[done + col]] : -INFINITY;
+            if (!(window < 1e37f)) s_count[3] = C::FOUND + 1;         // (no window: not for this walk)
+            __syncthreads();
+            if (s_count[3] > C::FOUND) break;                         // uniform
+            // (a wavefront reads the centroids of its tiles itself, AHEAD2 tiles ahead, and needs nothing from the others: with stages of the
+            // workgroup as above every one of them waited for its loads, 0.25 ms a walk of 65536)
+            constexpr int AHEAD2 = KH == 1 ? 4 : KH == 2 ? 2 : 1;
+            const int ntiles = (ncent + 31) / 32;
+            float *wnorm = reinterpret_cast<float *>(smem) + wave * 32 * AHEAD2;            // |c|^2 of these tiles
+            float raw[AHEAD2][KH][8];
+            auto component = [&](int ks, int e) { return (C::TWO ? 0 : 16 * ks + 8 * half) + e; };       // of K position 16 ks + 8 half + e
+            auto load_tile = [&](int t, float (&r)[KH][8]) __attribute__((always_inline)) {
+                const int c = t * 32 + col;
+                const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+#pragma unroll
+                for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 4) {
+                        const int o = component(ks, e);
+                        if constexpr (FOURS) {
+                            const f4_any v = *reinterpret_cast<const f4_any *>(src + (o < dsub ? o : 0));
+#pragma unroll
+                            for (int z = 0; z < 4; ++z) r[ks][e + z] = v.v[z];
+                        } else {
+#pragma unroll
+                            for (int z = 0; z < 4; ++z) r[ks][e + z] = src[o + z < dsub ? o + z : 0];
+                        }
+                    }
+            };
+            __syncthreads();                                          // the points' rows are no longer read
+#pragma unroll
+            for (int d = 0; d < AHEAD2; ++d) load_tile(wave + 4 * d, raw[d]);
+            for (int t0 = wave; t0 < ntiles; t0 += 4 * AHEAD2) {      // uniform
+                v8h a[AHEAD2][KH];
+                v16f acc[AHEAD2];
+                float norm[AHEAD2], least = INFINITY;
+#pragma unroll
+                for (int d = 0; d < AHEAD2; ++d) {
+                    norm[d] = 0.0f;
+#pragma unroll
+                    for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const int o = component(ks, e);
+                            float v = fmaf(raw[d][ks][e], scale, mus[o]);
+                            if (o >= dsub) v = 0.0f;
+                            a[d][ks][e] = static_cast<_Float16>(v);
+                            norm[d] = fmaf(v, v, norm[d]);
+                        }
+                    load_tile(t0 + 4 * (d + AHEAD2), raw[d]);
+                }
+#pragma unroll
+                for (int d = 0; d < AHEAD2; ++d) {
+                    if (!C::TWO) norm[d] += __shfl_xor(norm[d], 32);
+                    if (half == 0) wnorm[32 * d + col] = (t0 + 4 * d) * 32 + col < ncent ? norm[d] : 3.0e38f;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+                for (int d = 0; d < AHEAD2; ++d)
+#pragma unroll
+                    for (int v = 0; v < 16; v += 4) {
+                        const float4 x = *reinterpret_cast<const float4 *>(wnorm + 32 * d + 4 * half + 2 * v);
+                        acc[d][v] = x.x; acc[d][v + 1] = x.y; acc[d][v + 2] = x.z; acc[d][v + 3] = x.w;
+                    }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+                for (int d = 0; d < AHEAD2; ++d)
+#pragma unroll
+                    for (int ks = 0; ks < KH; ++ks) acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[d][ks], bx[ks], acc[d], 0, 0, 0);
+#pragma unroll
+                for (int d = 0; d < AHEAD2; ++d) least = minimum(acc[d], least);
+                if (!__builtin_amdgcn_ballot_w64(least <= window)) continue;             // uniform
+#pragma unroll
+                for (int d = 0; d < AHEAD2; ++d)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        if (acc[d][v] <= window) {                    // (not past the last centroid: the window is below 1e37)
+                            const uint32_t to = atomicAdd(&s_count[3], 1u);
+                            if (to < C::FOUND) found[to] = make_key(col, (t0 + 4 * d) * 32 + 8 * (v >> 2) + 4 * half + (v & 3));
+                        }
+            }
+            __syncthreads();
+            const uint32_t nfound = s_count[3];
+            if (nfound > C::FOUND) break;                             // uniform
+            constexpr int PER = C::FOUND / 256;
+            double d[PER];
+#pragma unroll
+            for (int z = 0; z < PER; ++z) {
+                const uint32_t t = tid + 256 * z;
+                if (t >= nfound) continue;
+                const uint32_t p = static_cast<uint32_t>(found[t] >> 32), c = static_cast<uint32_t>(found[t]);
+                d[z] = exact_distance(points + static_cast<size_t>(q0 + open[done + p]) * ld + j * dsub, cbj + static_cast<size_t>(c) * dsub, dsub);
+                atomicMin(&nearest[p], static_cast<unsigned long long>(__double_as_longlong(d[z])));        // (distances are >= +0: they order like their bits)
+            }
+            __syncthreads();
+#pragma unroll
+            for (int z = 0; z < PER; ++z) {
+                const uint32_t t = tid + 256 * z;
+                if (t >= nfound) continue;
+                const uint32_t p = static_cast<uint32_t>(found[t] >> 32);
+                if (static_cast<unsigned long long>(__double_as_longlong(d[z])) == nearest[p]) atomicMin(&which[p], static_cast<uint32_t>(found[t]));
+            }
+            __syncthreads();
+            if (tid < static_cast<int>(mine)) put(q0 + open[done + tid], __longlong_as_double(static_cast<long long>(nearest[tid])), which[tid]);
+        }
+    }
+    while (done < n_open) {                                           // uniform
+        const uint32_t left = n_open - done, base = done;
+        const auto at = [&, base](uint32_t pt) { return q0 + open[base + pt]; };
+        __syncthreads();
+        if (left <= C::Few::PTS) {
+            nearest_by_split_products<KS, 1, C::SPLIT, FOURS>(smem, at, left, points, ld, cbj, j, m, dsub, dp, ncent, labels, label_bytes, dist);
+            done += left;
+        } else {
+            const uint32_t mine = min(left, static_cast<uint32_t>(C::Many::PTS));
+            nearest_by_split_products<KS, C::MANY_P, false, FOURS>(smem, at, mine, points, ld, cbj, j, m, dsub, dp, ncent, labels, label_bytes, dist);
+            done += mine;
+        }
     }
 }
 
@@ -856,6 +1508,28 @@ static int launch_assign_t(const float *points, uint64_t n, int ld, const float 
     return launch_assign_f<KS, P, SPLIT, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
 }
 
+template <int KS, int P, bool FOURS>
+static int launch_half_f(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                         void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    using C = HalfCfg<KS, P>;
+    const auto kernel = &assign_half_kernel<KS, P, FOURS>;
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
+    if (arc) return arc;
+    DCPQ_LAUNCH(kStageTrain, st, (assign_half_kernel<KS, P, FOURS>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
+                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
+    DCPQ_CHECK_LAUNCH("assign_half_kernel");
+    return DCPQ_OK;
+}
+
+template <int KS, int P>
+static int launch_half(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                       void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    if (dp == dsub) return launch_half_f<KS, P, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    return launch_half_f<KS, P, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+}
+
 template <int KS>
 static int launch_assign_ks(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
                             void *labels, int label_bytes, float *dist, hipStream_t st)
@@ -865,6 +1539,22 @@ static int launch_assign_ks(const float *points, uint64_t n, int ld, const float
     // 512 points at d = 16, 290 with 256); below that the four wavefronts split the centroids (2000 points, 8 x 16
     // components: 0.50 ms; 1.3 ms with 256-point tiles, which leave most CUs without work).
     auto enough = [&](int pts) { return (n + pts - 1) / pts * static_cast<uint64_t>(m) >= 512; };
+    // One fp16 product in the filter, where two workgroups per CU can have 512 points or more (256 with sub-vectors above 32 components), of 1024
+    // where these leave no more of the last round idle.  Rows of up to four components have all four bf16 products in one matrix
+    // instruction as it is; above 64 both forms take the same time (30000 x 4 of 84: 7.0 and 6.9 ms, of 128: 13.3 both).  Split products
+    // and this form, 65536 centroids, ms: 250007 x 8 of 16 components (whole numbers) 8.67 and 5.46; 250000 x 8 of 12 10.8 and 5.65; 70000 x 8 of 8 2.53
+    // and 1.87, of 24 5.5 and 3.2; 140000 x 4 of 32 7.6 and 4.15; 30000 x 8 of 64 5.8 and 3.5; 20000 x 16 of 60 9.8 and 5.5; 1024 centroids: 250000 x 8
+    // of 16 0.93 and 0.86.  Where every centroid repeats or all are close together, 4 to 7 % slower.
+    if constexpr (KS > 1 && KS <= 12) {
+        constexpr int P = KS <= 3 ? 8 : KS <= 6 ? 4 : 2, PTS = HalfCfg<KS, P>::PTS;
+        auto rounds = [&](int pts) { return ((n + pts - 1) / pts * static_cast<uint64_t>(m) + 511) / 512; };
+        if (ncent <= static_cast<int>(kCells * 32 * HalfCfg<KS, P>::TPC)) {
+            if constexpr (P == 8) {
+                if (enough(PTS / 2) && (!enough(PTS) || rounds(PTS / 2) * 11 < rounds(PTS) * 20)) return launch_half<KS, P / 2>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+            }
+            if (enough(PTS)) return launch_half<KS, P>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+        }
+    }
     if constexpr (KS <= 6) {
         if (enough(AssignCfg<KS, 4, false>::PTS)) return launch_assign_t<KS, 4, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
     }

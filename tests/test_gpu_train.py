@@ -344,3 +344,48 @@ def test_training_argument_errors():
         binding.kmeans_same_size(p, p[:8].clone(), 1)            # 100 is not a multiple of 8
     with pytest.raises(binding.DcpqError):
         binding.build_quantizers(p, torch.zeros((1, 4096, 4), device=DEV), 8, 1, 1)     # b = 12
+
+
+@pytest.mark.parametrize("dsub,m", [(5, 4), (8, 8), (12, 8), (16, 8), (21, 8), (32, 8), (40, 8), (52, 8), (60, 8), (64, 8)])
+@pytest.mark.parametrize("data", ["normal", "bytes", "near", "repeats", "offset", "outlier"])
+def test_assign_of_many_points_agrees_with_few(dsub, m, data):
+    # From 2^18 sub-vectors on (2^17 above 32 components) the filter has one fp16 product; few points take other kernels: the same labels and bits of
+    # the distances.  "near": points whose window holds many centroids of many cells (the second walk), "repeats" and "offset": too
+    # many for that, values that are not finite; "outlier": a centroid and a point far outside the range of fp16.  Point and centroid
+    # counts that no tile divides.
+    print("assign many points dsub=%d m=%d %s" % (dsub, m, data), flush=True)
+    g = gen(dsub + 1000 * len(data))
+    n, ncent = 517, 1337
+    pts = torch.randn((n, m * dsub), generator=g, device=DEV)
+    cb = torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    if data == "bytes":
+        pts = (40 * pts + 120).clamp(0, 255).round()
+        cb = (40 * cb + 120).clamp(0, 255).round()
+        cb[:, 3:n + 3] = pts.view(n, m, dsub).transpose(0, 1)
+    elif data == "near":                                         # 40 centroids all over the codebook within 1e-4 of one of them
+        cb[:, 7::33] = 3.0 + cb[:, 7:8] + 1e-4 * torch.randn(cb[:, 7::33].shape, generator=g, device=DEV)
+        pts.view(n, m, dsub)[::61] = 3.0 + cb[:, 7][None] + 1e-3 * torch.randn((len(range(0, n, 61)), m, dsub), generator=g, device=DEV)
+    elif data == "repeats":
+        cb = cb[:, torch.randint(0, 7, (ncent,), generator=g, device=DEV)].contiguous()
+        pts[5, dsub // 2], pts[7, 0] = float("nan"), float("inf")
+    elif data == "offset":
+        cb, pts = 3000.0 + 1e-3 * cb, 3000.0 + 1e-3 * pts
+        cb[0, 17, 0] = float("nan")
+    elif data == "outlier":
+        cb[0, 77] *= 1e6
+        pts[3] *= 1e5
+    times = ((1 << 18) // m + n) // n + 1 + (300 if data == "normal" else 0)
+    few, few_dist = binding.assign(pts, cb, want_dist=True)
+    many, many_dist = binding.assign(pts.repeat(times, 1), cb, want_dist=True)
+    many2 = binding.assign(pts.repeat(times, 1), cb)
+    torch.cuda.synchronize()
+    for got in (many, many2):
+        np.testing.assert_array_equal(to_np(got), to_np(few.repeat(times, 1)))
+    np.testing.assert_array_equal(to_np(many_dist), to_np(few_dist.repeat(times, 1)))
+    p64, c64 = pts.double().view(n, m, dsub).cpu(), cb.double().cpu()
+    fine = torch.isfinite(p64).all(2).all(1).numpy()
+    for j in range(m):
+        d2 = ((p64[:, j, None, :] - c64[j][None]) ** 2).sum(2).numpy()[fine]
+        best = np.nanmin(d2, 1)
+        chosen = d2[np.arange(fine.sum()), to_np(few)[fine, j]]
+        assert (chosen <= best * (1 + 4 * (dsub + 1) * 2.0 ** -53)).all(), "sub-quantizer %d" % j
