@@ -21,6 +21,7 @@
 // Workgroups walk a list of (query tile, block of 4 units) items with a grid stride, so the same
 // launch shape serves "all queries" and "the few flagged queries" (count read on the device).
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include <mutex>
@@ -53,8 +54,9 @@ struct TileEnd {
     bool guess;             // a guess below the bound is asked for too
 };
 
-template <int M, int QT, int MODE, typename CodeT>
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+// WAVES: wavefronts, and units of codes, per workgroup.
+template <int M, int QT, int MODE, typename CodeT, int WAVES = kScanWaves>
+__global__ __launch_bounds__(64 * WAVES) void scan_kernel(
     const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t unit_stride,
     const uint8_t *__restrict__ qtab, int nq_host, const int *__restrict__ qlist,
     const uint32_t *__restrict__ nq_dev, uint32_t r,
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nq = nq_dev ? static_cast<int>(*nq_dev) : nq_host;
-    const uint32_t nxb = (nunits + kScanWaves - 1) / kScanWaves;
+    const uint32_t nxb = (nunits + WAVES - 1) / WAVES;
     const uint64_t nitems = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb;
 
     for (uint64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
@@ -84,13 +86,13 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
             const int qid = qlist ? qlist[q0 + q] : q0 + q;
             const uint4 *src = reinterpret_cast<const uint4 *>(qtab + static_cast<size_t>(qid) * M * 256);
             uint4 *dst = reinterpret_cast<uint4 *>(ltab + q * M * 256);
-            for (int v = tid; v < M * 256 / 16; v += kScanThreads) dst[v] = src[v];
+            for (int v = tid; v < M * 256 / 16; v += 64 * WAVES) dst[v] = src[v];
         }
         if (MODE == kHist)
-            for (int v = tid; v < QT * 256; v += kScanThreads) lhist[v] = 0;
+            for (int v = tid; v < QT * 256; v += 64 * WAVES) lhist[v] = 0;
         __syncthreads();
 
-        const uint32_t u = xb * kScanWaves + wave;          // this wavefront's unit
+        const uint32_t u = xb * WAVES + wave;          // this wavefront's unit
         const uint64_t begin = static_cast<uint64_t>(u) * unit_stride;
         const uint64_t end = (u < nunits) ? min(n_codes, begin + unit) : begin;
 
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
 
         if (MODE == kHist) {
             __syncthreads();
-            for (int v = tid; v < nqt * 256; v += kScanThreads) {
+            for (int v = tid; v < nqt * 256; v += 64 * WAVES) {
                 const uint32_t c = lhist[v];
                 if (c) atomicAdd(&hist[static_cast<size_t>(q0) * 256 + v], c);
             }
@@ -181,14 +183,14 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
             __syncthreads();
             if (mine) {                                               // uniform
                 if (MODE == kHist) {
-                    for (int q = wave; q < nqt; q += kScanWaves) {
+                    for (int q = wave; q < nqt; q += WAVES) {
                         const uint32_t *h = hist + static_cast<size_t>(q0 + q) * 256;
                         if (end_of.bound && end_of.guess) starting_bound<true>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
                         else if (end_of.bound) starting_bound<false>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
                         else exact_threshold(h, r, end_of.thr + 2 * (q0 + q));
                     }
                 } else {
-                    for (int q = wave; q < nqt; q += kScanWaves)
+                    for (int q = wave; q < nqt; q += WAVES)
                         tie_quotas(tie + static_cast<size_t>(q0 + q) * nunits, nunits, end_of.thr[2 * (q0 + q) + 1]);
                 }
             }
@@ -479,20 +481,20 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t
     return p;
 }
 
-template <int M, int MODE, typename CodeT>
+template <int M, int MODE, int WAVES = kScanWaves, typename CodeT>
 static void launch_scan_pass(int stage, const CodeT *codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
                              uint64_t stride, const uint8_t *qtab, int nq, const int *qlist, const uint32_t *nq_dev,
                              uint32_t r, uint32_t *hist, const uint32_t *thr, uint32_t *tie, uint32_t *counter,
                              uint64_t *keys, const TileEnd &end_of, bool few_expected, hipStream_t st)
 {
     constexpr int QT = scan_qt(M);
-    const uint64_t nxb = (nunits + kScanWaves - 1) / kScanWaves;
+    const uint64_t nxb = (nunits + WAVES - 1) / WAVES;
     const uint64_t items = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb;
     // Redo launches expect few (usually zero) active queries: keep the grid small, it strides.
     const uint64_t most = few_expected ? 4096 : (1u << 20);
     const uint32_t grid = static_cast<uint32_t>(items < most ? (items ? items : 1) : most);
     const size_t lds = static_cast<size_t>(QT) * M * 256 + (MODE == kHist ? QT * 256 * 4 : 0);
-    DCPQ_LAUNCH(stage, st, (scan_kernel<M, QT, MODE, CodeT>), dim3(grid), dim3(kScanThreads), lds, codes, n_codes, unit,
+    DCPQ_LAUNCH(stage, st, (scan_kernel<M, QT, MODE, CodeT, WAVES>), dim3(grid), dim3(64 * WAVES), lds, codes, n_codes, unit,
                 nunits, stride, qtab, nq, qlist, nq_dev, r, hist, thr, tie, counter, keys, end_of);
 }
 
@@ -544,13 +546,32 @@ static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t
     return DCPQ_OK;
 }
 
+// The sample's histogram: wavefronts per workgroup.  They share the tables of a tile, 48 KB of LDS with the counts at m = 8: with four of them a CU holds 12,
+// with 16 as many as it can.  But a CU that gets one workgroup more than the others is the last one: the fewest units per CU
+// decide, and more wavefronts per workgroup where these are equal (251 queries, 65536 codes, m = 8: 46 us with four, 33 with 16; 136 queries, m = 16, 17 tiles
+// of 256 units, where 16 make 272 workgroups: 12 us more).
+static int sample_waves(uint64_t tiles, uint64_t units)
+{
+    auto per_cu = [&](uint64_t waves) { return (tiles * ((units + waves - 1) / waves) + 255) / 256 * waves; };
+    const uint64_t c4 = per_cu(4), c8 = per_cu(8), c16 = per_cu(16);
+    return c16 <= c8 && c16 <= c4 ? 16 : c8 <= c4 ? 8 : 4;
+}
+
 template <int M, typename CodeT>
 static int launch_sample_hist_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r,
                                 uint32_t *shist, const ScanPlan &p, const TileEnd &end_of, hipStream_t st)
 {
     // (with a pilot pass: runs 0, kPilotEvery, 2 kPilotEvery, ... of the sample)
-    launch_scan_pass<M, kHist>(kStageScanHist, codes, n_codes, p.s_unit, p.s1_nunits, p.pilot ? p.s_stride * kPilotEvery : p.s_stride,
-                               qtab, nq, nullptr, nullptr, r, shist, nullptr, nullptr, nullptr, nullptr, end_of, false, st);
+    const uint64_t stride = p.pilot ? p.s_stride * kPilotEvery : p.s_stride;
+    auto launch = [&](auto waves) {
+        launch_scan_pass<M, kHist, decltype(waves)::value>(kStageScanHist, codes, n_codes, p.s_unit, p.s1_nunits, stride, qtab, nq, nullptr, nullptr, r, shist, nullptr, nullptr,
+                                                           nullptr, nullptr, end_of, false, st);
+    };
+    switch (sample_waves((nq + scan_qt(M) - 1) / scan_qt(M), p.s1_nunits)) {
+    case 16: launch(std::integral_constant<int, 16>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    default: launch(std::integral_constant<int, kScanWaves>{});
+    }
     DCPQ_CHECK_LAUNCH("scan_kernel<sample hist>");
     return DCPQ_OK;
 }
