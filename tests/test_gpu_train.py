@@ -389,3 +389,26 @@ def test_assign_of_many_points_agrees_with_few(dsub, m, data):
         best = np.nanmin(d2, 1)
         chosen = d2[np.arange(fine.sum()), to_np(few)[fine, j]]
         assert (chosen <= best * (1 + 4 * (dsub + 1) * 2.0 ** -53)).all(), "sub-quantizer %d" % j
+
+
+@pytest.mark.parametrize("iters_same", [1, 2])
+def test_training_where_a_balanced_assignment_takes_more_rounds_than_it_is_given(iters_same):
+    # Sub-quantizers 0 and 2: sixteen groups in a row and all other centroids before the first of them, so that a round fills one
+    # group and sixteen are needed (twelve are enqueued ahead); 1 and 3: a few rounds.  The same codebooks as step by step.
+    m, dsub, b, bbar = 4, 4, 8, 4
+    g = gen(71)
+    init = torch.randint(-300, 300, (m, 1 << b, dsub), generator=g, device=DEV).float() / 64.0        # (sums of these are exact)
+    for j in (0, 2):
+        init[j] = 0.0
+        init[j, :, 1] = torch.arange(1 << b, device=DEV) / 1024.0
+        init[j, :16, 0] = torch.arange(1, 17, device=DEV).float()
+    x = torch.randn((300, m * dsub), generator=g, device=DEV)
+    cb, derived = binding.build_quantizers(x, init, bbar, 0, iters_same)
+    torch.cuda.synchronize()
+    for j in range(m):
+        _, labels = binding.kmeans_same_size(init[j].contiguous(), init[j, :1 << bbar].contiguous(), iters_same)
+        final, _ = binding.build_final_codebook(init[j].contiguous(), labels, bbar)
+        np.testing.assert_array_equal(to_np(cb)[j], to_np(final), err_msg="sub-quantizer %d" % j)
+        lab, _ = oracle.kmeans_same_size(to_np(init[j]), to_np(init[j, :1 << bbar]), iters_same)[::-1]
+        np.testing.assert_array_equal(to_np(labels), lab)
+    np.testing.assert_array_equal(to_np(derived), to_np(binding.derive_codebooks(cb, bbar)))
