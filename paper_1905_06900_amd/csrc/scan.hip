@@ -18,8 +18,8 @@
 // at a time (lane = code, fully coalesced 2m-byte loads), so id order inside a unit is
 // (iteration, lane).  A workgroup is 4 wavefronts and serves a tile of QT queries whose u8 tables
 // (QT * m * 256 bytes) sit in LDS; each lane gathers its m table bytes per query from LDS.
-// Workgroups walk a list of (query tile, block of 4 units) items with a grid stride, so the same
-// launch shape serves "all queries" and "the few flagged queries" (count read on the device).
+// Over a whole batch the passes are launches of their own; for the few flagged queries (as a rule none, their number is known on the
+// device only) all of them and the sort are one launch (scan_redo_kernel).
 #include <cmath>
 #include <type_traits>
 
@@ -38,140 +38,153 @@ enum ScanMode { kHist = 0, kTieCount = 1, kCollect = 2 };
 // Queries are addressed by their position p in the active list: query id = qlist ? qlist[p] : p.
 // Workspace arrays (hist, thr, tie, counter, keys) are indexed by p; qtab by the query id.
 // CodeT: uint16_t (the codes as stored) or uint8_t (their low-byte plane).
-// The short step that follows a histogram or a tie count is done by the workgroup that finishes a query tile last
-// (done: one counter per tile, at zero on entry), which saves a launch of its own (4.5 us each on a stream of
-// short kernels):
-//   sample histogram   starting bounds (starting_bound, with want_r, want_n and crowded)
-//   histogram          thr = (bucket of the r-th smallest, ids still needed from it)
-//   tie count          counts of the bucket per unit -> quotas per unit, in place
+struct ScanArrays {
+    const uint8_t *qtab;
+    const int *qlist;       // NULL: all queries
+    uint32_t r;
+    uint32_t *hist;         // [nq][256]     (kHist: accumulated)
+    uint32_t *thr;          // [nq][2]       (kTieCount, kCollect: read)
+    uint32_t *tie;          // [nq][nunits]  (kTieCount: counts out; kCollect: quotas in)
+    uint32_t *counter;      // [nq]          (kCollect)
+    uint64_t *keys;         // [nq][r]       (kCollect)
+};
+
+// The starting bounds are taken by the workgroup that finishes a query tile of the sample's histogram last, which saves a launch (4.5 us on
+// a stream of short kernels).
 struct TileEnd {
-    uint32_t *done;         // NULL: nothing follows
-    Bound *bound;           // NULL unless this is the sample histogram
-    uint32_t *thr;
-    uint32_t want_r;
+    uint32_t *done;         // a counter per tile, at zero on entry and again at the end; NULL: nothing follows
+    Bound *bound;
+    uint32_t want_r;        // of starting_bound
     uint64_t want_n;
     Crowded crowded;
     bool guess;             // a guess below the bound is asked for too
 };
 
-// WAVES: wavefronts, and units of codes, per workgroup.
-template <int M, int QT, int MODE, typename CodeT, int WAVES = kScanWaves>
-__global__ __launch_bounds__(64 * WAVES) void scan_kernel(
-    const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t unit_stride,
-    const uint8_t *__restrict__ qtab, int nq_host, const int *__restrict__ qlist,
-    const uint32_t *__restrict__ nq_dev, uint32_t r,
-    uint32_t *__restrict__ hist,        // [nq][256]          (kHist: accumulated)
-    const uint32_t *__restrict__ thr,   // [nq][2]            (kTieCount, kCollect: read)
-    uint32_t *__restrict__ tie,         // [nq][nunits]       (kTieCount: counts out; kCollect: quotas in)
-    uint32_t *__restrict__ counter,     // [nq]               (kCollect)
-    uint64_t *__restrict__ keys,        // [nq][r]            (kCollect)
-    const TileEnd end_of)               // what follows when all workgroups of a query tile have finished
+template <typename T>
+__device__ inline T agent_load(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ inline void agent_store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// One item of a pass: WAVES units (from unit xb * WAVES on) for the queries at positions q0 .. q0 + QT - 1, by a workgroup.
+// REDO: passes run in one launch, and what one of them leaves for the next goes through device-scope stores and loads.
+template <int M, int QT, int MODE, typename CodeT, int WAVES, bool REDO>
+__device__ __forceinline__ void scan_item(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t unit_stride, int q0, int nqt,
+                                          uint32_t xb, const ScanArrays &w, uint8_t *smem)
 {
-    extern __shared__ __align__(16) uint8_t smem[];
     uint8_t *ltab = smem;                                                   // [QT][M][256]
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + QT * M * 256);    // [QT][256] (kHist)
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nq = nq_dev ? static_cast<int>(*nq_dev) : nq_host;
-    const uint32_t nxb = (nunits + WAVES - 1) / WAVES;
-    const uint64_t nitems = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb;
 
-    for (uint64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
-        const int q0 = static_cast<int>(item / nxb) * QT;
-        const uint32_t xb = static_cast<uint32_t>(item % nxb);
-        const int nqt = min(QT, nq - q0);
+    __syncthreads();                           // previous item's LDS is no longer in use
+    for (int q = 0; q < nqt; ++q) {            // stage the tile's tables (rows of absent queries are never read)
+        const int qid = w.qlist ? w.qlist[q0 + q] : q0 + q;
+        const uint4 *src = reinterpret_cast<const uint4 *>(w.qtab + static_cast<size_t>(qid) * M * 256);
+        uint4 *dst = reinterpret_cast<uint4 *>(ltab + q * M * 256);
+        for (int v = tid; v < M * 256 / 16; v += 64 * WAVES) dst[v] = src[v];
+    }
+    if (MODE == kHist)
+        for (int v = tid; v < QT * 256; v += 64 * WAVES) lhist[v] = 0;
+    __syncthreads();
 
-        __syncthreads();                       // previous item's LDS is no longer in use
-        for (int q = 0; q < nqt; ++q) {        // stage the tile's tables (rows of absent queries are never read)
-            const int qid = qlist ? qlist[q0 + q] : q0 + q;
-            const uint4 *src = reinterpret_cast<const uint4 *>(qtab + static_cast<size_t>(qid) * M * 256);
-            uint4 *dst = reinterpret_cast<uint4 *>(ltab + q * M * 256);
-            for (int v = tid; v < M * 256 / 16; v += 64 * WAVES) dst[v] = src[v];
+    const uint32_t u = xb * WAVES + wave;               // this wavefront's unit
+    const uint64_t begin = static_cast<uint64_t>(u) * unit_stride;
+    const uint64_t end = (u < nunits) ? min(n_codes, begin + unit) : begin;
+
+    uint32_t T[QT], aux[QT];   // threshold bucket; kTieCount: running count, kCollect: quota left
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        T[q] = 0; aux[q] = 0;
+        if (MODE != kHist && q < nqt) {
+            const uint32_t *t = w.thr + 2 * (q0 + q), *e = w.tie + static_cast<size_t>(q0 + q) * nunits + u;
+            T[q] = REDO ? agent_load(t) : *t;
+            if (MODE == kCollect && u < nunits) aux[q] = REDO ? agent_load(e) : *e;
         }
-        if (MODE == kHist)
-            for (int v = tid; v < QT * 256; v += 64 * WAVES) lhist[v] = 0;
-        __syncthreads();
+    }
 
-        const uint32_t u = xb * WAVES + wave;          // this wavefront's unit
-        const uint64_t begin = static_cast<uint64_t>(u) * unit_stride;
-        const uint64_t end = (u < nunits) ? min(n_codes, begin + unit) : begin;
-
-        uint32_t T[QT], aux[QT];   // threshold bucket; kTieCount: running count, kCollect: quota left
+    for (uint64_t base = begin; base < end; base += kWave) {
+        const uint64_t i = base + lane;
+        const bool live = i < end;
+        uint32_t low[M];
+        if (live) {
+            load_low_bytes<M>(codes, i, low);
+        } else {
+#pragma unroll
+            for (int j = 0; j < M; ++j) low[j] = 0;
+        }
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
-            T[q] = 0; aux[q] = 0;
-            if (MODE != kHist && q < nqt) {
-                T[q] = thr[2 * (q0 + q)];
-                if (MODE == kCollect && u < nunits) aux[q] = tie[static_cast<size_t>(q0 + q) * nunits + u];
-            }
-        }
-
-        for (uint64_t base = begin; base < end; base += kWave) {
-            const uint64_t i = base + lane;
-            const bool live = i < end;
-            uint32_t low[M];
-            if (live) {
-                load_low_bytes<M>(codes, i, low);
+            if (q >= nqt) continue;                               // uniform
+            const uint8_t *t = ltab + q * (M * 256);
+            uint32_t s = 0;
+#pragma unroll
+            for (int j = 0; j < M; ++j) s += t[j * 256 + low[j]];
+            const uint32_t qd = min(s, 255u);                     // saturate: 255 = beyond qmax
+            if (MODE == kHist) {
+                if (live) atomicAdd(&lhist[q * 256 + qd], 1u);
+            } else if (MODE == kTieCount) {
+                aux[q] += __popcll(__ballot(live && qd == T[q]));
             } else {
-#pragma unroll
-                for (int j = 0; j < M; ++j) low[j] = 0;
-            }
-#pragma unroll
-            for (int q = 0; q < QT; ++q) {
-                if (q >= nqt) continue;                               // uniform
-                const uint8_t *t = ltab + q * (M * 256);
-                uint32_t s = 0;
-#pragma unroll
-                for (int j = 0; j < M; ++j) s += t[j * 256 + low[j]];
-                const uint32_t qd = min(s, 255u);                     // saturate: 255 = beyond qmax
-                if (MODE == kHist) {
-                    if (live) atomicAdd(&lhist[q * 256 + qd], 1u);
-                } else if (MODE == kTieCount) {
-                    aux[q] += __popcll(__ballot(live && qd == T[q]));
-                } else {
-                    const bool below = live && qd < T[q];
-                    const bool tied = live && qd == T[q];
-                    const uint64_t tied_mask = __ballot(tied);
-                    bool take = below;
-                    if (tied_mask) {                                  // uniform
-                        const uint32_t rank = __popcll(tied_mask & ((1ull << lane) - 1ull));
-                        take = below || (tied && rank < aux[q]);
-                        const uint32_t n_tied = __popcll(tied_mask);
-                        aux[q] = aux[q] > n_tied ? aux[q] - n_tied : 0u;
-                    }
-                    const uint64_t take_mask = __ballot(take);
-                    if (take_mask) {                                  // uniform, rare
-                        const uint32_t n_take = __popcll(take_mask);
-                        uint32_t slot0 = 0;
-                        if (lane == 0) slot0 = atomicAdd(&counter[q0 + q], n_take);
-                        slot0 = __shfl(slot0, 0, kWave);
-                        if (take) {
-                            const uint32_t slot = slot0 + __popcll(take_mask & ((1ull << lane) - 1ull));
-                            if (slot < r)   // exactly r ids are taken over the whole scan; guard anyway
-                                keys[static_cast<size_t>(q0 + q) * r + slot] = make_key(qd, static_cast<uint32_t>(i));
+                const bool below = live && qd < T[q];
+                const bool tied = live && qd == T[q];
+                const uint64_t tied_mask = __ballot(tied);
+                bool take = below;
+                if (tied_mask) {                                  // uniform
+                    const uint32_t rank = __popcll(tied_mask & ((1ull << lane) - 1ull));
+                    take = below || (tied && rank < aux[q]);
+                    const uint32_t n_tied = __popcll(tied_mask);
+                    aux[q] = aux[q] > n_tied ? aux[q] - n_tied : 0u;
+                }
+                const uint64_t take_mask = __ballot(take);
+                if (take_mask) {                                  // uniform, rare
+                    const uint32_t n_take = __popcll(take_mask);
+                    uint32_t slot0 = 0;
+                    if (lane == 0) slot0 = atomicAdd(&w.counter[q0 + q], n_take);
+                    slot0 = __shfl(slot0, 0, kWave);
+                    if (take) {
+                        const uint32_t slot = slot0 + __popcll(take_mask & ((1ull << lane) - 1ull));
+                        if (slot < w.r) { // exactly r ids are taken over the whole scan; guard anyway
+                            uint64_t *to = w.keys + static_cast<size_t>(q0 + q) * w.r + slot;
+                            if (REDO) agent_store(to, make_key(qd, static_cast<uint32_t>(i)));
+                            else *to = make_key(qd, static_cast<uint32_t>(i));
                         }
                     }
                 }
             }
         }
+    }
 
-        if (MODE == kHist) {
-            __syncthreads();
-            for (int v = tid; v < nqt * 256; v += 64 * WAVES) {
-                const uint32_t c = lhist[v];
-                if (c) atomicAdd(&hist[static_cast<size_t>(q0) * 256 + v], c);
-            }
-        } else if (MODE == kTieCount) {
-            if (u < nunits && lane == 0) {
-#pragma unroll
-                for (int q = 0; q < QT; ++q)
-                    if (q < nqt) __hip_atomic_store(&tie[static_cast<size_t>(q0 + q) * nunits + u], aux[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+    if (MODE == kHist) {
+        __syncthreads();
+        for (int v = tid; v < nqt * 256; v += 64 * WAVES) {
+            const uint32_t c = lhist[v];
+            if (c) atomicAdd(&w.hist[static_cast<size_t>(q0) * 256 + v], c);
         }
+    } else if (MODE == kTieCount) {
+        if (u < nunits && lane == 0) {
+#pragma unroll
+            for (int q = 0; q < QT; ++q)
+                if (q < nqt) agent_store(&w.tie[static_cast<size_t>(q0 + q) * nunits + u], aux[q]);
+        }
+    }
+}
 
-        if (MODE != kCollect && end_of.done) {
+// WAVES: wavefronts, and units of codes, per workgroup.
+template <int M, int QT, int MODE, typename CodeT, int WAVES = kScanWaves>
+__global__ __launch_bounds__(64 * WAVES) void scan_kernel(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
+                                                          uint64_t unit_stride, int nq, const ScanArrays w, const TileEnd end_of)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t nxb = (nunits + WAVES - 1) / WAVES;
+    const uint64_t nitems = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb;
+
+    for (uint64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const int q0 = static_cast<int>(item / nxb) * QT;
+        const int nqt = min(QT, nq - q0);
+        scan_item<M, QT, MODE, CodeT, WAVES, false>(codes, n_codes, unit, nunits, unit_stride, q0, nqt, static_cast<uint32_t>(item % nxb), w, smem);
+        if (MODE == kHist && end_of.done) {
             // Everything this workgroup has added is in place before its count is.  (Histograms are only added to by
-            // device-scope atomics, and tie counts written by device-scope stores, whose completion is all there is to wait
+            // device-scope atomics, whose completion is all there is to wait
             // for; a release fence would write back the second-level cache once per workgroup: 100 us for the sample of 251
             // queries.)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -182,23 +195,101 @@ __global__ __launch_bounds__(64 * WAVES) void scan_kernel(
             const bool mine = *last != 0;
             __syncthreads();
             if (mine) {                                               // uniform
-                if (MODE == kHist) {
-                    for (int q = wave; q < nqt; q += WAVES) {
-                        const uint32_t *h = hist + static_cast<size_t>(q0 + q) * 256;
-                        if (end_of.bound && end_of.guess) starting_bound<true>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
-                        else if (end_of.bound) starting_bound<false>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
-                        else exact_threshold(h, r, end_of.thr + 2 * (q0 + q));
-                    }
-                } else {
-                    for (int q = wave; q < nqt; q += WAVES)
-                        tie_quotas(tie + static_cast<size_t>(q0 + q) * nunits, nunits, end_of.thr[2 * (q0 + q) + 1]);
+                if (tid == 0) agent_store(&end_of.done[q0 / QT], 0u);
+                for (int q = wave; q < nqt; q += WAVES) {
+                    const uint32_t *h = w.hist + static_cast<size_t>(q0 + q) * 256;
+                    if (end_of.guess) starting_bound<true>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
+                    else starting_bound<false>(h, end_of.want_r, end_of.want_n, end_of.crowded, end_of.bound + q0 + q);
                 }
             }
         }
     }
 }
 
-// The same steps as kernels of their own, a wavefront per query: for the inverted-list variant, and for three passes over
+// The three passes and the sort for the flagged queries qlist[0 .. *nflag), in one launch: as four of them, where nothing is flagged, which is
+// the rule, each took 4.5 us.
+// Items are handed out in order -- the histogram's of all query tiles, then the tie counts', the collection's, the queries
+// to sort -- by one counter, and an item waits for those of the pass before it: these have been handed out already, to workgroups that are running
+// and wait, if at all, for items handed out earlier still, so that every wait ends whatever number of workgroups the chip holds at a time.
+// What one item leaves for another goes through device-scope atomics, stores and loads, and is in place before the item is counted as done.
+// sync: [3][tiles] items that are done, of each pass (one more once thresholds or quotas are there); ticket: the counter (both at zero on entry).
+template <int M, int QT, typename CodeT>
+__global__ __launch_bounds__(kScanThreads) void scan_redo_kernel(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
+                                                                 const uint32_t *__restrict__ nflag, const ScanArrays w, uint32_t *done_hist, uint32_t *done_tie,
+                                                                 uint32_t *done_collect, unsigned long long *ticket, uint32_t n_pow2, int use_lds,
+                                                                 uint64_t *__restrict__ spill, uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
+{
+    const int nq = static_cast<int>(*nflag);
+    if (nq == 0) return;
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ unsigned long long s_item;
+    __shared__ uint32_t s_last;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t nxb = (nunits + kScanWaves - 1) / kScanWaves;
+    const uint64_t per = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb, all = 3 * per + nq;
+    auto wait_for = [&](const uint32_t *count, uint32_t n) {
+        if (tid == 0)
+            while (agent_load(count) != n) __builtin_amdgcn_s_sleep(16);
+        __syncthreads();
+    };
+    // counts the item; true for the one that ends its tile
+    auto finished = [&](uint32_t *count) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(count, 1u) == nxb - 1;
+        __syncthreads();
+        return s_last != 0;
+    };
+    auto ready = [&](uint32_t *count) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) atomicAdd(count, 1u);
+    };
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) s_item = atomicAdd(ticket, 1ull);
+        __syncthreads();
+        const uint64_t item = s_item;
+        if (item >= all) return;                                      // uniform
+        if (item < 3 * per) {
+            const uint64_t in_pass = item % per;
+            const uint32_t tile = static_cast<uint32_t>(in_pass / nxb), xb = static_cast<uint32_t>(in_pass % nxb);
+            const int q0 = static_cast<int>(tile) * QT, nqt = min(QT, nq - q0);
+            if (item < per) {
+                scan_item<M, QT, kHist, CodeT, kScanWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                if (finished(&done_hist[tile])) {                     // uniform
+                    for (int q = wave; q < nqt; q += kScanWaves) exact_threshold(w.hist + static_cast<size_t>(q0 + q) * 256, w.r, w.thr + 2 * (q0 + q));
+                    ready(&done_hist[tile]);
+                }
+            } else if (item < 2 * per) {
+                wait_for(&done_hist[tile], nxb + 1);
+                scan_item<M, QT, kTieCount, CodeT, kScanWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                if (finished(&done_tie[tile])) {                      // uniform
+                    for (int q = wave; q < nqt; q += kScanWaves)
+                        tie_quotas(w.tie + static_cast<size_t>(q0 + q) * nunits, nunits, agent_load(&w.thr[2 * (q0 + q) + 1]));
+                    ready(&done_tie[tile]);
+                }
+            } else {
+                wait_for(&done_tie[tile], nxb + 1);
+                scan_item<M, QT, kCollect, CodeT, kScanWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                finished(&done_collect[tile]);
+            }
+            continue;
+        }
+        const int p = static_cast<int>(item - 3 * per);
+        wait_for(&done_collect[p / QT], nxb);
+        uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(p) * n_pow2;
+        for (uint32_t t = tid; t < n_pow2; t += kScanThreads) a[t] = t < w.r ? agent_load(&w.keys[static_cast<size_t>(p) * w.r + t]) : ~0ull;
+        bitonic_sort(a, n_pow2);
+        const size_t out = static_cast<size_t>(w.qlist[p]) * w.r;
+        for (uint32_t t = tid; t < w.r; t += kScanThreads) {
+            cand_id[out + t] = static_cast<uint32_t>(a[t]);
+            cand_qd[out + t] = static_cast<uint8_t>(a[t] >> 32);
+        }
+    }
+}
+
+// Thresholds and quotas as kernels of their own, a wavefront per query: for three passes over
 // all queries of a batch, where the launches are worth it (each tile's queries would wait for the one workgroup that ends
 // it: 21 queries over 1.6 M codes of one sub-code 738 us, 153 this way; 138 queries over 0.26 M 153 and 140).
 __global__ __launch_bounds__(256) void threshold_kernel(const uint32_t *__restrict__ hist, int nq, uint32_t r, uint32_t *__restrict__ thr)
@@ -213,30 +304,23 @@ __global__ __launch_bounds__(64) void tie_quota_kernel(uint32_t *__restrict__ ti
     tie_quotas(tie + static_cast<size_t>(q) * nunits, nunits, thr[2 * q + 1]);
 }
 
-// Sort the r collected keys of each active query by (qd, id) and split them into the two outputs.
+// Sort the r collected keys of each query (of those with a flag, where there are flags) by (qd, id) and split them into the two outputs.
 // use_lds: the padded array fits the dynamic LDS allocation; otherwise it is sorted in `spill`.
-__global__ __launch_bounds__(1024) void sort_candidates_kernel(const uint64_t *__restrict__ keys, uint32_t r,
-                                                              uint32_t n_pow2, int use_lds,
-                                                              uint64_t *__restrict__ spill,
-                                                              const int *__restrict__ qlist,
-                                                              const uint32_t *__restrict__ nq_dev,
-                                                              const uint32_t *__restrict__ flags,
-                                                              uint32_t *__restrict__ cand_id,
-                                                              uint8_t *__restrict__ cand_qd)
+__global__ __launch_bounds__(1024) void sort_candidates_kernel(const uint64_t *__restrict__ keys, uint32_t r, uint32_t n_pow2, int use_lds,
+                                                              uint64_t *__restrict__ spill, const uint32_t *__restrict__ flags,
+                                                              uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
 {
     extern __shared__ __align__(16) uint8_t smem[];
-    const int p = blockIdx.x;
-    if (nq_dev && p >= static_cast<int>(*nq_dev)) return;
-    const int qid = qlist ? qlist[p] : p;
-    if (flags && flags[qid] == 0) return;
-    uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(p) * n_pow2;
+    const int q = blockIdx.x;
+    if (flags && flags[q] == 0) return;
+    uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(q) * n_pow2;
     for (uint32_t t = threadIdx.x; t < n_pow2; t += blockDim.x)
-        a[t] = t < r ? keys[static_cast<size_t>(p) * r + t] : ~0ull;
+        a[t] = t < r ? keys[static_cast<size_t>(q) * r + t] : ~0ull;
     bitonic_sort(a, n_pow2);
     for (uint32_t t = threadIdx.x; t < r; t += blockDim.x) {
         const uint64_t key = a[t];
-        cand_id[static_cast<size_t>(qid) * r + t] = static_cast<uint32_t>(key);
-        cand_qd[static_cast<size_t>(qid) * r + t] = static_cast<uint8_t>(key >> 32);
+        cand_id[static_cast<size_t>(q) * r + t] = static_cast<uint32_t>(key);
+        cand_qd[static_cast<size_t>(q) * r + t] = static_cast<uint8_t>(key >> 32);
     }
 }
 
@@ -304,7 +388,7 @@ int launch_sort_candidates(const uint64_t *keys, int nq, uint32_t r, uint64_t *s
     const uint32_t np2 = next_pow2(r);
     const bool use_spill = np2 > kSortLdsKeys;
     DCPQ_LAUNCH(kStageSelect, st, sort_candidates_kernel, dim3(nq), dim3(1024), use_spill ? 0 : sizeof(uint64_t) * np2,
-                keys, r, np2, use_spill ? 0 : 1, spill, nullptr, nullptr, flags, cand_id, cand_qd);
+                keys, r, np2, use_spill ? 0 : 1, spill, flags, cand_id, cand_qd);
     DCPQ_CHECK_LAUNCH("sort_candidates_kernel");
     return DCPQ_OK;
 }
@@ -482,67 +566,62 @@ ScanPlan plan_scan(uint64_t n_codes, int m, int nq, uint32_t r, int mode, size_t
 }
 
 template <int M, int MODE, int WAVES = kScanWaves, typename CodeT>
-static void launch_scan_pass(int stage, const CodeT *codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
-                             uint64_t stride, const uint8_t *qtab, int nq, const int *qlist, const uint32_t *nq_dev,
-                             uint32_t r, uint32_t *hist, const uint32_t *thr, uint32_t *tie, uint32_t *counter,
-                             uint64_t *keys, const TileEnd &end_of, bool few_expected, hipStream_t st)
+static void launch_scan_pass(int stage, const CodeT *codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t stride, int nq, const ScanArrays &w,
+                             const TileEnd &end_of, hipStream_t st)
 {
     constexpr int QT = scan_qt(M);
     const uint64_t nxb = (nunits + WAVES - 1) / WAVES;
-    const uint64_t items = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb;
-    // Redo launches expect few (usually zero) active queries: keep the grid small, it strides.
-    const uint64_t most = few_expected ? 4096 : (1u << 20);
+    const uint64_t items = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb, most = 1u << 20;
     const uint32_t grid = static_cast<uint32_t>(items < most ? (items ? items : 1) : most);
     const size_t lds = static_cast<size_t>(QT) * M * 256 + (MODE == kHist ? QT * 256 * 4 : 0);
-    DCPQ_LAUNCH(stage, st, (scan_kernel<M, QT, MODE, CodeT, WAVES>), dim3(grid), dim3(64 * WAVES), lds, codes, n_codes, unit,
-                nunits, stride, qtab, nq, qlist, nq_dev, r, hist, thr, tie, counter, keys, end_of);
+    DCPQ_LAUNCH(stage, st, (scan_kernel<M, QT, MODE, CodeT, WAVES>), dim3(grid), dim3(64 * WAVES), lds, codes, n_codes, unit, nunits, stride, nq, w, end_of);
 }
 
-// The three passes for the queries qlist[0 .. *nq_dev) (or all nq when qlist is null).  The counters (zero_bytes of the
-// workspace) are at zero.
+static ScanArrays redo_arrays(const uint8_t *qtab, const int *qlist, uint32_t r, uint8_t *base, const ScanPlan &p)
+{
+    auto words = [&](size_t off) { return reinterpret_cast<uint32_t *>(base + off); };
+    return ScanArrays{qtab, qlist, r, words(p.off_hist), words(p.off_thr), words(p.off_tie), words(p.off_counter), reinterpret_cast<uint64_t *>(base + p.off_keys)};
+}
+
+// The three passes for all nq queries.  The counters (zero_bytes of the workspace) are at zero.
 template <int M, typename CodeT>
-static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, const int *qlist,
-                             const uint32_t *nq_dev, uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base,
+static int launch_three_pass(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base,
                              const ScanPlan &p, hipStream_t st)
 {
-    uint32_t *hist = reinterpret_cast<uint32_t *>(base + p.off_hist);
-    uint32_t *thr = reinterpret_cast<uint32_t *>(base + p.off_thr);
-    uint32_t *counter = reinterpret_cast<uint32_t *>(base + p.off_counter);
-    uint32_t *tie = reinterpret_cast<uint32_t *>(base + p.off_tie);
-    const bool spill = next_pow2(r) > kSortLdsKeys;
-    uint64_t *keys = reinterpret_cast<uint64_t *>(base + p.off_keys);
-    uint64_t *sorted = reinterpret_cast<uint64_t *>(base + p.off_spill);
-    const bool few = qlist != nullptr;
-    uint32_t *done = reinterpret_cast<uint32_t *>(base + p.off_done);
-    const size_t qtiles = (static_cast<size_t>(nq) + p.qt - 1) / p.qt;
-    TileEnd after_hist{}, after_ties{};
-    if (few) {
-        after_hist.done = done + qtiles;
-        after_ties.done = done + 2 * qtiles;
-    }
-    after_hist.thr = after_ties.thr = thr;
-
-    launch_scan_pass<M, kHist>(kStageScanHist, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist, nq_dev, r,
-                               hist, thr, tie, counter, keys, after_hist, few, st);
+    const ScanArrays w = redo_arrays(qtab, nullptr, r, base, p);
+    launch_scan_pass<M, kHist>(kStageScanHist, codes, n_codes, p.unit, p.nunits, p.unit, nq, w, TileEnd{}, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<hist>");
-    if (!few) {
-        const int rc = launch_threshold(hist, nq, r, thr, st);
-        if (rc) return rc;
-    }
-    launch_scan_pass<M, kTieCount>(kStageScanTieCount, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist,
-                                   nq_dev, r, hist, thr, tie, counter, keys, after_ties, few, st);
+    int rc = launch_threshold(w.hist, nq, r, w.thr, st);
+    if (rc) return rc;
+    launch_scan_pass<M, kTieCount>(kStageScanTieCount, codes, n_codes, p.unit, p.nunits, p.unit, nq, w, TileEnd{}, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<tiecount>");
-    if (!few) {
-        const int rc = launch_tie_quota(tie, p.nunits, nq, thr, st);
-        if (rc) return rc;
-    }
-    launch_scan_pass<M, kCollect>(kStageScanCollect, codes, n_codes, p.unit, p.nunits, p.unit, qtab, nq, qlist,
-                                  nq_dev, r, hist, thr, tie, counter, keys, TileEnd{}, few, st);
+    rc = launch_tie_quota(w.tie, p.nunits, nq, w.thr, st);
+    if (rc) return rc;
+    launch_scan_pass<M, kCollect>(kStageScanCollect, codes, n_codes, p.unit, p.nunits, p.unit, nq, w, TileEnd{}, st);
     DCPQ_CHECK_LAUNCH("scan_kernel<collect>");
+    return launch_sort_candidates(w.keys, nq, r, reinterpret_cast<uint64_t *>(base + p.off_spill), cand_id, cand_qd, st);
+}
+
+// The same for the queries that the single pass has flagged.
+template <int M, typename CodeT>
+static int launch_redo(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base,
+                       const ScanPlan &p, hipStream_t st)
+{
+    constexpr int QT = scan_qt(M);
+    const ScanArrays w = redo_arrays(qtab, reinterpret_cast<const int *>(base + p.off_qlist), r, base, p);
     const uint32_t np2 = next_pow2(r);
-    DCPQ_LAUNCH(kStageSelect, st, sort_candidates_kernel, dim3(nq), dim3(1024), spill ? 0 : sizeof(uint64_t) * np2,
-                keys, r, np2, spill ? 0 : 1, sorted, qlist, nq_dev, nullptr, cand_id, cand_qd);
-    DCPQ_CHECK_LAUNCH("sort_candidates_kernel");
+    const bool spill = np2 > kSortLdsKeys;
+    size_t lds = static_cast<size_t>(QT) * M * 256 + QT * 256 * 4;
+    if (!spill && sizeof(uint64_t) * np2 > lds) lds = sizeof(uint64_t) * np2;
+    const int rc = allow_dynamic_lds(reinterpret_cast<const void *>(&scan_redo_kernel<M, QT, CodeT>), static_cast<int>(lds));
+    if (rc) return rc;
+    // as many workgroups as the chip holds at once (more would come when there is nothing left to hand out)
+    const size_t qtiles = (static_cast<size_t>(nq) + p.qt - 1) / p.qt;
+    uint32_t *nflag = reinterpret_cast<uint32_t *>(base + p.off_nflag), *done = reinterpret_cast<uint32_t *>(base + p.off_done);
+    DCPQ_LAUNCH(kStageScanCollect, st, (scan_redo_kernel<M, QT, CodeT>), dim3(static_cast<unsigned>(256 * (160 * 1024 / (lds + 256)))), dim3(kScanThreads), lds, codes, n_codes, p.unit,
+                p.nunits, nflag, w, done + qtiles, done + 2 * qtiles, done, reinterpret_cast<unsigned long long *>(nflag + 2), np2, spill ? 0 : 1,
+                reinterpret_cast<uint64_t *>(base + p.off_spill), cand_id, cand_qd);
+    DCPQ_CHECK_LAUNCH("scan_redo_kernel");
     return DCPQ_OK;
 }
 
@@ -563,9 +642,12 @@ static int launch_sample_hist_m(const CodeT *codes, uint64_t n_codes, const uint
 {
     // (with a pilot pass: runs 0, kPilotEvery, 2 kPilotEvery, ... of the sample)
     const uint64_t stride = p.pilot ? p.s_stride * kPilotEvery : p.s_stride;
+    ScanArrays w{};
+    w.qtab = qtab;
+    w.r = r;
+    w.hist = shist;
     auto launch = [&](auto waves) {
-        launch_scan_pass<M, kHist, decltype(waves)::value>(kStageScanHist, codes, n_codes, p.s_unit, p.s1_nunits, stride, qtab, nq, nullptr, nullptr, r, shist, nullptr, nullptr,
-                                                           nullptr, nullptr, end_of, false, st);
+        launch_scan_pass<M, kHist, decltype(waves)::value>(kStageScanHist, codes, n_codes, p.s_unit, p.s1_nunits, stride, nq, w, end_of, st);
     };
     switch (sample_waves((nq + scan_qt(M) - 1) / scan_qt(M), p.s1_nunits)) {
     case 16: launch(std::integral_constant<int, 16>{}); break;
@@ -613,13 +695,12 @@ static int launch_scan_m(const CodeT *codes, uint64_t n_codes, const uint8_t *qt
     if (!cleared) rc = launch_zero_words(reinterpret_cast<uint32_t *>(base), p.zero_bytes / sizeof(uint32_t), st);
     if (rc) return rc;
     if (!p.fast)
-        return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, nullptr, nullptr, r, cand_id, cand_qd, base, p, st);
+        return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
     rc = launch_scan_fast(codes, n_codes, M, qtab, nq, r, cand_id, cand_qd, base, p, cells, st);
     if (rc) return rc;
     // queries the single pass could not finish (their count is known on the device only)
-    return launch_three_pass<M, CodeT>(codes, n_codes, qtab, nq, reinterpret_cast<const int *>(base + p.off_qlist),
-                                reinterpret_cast<const uint32_t *>(base + p.off_nflag), r, cand_id, cand_qd, base,
-                                p, st);
+    if constexpr (M >= 4) return launch_redo<M, CodeT>(codes, n_codes, qtab, nq, r, cand_id, cand_qd, base, p, st);
+    return DCPQ_OK;
 }
 
 template <typename CodeT>

@@ -43,7 +43,7 @@ struct ScanPlan {
     size_t off_hist;      // uint32 [nq][256]
     size_t off_thr;       // uint32 [nq][2]   (threshold bucket, ids still needed from it)
     size_t off_counter;   // uint32 [nq]
-    size_t off_done;      // uint32 [3][ceil(nq / qt)]  finished workgroups of a query tile (sample, redo histogram, redo tie count)
+    size_t off_done;      // uint32 [3][ceil(nq / qt)]  finished items of a query tile (sample, and again zero, redo collection; redo histogram; redo tie count)
     size_t zero_bytes;    // everything that a call expects at zero lies together from offset 0: the four arrays
                           // above and, for the single-pass path, fcount, chist, shist and nflag
     size_t off_tie;       // uint32 [nq][nunits]
@@ -74,7 +74,7 @@ struct ScanPlan {
     size_t off_fcount;    // uint32 [nq][slices]
     size_t off_chist;     // uint32 [nq][256]
     size_t off_shist;     // uint32 [nq][256]
-    size_t off_nflag;     // uint32 [1] (+ padding)
+    size_t off_nflag;     // uint32 [1], two words on the uint64 counter that hands out the redo's items
     size_t off_bound;     // Bound [nq], in the place of tie, keys and spill: only the redo uses those, and it never reads a bound
     size_t off_flags;     // uint32 [nq]
     size_t off_qlist;     // int32 [nq]
@@ -180,9 +180,15 @@ __device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, uint32_
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int z = 0; z < 4; ++z)
-        if (cum[z] - c[z] < r && cum[z] >= r) { thr[0] = 4 * lane + z; thr[1] = r - (cum[z] - c[z]); }
+        if (cum[z] - c[z] < r && cum[z] >= r) {                  // (device-scope stores: workgroups of the same launch may read them)
+            __hip_atomic_store(&thr[0], static_cast<uint32_t>(4 * lane + z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&thr[1], r - (cum[z] - c[z]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     // fewer than r codes in all (inverted lists only): bucket "256" takes everything
-    if (lane == 63 && cum[3] < r) { thr[0] = 256; thr[1] = 0; }
+    if (lane == 63 && cum[3] < r) {
+        __hip_atomic_store(&thr[0], 256u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&thr[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // Turns per-unit counts of bucket T into per-unit quotas: units are in id order, so unit u may
@@ -218,7 +224,7 @@ __device__ inline void tie_quotas(uint32_t *row, uint32_t nunits, uint32_t need)
 #pragma unroll
         for (uint32_t z = 0; z < PER; ++z) {
             const uint32_t u = base + lane * PER + z;
-            if (u < nunits) row[u] = before >= need ? 0u : min(c[z], need - before);
+            if (u < nunits) __hip_atomic_store(&row[u], before >= need ? 0u : min(c[z], need - before), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             before += c[z];
         }
         carry += __shfl(incl, 63);
