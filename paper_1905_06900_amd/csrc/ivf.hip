@@ -17,6 +17,8 @@
 //   Refine  ivf_refine_topk     Eq. 3 on the residual of each candidate's own list, directly from
 //                               the full codebooks in double precision (per-list 2^16-entry tables
 //                               would cost nprobe table builds per query), then the k best
+#include <type_traits>
+
 #include "common.h"
 #include "scan_internal.h"
 
@@ -639,12 +641,15 @@ __global__ __launch_bounds__(256) void ivf_parts_kernel(const int32_t *__restric
 enum IvfMode { kIvfHist = 0, kIvfTieCount = 1, kIvfCollect = 2 };
 constexpr int kIvfAhead = 4;     // 64-code groups whose codes a wavefront loads together
 
-// One wavefront per unit; grid (kIvfUnitsPerQuery / 4, nq), 256 threads.  The wavefront keeps the
-// 8-bit tables of its (query, list) in its own LDS slot and walks the unit 64 codes at a time.
-// CodeT: uint16_t (the codes as stored) or uint8_t (their low-byte plane).
-// One (query, unit) by one wavefront; nothing in it waits for another wavefront.
+constexpr int kIvfRedoLine = 32;             // words from one count of the redo to the next
+constexpr int kIvfRedoWaves = 16;
+
+// One (query, unit) by one wavefront, which keeps the
+// 8-bit tables of its (query, list) in its own LDS slot and walks the unit 64 codes at a time; nothing in it waits for another wavefront.
+// CodeT: uint16_t (the codes as stored) or uint8_t (their low-byte plane).  What a pass leaves for the next, in the same launch, goes through
+// device-scope atomics, stores and loads.
 template <int M, int MODE, typename CodeT>
-__device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
+__device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
                                      const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab,
                                      int nprobe, uint32_t r, uint32_t *__restrict__ hist,
                                      const uint32_t *__restrict__ thr, uint32_t *__restrict__ tie,
@@ -652,9 +657,8 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t u = blockIdx.x * 4 + wave;
     uint8_t *tab = smem + wave * (M * 256);                                      // [M][256]
-    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + 4 * M * 256) + wave * 256;   // kIvfHist only
+    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + kIvfRedoWaves * M * 256) + wave * 256;   // kIvfHist only
     const bool active = u < nunits[q];
     IvfUnit un{0, 0, 0};
     if (active) un = units[static_cast<size_t>(q) * kIvfUnitsPerQuery + u];
@@ -673,8 +677,8 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
 
     uint32_t T = 0, aux = 0;
     if (MODE != kIvfHist) {
-        T = thr[2 * q];
-        if (MODE == kIvfCollect) aux = tie[static_cast<size_t>(q) * kIvfUnitsPerQuery + u];
+        T = __hip_atomic_load(&thr[2 * q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (MODE == kIvfCollect) aux = __hip_atomic_load(&tie[static_cast<size_t>(q) * kIvfUnitsPerQuery + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // The unit is walked 64 codes at a time, in id order; the codes of kIvfAhead such groups are loaded
     // together, so that one memory latency covers all of them.
@@ -723,7 +727,8 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
                 slot0 = __shfl(slot0, 0, kWave);
                 if (take) {
                     const uint32_t slot = slot0 + __popcll(take_mask & ((1ull << lane) - 1ull));
-                    if (slot < r) keys[static_cast<size_t>(q) * r + slot] = make_key(qd, static_cast<uint32_t>(id));
+                    if (slot < r)
+                        __hip_atomic_store(&keys[static_cast<size_t>(q) * r + slot], make_key(qd, static_cast<uint32_t>(id)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         }
@@ -742,44 +747,97 @@ __device__ inline void ivf_scan_unit(int q, const CodeT *__restrict__ codes, con
     }
 }
 
-// Grid (kIvfUnitsPerQuery / 4, min(nq, kIvfRedoRows)): a wavefront takes the same unit number of every
-// kIvfRedoRows-th query.  Only flagged queries are scanned (*nflag of them), and since that is the rare case
-// (the three passes redo what the single pass could not finish) a row of workgroups serves many queries, so
-// that a launch with nothing to do costs a few thousand empty workgroups, not one per (query, 4 units).
-// The short step that follows a histogram (thresholds) or a tie count (quotas) is done by the workgroup that finishes a row
-// last, for the row's queries (done: a counter per row, zero on entry): two launches fewer, 4.5 us each where nothing is flagged.
-// The counters lie a memory line apart: side by side, their returning atomics from all rows queue for one line (72 queries, all
-// flagged: 24 us for the histogram and 19 for the tie count so, 89 and 86 with the counters in one line).
-constexpr int kIvfRedoRows = 32, kIvfRedoLine = 32;          // rows; words from one counter to the next
+// The three passes and the sort for the flagged queries qlist[0 .. *nflag), in one launch, as for the flat scan (scan_redo_kernel, where the
+// waits are explained): the items of a pass are parts of a query's units, handed out in order by one counter.  A query has 64 parts, of a unit per
+// wavefront, where few are flagged, and as few as bring a pass to 1024 items where many are (the counter's atomics follow each other at 15 ns).
+// done: [3][nq] items that are done, of each pass, a memory line apart (side by side their returning atomics queue for one line); ticket: the
+// counter; all at zero on entry.
 
-template <int M, int MODE, typename CodeT>
-__global__ __launch_bounds__(256) void ivf_scan_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
-                                                      const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab,
-                                                      int nprobe, int nq, uint32_t r, const uint32_t *__restrict__ nflag,
-                                                      const uint32_t *__restrict__ flags, uint32_t *hist, uint32_t *thr, uint32_t *tie,
-                                                      uint32_t *__restrict__ counter, uint64_t *__restrict__ keys, uint32_t *__restrict__ done)
+template <int M, typename CodeT>
+__global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
+                                                      const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab, int nprobe, int nq, uint32_t r,
+                                                      const uint32_t *__restrict__ nflag, const int *__restrict__ qlist, uint32_t *hist, uint32_t *thr, uint32_t *tie,
+                                                      uint32_t *counter, uint64_t *keys, uint32_t *done, unsigned long long *ticket, uint32_t n_pow2, int use_lds,
+                                                      uint64_t *__restrict__ spill, uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
 {
-    if (*nflag == 0) return;                                 // no query is flagged: one load, not nq / gridDim.y
-    for (int q = blockIdx.y; q < nq; q += gridDim.y) {
-        if (flags[q] == 0) continue;
-        ivf_scan_unit<M, MODE, CodeT>(q, codes, units, nunits, qtab, nprobe, r, hist, thr, tie, counter, keys);
-        // the next query's tables overwrite this one's: every lane is done with them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    if constexpr (MODE != kIvfCollect) {
-        __shared__ uint32_t s_last;
-        // (all that this workgroup has written went by device-scope atomics and stores: it is in place once they are complete)
+    const uint32_t nf = *nflag;
+    if (nf == 0) return;
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ unsigned long long s_item;
+    __shared__ uint32_t s_last;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    uint32_t parts = kIvfUnitsPerQuery / kIvfRedoWaves;                          // ... of a query
+    while (parts > 1 && parts * nf > 1024) parts >>= 1;
+    const uint64_t per = static_cast<uint64_t>(nf) * parts, all = 3 * per + nf;
+    auto count_of = [&](uint32_t pass, uint32_t f) { return done + (static_cast<size_t>(pass) * nq + f) * kIvfRedoLine; };
+    auto wait_for = [&](const uint32_t *count, uint32_t n) {
+        if (tid == 0)
+            while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n) __builtin_amdgcn_s_sleep(16);
+        __syncthreads();
+    };
+    auto finished = [&](uint32_t *count) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(&done[blockIdx.y * kIvfRedoLine], 1u) == gridDim.x - 1;
+        if (tid == 0) s_last = atomicAdd(count, 1u) == parts - 1;
         __syncthreads();
-        if (s_last == 0) return;                             // uniform
-        for (int q = blockIdx.y + (threadIdx.x >> 6) * gridDim.y; q < nq; q += 4 * gridDim.y) {
-            if (flags[q] == 0) continue;
-            if (MODE == kIvfHist) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
-            else tie_quotas(tie + static_cast<size_t>(q) * kIvfUnitsPerQuery, nunits[q], thr[2 * q + 1]);
+        return s_last != 0;
+    };
+    auto ready = [&](uint32_t *count) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) atomicAdd(count, 1u);
+    };
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) s_item = atomicAdd(ticket, 1ull);
+        __syncthreads();
+        const uint64_t item = s_item;
+        if (item >= all) return;                                      // uniform
+        if (item < 3 * per) {
+            const uint32_t pass = static_cast<uint32_t>(item / per), in_pass = static_cast<uint32_t>(item % per), f = in_pass / parts, part = in_pass % parts;
+            const int q = qlist[f];
+            auto walk = [&](auto mode) {
+                const uint32_t n = nunits[q];
+                for (uint32_t u = part * kIvfRedoWaves + wave; u < n; u += kIvfRedoWaves * parts) {
+                    ivf_scan_unit<M, decltype(mode)::value, CodeT>(q, u, codes, units, nunits, qtab, nprobe, r, hist, thr, tie, counter, keys);
+                    // the next unit's tables overwrite this one's: every lane is done with them
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                }
+            };
+            if (pass == 0) {
+                walk(std::integral_constant<int, kIvfHist>{});
+                if (finished(count_of(0, f))) {                       // uniform
+                    if (wave == 0) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
+                    ready(count_of(0, f));
+                }
+            } else if (pass == 1) {
+                wait_for(count_of(0, f), parts + 1);
+                walk(std::integral_constant<int, kIvfTieCount>{});
+                if (finished(count_of(1, f))) {                       // uniform
+                    if (wave == 0)
+                        tie_quotas(tie + static_cast<size_t>(q) * kIvfUnitsPerQuery, nunits[q],
+                                   __hip_atomic_load(&thr[2 * q + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                    ready(count_of(1, f));
+                }
+            } else {
+                wait_for(count_of(1, f), parts + 1);
+                walk(std::integral_constant<int, kIvfCollect>{});
+                finished(count_of(2, f));
+            }
+            continue;
+        }
+        const uint32_t f = static_cast<uint32_t>(item - 3 * per);
+        wait_for(count_of(2, f), parts);
+        const size_t q = qlist[f];
+        uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + q * n_pow2;
+        for (uint32_t t = tid; t < n_pow2; t += 64 * kIvfRedoWaves)
+            a[t] = t < r ? __hip_atomic_load(&keys[q * r + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+        bitonic_sort(a, n_pow2);
+        for (uint32_t t = tid; t < r; t += 64 * kIvfRedoWaves) {
+            cand_id[q * r + t] = static_cast<uint32_t>(a[t]);
+            cand_qd[q * r + t] = static_cast<uint8_t>(a[t] >> 32);
         }
     }
 }
@@ -1252,7 +1310,7 @@ struct IvfScanPlan {
     // single pass: sample histogram, cursors, appended histogram (cleared with the rest); bounds, flags, buffers
     size_t off_shist, off_fcount, off_chist, off_bound, off_flags, off_fkeys, off_fsort, off_probed;
     // its parts: bins of list ids, cursor, finished sample workgroups (cleared with the rest); places, lengths, records
-    size_t off_bins, off_cursor, off_done, off_redo, redo_rows, off_rank, off_part, off_items, off_qlist;
+    size_t off_bins, off_cursor, off_done, off_redo, off_rank, off_part, off_items, off_qlist;
     bool order;              // parts ordered by list ...
     uint32_t nbins;          // ... in so many bins
     uint32_t parts;          // parts per query, about (and one more per probed list at most) ...
@@ -1281,10 +1339,9 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     p.min_part = nq >= 256 ? 2 * kIvfMinPart : kIvfMinPart;
     p.order = nq > 4;
     p.nbins = Q * 4096 < kIvfBins ? static_cast<uint32_t>(Q) * 4096 : kIvfBins;
-    p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);
+    p.off_cursor = off;  off = align_up(off + sizeof(uint32_t), 256);             // (two words on: the uint64 counter that hands out the redo's items)
     p.off_done = off;    off = align_up(off + sizeof(uint32_t) * (Q + 1), 256);
-    p.redo_rows = nq < kIvfRedoRows ? nq : kIvfRedoRows;
-    const size_t redo_bytes = sizeof(uint32_t) * 2 * kIvfRedoLine * p.redo_rows;      // (a multiple of 256)
+    const size_t redo_bytes = align_up(sizeof(uint32_t) * 3 * kIvfRedoLine * Q, 256);
     p.off_redo = off;    off += redo_bytes;
     p.off_bins = off;    off = align_up(off + (p.order ? sizeof(uint32_t) * p.nbins : 0), 256);
     p.zero_bytes = off;  // everything above is cleared together
@@ -1302,7 +1359,7 @@ static IvfScanPlan plan_ivf_scan(int nq, uint32_t r)
     {
         const size_t parts_bytes = redo_bytes + (p.order ? sizeof(uint32_t) * (p.nbins + Q * kIvfMaxProbe) : 0) + sizeof(IvfUnit) * Q * (p.parts + kIvfMaxProbe);
         const size_t slices_bytes = sizeof(uint64_t) * Q * kFastSlices;
-        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 322 of 1024 and more)
+        p.cap -= static_cast<uint32_t>((parts_bytes + slices_bytes - 1) / slices_bytes);     // (at most 325 of 1024 and more)
     }
     p.upd = r / 16 < 16 ? 16 : r / 16;                   // appends to one slice between bound updates
     p.sortcap = next_pow2(2 * r) < kSortLdsKeys ? kSortLdsKeys : next_pow2(2 * r);
@@ -1352,8 +1409,6 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
                     static_cast<uint32_t>(nprobe), offsets, static_cast<uint32_t>(nlist), bins, p.nbins, rank, part_of, items);
         DCPQ_CHECK_LAUNCH("ivf_parts_kernel");
     }
-    const dim3 grid(kIvfUnitsPerQuery / 4, static_cast<uint32_t>(p.redo_rows));
-    const size_t lds_tab = 4 * M * 256;
     uint32_t *shist = reinterpret_cast<uint32_t *>(base + p.off_shist);
     uint32_t *fcount = reinterpret_cast<uint32_t *>(base + p.off_fcount);
     uint32_t *chist = reinterpret_cast<uint32_t *>(base + p.off_chist);
@@ -1388,17 +1443,17 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
                             reinterpret_cast<int *>(base + p.off_qlist), nflag);
     if (rc) return rc;
     // the queries it flagged (a full slice, or fewer than r codes in the probed lists): three passes
-    uint32_t *redo_done = reinterpret_cast<uint32_t *>(base + p.off_redo);
-    DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfHist, CodeT>), grid, dim3(256), lds_tab + 4 * 256 * 4, codes, units,
-                nunits, qtab, nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done);
-    DCPQ_CHECK_LAUNCH("ivf_scan_kernel<hist>");
-    DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfTieCount, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, redo_done + kIvfRedoLine * p.redo_rows);
-    DCPQ_CHECK_LAUNCH("ivf_scan_kernel<tiecount>");
-    DCPQ_LAUNCH(kStageIvf, st, (ivf_scan_kernel<M, kIvfCollect, CodeT>), grid, dim3(256), lds_tab, codes, units, nunits, qtab,
-                nprobe, nq, r, nflag, flags, hist, thr, tie, counter, keys, nullptr);
-    DCPQ_CHECK_LAUNCH("ivf_scan_kernel<collect>");
-    return launch_sort_candidates(keys, nq, r, spill, cand_id, cand_qd, st, flags);
+    const uint32_t np2 = next_pow2(r);
+    const bool use_lds = np2 <= kSortLdsKeys;
+    size_t lds = kIvfRedoWaves * (M * 256 + 256 * 4);
+    if (use_lds && sizeof(uint64_t) * np2 > lds) lds = sizeof(uint64_t) * np2;
+    rc = allow_dynamic_lds(reinterpret_cast<const void *>(&ivf_redo_kernel<M, CodeT>), static_cast<int>(lds));
+    if (rc) return rc;
+    DCPQ_LAUNCH(kStageIvf, st, (ivf_redo_kernel<M, CodeT>), dim3(512), dim3(64 * kIvfRedoWaves), lds, codes, units, nunits, qtab, nprobe, nq, r,
+                nflag, reinterpret_cast<const int *>(base + p.off_qlist), hist, thr, tie, counter, keys, reinterpret_cast<uint32_t *>(base + p.off_redo),
+                reinterpret_cast<unsigned long long *>(cursor + 2), np2, use_lds ? 1 : 0, spill, cand_id, cand_qd);
+    DCPQ_CHECK_LAUNCH("ivf_redo_kernel");
+    return DCPQ_OK;
 }
 
 static int ivf_check_common(const char *what, int nq, int m, int dsub, int nlist, int nprobe)

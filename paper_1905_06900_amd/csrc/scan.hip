@@ -213,8 +213,10 @@ __global__ __launch_bounds__(64 * WAVES) void scan_kernel(const CodeT *__restric
 // and wait, if at all, for items handed out earlier still, so that every wait ends whatever number of workgroups the chip holds at a time.
 // What one item leaves for another goes through device-scope atomics, stores and loads, and is in place before the item is counted as done.
 // sync: [3][tiles] items that are done, of each pass (one more once thresholds or quotas are there); ticket: the counter (both at zero on entry).
+// (Sixteen wavefronts share a tile's tables, and sort.)
+constexpr int kRedoWaves = 16;
 template <int M, int QT, typename CodeT>
-__global__ __launch_bounds__(kScanThreads) void scan_redo_kernel(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
+__global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
                                                                  const uint32_t *__restrict__ nflag, const ScanArrays w, uint32_t *done_hist, uint32_t *done_tie,
                                                                  uint32_t *done_collect, unsigned long long *ticket, uint32_t n_pow2, int use_lds,
                                                                  uint64_t *__restrict__ spill, uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
@@ -225,7 +227,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_redo_kernel(const CodeT *__
     __shared__ unsigned long long s_item;
     __shared__ uint32_t s_last;
     const int tid = threadIdx.x, wave = tid >> 6;
-    const uint32_t nxb = (nunits + kScanWaves - 1) / kScanWaves;
+    const uint32_t nxb = (nunits + kRedoWaves - 1) / kRedoWaves;
     const uint64_t per = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb, all = 3 * per + nq;
     auto wait_for = [&](const uint32_t *count, uint32_t n) {
         if (tid == 0)
@@ -256,22 +258,22 @@ __global__ __launch_bounds__(kScanThreads) void scan_redo_kernel(const CodeT *__
             const uint32_t tile = static_cast<uint32_t>(in_pass / nxb), xb = static_cast<uint32_t>(in_pass % nxb);
             const int q0 = static_cast<int>(tile) * QT, nqt = min(QT, nq - q0);
             if (item < per) {
-                scan_item<M, QT, kHist, CodeT, kScanWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                scan_item<M, QT, kHist, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
                 if (finished(&done_hist[tile])) {                     // uniform
-                    for (int q = wave; q < nqt; q += kScanWaves) exact_threshold(w.hist + static_cast<size_t>(q0 + q) * 256, w.r, w.thr + 2 * (q0 + q));
+                    for (int q = wave; q < nqt; q += kRedoWaves) exact_threshold(w.hist + static_cast<size_t>(q0 + q) * 256, w.r, w.thr + 2 * (q0 + q));
                     ready(&done_hist[tile]);
                 }
             } else if (item < 2 * per) {
                 wait_for(&done_hist[tile], nxb + 1);
-                scan_item<M, QT, kTieCount, CodeT, kScanWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                scan_item<M, QT, kTieCount, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
                 if (finished(&done_tie[tile])) {                      // uniform
-                    for (int q = wave; q < nqt; q += kScanWaves)
+                    for (int q = wave; q < nqt; q += kRedoWaves)
                         tie_quotas(w.tie + static_cast<size_t>(q0 + q) * nunits, nunits, agent_load(&w.thr[2 * (q0 + q) + 1]));
                     ready(&done_tie[tile]);
                 }
             } else {
                 wait_for(&done_tie[tile], nxb + 1);
-                scan_item<M, QT, kCollect, CodeT, kScanWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                scan_item<M, QT, kCollect, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
                 finished(&done_collect[tile]);
             }
             continue;
@@ -279,10 +281,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_redo_kernel(const CodeT *__
         const int p = static_cast<int>(item - 3 * per);
         wait_for(&done_collect[p / QT], nxb);
         uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(p) * n_pow2;
-        for (uint32_t t = tid; t < n_pow2; t += kScanThreads) a[t] = t < w.r ? agent_load(&w.keys[static_cast<size_t>(p) * w.r + t]) : ~0ull;
+        for (uint32_t t = tid; t < n_pow2; t += 64 * kRedoWaves) a[t] = t < w.r ? agent_load(&w.keys[static_cast<size_t>(p) * w.r + t]) : ~0ull;
         bitonic_sort(a, n_pow2);
         const size_t out = static_cast<size_t>(w.qlist[p]) * w.r;
-        for (uint32_t t = tid; t < w.r; t += kScanThreads) {
+        for (uint32_t t = tid; t < w.r; t += 64 * kRedoWaves) {
             cand_id[out + t] = static_cast<uint32_t>(a[t]);
             cand_qd[out + t] = static_cast<uint8_t>(a[t] >> 32);
         }
@@ -304,15 +306,13 @@ __global__ __launch_bounds__(64) void tie_quota_kernel(uint32_t *__restrict__ ti
     tie_quotas(tie + static_cast<size_t>(q) * nunits, nunits, thr[2 * q + 1]);
 }
 
-// Sort the r collected keys of each query (of those with a flag, where there are flags) by (qd, id) and split them into the two outputs.
+// Sort the r collected keys of each query by (qd, id) and split them into the two outputs.
 // use_lds: the padded array fits the dynamic LDS allocation; otherwise it is sorted in `spill`.
 __global__ __launch_bounds__(1024) void sort_candidates_kernel(const uint64_t *__restrict__ keys, uint32_t r, uint32_t n_pow2, int use_lds,
-                                                              uint64_t *__restrict__ spill, const uint32_t *__restrict__ flags,
-                                                              uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
+                                                              uint64_t *__restrict__ spill, uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const int q = blockIdx.x;
-    if (flags && flags[q] == 0) return;
     uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(q) * n_pow2;
     for (uint32_t t = threadIdx.x; t < n_pow2; t += blockDim.x)
         a[t] = t < r ? keys[static_cast<size_t>(q) * r + t] : ~0ull;
@@ -382,13 +382,12 @@ int launch_tie_quota(uint32_t *tie, uint32_t nunits, int nq, const uint32_t *thr
     return DCPQ_OK;
 }
 
-int launch_sort_candidates(const uint64_t *keys, int nq, uint32_t r, uint64_t *spill, uint32_t *cand_id,
-                           uint8_t *cand_qd, hipStream_t st, const uint32_t *flags)
+int launch_sort_candidates(const uint64_t *keys, int nq, uint32_t r, uint64_t *spill, uint32_t *cand_id, uint8_t *cand_qd, hipStream_t st)
 {
     const uint32_t np2 = next_pow2(r);
     const bool use_spill = np2 > kSortLdsKeys;
     DCPQ_LAUNCH(kStageSelect, st, sort_candidates_kernel, dim3(nq), dim3(1024), use_spill ? 0 : sizeof(uint64_t) * np2,
-                keys, r, np2, use_spill ? 0 : 1, spill, flags, cand_id, cand_qd);
+                keys, r, np2, use_spill ? 0 : 1, spill, cand_id, cand_qd);
     DCPQ_CHECK_LAUNCH("sort_candidates_kernel");
     return DCPQ_OK;
 }
@@ -618,7 +617,7 @@ static int launch_redo(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab
     // as many workgroups as the chip holds at once (more would come when there is nothing left to hand out)
     const size_t qtiles = (static_cast<size_t>(nq) + p.qt - 1) / p.qt;
     uint32_t *nflag = reinterpret_cast<uint32_t *>(base + p.off_nflag), *done = reinterpret_cast<uint32_t *>(base + p.off_done);
-    DCPQ_LAUNCH(kStageScanCollect, st, (scan_redo_kernel<M, QT, CodeT>), dim3(static_cast<unsigned>(256 * (160 * 1024 / (lds + 256)))), dim3(kScanThreads), lds, codes, n_codes, p.unit,
+    DCPQ_LAUNCH(kStageScanCollect, st, (scan_redo_kernel<M, QT, CodeT>), dim3(512), dim3(64 * kRedoWaves), lds, codes, n_codes, p.unit,
                 p.nunits, nflag, w, done + qtiles, done + 2 * qtiles, done, reinterpret_cast<unsigned long long *>(nflag + 2), np2, spill ? 0 : 1,
                 reinterpret_cast<uint64_t *>(base + p.off_spill), cand_id, cand_qd);
     DCPQ_CHECK_LAUNCH("scan_redo_kernel");

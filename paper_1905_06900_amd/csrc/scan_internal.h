@@ -116,9 +116,7 @@ int launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
 int launch_zero_and_fill(uint64_t *z, size_t nz, uint64_t *p, size_t n, uint64_t v, hipStream_t st);      // z to zero, p to v
 int launch_threshold(const uint32_t *hist, int nq, uint32_t r, uint32_t *thr, hipStream_t st);
 int launch_tie_quota(uint32_t *tie, uint32_t nunits, int nq, const uint32_t *thr, hipStream_t st);
-// flags (may be null): only queries with a non-zero flag are sorted and written
-int launch_sort_candidates(const uint64_t *keys, int nq, uint32_t r, uint64_t *spill, uint32_t *cand_id,
-                           uint8_t *cand_qd, hipStream_t st, const uint32_t *flags = nullptr);
+int launch_sort_candidates(const uint64_t *keys, int nq, uint32_t r, uint64_t *spill, uint32_t *cand_id, uint8_t *cand_qd, hipStream_t st);
 
 #ifdef __HIPCC__
 }  // namespace dcpq
