@@ -651,14 +651,14 @@ constexpr int kIvfRedoWaves = 16;
 template <int M, int MODE, typename CodeT>
 __device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
                                      const uint32_t *__restrict__ nunits, const uint8_t *__restrict__ qtab,
-                                     int nprobe, uint32_t r, uint32_t *__restrict__ hist,
+                                     int nprobe, uint32_t r,
                                      const uint32_t *__restrict__ thr, uint32_t *__restrict__ tie,
                                      uint32_t *__restrict__ counter, uint64_t *__restrict__ keys)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint8_t *tab = smem + wave * (M * 256);                                      // [M][256]
-    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + kIvfRedoWaves * M * 256) + wave * 256;   // kIvfHist only
+    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + kIvfRedoWaves * M * 256);   // kIvfHist: the workgroup's
     const bool active = u < nunits[q];
     IvfUnit un{0, 0, 0};
     if (active) un = units[static_cast<size_t>(q) * kIvfUnitsPerQuery + u];
@@ -666,8 +666,6 @@ __device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict_
         const uint4 *src = reinterpret_cast<const uint4 *>(qtab + (static_cast<size_t>(q) * nprobe + un.p) * M * 256);
         uint4 *dst = reinterpret_cast<uint4 *>(tab);
         for (int v = lane; v < M * 256 / 16; v += 64) dst[v] = src[v];
-        if (MODE == kIvfHist)
-            for (int v = lane; v < 256; v += 64) lhist[v] = 0;
     }
     // the tables are this wavefront's own: its lanes run in lockstep, the fences order the LDS accesses
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -734,24 +732,20 @@ __device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict_
         }
       }
     }
-    if (MODE == kIvfHist) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (int v = lane; v < 256; v += 64) {
-            const uint32_t c = lhist[v];
-            if (c) atomicAdd(&hist[static_cast<size_t>(q) * 256 + v], c);
-        }
-    } else if (MODE == kIvfTieCount) {
+    if (MODE == kIvfTieCount) {
         if (lane == 0) __hip_atomic_store(&tie[static_cast<size_t>(q) * kIvfUnitsPerQuery + u], aux, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 // The three passes and the sort for the flagged queries qlist[0 .. *nflag), in one launch, as for the flat scan (scan_redo_kernel, where the
-// waits are explained): the items of a pass are parts of a query's units, handed out in order by one counter.  A query has 64 parts, of a unit per
-// wavefront, where few are flagged, and as few as bring a pass to 1024 items where many are (the counter's atomics follow each other at 15 ns).
-// done: [3][nq] items that are done, of each pass, a memory line apart (side by side their returning atomics queue for one line); ticket: the
-// counter; all at zero on entry.
+// waits are explained): the items of a pass are parts of a query's units, handed out in order by one counter.  A query has as many parts, units
+// that far apart, as bring a pass to 512 items, and at most 256 (of 1024 units four wavefronts of a workgroup have one then, and every CU has
+// work): the counter's atomics follow each other at 15 ns, and with 11 queries over 31M codes (800 000 a query) and few of them flagged 64
+// parts and 512 cost 20 and 30 us more than 256.
+// What the items of the next pass wait for is a word away from the count that the workgroups of this one add to: their loads of that line
+// queued the adds (106 -> 100 us there).  A workgroup adds its counts to the query's histogram once, from its own in LDS.
+// done: [3][nq] items that are done, of each pass, a memory line apart (side by side their returning atomics queue for one line), and beside
+// the last pass's count the two words that the first two passes set; ticket: the counter; all at zero on entry.
 
 template <int M, typename CodeT>
 __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
@@ -765,11 +759,12 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ unsigned long long s_item;
     __shared__ uint32_t s_last;
+    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + kIvfRedoWaves * M * 256);
     const int tid = threadIdx.x, wave = tid >> 6;
-    uint32_t parts = kIvfUnitsPerQuery / kIvfRedoWaves;                          // ... of a query
-    while (parts > 1 && parts * nf > 1024) parts >>= 1;
+    const uint32_t parts = min(256u, max(1u, 512u / nf));             // ... of a query
     const uint64_t per = static_cast<uint64_t>(nf) * parts, all = 3 * per + nf;
     auto count_of = [&](uint32_t pass, uint32_t f) { return done + (static_cast<size_t>(pass) * nq + f) * kIvfRedoLine; };
+    auto word_of = [&](uint32_t pass, uint32_t f) { return count_of(2, f) + 1 + pass; };
     auto wait_for = [&](const uint32_t *count, uint32_t n) {
         if (tid == 0)
             while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n) __builtin_amdgcn_s_sleep(16);
@@ -782,10 +777,10 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
         __syncthreads();
         return s_last != 0;
     };
-    auto ready = [&](uint32_t *count) {
+    auto ready = [&](uint32_t *word) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) atomicAdd(count, 1u);
+        if (tid == 0) atomicAdd(word, 1u);
     };
     for (;;) {
         __syncthreads();
@@ -798,8 +793,8 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
             const int q = qlist[f];
             auto walk = [&](auto mode) {
                 const uint32_t n = nunits[q];
-                for (uint32_t u = part * kIvfRedoWaves + wave; u < n; u += kIvfRedoWaves * parts) {
-                    ivf_scan_unit<M, decltype(mode)::value, CodeT>(q, u, codes, units, nunits, qtab, nprobe, r, hist, thr, tie, counter, keys);
+                for (uint32_t u = part + wave * parts; u < n; u += kIvfRedoWaves * parts) {
+                    ivf_scan_unit<M, decltype(mode)::value, CodeT>(q, u, codes, units, nunits, qtab, nprobe, r, thr, tie, counter, keys);
                     // the next unit's tables overwrite this one's: every lane is done with them
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
@@ -807,22 +802,26 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
                 }
             };
             if (pass == 0) {
+                if (tid < 256) lhist[tid] = 0;
+                __syncthreads();
                 walk(std::integral_constant<int, kIvfHist>{});
+                __syncthreads();
+                if (tid < 256 && lhist[tid]) atomicAdd(&hist[static_cast<size_t>(q) * 256 + tid], lhist[tid]);
                 if (finished(count_of(0, f))) {                       // uniform
                     if (wave == 0) exact_threshold(hist + static_cast<size_t>(q) * 256, r, thr + 2 * q);
-                    ready(count_of(0, f));
+                    ready(word_of(0, f));
                 }
             } else if (pass == 1) {
-                wait_for(count_of(0, f), parts + 1);
+                wait_for(word_of(0, f), 1);
                 walk(std::integral_constant<int, kIvfTieCount>{});
                 if (finished(count_of(1, f))) {                       // uniform
                     if (wave == 0)
                         tie_quotas(tie + static_cast<size_t>(q) * kIvfUnitsPerQuery, nunits[q],
                                    __hip_atomic_load(&thr[2 * q + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                    ready(count_of(1, f));
+                    ready(word_of(1, f));
                 }
             } else {
-                wait_for(count_of(1, f), parts + 1);
+                wait_for(word_of(1, f), 1);
                 walk(std::integral_constant<int, kIvfCollect>{});
                 finished(count_of(2, f));
             }
@@ -1445,7 +1444,7 @@ static int ivf_scan_m(const CodeT *codes, const int64_t *offsets, int nlist, con
     // the queries it flagged (a full slice, or fewer than r codes in the probed lists): three passes
     const uint32_t np2 = next_pow2(r);
     const bool use_lds = np2 <= kSortLdsKeys;
-    size_t lds = kIvfRedoWaves * (M * 256 + 256 * 4);
+    size_t lds = kIvfRedoWaves * M * 256 + 256 * 4;
     if (use_lds && sizeof(uint64_t) * np2 > lds) lds = sizeof(uint64_t) * np2;
     rc = allow_dynamic_lds(reinterpret_cast<const void *>(&ivf_redo_kernel<M, CodeT>), static_cast<int>(lds));
     if (rc) return rc;
