@@ -82,6 +82,9 @@ int launch_small_tables(const float *queries, int nq, const float *derived, int 
                         const void *codes, int code_bytes, uint64_t n_codes, uint32_t r, uint8_t *qtab,
                         float *bounds, float *small, hipStream_t st, uint32_t *clear = nullptr, size_t clear_words = 0);
 int launch_derive(const float *codebooks, int m, int dsub, int full_bits, int small_bits, float *derived, hipStream_t st);
+// the Index step for many queries (ivf_probe.hip); ws: dcpq_ivf_probe_workspace_bytes
+bool probe_filter_serves(const float *queries, int nq, int D, const float *coarse, int nlist, int nprobe);
+int launch_probe_filter(const float *queries, int nq, int D, const float *coarse, int nlist, int nprobe, void *ws, int32_t *probe, hipStream_t st);
 int launch_full_tables(const float *queries, int nq, const float *codebooks, int m, int dsub,
                        float *tables, hipStream_t st);
 // Same kernel for any number of centroids (the coarse quantizer: m = 1, dsub = D, ncent = nlist).

@@ -191,3 +191,47 @@ def test_low_byte_plane_every_m(m):
     plane = binding.pack_low_bytes(codes)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(to_np(plane), (to_np(codes) & 255).astype(np.uint8))
+
+
+@pytest.mark.parametrize("D,nlist,nq,nprobe", [(128, 4100, 1100, 16), (64, 8192, 600, 30), (96, 65536, 70, 64), (16, 40004, 130, 7), (192, 4096, 1025, 16), (256, 4128, 1030, 3)])
+@pytest.mark.parametrize("data", ["clustered", "equal", "offset", "few places", "not finite"])
+def test_probe_of_many_queries_from_estimates(D, nlist, nq, nprobe, data):
+    # From 2^22 (query, centre) pairs on the distances are estimated first.  The centres that a query probes, in order, are those of the distances
+    # in double precision, rounded to fp32, equal ones by number.  "equal": every centre sixteen times; "offset": differences far smaller than the
+    # components; "few places": more centres within the error of the estimate than there is room for; "not finite": centres and a
+    # query that are not, or far out of the range of fp16.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + nlist)
+    means = 40.0 * torch.randn((64, D), generator=g, device=DEV)
+    def draw(n, spread):
+        return means[torch.randint(0, 64, (n,), generator=g, device=DEV)] + spread * torch.randn((n, D), generator=g, device=DEV)
+    coarse, y = draw(nlist, 5.0), draw(nq, 5.0)
+    if data == "equal":
+        coarse = coarse[torch.arange(nlist, device=DEV) % (nlist // 16)].contiguous()
+    elif data == "offset":
+        coarse, y = 5000.0 + 1e-2 * coarse, 5000.0 + 1e-2 * y
+    elif data == "few places":
+        coarse = means[torch.arange(nlist, device=DEV) % 2] + 1e-4 * torch.randn((nlist, D), generator=g, device=DEV)
+    elif data == "not finite":
+        coarse[5, 3], coarse[7, 0], coarse[11] = float("nan"), float("inf"), 1e7
+        coarse[13] *= 1e6
+        y[3] = coarse[13] + 1.0
+        y[9, 1] = float("nan")
+    probe = binding.ivf_probe(y, coarse, nprobe)
+    torch.cuda.synchronize()
+    probe = probe.long()
+    for q0 in range(0, nq, 32):
+        yq = y[q0:q0 + 32].double()
+        d = torch.zeros((yq.shape[0], nlist), dtype=torch.float64, device=DEV)
+        for t in range(0, D, 16):
+            d += ((yq[:, None, t:t + 16] - coarse[None, :, t:t + 16].double()) ** 2).sum(2)
+        fine = torch.isfinite(yq).all(1)
+        d32 = d.float()
+        d32[torch.isnan(d32)] = float("inf")
+        want = torch.sort(d32, dim=1, stable=True).indices[:, :nprobe]
+        got = probe[q0:q0 + 32]
+        assert (torch.sort(got[fine], 1).values.diff(dim=1) > 0).all()
+        # (a double-precision sum in another order can round to the neighbouring fp32 number)
+        np.testing.assert_allclose(to_np(d.gather(1, got)[fine]), to_np(d.gather(1, want)[fine]), rtol=2.0 ** -23)
+        if data in ("clustered", "equal"):
+            assert (got != want).sum() <= 2
