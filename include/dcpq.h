@@ -299,8 +299,8 @@ int dcpq_plain_search(const float *tables, uint32_t n_entries, const void *codes
  *                       point) up to its room, until no point is left; distances as fp32;
  *   final codebook      (step 3) the members of group l in increasing temporary index get the final
  *                       indices (0 << bbar) | l, (1 << bbar) | l, ...  (property P1).
- * dcpq_kmeans_same_size (and dcpq_build_quantizers, which calls it) reads a counter back after every few
- * rounds and so SYNCHRONIZES the stream; the other calls only enqueue.  Workspaces 256-byte aligned.
+ * dcpq_kmeans_same_size and dcpq_build_quantizers read counters of the balanced assignments back and so
+ * SYNCHRONIZE the stream; the other calls only enqueue.  Workspaces 256-byte aligned.
  *
  *   dcpq_assign   points: n rows of ld floats, sub-vector j in columns j*dsub .. (j+1)*dsub-1;
  *                 codebooks [m][n_entries][dsub]; labels [n][m] of label_bytes (1, 2 or 4) each;

@@ -37,9 +37,7 @@ __global__ __launch_bounds__(256) void accumulate_kernel(const float *__restrict
     if (e >= n * static_cast<uint64_t>(m * d)) return;
     const uint64_t i = e / (m * d);
     const int at = static_cast<int>(e % (m * d)), j = at / d, t = at - j * d;
-    const uint32_t label = labels[i * m + j];
-    if (label >= static_cast<uint32_t>(k)) return;               // (no group: an assignment that was not finished, whose means nobody uses)
-    const size_t c = static_cast<size_t>(j) * k + label;
+    const size_t c = static_cast<size_t>(j) * k + labels[i * m + j];
     unsafeAtomicAdd(&sums[c * d + t], static_cast<double>(points[i * ld + at]));
     if (t == 0) atomicAdd(&counts[c], 1u);
 }
@@ -63,17 +61,28 @@ constexpr uint32_t kAcceptKeys = 4096;        // proposers of a group that are s
 
 // ---- balanced assignment ----------------------------------------------------------------------------
 // state: labels[n] (0xFFFFFFFF = no group yet), room[kbar], left[0] = points without a group; count[kbar]: proposers of a round
-// unfinished (optional): set to zero by the first iteration, and by a later one to one where the iteration before it has left points without a group
-__global__ __launch_bounds__(256) void balanced_init_kernel(uint32_t *labels, int n, uint32_t *room, uint32_t *count, int kbar, uint32_t *left,
-                                                            uint32_t *unfinished, int first)
+__global__ __launch_bounds__(256) void balanced_init_kernel(uint32_t *labels, int n, uint32_t *room, uint32_t *count, int kbar, uint32_t *left)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) labels[i] = 0xFFFFFFFFu;
     if (i < kbar) { room[i] = static_cast<uint32_t>(n / kbar); count[i] = 0; }
-    if (i == 0) {
-        if (unfinished) { if (first) *unfinished = 0; else if (left[0]) *unfinished = 1; }
-        left[0] = static_cast<uint32_t>(n);
+    if (i == 0) left[0] = static_cast<uint32_t>(n);
+}
+
+// The room that an assignment which was left after some rounds leaves the groups, from its labels.  One workgroup.
+__global__ __launch_bounds__(1024) void balanced_resume_kernel(const uint32_t *__restrict__ labels, int n, uint32_t *__restrict__ room, uint32_t *__restrict__ count,
+                                                               int kbar)
+{
+    __shared__ uint32_t have[256];
+    const int tid = threadIdx.x;
+    if (tid < 256) have[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += 1024) {
+        const uint32_t l = labels[i];
+        if (l < static_cast<uint32_t>(kbar)) atomicAdd(&have[l], 1u);
     }
+    __syncthreads();
+    if (tid < kbar) { room[tid] = static_cast<uint32_t>(n / kbar) - have[tid]; count[tid] = 0; }
 }
 
 // Every point without a group goes into the list of the group with room that is nearest to it (smallest (distance, index)), as a
@@ -180,14 +189,8 @@ __global__ __launch_bounds__(1024) void accept_kernel(uint32_t *__restrict__ lab
 // together at the end (a walk by the whole workgroup, three barriers for 1024 labels, copying as it goes: 167 us at k = 65536, 256 groups; so 22).
 __global__ __launch_bounds__(1024) void final_codebook_kernel(const float *__restrict__ temp, int k, int d,
                                                               const uint32_t *__restrict__ labels, int bbar,
-                                                              float *__restrict__ final_cb, uint32_t *perm,
-                                                              const uint32_t *__restrict__ left, uint32_t *__restrict__ unfinished)
+                                                              float *__restrict__ final_cb, uint32_t *perm)
 {
-    // (left, unfinished: of an assignment that was not waited for; where it is not done the codebook is left as it is)
-    if (left && (*left || *unfinished)) {                        // uniform
-        if (*left && blockIdx.x == 0 && threadIdx.x == 0) *unfinished = 1;
-        return;
-    }
     __shared__ uint32_t wsum[16];
     const uint32_t l = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -267,6 +270,8 @@ static uint32_t pow2_at_least(uint32_t x)
     return p;
 }
 
+constexpr int kRoundsAhead = 12;             // of a balanced assignment, before it is looked at with others
+constexpr int kMostLeft = 64;                // words for points without a group
 struct SameSizePlan { size_t off_T, off_count, off_room, off_left, off_list, off_means, total; uint32_t np2; };
 
 static SameSizePlan plan_same_size(int n, int d, int kbar)
@@ -277,68 +282,83 @@ static SameSizePlan plan_same_size(int n, int d, int kbar)
     p.off_T = off;     off = align_up(off + sizeof(float) * static_cast<size_t>(n) * kbar, 256);
     p.off_count = off; off = align_up(off + sizeof(uint32_t) * static_cast<size_t>(n), 256);     // (kbar <= n counters; as much as there always was here)
     p.off_room = off;  off = align_up(off + sizeof(uint32_t) * kbar, 256);
-    p.off_left = off;  off = align_up(off + 256, 256);
+    p.off_left = off;  off = align_up(off + sizeof(uint32_t) * kMostLeft, 256);
     p.off_list = off;  off = align_up(off + sizeof(uint64_t) * static_cast<size_t>(kbar) * p.np2, 256);
     p.off_means = off; off = align_up(off + means_bytes(kbar, d), 256);
     p.total = off;
     return p;
 }
 
-// Iterations of same-size k-means in a workspace of the plan.  unfinished: NULL, and every balanced assignment is waited for; or a word (of the 64 that
-// begin at off_left, not the first) that says whether one was not done in the rounds it was given, as a rule enough: the caller looks
-// at it once for all that it has enqueued, and starts again where it is set.
-constexpr int kRoundsAhead = 12;
-static int same_size_iterations(const float *points, int n, int d, int kbar, int iters, float *centroids, uint32_t *labels, uint8_t *base, const SameSizePlan &p,
-                                uint32_t *unfinished, hipStream_t st)
-{
-    float *T = reinterpret_cast<float *>(base + p.off_T);
-    uint32_t *count = reinterpret_cast<uint32_t *>(base + p.off_count);
-    uint32_t *room = reinterpret_cast<uint32_t *>(base + p.off_room);
-    uint32_t *left = reinterpret_cast<uint32_t *>(base + p.off_left);
-    uint64_t *list = reinterpret_cast<uint64_t *>(base + p.off_list);
-    for (int it = 0; it < iters; ++it) {
-        int rc = launch_distance_tables(points, n, centroids, 1, d, kbar, T, kStageTrain, st);
-        if (rc) return rc;
-        const int nb = (n > kbar ? n : kbar);
-        DCPQ_LAUNCH(kStageTrain, st, balanced_init_kernel, dim3((nb + 255) / 256), dim3(256), 0, labels, n, room, count, kbar, left, unfinished, it == 0);
-        DCPQ_CHECK_LAUNCH("balanced_init_kernel");
-        auto rounds = [&](int how_many) {
-            for (int round = 0; round < how_many; ++round) {
-                DCPQ_LAUNCH(kStageTrain, st, propose_kernel, dim3((n + kProposeBlock - 1) / kProposeBlock), dim3(64 * kProposeWaves), 0, T, n, kbar, labels, room,
-                            left, count, list, p.np2);
-                DCPQ_CHECK_LAUNCH("propose_kernel");
-                DCPQ_LAUNCH(kStageTrain, st, accept_kernel, dim3(kbar), dim3(1024), 0, labels, room, count, left, list, p.np2);
-                DCPQ_CHECK_LAUNCH("accept_kernel");
-            }
-            return DCPQ_OK;
-        };
-        if (unfinished) {
-            rc = rounds(kbar < kRoundsAhead ? kbar : kRoundsAhead);
-            if (rc) return rc;
-        } else {
-            // rounds until every point has a group; every round gives at least one point a group.  The count is read back after eight rounds,
-            // which is what it takes as a rule, and after every four more: a round too many returns at once.  (A round that
-            // leaves points without a group has filled one that turned them away: kbar rounds are enough.)
-            uint32_t h_left = static_cast<uint32_t>(n);
-            for (int round = 0, ahead = kbar < 8 ? kbar : 8; h_left > 0; ahead = 4) {
-                if (round > kbar) return fail(DCPQ_EHIP, "kmeans_same_size: balanced assignment did not finish");
-                rc = rounds(ahead);
-                if (rc) return rc;
-                round += ahead;
-                DCPQ_CHECK_HIP(hipMemcpyAsync(&h_left, left, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-                DCPQ_CHECK_HIP(hipStreamSynchronize(st));
-            }
-        }
-        rc = launch_means(points, static_cast<uint64_t>(n), d, 1, d, labels, kbar, centroids, base + p.off_means, st);
-        if (rc) return rc;
-    }
-    return DCPQ_OK;
-}
+// A balanced assignment of n points in a workspace of the plan, in parts: distances and empty groups (begin) or, for one that was left after some rounds, distances
+// and the room there still is (resume); rounds.  left: points without a group, one word.
+struct Balanced {
+    const float *points;
+    int n, d, kbar;
+    const float *centroids;
+    uint32_t *labels, *left;
+    uint8_t *base;
+    const SameSizePlan &p;
+    hipStream_t st;
 
-static int launch_final_codebook(const float *temp, int k, int d, const uint32_t *labels, int bbar, float *final_cb, uint32_t *perm, const uint32_t *left,
-                                 uint32_t *unfinished, hipStream_t st)
+    uint32_t *count() const { return reinterpret_cast<uint32_t *>(base + p.off_count); }
+    uint32_t *room() const { return reinterpret_cast<uint32_t *>(base + p.off_room); }
+
+    int distances() const { return launch_distance_tables(points, n, centroids, 1, d, kbar, reinterpret_cast<float *>(base + p.off_T), kStageTrain, st); }
+
+    int begin() const
+    {
+        const int rc = distances(), nb = n > kbar ? n : kbar;
+        if (rc) return rc;
+        DCPQ_LAUNCH(kStageTrain, st, balanced_init_kernel, dim3((nb + 255) / 256), dim3(256), 0, labels, n, room(), count(), kbar, left);
+        DCPQ_CHECK_LAUNCH("balanced_init_kernel");
+        return DCPQ_OK;
+    }
+
+    int resume() const
+    {
+        const int rc = distances();
+        if (rc) return rc;
+        DCPQ_LAUNCH(kStageTrain, st, balanced_resume_kernel, dim3(1), dim3(1024), 0, labels, n, room(), count(), kbar);
+        DCPQ_CHECK_LAUNCH("balanced_resume_kernel");
+        return DCPQ_OK;
+    }
+
+    int rounds(int how_many) const
+    {
+        uint64_t *list = reinterpret_cast<uint64_t *>(base + p.off_list);
+        for (int round = 0; round < how_many; ++round) {
+            DCPQ_LAUNCH(kStageTrain, st, propose_kernel, dim3((n + kProposeBlock - 1) / kProposeBlock), dim3(64 * kProposeWaves), 0,
+                        reinterpret_cast<const float *>(base + p.off_T), n, kbar, labels, room(), left, count(), list, p.np2);
+            DCPQ_CHECK_LAUNCH("propose_kernel");
+            DCPQ_LAUNCH(kStageTrain, st, accept_kernel, dim3(kbar), dim3(1024), 0, labels, room(), count(), left, list, p.np2);
+            DCPQ_CHECK_LAUNCH("accept_kernel");
+        }
+        return DCPQ_OK;
+    }
+
+    // Rounds until every point has a group, `ahead` at first; every round gives at least one point a group.  The count is read back after
+    // these and after every four more: a round too many returns at once.  (A round that
+    // leaves points without a group has filled one that turned them away: kbar rounds are enough.)
+    int finish(int ahead) const
+    {
+        uint32_t h_left = static_cast<uint32_t>(n);
+        for (int round = 0; h_left > 0; ahead = 4) {
+            if (round > kbar) return fail(DCPQ_EHIP, "kmeans_same_size: balanced assignment did not finish");
+            const int rc = rounds(ahead);
+            if (rc) return rc;
+            round += ahead;
+            DCPQ_CHECK_HIP(hipMemcpyAsync(&h_left, left, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+            DCPQ_CHECK_HIP(hipStreamSynchronize(st));
+        }
+        return DCPQ_OK;
+    }
+
+    int means(float *to) const { return launch_means(points, static_cast<uint64_t>(n), d, 1, d, labels, kbar, to, base + p.off_means, st); }
+};
+
+static int launch_final_codebook(const float *temp, int k, int d, const uint32_t *labels, int bbar, float *final_cb, uint32_t *perm, hipStream_t st)
 {
-    DCPQ_LAUNCH(kStageTrain, st, final_codebook_kernel, dim3(1 << bbar), dim3(1024), 0, temp, k, d, labels, bbar, final_cb, perm, left, unfinished);
+    DCPQ_LAUNCH(kStageTrain, st, final_codebook_kernel, dim3(1 << bbar), dim3(1024), 0, temp, k, d, labels, bbar, final_cb, perm);
     DCPQ_CHECK_LAUNCH("final_codebook_kernel");
     return DCPQ_OK;
 }
@@ -412,7 +432,17 @@ extern "C" int dcpq_kmeans_same_size(const float *points, int n, int d, int kbar
     DCPQ_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255) == 0, "kmeans_same_size: workspace must be 256-byte aligned");
     const SameSizePlan p = plan_same_size(n, d, kbar);
     if (workspace_bytes < p.total) return fail(DCPQ_EWORKSPACE, "kmeans_same_size: workspace %zu < %zu bytes", workspace_bytes, p.total);
-    return same_size_iterations(points, n, d, kbar, iters, centroids, labels, static_cast<uint8_t *>(workspace), p, nullptr, as_stream(stream));
+    uint8_t *base = static_cast<uint8_t *>(workspace);
+    const Balanced a{points, n, d, kbar, centroids, labels, reinterpret_cast<uint32_t *>(base + p.off_left), base, p, as_stream(stream)};
+    for (int it = 0; it < iters; ++it) {
+        int rc = a.begin();
+        if (rc) return rc;
+        rc = a.finish(kbar < 8 ? kbar : 8);                      // (eight rounds are what it takes as a rule)
+        if (rc) return rc;
+        rc = a.means(centroids);
+        if (rc) return rc;
+    }
+    return DCPQ_OK;
 }
 
 extern "C" int dcpq_build_final_codebook(const float *temp_codebook, int k, int d, const uint32_t *labels, int bbar,
@@ -422,23 +452,23 @@ extern "C" int dcpq_build_final_codebook(const float *temp_codebook, int k, int 
     DCPQ_REQUIRE(k >= 1 && d >= 1 && bbar >= 0 && bbar <= 8 && k % (1 << bbar) == 0, "build_final_codebook: k=%d d=%d bbar=%d", k, d, bbar);
     DCPQ_REQUIRE(temp_codebook && labels && final_codebook && perm, "build_final_codebook: null pointer");
     DCPQ_REQUIRE(temp_codebook != final_codebook, "build_final_codebook: in place is not supported");
-    return launch_final_codebook(temp_codebook, k, d, labels, bbar, final_codebook, perm, nullptr, nullptr, as_stream(stream));
+    return launch_final_codebook(temp_codebook, k, d, labels, bbar, final_codebook, perm, as_stream(stream));
 }
 
-// Alg. 2 for all m sub-quantizers.  Workspace: labels of the training points, the temporary codebook, labels
-// and order of its centroids, and the larger of the two k-means workspaces.
-struct BuildPlan { size_t off_plabels, off_temp, off_clabels, off_perm, off_cbar, off_ws, ws_bytes, total; };
+// Alg. 2 for all m sub-quantizers.  Workspace: labels of the training points, labels and groups' centroids of a codebook, a copy
+// and the order of one, and the larger of the two k-means workspaces.
+struct BuildPlan { size_t off_clabels, clabels_bytes, group_bytes, off_temp, off_perm, off_ws, ws_bytes, total; };
 
 static BuildPlan plan_build(uint64_t n, int dsub, int b, int bbar)
 {
     BuildPlan p{};
     const int k = 1 << b, kbar = 1 << bbar;
-    size_t off = 0;
-    p.off_plabels = off; off = align_up(off + sizeof(uint32_t) * n, 256);
+    p.clabels_bytes = align_up(sizeof(uint32_t) * k, 256);
+    p.group_bytes = align_up(sizeof(float) * static_cast<size_t>(kbar) * dsub, 256);
+    size_t off = align_up(sizeof(uint32_t) * n, 256);
+    p.off_clabels = off; off += p.clabels_bytes + p.group_bytes;
     p.off_temp = off;    off = align_up(off + sizeof(float) * static_cast<size_t>(k) * dsub, 256);
-    p.off_clabels = off; off = align_up(off + sizeof(uint32_t) * k, 256);
     p.off_perm = off;    off = align_up(off + sizeof(uint32_t) * k, 256);
-    p.off_cbar = off;    off = align_up(off + sizeof(float) * static_cast<size_t>(kbar) * dsub, 256);
     const size_t a = means_bytes(k, dsub), c = plan_same_size(k, dsub, kbar).total;
     p.ws_bytes = a > c ? a : c;
     p.off_ws = off;      off = align_up(off + p.ws_bytes, 256);
@@ -466,11 +496,6 @@ extern "C" int dcpq_build_quantizers(const float *train, uint64_t n_train, int m
     const BuildPlan p = plan_build(n_train, dsub, b, bbar);
     if (workspace_bytes < p.total) return fail(DCPQ_EWORKSPACE, "build_quantizers: workspace %zu < %zu bytes", workspace_bytes, p.total);
     uint8_t *base = static_cast<uint8_t *>(workspace);
-    uint32_t *plabels = reinterpret_cast<uint32_t *>(base + p.off_plabels);
-    float *temp = reinterpret_cast<float *>(base + p.off_temp);
-    uint32_t *clabels = reinterpret_cast<uint32_t *>(base + p.off_clabels);
-    uint32_t *perm = reinterpret_cast<uint32_t *>(base + p.off_perm);
-    float *cbar = reinterpret_cast<float *>(base + p.off_cbar);
     const int k = 1 << b, kbar = 1 << bbar, D = m * dsub;
     hipStream_t st = as_stream(stream);
     // step 1: k-means of the centroids the caller left in `codebooks`, in place (the points' labels after the last iteration are no
@@ -481,40 +506,62 @@ extern "C" int dcpq_build_quantizers(const float *train, uint64_t n_train, int m
     while (together < m && align_up(sizeof(uint32_t) * n_train * (together + 1), 256) + means_bytes(static_cast<size_t>(together + 1) * k, dsub) <= p.ws_bytes) ++together;
     for (int j = 0; j < m; j += together ? together : 1) {
         const int mj = !together ? 1 : m - j < together ? m - j : together;
-        uint32_t *labels = together ? reinterpret_cast<uint32_t *>(base + p.off_ws) : plabels;
+        uint32_t *labels = reinterpret_cast<uint32_t *>(together ? base + p.off_ws : base);
         void *sums = together ? base + p.off_ws + align_up(sizeof(uint32_t) * n_train * mj, 256) : base + p.off_ws;
         const int rc = launch_kmeans(train + static_cast<size_t>(j) * dsub, n_train, D, mj, dsub, k, iters, codebooks + static_cast<size_t>(j) * k * dsub,
                                      labels, sums, st);
         if (rc) return rc;
     }
-    // Steps 2 and 3 of all sub-quantizers are enqueued without waiting for the balanced assignments, and looked at together: those
-    // that were not done have left their codebook as it was, and are run again, waited for (131072 x 8 x 16: 9.45 ms with every assignment waited for, 9.0 so).
+    // Steps 2 and 3.  An iteration's balanced assignments of several sub-quantizers are enqueued one after the other, each with the rounds that it takes as a rule and
+    // some more, and looked at together, which saves a wait for each (131072 x 8 x 16: 9.45 ms with every assignment waited for, 9.0 so).  One
+    // that was not done (crowded centroids: as many rounds as there are groups) goes on from the labels it has reached; only its distances are
+    // computed again.  So labels and centroids of every sub-quantizer of a batch are kept: in the place of the training points' labels, and of the
+    // codebook's copy too where the lists of proposers, which nobody reads once the assignments are done, are long enough to take copy and order.
     const SameSizePlan sp = plan_same_size(k, dsub, kbar);
-    uint32_t *left = reinterpret_cast<uint32_t *>(base + p.off_ws + sp.off_left);
-    auto steps23 = [&](int j, uint32_t *unfinished) {
-        float *cj = codebooks + static_cast<size_t>(j) * k * dsub;
-        // (step 3 reads the temporary codebook while it writes the final one)
-        DCPQ_CHECK_HIP(hipMemcpyAsync(temp, cj, sizeof(float) * static_cast<size_t>(k) * dsub, hipMemcpyDeviceToDevice, st));
-        // step 2: groups of equal size, started from the first 2^bbar temporary centroids
-        DCPQ_CHECK_HIP(hipMemcpyAsync(cbar, temp, sizeof(float) * static_cast<size_t>(kbar) * dsub, hipMemcpyDeviceToDevice, st));
-        int rc = same_size_iterations(temp, k, dsub, kbar, iters_same_size, cbar, clabels, base + p.off_ws, sp, unfinished, st);
-        if (rc) return rc;
-        // step 3: final order; the derived codebook is the mean of every low-bits group of it
-        rc = launch_final_codebook(temp, k, dsub, clabels, bbar, cj, perm, unfinished ? left : nullptr, unfinished, st);
-        return rc;
-    };
-    static_assert(32 + 1 <= 64, "a word per sub-quantizer behind the counter");
-    for (int j = 0; j < m; ++j) {
-        const int rc = steps23(j, left + 1 + j);
-        if (rc) return rc;
-    }
-    uint32_t unfinished[32];
-    DCPQ_CHECK_HIP(hipMemcpyAsync(unfinished, left + 1, sizeof(uint32_t) * m, hipMemcpyDeviceToHost, st));
-    DCPQ_CHECK_HIP(hipStreamSynchronize(st));
-    for (int j = 0; j < m; ++j) {
-        if (!unfinished[j]) continue;
-        const int rc = steps23(j, nullptr);
-        if (rc) return rc;
+    const size_t copy_bytes = align_up(sizeof(float) * static_cast<size_t>(k) * dsub, 256);
+    const bool in_lists = copy_bytes + sizeof(uint32_t) * k <= sizeof(uint64_t) * static_cast<size_t>(kbar) * sp.np2;
+    float *temp = reinterpret_cast<float *>(base + (in_lists ? p.off_ws + sp.off_list : p.off_temp));
+    uint32_t *perm = reinterpret_cast<uint32_t *>(in_lists ? base + p.off_ws + sp.off_list + copy_bytes : base + p.off_perm);
+    const size_t per = p.clabels_bytes + p.group_bytes, places = (in_lists ? p.off_ws : p.off_temp) / per;        // (one at least)
+    const int batch = places < static_cast<size_t>(m) ? static_cast<int>(places) : m, ahead = kbar < kRoundsAhead ? kbar : kRoundsAhead;
+    uint32_t *left = reinterpret_cast<uint32_t *>(base + p.off_ws + sp.off_left);         // a word per sub-quantizer of a batch
+    for (int j0 = 0; j0 < m; j0 += batch) {
+        const int mj = m - j0 < batch ? m - j0 : batch;
+        auto codebook = [&](int i) { return codebooks + static_cast<size_t>(j0 + i) * k * dsub; };
+        auto labels = [&](int i) { return reinterpret_cast<uint32_t *>(base + per * i); };
+        auto groups = [&](int i) { return reinterpret_cast<float *>(base + per * i + p.clabels_bytes); };
+        for (int it = 0; it < iters_same_size; ++it) {
+            // (groups are started from the first 2^bbar temporary centroids)
+            auto assignment = [&](int i) { return Balanced{codebook(i), k, dsub, kbar, it ? groups(i) : codebook(i), labels(i), left + i, base + p.off_ws, sp, st}; };
+            for (int i = 0; i < mj; ++i) {
+                const Balanced a = assignment(i);
+                int rc = a.begin();
+                if (rc) return rc;
+                rc = a.rounds(ahead);
+                if (rc) return rc;
+            }
+            uint32_t h_left[kMostLeft];
+            DCPQ_CHECK_HIP(hipMemcpyAsync(h_left, left, sizeof(uint32_t) * mj, hipMemcpyDeviceToHost, st));
+            DCPQ_CHECK_HIP(hipStreamSynchronize(st));
+            for (int i = 0; i < mj; ++i) {
+                const Balanced a = assignment(i);
+                int rc = DCPQ_OK;
+                if (h_left[i]) {
+                    rc = a.resume();
+                    if (rc) return rc;
+                    rc = a.finish(4);
+                    if (rc) return rc;
+                }
+                if (it + 1 < iters_same_size) rc = a.means(groups(i));       // (nobody reads those of the last assignment)
+                if (rc) return rc;
+            }
+        }
+        for (int i = 0; i < mj; ++i) {
+            // step 3: final order; it reads the temporary codebook while it writes the final one.  The derived codebook is the mean of every low-bits group of it
+            DCPQ_CHECK_HIP(hipMemcpyAsync(temp, codebook(i), sizeof(float) * static_cast<size_t>(k) * dsub, hipMemcpyDeviceToDevice, st));
+            const int rc = launch_final_codebook(temp, k, dsub, labels(i), bbar, codebook(i), perm, st);
+            if (rc) return rc;
+        }
     }
     return launch_derive(codebooks, m, dsub, b, bbar, derived, st);
 }

@@ -391,24 +391,57 @@ def test_assign_of_many_points_agrees_with_few(dsub, m, data):
         assert (chosen <= best * (1 + 4 * (dsub + 1) * 2.0 ** -53)).all(), "sub-quantizer %d" % j
 
 
-@pytest.mark.parametrize("iters_same", [1, 2])
-def test_training_where_a_balanced_assignment_takes_more_rounds_than_it_is_given(iters_same):
-    # Sub-quantizers 0 and 2: sixteen groups in a row and all other centroids before the first of them, so that a round fills one
-    # group and sixteen are needed (twelve are enqueued ahead); 1 and 3: a few rounds.  The same codebooks as step by step.
-    m, dsub, b, bbar = 4, 4, 8, 4
-    g = gen(71)
+def crowded_codebooks(m, b, dsub, bbar, crowded, seed):
+    """Starting centroids; of the sub-quantizers `crowded` 2^bbar groups lie in a row and all other centroids before the first of them, so that a
+    round of the balanced assignment fills one group and as many rounds as groups are needed."""
+    g = gen(seed)
     init = torch.randint(-300, 300, (m, 1 << b, dsub), generator=g, device=DEV).float() / 64.0        # (sums of these are exact)
-    for j in (0, 2):
+    for j in crowded:
         init[j] = 0.0
-        init[j, :, 1] = torch.arange(1 << b, device=DEV) / 1024.0
-        init[j, :16, 0] = torch.arange(1, 17, device=DEV).float()
-    x = torch.randn((300, m * dsub), generator=g, device=DEV)
+        init[j, :, 1] = torch.arange(1 << b, device=DEV) / (4.0 * (1 << b))
+        init[j, :1 << bbar, 0] = torch.arange(1, (1 << bbar) + 1, device=DEV).float()
+    return init, torch.randn((300, m * dsub), generator=g, device=DEV)
+
+
+@pytest.mark.parametrize("m,dsub,b,bbar,iters_same,crowded", [
+    (4, 4, 8, 4, 1, (0, 2)), (4, 4, 8, 4, 2, (0, 2)), (4, 4, 8, 4, 3, (0, 1, 2, 3)),
+    (8, 3, 8, 5, 2, (7,)),                                       # 300 training points: labels of several codebooks in the place of theirs
+    (32, 2, 8, 4, 2, (0, 13, 31)), (2, 40, 8, 8, 1, (1,)),
+    (4, 1, 16, 4, 2, ()), (4, 8, 16, 4, 2, (1, 3)),              # 65536 centroids: a batch of two or more, one with a copy outside the lists
+    (2, 40, 16, 4, 2, (0,)), (8, 2, 16, 1, 1, ()),               # lists of proposers too short for a codebook's copy
+])
+def test_training_where_a_balanced_assignment_takes_more_rounds_than_it_is_given(m, dsub, b, bbar, iters_same, crowded):
+    # Twelve rounds are enqueued ahead; the same codebooks as step by step, where every assignment is waited for.
+    init, x = crowded_codebooks(m, b, dsub, bbar, crowded, 71)
     cb, derived = binding.build_quantizers(x, init, bbar, 0, iters_same)
     torch.cuda.synchronize()
     for j in range(m):
         _, labels = binding.kmeans_same_size(init[j].contiguous(), init[j, :1 << bbar].contiguous(), iters_same)
         final, _ = binding.build_final_codebook(init[j].contiguous(), labels, bbar)
         np.testing.assert_array_equal(to_np(cb)[j], to_np(final), err_msg="sub-quantizer %d" % j)
-        lab, _ = oracle.kmeans_same_size(to_np(init[j]), to_np(init[j, :1 << bbar]), iters_same)[::-1]
-        np.testing.assert_array_equal(to_np(labels), lab)
+        if b == 8:
+            lab, _ = oracle.kmeans_same_size(to_np(init[j]), to_np(init[j, :1 << bbar]), iters_same)[::-1]
+            np.testing.assert_array_equal(to_np(labels), lab)
     np.testing.assert_array_equal(to_np(derived), to_np(binding.derive_codebooks(cb, bbar)))
+
+
+def test_training_repeats_no_rounds_of_a_balanced_assignment():
+    # Crowded starting centroids: what is enqueued ahead counts, and an assignment that takes more goes on from there.  Fewer launches than step
+    # by step, plus what an assignment that is taken up again costs: a distance table, the rooms, and at most as many rounds too many as are enqueued at a time (two launches each).
+    m, b, dsub, bbar, iters = 8, 8, 4, 4, 5
+    init, x = crowded_codebooks(m, b, dsub, bbar, range(m), 72)
+    counts = []
+    for whole in (True, False):
+        binding.profile_enable(True)
+        try:
+            if whole:
+                binding.build_quantizers(x, init, bbar, 0, iters)
+            else:
+                for j in range(m):
+                    _, labels = binding.kmeans_same_size(init[j].contiguous(), init[j, :1 << bbar].contiguous(), iters)
+                    binding.build_final_codebook(init[j].contiguous(), labels, bbar)
+            torch.cuda.synchronize()
+            counts.append(binding.profile_read()["train"][1])
+        finally:
+            binding.profile_enable(False)
+    assert counts[0] <= counts[1] + m * iters * (2 + 2 * 4)
