@@ -65,15 +65,15 @@ __device__ inline T agent_load(const T *p) { return __hip_atomic_load(p, __ATOMI
 template <typename T>
 __device__ inline void agent_store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// One item of a pass: WAVES units (from unit xb * WAVES on) for the queries at positions q0 .. q0 + QT - 1, by a workgroup.
+// One item of a pass: a unit for each of the WAVES wavefronts of a workgroup (u: this wavefront's, past the last: none), for the queries at positions q0 .. q0 + QT - 1.
 // REDO: passes run in one launch, and what one of them leaves for the next goes through device-scope stores and loads.
 template <int M, int QT, int MODE, typename CodeT, int WAVES, bool REDO>
 __device__ __forceinline__ void scan_item(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t unit_stride, int q0, int nqt,
-                                          uint32_t xb, const ScanArrays &w, uint8_t *smem)
+                                          uint32_t u, const ScanArrays &w, uint8_t *smem)
 {
     uint8_t *ltab = smem;                                                   // [QT][M][256]
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + QT * M * 256);    // [QT][256] (kHist)
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
 
     __syncthreads();                           // previous item's LDS is no longer in use
     for (int q = 0; q < nqt; ++q) {            // stage the tile's tables (rows of absent queries are never read)
@@ -86,7 +86,6 @@ __device__ __forceinline__ void scan_item(const CodeT *__restrict__ codes, uint6
         for (int v = tid; v < QT * 256; v += 64 * WAVES) lhist[v] = 0;
     __syncthreads();
 
-    const uint32_t u = xb * WAVES + wave;               // this wavefront's unit
     const uint64_t begin = static_cast<uint64_t>(u) * unit_stride;
     const uint64_t end = (u < nunits) ? min(n_codes, begin + unit) : begin;
 
@@ -181,7 +180,9 @@ __global__ __launch_bounds__(64 * WAVES) void scan_kernel(const CodeT *__restric
     for (uint64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
         const int q0 = static_cast<int>(item / nxb) * QT;
         const int nqt = min(QT, nq - q0);
-        scan_item<M, QT, MODE, CodeT, WAVES, false>(codes, n_codes, unit, nunits, unit_stride, q0, nqt, static_cast<uint32_t>(item % nxb), w, smem);
+        // (of the sample a workgroup takes units that lie far apart: neighbouring ones may hold the same code all over, whose counts queue for one word of LDS)
+        const uint32_t xb = static_cast<uint32_t>(item % nxb), u = MODE == kHist && end_of.done ? xb + wave * nxb : xb * WAVES + wave;
+        scan_item<M, QT, MODE, CodeT, WAVES, false>(codes, n_codes, unit, nunits, unit_stride, q0, nqt, u, w, smem);
         if (MODE == kHist && end_of.done) {
             // Everything this workgroup has added is in place before its count is.  (Histograms are only added to by
             // device-scope atomics, whose completion is all there is to wait
@@ -255,17 +256,17 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
         if (item >= all) return;                                      // uniform
         if (item < 3 * per) {
             const uint64_t in_pass = item % per;
-            const uint32_t tile = static_cast<uint32_t>(in_pass / nxb), xb = static_cast<uint32_t>(in_pass % nxb);
+            const uint32_t tile = static_cast<uint32_t>(in_pass / nxb), u = static_cast<uint32_t>(in_pass % nxb) * kRedoWaves + wave;
             const int q0 = static_cast<int>(tile) * QT, nqt = min(QT, nq - q0);
             if (item < per) {
-                scan_item<M, QT, kHist, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                scan_item<M, QT, kHist, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
                 if (finished(&done_hist[tile])) {                     // uniform
                     for (int q = wave; q < nqt; q += kRedoWaves) exact_threshold(w.hist + static_cast<size_t>(q0 + q) * 256, w.r, w.thr + 2 * (q0 + q));
                     ready(&done_hist[tile]);
                 }
             } else if (item < 2 * per) {
                 wait_for(&done_hist[tile], nxb + 1);
-                scan_item<M, QT, kTieCount, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                scan_item<M, QT, kTieCount, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
                 if (finished(&done_tie[tile])) {                      // uniform
                     for (int q = wave; q < nqt; q += kRedoWaves)
                         tie_quotas(w.tie + static_cast<size_t>(q0 + q) * nunits, nunits, agent_load(&w.thr[2 * (q0 + q) + 1]));
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
                 }
             } else {
                 wait_for(&done_tie[tile], nxb + 1);
-                scan_item<M, QT, kCollect, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, xb, w, smem);
+                scan_item<M, QT, kCollect, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
                 finished(&done_collect[tile]);
             }
             continue;

@@ -615,6 +615,33 @@ def test_scan_estimated_bound_too_low_is_redone(N, Q, pilot):
           % (stages.get("scan_hist"), stages.get("scan_tiecount"), stages.get("scan_collect")), flush=True)
 
 
+@pytest.mark.parametrize("Q", [100, 251])
+def test_sample_of_an_array_with_a_crowded_stretch_takes_no_longer(Q):
+    """A stretch of the array that holds one code over and over: the counts of the sampled units that lie in it queue for single words of LDS, and
+    must not fall to a few workgroups (of neighbouring units: 1.9 times as long as over random codes; of units far apart 1.05)."""
+    N, m, r = 8_000_000, 8, 3000
+    g = torch.Generator(device=DEV)
+    g.manual_seed(6)
+    codes = torch.randint(-32768, 32768, (N, m), generator=g, device=DEV, dtype=torch.int16)
+    crowded = codes.clone()
+    crowded[-N // 20:] = codes[-1]
+    qtab = torch.randint(0, 60, (Q, m, 256), generator=g, device=DEV, dtype=torch.uint8)
+    ms = []
+    for c in (codes, crowded):
+        times = []
+        for _ in range(8):
+            binding.profile_enable(True)
+            try:
+                binding.scan_candidates(c.view(torch.uint16), qtab, r)
+                torch.cuda.synchronize()
+                times.append(binding.profile_read()["scan_hist"][0])
+            finally:
+                binding.profile_enable(False)
+        ms.append(min(times))
+    print("sample histogram, ms: random %.4f, crowded %.4f" % tuple(ms), flush=True)
+    assert ms[1] < 1.5 * ms[0]
+
+
 @pytest.mark.parametrize("m,N,Q,r", [(4, 90_001, 5, 600), (8, 300_017, 70, 1500), (8, 2_000_003, 17, 4000), (16, 33_001, 130, 9000)])
 def test_smallest_workspace_gives_the_same_results(m, N, Q, r):
     """A workspace smaller than the stated size is accepted as long as it holds what the scan cannot do without; the
