@@ -155,7 +155,8 @@ int dcpq_scan_candidates_packed(const uint8_t *plane, uint64_t n_codes, int m, c
  * itself allocates nothing.  A problem whose smallest workspace (dcpq_scan_plan) exceeds
  * dcpq_static_scratch_bytes() by more than 256 KiB (counters that the stated size has never included)
  * is refused with DCPQ_EWORKSPACE before anything is launched.  All
- * calls on one GPU share the one array: two of them must not overlap in time (they would race),
+ * calls on one GPU share the one array: two of them must not overlap in time (they would race:
+ * wrong candidates, after some twenty seconds where one waits for what the other has overwritten),
  * whichever streams they use. */
 #define DCPQ_STATIC_SCRATCH_BYTES (64u << 20)
 size_t dcpq_static_scratch_bytes(void);

@@ -22,6 +22,7 @@
 
 #include "common.h"
 #include "ivf_select.h"
+#include "redo_wait.h"
 #include "scan_internal.h"
 
 namespace dcpq {
@@ -591,7 +592,8 @@ __device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict_
 // What the items of the next pass wait for is a word away from the count that the workgroups of this one add to: their loads of that line
 // queued the adds (106 -> 100 us there).  A workgroup adds its counts to the query's histogram once, from its own in LDS.
 // done: [3][nq] items that are done, of each pass, a memory line apart (side by side their returning atomics queue for one line), and beside
-// the last pass's count the two words that the first two passes set; ticket: the counter; all at zero on entry.
+// the last pass's count the two words that the first two passes set; ticket: the counter; all at zero on entry.  (Not this call's own: given up,
+// redo_wait.h; queries that were not finished get no candidates then.)
 
 template <int M, typename CodeT>
 __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const CodeT *__restrict__ codes, const IvfUnit *__restrict__ units,
@@ -604,7 +606,7 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
     if (nf == 0) return;
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ unsigned long long s_item;
-    __shared__ uint32_t s_last;
+    __shared__ uint32_t s_last, s_there;
     uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + kIvfRedoWaves * M * 256);
     const int tid = threadIdx.x, wave = tid >> 6;
     const uint32_t parts = min(256u, max(1u, 512u / nf));             // ... of a query
@@ -612,9 +614,13 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
     auto count_of = [&](uint32_t pass, uint32_t f) { return done + (static_cast<size_t>(pass) * nq + f) * kIvfRedoLine; };
     auto word_of = [&](uint32_t pass, uint32_t f) { return count_of(2, f) + 1 + pass; };
     auto wait_for = [&](const uint32_t *count, uint32_t n) {
-        if (tid == 0)
-            while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n) __builtin_amdgcn_s_sleep(16);
+        if (tid == 0) {
+            s_there = wait_until([count] { return __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                                 [] { __builtin_amdgcn_s_sleep(16); }, n, kRedoPatience);
+            if (!s_there) atomicOr(ticket, kRedoGivenUp);
+        }
         __syncthreads();
+        return s_there != 0;
     };
     auto finished = [&](uint32_t *count) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -632,9 +638,11 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
         __syncthreads();
         if (tid == 0) s_item = atomicAdd(ticket, 1ull);
         __syncthreads();
-        const uint64_t item = s_item;
+        const uint64_t item = s_item & ~kRedoGivenUp;
+        const bool given_up = s_item != item;
         if (item >= all) return;                                      // uniform
         if (item < 3 * per) {
+            if (given_up) continue;                                   // uniform
             const uint32_t pass = static_cast<uint32_t>(item / per), in_pass = static_cast<uint32_t>(item % per), f = in_pass / parts, part = in_pass % parts;
             const int q = qlist[f];
             auto walk = [&](auto mode) {
@@ -658,7 +666,7 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
                     ready(word_of(0, f));
                 }
             } else if (pass == 1) {
-                wait_for(word_of(0, f), 1);
+                if (!wait_for(word_of(0, f), 1)) continue;            // uniform
                 walk(std::integral_constant<int, kIvfTieCount>{});
                 if (finished(count_of(1, f))) {                       // uniform
                     if (wave == 0)
@@ -667,15 +675,18 @@ __global__ __launch_bounds__(64 * kIvfRedoWaves) void ivf_redo_kernel(const Code
                     ready(word_of(1, f));
                 }
             } else {
-                wait_for(word_of(1, f), 1);
+                if (!wait_for(word_of(1, f), 1)) continue;            // uniform
                 walk(std::integral_constant<int, kIvfCollect>{});
                 finished(count_of(2, f));
             }
             continue;
         }
         const uint32_t f = static_cast<uint32_t>(item - 3 * per);
-        wait_for(count_of(2, f), parts);
         const size_t q = qlist[f];
+        if (given_up || !wait_for(count_of(2, f), parts)) {           // uniform
+            for (uint32_t t = tid; t < r; t += 64 * kIvfRedoWaves) { cand_id[q * r + t] = 0xFFFFFFFFu; cand_qd[q * r + t] = 255; }
+            continue;
+        }
         uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + q * n_pow2;
         for (uint32_t t = tid; t < n_pow2; t += 64 * kIvfRedoWaves)
             a[t] = t < r ? __hip_atomic_load(&keys[q * r + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;

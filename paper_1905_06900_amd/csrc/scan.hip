@@ -16,7 +16,7 @@
 //
 // Three-pass work layout: a wavefront owns one "unit" of consecutive codes and walks it 64 codes
 // at a time (lane = code, fully coalesced 2m-byte loads), so id order inside a unit is
-// (iteration, lane).  A workgroup is 4 wavefronts and serves a tile of QT queries whose u8 tables
+// (iteration, lane).  A workgroup is 4 wavefronts (the sample's 4, 8 or 16, the redo's 16) and serves a tile of QT queries whose u8 tables
 // (QT * m * 256 bytes) sit in LDS; each lane gathers its m table bytes per query from LDS.
 // Over a whole batch the passes are launches of their own; for the few flagged queries (as a rule none, their number is known on the
 // device only) all of them and the sort are one launch (scan_redo_kernel).
@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "redo_wait.h"
 #include <mutex>
 
 #include "scan_internal.h"
@@ -212,8 +213,9 @@ __global__ __launch_bounds__(64 * WAVES) void scan_kernel(const CodeT *__restric
 // Items are handed out in order -- the histogram's of all query tiles, then the tie counts', the collection's, the queries
 // to sort -- by one counter, and an item waits for those of the pass before it: these have been handed out already, to workgroups that are running
 // and wait, if at all, for items handed out earlier still, so that every wait ends whatever number of workgroups the chip holds at a time.
+// (Should the counters not be this call's own, it is given up; redo_wait.h.  Queries that were not finished then get the first r ids.)
 // What one item leaves for another goes through device-scope atomics, stores and loads, and is in place before the item is counted as done.
-// sync: [3][tiles] items that are done, of each pass (one more once thresholds or quotas are there); ticket: the counter (both at zero on entry).
+// done_hist, done_tie, done_collect: items of a tile that are done, of each pass (one more once thresholds or quotas are there); ticket: the counter (all at zero on entry).
 // (Sixteen wavefronts share a tile's tables, and sort.)
 constexpr int kRedoWaves = 16;
 template <int M, int QT, typename CodeT>
@@ -226,20 +228,23 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
     if (nq == 0) return;
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ unsigned long long s_item;
-    __shared__ uint32_t s_last;
+    __shared__ uint32_t s_last, s_there;
     const int tid = threadIdx.x, wave = tid >> 6;
-    const uint32_t nxb = (nunits + kRedoWaves - 1) / kRedoWaves;
-    const uint64_t per = static_cast<uint64_t>((nq + QT - 1) / QT) * nxb, all = 3 * per + nq;
+    const uint32_t tiles = static_cast<uint32_t>(nq + QT - 1) / QT, parts = (nunits + kRedoWaves - 1) / kRedoWaves;       // (parts of a tile)
+    const uint64_t per = static_cast<uint64_t>(tiles) * parts, all = 3 * per + nq;
     auto wait_for = [&](const uint32_t *count, uint32_t n) {
-        if (tid == 0)
-            while (agent_load(count) != n) __builtin_amdgcn_s_sleep(16);
+        if (tid == 0) {
+            s_there = wait_until([count] { return agent_load(count); }, [] { __builtin_amdgcn_s_sleep(16); }, n, kRedoPatience);
+            if (!s_there) atomicOr(ticket, kRedoGivenUp);
+        }
         __syncthreads();
+        return s_there != 0;
     };
     // counts the item; true for the one that ends its tile
     auto finished = [&](uint32_t *count) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) s_last = atomicAdd(count, 1u) == nxb - 1;
+        if (tid == 0) s_last = atomicAdd(count, 1u) == parts - 1;
         __syncthreads();
         return s_last != 0;
     };
@@ -252,11 +257,13 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
         __syncthreads();
         if (tid == 0) s_item = atomicAdd(ticket, 1ull);
         __syncthreads();
-        const uint64_t item = s_item;
+        const uint64_t item = s_item & ~kRedoGivenUp;
+        const bool given_up = s_item != item;
         if (item >= all) return;                                      // uniform
         if (item < 3 * per) {
+            if (given_up) continue;                                   // uniform
             const uint64_t in_pass = item % per;
-            const uint32_t tile = static_cast<uint32_t>(in_pass / nxb), u = static_cast<uint32_t>(in_pass % nxb) * kRedoWaves + wave;
+            const uint32_t tile = static_cast<uint32_t>(in_pass / parts), u = static_cast<uint32_t>(in_pass % parts) * kRedoWaves + wave;
             const int q0 = static_cast<int>(tile) * QT, nqt = min(QT, nq - q0);
             if (item < per) {
                 scan_item<M, QT, kHist, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
@@ -265,7 +272,7 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
                     ready(&done_hist[tile]);
                 }
             } else if (item < 2 * per) {
-                wait_for(&done_hist[tile], nxb + 1);
+                if (!wait_for(&done_hist[tile], parts + 1)) continue;  // uniform
                 scan_item<M, QT, kTieCount, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
                 if (finished(&done_tie[tile])) {                      // uniform
                     for (int q = wave; q < nqt; q += kRedoWaves)
@@ -273,18 +280,21 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
                     ready(&done_tie[tile]);
                 }
             } else {
-                wait_for(&done_tie[tile], nxb + 1);
+                if (!wait_for(&done_tie[tile], parts + 1)) continue;   // uniform
                 scan_item<M, QT, kCollect, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
                 finished(&done_collect[tile]);
             }
             continue;
         }
         const int p = static_cast<int>(item - 3 * per);
-        wait_for(&done_collect[p / QT], nxb);
+        const size_t out = static_cast<size_t>(w.qlist[p]) * w.r;
+        if (given_up || !wait_for(&done_collect[p / QT], parts)) {    // uniform
+            for (uint32_t t = tid; t < w.r; t += 64 * kRedoWaves) { cand_id[out + t] = t; cand_qd[out + t] = 255; }
+            continue;
+        }
         uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(p) * n_pow2;
         for (uint32_t t = tid; t < n_pow2; t += 64 * kRedoWaves) a[t] = t < w.r ? agent_load(&w.keys[static_cast<size_t>(p) * w.r + t]) : ~0ull;
         bitonic_sort(a, n_pow2);
-        const size_t out = static_cast<size_t>(w.qlist[p]) * w.r;
         for (uint32_t t = tid; t < w.r; t += 64 * kRedoWaves) {
             cand_id[out + t] = static_cast<uint32_t>(a[t]);
             cand_qd[out + t] = static_cast<uint8_t>(a[t] >> 32);
