@@ -486,7 +486,7 @@ __global__ __launch_bounds__(256) void ivf_parts_kernel(const int32_t *__restric
 }
 
 enum IvfMode { kIvfHist = 0, kIvfTieCount = 1, kIvfCollect = 2 };
-constexpr int kIvfAhead = 4;     // 64-code groups whose codes a wavefront loads together
+constexpr int ivf_ahead(int m) { return m <= 16 ? 4 : 2; }      // 64-code groups whose codes a wavefront loads together (four of m = 32 do not fit the registers)
 
 constexpr int kIvfRedoLine = 32;             // words from one count of the redo to the next
 constexpr int kIvfRedoWaves = 16;
@@ -525,12 +525,13 @@ __device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict_
         T = __hip_atomic_load(&thr[2 * q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (MODE == kIvfCollect) aux = __hip_atomic_load(&tie[static_cast<size_t>(q) * kIvfUnitsPerQuery + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // The unit is walked 64 codes at a time, in id order; the codes of kIvfAhead such groups are loaded
+    // The unit is walked 64 codes at a time, in id order; the codes of AHEAD such groups are loaded
     // together, so that one memory latency covers all of them.
-    for (uint32_t base0 = 0; base0 < un.count; base0 += 64 * kIvfAhead) {
-        uint32_t low[kIvfAhead][M];
+    constexpr int AHEAD = ivf_ahead(M);
+    for (uint32_t base0 = 0; base0 < un.count; base0 += 64 * AHEAD) {
+        uint32_t low[AHEAD][M];
 #pragma unroll
-        for (int g = 0; g < kIvfAhead; ++g) {
+        for (int g = 0; g < AHEAD; ++g) {
             const uint32_t k = base0 + g * 64 + lane;
             if (k < un.count) {
                 load_low_bytes<M>(codes, un.begin + k, low[g]);
@@ -540,7 +541,7 @@ __device__ inline void ivf_scan_unit(int q, uint32_t u, const CodeT *__restrict_
             }
         }
 #pragma unroll
-      for (int g = 0; g < kIvfAhead; ++g) {
+      for (int g = 0; g < AHEAD; ++g) {
         const uint32_t base = base0 + g * 64;
         if (base >= un.count) break;                                  // uniform
         const uint32_t k = base + lane;

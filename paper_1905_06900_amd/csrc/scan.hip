@@ -67,8 +67,7 @@ template <typename T>
 __device__ inline void agent_store(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // One item of a pass: a unit for each of the WAVES wavefronts of a workgroup (u: this wavefront's, past the last: none), for the queries at positions q0 .. q0 + QT - 1.
-// REDO: passes run in one launch, and what one of them leaves for the next goes through device-scope stores and loads.
-template <int M, int QT, int MODE, typename CodeT, int WAVES, bool REDO>
+template <int M, int QT, int MODE, typename CodeT, int WAVES>
 __device__ __forceinline__ void scan_item(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint64_t unit_stride, int q0, int nqt,
                                           uint32_t u, const ScanArrays &w, uint8_t *smem)
 {
@@ -95,9 +94,8 @@ __device__ __forceinline__ void scan_item(const CodeT *__restrict__ codes, uint6
     for (int q = 0; q < QT; ++q) {
         T[q] = 0; aux[q] = 0;
         if (MODE != kHist && q < nqt) {
-            const uint32_t *t = w.thr + 2 * (q0 + q), *e = w.tie + static_cast<size_t>(q0 + q) * nunits + u;
-            T[q] = REDO ? agent_load(t) : *t;
-            if (MODE == kCollect && u < nunits) aux[q] = REDO ? agent_load(e) : *e;
+            T[q] = w.thr[2 * (q0 + q)];
+            if (MODE == kCollect && u < nunits) aux[q] = w.tie[static_cast<size_t>(q0 + q) * nunits + u];
         }
     }
 
@@ -142,11 +140,8 @@ __device__ __forceinline__ void scan_item(const CodeT *__restrict__ codes, uint6
                     slot0 = __shfl(slot0, 0, kWave);
                     if (take) {
                         const uint32_t slot = slot0 + __popcll(take_mask & ((1ull << lane) - 1ull));
-                        if (slot < w.r) { // exactly r ids are taken over the whole scan; guard anyway
-                            uint64_t *to = w.keys + static_cast<size_t>(q0 + q) * w.r + slot;
-                            if (REDO) agent_store(to, make_key(qd, static_cast<uint32_t>(i)));
-                            else *to = make_key(qd, static_cast<uint32_t>(i));
-                        }
+                        if (slot < w.r)   // exactly r ids are taken over the whole scan; guard anyway
+                            w.keys[static_cast<size_t>(q0 + q) * w.r + slot] = make_key(qd, static_cast<uint32_t>(i));
                     }
                 }
             }
@@ -183,7 +178,7 @@ __global__ __launch_bounds__(64 * WAVES) void scan_kernel(const CodeT *__restric
         const int nqt = min(QT, nq - q0);
         // (of the sample a workgroup takes units that lie far apart: neighbouring ones may hold the same code all over, whose counts queue for one word of LDS)
         const uint32_t xb = static_cast<uint32_t>(item % nxb), u = MODE == kHist && end_of.done ? xb + wave * nxb : xb * WAVES + wave;
-        scan_item<M, QT, MODE, CodeT, WAVES, false>(codes, n_codes, unit, nunits, unit_stride, q0, nqt, u, w, smem);
+        scan_item<M, QT, MODE, CodeT, WAVES>(codes, n_codes, unit, nunits, unit_stride, q0, nqt, u, w, smem);
         if (MODE == kHist && end_of.done) {
             // Everything this workgroup has added is in place before its count is.  (Histograms are only added to by
             // device-scope atomics, whose completion is all there is to wait
@@ -208,50 +203,164 @@ __global__ __launch_bounds__(64 * WAVES) void scan_kernel(const CodeT *__restric
     }
 }
 
+// ---- the flagged queries ------------------------------------------------------------------------------
+constexpr int kRedoWaves = 16, kRedoThreads = 64 * kRedoWaves;
+constexpr int redo_qt(int m) { return m <= 8 ? 8 : 64 / m; }              // queries of a tile
+constexpr int redo_ahead(int m) { return m <= 8 ? 4 : 2; }                             // groups of 64 codes that a wavefront loads together
+constexpr int redo_per_cu(int m) { return m <= 8 ? 2 : 1; }                // workgroups that a CU has the registers for
+// In the threshold of a query, bucket | ids still needed from it << 32: it is there; the quotas of its units are there.
+constexpr uint64_t kThresholdThere = 1ull << 31, kQuotasThere = 1ull << 30, kThresholdBucket = 511;
+
+// A pass over one unit of codes by a wavefront, for a tile of nqt queries whose tables and thresholds are in LDS.  What it leaves for the next pass goes through
+// device-scope atomics and stores; it waits for nothing.
+template <int M, int QT, int MODE, typename CodeT>
+__device__ __forceinline__ void redo_unit(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits, uint32_t u, int q0, int nqt,
+                                          const ScanArrays &w, const uint8_t *ltab, uint32_t *lhist, const uint64_t *s_thr)
+{
+    constexpr int AHEAD = redo_ahead(M), W = sizeof(CodeT), WORDS = M * W / 4, PIECE = WORDS < 4 ? WORDS : 4;       // dwords of a code; of a load
+    struct __attribute__((aligned(4 * PIECE))) Piece { uint32_t v[PIECE]; };
+    const int lane = threadIdx.x & 63;
+    const uint64_t begin = static_cast<uint64_t>(u) * unit, end = min(n_codes, begin + unit);
+    uint32_t T[QT], aux[QT];                                          // threshold bucket; kTieCount: running count, kCollect: quota left
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const int p = min(q, nqt - 1);
+        T[q] = MODE == kHist ? 0u : static_cast<uint32_t>(s_thr[p] & kThresholdBucket);
+        aux[q] = MODE == kCollect ? agent_load(&w.tie[static_cast<size_t>(q0 + p) * nunits + u]) : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {                                    // (the same in all lanes)
+        T[q] = __builtin_amdgcn_readfirstlane(T[q]);
+        aux[q] = __builtin_amdgcn_readfirstlane(aux[q]);
+    }
+    for (uint64_t base0 = begin; base0 < end; base0 += 64 * AHEAD) {  // uniform
+        uint32_t raw[AHEAD][WORDS];
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g) {
+            const Piece *from = reinterpret_cast<const Piece *>(codes + min(base0 + 64 * g + lane, end - 1) * M);
+#pragma unroll
+            for (int v = 0; v < WORDS / PIECE; ++v) {
+                const Piece x = from[v];
+#pragma unroll
+                for (int z = 0; z < PIECE; ++z) raw[g][PIECE * v + z] = x.v[z];
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g) {
+            const uint64_t i = base0 + 64 * g + lane;
+            if (base0 + 64 * g >= end) break;                         // uniform
+            const bool live = i < end;
+            uint32_t low[M];
+#pragma unroll
+            for (int j = 0; j < M; ++j) low[j] = raw[g][j * W / 4] >> (j * W % 4 * 8) & 255u;
+#pragma unroll
+            for (int q = 0; q < QT; ++q) {
+                if (q >= nqt) break;                                  // uniform
+                const uint8_t *t = ltab + q * (M * 256);
+                uint32_t s = 0;
+#pragma unroll
+                for (int j = 0; j < M; ++j) s += t[j * 256 + low[j]];
+                const uint32_t qd = min(s, 255u);
+                if (MODE == kHist) {
+                    if (live) atomicAdd(&lhist[q * 256 + qd], 1u);
+                } else if (MODE == kTieCount) {
+                    aux[q] += __popcll(__ballot(live && qd == T[q]));
+                } else {
+                    const bool tied = live && qd == T[q];
+                    const uint64_t tied_mask = __ballot(tied);
+                    bool take = live && qd < T[q];
+                    if (tied_mask) {                                  // uniform
+                        take = take || (tied && static_cast<uint32_t>(__popcll(tied_mask & ((1ull << lane) - 1ull))) < aux[q]);
+                        const uint32_t n_tied = __popcll(tied_mask);
+                        aux[q] = aux[q] > n_tied ? aux[q] - n_tied : 0u;
+                    }
+                    const uint64_t take_mask = __ballot(take);
+                    if (take_mask) {                                  // uniform, rare
+                        uint32_t slot = 0;
+                        if (lane == 0) slot = atomicAdd(&w.counter[q0 + q], static_cast<uint32_t>(__popcll(take_mask)));
+                        slot = __shfl(slot, 0, kWave) + __popcll(take_mask & ((1ull << lane) - 1ull));
+                        if (take && slot < w.r) agent_store(&w.keys[static_cast<size_t>(q0 + q) * w.r + slot], make_key(qd, static_cast<uint32_t>(i)));
+                    }
+                }
+            }
+        }
+    }
+    if (MODE == kTieCount && lane == 0) {
+#pragma unroll
+        for (int q = 0; q < QT; ++q)
+            if (q < nqt) agent_store(&w.tie[static_cast<size_t>(q0 + q) * nunits + u], aux[q]);
+    }
+}
+
 // The three passes and the sort for the flagged queries qlist[0 .. *nflag), in one launch: as four of them, where nothing is flagged, which is
 // the rule, each took 4.5 us.
 // Items are handed out in order -- the histogram's of all query tiles, then the tie counts', the collection's, the queries
 // to sort -- by one counter, and an item waits for those of the pass before it: these have been handed out already, to workgroups that are running
 // and wait, if at all, for items handed out earlier still, so that every wait ends whatever number of workgroups the chip holds at a time.
 // (Should the counters not be this call's own, it is given up; redo_wait.h.  Queries that were not finished then get the first r ids.)
-// What one item leaves for another goes through device-scope atomics, stores and loads, and is in place before the item is counted as done.
-// done_hist, done_tie, done_collect: items of a tile that are done, of each pass (one more once thresholds or quotas are there); ticket: the counter (all at zero on entry).
-// (Sixteen wavefronts share a tile's tables, and sort.)
-constexpr int kRedoWaves = 16;
+// What one item leaves for another goes through device-scope atomics, stores and loads, and is in place before the item is counted as done, or the word that
+// others look at is set: the threshold of a query, which says whether it and the quotas are there.  (Those who wait look at it and not at the counts, whose
+// additions their loads would queue.)
+// done: items of a tile that are done, of all passes; ticket: the counter; thresholds and these are at zero on entry.
+// An item is a share of the units, those a share's distance apart, of which a wavefront has one at most: as many shares as there are sixteens of units, and so
+// many more, down to four units each, as fill the last round of workgroups.
+// What bounds it: for few queries the latency of the loads of a unit, 64 codes of 64 to 256 groups one after the other, so that groups are loaded four at a time (two with
+// longer codes); for many the table gathers and histogram counts in LDS.  Tiles of eight queries (four, two with longer codes) let two workgroups share a CU up
+// to m = 8; with tiles of sixteen the three passes in one kernel ran out of registers.  N = 4.2e6, m = 8, of 130 queries 1 / 16 / 130 redone: 223 / 996 / 2223 us
+// with those, a group at a time, 104 / 375 / 1550 so; m = 16, 9 of 100: 778 and 410.
 template <int M, int QT, typename CodeT>
-__global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
-                                                                 const uint32_t *__restrict__ nflag, const ScanArrays w, uint32_t *done_hist, uint32_t *done_tie,
-                                                                 uint32_t *done_collect, unsigned long long *ticket, uint32_t n_pow2, int use_lds,
-                                                                 uint64_t *__restrict__ spill, uint32_t *__restrict__ cand_id, uint8_t *__restrict__ cand_qd)
+__global__ __launch_bounds__(kRedoThreads, 4 * redo_per_cu(M)) void scan_redo_kernel(const CodeT *__restrict__ codes, uint64_t n_codes, uint32_t unit, uint32_t nunits,
+                                                              const uint32_t *__restrict__ nflag, const ScanArrays w, uint32_t *done, unsigned long long *ticket,
+                                                              uint32_t n_pow2, int use_lds, uint64_t *__restrict__ spill, uint32_t *__restrict__ cand_id,
+                                                              uint8_t *__restrict__ cand_qd)
 {
-    const int nq = static_cast<int>(*nflag);
+    const uint32_t nq = *nflag;
     if (nq == 0) return;
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ unsigned long long s_item;
+    __shared__ uint64_t s_thr[QT];
     __shared__ uint32_t s_last, s_there;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const uint32_t tiles = static_cast<uint32_t>(nq + QT - 1) / QT, parts = (nunits + kRedoWaves - 1) / kRedoWaves;       // (parts of a tile)
+    uint32_t *lhist = reinterpret_cast<uint32_t *>(smem + QT * M * 256);      // [QT][256] behind the tables
+    uint64_t *thr = reinterpret_cast<uint64_t *>(w.thr);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tiles = (nq + QT - 1) / QT, sixteens = (nunits + kRedoWaves - 1) / kRedoWaves;
+    constexpr uint32_t SLOTS = 256 * redo_per_cu(M);
+    const uint64_t rounds = (static_cast<uint64_t>(tiles) * sixteens + SLOTS - 1) / SLOTS;
+    const uint32_t parts = static_cast<uint32_t>(min(static_cast<uint64_t>((nunits + 3) / 4), rounds * SLOTS / tiles));       // ... of a tile; sixteens or more
     const uint64_t per = static_cast<uint64_t>(tiles) * parts, all = 3 * per + nq;
-    auto wait_for = [&](const uint32_t *count, uint32_t n) {
+    const auto pause = [] { __builtin_amdgcn_s_sleep(16); };
+    // thresholds of the tile's queries, once they say that `what` is there
+    auto wait_for_thresholds = [&](uint32_t q0, uint32_t nqt, uint64_t what) {
+        if (wave == 0) {
+            uint64_t t = what;
+            const bool there = wait_until([&] {
+                if (static_cast<uint32_t>(lane) < nqt) t = agent_load(&thr[q0 + lane]);
+                return static_cast<uint32_t>(__popcll(__ballot((t & what) != 0)));
+            }, pause, 64, kRedoPatience);
+            if (static_cast<uint32_t>(lane) < nqt) s_thr[lane] = t;
+            if (lane == 0) {
+                s_there = there;
+                if (!there) atomicOr(ticket, kRedoGivenUp);
+            }
+        }
+        __syncthreads();
+        return s_there != 0;
+    };
+    auto wait_for_count = [&](const uint32_t *count, uint32_t n) {
         if (tid == 0) {
-            s_there = wait_until([count] { return agent_load(count); }, [] { __builtin_amdgcn_s_sleep(16); }, n, kRedoPatience);
+            s_there = wait_until([count] { return agent_load(count); }, pause, n, kRedoPatience);
             if (!s_there) atomicOr(ticket, kRedoGivenUp);
         }
         __syncthreads();
         return s_there != 0;
     };
-    // counts the item; true for the one that ends its tile
-    auto finished = [&](uint32_t *count) {
+    // counts the item; true for the last of its pass and tile
+    auto finished = [&](uint32_t tile, uint32_t pass) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) s_last = atomicAdd(count, 1u) == parts - 1;
+        if (tid == 0) s_last = atomicAdd(&done[tile], 1u) == (pass + 1) * parts - 1;
         __syncthreads();
         return s_last != 0;
-    };
-    auto ready = [&](uint32_t *count) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) atomicAdd(count, 1u);
     };
     for (;;) {
         __syncthreads();
@@ -262,40 +371,60 @@ __global__ __launch_bounds__(64 * kRedoWaves) void scan_redo_kernel(const CodeT 
         if (item >= all) return;                                      // uniform
         if (item < 3 * per) {
             if (given_up) continue;                                   // uniform
-            const uint64_t in_pass = item % per;
-            const uint32_t tile = static_cast<uint32_t>(in_pass / parts), u = static_cast<uint32_t>(in_pass % parts) * kRedoWaves + wave;
-            const int q0 = static_cast<int>(tile) * QT, nqt = min(QT, nq - q0);
-            if (item < per) {
-                scan_item<M, QT, kHist, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
-                if (finished(&done_hist[tile])) {                     // uniform
-                    for (int q = wave; q < nqt; q += kRedoWaves) exact_threshold(w.hist + static_cast<size_t>(q0 + q) * 256, w.r, w.thr + 2 * (q0 + q));
-                    ready(&done_hist[tile]);
+            const uint32_t pass = static_cast<uint32_t>(item / per), in_pass = static_cast<uint32_t>(item % per), tile = in_pass / parts, u = in_pass % parts + wave * parts;
+            const uint32_t q0 = tile * QT, nqt = min(static_cast<uint32_t>(QT), nq - q0);
+            constexpr uint32_t ROWS = M * 256 / 16;                   // tables of a query, in sixteen bytes
+            for (uint32_t t = tid; t < nqt * ROWS; t += kRedoThreads)
+                reinterpret_cast<uint4 *>(smem)[t] = reinterpret_cast<const uint4 *>(w.qtab + static_cast<size_t>(w.qlist[q0 + t / ROWS]) * M * 256)[t % ROWS];
+            if (pass == 0) {
+                for (uint32_t t = tid; t < nqt * 256; t += kRedoThreads) lhist[t] = 0;
+            } else {
+                if (!wait_for_thresholds(q0, nqt, pass == 1 ? kThresholdThere : kQuotasThere)) continue;       // uniform
+            }
+            __syncthreads();
+            auto walk = [&](auto mode) __attribute__((always_inline)) {
+                if (u < nunits) redo_unit<M, QT, decltype(mode)::value, CodeT>(codes, n_codes, unit, nunits, u, q0, nqt, w, smem, lhist, s_thr);
+            };
+            if (pass == 0) {
+                walk(std::integral_constant<int, kHist>{});
+                __syncthreads();
+                for (uint32_t t = tid; t < nqt * 256; t += kRedoThreads)
+                    if (lhist[t]) atomicAdd(&w.hist[static_cast<size_t>(q0) * 256 + t], lhist[t]);
+                if (finished(tile, 0) && static_cast<uint32_t>(wave) < nqt) {
+                    uint64_t *to = thr + q0 + wave;
+                    exact_threshold(w.hist + static_cast<size_t>(q0 + wave) * 256, w.r,
+                                    [to](uint32_t t, uint32_t need) { agent_store(to, static_cast<uint64_t>(need) << 32 | kThresholdThere | t); });
                 }
-            } else if (item < 2 * per) {
-                if (!wait_for(&done_hist[tile], parts + 1)) continue;  // uniform
-                scan_item<M, QT, kTieCount, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
-                if (finished(&done_tie[tile])) {                      // uniform
-                    for (int q = wave; q < nqt; q += kRedoWaves)
-                        tie_quotas(w.tie + static_cast<size_t>(q0 + q) * nunits, nunits, agent_load(&w.thr[2 * (q0 + q) + 1]));
-                    ready(&done_tie[tile]);
+            } else if (pass == 1) {
+                walk(std::integral_constant<int, kTieCount>{});
+                if (finished(tile, 1) && static_cast<uint32_t>(wave) < nqt) {
+                    tie_quotas(w.tie + static_cast<size_t>(q0 + wave) * nunits, nunits, static_cast<uint32_t>(s_thr[wave] >> 32));
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    if (lane == 0) agent_store(thr + q0 + wave, s_thr[wave] | kQuotasThere);
                 }
             } else {
-                if (!wait_for(&done_tie[tile], parts + 1)) continue;   // uniform
-                scan_item<M, QT, kCollect, CodeT, kRedoWaves, true>(codes, n_codes, unit, nunits, unit, q0, nqt, u, w, smem);
-                finished(&done_collect[tile]);
+                walk(std::integral_constant<int, kCollect>{});
+                finished(tile, 2);
             }
             continue;
         }
-        const int p = static_cast<int>(item - 3 * per);
+        const uint32_t p = static_cast<uint32_t>(item - 3 * per);
         const size_t out = static_cast<size_t>(w.qlist[p]) * w.r;
-        if (given_up || !wait_for(&done_collect[p / QT], parts)) {    // uniform
-            for (uint32_t t = tid; t < w.r; t += 64 * kRedoWaves) { cand_id[out + t] = t; cand_qd[out + t] = 255; }
+        if (given_up || !wait_for_count(&done[p / QT], 3 * parts)) {  // uniform
+            for (uint32_t t = tid; t < w.r; t += kRedoThreads) { cand_id[out + t] = t; cand_qd[out + t] = 255; }
             continue;
         }
         uint64_t *a = use_lds ? reinterpret_cast<uint64_t *>(smem) : spill + static_cast<size_t>(p) * n_pow2;
-        for (uint32_t t = tid; t < n_pow2; t += 64 * kRedoWaves) a[t] = t < w.r ? agent_load(&w.keys[static_cast<size_t>(p) * w.r + t]) : ~0ull;
+        for (uint32_t t0 = tid; t0 < n_pow2; t0 += 4 * kRedoThreads) {
+            uint64_t key[4];
+#pragma unroll
+            for (int z = 0; z < 4; ++z) key[z] = t0 + z * kRedoThreads < w.r ? agent_load(&w.keys[static_cast<size_t>(p) * w.r + t0 + z * kRedoThreads]) : ~0ull;
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+                if (t0 + z * kRedoThreads < n_pow2) a[t0 + z * kRedoThreads] = key[z];
+        }
         bitonic_sort(a, n_pow2);
-        for (uint32_t t = tid; t < w.r; t += 64 * kRedoWaves) {
+        for (uint32_t t = tid; t < w.r; t += kRedoThreads) {
             cand_id[out + t] = static_cast<uint32_t>(a[t]);
             cand_qd[out + t] = static_cast<uint8_t>(a[t] >> 32);
         }
@@ -617,7 +746,8 @@ template <int M, typename CodeT>
 static int launch_redo(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab, int nq, uint32_t r, uint32_t *cand_id, uint8_t *cand_qd, uint8_t *base,
                        const ScanPlan &p, hipStream_t st)
 {
-    constexpr int QT = scan_qt(M);
+    constexpr int QT = redo_qt(M);
+    static_assert(2 * QT >= scan_qt(M), "tiles of the redo have counters in two of the rows for tiles of scan_qt(M) queries");
     const ScanArrays w = redo_arrays(qtab, reinterpret_cast<const int *>(base + p.off_qlist), r, base, p);
     const uint32_t np2 = next_pow2(r);
     const bool spill = np2 > kSortLdsKeys;
@@ -627,9 +757,9 @@ static int launch_redo(const CodeT *codes, uint64_t n_codes, const uint8_t *qtab
     if (rc) return rc;
     // as many workgroups as the chip holds at once (more would come when there is nothing left to hand out)
     const size_t qtiles = (static_cast<size_t>(nq) + p.qt - 1) / p.qt;
-    uint32_t *nflag = reinterpret_cast<uint32_t *>(base + p.off_nflag), *done = reinterpret_cast<uint32_t *>(base + p.off_done);
-    DCPQ_LAUNCH(kStageScanCollect, st, (scan_redo_kernel<M, QT, CodeT>), dim3(512), dim3(64 * kRedoWaves), lds, codes, n_codes, p.unit,
-                p.nunits, nflag, w, done + qtiles, done + 2 * qtiles, done, reinterpret_cast<unsigned long long *>(nflag + 2), np2, spill ? 0 : 1,
+    uint32_t *nflag = reinterpret_cast<uint32_t *>(base + p.off_nflag), *done = reinterpret_cast<uint32_t *>(base + p.off_done) + qtiles;
+    DCPQ_LAUNCH(kStageScanCollect, st, (scan_redo_kernel<M, QT, CodeT>), dim3(512), dim3(kRedoThreads), lds, codes, n_codes, p.unit,
+                p.nunits, nflag, w, done, reinterpret_cast<unsigned long long *>(nflag + 2), np2, spill ? 0 : 1,
                 reinterpret_cast<uint64_t *>(base + p.off_spill), cand_id, cand_qd);
     DCPQ_CHECK_LAUNCH("scan_redo_kernel");
     return DCPQ_OK;

@@ -43,7 +43,7 @@ struct ScanPlan {
     size_t off_hist;      // uint32 [nq][256]
     size_t off_thr;       // uint32 [nq][2]   (threshold bucket, ids still needed from it)
     size_t off_counter;   // uint32 [nq]
-    size_t off_done;      // uint32 [3][ceil(nq / qt)]  finished items of a query tile (sample, and again zero, redo collection; redo histogram; redo tie count)
+    size_t off_done;      // uint32 [3][ceil(nq / qt)]  finished workgroups of a query tile of the sample, and again zero; from the second row on finished items of a tile of the redo (at least half as many queries)
     size_t zero_bytes;    // everything that a call expects at zero lies together from offset 0: the four arrays
                           // above and, for the single-pass path, fcount, chist, shist and nflag
     size_t off_tie;       // uint32 [nq][nunits]
@@ -170,23 +170,27 @@ __device__ inline void wave_prefix_of_buckets(const uint32_t *hist, uint32_t (&c
     for (int z = 0; z < 4; ++z) { run += c[z]; cum[z] = run; }
 }
 
-// T = bucket holding the r-th smallest qd; need = ids still to take from bucket T (one wavefront).
-__device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, uint32_t *thr)
+// put(T, need): T = bucket holding the r-th smallest qd; need = ids still to take from bucket T (called by one lane of a wavefront).
+template <typename Put>
+__device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, Put put)
 {
     uint32_t c[4], cum[4];
     wave_prefix_of_buckets(hist, c, cum);
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int z = 0; z < 4; ++z)
-        if (cum[z] - c[z] < r && cum[z] >= r) {                  // (device-scope stores: workgroups of the same launch may read them)
-            __hip_atomic_store(&thr[0], static_cast<uint32_t>(4 * lane + z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&thr[1], r - (cum[z] - c[z]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (cum[z] - c[z] < r && cum[z] >= r) put(static_cast<uint32_t>(4 * lane + z), r - (cum[z] - c[z]));
     // fewer than r codes in all (inverted lists only): bucket "256" takes everything
-    if (lane == 63 && cum[3] < r) {
-        __hip_atomic_store(&thr[0], 256u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&thr[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (lane == 63 && cum[3] < r) put(256u, 0u);
+}
+
+// The same into thr[0 .. 1].  (Device-scope stores: workgroups of the same launch may read them.)
+__device__ inline void exact_threshold(const uint32_t *hist, uint32_t r, uint32_t *thr)
+{
+    exact_threshold(hist, r, [thr](uint32_t t, uint32_t need) {
+        __hip_atomic_store(&thr[0], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&thr[1], need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
 }
 
 // Turns per-unit counts of bucket T into per-unit quotas: units are in id order, so unit u may

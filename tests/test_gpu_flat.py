@@ -611,8 +611,81 @@ def test_scan_estimated_bound_too_low_is_redone(N, Q, pilot):
         stages = binding.profile_read()
     finally:
         binding.profile_enable(False)
-    print("redo stages (ms, launches): hist+sample %s, tie count %s, collect %s"
-          % (stages.get("scan_hist"), stages.get("scan_tiecount"), stages.get("scan_collect")), flush=True)
+    print("redo (ms, launches): %s" % (stages["scan_collect"],), flush=True)
+    assert stages["scan_collect"][1] == 2                        # (the codes and their plane)
+
+
+def misleading_sample(m, N, Q, r, few):
+    """Codes and tables of which the first `few` queries are redone: their near codes lie exactly in the runs of 256 codes that the sample reads, and no bucket
+    holds r of them, so that the single pass starts from a bound that leaves it with fewer than r.  The other tables are random."""
+    plan = binding.scan_plan(N, m, Q, r)
+    runs, stride = plan["sample_runs"], plan["sample_stride"]
+    assert plan["pilot_every"] == 1 and runs * 256 * 2 <= N
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + m + Q + few)
+    pos = (torch.arange(runs, device=DEV)[:, None] * stride + torch.arange(256, device=DEV)[None]).flatten()
+    buckets = min(200, int(runs * 256 / (0.7 * r)))              # of about 0.7 r codes or fewer
+    assert buckets >= 2
+    low = torch.randint(200, 256, (N,), generator=g, device=DEV, dtype=torch.int32)
+    low[pos] = torch.randint(0, buckets, (pos.numel(),), generator=g, device=DEV, dtype=torch.int32)
+    codes = torch.randint(-32768, 32768, (N, m), generator=g, device=DEV, dtype=torch.int16)
+    codes[:, 0] = ((codes[:, 0].int() & 0xFF00) | low).to(torch.int16)
+    qtab = torch.randint(0, 320 // m, (Q, m, 256), generator=g, device=DEV, dtype=torch.int32).to(torch.uint8)
+    qtab[:few] = 0
+    qtab[:few, 0] = torch.arange(256, device=DEV).to(torch.uint8)
+    return codes.view(torch.uint16), qtab
+
+
+@pytest.mark.parametrize("m,N,Q,few,r", [
+    (4, 1_000_003, 70, 1, 700), (4, 1_000_003, 70, 8, 700), (4, 700_001, 20, 20, 9000),           # tiles of eight queries ...
+    (8, 1_000_003, 130, 7, 700), (8, 1_000_003, 130, 9, 700), (8, 900_007, 60, 60, 700), (8, 1_000_003, 40, 17, 9000),
+    (16, 1_000_003, 50, 1, 700), (16, 1_000_003, 50, 4, 700), (16, 600_011, 21, 21, 1000), (16, 1_000_003, 20, 5, 9000),      # ... of four ...
+    (32, 1_000_003, 30, 1, 700), (32, 600_011, 15, 3, 1000), (32, 1_000_003, 12, 12, 9000),       # ... of two; r above and below what is sorted in LDS
+])
+def test_redo_of_flagged_queries(m, N, Q, few, r):
+    print("redo m=%d N=%d Q=%d flagged=%d r=%d" % (m, N, Q, few, r), flush=True)
+    codes, qtab = misleading_sample(m, N, Q, r, few)
+    want_id, want_qd = binding.scan_candidates(codes, qtab, r, mode=binding.SCAN_THREE_PASS)
+    low = (codes.view(torch.int16).long() & 255)
+    for q in (0, few - 1):                                       # the candidates are the r smallest (integer distance, id)
+        qd = sum(qtab[q, j].long()[low[:, j]] for j in range(m)).clamp(max=255)
+        key = (qd << 32 | torch.arange(N, device=DEV)).sort().values[:r]
+        assert torch.equal(want_qd[q].long() << 32 | (want_id[q].view(torch.int32).long() & 0xFFFFFFFF), key)
+    for src in (codes, binding.pack_low_bytes(codes)):
+        binding.profile_enable(True)
+        try:
+            got_id, got_qd = binding.scan_candidates(src, qtab, r)
+            torch.cuda.synchronize()
+            redo = binding.profile_read()["scan_collect"]
+        finally:
+            binding.profile_enable(False)
+        assert redo[1] == 1 and redo[0] > 0.02, "nothing was redone"        # (6 us where nothing is flagged)
+        assert torch.equal(got_id.view(torch.int32), want_id.view(torch.int32))
+        assert torch.equal(got_qd, want_qd)
+
+
+@pytest.mark.parametrize("m,few", [(4, 1), (8, 1), (8, 16), (8, 130), (16, 9)])
+def test_redo_takes_no_longer_than_the_passes_on_their_own(m, few):
+    """The redo's one launch against the three-pass scan of as many queries.  (A form of it that ran out of registers took up to 4.4 times as long.)"""
+    N, Q, r = 4_200_003, 130, 700
+    codes, qtab = misleading_sample(m, N, Q, r, few)
+    stages = ("scan_hist", "scan_tiecount", "scan_collect", "select", "misc")
+    def shortest(tables, mode, which):
+        times = []
+        for _ in range(6):
+            binding.profile_enable(True)
+            try:
+                binding.scan_candidates(codes, tables, r, mode=mode)
+                torch.cuda.synchronize()
+                p = binding.profile_read()
+                times.append(sum(p[s][0] for s in which if s in p))
+            finally:
+                binding.profile_enable(False)
+        return min(times)
+    redo = shortest(qtab, binding.SCAN_AUTO, ("scan_collect",))
+    passes = shortest(qtab[:few].contiguous(), binding.SCAN_THREE_PASS, stages)
+    print("m=%d flagged=%d: redo %.3f ms, three passes %.3f" % (m, few, redo, passes), flush=True)
+    assert redo < 1.4 * passes                                   # (the flagged queries' tiles may be one more, and their units longer)
 
 
 @pytest.mark.parametrize("Q", [100, 251])

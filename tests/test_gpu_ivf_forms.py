@@ -26,8 +26,11 @@ def _case(kind, m, dsub, n, nq, nlist, seed):
     ("random", 4, 6, 50_021, 37, 64, 33, 777, 100),        # codes of 8 bytes; more lists than a wavefront's half
     ("random", 16, 3, 30_011, 300, 32, 5, 129, 129),       # rows that are no whole 16 bytes
     ("random", 8, 16, 3_001, 70, 64, 3, 2000, 60),         # fewer codes than r in the lists: every query is done again, and padded
-    ("ties", 8, 4, 400_009, 45, 16, 7, 600, 50),           # more queries than rows of the redo, quotas for ties
+    ("ties", 8, 4, 400_009, 45, 16, 7, 600, 50),           # quotas for ties
     ("random", 8, 8, 300_007, 5, 32, 8, 20_000, 100),      # keys beyond what is sorted in LDS
+    ("random", 32, 2, 20_011, 70, 64, 3, 2000, 60),        # every query done again: long codes, ...
+    ("random", 16, 2, 20_011, 600, 64, 3, 2000, 60),       # ... more of them than a pass has items, ...
+    ("random", 4, 4, 30_011, 3, 64, 3, 9000, 60),          # ... keys beyond what is sorted in LDS
 ])
 def test_search_equals_its_steps(kind, m, dsub, n, nq, nlist, nprobe, r, k):
     cb, coarse, codes, offsets, queries = _case(kind, m, dsub, n, nq, nlist, 77 + m)
