@@ -42,11 +42,12 @@ struct IvfUnit {
 
 // ------------------------------------------------------------------------------------------------
 // Index step: nprobe smallest coarse distances per query, ordered by (distance, list id).
-// dist: [nq][nlist] fp32 squared distances.  One workgroup per query.
+// dist: [nq][nlist] fp32 squared distances.  One workgroup per query; redo: only for those that have a negative number in the place of their first list.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void ivf_select_probe_kernel(const float *__restrict__ dist, int nlist, int nprobe,
-                                                               int32_t *__restrict__ probe)
+                                                               int32_t *__restrict__ probe, int redo)
 {
+    if (redo && probe[static_cast<size_t>(blockIdx.x) * nprobe] >= 0) return;      // uniform
     select_probe_of_row(dist + static_cast<size_t>(blockIdx.x) * nlist, nlist, nprobe, probe + static_cast<size_t>(blockIdx.x) * nprobe);
 }
 
@@ -1345,11 +1346,13 @@ extern "C" int dcpq_ivf_probe(const float *queries, int nq, int D, const float *
     const size_t need = dcpq_ivf_probe_workspace_bytes(nq, nlist);
     if (workspace_bytes < need) return fail(DCPQ_EWORKSPACE, "ivf_probe: workspace %zu < %zu bytes", workspace_bytes, need);
     hipStream_t st = as_stream(stream);
-    if (probe_filter_serves(queries, nq, D, coarse, nlist, nprobe)) return launch_probe_filter(queries, nq, D, coarse, nlist, nprobe, workspace, probe, st);
     float *dist = static_cast<float *>(workspace);
-    int rc = launch_distance_tables(queries, nq, coarse, 1, D, nlist, dist, kStageIvfProbe, st);
+    const bool filter = probe_filter_serves(queries, nq, D, coarse, nlist, nprobe);
+    // (the filter's: of the queries that it has left)
+    const int rc = filter ? launch_probe_filter(queries, nq, D, coarse, nlist, nprobe, workspace, probe, st)
+                          : launch_distance_tables(queries, nq, coarse, 1, D, nlist, dist, kStageIvfProbe, st);
     if (rc) return rc;
-    DCPQ_LAUNCH(kStageIvfProbe, st, ivf_select_probe_kernel, dim3(nq), dim3(1024), 0, dist, nlist, nprobe, probe);
+    DCPQ_LAUNCH(kStageIvfProbe, st, ivf_select_probe_kernel, dim3(nq), dim3(1024), 0, dist, nlist, nprobe, probe, filter ? 1 : 0);
     DCPQ_CHECK_LAUNCH("ivf_select_probe_kernel");
     return DCPQ_OK;
 }

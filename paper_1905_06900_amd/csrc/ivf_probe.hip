@@ -7,11 +7,12 @@
 // that walks them three times: 1024 queries, 65536 centres of 128 components 312 + 115 us).
 //
 // The estimate.  Queries and centres are taken relative to a reference vector (the mean of 32 centres), multiplied by a power of two that
-// brings the largest component of those centres to 2^4, or of the 256 queries of a workgroup below 2^14, whichever is less, and rounded to fp16.
+// brings the largest component of those centres to 2^4, and rounded to fp16.  (Queries do not have a say in it: one that is thousands of times farther out has no estimates, whatever the
+// scale, since these end at 65504, and would take those of its neighbours.)
 // What the product loses is bounded by the lengths at hand: the remainder of the query is known, that of a centre is at most 2^-11 of its length
 // (components below 2^-14 may be lost whole).  A centre of length c is at least |c - x| away, so that the centres that matter are not longer than a bound that follows from
-// the estimate itself.  Where the bound leaves more centres than there is room for, or values are not finite, a workgroup works out
-// all of a query's distances in double precision (0.4 ms for 65536 centres).
+// the estimate itself.  Where the bound leaves more centres than there is room for, or values are not finite, a query is left to two more launches, which as a rule
+// find nothing to do (5 to 10 us): probe_left_kernel works out all its distances, and they are selected from as in the other form.
 #include "common.h"
 #include "device_util.h"
 #include "ivf_select.h"
@@ -49,12 +50,12 @@ __global__ __launch_bounds__(256, 2) void probe_filter_kernel(const float *__res
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ __align__(16) float mu[C::DP], mus[C::DP];
     __shared__ float xnorm2[C::QPW], xrest2[C::QPW];
-    __shared__ uint32_t s_cabs, s_xmax;
+    __shared__ uint32_t s_cabs;
     float *gmin = reinterpret_cast<float *>(smem + 2 * C::BUF_BYTES);        // [QPW][kProbeMostTiles + 1]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5, srow = tid >> 2, spart = tid & 3;
     const int q0 = blockIdx.y * C::QPW;
-    if (tid == 0) s_cabs = s_xmax = 0;
+    if (tid == 0) s_cabs = 0;
     for (int t = tid; t < 2 * C::BUF_BYTES / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     if (tid < C::DP) {
@@ -73,21 +74,8 @@ __global__ __launch_bounds__(256, 2) void probe_filter_kernel(const float *__res
         if (far < INFINITY) atomicMax(&s_cabs, __float_as_uint(far));
     }
     __syncthreads();
-    {
-        float most = 0.0f;
-        for (int qq = srow; qq < C::QPW && q0 + qq < nq; qq += 64)
-            for (int o = 4 * spart; o < D; o += 16) {
-                const float4 x = *reinterpret_cast<const float4 *>(queries + static_cast<size_t>(q0 + qq) * D + o), m = *reinterpret_cast<const float4 *>(mu + o);
-                const float v = fmaxf(fmaxf(fabsf(x.x - m.x), fabsf(x.y - m.y)), fmaxf(fabsf(x.z - m.z), fabsf(x.w - m.w)));
-                most = v < INFINITY ? fmaxf(most, v) : most;
-            }
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) most = fmaxf(most, __shfl_xor(most, off));
-        if (lane == 0) atomicMax(&s_xmax, __float_as_uint(most));
-    }
-    __syncthreads();
-    const int ec = static_cast<int>(s_cabs >> 23) - 126, ex = static_cast<int>(s_xmax >> 23) - 126;       // (x < 2^(exponent - 126))
-    const float scale = __uint_as_float(static_cast<uint32_t>(min(max(min(4 - ec, 14 - ex), -120), 120) + 127) << 23);
+    const int ec = static_cast<int>(s_cabs >> 23) - 126;                // (x < 2^(exponent - 126))
+    const float scale = __uint_as_float(static_cast<uint32_t>(min(max(4 - ec, -120), 120) + 127) << 23);
     if (tid < C::DP) mus[tid] = -mu[tid] * scale;
     __syncthreads();
 
@@ -125,14 +113,19 @@ __global__ __launch_bounds__(256, 2) void probe_filter_kernel(const float *__res
             }
         __syncthreads();
     }
+    // (a workgroup whose queries are all so far out that no estimate is below 60000, unless a centre is as well, leaves them at once)
+    bool near = false;
+    for (int qq = tid; qq < C::QPW && q0 + qq < nq; qq += 256) near = near || xnorm2[qq] < 250000.0f;
+    const bool any = __syncthreads_or(near);
 #pragma unroll
     for (int p = 0; p < P; ++p) xn2[p] = xnorm2[(wave * P + p) * 32 + col];
     if (blockIdx.x == 0)
         for (int qq = tid; qq < C::QPW && q0 + qq < nq; qq += 256) {
             float *info = reinterpret_cast<float *>(out + static_cast<size_t>(q0 + qq) * nlist * 4 + probe_info_offset(nlist));
-            info[0] = sqrtf(xnorm2[qq]) * 1.001f;
+            info[0] = any ? sqrtf(xnorm2[qq]) * 1.001f : INFINITY;
             info[1] = sqrtf(xrest2[qq]) * 1.001f;
         }
+    if (!any) return;                                                 // uniform
 
     const int ntiles = (nlist + kProbeGroup - 1) / kProbeGroup, tile0 = blockIdx.x * tiles_per_block, tiles = min(tiles_per_block, ntiles - tile0);
     if (tiles <= 0) return;                                           // uniform
@@ -237,6 +230,10 @@ __global__ __launch_bounds__(1024) void probe_pick_kernel(const float *__restric
     const float *gm = reinterpret_cast<const float *>(row + probe_min_offset(nlist));
     const float xn = reinterpret_cast<const float *>(row + probe_info_offset(nlist))[0], xr0 = reinterpret_cast<const float *>(row + probe_info_offset(nlist))[1];
 
+    if (!(xn < INFINITY)) {                                           // uniform: no estimates
+        if (tid == 0) probe[static_cast<size_t>(q) * nprobe] = -1;
+        return;
+    }
     // an upper bound v of the nprobe-th smallest of the groups' smallest estimates: the largest in the step of equal width that has it
     uint32_t lo = 0xFFFFFFFFu, hi = 0;
     for (int t = tid; t < ngroups; t += 1024) {
@@ -326,15 +323,8 @@ __global__ __launch_bounds__(1024) void probe_pick_kernel(const float *__restric
         s += __shfl_xor(s, 1); s += __shfl_xor(s, 2); s += __shfl_xor(s, 4); s += __shfl_xor(s, 8);
         return s;
     };
-    if (!done) {                                                      // uniform: the distances of all centres, and the selection of the other form
-        float *dist = reinterpret_cast<float *>(row);
-        __syncthreads();                                              // the estimates are no longer read
-        for (int l = tid >> 4; l < (nlist + 63) / 64 * 64; l += 64) {
-            const double d = distance(l < nlist ? l : nlist - 1);
-            if ((tid & 15) == 0 && l < nlist) dist[l] = static_cast<float>(d);
-        }
-        __syncthreads();
-        select_probe_of_row(dist, nlist, nprobe, probe + static_cast<size_t>(q) * nprobe);
+    if (!done) {                                                      // uniform
+        if (tid == 0) probe[static_cast<size_t>(q) * nprobe] = -1;    // left
         return;
     }
     const uint32_t n = s_ncand;
@@ -364,11 +354,75 @@ __global__ __launch_bounds__(1024) void probe_pick_kernel(const float *__restric
     for (int t = tid; t < nprobe; t += 1024) probe[static_cast<size_t>(q) * nprobe + t] = static_cast<int32_t>(sel[t] & 0xFFFFFFFFu);
 }
 
+// The distances of the queries that are left (a negative number in the place of their first list), by difference in double precision, into their part of the
+// workspace.  A workgroup takes kLeftCents centres, two a thread, sixteen components at a time through LDS, and those of 64 queries that are left, kLeftTogether
+// at a time, from scalar registers.  Bound by the two double-precision instructions per component and pair and the conversions (2.6 of them in all).  1024 queries, 65536 centres of 128
+// components, the whole call: one query left 0.17 ms, a tenth 0.27, all 1.08 (0.11 where none is; 1.01, 1.25 and 2.5 with a workgroup a query, each reading all centres).
+constexpr int kLeftTogether = 8, kLeftCents = 512, kLeftStride = 20;
+__global__ __launch_bounds__(256) void probe_left_kernel(const float *__restrict__ queries, int nq, int D, const float *__restrict__ coarse, int nlist, int nprobe,
+                                                        const int32_t *__restrict__ probe, float *__restrict__ dist)
+{
+    __shared__ __align__(16) float cents[kLeftCents * kLeftStride];
+    __shared__ int left[64];
+    __shared__ uint32_t s_n;
+    const int tid = threadIdx.x;
+    const int q0 = blockIdx.y * 64, c0 = blockIdx.x * kLeftCents;
+    if (tid < 64) {
+        const bool is = q0 + tid < nq && probe[static_cast<size_t>(q0 + tid) * nprobe] < 0;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(is);
+        if (is) left[__popcll(mask & ((1ull << tid) - 1ull))] = q0 + tid;
+        if (tid == 0) s_n = __popcll(mask);
+    }
+    __syncthreads();
+    const int n = static_cast<int>(s_n);
+    if (n == 0) return;                                               // uniform
+    for (int g = 0; g < n; g += kLeftTogether) {                      // uniform
+        const float *x[kLeftTogether];                                // (in scalar registers)
+#pragma unroll
+        for (int i = 0; i < kLeftTogether; ++i) x[i] = queries + static_cast<size_t>(__builtin_amdgcn_readfirstlane(left[g + i < n ? g + i : n - 1])) * D;
+        double sum[kLeftTogether][2];
+#pragma unroll
+        for (int i = 0; i < kLeftTogether; ++i) sum[i][0] = sum[i][1] = 0.0;
+        for (int o = 0; o < D; o += 16) {                             // uniform
+            __syncthreads();
+            for (int t = tid; t < kLeftCents * 4; t += 256) {
+                const int c = c0 + t / 4;
+                *reinterpret_cast<float4 *>(cents + t / 4 * kLeftStride + t % 4 * 4) =
+                    *reinterpret_cast<const float4 *>(coarse + static_cast<size_t>(c < nlist ? c : nlist - 1) * D + o + t % 4 * 4);
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int e = 0; e < 16; e += 4) {
+                const float4 a = *reinterpret_cast<const float4 *>(cents + tid * kLeftStride + e), b = *reinterpret_cast<const float4 *>(cents + (tid + 256) * kLeftStride + e);
+                const double ca[4] = {a.x, a.y, a.z, a.w}, cb[4] = {b.x, b.y, b.z, b.w};
+                float xv[kLeftTogether][4];
+#pragma unroll
+                for (int i = 0; i < kLeftTogether; ++i)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) xv[i][z] = x[i][o + e + z];
+#pragma unroll
+                for (int i = 0; i < kLeftTogether; ++i)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const double v = xv[i][z], da = v - ca[z], db = v - cb[z];
+                        sum[i][0] = fma(da, da, sum[i][0]);
+                        sum[i][1] = fma(db, db, sum[i][1]);
+                    }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kLeftTogether; ++i)
+#pragma unroll
+            for (int z = 0; z < 2; ++z)
+                if (g + i < n && c0 + tid + 256 * z < nlist) dist[static_cast<size_t>(left[g + i]) * nlist + c0 + tid + 256 * z] = static_cast<float>(sum[i][z]);
+    }
+}
+
 // Rows of whole 64-byte pieces up to 256 components, read 16 bytes at a time (a query's part of the workspace too: lists in fours); a cut that
 // leaves few groups of 32 (eight times the probed lists are groups); and pairs enough that the estimate pays.  Against the distances of all
 // centres in double precision, D = 128: 4096 lists x 1024 queries 0.97 of the time, 16384 x 256 0.91, 65536 x 64 0.82, x 256 0.46, x 1024
-// 0.28 (427 -> 119 us); below 2^22 pairs the two launches' latency is all there is.  With all centres equal every distance
-// is worked out one workgroup a query: 65536 x 1024 1.7 -> 4.2 ms.
+// 0.28 (427 -> 119 us); below 2^22 pairs the launches' latency is all there is (4096 lists x 1024 queries of 96 components 43 and 45 us).  Batches that are left whole are slower than without
+// estimates: 65536 x 1024, all queries far out 0.43 and 1.08 ms; all centres equal, where the selection takes most of it, 1.70 and 1.69.
 bool probe_filter_serves(const float *queries, int nq, int D, const float *coarse, int nlist, int nprobe)
 {
     return D % 16 == 0 && D <= 256 && nlist >= 4096 && nlist % 4 == 0 && nlist <= kProbeGroup * 65536 && nprobe * 8 <= nlist / kProbeGroup &&
@@ -391,6 +445,7 @@ static int launch_filter(const float *queries, int nq, int D, const float *coars
     return DCPQ_OK;
 }
 
+// (leaves queries that have a negative number in the place of their first list, and the distances of all centres in their part of the workspace)
 int launch_probe_filter(const float *queries, int nq, int D, const float *coarse, int nlist, int nprobe, void *ws, int32_t *probe, hipStream_t st)
 {
     uint8_t *est = static_cast<uint8_t *>(ws);
@@ -406,6 +461,9 @@ int launch_probe_filter(const float *queries, int nq, int D, const float *coarse
     if (rc) return rc;
     DCPQ_LAUNCH(kStageIvfProbe, st, probe_pick_kernel, dim3(nq), dim3(1024), 0, queries, D, coarse, nlist, nprobe, used, est, probe);
     DCPQ_CHECK_LAUNCH("probe_pick_kernel");
+    DCPQ_LAUNCH(kStageIvfProbe, st, probe_left_kernel, dim3((nlist + kLeftCents - 1) / kLeftCents, (nq + 63) / 64), dim3(256), 0, queries, nq, D, coarse, nlist, nprobe,
+                probe, static_cast<float *>(ws));
+    DCPQ_CHECK_LAUNCH("probe_left_kernel");
     return DCPQ_OK;
 }
 

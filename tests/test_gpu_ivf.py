@@ -193,13 +193,14 @@ def test_low_byte_plane_every_m(m):
     np.testing.assert_array_equal(to_np(plane), (to_np(codes) & 255).astype(np.uint8))
 
 
-@pytest.mark.parametrize("D,nlist,nq,nprobe", [(128, 4100, 1100, 16), (64, 8192, 600, 30), (96, 65536, 70, 64), (16, 40004, 130, 7), (192, 4096, 1025, 16), (256, 4128, 1030, 3)])
-@pytest.mark.parametrize("data", ["clustered", "equal", "offset", "few places", "not finite"])
+@pytest.mark.parametrize("D,nlist,nq,nprobe", [(128, 4100, 1100, 16), (64, 8192, 600, 30), (96, 65536, 70, 64), (16, 40004, 130, 7), (192, 4096, 1025, 16), (256, 4128, 1030, 3),
+                                                  (64, 65536, 70, 256), (64, 131072, 40, 512)])       # (an eighth of the groups; more candidates than are ranked by counting)
+@pytest.mark.parametrize("data", ["clustered", "equal", "all equal", "offset", "few places", "far queries", "not finite"])
 def test_probe_of_many_queries_from_estimates(D, nlist, nq, nprobe, data):
     # From 2^22 (query, centre) pairs on the distances are estimated first.  The centres that a query probes, in order, are those of the distances
     # in double precision, rounded to fp32, equal ones by number.  "equal": every centre sixteen times; "offset": differences far smaller than the
-    # components; "few places": more centres within the error of the estimate than there is room for; "not finite": centres and a
-    # query that are not, or far out of the range of fp16.
+    # components; "few places", "all equal": more centres within the error of the estimate than there is room for; "far queries": some, and all of the
+    # first 256, out of the range of the estimates; "not finite": centres and a query that are not, or far out of the range of fp16.
     g = torch.Generator(device=DEV)
     g.manual_seed(D + nlist)
     means = 40.0 * torch.randn((64, D), generator=g, device=DEV)
@@ -208,6 +209,11 @@ def test_probe_of_many_queries_from_estimates(D, nlist, nq, nprobe, data):
     coarse, y = draw(nlist, 5.0), draw(nq, 5.0)
     if data == "equal":
         coarse = coarse[torch.arange(nlist, device=DEV) % (nlist // 16)].contiguous()
+    elif data == "all equal":
+        coarse = coarse[:1].repeat(nlist, 1)
+    elif data == "far queries":
+        y[:256] *= 1e4
+        y[300::50] *= 1e6
     elif data == "offset":
         coarse, y = 5000.0 + 1e-2 * coarse, 5000.0 + 1e-2 * y
     elif data == "few places":
@@ -235,3 +241,30 @@ def test_probe_of_many_queries_from_estimates(D, nlist, nq, nprobe, data):
         np.testing.assert_allclose(to_np(d.gather(1, got)[fine]), to_np(d.gather(1, want)[fine]), rtol=2.0 ** -23)
         if data in ("clustered", "equal"):
             assert (got != want).sum() <= 2
+        elif data == "all equal":
+            assert torch.equal(got, want)
+
+
+def test_probe_of_queries_that_have_no_estimates_is_not_much_slower():
+    # A query far out leaves its neighbours their estimates (it took them from 255 of them: 9 times as long as without it); queries without estimates
+    # share their reads of the centres (one workgroup each: 35 times as long with all centres equal).
+    nq, nlist, D, nprobe = 1024, 65536, 128, 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+    coarse, y = torch.randn((nlist, D), generator=g, device=DEV), torch.randn((nq, D), generator=g, device=DEV)
+    out = y.clone()
+    out[5] *= 1e6
+    ms = []
+    for queries, centres in ((y, coarse), (out, coarse), (y, coarse[:1].repeat(nlist, 1))):
+        times = []
+        for _ in range(6):
+            binding.profile_enable(True)
+            try:
+                binding.ivf_probe(queries, centres, nprobe)
+                torch.cuda.synchronize()
+                times.append(binding.profile_read()["ivf_probe"][0])
+            finally:
+                binding.profile_enable(False)
+        ms.append(min(times))
+    print("probe, ms: %.3f, one query far out %.3f, centres equal %.3f" % tuple(ms), flush=True)
+    assert ms[1] < 2.5 * ms[0] and ms[2] < 16 * ms[0]
