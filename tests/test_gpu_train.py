@@ -445,3 +445,52 @@ def test_training_repeats_no_rounds_of_a_balanced_assignment():
         finally:
             binding.profile_enable(False)
     assert counts[0] <= counts[1] + m * iters * (2 + 2 * 4)
+
+
+def check_many_points_against_few(pts, cb, times, tag):
+    """Labels and distances of `pts` are those that the same points have `times` over, where their number takes another kernel; and the nearest
+    in double precision."""
+    n, m, dsub = pts.shape[0], cb.shape[0], cb.shape[2]
+    few, few_dist = binding.assign(pts, cb, want_dist=True)
+    many, many_dist = binding.assign(pts.repeat(times, 1), cb, want_dist=True)
+    many2 = binding.assign(pts.repeat(times, 1), cb)
+    assert torch.equal(many, few.repeat(times, 1)) and torch.equal(many2, many), tag
+    np.testing.assert_array_equal(to_np(many_dist), to_np(few_dist.repeat(times, 1)), err_msg=tag)
+    for j in range(m):
+        x, c = pts[:, j * dsub:(j + 1) * dsub].double(), cb[j].double()
+        for i in range(0, n, 64):
+            d2 = torch.zeros((x[i:i + 64].shape[0], c.shape[0]), dtype=torch.float64, device=DEV)
+            for t in range(dsub):
+                d2 += (x[i:i + 64, t:t + 1] - c[None, :, t]) ** 2
+            d2 = torch.where(d2.isnan(), float("inf"), d2)
+            chosen = d2.gather(1, few[i:i + 64, j:j + 1].long())[:, 0]
+            assert bool((chosen <= d2.min(1).values * (1 + 4 * (dsub + 1) * 2.0 ** -53)).all()), "%s, sub-quantizer %d" % (tag, j)
+
+
+@pytest.mark.parametrize("ncent", [65535, 65536, 65537])
+@pytest.mark.parametrize("dsub,m", [(8, 4), (12, 4), (16, 4), (20, 4), (23, 4), (32, 4), (40, 4), (64, 4)])
+@pytest.mark.parametrize("data", ["normal", "bytes", "near"])
+def test_assign_of_many_points_to_the_largest_codebooks(dsub, m, ncent, data):
+    # 65536 centroids are as many cells as their numbers have room for in the filter with one fp16 product; one more takes the split products, in the
+    # large tiles of points up to 32 components.  Nearest centroids in the first and last cells, and ("near") windows that hold
+    # centroids of many cells up to the last (the second walk); "bytes": whole numbers, whose second bf16 parts are zero, and equal distances.
+    print("assign to %d centroids dsub=%d m=%d %s" % (ncent, dsub, m, data), flush=True)
+    g = gen(dsub + ncent)
+    n = 517
+    pts = torch.randn((n, m * dsub), generator=g, device=DEV)
+    cb = torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    if data == "bytes":
+        pts = (40 * pts + 120).clamp(0, 255).round()
+        cb = (40 * cb + 120).clamp(0, 255).round()
+        cb[:, -9:] = cb[:, :9]
+    per_point = pts.view(n, m, dsub)
+    places = torch.tensor([0, 31, 127, 128, 32767, 32768, 65407, 65408, 65500, ncent - 65, ncent - 2, ncent - 1], device=DEV)
+    step = 0.0 if data == "bytes" else 1e-2
+    near = cb[:, places].transpose(0, 1).repeat(20, 1, 1)
+    per_point[:near.shape[0]] = near + step * torch.randn(near.shape, generator=g, device=DEV)
+    if data == "near":                                           # 50 centroids all over the codebook, the last among them, within 1e-4 of one of them
+        at = torch.cat([torch.arange(7, ncent - 1, 1337, device=DEV), torch.tensor([ncent - 1], device=DEV)])
+        cb[:, at] = 3.0 + cb[:, 7:8] + 1e-4 * torch.randn((m, at.numel(), dsub), generator=g, device=DEV)
+        per_point[::61] = cb[:, ncent - 1][None] + 1e-4 * torch.randn((len(range(0, n, 61)), m, dsub), generator=g, device=DEV)
+    # (tiles of 512 points; of 1024 with up to 16 components where the data is "normal")
+    check_many_points_against_few(pts, cb, (1 << 19) // (m * n) if dsub <= 16 and data == "normal" else (1 << 18) // (m * n) + 1, "%d centroids" % ncent)
