@@ -494,3 +494,57 @@ def test_assign_of_many_points_to_the_largest_codebooks(dsub, m, ncent, data):
         per_point[::61] = cb[:, ncent - 1][None] + 1e-4 * torch.randn((len(range(0, n, 61)), m, dsub), generator=g, device=DEV)
     # (tiles of 512 points; of 1024 with up to 16 components where the data is "normal")
     check_many_points_against_few(pts, cb, (1 << 19) // (m * n) if dsub <= 16 and data == "normal" else (1 << 18) // (m * n) + 1, "%d centroids" % ncent)
+
+
+@pytest.mark.parametrize("dsub,m", [(7, 8), (8, 8), (16, 8), (30, 8), (64, 8)])
+@pytest.mark.parametrize("which", ["point", "points", "all points", "centroid", "centroids", "both", "not finite"])
+def test_assign_of_many_points_where_some_lie_far_out(dsub, m, which):
+    # The scale of the fp16 filter follows 64 centroids.  What it makes infinite: points (one or two of a workgroup, more, all), and centroids, which are ruled out by
+    # their length, but not for points as far out.
+    print("assign far out dsub=%d m=%d %s" % (dsub, m, which), flush=True)
+    g = gen(dsub + 7)
+    n, ncent = 2003, 1500
+    pts = torch.randn((n, m * dsub), generator=g, device=DEV)
+    cb = torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    if which in ("point", "both"):
+        pts[1001] *= 1e6
+        pts[77] *= 3e3
+    elif which == "points":
+        pts[100::50] *= 10.0 ** torch.linspace(2, 12, len(range(100, n, 50)), device=DEV)[:, None]
+    elif which == "all points":
+        pts *= 1e6
+    if which in ("centroid", "both"):
+        cb[:, 1497] *= 1e5
+    if which in ("centroids", "both"):
+        cb[:, 5::100] *= 1e4
+        cb[0, 1400:] = 1e7
+        pts[5::64] = cb[:, 1305].reshape(1, m * dsub) + 1e3       # (nearest to a centroid far out)
+        pts[6::64] = cb[:, 1305].reshape(1, m * dsub) / 2          # (about as far from it as from the others)
+    if which == "not finite":
+        cb[:, 9], cb[:, 11] = float("nan"), float("inf")
+        cb[:, 1499] = -float("inf")
+    check_many_points_against_few(pts, cb, (1 << 18) // (m * n) + 1, which)
+
+
+def test_assign_beside_centroids_and_points_far_out_takes_as_long():
+    # A centroid far out left the filter without windows: 35 times as long (the split products cannot tell centroids apart beside it either).
+    n, m, dsub, ncent = 65536, 8, 16, 16384
+    g = gen(3)
+    pts, cb = torch.randn((n, m * dsub), generator=g, device=DEV), torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    far_points, far_centroid = pts.clone(), cb.clone()
+    far_points[::2000] *= 1e9
+    far_centroid[:, 77] *= 1e6
+    ms = []
+    for x, c in ((pts, cb), (far_points, cb), (pts, far_centroid)):
+        times = []
+        for _ in range(6):
+            binding.profile_enable(True)
+            try:
+                binding.assign(x, c)
+                torch.cuda.synchronize()
+                times.append(binding.profile_read()["train"][0])
+            finally:
+                binding.profile_enable(False)
+        ms.append(min(times))
+    print("assign, ms: %.3f, points far out %.3f, a centroid %.3f" % tuple(ms), flush=True)
+    assert ms[1] < 2 * ms[0] and ms[2] < 2 * ms[0]
