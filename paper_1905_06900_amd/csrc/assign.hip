@@ -713,9 +713,9 @@ __global__ __launch_bounds__(256, KS <= 3 && P == 2 ? 3 : KS <= 16 ? 2 : 1) void
 // The same result, with ONE fp16 product in the filter where the form above takes three or four bf16 ones: fp16 keeps 11 significant
 // bits, and the window that this leaves around the smallest filter value holds 1.05 to 1.25 centroids on average (65536 centroids of 12 to
 // 60 components, encoded data as well as Gaussian).  It is proven as above: from |x|, |c| and the lengths of the remainders x - xh and c - ch
-// themselves.  Points with four or more cells of one half of a tile in their window, 1 in 1000 or fewer, are walked again, 32 at a time, the
+// themselves.  Points with four or more cells of one half of a tile in their window, as a rule 1 in 1000 or fewer, are walked again, 32 or 128 at a time, the
 // wavefronts sharing the centroids, and now that the window is known every centroid in it is listed and compared in double precision.  Where
-// the windows hold too many for that (centroids closer together than 2^-11 of their distance from the reference vector), the points
+// the windows hold too many for that (more than 32 to 128 centroids closer together than 2^-11 of their distance from the reference vector), the points
 // left go through the split products.
 //
 // Scale: points and centroids are multiplied by a power of two that brings the largest component of 64 centroids to 2^4; it follows no other number, so that
@@ -747,9 +747,10 @@ struct HalfCfg {
     static constexpr int KEEP = 4, SLOTS = NE * KEEP;
     static constexpr uint32_t ITEMS = 2 * PTS;                      // cells that are looked at for all points together, at most
     static constexpr int ENT_BYTES = 2 * ITEMS * 2 + PTS * SLOTS * 4 + PTS * 5;
-    // the second walk: centroids listed for 32 points
-    static constexpr uint32_t FOUND = 2048;
-    static constexpr int FOUND_BYTES = STAGE_BYTES + FOUND * 8 + 32 * 12;
+    // the second walk: centroids listed for 32 points,
+    static constexpr int TILES2 = 4;                                // ... or for so many times 32
+    static constexpr uint32_t FOUND = 4096;
+    static constexpr int FOUND_BYTES = STAGE_BYTES + FOUND * 4 + 32 * TILES2 * 12;
     // the rest: up to 32 points whose centroids are split between the wavefronts, or each wavefront with points of its own
     static constexpr bool SPLIT = KS <= 6;
     static constexpr int MANY_P = KS <= 12 ? 2 : 1;
@@ -1210,146 +1211,161 @@ __global__ __launch_bounds__(256, 2) void assign_half_kernel(const float *__rest
     if (n_open + n_no_window == 0) return;                            // uniform
 
     // ---- the second walk --------------------------------------------------------------------------------------
-    // 32 points at a time, up to a sixteenth of the workgroup's.  (More than that are open because their windows are crowded: an eighth of points
-    // and centroids zeros, 70000 x 8 x 16, 16384 centroids, 3.6 ms where this walk was tried first.)
+    // 32 points at a time, or 128 where more are open (all of them with 4096 clusters of 16 centroids, 250007 x 8 x 16: 17.3 ms; with split products for more than a
+    // sixteenth of a workgroup's points 30.2, for all without this filter 19.0; 140000 x 4 x 32 9.8, 12.1 and 8.0).  A walk that finds more than there is room for ends at once.
     uint32_t done = 0;
-    if (n_open <= C::PTS / 16) {                                       // uniform
-        __syncthreads();                                              // the minima are no longer read
-        uint64_t *found = reinterpret_cast<uint64_t *>(smem + C::STAGE_BYTES);                    // (point << 32) | centroid
+    auto walk_again = [&](auto tiles) __attribute__((always_inline)) {
+        constexpr int W = decltype(tiles)::value, MOST = 32 * W;
+        uint32_t *found = reinterpret_cast<uint32_t *>(smem + C::STAGE_BYTES);                    // (point << 16) | centroid
         unsigned long long *nearest = reinterpret_cast<unsigned long long *>(found + C::FOUND);       // of every point: distance, then ...
-        uint32_t *which = reinterpret_cast<uint32_t *>(nearest + 32);                             // ... centroid
-        for (; done < n_open; done = min(done + 32, n_open)) {        // uniform
-            const uint32_t mine = min(32u, n_open - done);
-            __syncthreads();                                          // (nor what the last 32 points left)
-            for (int t = tid; t < 32 * C::STRIDE / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);        // rows: zero past dp
-            __syncthreads();
-            if (srow < 32) {
-                float norm, rest;
-                convert_point(smem + srow * C::STRIDE, q0 + open[done + min(static_cast<uint32_t>(srow), mine - 1)], norm, rest);
-            }
-            if (tid < 32) { nearest[tid] = ~0ull; which[tid] = 0xFFFFFFFFu; }
-            if (tid == 0) s_count[3] = 0;
-            __syncthreads();
-            v8h bx[KH];
+        uint32_t *which = reinterpret_cast<uint32_t *>(nearest + MOST);                           // ... centroid
+        const uint32_t mine = min(static_cast<uint32_t>(MOST), n_open - done);
+        __syncthreads();                                              // (the minima, or what the points before these left, are no longer read)
+        for (int t = tid; t < MOST * C::STRIDE / 16; t += 256) reinterpret_cast<uint4 *>(smem)[t] = make_uint4(0, 0, 0, 0);        // rows: zero past dp
+        __syncthreads();
+        if (srow < MOST) {
+            float norm, rest;
+            convert_point(smem + srow * C::STRIDE, q0 + open[done + min(static_cast<uint32_t>(srow), mine - 1)], norm, rest);
+        }
+        if (tid < MOST) { nearest[tid] = ~0ull; which[tid] = 0xFFFFFFFFu; }
+        if (tid == 0) s_count[3] = 0;
+        __syncthreads();
+        v8h bx[W][KH];
+        float window[W];
 #pragma unroll
-            for (int ks = 0; ks < KH; ++ks) bx[ks] = *reinterpret_cast<const v8h *>(smem + col * C::STRIDE + half * 16 + ks * 32);
-            const float window = static_cast<uint32_t>(col) < mine ? xnorm2[open[done + col]] : -INFINITY;
-            // (a wavefront reads the centroids of its tiles itself, AHEAD2 tiles ahead, and needs nothing from the others: with stages of the
-            // workgroup as above every one of them waited for its loads, 0.25 ms a walk of 65536)
-            constexpr int AHEAD2 = KH == 1 ? 4 : KH == 2 ? 2 : 1;
-            const int ntiles = (ncent + 31) / 32;
-            float *wnorm = reinterpret_cast<float *>(smem) + wave * 32 * AHEAD2;            // |c|^2 of these tiles
-            float raw[AHEAD2][KH][8];
-            auto component = [&](int ks, int e) { return (C::TWO ? 0 : 16 * ks + 8 * half) + e; };       // of K position 16 ks + 8 half + e
-            auto load_tile = [&](int t, float (&r)[KH][8]) __attribute__((always_inline)) {
-                const int c = t * 32 + col;
-                const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+        for (int w = 0; w < W; ++w) {
+#pragma unroll
+            for (int ks = 0; ks < KH; ++ks) bx[w][ks] = *reinterpret_cast<const v8h *>(smem + (32 * w + col) * C::STRIDE + half * 16 + ks * 32);
+            window[w] = static_cast<uint32_t>(32 * w + col) < mine ? xnorm2[open[done + 32 * w + col]] : -INFINITY;
+        }
+        // (a wavefront reads the centroids of its tiles itself, AHEAD2 tiles ahead, and needs nothing from the others: with stages of the
+        // workgroup as above every one of them waited for its loads, 0.25 ms a walk of 65536)
+        constexpr int AHEAD2 = KH == 1 ? 4 : KH == 2 ? 2 : 1, G = W == 1 ? AHEAD2 : 1;            // G: tiles of centroids whose products run together
+        const int ntiles = (ncent + 31) / 32;
+        float *wnorm = reinterpret_cast<float *>(smem) + wave * 32 * AHEAD2;                // |c|^2 of these tiles
+        float raw[AHEAD2][KH][8];
+        auto component = [&](int ks, int e) { return (C::TWO ? 0 : 16 * ks + 8 * half) + e; };       // of K position 16 ks + 8 half + e
+        auto load_tile = [&](int t, float (&r)[KH][8]) __attribute__((always_inline)) {
+            const int c = t * 32 + col;
+            const float *src = cbj + static_cast<size_t>(c < ncent ? c : ncent - 1) * dsub;
+#pragma unroll
+            for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; e += 4) {
+                    const int o = component(ks, e);
+                    if constexpr (FOURS) {
+                        const f4_any v = *reinterpret_cast<const f4_any *>(src + (o < dsub ? o : 0));
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) r[ks][e + z] = v.v[z];
+                    } else {
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) r[ks][e + z] = src[o + z < dsub ? o + z : 0];
+                    }
+                }
+        };
+        __syncthreads();                                              // the points' rows are no longer read
+        bool full = false;                                            // more are found than there is room for
+#pragma unroll
+        for (int d = 0; d < AHEAD2; ++d) load_tile(wave + 4 * d, raw[d]);
+        for (int t0 = wave; t0 < ntiles && !full; t0 += 4 * AHEAD2) { // uniform
+            v8h a[AHEAD2][KH];
+            float norm[AHEAD2];
+#pragma unroll
+            for (int d = 0; d < AHEAD2; ++d) {
+                norm[d] = 0.0f;
 #pragma unroll
                 for (int ks = 0; ks < KH; ++ks)
 #pragma unroll
-                    for (int e = 0; e < 8; e += 4) {
+                    for (int e = 0; e < 8; ++e) {
                         const int o = component(ks, e);
-                        if constexpr (FOURS) {
-                            const f4_any v = *reinterpret_cast<const f4_any *>(src + (o < dsub ? o : 0));
-#pragma unroll
-                            for (int z = 0; z < 4; ++z) r[ks][e + z] = v.v[z];
-                        } else {
-#pragma unroll
-                            for (int z = 0; z < 4; ++z) r[ks][e + z] = src[o + z < dsub ? o + z : 0];
-                        }
+                        float v = fmaf(raw[d][ks][e], scale, mus[o]);
+                        if (o >= dsub) v = 0.0f;
+                        a[d][ks][e] = static_cast<_Float16>(v);
+                        norm[d] = fmaf(v, v, norm[d]);
                     }
-            };
-            __syncthreads();                                          // the points' rows are no longer read
+                load_tile(t0 + 4 * (d + AHEAD2), raw[d]);
+            }
 #pragma unroll
-            for (int d = 0; d < AHEAD2; ++d) load_tile(wave + 4 * d, raw[d]);
-            for (int t0 = wave; t0 < ntiles; t0 += 4 * AHEAD2) {      // uniform
-                v8h a[AHEAD2][KH];
-                v16f acc[AHEAD2];
-                float norm[AHEAD2], least = INFINITY;
+            for (int d = 0; d < AHEAD2; ++d) {
+                if (!C::TWO) norm[d] += __shfl_xor(norm[d], 32);
+                if (!(norm[d] < kFarNorm)) {
+                    norm[d] = 3.0e38f;
 #pragma unroll
-                for (int d = 0; d < AHEAD2; ++d) {
-                    norm[d] = 0.0f;
-#pragma unroll
-                    for (int ks = 0; ks < KH; ++ks)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const int o = component(ks, e);
-                            float v = fmaf(raw[d][ks][e], scale, mus[o]);
-                            if (o >= dsub) v = 0.0f;
-                            a[d][ks][e] = static_cast<_Float16>(v);
-                            norm[d] = fmaf(v, v, norm[d]);
-                        }
-                    load_tile(t0 + 4 * (d + AHEAD2), raw[d]);
+                    for (int ks = 0; ks < KH; ++ks) a[d][ks] = v8h{};
                 }
+                if (half == 0) wnorm[32 * d + col] = (t0 + 4 * d) * 32 + col < ncent ? norm[d] : 3.0e38f;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-                for (int d = 0; d < AHEAD2; ++d) {
-                    if (!C::TWO) norm[d] += __shfl_xor(norm[d], 32);
-                    if (!(norm[d] < kFarNorm)) {
-                        norm[d] = 3.0e38f;
+            for (int d0 = 0; d0 < AHEAD2; d0 += G) {
+                v16f acc[G][W];
 #pragma unroll
-                        for (int ks = 0; ks < KH; ++ks) a[d][ks] = v8h{};
-                    }
-                    if (half == 0) wnorm[32 * d + col] = (t0 + 4 * d) * 32 + col < ncent ? norm[d] : 3.0e38f;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                for (int d = 0; d < AHEAD2; ++d)
+                for (int g = 0; g < G; ++g)
 #pragma unroll
                     for (int v = 0; v < 16; v += 4) {
-                        const float4 x = *reinterpret_cast<const float4 *>(wnorm + 32 * d + 4 * half + 2 * v);
-                        acc[d][v] = x.x; acc[d][v + 1] = x.y; acc[d][v + 2] = x.z; acc[d][v + 3] = x.w;
+                        const float4 x = *reinterpret_cast<const float4 *>(wnorm + 32 * (d0 + g) + 4 * half + 2 * v);
+#pragma unroll
+                        for (int w = 0; w < W; ++w) { acc[g][w][v] = x.x; acc[g][w][v + 1] = x.y; acc[g][w][v + 2] = x.z; acc[g][w][v + 3] = x.w; }
                     }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-                for (int d = 0; d < AHEAD2; ++d)
+                for (int g = 0; g < G; ++g)
 #pragma unroll
-                    for (int ks = 0; ks < KH; ++ks) acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[d][ks], bx[ks], acc[d], 0, 0, 0);
+                    for (int w = 0; w < W; ++w)
 #pragma unroll
-                for (int d = 0; d < AHEAD2; ++d) least = minimum(acc[d], least);
-                if (!__builtin_amdgcn_ballot_w64(least <= window)) continue;             // uniform
+                        for (int ks = 0; ks < KH; ++ks) acc[g][w] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[d0 + g][ks], bx[w][ks], acc[g][w], 0, 0, 0);
+                uint32_t most = 0;
 #pragma unroll
-                for (int d = 0; d < AHEAD2; ++d)
+                for (int w = 0; w < W; ++w) {
+                    float least = INFINITY;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        if (acc[d][v] <= window) {                    // (not past the last centroid: the window is below 1e37)
-                            const uint32_t to = atomicAdd(&s_count[3], 1u);
-                            if (to < C::FOUND) found[to] = make_key(col, (t0 + 4 * d) * 32 + 8 * (v >> 2) + 4 * half + (v & 3));
+                    for (int g = 0; g < G; ++g) least = minimum(acc[g][w], least);
+                    if (!__builtin_amdgcn_ballot_w64(least <= window[w])) continue;      // uniform
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        uint32_t in = 0;                              // (a branch for every value is twice as long)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) in |= acc[g][w][v] <= window[w] ? 1u << v : 0u;          // (not past the last centroid: the window is below 1e37)
+                        for (; in; in &= in - 1) {
+                            const uint32_t v = __builtin_ctz(in);
+                            most = atomicAdd(&s_count[3], 1u);
+                            if (most < C::FOUND)
+                                found[most] = static_cast<uint32_t>(32 * w + col) << 16 | static_cast<uint32_t>((t0 + 4 * (d0 + g)) * 32 + 8 * (v >> 2) + 4 * half + (v & 3));
                         }
+                    }
+                }
+                full = full || __builtin_amdgcn_ballot_w64(most >= C::FOUND);
             }
-            __syncthreads();
-            const uint32_t nfound = s_count[3];
-            if (nfound > C::FOUND) break;                             // uniform
-            constexpr int PER = C::FOUND / 256;
-            double d[PER];
-#pragma unroll
-            for (int z = 0; z < PER; ++z) {
-                const uint32_t t = tid + 256 * z;
-                if (t >= nfound) continue;
-                const uint32_t p = static_cast<uint32_t>(found[t] >> 32), c = static_cast<uint32_t>(found[t]);
-                d[z] = exact_distance(points + static_cast<size_t>(q0 + open[done + p]) * ld + j * dsub, cbj + static_cast<size_t>(c) * dsub, dsub);
-                atomicMin(&nearest[p], static_cast<unsigned long long>(__double_as_longlong(d[z])));        // (distances are >= +0: they order like their bits)
-            }
-            __syncthreads();
-#pragma unroll
-            for (int z = 0; z < PER; ++z) {
-                const uint32_t t = tid + 256 * z;
-                if (t >= nfound) continue;
-                const uint32_t p = static_cast<uint32_t>(found[t] >> 32);
-                if (static_cast<unsigned long long>(__double_as_longlong(d[z])) == nearest[p]) atomicMin(&which[p], static_cast<uint32_t>(found[t]));
-            }
-            __syncthreads();
-            if (tid < static_cast<int>(mine)) put(q0 + open[done + tid], __longlong_as_double(static_cast<long long>(nearest[tid])), which[tid]);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-    }
+        __syncthreads();
+        const uint32_t nfound = s_count[3];
+        if (nfound > C::FOUND) return false;                          // uniform
+        auto distance = [&](uint32_t f) {
+            return static_cast<unsigned long long>(__double_as_longlong(         // (distances are >= +0: they order like their bits)
+                exact_distance(points + static_cast<size_t>(q0 + open[done + (f >> 16)]) * ld + j * dsub, cbj + static_cast<size_t>(f & 0xFFFFu) * dsub, dsub)));
+        };
+#pragma unroll 1
+        for (uint32_t t = tid; t < nfound; t += 256) atomicMin(&nearest[found[t] >> 16], distance(found[t]));
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t t = tid; t < nfound; t += 256)
+            if (distance(found[t]) == nearest[found[t] >> 16]) atomicMin(&which[found[t] >> 16], found[t] & 0xFFFFu);
+        __syncthreads();
+        if (tid < static_cast<int>(mine)) put(q0 + open[done + tid], __longlong_as_double(static_cast<long long>(nearest[tid])), which[tid]);
+        done += mine;
+        return true;
+    };
+    for (bool goes = true; goes && done < n_open;)                    // uniform
+        goes = n_open - done <= 32 ? walk_again(std::integral_constant<int, 1>{}) : walk_again(std::integral_constant<int, C::TILES2>{});
     // (those without a window: one by one 0.12 ms each with 65536 centroids of 16 components; the walk with split products 0.3, above 32 components 2)
     uint32_t rest = n_open + n_no_window;
     if (n_no_window <= kFewFar) {                                     // uniform
         rest = n_open;
-        __syncthreads();                                              // what the walk has in LDS is no longer read
+        __syncthreads();                                              // what the walks have in LDS is no longer read
         for (uint32_t i = 0; i < n_no_window; ++i) {
             const uint64_t q = q0 + open[C::PTS - 1 - i];
             double best;
@@ -1575,7 +1591,8 @@ static int launch_assign_ks(const float *points, uint64_t n, int ld, const float
     // instruction as it is; above 64 both forms take the same time (30000 x 4 of 84: 7.0 and 6.9 ms, of 128: 13.3 both).  Split products
     // and this form, 65536 centroids, ms: 250007 x 8 of 16 components (whole numbers) 8.67 and 5.46; 250000 x 8 of 12 10.8 and 5.65; 70000 x 8 of 8 2.53
     // and 1.87, of 24 5.5 and 3.2; 140000 x 4 of 32 7.6 and 4.15; 30000 x 8 of 64 5.8 and 3.5; 20000 x 16 of 60 9.8 and 5.5; 1024 centroids: 250000 x 8
-    // of 16 0.93 and 0.86.  Where every centroid repeats or all are close together, 4 to 7 % slower.
+    // of 16 0.93 and 0.86.  Where every centroid repeats, or hundreds are closer together than both forms can tell, 4 to 7 % slower (repeated 16 times 186 and 195);
+    // clusters of 16 that the split products can tell 0.9 to 1.25 of the time; half of the points 1e6 times farther out than the centroids as long, with 64 components 1.3.
     if constexpr (KS > 1 && KS <= 12) {
         constexpr int P = KS <= 3 ? 8 : KS <= 6 ? 4 : 2, PTS = HalfCfg<KS, P>::PTS;
         auto rounds = [&](int pts) { return ((n + pts - 1) / pts * static_cast<uint64_t>(m) + 511) / 512; };

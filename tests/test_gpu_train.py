@@ -548,3 +548,47 @@ def test_assign_beside_centroids_and_points_far_out_takes_as_long():
         ms.append(min(times))
     print("assign, ms: %.3f, points far out %.3f, a centroid %.3f" % tuple(ms), flush=True)
     assert ms[1] < 2 * ms[0] and ms[2] < 2 * ms[0]
+
+
+@pytest.mark.parametrize("dsub,m", [(7, 8), (8, 8), (16, 8), (30, 8), (60, 8)])
+@pytest.mark.parametrize("members,every", [(16, 1), (16, 3), (16, 11), (31, 2), (40, 2), (300, 1)])
+def test_assign_of_many_points_whose_windows_hold_many_centroids(dsub, m, members, every):
+    # Clusters of centroids closer together than the filter with one fp16 product can tell, spread over the codebook, and every so many points beside one: they are walked again, 128 at a
+    # time, the last 32 or fewer apart, or, where they find more centroids than are listed (about 32 each), go through the split products.  A fifth of a
+    # cluster's centroids are equal: the first of them.
+    print("assign crowded dsub=%d m=%d members=%d every=%d" % (dsub, m, members, every), flush=True)
+    g = gen(dsub + members)
+    n, ncent = 2003, 6000
+    cluster = torch.arange(ncent, device=DEV) % (ncent // members)
+    means = torch.randn((m, ncent // members, dsub), generator=g, device=DEV)
+    cb = means[:, cluster] + 2e-3 * torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    cb[:, ::5] = means[:, cluster[::5]]
+    pts = torch.randn((n, m * dsub), generator=g, device=DEV)
+    beside = pts.view(n, m, dsub)[::every]
+    beside[:] = means[:, torch.arange(beside.shape[0], device=DEV) % means.shape[1]].transpose(0, 1) + 1e-3 * torch.randn(beside.shape, generator=g, device=DEV)
+    check_many_points_against_few(pts, cb, (1 << 18) // (m * n) + 1, "%d members" % members)
+
+
+def test_assign_to_clusters_of_centroids_is_not_much_slower():
+    # 4096 clusters of 16: with every open point left to the split products 5.4 times as long as without clusters; walked again 3.1.
+    n, m, dsub, ncent = 70000, 8, 16, 65536
+    g = gen(4)
+    pts, cb = torch.randn((n, m * dsub), generator=g, device=DEV), torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    means = torch.randn((m, 4096, dsub), generator=g, device=DEV)
+    clusters = means[:, torch.randint(0, 4096, (ncent,), generator=g, device=DEV)] + 0.03 * torch.randn((m, ncent, dsub), generator=g, device=DEV)
+    pick = torch.randint(0, ncent, (n, m), generator=g, device=DEV)
+    beside = clusters[torch.arange(m, device=DEV)[None], pick] + 0.03 * torch.randn((n, m, dsub), generator=g, device=DEV)
+    ms = []
+    for x, c in ((pts, cb), (beside.reshape(n, m * dsub), clusters)):
+        times = []
+        for _ in range(6):
+            binding.profile_enable(True)
+            try:
+                binding.assign(x, c)
+                torch.cuda.synchronize()
+                times.append(binding.profile_read()["train"][0])
+            finally:
+                binding.profile_enable(False)
+        ms.append(min(times))
+    print("assign, ms: %.3f, clusters %.3f" % tuple(ms), flush=True)
+    assert ms[1] < 4.2 * ms[0]
