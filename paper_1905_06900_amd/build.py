@@ -31,6 +31,8 @@ HIP_FLAGS = [
 EXTRA_FLAGS = {
     "tables_full.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "assign.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "assign_middle.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "assign_long.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     # a few lanes of a wavefront count their hits with an LDS atomic each; the compiler's scan over all 64
     # lanes in its place costs several times the instructions
     "scan_cells.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],

@@ -1389,6 +1389,98 @@ __global__ __launch_bounds__(256, 2) void assign_half_kernel(const float *__rest
     }
 }
 
+template <int KS, int P, bool SPLIT, bool FOURS>
+static int launch_assign_f(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                           void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    using C = AssignCfg<KS, P, SPLIT>;
+    const auto kernel = &assign_kernel<KS, P, SPLIT, FOURS>;
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
+    if (arc) return arc;
+    DCPQ_LAUNCH(kStageTrain, st, (assign_kernel<KS, P, SPLIT, FOURS>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
+                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
+    DCPQ_CHECK_LAUNCH("assign_kernel");
+    return DCPQ_OK;
+}
+
+template <int KS, int P, bool SPLIT>
+static int launch_assign_t(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                           void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    if (dp == dsub) return launch_assign_f<KS, P, SPLIT, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    return launch_assign_f<KS, P, SPLIT, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+}
+
+template <int KS, int P, bool FOURS>
+static int launch_half_f(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                         void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    using C = HalfCfg<KS, P>;
+    const auto kernel = &assign_half_kernel<KS, P, FOURS>;
+    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
+    if (arc) return arc;
+    DCPQ_LAUNCH(kStageTrain, st, (assign_half_kernel<KS, P, FOURS>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
+                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
+    DCPQ_CHECK_LAUNCH("assign_half_kernel");
+    return DCPQ_OK;
+}
+
+template <int KS, int P>
+static int launch_half(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                       void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    if (dp == dsub) return launch_half_f<KS, P, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    return launch_half_f<KS, P, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+}
+
+template <int KS>
+static int launch_assign_ks(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                            void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    // The largest tile of points that still gives two workgroups per CU (the centroids are converted once per
+    // workgroup and read from LDS once per wavefront, so large tiles are cheaper: 204 cycles per 32 x 32 distances with
+    // 512 points at d = 16, 290 with 256); below that the four wavefronts split the centroids (2000 points, 8 x 16
+    // components: 0.50 ms; 1.3 ms with 256-point tiles, which leave most CUs without work).
+    auto enough = [&](int pts) { return (n + pts - 1) / pts * static_cast<uint64_t>(m) >= 512; };
+    // One fp16 product in the filter, where two workgroups per CU can have 512 points or more (256 with sub-vectors above 32 components), of 1024
+    // where these leave no more of the last round idle.  Rows of up to four components have all four bf16 products in one matrix
+    // instruction as it is; above 64 both forms take the same time (30000 x 4 of 84: 7.0 and 6.9 ms, of 128: 13.3 both).  Split products
+    // and this form, 65536 centroids, ms: 250007 x 8 of 16 components (whole numbers) 8.67 and 5.46; 250000 x 8 of 12 10.8 and 5.65; 70000 x 8 of 8 2.53
+    // and 1.87, of 24 5.5 and 3.2; 140000 x 4 of 32 7.6 and 4.15; 30000 x 8 of 64 5.8 and 3.5; 20000 x 16 of 60 9.8 and 5.5; 1024 centroids: 250000 x 8
+    // of 16 0.93 and 0.86.  Where every centroid repeats, or hundreds are closer together than both forms can tell, 4 to 7 % slower (repeated 16 times 186 and 195);
+    // clusters of 16 that the split products can tell 0.9 to 1.25 of the time; half of the points 1e6 times farther out than the centroids as long, with 64 components 1.3.
+    if constexpr (KS > 1 && KS <= 12) {
+        constexpr int P = KS <= 3 ? 8 : KS <= 6 ? 4 : 2, PTS = HalfCfg<KS, P>::PTS;
+        auto rounds = [&](int pts) { return ((n + pts - 1) / pts * static_cast<uint64_t>(m) + 511) / 512; };
+        if (ncent <= static_cast<int>(kCells * 32 * HalfCfg<KS, P>::TPC)) {
+            if constexpr (P == 8) {
+                if (enough(PTS / 2) && (!enough(PTS) || rounds(PTS / 2) * 11 < rounds(PTS) * 20)) return launch_half<KS, P / 2>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+            }
+            if (enough(PTS)) return launch_half<KS, P>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+        }
+    }
+    if constexpr (KS <= 6) {
+        if (enough(AssignCfg<KS, 4, false>::PTS)) return launch_assign_t<KS, 4, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    }
+    if (enough(AssignCfg<KS, KS <= 12 ? 2 : 1, false>::PTS) || KS > 6)
+        return launch_assign_t<KS, KS <= 12 ? 2 : 1, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    if constexpr (KS <= 6) return launch_assign_t<KS, 1, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    return DCPQ_OK;
+}
+
+// The kernels of longer sub-vectors are compiled by themselves, by files that include this one as far as here: together they take the compiler six
+// minutes, apart a bit more than two.
+#ifndef DCPQ_ASSIGN_KERNELS_ONLY
+
+int launch_assign_short(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
+                        void *labels, int label_bytes, float *dist, hipStream_t st)
+{
+    const int ks = (3 * dp + 15) / 16;
+    if (ks <= 1) return launch_assign_ks<1>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    if (ks <= 2) return launch_assign_ks<2>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    return launch_assign_ks<3>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+}
+
 // The same result with all inner products on the double-precision matrix pipe (f64_is_faster: where).  A workgroup takes kF64Points points and walks the centroids in steps of
 // kF64Cents; |c|^2 - 2 <x, c> and the distance by difference are each within (dsub + 8) 2^-53 of the magnitudes they are
 // made of, so a smallest value that no other comes near is the nearest centroid in either form.  Where another does (equal
@@ -1533,85 +1625,6 @@ __global__ __launch_bounds__(256, 2) void assign_f64_kernel(const float *__restr
     }
 }
 
-template <int KS, int P, bool SPLIT, bool FOURS>
-static int launch_assign_f(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
-                           void *labels, int label_bytes, float *dist, hipStream_t st)
-{
-    using C = AssignCfg<KS, P, SPLIT>;
-    const auto kernel = &assign_kernel<KS, P, SPLIT, FOURS>;
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
-    if (arc) return arc;
-    DCPQ_LAUNCH(kStageTrain, st, (assign_kernel<KS, P, SPLIT, FOURS>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
-                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
-    DCPQ_CHECK_LAUNCH("assign_kernel");
-    return DCPQ_OK;
-}
-
-template <int KS, int P, bool SPLIT>
-static int launch_assign_t(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
-                           void *labels, int label_bytes, float *dist, hipStream_t st)
-{
-    if (dp == dsub) return launch_assign_f<KS, P, SPLIT, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    return launch_assign_f<KS, P, SPLIT, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-}
-
-template <int KS, int P, bool FOURS>
-static int launch_half_f(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
-                         void *labels, int label_bytes, float *dist, hipStream_t st)
-{
-    using C = HalfCfg<KS, P>;
-    const auto kernel = &assign_half_kernel<KS, P, FOURS>;
-    const int arc = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), C::LDS_BYTES);
-    if (arc) return arc;
-    DCPQ_LAUNCH(kStageTrain, st, (assign_half_kernel<KS, P, FOURS>), dim3(static_cast<unsigned>((n + C::PTS - 1) / C::PTS), m), dim3(256),
-                C::LDS_BYTES, points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist);
-    DCPQ_CHECK_LAUNCH("assign_half_kernel");
-    return DCPQ_OK;
-}
-
-template <int KS, int P>
-static int launch_half(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
-                       void *labels, int label_bytes, float *dist, hipStream_t st)
-{
-    if (dp == dsub) return launch_half_f<KS, P, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    return launch_half_f<KS, P, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-}
-
-template <int KS>
-static int launch_assign_ks(const float *points, uint64_t n, int ld, const float *cb, int m, int dsub, int dp, int ncent,
-                            void *labels, int label_bytes, float *dist, hipStream_t st)
-{
-    // The largest tile of points that still gives two workgroups per CU (the centroids are converted once per
-    // workgroup and read from LDS once per wavefront, so large tiles are cheaper: 204 cycles per 32 x 32 distances with
-    // 512 points at d = 16, 290 with 256); below that the four wavefronts split the centroids (2000 points, 8 x 16
-    // components: 0.50 ms; 1.3 ms with 256-point tiles, which leave most CUs without work).
-    auto enough = [&](int pts) { return (n + pts - 1) / pts * static_cast<uint64_t>(m) >= 512; };
-    // One fp16 product in the filter, where two workgroups per CU can have 512 points or more (256 with sub-vectors above 32 components), of 1024
-    // where these leave no more of the last round idle.  Rows of up to four components have all four bf16 products in one matrix
-    // instruction as it is; above 64 both forms take the same time (30000 x 4 of 84: 7.0 and 6.9 ms, of 128: 13.3 both).  Split products
-    // and this form, 65536 centroids, ms: 250007 x 8 of 16 components (whole numbers) 8.67 and 5.46; 250000 x 8 of 12 10.8 and 5.65; 70000 x 8 of 8 2.53
-    // and 1.87, of 24 5.5 and 3.2; 140000 x 4 of 32 7.6 and 4.15; 30000 x 8 of 64 5.8 and 3.5; 20000 x 16 of 60 9.8 and 5.5; 1024 centroids: 250000 x 8
-    // of 16 0.93 and 0.86.  Where every centroid repeats, or hundreds are closer together than both forms can tell, 4 to 7 % slower (repeated 16 times 186 and 195);
-    // clusters of 16 that the split products can tell 0.9 to 1.25 of the time; half of the points 1e6 times farther out than the centroids as long, with 64 components 1.3.
-    if constexpr (KS > 1 && KS <= 12) {
-        constexpr int P = KS <= 3 ? 8 : KS <= 6 ? 4 : 2, PTS = HalfCfg<KS, P>::PTS;
-        auto rounds = [&](int pts) { return ((n + pts - 1) / pts * static_cast<uint64_t>(m) + 511) / 512; };
-        if (ncent <= static_cast<int>(kCells * 32 * HalfCfg<KS, P>::TPC)) {
-            if constexpr (P == 8) {
-                if (enough(PTS / 2) && (!enough(PTS) || rounds(PTS / 2) * 11 < rounds(PTS) * 20)) return launch_half<KS, P / 2>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-            }
-            if (enough(PTS)) return launch_half<KS, P>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-        }
-    }
-    if constexpr (KS <= 6) {
-        if (enough(AssignCfg<KS, 4, false>::PTS)) return launch_assign_t<KS, 4, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    }
-    if (enough(AssignCfg<KS, KS <= 12 ? 2 : 1, false>::PTS) || KS > 6)
-        return launch_assign_t<KS, KS <= 12 ? 2 : 1, false>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    if constexpr (KS <= 6) return launch_assign_t<KS, 1, true>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    return DCPQ_OK;
-}
-
 // Which kernel.  The filter saves products, and what follows it costs each point the reading of a few rows one by one, 256
 // to 512 points to a workgroup; the double-precision products cost more per distance but nothing after them, and take
 // points in tens.  So they are the faster where centroids are few, or points so few that the filter's tiles leave the chip
@@ -1643,12 +1656,12 @@ int launch_assign(const float *points, uint64_t n, int ld, const float *cb, int 
         return DCPQ_OK;
     }
     const int dp = (dsub + 3) & ~3, ks = (3 * dp + 15) / 16;
-#define DCPQ_ASSIGN_KS(K) \
-    if (ks <= K) return launch_assign_ks<K>(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
-    DCPQ_ASSIGN_KS(1) DCPQ_ASSIGN_KS(2) DCPQ_ASSIGN_KS(3) DCPQ_ASSIGN_KS(4) DCPQ_ASSIGN_KS(5) DCPQ_ASSIGN_KS(6)
-    DCPQ_ASSIGN_KS(8) DCPQ_ASSIGN_KS(10) DCPQ_ASSIGN_KS(12) DCPQ_ASSIGN_KS(16) DCPQ_ASSIGN_KS(20) DCPQ_ASSIGN_KS(24)
-#undef DCPQ_ASSIGN_KS
+    if (ks <= 3) return launch_assign_short(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    if (ks <= 6) return launch_assign_middle(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
+    if (ks <= 24) return launch_assign_long(points, n, ld, cb, m, dsub, dp, ncent, labels, label_bytes, dist, st);
     return fail(DCPQ_EUNSUPPORTED, "assign: dsub=%d not supported", dsub);
 }
+
+#endif
 
 }  // namespace dcpq
